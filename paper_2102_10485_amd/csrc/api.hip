@@ -32,7 +32,7 @@ inline long long round_up(long long x, long long m) { return (x + m - 1) / m * m
 // Row splits of the image-side weight gradients (one or a few output tiles per model): 8 when there are many
 // models, more when the models alone would leave most of the chip idle.  A function of the model count only.
 static int img_ksplit_for(int L) { return std::min(std::max(800 / L, 8), 128); }
-constexpr int WG_MAX_KSPLIT = 16;
+constexpr int WG_MAX_KSPLIT = 64;
 
 // A (transposed) convolution between a "big" tensor (Cb channels, side 2*Hs) and a "small" one (Cs, side Hs).
 // Internal weight layout [tap][Cb (or CBT)][Cs].
@@ -582,12 +582,25 @@ void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, c
   launch_conv<T>(mode, epi, a, c->st);
 }
 
-// Row splits of a weight-gradient launch whose output tiles alone would not fill the chip (few models): every
-// model's rows are shared by this many blocks per tile, whose partial results are added in a fixed order.  A function
-// of the configuration only -- the number of models and the layer's shape -- never of the batch.
-int wgrad_ksplit(const gan_ctx* c, int Cb, int Cs, int ntaps) {
-  const long long blocks = (long long)c->L * wgrad_tiles_per_model(ntaps, Cb, Cs);
-  return (int)std::min<long long>(std::max<long long>(512 / blocks, 1), WG_MAX_KSPLIT);
+// Row splits of a weight-gradient launch whose output tiles alone would leave part of the chip idle: every model's rows
+// are shared by this many blocks per tile, whose partial results are added in a fixed order.  The number with the
+// smallest estimated time: the products at the rate a full chip reaches, stretched by what the last round of blocks
+// leaves idle, plus writing and adding the partial results.  A function of the configuration only -- the number of
+// models, the sizing batch and the layer's shape -- never of a call's batch.
+int wgrad_ksplit(const gan_ctx* c, int Cb, int Cs, int ntaps, int Hs, int nseg) {
+  const double blocks = (double)c->L * wgrad_tiles_per_model((int)esize(c), ntaps, Cb, Cs);
+  const double rows = (double)c->NB * nseg * Hs * Hs, out = (double)c->L * ntaps * Cb * Cs * 4;
+  const double product = 2.0 * rows * ntaps * Cb * Cs / (c->bf16 ? 900e12 : 140e12);
+  const double chunk_rows = 128 / (double)esize(c);
+  int best = 1;
+  double best_t = 0;
+  for (int k = 1; k <= WG_MAX_KSPLIT; ++k) {
+    if (k > 1 && rows / nseg / c->L < 2 * chunk_rows * k) break;             // at least two chunks for every block
+    const double b = blocks * k, rounds = (double)(((long long)b + 255) / 256);
+    const double t = product * rounds * 256 / b + (k > 1 ? 5e-6 + (2 * k + 1) * out / 4e12 : 0);
+    if (k == 1 || t < best_t) { best = k; best_t = t; }
+  }
+  return best;
 }
 
 // ksplit == 0: split as wgrad_ksplit says, through c->wg_part, and leave the sum in dW; ksplit >= 1: the caller's
@@ -601,7 +614,7 @@ void wgrad_call(gan_ctx* c, const char* name, const void* Big, const void* Small
   a.L = c->L; a.nseg = nseg; a.seg_samples = n; a.Cb = Cb; a.Cs = Cs; a.Hs = Hs; a.ntaps = ntaps; a.ksplit = ksplit;
   a.split_stride = (long long)c->L * stride;
   const long long layer = (long long)ntaps * Cb * Cs;
-  const int auto_split = ksplit == 0 ? wgrad_ksplit(c, Cb, Cs, ntaps) : 0;
+  const int auto_split = ksplit == 0 ? wgrad_ksplit(c, Cb, Cs, ntaps, Hs, nseg) : 0;
   if (ksplit == 0) {
     a.ksplit = auto_split;
     if (auto_split > 1) {
@@ -616,7 +629,7 @@ void wgrad_call(gan_ctx* c, const char* name, const void* Big, const void* Small
   snprintf(detail, sizeof(detail), "[Cb%d Cs%d H%d seg%d]", Cb, Cs, Hs, nseg);
   (void)name;
   {
-    Scope s(c, wgrad_variant_name(a), flops_alg >= 0 ? flops_alg : 2.0 * rows * Cb * Cs * ntaps * frac, bytes, detail, st);
+    Scope s(c, wgrad_variant_name((int)sizeof(T), a), flops_alg >= 0 ? flops_alg : 2.0 * rows * Cb * Cs * ntaps * frac, bytes, detail, st);
     launch_wgrad<T>(a, st);
   }
   if (auto_split > 1) launch_sum_splits(c->wg_part, dW, stride, layer, c->L, auto_split, st);
@@ -1367,13 +1380,13 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
   {
     // partial blocks of the weight gradients that are split over rows (few models only)
     size_t need = 0;
-    auto want = [&](int Cb, int Cs, int ntaps) {
-      const int ks = wgrad_ksplit(c, Cb, Cs, ntaps);
+    auto want = [&](int Cb, int Cs, int ntaps, int Hs, int nseg) {      // as the training step calls wgrad_call
+      const int ks = wgrad_ksplit(c, Cb, Cs, ntaps, Hs, nseg);
       if (ks > 1) need = std::max(need, (size_t)ks * L * ntaps * Cb * Cs * 4);
     };
-    for (size_t j = 1; j < c->D.conv.size(); ++j) want(c->D.conv[j].Cb, c->D.conv[j].Cs, 16);
-    for (size_t i = 0; i + 1 < c->G.conv.size(); ++i) want(c->G.conv[i].Cb, c->G.conv[i].Cs, 16);
-    want(c->G.J, c->G.Kp, 1);
+    for (size_t j = 1; j < c->D.conv.size(); ++j) want(c->D.conv[j].Cb, c->D.conv[j].Cs, 16, c->D.conv[j].Hs, 2);
+    for (size_t i = 0; i + 1 < c->G.conv.size(); ++i) want(c->G.conv[i].Cb, c->G.conv[i].Cs, 16, c->G.conv[i].Hs, 1);
+    want(c->G.J, c->G.Kp, 1, 1, 1);
     c->wg_part = nullptr;
     if (need) ok = ok && dev_alloc(c, (void**)&c->wg_part, need);
     if (c->paper) {

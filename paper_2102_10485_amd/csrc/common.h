@@ -100,15 +100,16 @@ struct WgradArgs {
   int ksplit;            // >= 1: the rows of each segment are shared by this many blocks, each writing its own
   long long split_stride;//        partial block dW + split * split_stride (the caller adds them in order)
   int hs_shift;          // log2(Hs) or -1 (filled by the launcher)
+  unsigned rps_inv, hs_inv;   // sides that are no power of two: reciprocals of Hs*Hs and Hs (filled by the launcher; 0: divide)
 };
 
 template <typename T> void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st);
 template <typename T> void launch_wgrad(const WgradArgs& a, hipStream_t st);
 // names of the kernel instantiations the two launchers pick (per-kernel timing)
 const char* conv_variant_name(int mode, int epi, const ConvArgs& a);
-const char* wgrad_variant_name(const WgradArgs& a);
-// output tiles per model of the weight-gradient launch for this layer shape
-int wgrad_tiles_per_model(int ntaps, int Cb, int Cs);
+const char* wgrad_variant_name(int esize, const WgradArgs& a);
+// output tiles per model of the weight-gradient launch for this layer shape (esize: bytes per stored element)
+int wgrad_tiles_per_model(int esize, int ntaps, int Cb, int Cs);
 
 // rows per M-tile the forward-type kernel will use for n_out output channels and about rows_per_model rows
 int conv_tile_rows(int n_out, long long rows_per_model_hint, int n_models);

@@ -8,19 +8,18 @@
 //   up   : rows are the pixels of one output phase (Y%2, X%2) of the big tensor, 4 taps gathered from the small one
 //   dense: one tap, rows are read directly (linear layer, patch-matrix layers)
 // Weight-gradient kernel (wgrad_kernel): dW[tap][cb][cs] = sum_rows Big(row, tap)[cb] * Small(row)[cs]; the
-//   reduction index is the slow memory index of both operands, so tiles are transposed in registers on their
-//   way into LDS.
+//   reduction index is the slow memory index of both operands: tiles go into LDS as they lie in memory, and the operand
+//   reads do the transposition.
 //
-// Both stage 128-byte K-rows in LDS (two buffers) and feed v_mfma_f32_32x32x16_bf16 (bf16 storage) or
-// v_mfma_f32_32x32x2_f32 (fp32 storage) from 16-byte LDS reads; accumulation is fp32 in both cases.
+// Both stage K-chunks in LDS and feed v_mfma_f32_32x32x16_bf16 (bf16 storage) or v_mfma_f32_32x32x2_f32 (fp32
+// storage) from it; accumulation is fp32 in both cases.
 // Forward-type kernel: K-chunks of KB bytes per row travel global -> LDS directly (buffer_load_dwordx4 ... lds, no
 // registers in between) into a ring of NST buffers while the MFMAs of the current chunk run.  The 256 x 256 tile uses
 // KB = 128 with two buffers (one block per CU); the 256 x 128 and 128 x 128 tiles use KB = 64 with three, which leaves
 // room for two blocks per CU so that one block's epilogue and barriers hide behind the other's MFMAs; the 256 x 64
 // tile fits two blocks per CU with KB = 128 and two buffers.  The 16-byte chunk c of row
 // R sits at position c ^ ((R / (256/KB)) % (KB/16)), which keeps both the 1 KiB-per-wave copies and the MFMA operand
-// reads conflict-free.  Weight-gradient kernels: bf16 copies tiles in memory layout and transposes while reading LDS;
-// fp32 goes global -> registers (transposes) -> LDS, row stride 144 bytes.
+// reads conflict-free.
 // One barrier per chunk in both.
 #include <stdio.h>
 #include <stdlib.h>
@@ -32,9 +31,6 @@ namespace gan {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
-constexpr int BKB = 128;         // bytes of K per LDS row
-constexpr int LDS_STRIDE = BKB + 16;
 
 // Block tile BM x BN computed by WM x WN waves, each (TM*32) x (TN*32); forward kernel: KB bytes of K per LDS row,
 // NST buffers.
@@ -74,32 +70,6 @@ __device__ inline void mma16B(floatx16& acc, const uint4& a, const uint4& b, flo
   acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
   acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
   acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
-}
-
-// One K-chunk of the fp32 weight-gradient kernel held in LDS: every wave multiplies its (TM*32) x (TN*32) sub-tile.
-// Rows 144 bytes apart, chunk c of tile row R at position (c + R/16) mod 8 (that kernel writes its tiles transposed,
-// eight rows apart per lane; the rotation spreads those writes over the banks).
-template <typename T, int TM, int TN>
-__device__ inline void tile_mma(floatx16 (&acc)[TM][TN], const unsigned char* As, const unsigned char* Bs, int wm, int wn,
-                                int lane) {
-  const int r = lane & 31, h = lane >> 5;
-  const int rot = r >> 4;        // tile rows start at multiples of 32, so R/16 = const + r/16
-#pragma unroll
-  for (int vs = 0; vs < BKB / 32; ++vs) {
-    uint4 a[TM], b[TN];
-#pragma unroll
-    for (int t = 0; t < TM; ++t)
-      a[t] = *reinterpret_cast<const uint4*>(As + (wm * TM * 32 + t * 32 + r) * LDS_STRIDE +
-                                             ((vs * 2 + h + 2 * (wm * TM + t) + rot) & 7) * 16);
-#pragma unroll
-    for (int t = 0; t < TN; ++t)
-      b[t] = *reinterpret_cast<const uint4*>(Bs + (wn * TN * 32 + t * 32 + r) * LDS_STRIDE +
-                                             ((vs * 2 + h + 2 * (wn * TN + t) + rot) & 7) * 16);
-#pragma unroll
-    for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn) mma16B(acc[tm][tn], a[tm], b[tn], T());
-  }
 }
 
 // One K-chunk of the forward-type kernel: rows KB bytes apart, the 16-byte chunk c of tile row R at position
@@ -642,33 +612,12 @@ const char* conv_variant_name(int mode, int epi, const ConvArgs& a) {
   if (!n[0]) snprintf(n, 48, "gemm_%s%s<%s>", modes[mode], epis[epi], tiles[tile]);
   return n;
 }
-const char* wgrad_variant_name(const WgradArgs& a) {
-  if (a.ntaps * a.Cb <= 64) return "wgrad<64x128>";
-  return a.Cs % 256 == 0 ? "wgrad<256x256>" : "wgrad<256x128>";
-}
 template void launch_conv<float>(int, int, const ConvArgs&, hipStream_t);
 template void launch_conv<bf16_t>(int, int, const ConvArgs&, hipStream_t);
 
 // ---------------------------------------------------------------------------------------------------------
 // weight gradient
 // ---------------------------------------------------------------------------------------------------------
-
-// 8 x 8 transpose of 16-bit values held as 8 rows of uint4 (in place).
-__device__ inline void transpose8x8_b16(uint4 (&r)[8]) {
-  unsigned in[8][4];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) { in[i][0] = r[i].x; in[i][1] = r[i].y; in[i][2] = r[i].z; in[i][3] = r[i].w; }
-  unsigned out[8][4];
-#pragma unroll
-  for (int j = 0; j < 8; ++j)        // output row j = input column j
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {    // output dword q holds input rows 2q, 2q+1
-      const unsigned a = in[2 * q][j >> 1], b = in[2 * q + 1][j >> 1];
-      out[j][q] = (j & 1) ? ((a >> 16) | (b & 0xffff0000u)) : ((a & 0xffffu) | (b << 16));
-    }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) r[i] = make_uint4(out[i][0], out[i][1], out[i][2], out[i][3]);
-}
 
 // Which model the i-th group of blocks works on.  Groups are dealt round-robin to the 8 XCDs in rows of eight; with
 // the models sorted by decreasing size the rows alternate direction, so that every XCD gets the same share of the
@@ -680,172 +629,21 @@ __device__ inline int wgrad_model(const WgradArgs& p, int i) {
   return p.order[i];
 }
 
-// A loader task = 8 rows of the reduction index x one 16-byte channel group of one operand.
-//   bf16: 8 consecutive rows x 8 channels, transposed in registers, written as 8 x 16 bytes
-//   fp32: 8 rows strided by 4 x 4 channels, written as 32 scalars
-template <typename T, typename TL>
-__global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
-  constexpr int BM = TL::BM, BN = TL::BN, TM = TL::TM, TN = TL::TN;
-  __shared__ __attribute__((aligned(16))) unsigned char As[2][BM * LDS_STRIDE];
-  __shared__ __attribute__((aligned(16))) unsigned char Bs[2][BN * LDS_STRIDE];
-  constexpr int BKR = BKB / (int)sizeof(T);     // rows (reduction index) per chunk: 64 (bf16) or 32 (fp32)
-  constexpr bool IS16 = sizeof(T) == 2;
-  constexpr int EPV = 16 / (int)sizeof(T);
-  constexpr int NTASK = (BM + BN + TL::NT - 1) / TL::NT;   // loader tasks per thread
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / TL::WN, wn = wave % TL::WN;
-
-  // ---- tile: all tiles of one (model, row split) run on one XCD -- they read the same rows -- and the
-  // (model, split) pairs are dealt round-robin to the XCDs
-  const int Cb = p.Cb, Cs = p.Cs, Hs = p.Hs;
-  const int Mtot = p.ntaps * Cb;
-  const int MT = (Mtot + BM - 1) / BM, NT = (Cs + BN - 1) / BN;
-  const int bid = blockIdx.x;
-  const int unit = (bid / (8 * MT * NT)) * 8 + (bid & 7);
-  if (unit >= p.L * p.ksplit) return;
-  const int l = wgrad_model(p, unit / p.ksplit), split = unit % p.ksplit;
-  const int tile = (bid >> 3) % (MT * NT);
-  const int mt = tile / NT, nt = tile - mt * NT;
-  const int s0 = p.offs[l], s1 = p.offs[l + 1];
-  const int rps = Hs * Hs;
-  const int R = (s1 - s0) * rps;
-  const int Hb = 2 * Hs;
-  const T* __restrict__ Big = static_cast<const T*>(p.Big);
-  const T* __restrict__ Small = static_cast<const T*>(p.Small);
-  // this block's share of each segment's rows
-  const int rows_split = ((R + p.ksplit - 1) / p.ksplit + BKR - 1) / BKR * BKR;
-  const int r_lo = split * rows_split, r_hi = min(R, r_lo + rows_split);
-
-  // ---- loader tasks
-  int t_ch[NTASK], t_ky[NTASK], t_kx[NTASK], t_cg[NTASK], t_rg[NTASK];
-  bool t_isA[NTASK], t_ok[NTASK];
-#pragma unroll
-  for (int k = 0; k < NTASK; ++k) {
-    const int t = tid + k * TL::NT;
-    t_isA[k] = t < BM;
-    const int u = t_isA[k] ? t : t - BM;                  // task index inside its operand
-    const int groups = (t_isA[k] ? BM : BN) / EPV;        // channel groups
-    t_cg[k] = u % groups;
-    t_rg[k] = u / groups;
-    t_ky[k] = 1; t_kx[k] = 1;
-    if (t_isA[k]) {
-      const int m = mt * BM + t_cg[k] * EPV;
-      t_ok[k] = m < Mtot;
-      const int tap = m / Cb;
-      t_ch[k] = m - tap * Cb;
-      if (p.ntaps != 1) { t_ky[k] = tap >> 2; t_kx[k] = tap & 3; }
-    } else {
-      t_ch[k] = nt * BN + t_cg[k] * EPV;
-      t_ok[k] = t < BM + BN && t_ch[k] < Cs;
-    }
-  }
-
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  uint4 reg[NTASK][8];
-  auto load_chunk = [&](long long sample_base, int k0) {
-#pragma unroll
-    for (int k = 0; k < NTASK; ++k)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int r = k0 + (IS16 ? t_rg[k] * 8 + j : t_rg[k] + 4 * j);
-        uint4 val = make_uint4(0, 0, 0, 0);
-        if (r < r_hi && t_ok[k]) {
-          if (!t_isA[k]) {
-            val = *reinterpret_cast<const uint4*>(Small + (sample_base * rps + r) * (long long)Cs + t_ch[k]);
-          } else if (p.ntaps == 1) {             // rows of the big tensor are read directly
-            val = *reinterpret_cast<const uint4*>(Big + (sample_base * rps + r) * (long long)Cb + t_ch[k]);
-          } else {
-            int n, y, x;
-            decode_row(r, Hs, rps, p.hs_shift, n, y, x);
-            const int iy = 2 * y - 1 + t_ky[k], ix = 2 * x - 1 + t_kx[k];
-            if ((unsigned)iy < (unsigned)Hb && (unsigned)ix < (unsigned)Hb)
-              val = *reinterpret_cast<const uint4*>(Big + (((sample_base + n) * Hb + iy) * Hb + ix) * (long long)Cb + t_ch[k]);
-          }
-        }
-        reg[k][j] = val;
-      }
-  };
-  auto store_chunk = [&](int buf) {
-#pragma unroll
-    for (int k = 0; k < NTASK; ++k) {
-      if (tid + k * TL::NT >= BM + BN) continue;
-      unsigned char* dst = t_isA[k] ? As[buf] : Bs[buf];
-      if (IS16) {
-        transpose8x8_b16(reg[k]);
-#pragma unroll
-        for (int j = 0; j < 8; ++j)   // row t_cg*8 + j, chunk t_rg rotated by row/16 = t_cg/2
-          *reinterpret_cast<uint4*>(dst + (t_cg[k] * 8 + j) * LDS_STRIDE + ((t_rg[k] + (t_cg[k] >> 1)) & 7) * 16) = reg[k][j];
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int kr = t_rg[k] + 4 * j;                       // rows t_cg*4 .. +3 share row/16 = t_cg/4
-          unsigned* d0 = reinterpret_cast<unsigned*>(dst + (t_cg[k] * 4) * LDS_STRIDE +
-                                                     (((kr >> 2) + (t_cg[k] >> 2)) & 7) * 16 + (kr & 3) * 4);
-          d0[0] = reg[k][j].x;
-          d0[LDS_STRIDE / 4] = reg[k][j].y;
-          d0[2 * LDS_STRIDE / 4] = reg[k][j].z;
-          d0[3 * LDS_STRIDE / 4] = reg[k][j].w;
-        }
-      }
-    }
-  };
-
-  // chunks of all segments as one sequence
-  const int per_seg = r_hi > r_lo ? (r_hi - r_lo + BKR - 1) / BKR : 0;
-  const int nchunks = per_seg * p.nseg;
-  auto chunk_pos = [&](int c, long long& sample_base, int& k0) {
-    const int seg = c / per_seg;
-    sample_base = (long long)seg * p.seg_samples + s0;
-    k0 = r_lo + (c - seg * per_seg) * BKR;
-  };
-  if (nchunks > 0) {
-    long long sb; int k0;
-    chunk_pos(0, sb, k0);
-    load_chunk(sb, k0);
-    store_chunk(0);
-    __syncthreads();
-    for (int c = 0; c < nchunks; ++c) {
-      const bool more = c + 1 < nchunks;
-      if (more) { chunk_pos(c + 1, sb, k0); load_chunk(sb, k0); }
-      tile_mma<T, TM, TN>(acc, As[c & 1], Bs[c & 1], wm, wn, lane);
-      if (more) store_chunk((c + 1) & 1);
-      __syncthreads();
-    }
-  }
-
-  float* __restrict__ dW = p.dW + (long long)split * p.split_stride + (long long)l * p.dw_stride;
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-    for (int tn = 0; tn < TN; ++tn) {
-      const int col = nt * BN + wn * TN * 32 + tn * 32 + (lane & 31);
-      if (col >= Cs) continue;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int m = mt * BM + wm * TM * 32 + tm * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-        if (m < Mtot) dW[(long long)m * Cs + col] = acc[tm][tn][e];
-      }
-    }
-}
-
-// ---- bf16 weight gradient: tiles stay in their memory layout ---------------------------------------------
-// Both operands are stored [row][channel] in HBM while the MFMA wants, per lane, eight consecutive rows (the
-// reduction index) of one channel.  The bf16 kernel copies K-chunks of 64 rows x BM (BN) channels global -> LDS
-// as they are and lets ds_read_b64_tr_b16 do the transposition on the way to the registers: within each block of
-// 16 lanes, lane i receives element i%4 of the 8-byte groups addressed by lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4.
-// Pointing lane s of a block at row (s/4), channel group (s%4) therefore hands lane i rows 0..3 of channel i.
-// LDS rows are BM*2 (BN*2) bytes; the 16-byte chunk c of row R sits at position c ^ swz(R) so that the four rows
-// a 32-lane half reads fall into different 64-byte bank groups.
-constexpr int WG_KR = 64;      // rows (reduction index) per chunk
-template <int ROWB>
+// Both operands are stored [row][channel] in HBM while the MFMA wants, per lane, consecutive rows (the reduction
+// index) of one channel.  The kernel copies K-chunks of WG_KR rows x BM (BN) channels global -> LDS as they are.
+// bf16: ds_read_b64_tr_b16 does the transposition on the way to the registers: within each block of 16 lanes, lane i
+// receives element i%4 of the 8-byte groups addressed by lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4; pointing lane s of a
+// block at row (s/4), channel group (s%4) therefore hands lane i rows 0..3 of channel i.
+// fp32: an operand of v_mfma_f32_32x32x2_f32 is one value per lane, (channel lane%32, row lane/32): a plain 4-byte read
+// of the tile as it lies.  The kernel is bound by the MFMAs (64 cycles each against one such read).  (Its predecessor
+// went global -> registers -> 32 scalar LDS writes per task with two divisions per row: 65-75 TFLOP/s on 128 -> 256
+// channels at side 8, and 11 TFLOP/s at side 7, where nothing was a shift.)
+// The 16-byte chunk c of row R sits at position c ^ swz(R), so that the rows one read touches fall into different
+// bank groups.
+template <typename T> constexpr int wg_kr() { return 128 / (int)sizeof(T); }     // rows (reduction index) per chunk: 64 or 32
+template <typename T, int ROWB>
 __device__ inline int wg_swz(int row) {   // in 16-byte chunks
+  if (sizeof(T) == 4) return 8 * (row & 1);
   return ROWB >= 256 ? 4 * (row & 3) : 4 * ((row >> 1) & 1);
 }
 typedef short short4v __attribute__((ext_vector_type(4)));
@@ -854,12 +652,12 @@ __device__ inline uint2 lds_read_tr16(const unsigned char* p) {
   return __builtin_bit_cast(uint2, v);
 }
 
-template <typename TL>
-__global__ __launch_bounds__(TL::NT) void wgrad_tr_kernel(WgradArgs p) {
-  typedef bf16_t T;
+template <typename T, typename TL>
+__global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
+  constexpr int SZ = (int)sizeof(T), EPV = 16 / SZ, WG_KR = wg_kr<T>();
   constexpr int BM = TL::BM, BN = TL::BN, TM = TL::TM, TN = TL::TN, NT_ = TL::NT;
-  constexpr int RBA = BM * 2, RBB = BN * 2;                 // bytes per LDS row
-  constexpr int CPA = BM / 8, CPB = BN / 8;                 // 16-byte chunks per row
+  constexpr int RBA = BM * SZ, RBB = BN * SZ;               // bytes per LDS row
+  constexpr int CPA = BM / EPV, CPB = BN / EPV;             // 16-byte chunks per row
   constexpr int PA = WG_KR * CPA / NT_, PB = WG_KR * CPB / NT_;
   constexpr int RPA = NT_ / CPA, RPB = NT_ / CPB;           // rows per loader pass (multiples of 4)
   static_assert(WG_KR * CPA % NT_ == 0 && WG_KR * CPB % NT_ == 0 && RPA % 4 == 0 && RPB % 4 == 0, "loader shape");
@@ -888,22 +686,22 @@ __global__ __launch_bounds__(TL::NT) void wgrad_tr_kernel(WgradArgs p) {
 
   // ---- loader: slot = pass * NT + tid is the 16-byte LDS slot; it holds chunk (slot % CP) ^ swz(row) of row slot / CP
   const int rowA0 = tid / CPA, rowB0 = tid / CPB;
-  const int chA = (tid % CPA) ^ wg_swz<RBA>(rowA0), chB = (tid % CPB) ^ wg_swz<RBB>(rowB0);
-  const int mA = mt * BM + chA * 8;                          // first of this thread's 8 channels along M
+  const int chA = (tid % CPA) ^ wg_swz<T, RBA>(rowA0), chB = (tid % CPB) ^ wg_swz<T, RBB>(rowB0);
+  const int mA = mt * BM + chA * EPV;                        // first of this thread's channels along M
   const bool okA = mA < Mtot;
   const int tapA = okA ? mA / Cb : 0;
   const int cA = mA - tapA * Cb;
   const int kyA = p.ntaps == 1 ? 1 : (tapA >> 2), kxA = p.ntaps == 1 ? 1 : (tapA & 3);
-  const int cB = nt * BN + chB * 8;
+  const int cB = nt * BN + chB * EPV;
   const bool okB = cB < Cs;
   const unsigned lds0 = (unsigned)(uintptr_t)smem;
   const long long big_per_sample = p.ntaps == 1 ? (long long)rps * Cb : (long long)Hb * Hb * Cb;
 
-  // Chunks start at multiples of 64 rows.  With a power-of-two side of at most 64 a chunk is a whole number of
+  // Chunks start at multiples of WG_KR rows.  With a power-of-two side of at most WG_KR a chunk is a whole number of
   // samples or of pixel rows, so a thread's rows keep their x, their y offset inside the chunk and their sample
   // offset: everything that depends on the row is computed once, and a chunk only adds a wave-uniform offset
   // (sample n0, pixel row y0 of the chunk's first row) and re-tests the vertical border.
-  const bool fast = p.ntaps == 1 || (p.hs_shift >= 0 && Hs <= 64);
+  const bool fast = p.ntaps == 1 || (p.hs_shift >= 0 && Hs <= WG_KR);
   // Reduction order "pixel row first" (y, sample, x) for the models whose samples * H rows per pixel row are whole
   // chunks: a chunk then lies inside one pixel row y0, the vertical border test is the same for the whole chunk, and
   // the chunks of the one pixel row whose tap row ky falls outside the map (y0 = 0 for ky = 0, y0 = H - 1 for
@@ -921,7 +719,7 @@ __global__ __launch_bounds__(TL::NT) void wgrad_tr_kernel(WgradArgs p) {
     fa_iy[i] = 1 << 20;
     if (okA) {
       if (p.ntaps == 1) {
-        fa_off[i] = (unsigned)((c * Cb + cA) * 2);
+        fa_off[i] = (unsigned)((c * Cb + cA) * SZ);
         fa_iy[i] = 0;
       } else if (yfirst) {
         // row c of a chunk: sample n0 + c / H, x = c % H, pixel row y0 (chunk-uniform)
@@ -930,7 +728,7 @@ __global__ __launch_bounds__(TL::NT) void wgrad_tr_kernel(WgradArgs p) {
         const int ix = 2 * xi - 1 + kxA;
         if ((unsigned)ix < (unsigned)Hb) {
           fa_iy[i] = kyA - 1;
-          fa_off[i] = (unsigned)((((ni * Hb + fa_iy[i]) * Hb + ix) * Cb + cA) * 2);    // may wrap below zero: masked
+          fa_off[i] = (unsigned)((((ni * Hb + fa_iy[i]) * Hb + ix) * Cb + cA) * SZ);    // may wrap below zero: masked
         }
       } else if (fast) {
         const int sh = p.hs_shift;
@@ -939,7 +737,7 @@ __global__ __launch_bounds__(TL::NT) void wgrad_tr_kernel(WgradArgs p) {
         const int ix = 2 * xi - 1 + kxA;
         if ((unsigned)ix < (unsigned)Hb) {
           fa_iy[i] = 2 * yi - 1 + kyA;
-          fa_off[i] = (unsigned)((((ni * Hb + fa_iy[i]) * Hb + ix) * Cb + cA) * 2);    // may wrap below zero: masked
+          fa_off[i] = (unsigned)((((ni * Hb + fa_iy[i]) * Hb + ix) * Cb + cA) * SZ);    // may wrap below zero: masked
         }
       }
     }
@@ -947,31 +745,31 @@ __global__ __launch_bounds__(TL::NT) void wgrad_tr_kernel(WgradArgs p) {
 #pragma unroll
   for (int i = 0; i < PB; ++i) {
     const int c = rowB0 + i * RPB;
-    if (yfirst) fb_off[i] = (unsigned)((((c >> p.hs_shift) * rps + (c & (Hs - 1))) * Cs + cB) * 2);
-    else fb_off[i] = (unsigned)((c * Cs + cB) * 2);
+    if (yfirst) fb_off[i] = (unsigned)((((c >> p.hs_shift) * rps + (c & (Hs - 1))) * Cs + cB) * SZ);
+    else fb_off[i] = (unsigned)((c * Cs + cB) * SZ);
   }
 
   auto load_chunk = [&](int seg, int k0, int stage) {
     const long long sb = (long long)seg * p.seg_samples + s0;
-    const int4v a_rsrc = make_rsrc(static_cast<const T*>(p.Big) + sb * big_per_sample, (unsigned long long)(s1 - s0) * big_per_sample * 2);
-    const int4v b_rsrc = make_rsrc(static_cast<const T*>(p.Small) + sb * rps * Cs, (unsigned long long)R * Cs * 2);
+    const int4v a_rsrc = make_rsrc(static_cast<const T*>(p.Big) + sb * big_per_sample, (unsigned long long)(s1 - s0) * big_per_sample * SZ);
+    const int4v b_rsrc = make_rsrc(static_cast<const T*>(p.Small) + sb * rps * Cs, (unsigned long long)R * Cs * SZ);
     const unsigned a_dst = lds0 + stage * STAGE_A + wave * 1024;
     const unsigned b_dst = lds0 + 2 * STAGE_A + stage * STAGE_B + wave * 1024;
     const int left = r_hi - k0;                 // rows of this chunk that exist
-    unsigned b_delta = (unsigned)(k0 * Cs * 2);
+    unsigned b_delta = (unsigned)(k0 * Cs * SZ);
     if (fast) {
       unsigned a_delta;
       int y2 = 0;
       if (p.ntaps == 1) {
-        a_delta = (unsigned)(k0 * Cb * 2);
+        a_delta = (unsigned)(k0 * Cb * SZ);
       } else if (yfirst) {
         const int y0 = k0 / rb, n0 = (k0 - y0 * rb) >> p.hs_shift;
-        a_delta = (unsigned)(((n0 * Hb + 2 * y0) * Hb) * Cb * 2);
+        a_delta = (unsigned)(((n0 * Hb + 2 * y0) * Hb) * Cb * SZ);
         y2 = 2 * y0;
-        b_delta = (unsigned)(((n0 * Hs + y0) * Hs) * Cs * 2);
+        b_delta = (unsigned)(((n0 * Hs + y0) * Hs) * Cs * SZ);
       } else {
         const int n0 = k0 >> (2 * p.hs_shift), y0 = (k0 & (rps - 1)) >> p.hs_shift;
-        a_delta = (unsigned)(((n0 * Hb + 2 * y0) * Hb) * Cb * 2);
+        a_delta = (unsigned)(((n0 * Hb + 2 * y0) * Hb) * Cb * SZ);
         y2 = 2 * y0;
       }
 #pragma unroll
@@ -986,9 +784,16 @@ __global__ __launch_bounds__(TL::NT) void wgrad_tr_kernel(WgradArgs p) {
         unsigned off = NO_ROW;
         if (r < r_hi && okA) {
           int n, y, x;
-          decode_row(r, Hs, rps, p.hs_shift, n, y, x);
+          if (p.rps_inv) {                        // r / rps and rem / Hs as products with the rounded-up reciprocals
+            n = (int)__umulhi((unsigned)r, p.rps_inv);
+            const int rem = r - n * rps;
+            y = (int)__umulhi((unsigned)rem, p.hs_inv);
+            x = rem - y * Hs;
+          } else {
+            decode_row(r, Hs, rps, p.hs_shift, n, y, x);
+          }
           const int iy = 2 * y - 1 + kyA, ix = 2 * x - 1 + kxA;
-          if ((unsigned)iy < (unsigned)Hb && (unsigned)ix < (unsigned)Hb) off = (unsigned)((((n * Hb + iy) * Hb + ix) * Cb + cA) * 2);
+          if ((unsigned)iy < (unsigned)Hb && (unsigned)ix < (unsigned)Hb) off = (unsigned)((((n * Hb + iy) * Hb + ix) * Cb + cA) * SZ);
         }
         load16_to_lds(a_rsrc, off, a_dst + i * NT_ * 16);
       }
@@ -1012,8 +817,8 @@ __global__ __launch_bounds__(TL::NT) void wgrad_tr_kernel(WgradArgs p) {
   const int frow = 8 * kgrp + (s16 >> 2);                    // + 16 * kstep + 4 * half
   const int fch = 2 * hb + ((s16 & 3) >> 1);                 // 16-byte chunk inside the 32-channel fragment (0..3)
   const int fbyte = 8 * (s16 & 1);
-  const int swzA = wg_swz<RBA>(frow), swzB = wg_swz<RBB>(frow);   // frow % 4 (and (frow/2) % 2) do not change with kstep or half
-  auto mma_chunk = [&](int stage) {
+  const int swzA = wg_swz<T, RBA>(frow), swzB = wg_swz<T, RBB>(frow);   // frow % 4 (and (frow/2) % 2) do not change with kstep or half
+  auto mma_chunk16 = [&](int stage) {
     const unsigned char* As = smem + stage * STAGE_A;
     const unsigned char* Bs = smem + 2 * STAGE_A + stage * STAGE_B;
 #pragma unroll
@@ -1036,8 +841,37 @@ __global__ __launch_bounds__(TL::NT) void wgrad_tr_kernel(WgradArgs p) {
 #pragma unroll
       for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn) mma16B(acc[tm][tn], a[tm], b[tn], T());
+        for (int tn = 0; tn < TN; ++tn) mma16B(acc[tm][tn], a[tm], b[tn], bf16_t());
     }
+  };
+
+  // fp32: K-step ks is rows 2 ks, 2 ks + 1 of the chunk; lane half h reads row 2 ks + h (swz flips with h only)
+  auto mma_chunk32 = [&](int stage) {
+    const int r = lane & 31, h = lane >> 5;
+    const unsigned char* As = smem + stage * STAGE_A + h * RBA + (r & 3) * 4;
+    const unsigned char* Bs = smem + 2 * STAGE_A + stage * STAGE_B + h * RBB + (r & 3) * 4;
+    const float* ap[TM];
+    const float* bp[TN];
+#pragma unroll
+    for (int t = 0; t < TM; ++t) ap[t] = reinterpret_cast<const float*>(As + ((((wm * TM + t) * 8 + (r >> 2)) ^ (8 * h)) * 16));
+#pragma unroll
+    for (int t = 0; t < TN; ++t) bp[t] = reinterpret_cast<const float*>(Bs + ((((wn * TN + t) * 8 + (r >> 2)) ^ (8 * h)) * 16));
+#pragma unroll
+    for (int ks = 0; ks < WG_KR / 2; ++ks) {
+      float a[TM], b[TN];
+#pragma unroll
+      for (int t = 0; t < TM; ++t) a[t] = ap[t][ks * 2 * BM];
+#pragma unroll
+      for (int t = 0; t < TN; ++t) b[t] = bp[t][ks * 2 * BN];
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[tm], b[tn], acc[tm][tn], 0, 0, 0);
+    }
+  };
+  auto mma_chunk = [&](int stage) {
+    if constexpr (SZ == 2) mma_chunk16(stage);
+    else mma_chunk32(stage);
   };
 
   // chunks of all segments as one sequence; in pixel-row-first order the chunks [bad0, bad0 + nbad) of every segment
@@ -1106,7 +940,15 @@ __global__ __launch_bounds__(TL::NT) void wgrad_tr_kernel(WgradArgs p) {
   }
 }
 
+// Tiles of the weight gradient.  bf16: the largest tile the output fills, because the loop lives on the CU's path from
+// L2 (operand bytes per product fall with the tile's sides).  fp32: sixteen times the matrix-pipe time per byte, so
+// tiles are small: 128 x 128 with two blocks per CU leaves little of a last round of blocks idle where 256-row tiles
+// (about 1 ms each) idled up to half of it.
 typedef Tile<64, 128, 1, 4> TileWgImg;    // patch-matrix layers: 64 packed columns x 128 feature channels
+typedef Tile<64, 64, 2, 2> TileWgImg64;   //   and x 64
+typedef Tile<256, 64, 4, 1> TileWg64;     // 64 channels on the N side, bf16
+typedef Tile<128, 128, 2, 2> TileWgF32;
+typedef Tile<128, 64, 2, 2> TileWgF32N;
 
 template <typename T, typename TL>
 static void launch_wgrad_one(WgradArgs a, hipStream_t st) {
@@ -1114,15 +956,28 @@ static void launch_wgrad_one(WgradArgs a, hipStream_t st) {
   const int MT = (a.ntaps * a.Cb + TL::BM - 1) / TL::BM, NT = (a.Cs + TL::BN - 1) / TL::BN;
   const long long blocks = ((long long)a.L * a.ksplit + 7) / 8 * 8 * MT * NT;
   if (blocks == 0) return;
-  if (sizeof(T) == 2) {
-    // 32-bit byte offsets inside one model's slice of either operand
-    const long long side = a.ntaps == 1 ? a.Hs : 2 * a.Hs;
-    if ((long long)a.seg_samples * side * side * a.Cb * 2 >= (1LL << 31) || (long long)a.seg_samples * a.Hs * a.Hs * a.Cs * 2 >= (1LL << 31))
-      return launch_fail("weight gradient: one segment of an operand is 2 GiB or larger");
-    hipLaunchKernelGGL((wgrad_tr_kernel<TL>), dim3((unsigned)blocks), dim3(TL::NT), 0, st, a);
-  } else {
-    hipLaunchKernelGGL((wgrad_kernel<T, TL>), dim3((unsigned)blocks), dim3(TL::NT), 0, st, a);
+  // 32-bit byte offsets inside one model's slice of either operand
+  const long long side = a.ntaps == 1 ? a.Hs : 2 * a.Hs, rps = (long long)a.Hs * a.Hs;
+  if ((long long)a.seg_samples * side * side * a.Cb * (long long)sizeof(T) >= (1LL << 31) ||
+      (long long)a.seg_samples * rps * a.Cs * (long long)sizeof(T) >= (1LL << 31))
+    return launch_fail("weight gradient: one segment of an operand is 2 GiB or larger");
+  // ceil(2^32 / d): the high half of its product with r is r / d exactly while r * d < 2^32
+  a.rps_inv = a.hs_inv = 0;
+  if (a.hs_shift < 0 && a.seg_samples * rps * rps < (1LL << 32)) {
+    a.rps_inv = (unsigned)(((1ULL << 32) + rps - 1) / rps);
+    a.hs_inv = (unsigned)(((1ULL << 32) + a.Hs - 1) / a.Hs);
   }
+  hipLaunchKernelGGL((wgrad_kernel<T, TL>), dim3((unsigned)blocks), dim3(TL::NT), 0, st, a);
+}
+
+// Which tile a layer's weight gradient uses, as f(tile, name)
+template <typename F>
+static void with_wgrad_tile(int esize, int ntaps, int Cb, int Cs, F&& f) {
+  if (ntaps * Cb <= 64) { if (Cs <= 64) f(TileWgImg64(), "wgrad<64x64>"); else f(TileWgImg(), "wgrad<64x128>"); }
+  else if (esize == 4) { if (Cs <= 64) f(TileWgF32N(), "wgrad<128x64>"); else f(TileWgF32(), "wgrad<128x128>"); }
+  else if (Cs % 256 == 0) f(TileBig(), "wgrad<256x256>");
+  else if (Cs <= 64) f(TileWg64(), "wgrad<256x64>");
+  else f(TileMid(), "wgrad<256x128>");
 }
 
 template <typename T>
@@ -1130,15 +985,19 @@ void launch_wgrad(const WgradArgs& a, hipStream_t st) {
   if (!a.Big || !a.Small || !a.dW || !a.offs || a.Cb % 8 || a.Cs % 8 || (a.ntaps != 1 && a.ntaps != 16) || a.ksplit < 1 ||
       (a.ksplit > 1 && a.split_stride <= 0))
     return launch_fail("weight gradient: null operand, channel counts that are not multiples of 8, or a bad row split");
-  if (a.ntaps * a.Cb <= 64) return launch_wgrad_one<T, TileWgImg>(a, st);
-  if (a.Cs % 256 == 0) return launch_wgrad_one<T, TileBig>(a, st);
-  return launch_wgrad_one<T, TileMid>(a, st);
+  with_wgrad_tile((int)sizeof(T), a.ntaps, a.Cb, a.Cs, [&](auto tile, const char*) { launch_wgrad_one<T, decltype(tile)>(a, st); });
 }
-int wgrad_tiles_per_model(int ntaps, int Cb, int Cs) {
-  const int M = ntaps * Cb;
-  if (M <= 64) return (M + TileWgImg::BM - 1) / TileWgImg::BM * ((Cs + TileWgImg::BN - 1) / TileWgImg::BN);
-  if (Cs % 256 == 0) return (M + TileBig::BM - 1) / TileBig::BM * (Cs / TileBig::BN);
-  return (M + TileMid::BM - 1) / TileMid::BM * ((Cs + TileMid::BN - 1) / TileMid::BN);
+int wgrad_tiles_per_model(int esize, int ntaps, int Cb, int Cs) {
+  int tiles = 0;
+  with_wgrad_tile(esize, ntaps, Cb, Cs, [&](auto tile, const char*) {
+    tiles = (ntaps * Cb + tile.BM - 1) / tile.BM * ((Cs + tile.BN - 1) / tile.BN);
+  });
+  return tiles;
+}
+const char* wgrad_variant_name(int esize, const WgradArgs& a) {
+  const char* name = "";
+  with_wgrad_tile(esize, a.ntaps, a.Cb, a.Cs, [&](auto, const char* n) { name = n; });
+  return name;
 }
 template void launch_wgrad<float>(const WgradArgs&, hipStream_t);
 template void launch_wgrad<bf16_t>(const WgradArgs&, hipStream_t);

@@ -147,3 +147,34 @@ def test_upsample_conv3_runs_on_the_transposed_convolution_engine(ctxs, prec, ci
     tol = tolerance(prec)
     assert np.max(np.abs(got - ref4)) <= tol * np.max(np.abs(ref4))
     assert np.max(np.abs(got - lit)) <= (2e-5 if not bf else 2e-2) * np.max(np.abs(lit))
+
+
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+@pytest.mark.parametrize("cb,cs,hs,groups", [(64, 64, 32, [1, 1]), (64, 64, 64, [1]), (64, 128, 14, [3, 0, 2]), (128, 64, 5, [33, 1]),
+                                             (8, 8, 7, [4]), (72, 136, 6, [5, 2]), (64, 256, 1, [70])])
+def test_wgrad_row_decoding_and_narrow_tiles(ctxs, prec, cb, cs, hs, groups):
+    """The weight gradient where its row decoding changes: sides of one K-chunk (32 rows in fp32, 64 in bf16) and above, sides
+    that are no power of two (reciprocal products), a side of one, and outputs that fill no tile in either direction."""
+    torch = U.torch_mod()
+    g = ctxs[prec]
+    bf = prec == binding.BF16
+    rng = np.random.default_rng(cb + cs + hs)
+    n, G = int(sum(groups)), len(groups)
+    offs = np.concatenate([[0], np.cumsum(groups)]).astype(np.int32)
+    big = U.round_to(rng.normal(0, 1, (n, cb, 2 * hs, 2 * hs)), bf)
+    small = U.round_to(rng.normal(0, 1, (n, cs, hs, hs)), bf)
+    d_offs = U.dev(offs)
+    d_big = U.dev(U.pack(big.transpose(0, 2, 3, 1), bf))
+    d_small = U.dev(U.pack(small.transpose(0, 2, 3, 1), bf))
+    dw = torch.full((G * 16 * cb * cs,), 7.0, dtype=torch.float32, device="cuda")
+    g.op_conv_wgrad(d_big.data_ptr(), d_small.data_ptr(), dw.data_ptr(), d_offs.data_ptr(), G, n, cb, cs, hs)
+    got = dw.cpu().numpy().reshape(G, 4, 4, cb, cs)
+    for i in range(G):
+        if groups[i] == 0:
+            assert np.all(got[i] == 0)
+            continue
+        W = np.zeros((cs, cb, 4, 4))
+        _, dW, _ = O.conv2d_bwd(big[offs[i]:offs[i + 1]], W, small[offs[i]:offs[i + 1]], need_dx=False)
+        ref = dW.transpose(2, 3, 1, 0)
+        # fp32 sums of up to 4096 products in another order; bf16 inputs are exact here, so only the sums differ too
+        assert np.max(np.abs(got[i] - ref)) <= 2e-5 * np.max(np.abs(ref)), "wgrad group %d" % i
