@@ -185,10 +185,10 @@ const int* tpre_of(gan_ctx* c, int rps, int tile_rows) {
   }
   return c->rb.tpre + (long long)g * (c->L + 1);
 }
-// tile height for a layer: from the average rows per model at the sizing batch (fixed at create, so the prefix
+// the tile of a layer's launch: from the average rows per model at the sizing batch (fixed at create, so the prefix
 // arrays built at every routing match)
-int layer_tile_rows(const gan_ctx* c, int n_out, int rps) {
-  return conv_tile_rows(n_out, (long long)c->NB * rps / c->L, c->L);
+ConvTile layer_tile(const gan_ctx* c, int mode, int n_out, int rps, int nseg) {
+  return conv_choose_tile((int)esize(c), n_out, (double)c->NB * rps / c->L, c->L, nseg * (mode == MODE_UP ? 4 : 1));
 }
 int ub_tiles(const gan_ctx* c, int n, int rps, int tile_rows) {
   return (int)(((long long)n * rps) / tile_rows) + (n < c->L ? n : c->L);
@@ -562,8 +562,9 @@ void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, c
                double flops_alg = -1.0, bool stats = false) {
   ConvArgs a = {};
   a.A = A; a.W = W; a.Out = Out; a.Aux = Aux; a.w_nstride = w_nstride ? w_nstride : N;
-  const int tr = layer_tile_rows(c, N, Hr * Hr);
-  a.offs = c->rb.offs; a.tpre = tpre_of(c, Hr * Hr, tr); a.tmodel = tmodel_of(c, Hr * Hr, tr); a.tile_rows = tr;
+  a.tile = layer_tile(c, mode, N, Hr * Hr, nseg);
+  const int tr = conv_tile_rows(a.tile);
+  a.offs = c->rb.offs; a.tpre = tpre_of(c, Hr * Hr, tr); a.tmodel = tmodel_of(c, Hr * Hr, tr);
   a.w_stride = wstride; a.L = c->L; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n;
   a.C = C; a.N = N; a.Hin = Hin; a.Hr = Hr; a.ub_tiles = ub_tiles(c, n, Hr * Hr, tr);
   a.slope = c->cfg.leaky_slope;
@@ -651,19 +652,20 @@ NormArgs norm_args(gan_ctx* c, Net& net, int C, int rps, long long gamma, long l
 }
 
 // BatchNorm (batch statistics, or the running ones) + activation: x -> y
-// gemm_rps / gemm_phases describe the GEMM that produced x and left per-tile column sums in c->stat_partial
+// gemm_mode / gemm_rps describe the GEMM that produced x and left per-tile column sums in c->stat_partial
 template <typename T>
-void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool use_running, bool update_running, int gemm_rps,
-                int gemm_phases, int col_groups = 1) {
+void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool use_running, bool update_running, int gemm_mode,
+                int gemm_rps, int col_groups = 1) {
   a.x = x; a.y = y;
   const double elems = (double)a.n * a.nseg * a.rps * a.C;
   if (use_running) {
     launch_bn_from_running(a, c->st);
   } else {
-    const int tr = layer_tile_rows(c, a.C * col_groups, gemm_rps);     // the tile height of the GEMM that left the partials (N = C * col_groups)
+    const ConvTile tile = layer_tile(c, gemm_mode, a.C * col_groups, gemm_rps, a.nseg);   // of the GEMM that left the partials (N = C * col_groups)
+    const int tr = conv_tile_rows(tile), gemm_phases = gemm_mode == MODE_UP ? 4 : 1;
     a.fold_running = update_running && a.nseg == 1 && a.run_mean && a.run_var;
     launch_bn_stats_from_partial(a, c->stat_partial, tpre_of(c, gemm_rps, tr), ub_tiles(c, a.n, gemm_rps, tr), gemm_phases, col_groups, tr,
-                                 gemm_rps, conv_stat_split(a.C * col_groups, tr), c->st);
+                                 gemm_rps, conv_stat_split(tile), c->st);
     if (update_running && !a.fold_running) launch_bn_running(a, c->st);
   }
   Scope s(c, "bn_apply", 0, 2 * elems * sizeof(T));
@@ -734,7 +736,7 @@ void g_forward(gan_ctx* c, int n, bool use_running, bool update_running) {
                1, 1, 0, 1, n, 0, -1.0, !use_running);
   bn_forward<T>(c, norm_args<T>(c, G, G.C0, G.h0 * G.h0, G.fc_gamma, G.fc_beta, G.fc_rs, c->g_mean[0], c->g_var[0], c->g_rstd[0],
                                 c->g_sums[0], 0, 1, n, relu),
-                c->gpre[0], c->gact[0], use_running, update_running, 1, 1, G.h0 * G.h0);
+                c->gpre[0], c->gact[0], use_running, update_running, MODE_DENSE, 1, G.h0 * G.h0);
   const int nl = (int)G.conv.size();
   for (int i = 0; i + 1 < nl; ++i) {
     const ConvLayer& cl = G.conv[i];
@@ -742,7 +744,7 @@ void g_forward(gan_ctx* c, int n, bool use_running, bool update_running) {
                  cl.Hs, cl.Hs, 0, 1, n, 0, -1.0, !use_running);
     bn_forward<T>(c, norm_args<T>(c, G, cl.Cb, 4 * cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->g_mean[i + 1], c->g_var[i + 1],
                                   c->g_rstd[i + 1], c->g_sums[i + 1], 0, 1, n, relu),
-                  c->gpre[i + 1], c->gact[i + 1], use_running, update_running, cl.Hs * cl.Hs, 4);
+                  c->gpre[i + 1], c->gact[i + 1], use_running, update_running, MODE_UP, cl.Hs * cl.Hs);
   }
   // last transposed conv (+bias, tanh) straight into the fake half of D's image buffer
   const ConvLayer& cl = G.conv[nl - 1];
@@ -766,7 +768,7 @@ void d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_running) 
                  cl.Cs, 2 * cl.Hs, cl.Hs, seg_first, nseg, n, 0, -1.0, true);
     bn_forward<T>(c, norm_args<T>(c, D, cl.Cs, cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->d_mean[j], c->d_var[j], c->d_rstd[j],
                                   c->d_sums[j], seg_first, nseg, n, slope),
-                  c->dpre[j], c->dact[j], false, update_running, cl.Hs * cl.Hs, 1);
+                  c->dpre[j], c->dact[j], false, update_running, MODE_DOWN, cl.Hs * cl.Hs);
   }
   HeadArgs h;
   memset(&h, 0, sizeof(h));
@@ -940,7 +942,7 @@ void paper_g_forward(gan_ctx* c, int n, bool use_running, bool update_running) {
                  cl.Hs, cl.Hs, 0, 1, n, 0, -1.0, !use_running);
     NormArgs a = norm_args<T>(c, G, cl.Cb, 4 * cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->g_mean[i + 1], c->g_var[i + 1],
                               c->g_rstd[i + 1], c->g_sums[i + 1], 0, 1, n, f.leaky_slope);
-    bn_forward<T>(c, a, c->gpre[i + 1], c->gact[i + 1], use_running, update_running, cl.Hs * cl.Hs, 4);
+    bn_forward<T>(c, a, c->gpre[i + 1], c->gact[i + 1], use_running, update_running, MODE_UP, cl.Hs * cl.Hs);
   }
   const ConvLayer& cl = G.conv[nl - 1];                // Conv k3 s1 p1 (+bias) -> tanh, into the fake half of D's image buffer
   Conv3Args a;
@@ -1264,21 +1266,24 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
   // geometries used by any launch: (rows per sample, tile height) of every GEMM's row space
   {
     auto reg = [&](int rps, int tile_rows) { if (geom_id(c, rps, tile_rows) < 0) ok = false; };
+    auto reg_gemm = [&](int mode, int n_out, int rps, int nseg) { reg(rps, conv_tile_rows(layer_tile(c, mode, n_out, rps, nseg))); };
     const ConvLayer& gl = c->G.conv.back();
     const ConvLayer& d1 = c->D.conv.front();
-    reg(1, layer_tile_rows(c, c->G.J, 1));                                      // G's linear layer
+    reg_gemm(MODE_DENSE, c->G.J, 1, 1);                                         // G's linear layer
     for (size_t i = 0; i + 1 < c->G.conv.size(); ++i) {
       const ConvLayer& cl = c->G.conv[i];
-      reg(cl.Hs * cl.Hs, layer_tile_rows(c, cl.Cb, cl.Hs * cl.Hs));             // forward (up)
-      reg(cl.Hs * cl.Hs, layer_tile_rows(c, cl.Cs, cl.Hs * cl.Hs));             // data gradient (down)
+      reg_gemm(MODE_UP, cl.Cb, cl.Hs * cl.Hs, 1);                               // forward
+      reg_gemm(MODE_DOWN, cl.Cs, cl.Hs * cl.Hs, 1);                             // data gradient
     }
-    reg(gl.Hs * gl.Hs, layer_tile_rows(c, gl.Cs, gl.Hs * gl.Hs));               // its data gradient (patch GEMM)
-    for (size_t j = 1; j < c->D.conv.size(); ++j) {
-      const ConvLayer& cl = c->D.conv[j];
-      reg(cl.Hs * cl.Hs, layer_tile_rows(c, cl.Cs, cl.Hs * cl.Hs));             // forward (down)
-      reg(cl.Hs * cl.Hs, layer_tile_rows(c, cl.Cb, cl.Hs * cl.Hs));             // data gradient (up)
+    reg_gemm(MODE_DENSE, gl.Cs, gl.Hs * gl.Hs, 1);                              // G's last layer: its data gradient (patch GEMM)
+    for (int nseg = 1; nseg <= 2; ++nseg) {                                     // D runs on one segment and on both
+      for (size_t j = 1; j < c->D.conv.size(); ++j) {
+        const ConvLayer& cl = c->D.conv[j];
+        reg_gemm(MODE_DOWN, cl.Cs, cl.Hs * cl.Hs, nseg);                        // forward
+        reg_gemm(MODE_UP, cl.Cb, cl.Hs * cl.Hs, nseg);                          // data gradient
+      }
+      reg_gemm(MODE_DENSE, d1.Cs, d1.Hs * d1.Hs, nseg);                         // first conv (patch GEMM)
     }
-    reg(d1.Hs * d1.Hs, layer_tile_rows(c, d1.Cs, d1.Hs * d1.Hs));               // first conv (patch GEMM)
     // row space of every BatchNorm, in blocks of BN_RED_ROWS rows (backward reduction)
     reg(c->G.h0 * c->G.h0, BN_RED_ROWS);
     for (size_t i = 0; i + 1 < c->G.conv.size(); ++i) reg(4 * c->G.conv[i].Hs * c->G.conv[i].Hs, BN_RED_ROWS);
@@ -1334,16 +1339,18 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
   }
   {
     // column sums left by the GEMM in front of every BatchNorm: phases x segments x tiles x sub-tiles (at most 4) x columns x 2
-    size_t mx = (size_t)4 * ub_tiles(c, NB, 1, layer_tile_rows(c, c->G.J, 1)) * c->G.J;
+    size_t mx = (size_t)4 * ub_tiles(c, NB, 1, conv_tile_rows(layer_tile(c, MODE_DENSE, c->G.J, 1, 1))) * c->G.J;
     for (size_t i = 0; i + 1 < c->G.conv.size(); ++i) {
       const ConvLayer& cl = c->G.conv[i];
-      const size_t v = (size_t)4 * 4 * ub_tiles(c, NB, cl.Hs * cl.Hs, layer_tile_rows(c, cl.Cb, cl.Hs * cl.Hs)) * cl.Cb;
+      const size_t v = (size_t)4 * 4 * ub_tiles(c, NB, cl.Hs * cl.Hs, conv_tile_rows(layer_tile(c, MODE_UP, cl.Cb, cl.Hs * cl.Hs, 1))) * cl.Cb;
       mx = v > mx ? v : mx;
     }
     for (size_t j = 1; j < c->D.conv.size(); ++j) {
       const ConvLayer& cl = c->D.conv[j];
-      const size_t v = (size_t)4 * 2 * ub_tiles(c, NB, cl.Hs * cl.Hs, layer_tile_rows(c, cl.Cs, cl.Hs * cl.Hs)) * cl.Cs;
-      mx = v > mx ? v : mx;
+      for (int nseg = 1; nseg <= 2; ++nseg) {
+        const size_t v = (size_t)4 * nseg * ub_tiles(c, NB, cl.Hs * cl.Hs, conv_tile_rows(layer_tile(c, MODE_DOWN, cl.Cs, cl.Hs * cl.Hs, nseg))) * cl.Cs;
+        mx = v > mx ? v : mx;
+      }
     }
     // and the BatchNorm backward reduction: segments x row blocks x channels x 2
     {
@@ -1887,13 +1894,15 @@ static gan_status op_conv(gan_ctx* c, int mode, const void* A, const void* W, vo
     return fail(c, GAN_E_SHAPE, "an operand of 2 GiB or more (the kernels use 32-bit byte offsets)");
   (void)take_launch_error();
   int* tp = nullptr;
-  const int tr = c->op_tile_rows ? c->op_tile_rows : conv_tile_rows(N, (long long)n_samples * Hr * Hr / n_groups, n_groups);
+  const ConvTile tile = c->op_tile_rows ? conv_tile_of_rows(c->op_tile_rows, N)
+                                        : conv_choose_tile((int)esize(c), N, (double)n_samples * Hr * Hr / n_groups, n_groups, mode == MODE_UP ? 4 : 1);
+  const int tr = conv_tile_rows(tile);
   gan_status s = op_common(c, offs, n_groups, Hr * Hr, tr, &tp);
   if (s != GAN_OK) return s;
   ConvArgs a = {};
   a.A = A; a.W = W; a.Out = Out; a.Aux = nullptr; a.w_nstride = N; a.offs = offs; a.tpre = tp; a.w_stride = wstride; a.L = n_groups;
   a.seg_first = 0; a.nseg = 1; a.seg_samples = n_samples; a.C = C; a.N = N; a.Hin = Hin; a.Hr = Hr;
-  a.ub_tiles = (int)(((long long)n_samples * Hr * Hr) / tr) + n_groups; a.slope = 0.f; a.tile_rows = tr;
+  a.ub_tiles = (int)(((long long)n_samples * Hr * Hr) / tr) + n_groups; a.slope = 0.f; a.tile = tile;
   if (c->bf16) launch_conv<bf16_t>(mode, EPI_NONE, a, c->st); else launch_conv<float>(mode, EPI_NONE, a, c->st);
   s = finish_op(c);
   (void)hipFree(tp);

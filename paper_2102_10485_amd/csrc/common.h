@@ -55,6 +55,8 @@ template <> __host__ __device__ inline bf16_t from_float<bf16_t>(float f) {
 void launch_fail(const char* msg);
 const char* take_launch_error();   // the first reason recorded on this thread since the last call, or nullptr
 
+// Block tiles of the forward-type GEMM kernel (rows x columns): conv_gemm.hip
+enum ConvTile { TILE_BIG = 0, TILE_MID = 1, TILE_SMALL = 2, TILE_NARROW = 3, TILE_TINY = 4 };
 enum ConvMode { MODE_DOWN = 0, MODE_UP = 1, MODE_DENSE = 2 };
 enum Epilogue { EPI_NONE = 0, EPI_ACT_BWD = 1, EPI_LRELU = 2 };
 enum Act { ACT_RELU = 0, ACT_LRELU = 1 };
@@ -80,7 +82,7 @@ struct ConvArgs {
   int Hin;               // side of the gathered tensor
   int Hr;                // side of the row space (rows per sample = Hr*Hr)
   int ub_tiles;          // launched upper bound of M-tiles per (segment, phase)
-  int tile_rows;         // rows per M-tile the prefix array was built for (conv_tile_rows)
+  ConvTile tile;         // its height is what the prefix array was built for
   int hr_shift;          // log2(Hr) or -1 (filled by the launcher)
   float slope;           // EPI_ACT_BWD: derivative on the non-positive side
 };
@@ -111,9 +113,11 @@ const char* wgrad_variant_name(int esize, const WgradArgs& a);
 // output tiles per model of the weight-gradient launch for this layer shape (esize: bytes per stored element)
 int wgrad_tiles_per_model(int esize, int ntaps, int Cb, int Cs);
 
-// rows per M-tile the forward-type kernel will use for n_out output channels and about rows_per_model rows
-int conv_tile_rows(int n_out, long long rows_per_model_hint, int n_models);
-// row blocks per tile with their own BatchNorm partial sums, for the tile the forward-type kernel uses for n_out channels
-int conv_stat_split(int n_out, int tile_rows);
+// The forward-type kernel's tile for a launch shape (esize: bytes per stored element; groups: output phases x segments), its
+// rows, and its row blocks with BatchNorm partial sums of their own.
+ConvTile conv_choose_tile(int esize, int n_out, double rows_per_model, int n_models, int groups);
+ConvTile conv_tile_of_rows(int rows, int n_out);
+int conv_tile_rows(ConvTile t);
+int conv_stat_split(ConvTile t);
 
 }  // namespace gan

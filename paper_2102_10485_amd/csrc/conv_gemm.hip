@@ -21,8 +21,11 @@
 // R sits at position c ^ ((R / (256/KB)) % (KB/16)), which keeps both the 1 KiB-per-wave copies and the MFMA operand
 // reads conflict-free.
 // One barrier per chunk in both.
+#include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
+
+#include <algorithm>
 
 #include "common.h"
 #include <type_traits>
@@ -51,25 +54,69 @@ typedef Tile<256, 64, 4, 1, 128, 2> TileNarrow;  // 256 threads, wave tile 64 x 
 typedef Tile<64, 64, 2, 2, 64, 3> TileTiny;      // 256 threads, wave tile 32 x 32, 24 KiB of LDS: workloads so small that
                                                  // the larger tiles would leave most of the chip without a block
 
-int conv_tile_rows(int n_out, long long rows_per_model_hint, int n_models) {
-  // fewer than 128 tiles of 256 rows x 128 columns in a launch of one segment: the chip has 256 units to fill
-  if (rows_per_model_hint > 0 && n_models > 0) {
-    const long long tiles = n_models * ((rows_per_model_hint + 255) / 256) * ((n_out + 127) / 128);
-    if (tiles < 128) return TileTiny::BM;
+// What a tile is to the chooser: its shape, the blocks of it that a CU holds, and the rate a full chip of them reaches
+// against the fastest one of the storage type.
+struct TileInfo { ConvTile id; const char* name; int rows, cols, split, per_cu; double rate[2]; };   // rate: bf16, fp32
+static const TileInfo TILES[] = {
+    {TILE_BIG, "256x256", TileBig::BM, TileBig::BN, TileBig::WM, 1, {1.0, 0.95}},
+    {TILE_MID, "256x128", TileMid::BM, TileMid::BN, TileMid::WM, 2, {0.88, 0.95}},
+    {TILE_SMALL, "128x128", TileSmall::BM, TileSmall::BN, TileSmall::WM, 3, {0.75, 1.0}},
+    {TILE_NARROW, "256x64", TileNarrow::BM, TileNarrow::BN, TileNarrow::WM, 2, {0.70, 0.95}},
+    {TILE_TINY, "64x64", TileTiny::BM, TileTiny::BN, TileTiny::WM, 6, {0.43, 0.80}},
+};
+static const TileInfo& tile_info(ConvTile t) { return TILES[t]; }
+int conv_tile_rows(ConvTile t) { return tile_info(t).rows; }
+int conv_stat_split(ConvTile t) { return tile_info(t).split; }
+
+// The tile with the smallest estimated time for a launch of `groups` row spaces (phases x segments) of rows_per_model rows in
+// each of n_models models and n_out output columns: rounds of blocks over the chip's 256 CUs times a block's share of its
+// CU, at the tile's rate.  A last round that leaves CUs idle costs as much as a full one, which is what rules out large
+// tiles for small launches; blocks beyond the first round of their CU come in wherever one ends, so a partial round is
+// counted half a block longer than an even spread.
+ConvTile conv_choose_tile(int esize, int n_out, double rows_per_model, int n_models, int groups) {
+  const TileInfo* best = nullptr;
+  double best_t = 0;
+  for (const TileInfo& t : TILES) {
+    if (t.cols > 64 && n_out % t.cols != 0) continue;      // half-filled tiles
+    const double tiles = ceil(rows_per_model / t.rows) * n_models * groups * ((n_out + t.cols - 1) / t.cols);
+    const double per_round = 256.0 * t.per_cu, full = floor(tiles / per_round), rest = tiles - full * per_round;
+    double blocks = full * t.per_cu;                       // blocks one CU works through
+    if (rest > 0) blocks += std::min((double)t.per_cu, ceil(rest / 256.0) + (full > 0 ? 0.5 : 0.0));
+    const double time = blocks * t.rows * t.cols / t.rate[esize == 4 ? 1 : 0];
+    if (!best || time < best_t) { best = &t; best_t = time; }
   }
-  if (rows_per_model_hint > 0 && rows_per_model_hint <= 128) return TileSmall::BM;
-  return TileBig::BM;
+  return best->id;
+}
+// the tile of a given height (single-operation tests): with 256 rows the width follows the output channels
+ConvTile conv_tile_of_rows(int rows, int n_out) {
+  if (rows == TileTiny::BM) return TILE_TINY;
+  if (rows == TileSmall::BM) return TILE_SMALL;
+  return n_out <= TileNarrow::BN ? TILE_NARROW : (n_out % 256 == 0 ? TILE_BIG : TILE_MID);
 }
 
 __device__ inline void mma16B(floatx16& acc, const uint4& a, const uint4& b, bf16_t) {
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
 }
-__device__ inline void mma16B(floatx16& acc, const uint4& a, const uint4& b, float) {
-  // four k-pairs; lane half h supplies k = 4h + j to MFMA j, for A and B alike
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+// One K-step (16 bytes of every operand row) of a wave's TM x TN tiles.
+template <int TM, int TN>
+__device__ inline void mma_step(floatx16 (&acc)[TM][TN], const u32x4 (&a)[TM], const u32x4 (&b)[TN], bf16_t) {
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn) mma16B(acc[tm][tn], __builtin_bit_cast(uint4, a[tm]), __builtin_bit_cast(uint4, b[tn]), bf16_t());
+}
+// fp32: four k-pairs; lane half h supplies k = 4h + j to MFMA j, for A and B alike.  The pair is the outer loop, so that an
+// accumulator comes round only after all the others (one after the other, each MFMA waits for the one before it).
+template <int TM, int TN>
+__device__ inline void mma_step(floatx16 (&acc)[TM][TN], const u32x4 (&a)[TM], const u32x4 (&b)[TN], float) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn)
+        acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[tm][j]), __uint_as_float(b[tn][j]), acc[tm][tn], 0, 0, 0);
 }
 
 // One K-chunk of the forward-type kernel: rows KB bytes apart, the 16-byte chunk c of tile row R at position
@@ -80,7 +127,6 @@ __device__ inline int fwd_swz(int row) { return (row / (256 / KB)) % (KB / 16); 
 // The operand reads of the forward-type kernel are issued by hand so that the reads of K-step vs+1 are in flight
 // while the MFMAs of K-step vs run (two register sets).  The compiler does not count these reads, so the waits are
 // explicit; each wait names the registers it makes valid, which orders the MFMAs behind it.
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 template <int OFF>
 __device__ inline void lds_read16(u32x4& d, unsigned addr) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF) : "memory");
@@ -130,11 +176,7 @@ __device__ inline void tile_mma_fwd(floatx16 (&acc)[TM][TN], const unsigned char
     } else {
       lds_wait<0>(a[cur], b[cur]);
     }
-#pragma unroll
-    for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn)
-        mma16B(acc[tm][tn], __builtin_bit_cast(uint4, a[cur][tm]), __builtin_bit_cast(uint4, b[cur][tn]), T());
+    mma_step(acc, a[cur], b[cur], T());
     __builtin_amdgcn_sched_barrier(0);       // keep these MFMAs in front of the next K-step's wait
   });
 }
@@ -552,7 +594,6 @@ __global__ __launch_bounds__(TL::NT) void conv_gemm_kernel(ConvArgs p) {
 
 template <typename T, int MODE, int EPI, typename TL>
 static void launch_one(ConvArgs a, hipStream_t st) {
-  if (a.tile_rows != TL::BM) return launch_fail("GEMM: the tile prefix array was built for another tile height");
   a.hr_shift = log2_or_neg(a.Hr);
   const int NT = (a.N + TL::BN - 1) / TL::BN;
   const long long blocks = ((long long)a.ub_tiles * NT * a.nseg * (MODE == MODE_UP ? 4 : 1) + 7) / 8 * 8;
@@ -563,20 +604,13 @@ static void launch_one(ConvArgs a, hipStream_t st) {
 
 template <typename T, int MODE, int EPI>
 static void launch_wide(const ConvArgs& a, hipStream_t st) {
-  if (a.tile_rows == TileTiny::BM) return launch_one<T, MODE, EPI, TileTiny>(a, st);
-  if (a.tile_rows == TileSmall::BM) return launch_one<T, MODE, EPI, TileSmall>(a, st);
-  if (a.N <= TileNarrow::BN) return launch_one<T, MODE, EPI, TileNarrow>(a, st);
-  if (a.N % 256 == 0) return launch_one<T, MODE, EPI, TileBig>(a, st);
-  return launch_one<T, MODE, EPI, TileMid>(a, st);
-}
-
-// Row blocks per tile that leave their own BatchNorm partial sums (the WM of the tile launch_wide picks).
-int conv_stat_split(int n_out, int tile_rows) {
-  if (tile_rows == TileTiny::BM) return TileTiny::WM;
-  if (tile_rows == TileSmall::BM) return TileSmall::WM;
-  if (n_out <= TileNarrow::BN) return TileNarrow::WM;
-  if (n_out % 256 == 0) return TileBig::WM;
-  return TileMid::WM;
+  switch (a.tile) {
+    case TILE_BIG: return launch_one<T, MODE, EPI, TileBig>(a, st);
+    case TILE_MID: return launch_one<T, MODE, EPI, TileMid>(a, st);
+    case TILE_SMALL: return launch_one<T, MODE, EPI, TileSmall>(a, st);
+    case TILE_NARROW: return launch_one<T, MODE, EPI, TileNarrow>(a, st);
+    case TILE_TINY: return launch_one<T, MODE, EPI, TileTiny>(a, st);
+  }
 }
 
 // The (mode, epilogue, tile) combinations the networks use.
@@ -606,10 +640,8 @@ const char* conv_variant_name(int mode, int epi, const ConvArgs& a) {
   static const char* modes[3] = {"down", "up", "dense"};
   static const char* epis[3] = {"", "+actbwd", "+lrelu"};
   static char names[3][3][5][48];
-  const int tile = a.tile_rows == TileTiny::BM ? 4 : (a.tile_rows == TileSmall::BM ? 2 : (a.N <= TileNarrow::BN ? 3 : (a.N % 256 == 0 ? 0 : 1)));
-  static const char* tiles[5] = {"256x256", "256x128", "128x128", "256x64", "64x64"};
-  char* n = names[mode][epi][tile];
-  if (!n[0]) snprintf(n, 48, "gemm_%s%s<%s>", modes[mode], epis[epi], tiles[tile]);
+  char* n = names[mode][epi][a.tile];
+  if (!n[0]) snprintf(n, 48, "gemm_%s%s<%s>", modes[mode], epis[epi], tile_info(a.tile).name);
   return n;
 }
 template void launch_conv<float>(int, int, const ConvArgs&, hipStream_t);
@@ -818,34 +850,41 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
   const int fch = 2 * hb + ((s16 & 3) >> 1);                 // 16-byte chunk inside the 32-channel fragment (0..3)
   const int fbyte = 8 * (s16 & 1);
   const int swzA = wg_swz<T, RBA>(frow), swzB = wg_swz<T, RBB>(frow);   // frow % 4 (and (frow/2) % 2) do not change with kstep or half
+  // The reads of step ks + 1 are issued in front of the MFMAs of step ks (two register sets; the scheduling barriers keep
+  // the compiler from pulling them together, which left every step waiting for its own reads).
   auto mma_chunk16 = [&](int stage) {
     const unsigned char* As = smem + stage * STAGE_A;
     const unsigned char* Bs = smem + 2 * STAGE_A + stage * STAGE_B;
-#pragma unroll
-    for (int ks = 0; ks < WG_KR / 16; ++ks) {
-      uint4 a[TM], b[TN];
+    uint4 a[2][TM], b[2][TN];
+    auto fetch = [&](int ks, int set) {
 #pragma unroll
       for (int t = 0; t < TM; ++t) {
         const int ch = ((wm * TM + t) * 4 + fch) ^ swzA;
         const unsigned char* q0 = As + (ks * 16 + frow) * RBA + ch * 16 + fbyte;
         const uint2 lo = lds_read_tr16(q0), hi = lds_read_tr16(q0 + 4 * RBA);
-        a[t] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        a[set][t] = make_uint4(lo.x, lo.y, hi.x, hi.y);
       }
 #pragma unroll
       for (int t = 0; t < TN; ++t) {
         const int ch = ((wn * TN + t) * 4 + fch) ^ swzB;
         const unsigned char* q0 = Bs + (ks * 16 + frow) * RBB + ch * 16 + fbyte;
         const uint2 lo = lds_read_tr16(q0), hi = lds_read_tr16(q0 + 4 * RBB);
-        b[t] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        b[set][t] = make_uint4(lo.x, lo.y, hi.x, hi.y);
       }
+    };
+    fetch(0, 0);
+#pragma unroll
+    for (int ks = 0; ks < WG_KR / 16; ++ks) {
+      if (ks + 1 < WG_KR / 16) fetch(ks + 1, (ks + 1) & 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn) mma16B(acc[tm][tn], a[tm], b[tn], bf16_t());
+        for (int tn = 0; tn < TN; ++tn) mma16B(acc[tm][tn], a[ks & 1][tm], b[ks & 1][tn], bf16_t());
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
-
-  // fp32: K-step ks is rows 2 ks, 2 ks + 1 of the chunk; lane half h reads row 2 ks + h (swz flips with h only)
+  // fp32: a step is the row pairs 2 ks, 2 ks + 1 for two values of ks; lane half h reads row 2 ks + h (swz flips with h only)
   auto mma_chunk32 = [&](int stage) {
     const int r = lane & 31, h = lane >> 5;
     const unsigned char* As = smem + stage * STAGE_A + h * RBA + (r & 3) * 4;
@@ -856,17 +895,29 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
     for (int t = 0; t < TM; ++t) ap[t] = reinterpret_cast<const float*>(As + ((((wm * TM + t) * 8 + (r >> 2)) ^ (8 * h)) * 16));
 #pragma unroll
     for (int t = 0; t < TN; ++t) bp[t] = reinterpret_cast<const float*>(Bs + ((((wn * TN + t) * 8 + (r >> 2)) ^ (8 * h)) * 16));
+    float a[2][2][TM], b[2][2][TN];
+    auto fetch = [&](int step, int set) {
 #pragma unroll
-    for (int ks = 0; ks < WG_KR / 2; ++ks) {
-      float a[TM], b[TN];
+      for (int q = 0; q < 2; ++q) {
 #pragma unroll
-      for (int t = 0; t < TM; ++t) a[t] = ap[t][ks * 2 * BM];
+        for (int t = 0; t < TM; ++t) a[set][q][t] = ap[t][(2 * step + q) * 2 * BM];
 #pragma unroll
-      for (int t = 0; t < TN; ++t) b[t] = bp[t][ks * 2 * BN];
+        for (int t = 0; t < TN; ++t) b[set][q][t] = bp[t][(2 * step + q) * 2 * BN];
+      }
+    };
+    fetch(0, 0);
 #pragma unroll
-      for (int tm = 0; tm < TM; ++tm)
+    for (int st = 0; st < WG_KR / 4; ++st) {
+      if (st + 1 < WG_KR / 4) fetch(st + 1, (st + 1) & 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[tm], b[tn], acc[tm][tn], 0, 0, 0);
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+          for (int tn = 0; tn < TN; ++tn)
+            acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[st & 1][q][tm], b[st & 1][q][tn], acc[tm][tn], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
   auto mma_chunk = [&](int stage) {
@@ -971,13 +1022,17 @@ static void launch_wgrad_one(WgradArgs a, hipStream_t st) {
 }
 
 // Which tile a layer's weight gradient uses, as f(tile, name)
-template <typename F>
-static void with_wgrad_tile(int esize, int ntaps, int Cb, int Cs, F&& f) {
-  if (ntaps * Cb <= 64) { if (Cs <= 64) f(TileWgImg64(), "wgrad<64x64>"); else f(TileWgImg(), "wgrad<64x128>"); }
-  else if (esize == 4) { if (Cs <= 64) f(TileWgF32N(), "wgrad<128x64>"); else f(TileWgF32(), "wgrad<128x128>"); }
-  else if (Cs % 256 == 0) f(TileBig(), "wgrad<256x256>");
-  else if (Cs <= 64) f(TileWg64(), "wgrad<256x64>");
-  else f(TileMid(), "wgrad<256x128>");
+template <typename T, typename F>
+static void with_wgrad_tile(int ntaps, int Cb, int Cs, F&& f) {
+  if (ntaps * Cb <= 64) {
+    if (Cs <= 64) f(TileWgImg64(), "wgrad<64x64>"); else f(TileWgImg(), "wgrad<64x128>");
+  } else if constexpr (sizeof(T) == 4) {
+    if (Cs <= 64) f(TileWgF32N(), "wgrad<128x64>"); else f(TileWgF32(), "wgrad<128x128>");
+  } else {
+    if (Cs % 256 == 0) f(TileBig(), "wgrad<256x256>");
+    else if (Cs <= 64) f(TileWg64(), "wgrad<256x64>");
+    else f(TileMid(), "wgrad<256x128>");
+  }
 }
 
 template <typename T>
@@ -985,18 +1040,18 @@ void launch_wgrad(const WgradArgs& a, hipStream_t st) {
   if (!a.Big || !a.Small || !a.dW || !a.offs || a.Cb % 8 || a.Cs % 8 || (a.ntaps != 1 && a.ntaps != 16) || a.ksplit < 1 ||
       (a.ksplit > 1 && a.split_stride <= 0))
     return launch_fail("weight gradient: null operand, channel counts that are not multiples of 8, or a bad row split");
-  with_wgrad_tile((int)sizeof(T), a.ntaps, a.Cb, a.Cs, [&](auto tile, const char*) { launch_wgrad_one<T, decltype(tile)>(a, st); });
+  with_wgrad_tile<T>(a.ntaps, a.Cb, a.Cs, [&](auto tile, const char*) { launch_wgrad_one<T, decltype(tile)>(a, st); });
 }
 int wgrad_tiles_per_model(int esize, int ntaps, int Cb, int Cs) {
   int tiles = 0;
-  with_wgrad_tile(esize, ntaps, Cb, Cs, [&](auto tile, const char*) {
-    tiles = (ntaps * Cb + tile.BM - 1) / tile.BM * ((Cs + tile.BN - 1) / tile.BN);
-  });
+  const auto count = [&](auto tile, const char*) { tiles = (ntaps * Cb + tile.BM - 1) / tile.BM * ((Cs + tile.BN - 1) / tile.BN); };
+  if (esize == 4) with_wgrad_tile<float>(ntaps, Cb, Cs, count); else with_wgrad_tile<bf16_t>(ntaps, Cb, Cs, count);
   return tiles;
 }
 const char* wgrad_variant_name(int esize, const WgradArgs& a) {
   const char* name = "";
-  with_wgrad_tile(esize, a.ntaps, a.Cb, a.Cs, [&](auto, const char* n) { name = n; });
+  const auto take = [&](auto, const char* n) { name = n; };
+  if (esize == 4) with_wgrad_tile<float>(a.ntaps, a.Cb, a.Cs, take); else with_wgrad_tile<bf16_t>(a.ntaps, a.Cb, a.Cs, take);
   return name;
 }
 template void launch_wgrad<float>(const WgradArgs&, hipStream_t);

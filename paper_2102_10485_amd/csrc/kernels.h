@@ -7,7 +7,7 @@
 namespace gan {
 
 constexpr int ROUTE_CHUNKS = 256;   // sequential chunks of the flat batch, one thread each
-constexpr int MAX_GEOMS = 32;
+constexpr int MAX_GEOMS = 60;
 
 // One "geometry" = how rows of a layer split into tiles: rows per sample and rows per tile.
 struct GeomTable {
