@@ -196,18 +196,16 @@ __device__ inline int4v make_rsrc(const void* base, unsigned long long bytes) {
   r.w = 0x00020000;
   return r;
 }
-__device__ inline void load16_to_lds(const int4v& rsrc, unsigned byte_off, unsigned lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-               : : "v"(byte_off), "s"(rsrc), "s"(lds_base) : "memory", "m0");
+// The wave-uniform part of the offset (which tap, which channels) travels in a scalar register.
+__device__ inline void load16_to_lds(const int4v& rsrc, unsigned byte_off, unsigned uniform_off, unsigned lds_base) {
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               : : "v"(byte_off), "s"(rsrc), "s"(uniform_off), "s"(lds_base) : "memory", "m0");
 }
-__device__ inline void wait_vm0() { asm volatile("s_waitcnt vmcnt(0)" : : : "memory"); }
-// wait until at most `chunks` (wave-uniform; 2 or more counts as 2) groups of LPT loads are still in flight
-template <int LPT>
-__device__ inline void wait_vm_chunks(int chunks) {
-  static_assert(2 * LPT <= 63, "vmcnt range");
-  if (chunks >= 2) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * LPT) : "memory");
-  else if (chunks == 1) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(LPT) : "memory");
-  else asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+// wait until at most N loads are still in flight
+template <int N>
+__device__ inline void wait_vm() {
+  static_assert(N <= 63, "vmcnt range");
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
 __device__ inline void store_out(float* p, float v) { *p = v; }
@@ -259,7 +257,6 @@ __global__ __launch_bounds__(TL::NT) void conv_gemm_kernel(ConvArgs p) {
   unsigned char* const Bs = smem + NST * BM * KB;      // buffer s at Bs + s * BN * KB
   constexpr int BK = KB / (int)sizeof(T);              // elements of K per chunk
   constexpr int LINES = 128 / KB;                      // chunks per 128-byte line
-  constexpr int LINES_ = LINES;
   constexpr int EPV = 16 / (int)sizeof(T);
   constexpr int LPT = PA + PB;                         // loads per thread per chunk
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -324,7 +321,7 @@ __global__ __launch_bounds__(TL::NT) void conv_gemm_kernel(ConvArgs p) {
       if (py == 1 && bottom_only) { cnt_lo = 2; first_gone = true; }   // a = 0 (row y + 1) is gone
     }
   }
-  const int chunks_per_tap = cpl * LINES_;
+  const int chunks_per_tap = cpl * LINES;
   const int nk = (MODE == MODE_DOWN) ? 2 * (cnt_lo + cnt_hi) * chunks_per_tap
                                      : (MODE == MODE_UP ? cnt_lo * chunks_per_tap : C / BK);
   const int wns = p.w_nstride;   // rows per tap in the weight block (N, or more when only some rows are used)
@@ -332,46 +329,54 @@ __global__ __launch_bounds__(TL::NT) void conv_gemm_kernel(ConvArgs p) {
   const int nsamp = s1 - s0;
   const long long a_elems = (MODE == MODE_DENSE) ? (long long)nsamp * rps * C : (long long)nsamp * Hin * Hin * C;
   const T* a_base = static_cast<const T*>(p.A) + ((MODE == MODE_DENSE) ? sample_base * rps * C : sample_base * (long long)(Hin * Hin) * C);
-  const int4v a_rsrc = make_rsrc(a_base, (unsigned long long)a_elems * SZ);
+  // A tap's pixel offset can be negative: the gathered tensor's buffer starts `bias` bytes in front of the slice, and the
+  // offsets carry `bias` more (down: in the rows' part, which starts at pixel (-1, -1); up: in the taps' part).  No lane
+  // reads in front of the slice: those taps are masked.
+  const unsigned px_bytes = (unsigned)(C * SZ), row_bytes = (unsigned)(Hin * C * SZ), wtap_bytes = (unsigned)(wns * C * SZ);
+  const unsigned bias = (MODE == MODE_DENSE) ? 0u : row_bytes + px_bytes;
+  const int4v a_rsrc = make_rsrc(reinterpret_cast<const unsigned char*>(a_base) - bias, (unsigned long long)a_elems * SZ + bias);
   const int4v w_rsrc = make_rsrc(static_cast<const T*>(p.W) + (long long)l * p.w_stride,
                                  (unsigned long long)(MODE == MODE_DENSE ? 1 : 16) * wns * C * SZ);
 
   // ---- per-thread load assignment: rows tid/CPR + RPP i, LDS position tid % CPR of the row, which holds the row's
   // 16-byte chunk (tid % CPR) ^ swizzle(row) (RPP is a multiple of the swizzle period, so the same chunk in every
-  // pass).  Per row: byte offset of its pixel at tap offset (0, 0) and the set of taps that stay inside the map.
+  // pass).  Per row: byte offset of its pixel at tap offset (0, 0), and the set of taps that fall outside the map (all of
+  // them for a row past the model's end): a bit turned into a mask and or-ed into the offset sends the lane out of the
+  // buffer, so a load costs two vector instructions, one for the weights.
   constexpr int CPR = TL::CPR;
   const int row0 = tid / CPR;
   const int chunk = (tid % CPR) ^ fwd_swz<KB>(row0);
-  unsigned apix[PA], amask[PA], bcol[PB];
+  unsigned apix[PA], bcol[PB];
+  int outside[PA];
 #pragma unroll
   for (int i = 0; i < PA; ++i) {
     const int r = m0 + row0 + RPP * i;
     apix[i] = 0;
-    amask[i] = 0;
+    outside[i] = -1;
     if (r < Mrows) {
       if (MODE == MODE_DENSE) {
         apix[i] = (unsigned)((r * C + chunk * EPV) * SZ);
-        amask[i] = 1;
+        outside[i] = 0;
       } else {
         int n, y, x;
         decode_row_yfirst(r, Hr, row_block, p.hr_shift, n, y, x);
-        const int by = (MODE == MODE_DOWN) ? 2 * y - 1 : y, bx = (MODE == MODE_DOWN) ? 2 * x - 1 : x;
-        apix[i] = (unsigned)((((n * Hin + by) * Hin + bx) * C + chunk * EPV) * SZ);     // may wrap below zero: masked
-        if (MODE == MODE_DOWN) {             // tap (ky, kx) is inside iff row by + ky and column bx + kx are: separable
-          unsigned xm = 0;
+        const int by = (MODE == MODE_DOWN) ? 2 * y : y, bx = (MODE == MODE_DOWN) ? 2 * x : x;      // (down: + 1)
+        apix[i] = (unsigned)((((n * Hin + by) * Hin + bx) * C + chunk * EPV) * SZ);
+        int inside = 0;
+        if (MODE == MODE_DOWN) {             // tap (ky, kx) is inside iff row by - 1 + ky and column bx - 1 + kx are: separable
+          int xm = 0;
 #pragma unroll
-          for (int k = 0; k < 4; ++k) xm |= ((unsigned)(bx + k) < (unsigned)Hin ? 1u : 0u) << k;
+          for (int k = 0; k < 4; ++k) xm |= ((unsigned)(bx - 1 + k) < (unsigned)Hin ? 1 : 0) << k;
 #pragma unroll
           for (int k = 0; k < 4; ++k)
-            if ((unsigned)(by + k) < (unsigned)Hin) amask[i] |= xm << (4 * k);
+            if ((unsigned)(by - 1 + k) < (unsigned)Hin) inside |= xm << (4 * k);
         } else {
           for (int t = 0; t < 4; ++t) {
-            const int dy = py == 0 ? ((t >> 1) == 0 ? 0 : -1) : ((t >> 1) == 0 ? 1 : 0);
-            const int dx = px == 0 ? ((t & 1) == 0 ? 0 : -1) : ((t & 1) == 0 ? 1 : 0);
-            const int iy = by + dy, ix = bx + dx;
-            if ((unsigned)iy < (unsigned)Hin && (unsigned)ix < (unsigned)Hin) amask[i] |= 1u << t;
+            const int iy = by + py - (t >> 1), ix = bx + px - (t & 1);
+            if ((unsigned)iy < (unsigned)Hin && (unsigned)ix < (unsigned)Hin) inside |= 1 << t;
           }
         }
+        outside[i] = ~inside;
       }
     }
   }
@@ -382,65 +387,57 @@ __global__ __launch_bounds__(TL::NT) void conv_gemm_kernel(ConvArgs p) {
   }
 
   const unsigned lds0 = (unsigned)(uintptr_t)smem;     // LDS byte address of the buffers
-  // K-chunk kc -> which tap it gathers and the wave-uniform byte offsets it adds to a row's base offsets.
+  // The next K-chunk to load: which tap it gathers and the wave-uniform byte offsets it adds to the rows' and columns'.
   // K order, fastest first: the chunks of one 128-byte line; the taps whose gathers land on the same input pixels
   // shifted by one (down: the 4 taps of a (ky%2, kx%2) class, up: the phase's 4 taps), which find their rows in
-  // L2; the channel line; (down) the class.
-  auto chunk_offsets = [&](int kc, int& tap, unsigned& a_delta, unsigned& w_delta) {
-    int cc;
+  // L2; the channel line; (down) the class.  Carried along chunk by chunk: decoding the chunk's number took 90 scalar
+  // instructions a chunk, more issue time than the 8 MFMAs per wave of a 64-byte chunk.
+  // down: classes 0, 1 hold the taps with ky in {0, 2}, classes 2, 3 those with ky in {1, 3}; a class keeps cnt taps, and the
+  // two left in a class of two are its kx pair at the one valid ky: ky = 2 (top tile, even class) or 1 (bottom, odd).
+  int k_part = 0, k_j = 0, k_line = 0, k_cls = 0, k_cnt = MODE == MODE_DENSE ? 1 : cnt_lo, k_tap = 0;
+  unsigned k_aoff = 0, k_woff = 0;
+  auto k_set = [&]() {
     if (MODE == MODE_DOWN) {
-      // classes 0, 1 hold the taps with ky in {0, 2}, classes 2, 3 those with ky in {1, 3}; a class keeps cnt taps
-      const int per_lo = cnt_lo * chunks_per_tap;                 // chunks of one class with ky even
-      int cls, rest;
-      if (kc < 2 * per_lo) { cls = kc >= per_lo ? 1 : 0; rest = kc - cls * per_lo; }
-      else { const int k2 = kc - 2 * per_lo, per_hi = cnt_hi * chunks_per_tap; cls = k2 >= per_hi ? 3 : 2; rest = k2 - (cls - 2) * per_hi; }
-      const int cnt = cls < 2 ? cnt_lo : cnt_hi;
-      const int part = rest % LINES, jr = rest / LINES;
-      const int j = cnt == 4 ? (jr & 3) : (jr & 1);
-      const int line = cnt == 4 ? (jr >> 2) : (jr >> 1);
-      // the two taps left in a class of two are its kx pair at the one valid ky: ky = 2 (top tile, even class) or
-      // ky = 1 (bottom tile, odd class)
-      const int j4 = cnt == 4 ? j : j + ((cls < 2) ? 2 : 0);
-      cc = line * LINES + part;
-      tap = (((cls >> 1) + 2 * (j4 >> 1)) << 2) + (cls & 1) + 2 * (j4 & 1);
+      const int j = k_cnt == 4 ? k_j : k_j + (k_cls < 2 ? 2 : 0);
+      const int ky = (k_cls >> 1) + 2 * (j >> 1), kx = (k_cls & 1) + 2 * (j & 1);
+      k_tap = ky * 4 + kx;
+      k_aoff = ky * row_bytes + kx * px_bytes + k_line * 128;
+      k_woff = k_tap * wtap_bytes + k_line * 128;
     } else if (MODE == MODE_UP) {
-      const int part = kc % LINES, jr = kc / LINES;
-      const int j = cnt_lo == 4 ? (jr & 3) : (jr & 1);
-      const int line = cnt_lo == 4 ? (jr >> 2) : (jr >> 1);
-      cc = line * LINES + part;
-      tap = cnt_lo == 4 ? j : j + (first_gone ? 2 : 0);
+      // phase py = 0 gathers rows y and y - 1 through ky = 1 and 3, py = 1 rows y + 1 and y through ky = 0 and 2; likewise x
+      k_tap = k_cnt == 4 ? k_j : k_j + (first_gone ? 2 : 0);
+      const int a = k_tap >> 1, b = k_tap & 1;
+      k_aoff = (py - a + 1) * row_bytes + (px - b + 1) * px_bytes + k_line * 128;
+      k_woff = ((2 * a + 1 - py) * 4 + 2 * b + 1 - px) * wtap_bytes + k_line * 128;
     } else {
-      cc = kc;
-      tap = 0;
+      k_aoff = k_woff = k_line * 128;
     }
-    int dy, dx, wtap;
-    if (MODE == MODE_DOWN) {
-      dy = tap >> 2; dx = tap & 3; wtap = tap;
-    } else if (MODE == MODE_UP) {
-      const int a = tap >> 1, b = tap & 1;
-      dy = py == 0 ? (a == 0 ? 0 : -1) : (a == 0 ? 1 : 0);
-      dx = px == 0 ? (b == 0 ? 0 : -1) : (b == 0 ? 1 : 0);
-      const int ky = py == 0 ? (a == 0 ? 1 : 3) : (a == 0 ? 0 : 2);
-      const int kx = px == 0 ? (b == 0 ? 1 : 3) : (b == 0 ? 0 : 2);
-      wtap = ky * 4 + kx;
-    } else {
-      dy = 0; dx = 0; wtap = 0;
-    }
-    a_delta = (unsigned)(((dy * Hin + dx) * C + cc * BK) * SZ);    // wave-uniform
-    w_delta = (unsigned)((wtap * wns * C + cc * BK) * SZ);
   };
-  auto load_chunk = [&](int kc, int stage) {
-    int tap;
-    unsigned a_delta, w_delta;
-    chunk_offsets(kc, tap, a_delta, w_delta);
+  auto k_advance = [&]() {
+    if (LINES == 2) {
+      k_part ^= 1;
+      if (k_part) { k_aoff += KB; k_woff += KB; return; }
+    }
+    if (++k_j == k_cnt) {
+      k_j = 0;
+      if (++k_line == cpl && MODE == MODE_DOWN) {
+        k_line = 0;
+        ++k_cls;
+        k_cnt = k_cls < 2 ? cnt_lo : cnt_hi;
+      }
+    }
+    k_set();
+  };
+  k_set();
+  auto load_chunk = [&](int stage) {                   // the next chunk, into a buffer
     const unsigned a_dst = lds0 + (stage * BM + wave * (1024 / KB)) * KB;        // + pass * RPP rows
     const unsigned b_dst = lds0 + (NST * BM + stage * BN + wave * (1024 / KB)) * KB;
 #pragma unroll
     for (int i = 0; i < PA; ++i)
-      load16_to_lds(a_rsrc, ((amask[i] >> tap) & 1u) ? apix[i] + a_delta : NO_ROW, a_dst + i * RPP * KB);
+      load16_to_lds(a_rsrc, apix[i] | (unsigned)__builtin_amdgcn_sbfe(outside[i], k_tap, 1), k_aoff, a_dst + i * RPP * KB);
 #pragma unroll
-    for (int i = 0; i < PB; ++i)
-      load16_to_lds(w_rsrc, bcol[i] != NO_ROW ? bcol[i] + w_delta : NO_ROW, b_dst + i * RPP * KB);
+    for (int i = 0; i < PB; ++i) load16_to_lds(w_rsrc, bcol[i], k_woff, b_dst + i * RPP * KB);
+    k_advance();
   };
   floatx16 acc[TM][TN];
 #pragma unroll
@@ -453,13 +450,19 @@ __global__ __launch_bounds__(TL::NT) void conv_gemm_kernel(ConvArgs p) {
   // Ring of NST buffers: chunk c lives in buffer c % NST.  While chunk c is multiplied, chunks c+1 .. c+NST-1 are on
   // their way; the barrier that ends iteration c tells every wave that chunk c+1 has landed everywhere and that
   // buffer c % NST may be refilled (with chunk c+NST, by the next iteration).
-  for (int c = 0; c < NST - 1 && c < nk; ++c) load_chunk(c, c);
-  wait_vm_chunks<LPT>(min(nk, NST - 1) - 1);
+  int st_load = 0, st = 0;                             // buffers of the next chunk to load and of the current one
+  for (int c = 0; c < NST - 1 && c < nk; ++c) load_chunk(st_load++);
+  wait_vm<0>();
   __syncthreads();
   for (int kc = 0; kc < nk; ++kc) {
-    if (kc + NST - 1 < nk) load_chunk(kc + NST - 1, (kc + NST - 1) % NST);
-    tile_mma_fwd<T, TM, TN, KB>(acc, As + (kc % NST) * BM * KB, Bs + (kc % NST) * BN * KB, wm, wn, lane);
-    wait_vm_chunks<LPT>(min(nk - 1, kc + NST - 1) - (kc + 1));     // chunks after kc+1 may stay in flight
+    const bool more = kc + NST - 1 < nk;
+    if (more) {
+      load_chunk(st_load);
+      st_load = st_load == NST - 1 ? 0 : st_load + 1;
+    }
+    tile_mma_fwd<T, TM, TN, KB>(acc, As + st * BM * KB, Bs + st * BN * KB, wm, wn, lane);
+    st = st == NST - 1 ? 0 : st + 1;
+    if (more) wait_vm<(NST - 2) * LPT>(); else wait_vm<0>();       // chunk kc + 1 has landed; those behind it may stay in flight
     __syncthreads();
   }
 
@@ -807,7 +810,7 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
 #pragma unroll
       for (int i = 0; i < PA; ++i) {
         const bool ok = rowA0 + i * RPA < left && (unsigned)(fa_iy[i] + y2) < (unsigned)Hb;
-        load16_to_lds(a_rsrc, ok ? fa_off[i] + a_delta : NO_ROW, a_dst + i * NT_ * 16);
+        load16_to_lds(a_rsrc, ok ? fa_off[i] + a_delta : NO_ROW, 0u, a_dst + i * NT_ * 16);
       }
     } else {
 #pragma unroll
@@ -827,12 +830,12 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
           const int iy = 2 * y - 1 + kyA, ix = 2 * x - 1 + kxA;
           if ((unsigned)iy < (unsigned)Hb && (unsigned)ix < (unsigned)Hb) off = (unsigned)((((n * Hb + iy) * Hb + ix) * Cb + cA) * SZ);
         }
-        load16_to_lds(a_rsrc, off, a_dst + i * NT_ * 16);
+        load16_to_lds(a_rsrc, off, 0u, a_dst + i * NT_ * 16);
       }
     }
 #pragma unroll
     for (int i = 0; i < PB; ++i)
-      load16_to_lds(b_rsrc, (rowB0 + i * RPB < left && okB) ? fb_off[i] + b_delta : NO_ROW, b_dst + i * NT_ * 16);
+      load16_to_lds(b_rsrc, (rowB0 + i * RPB < left && okB) ? fb_off[i] + b_delta : NO_ROW, 0u, b_dst + i * NT_ * 16);
   };
 
   floatx16 acc[TM][TN];
@@ -939,7 +942,7 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
   auto chunk_row = [&](int cin) { return r_lo + (cin < bad0 ? cin : cin + nbad) * WG_KR; };
   if (nchunks > 0) {
     load_chunk(0, chunk_row(0), 0);
-    wait_vm0();
+    wait_vm<0>();
     __syncthreads();
     int seg = 0, cin = 0;
     for (int c = 0; c < nchunks; ++c) {
@@ -948,7 +951,7 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
         load_chunk(seg, chunk_row(cin), (c + 1) & 1);
       }
       mma_chunk(c & 1);
-      wait_vm0();
+      wait_vm<0>();
       __syncthreads();
     }
   }
