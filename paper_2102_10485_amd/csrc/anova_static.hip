@@ -1,5 +1,5 @@
 // gan_anova_f_static: the per-channel analysis of variance for callers that cannot allocate device memory.  The
-// intermediate results of its three kernels (per-image channel means, per-label sums, counts and squared deviations)
+// intermediate results of its two kernels (per-image channel means, per-label sums, counts and squared deviations)
 // live in one file-scope device array instead of buffers obtained from hipMalloc; every device the library runs
 // on holds its own copy of that array until the process ends.
 #include "../../include/gan.h"
@@ -17,10 +17,10 @@ constexpr int MAX_N = GAN_ANOVA_STATIC_MAX_IMAGES;
 constexpr int MAX_K = GAN_ANOVA_STATIC_MAX_LABELS;
 constexpr int MAX_C = 4;
 constexpr size_t OFF_X = 0;                                                     // double [MAX_N][MAX_C]
-constexpr size_t OFF_GSUM = OFF_X + (size_t)MAX_N * MAX_C * sizeof(double);      // double [MAX_K][MAX_C]
-constexpr size_t OFF_SSW = OFF_GSUM + (size_t)MAX_K * MAX_C * sizeof(double);    // double [MAX_K][MAX_C]
-constexpr size_t OFF_GCNT = OFF_SSW + (size_t)MAX_K * MAX_C * sizeof(double);    // int    [MAX_K]
-constexpr size_t SCRATCH_BYTES = OFF_GCNT + (size_t)MAX_K * sizeof(int);
+// results, packed for a call's K labels and C channels so that one copy fetches them: gsum, ssw double [K][C], gcnt int [K]
+constexpr size_t OFF_RES = OFF_X + (size_t)MAX_N * MAX_C * sizeof(double);
+constexpr size_t MAX_RES = (size_t)MAX_K * (2 * MAX_C * sizeof(double) + sizeof(int));
+constexpr size_t SCRATCH_BYTES = OFF_RES + MAX_RES;
 
 // In host code this name is only a handle for hipGetSymbolAddress, never an address to hand to a kernel.
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
@@ -72,21 +72,15 @@ gan_status gan_anova_f_static(const int32_t* label_ids, const float* images, int
   if (s != GAN_OK) return s;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   double* x = reinterpret_cast<double*>(base + OFF_X);
-  double* gsum = reinterpret_cast<double*>(base + OFF_GSUM);
-  double* ssw = reinterpret_cast<double*>(base + OFF_SSW);
-  int* gcnt = reinterpret_cast<int*>(base + OFF_GCNT);
-  // the three kernels write every element they later read (x[0, n*C), gsum / ssw [0, K*C), gcnt [0, K)), so nothing
+  const size_t kc = (size_t)n_labels * img_c, res_bytes = 2 * kc * sizeof(double) + (size_t)n_labels * sizeof(int);
+  double* gsum = reinterpret_cast<double*>(base + OFF_RES);
+  // the two kernels write every element they later read (x[0, n*C), gsum / ssw [0, K*C), gcnt [0, K)), so nothing
   // left by an earlier call has to be cleared
-  launch_anova(label_ids, images, n, n_labels, img_c, img_hw * img_hw, x, gsum, gcnt, ssw, st);
-  static thread_local double h_gsum[MAX_K * MAX_C], h_ssw[MAX_K * MAX_C];
-  static thread_local int h_gcnt[MAX_K];
-  const size_t kc = (size_t)n_labels * img_c;
-  if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess ||
-      hipMemcpy(h_gsum, gsum, kc * sizeof(double), hipMemcpyDeviceToHost) != hipSuccess ||
-      hipMemcpy(h_ssw, ssw, kc * sizeof(double), hipMemcpyDeviceToHost) != hipSuccess ||
-      hipMemcpy(h_gcnt, gcnt, (size_t)n_labels * sizeof(int), hipMemcpyDeviceToHost) != hipSuccess)
+  launch_anova(label_ids, images, n, n_labels, img_c, img_hw * img_hw, x, gsum, gsum + kc, reinterpret_cast<int*>(gsum + 2 * kc), st);
+  static thread_local double h_res[MAX_RES / sizeof(double)];
+  if (hipGetLastError() != hipSuccess || hipMemcpyWithStream(h_res, gsum, res_bytes, hipMemcpyDeviceToHost, st) != hipSuccess)
     return static_fail(GAN_E_HIP, "analysis of variance failed on the device");
-  if (!anova_f_from_sums(h_gsum, h_ssw, h_gcnt, n_labels, img_c, F))
+  if (!anova_f_from_sums(h_res, h_res + kc, reinterpret_cast<const int*>(h_res + 2 * kc), n_labels, img_c, F))
     return static_fail(GAN_E_STATE, "fewer than two labels present, or not more images than labels");
   return GAN_OK;
 }

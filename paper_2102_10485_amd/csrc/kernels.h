@@ -212,8 +212,9 @@ void launch_draw_labels(const float* u, const double* cdf, int n_labels, int las
 //   x[i][c]    = mean over the pixels of channel c of image i (images: NCHW fp32)
 //   gsum[k][c] = sum of x over the images of label k, gcnt[k] = their number
 //   ssw[k][c]  = sum over the images of label k of (x - gsum/gcnt)^2
+// (gsum, ssw and gcnt may be pinned host memory: the kernels only write them)
 void launch_anova(const int* label_ids, const float* images, int n, int n_labels, int C, int HW, double* x, double* gsum,
-                  int* gcnt, double* ssw, hipStream_t st);
+                  double* ssw, int* gcnt, hipStream_t st);
 
 // ---- pieces of the networks as printed in the paper's Tables 1 and 2 (paper_layers.hip) ----
 // In-place dropout of an NHWC tensor whose samples are grouped by model (offs[g] .. offs[g+1]): the keep-mask comes

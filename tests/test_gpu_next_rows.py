@@ -132,3 +132,20 @@ def test_anova_f_edge_cases():
     assert st == 0
     np.testing.assert_allclose(F4, [13.0] * C_, rtol=1e-12)
     gan.close()
+
+
+@pytest.mark.parametrize("hw,n", [(28, 37), (30, 10), (4, 70)])
+def test_anova_f_odd_sizes_and_unaligned_images(hw, n):
+    """Images whose pixel count is no multiple of the 256 floats one trip takes (or of 4), and a buffer off 16-byte alignment."""
+    torch = U.torch_mod()
+    rng = np.random.default_rng(hw + n)
+    lab = rng.integers(0, 5, n).astype(np.int32)
+    img = np.tanh(rng.normal(size=(n, 3, hw, hw)) + 0.3 * lab[:, None, None, None]).astype(np.float32)
+    rc, ref = O.anova_f(lab, img, 5)
+    dl = torch.from_numpy(lab).cuda()
+    for shift in (0, 1):
+        buf = torch.zeros(img.size + shift, dtype=torch.float32, device="cuda")
+        buf[shift:] = torch.from_numpy(img.reshape(-1)).cuda()
+        st, F = binding.anova_f_static(dl.data_ptr(), buf.data_ptr() + 4 * shift, n, 5, 3, hw, torch.cuda.current_stream().cuda_stream)
+        assert rc == 0 and st == binding.GAN_OK
+        np.testing.assert_allclose(F, ref, rtol=1e-9)
