@@ -12,7 +12,8 @@ import time
 
 import numpy as np
 
-PEAK = {"mfma_bf16": 2500.0, "mfma_fp32": 157.3, "hbm": 8000.0}   # TFLOP/s, TFLOP/s, GB/s (published MI355X figures)
+# TFLOP/s, TFLOP/s, GB/s (published MI355X figures; an fp32 product is six bf16 MFMAs)
+PEAK = {"mfma_bf16": 2500.0, "mfma_fp32": 2500.0 / 6, "hbm": 8000.0}
 
 # HBM bytes per launch from hardware counters (rocprofv3 --pmc FETCH_SIZE, then WRITE_SIZE, KiB per dispatch, averaged over the
 # launches of a kernel instantiation in `bench.py --steps 3 --warmup 1 --no-profile --copy-probe`, config 2 bf16), scaled by what

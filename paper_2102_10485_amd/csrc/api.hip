@@ -563,7 +563,7 @@ void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, c
   ConvArgs a = {};
   a.A = A; a.W = W; a.Out = Out; a.Aux = Aux; a.w_nstride = w_nstride ? w_nstride : N;
   a.tile = layer_tile(c, mode, N, Hr * Hr, nseg);
-  const int tr = conv_tile_rows(a.tile);
+  const int tr = conv_tile_rows((int)sizeof(T), a.tile);
   a.offs = c->rb.offs; a.tpre = tpre_of(c, Hr * Hr, tr); a.tmodel = tmodel_of(c, Hr * Hr, tr);
   a.w_stride = wstride; a.L = c->L; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n;
   a.C = C; a.N = N; a.Hin = Hin; a.Hr = Hr; a.ub_tiles = ub_tiles(c, n, Hr * Hr, tr);
@@ -591,7 +591,7 @@ void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, c
 int wgrad_ksplit(const gan_ctx* c, int Cb, int Cs, int ntaps, int Hs, int nseg) {
   const double blocks = (double)c->L * wgrad_tiles_per_model((int)esize(c), ntaps, Cb, Cs);
   const double rows = (double)c->NB * nseg * Hs * Hs, out = (double)c->L * ntaps * Cb * Cs * 4;
-  const double product = 2.0 * rows * ntaps * Cb * Cs / (c->bf16 ? 900e12 : 140e12);
+  const double product = 2.0 * rows * ntaps * Cb * Cs / (c->bf16 ? 900e12 : 150e12);
   const double chunk_rows = 128 / (double)esize(c);
   int best = 1;
   double best_t = 0;
@@ -662,10 +662,10 @@ void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool use_running
     launch_bn_from_running(a, c->st);
   } else {
     const ConvTile tile = layer_tile(c, gemm_mode, a.C * col_groups, gemm_rps, a.nseg);   // of the GEMM that left the partials (N = C * col_groups)
-    const int tr = conv_tile_rows(tile), gemm_phases = gemm_mode == MODE_UP ? 4 : 1;
+    const int tr = conv_tile_rows((int)sizeof(T), tile), gemm_phases = gemm_mode == MODE_UP ? 4 : 1;
     a.fold_running = update_running && a.nseg == 1 && a.run_mean && a.run_var;
     launch_bn_stats_from_partial(a, c->stat_partial, tpre_of(c, gemm_rps, tr), ub_tiles(c, a.n, gemm_rps, tr), gemm_phases, col_groups, tr,
-                                 gemm_rps, conv_stat_split(tile), c->st);
+                                 gemm_rps, conv_stat_split((int)sizeof(T), tile), c->st);
     if (update_running && !a.fold_running) launch_bn_running(a, c->st);
   }
   Scope s(c, "bn_apply", 0, 2 * elems * sizeof(T));
@@ -1266,7 +1266,7 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
   // geometries used by any launch: (rows per sample, tile height) of every GEMM's row space
   {
     auto reg = [&](int rps, int tile_rows) { if (geom_id(c, rps, tile_rows) < 0) ok = false; };
-    auto reg_gemm = [&](int mode, int n_out, int rps, int nseg) { reg(rps, conv_tile_rows(layer_tile(c, mode, n_out, rps, nseg))); };
+    auto reg_gemm = [&](int mode, int n_out, int rps, int nseg) { reg(rps, conv_tile_rows((int)es, layer_tile(c, mode, n_out, rps, nseg))); };
     const ConvLayer& gl = c->G.conv.back();
     const ConvLayer& d1 = c->D.conv.front();
     reg_gemm(MODE_DENSE, c->G.J, 1, 1);                                         // G's linear layer
@@ -1339,16 +1339,16 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
   }
   {
     // column sums left by the GEMM in front of every BatchNorm: phases x segments x tiles x sub-tiles (at most 4) x columns x 2
-    size_t mx = (size_t)4 * ub_tiles(c, NB, 1, conv_tile_rows(layer_tile(c, MODE_DENSE, c->G.J, 1, 1))) * c->G.J;
+    size_t mx = (size_t)4 * ub_tiles(c, NB, 1, conv_tile_rows((int)es, layer_tile(c, MODE_DENSE, c->G.J, 1, 1))) * c->G.J;
     for (size_t i = 0; i + 1 < c->G.conv.size(); ++i) {
       const ConvLayer& cl = c->G.conv[i];
-      const size_t v = (size_t)4 * 4 * ub_tiles(c, NB, cl.Hs * cl.Hs, conv_tile_rows(layer_tile(c, MODE_UP, cl.Cb, cl.Hs * cl.Hs, 1))) * cl.Cb;
+      const size_t v = (size_t)4 * 4 * ub_tiles(c, NB, cl.Hs * cl.Hs, conv_tile_rows((int)es, layer_tile(c, MODE_UP, cl.Cb, cl.Hs * cl.Hs, 1))) * cl.Cb;
       mx = v > mx ? v : mx;
     }
     for (size_t j = 1; j < c->D.conv.size(); ++j) {
       const ConvLayer& cl = c->D.conv[j];
       for (int nseg = 1; nseg <= 2; ++nseg) {
-        const size_t v = (size_t)4 * nseg * ub_tiles(c, NB, cl.Hs * cl.Hs, conv_tile_rows(layer_tile(c, MODE_DOWN, cl.Cs, cl.Hs * cl.Hs, nseg))) * cl.Cs;
+        const size_t v = (size_t)4 * nseg * ub_tiles(c, NB, cl.Hs * cl.Hs, conv_tile_rows((int)es, layer_tile(c, MODE_DOWN, cl.Cs, cl.Hs * cl.Hs, nseg))) * cl.Cs;
         mx = v > mx ? v : mx;
       }
     }
@@ -1892,9 +1892,9 @@ static gan_status op_conv(gan_ctx* c, int mode, const void* A, const void* W, vo
     return fail(c, GAN_E_SHAPE, "an operand of 2 GiB or more (the kernels use 32-bit byte offsets)");
   (void)take_launch_error();
   int* tp = nullptr;
-  const ConvTile tile = c->op_tile_rows ? conv_tile_of_rows(c->op_tile_rows, N)
+  const ConvTile tile = c->op_tile_rows ? conv_tile_of_rows((int)esize(c), c->op_tile_rows, N)
                                         : conv_choose_tile((int)esize(c), N, (double)n_samples * Hr * Hr / n_groups, n_groups, mode == MODE_UP ? 4 : 1);
-  const int tr = conv_tile_rows(tile);
+  const int tr = conv_tile_rows((int)esize(c), tile);
   gan_status s = op_common(c, offs, n_groups, Hr * Hr, tr, &tp);
   if (s != GAN_OK) return s;
   ConvArgs a = {};

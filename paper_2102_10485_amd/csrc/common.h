@@ -116,8 +116,8 @@ int wgrad_tiles_per_model(int esize, int ntaps, int Cb, int Cs);
 // The forward-type kernel's tile for a launch shape (esize: bytes per stored element; groups: output phases x segments), its
 // rows, and its row blocks with BatchNorm partial sums of their own.
 ConvTile conv_choose_tile(int esize, int n_out, double rows_per_model, int n_models, int groups);
-ConvTile conv_tile_of_rows(int rows, int n_out);
-int conv_tile_rows(ConvTile t);
-int conv_stat_split(ConvTile t);
+ConvTile conv_tile_of_rows(int esize, int rows, int n_out);
+int conv_tile_rows(int esize, ConvTile t);
+int conv_stat_split(int esize, ConvTile t);
 
 }  // namespace gan

@@ -11,10 +11,10 @@
 //   reduction index is the slow memory index of both operands: tiles go into LDS as they lie in memory, and the operand
 //   reads do the transposition.
 //
-// Both stage K-chunks in LDS and feed v_mfma_f32_32x32x16_bf16 (bf16 storage) or v_mfma_f32_32x32x2_f32 (fp32
-// storage) from it; accumulation is fp32 in both cases.
+// Both stage K-chunks in LDS and feed v_mfma_f32_32x32x16_bf16 from it (fp32 storage: three bf16 parts a value, six MFMAs a
+// product, see Split8); accumulation is fp32 in both cases.
 // Forward-type kernel: K-chunks of KB bytes per row travel global -> LDS directly (buffer_load_dwordx4 ... lds, no
-// registers in between) into a ring of NST buffers while the MFMAs of the current chunk run.  The 256 x 256 tile uses
+// registers in between) into a ring of NST buffers while the MFMAs of the current chunk run.  In bf16 the 256 x 256 tile uses
 // KB = 128 with two buffers (one block per CU); the 256 x 128 and 128 x 128 tiles use KB = 64 with three, which leaves
 // room for two blocks per CU so that one block's epilogue and barriers hide behind the other's MFMAs; the 256 x 64
 // tile fits two blocks per CU with KB = 128 and two buffers.  The 16-byte chunk c of row
@@ -46,27 +46,43 @@ struct Tile {
   static constexpr int RPP = NT / CPR;               // tile rows filled per loader pass
   static constexpr int PA = BM_ / RPP, PB = BN_ / RPP;
 };
-typedef Tile<256, 256, 2, 4, 128, 2> TileBig;    // 512 threads, wave tile 128 x 64, 128 KiB of LDS
-typedef Tile<256, 128, 4, 2, 64, 3> TileMid;     // 512 threads, wave tile 64 x 64, 72 KiB of LDS
-typedef Tile<128, 128, 2, 2, 64, 3> TileSmall;   // 256 threads, wave tile 64 x 64 (few rows per model), 48 KiB of LDS
-typedef Tile<256, 64, 4, 1, 128, 2> TileNarrow;  // 256 threads, wave tile 64 x 64, for layers with 64 output channels:
+// The forward-type kernel's tiles, by storage type (fp32: see the splits below; they hold two accumulators per element).
+template <typename T> struct FwdTiles;
+template <> struct FwdTiles<bf16_t> {
+  typedef Tile<256, 256, 2, 4, 128, 2> Big;      // 512 threads, wave tile 128 x 64, 128 KiB of LDS
+  typedef Tile<256, 128, 4, 2, 64, 3> Mid;       // 512 threads, wave tile 64 x 64, 72 KiB of LDS
+  typedef Tile<128, 128, 2, 2, 64, 3> Small;     // 256 threads, wave tile 64 x 64 (few rows per model), 48 KiB of LDS
+  typedef Tile<256, 64, 4, 1, 128, 2> Narrow;    // 256 threads, wave tile 64 x 64, for layers with 64 output channels:
                                                  // 128-byte chunks, two buffers of 40 KiB, so two blocks still share a CU
-typedef Tile<64, 64, 2, 2, 64, 3> TileTiny;      // 256 threads, wave tile 32 x 32, 24 KiB of LDS: workloads so small that
+  typedef Tile<64, 64, 2, 2, 64, 3> Tiny;        // 256 threads, wave tile 32 x 32, 24 KiB of LDS: workloads so small that
                                                  // the larger tiles would leave most of the chip without a block
-
-// What a tile is to the chooser: its shape, the blocks of it that a CU holds, and the rate a full chip of them reaches
-// against the fastest one of the storage type.
-struct TileInfo { ConvTile id; const char* name; int rows, cols, split, per_cu; double rate[2]; };   // rate: bf16, fp32
-static const TileInfo TILES[] = {
-    {TILE_BIG, "256x256", TileBig::BM, TileBig::BN, TileBig::WM, 1, {1.0, 0.95}},
-    {TILE_MID, "256x128", TileMid::BM, TileMid::BN, TileMid::WM, 2, {0.88, 0.95}},
-    {TILE_SMALL, "128x128", TileSmall::BM, TileSmall::BN, TileSmall::WM, 3, {0.75, 1.0}},
-    {TILE_NARROW, "256x64", TileNarrow::BM, TileNarrow::BN, TileNarrow::WM, 2, {0.70, 0.95}},
-    {TILE_TINY, "64x64", TileTiny::BM, TileTiny::BN, TileTiny::WM, 6, {0.43, 0.80}},
 };
-static const TileInfo& tile_info(ConvTile t) { return TILES[t]; }
-int conv_tile_rows(ConvTile t) { return tile_info(t).rows; }
-int conv_stat_split(ConvTile t) { return tile_info(t).split; }
+// fp32 is bound by the matrix and vector pipes together, so more than 128 x 128 brings nothing: 20 x 64 samples, 128 -> 256
+// channels at side 8, in TFLOP/s: 128x128 172, 256x128 162 (eight waves of 64 x 64) and 154 (four of 128 x 64, one wave per SIMD),
+// 256x64 162; the 64-byte chunks of the bf16 tiles 156-162.
+template <> struct FwdTiles<float> {
+  typedef Tile<128, 128, 2, 2, 128, 2> Small;    // 256 threads, wave tile 64 x 64, 64 KiB of LDS
+  typedef Tile<256, 64, 4, 1, 128, 2> Narrow;    // 256 threads, wave tile 64 x 64, 80 KiB
+  typedef Tile<64, 64, 2, 2, 128, 2> Tiny;       // 256 threads, wave tile 32 x 32, 32 KiB
+};
+
+// What a tile is to the chooser: its shape, the row blocks with statistics of their own, the blocks of it that a CU holds, and
+// the rate a full chip of them reaches against the fastest one of the storage type (0: the storage type has no such tile).
+struct TileInfo { ConvTile id; const char* name; int rows, cols, split, per_cu; double rate; };
+template <typename TL> constexpr TileInfo info(ConvTile id, const char* name, int per_cu, double rate) {
+  return {id, name, TL::BM, TL::BN, TL::WM, per_cu, rate};
+}
+static const TileInfo TILES[2][5] = {
+    {info<FwdTiles<bf16_t>::Big>(TILE_BIG, "256x256", 1, 1.0), info<FwdTiles<bf16_t>::Mid>(TILE_MID, "256x128", 2, 0.88),
+     info<FwdTiles<bf16_t>::Small>(TILE_SMALL, "128x128", 3, 0.75), info<FwdTiles<bf16_t>::Narrow>(TILE_NARROW, "256x64", 2, 0.70),
+     info<FwdTiles<bf16_t>::Tiny>(TILE_TINY, "64x64", 6, 0.43)},
+    {{TILE_BIG, "", 0, 0, 0, 0, 0}, {TILE_MID, "", 0, 0, 0, 0, 0},
+     info<FwdTiles<float>::Small>(TILE_SMALL, "128x128", 2, 1.0), info<FwdTiles<float>::Narrow>(TILE_NARROW, "256x64", 2, 0.95),
+     info<FwdTiles<float>::Tiny>(TILE_TINY, "64x64", 5, 0.64)},
+};
+static const TileInfo& tile_info(int esize, ConvTile t) { return TILES[esize == 4][t]; }
+int conv_tile_rows(int esize, ConvTile t) { return tile_info(esize, t).rows; }
+int conv_stat_split(int esize, ConvTile t) { return tile_info(esize, t).split; }
 
 // The tile with the smallest estimated time for a launch of `groups` row spaces (phases x segments) of rows_per_model rows in
 // each of n_models models and n_out output columns: rounds of blocks over the chip's 256 CUs times a block's share of its
@@ -76,22 +92,23 @@ int conv_stat_split(ConvTile t) { return tile_info(t).split; }
 ConvTile conv_choose_tile(int esize, int n_out, double rows_per_model, int n_models, int groups) {
   const TileInfo* best = nullptr;
   double best_t = 0;
-  for (const TileInfo& t : TILES) {
+  for (const TileInfo& t : TILES[esize == 4]) {
+    if (t.rate == 0) continue;
     if (t.cols > 64 && n_out % t.cols != 0) continue;      // half-filled tiles
     const double tiles = ceil(rows_per_model / t.rows) * n_models * groups * ((n_out + t.cols - 1) / t.cols);
     const double per_round = 256.0 * t.per_cu, full = floor(tiles / per_round), rest = tiles - full * per_round;
     double blocks = full * t.per_cu;                       // blocks one CU works through
     if (rest > 0) blocks += std::min((double)t.per_cu, ceil(rest / 256.0) + (full > 0 ? 0.5 : 0.0));
-    const double time = blocks * t.rows * t.cols / t.rate[esize == 4 ? 1 : 0];
+    const double time = blocks * t.rows * t.cols / t.rate;
     if (!best || time < best_t) { best = &t; best_t = time; }
   }
   return best->id;
 }
 // the tile of a given height (single-operation tests): with 256 rows the width follows the output channels
-ConvTile conv_tile_of_rows(int rows, int n_out) {
-  if (rows == TileTiny::BM) return TILE_TINY;
-  if (rows == TileSmall::BM) return TILE_SMALL;
-  return n_out <= TileNarrow::BN ? TILE_NARROW : (n_out % 256 == 0 ? TILE_BIG : TILE_MID);
+ConvTile conv_tile_of_rows(int esize, int rows, int n_out) {
+  if (rows == 64) return TILE_TINY;
+  if (rows == 128) return TILE_SMALL;
+  return n_out <= 64 || esize == 4 ? TILE_NARROW : (n_out % 256 == 0 ? TILE_BIG : TILE_MID);
 }
 
 __device__ inline void mma16B(floatx16& acc, const uint4& a, const uint4& b, bf16_t) {
@@ -100,16 +117,16 @@ __device__ inline void mma16B(floatx16& acc, const uint4& a, const uint4& b, bf1
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 // One K-step (16 bytes of every operand row) of a wave's TM x TN tiles.
 template <int TM, int TN>
-__device__ inline void mma_step(floatx16 (&acc)[TM][TN], const u32x4 (&a)[TM], const u32x4 (&b)[TN], bf16_t) {
+__device__ __forceinline__ void mma_step(floatx16 (&acc)[TM][TN], const u32x4 (&a)[TM], const u32x4 (&b)[TN], bf16_t) {
 #pragma unroll
   for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) mma16B(acc[tm][tn], __builtin_bit_cast(uint4, a[tm]), __builtin_bit_cast(uint4, b[tn]), bf16_t());
 }
-// fp32: four k-pairs; lane half h supplies k = 4h + j to MFMA j, for A and B alike.  The pair is the outer loop, so that an
-// accumulator comes round only after all the others (one after the other, each MFMA waits for the one before it).
+// fp32, one value at a time (tiles with infinities or NaN, see Split8): four k-pairs; lane half h supplies k = 4h + j to
+// MFMA j, for A and B alike.  The pair is the outer loop, so that an accumulator comes round only after all the others.
 template <int TM, int TN>
-__device__ inline void mma_step(floatx16 (&acc)[TM][TN], const u32x4 (&a)[TM], const u32x4 (&b)[TN], float) {
+__device__ __forceinline__ void mma_step(floatx16 (&acc)[TM][TN], const u32x4 (&a)[TM], const u32x4 (&b)[TN], float) {
 #pragma unroll
   for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -117,6 +134,102 @@ __device__ inline void mma_step(floatx16 (&acc)[TM][TN], const u32x4 (&a)[TM], c
 #pragma unroll
       for (int tn = 0; tn < TN; ++tn)
         acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[tm][j]), __uint_as_float(b[tn][j]), acc[tm][tn], 0, 0, 0);
+}
+
+// fp32 storage on the bf16 matrix cores.  x = h + m + l with h, m, l of eight significant bits each (h = bf16(x),
+// m = bf16(x - h), l = x - h - m: both differences are exact, and l needs eight bits), so a product of two fp32 values is nine
+// bf16 products, each exact in the MFMA.  The six down to 2^-16 of the product are taken, h*h into one fp32 accumulator and the
+// five smaller ones into a second that is added at the end; the three left out are below 2^-24 of it and of either sign.
+// Why: v_mfma_f32_32x32x2_f32 takes sixteen times the matrix-pipe time of the bf16 MFMA, six of which replace it.  Forward-type
+// kernel, 20 x 64 samples, 128 -> 256 channels at side 8: 100 TFLOP/s before, 172 now; weight gradient of the same layer 95 and
+// 126.  What bounds it now is the matrix pipe (1.0 PFLOP/s of bf16) and the 5.5 vector instructions that split a value (without
+// them, 15 % less time).
+// Error against 64-bit sums (relative, 64 .. 512 channels, sides 2 .. 16): 0.31-0.38 of the fp32 MFMA's on normal and on positive
+// inputs, 0.35-0.56 on inputs after a ReLU, because a bf16 MFMA rounds its accumulator once for several products and the small
+// terms have an accumulator of their own.  (All six into one accumulator: 0.85, but 1.1-1.4 after a ReLU, where half the products are zero
+// and the fp32 MFMA has nothing to round; not taken, although its 128 x 64 wave tiles were 8 % faster.)
+// What has no split -- infinities, NaN, values that round to a bf16 infinity -- leaves a NaN in the accumulators; a block that
+// finds one computes its tile again with the fp32 MFMAs.  (Below 2^-110 the parts fall under the smallest bf16 and are lost.)
+struct Split8 { u32x4 h, m, l; };
+__device__ __forceinline__ void split_pair(float x0, float x1, unsigned& h, unsigned& m, unsigned& l) {
+  h = pack2_bf16(x0, x1);
+  const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
+  m = pack2_bf16(r0, r1);
+  l = pack2_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
+}
+// eight values of one operand row (or column): elements 0..3 in lo, 4..7 in hi
+__device__ __forceinline__ Split8 split8(const u32x4& lo, const u32x4& hi) {
+  Split8 s;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const u32x4& v = i < 2 ? lo : hi;
+    const int j = 2 * (i & 1);
+    unsigned h, m, l;
+    split_pair(__uint_as_float(v[j]), __uint_as_float(v[j + 1]), h, m, l);
+    s.h[i] = h; s.m[i] = m; s.l[i] = l;
+  }
+  return s;
+}
+__device__ inline void mma_u4(floatx16& acc, const u32x4& a, const u32x4& b) {
+  mma16B(acc, __builtin_bit_cast(uint4, a), __builtin_bit_cast(uint4, b), bf16_t());
+}
+// one row fragment against TN column fragments: h*h into acc, the five smaller products into low
+template <int TN>
+__device__ __forceinline__ void mma_split(floatx16 (&acc)[TN], floatx16 (&low)[TN], const Split8& a, const Split8 (&b)[TN]) {
+#pragma unroll
+  for (int t = 0; t < TN; ++t) mma_u4(low[t], a.l, b[t].h);
+#pragma unroll
+  for (int t = 0; t < TN; ++t) mma_u4(acc[t], a.h, b[t].h);
+#pragma unroll
+  for (int t = 0; t < TN; ++t) mma_u4(low[t], a.h, b[t].l);
+#pragma unroll
+  for (int t = 0; t < TN; ++t) mma_u4(low[t], a.m, b[t].m);
+#pragma unroll
+  for (int t = 0; t < TN; ++t) mma_u4(low[t], a.m, b[t].h);
+#pragma unroll
+  for (int t = 0; t < TN; ++t) mma_u4(low[t], a.h, b[t].m);
+}
+// 1 if any of this lane's sums is an infinity or NaN
+template <int TM, int TN>
+__device__ inline int not_finite(const floatx16 (&acc)[TM][TN]) {
+  float z = 0.f;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) z = __builtin_fmaf(acc[i][j][e], 0.f, z);
+  return z != z;
+}
+// the same for the whole block, through a few bytes of LDS that nothing else is using (barriers on both sides)
+template <int WAVES>
+__device__ inline bool block_any(int flag, unsigned char* lds, int wave) {
+  int* const word = reinterpret_cast<int*>(lds);
+  const bool mine = __ballot(flag) != 0;
+  if ((threadIdx.x & 63) == 0) word[wave] = mine;
+  __syncthreads();
+  int any = 0;
+  for (int w = 0; w < WAVES; ++w) any |= word[w];
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(any) != 0;
+}
+template <int TM, int TN>
+__device__ inline void add_acc(floatx16 (&acc)[TM][TN], const floatx16 (&low)[TM][TN]) {
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] += low[i][j][e];
+}
+template <int TM, int TN>
+__device__ inline void clear_acc(floatx16 (&acc)[TM][TN]) {
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 }
 
 // One K-chunk of the forward-type kernel: rows KB bytes apart, the 16-byte chunk c of tile row R at position
@@ -145,14 +258,14 @@ __device__ inline void lds_wait(u32x4 (&a)[TM], u32x4 (&b)[TN]) {
     static_assert(TM == 4 && TN == 2, "add the operand list for this wave tile");
 }
 template <int I, int N, typename F>
-__device__ inline void static_for(F&& f) {
+__device__ __forceinline__ void static_for(F&& f) {
   if constexpr (I < N) {
     f(std::integral_constant<int, I>{});
     static_for<I + 1, N>(f);
   }
 }
 template <typename T, int TM, int TN, int KB>
-__device__ inline void tile_mma_fwd(floatx16 (&acc)[TM][TN], const unsigned char* As, const unsigned char* Bs, int wm, int wn,
+__device__ __forceinline__ void tile_mma_fwd(floatx16 (&acc)[TM][TN], const unsigned char* As, const unsigned char* Bs, int wm, int wn,
                                     int lane) {
   const int r = lane & 31, h = lane >> 5;
   const int sw = fwd_swz<KB>(r);   // tile rows start at multiples of 32, a multiple of the swizzle period
@@ -162,13 +275,13 @@ __device__ inline void tile_mma_fwd(floatx16 (&acc)[TM][TN], const unsigned char
   const unsigned a0 = (unsigned)(uintptr_t)As + (wm * TM * 32 + r) * KB + ((h ^ sw) << 4);
   const unsigned b0 = (unsigned)(uintptr_t)Bs + (wn * TN * 32 + r) * KB + ((h ^ sw) << 4);
   u32x4 a[2][TM], b[2][TN];
-  auto fetch = [&](auto vs, auto set) {
+  auto fetch = [&](auto vs, auto set) __attribute__((always_inline)) {
     const unsigned aa = a0 ^ (vs.value << 5), bb = b0 ^ (vs.value << 5);
-    static_for<0, TM>([&](auto t) { lds_read16<t.value * 32 * KB>(a[set.value][t.value], aa); });
-    static_for<0, TN>([&](auto t) { lds_read16<t.value * 32 * KB>(b[set.value][t.value], bb); });
+    static_for<0, TM>([&](auto t) __attribute__((always_inline)) { lds_read16<t.value * 32 * KB>(a[set.value][t.value], aa); });
+    static_for<0, TN>([&](auto t) __attribute__((always_inline)) { lds_read16<t.value * 32 * KB>(b[set.value][t.value], bb); });
   };
   fetch(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
-  static_for<0, NV>([&](auto vs) {
+  static_for<0, NV>([&](auto vs) __attribute__((always_inline)) {
     constexpr int cur = vs.value & 1;
     if constexpr (vs.value + 1 < NV) {
       fetch(std::integral_constant<int, vs.value + 1>{}, std::integral_constant<int, cur ^ 1>{});
@@ -178,6 +291,27 @@ __device__ inline void tile_mma_fwd(floatx16 (&acc)[TM][TN], const unsigned char
     }
     mma_step(acc, a[cur], b[cur], T());
     __builtin_amdgcn_sched_barrier(0);       // keep these MFMAs in front of the next K-step's wait
+  });
+}
+
+// fp32 through splits: two K-steps (16 values of K per row) are one step here; lane half h supplies the chunks 2 vs + h of both.
+template <int TM, int TN, int KB>
+__device__ __forceinline__ void tile_mma_split(floatx16 (&acc)[TM][TN], floatx16 (&low)[TM][TN], const unsigned char* As,
+                                               const unsigned char* Bs, int wm, int wn, int lane) {
+  const int r = lane & 31, h = lane >> 5;
+  const int sw = fwd_swz<KB>(r);
+  const unsigned char* const ap = As + (wm * TM * 32 + r) * KB;
+  const unsigned char* const bp = Bs + (wn * TN * 32 + r) * KB;
+  static_for<0, KB / 64>([&](auto ps) __attribute__((always_inline)) {
+    const int c0 = ((4 * ps.value + h) ^ sw) * 16, c1 = ((4 * ps.value + 2 + h) ^ sw) * 16;
+    Split8 b[TN];
+    static_for<0, TN>([&](auto t) __attribute__((always_inline)) {
+      b[t.value] = split8(*reinterpret_cast<const u32x4*>(bp + t.value * 32 * KB + c0), *reinterpret_cast<const u32x4*>(bp + t.value * 32 * KB + c1));
+    });
+    static_for<0, TM>([&](auto t) __attribute__((always_inline)) {
+      const Split8 a = split8(*reinterpret_cast<const u32x4*>(ap + t.value * 32 * KB + c0), *reinterpret_cast<const u32x4*>(ap + t.value * 32 * KB + c1));
+      mma_split(acc[t.value], low[t.value], a, b);
+    });
   });
 }
 
@@ -199,7 +333,7 @@ __device__ inline int4v make_rsrc(const void* base, unsigned long long bytes) {
 // The wave-uniform part of the offset (which tap, which channels) travels in a scalar register.
 __device__ inline void load16_to_lds(const int4v& rsrc, unsigned byte_off, unsigned uniform_off, unsigned lds_base) {
   asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-               : : "v"(byte_off), "s"(rsrc), "s"(uniform_off), "s"(lds_base) : "memory", "m0");
+               : : "v"(byte_off), "s"(rsrc), "s"(uniform_off), "s"(__builtin_amdgcn_readfirstlane((int)lds_base)) : "memory", "m0");
 }
 // wait until at most N loads are still in flight
 template <int N>
@@ -245,8 +379,10 @@ static int log2_or_neg(int v) {
   return -1;
 }
 
+// Waves a SIMD should hold, which bounds the registers: two for fp32 wave tiles of 64 x 64 with their two accumulators.
+template <typename T, typename TL> constexpr int waves_per_simd() { return sizeof(T) == 4 && TL::TM * TL::TN == 4 ? 2 : 1; }
 template <typename T, int MODE, int EPI, typename TL>
-__global__ __launch_bounds__(TL::NT) void conv_gemm_kernel(ConvArgs p) {
+__global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void conv_gemm_kernel(ConvArgs p) {
   constexpr int BM = TL::BM, BN = TL::BN, TM = TL::TM, TN = TL::TN, PA = TL::PA, PB = TL::PB, RPP = TL::RPP;
   constexpr int KB = TL::KB, NST = TL::NST;
   constexpr int SMEM_RING = NST * (BM + BN) * KB;
@@ -394,7 +530,7 @@ __global__ __launch_bounds__(TL::NT) void conv_gemm_kernel(ConvArgs p) {
   // instructions a chunk, more issue time than the 8 MFMAs per wave of a 64-byte chunk.
   // down: classes 0, 1 hold the taps with ky in {0, 2}, classes 2, 3 those with ky in {1, 3}; a class keeps cnt taps, and the
   // two left in a class of two are its kx pair at the one valid ky: ky = 2 (top tile, even class) or 1 (bottom, odd).
-  int k_part = 0, k_j = 0, k_line = 0, k_cls = 0, k_cnt = MODE == MODE_DENSE ? 1 : cnt_lo, k_tap = 0;
+  int k_part, k_j, k_line, k_cls, k_cnt, k_tap = 0;
   unsigned k_aoff = 0, k_woff = 0;
   auto k_set = [&]() {
     if (MODE == MODE_DOWN) {
@@ -428,7 +564,6 @@ __global__ __launch_bounds__(TL::NT) void conv_gemm_kernel(ConvArgs p) {
     }
     k_set();
   };
-  k_set();
   auto load_chunk = [&](int stage) {                   // the next chunk, into a buffer
     const unsigned a_dst = lds0 + (stage * BM + wave * (1024 / KB)) * KB;        // + pass * RPP rows
     const unsigned b_dst = lds0 + (NST * BM + stage * BN + wave * (1024 / KB)) * KB;
@@ -440,30 +575,40 @@ __global__ __launch_bounds__(TL::NT) void conv_gemm_kernel(ConvArgs p) {
     k_advance();
   };
   floatx16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
   // Ring of NST buffers: chunk c lives in buffer c % NST.  While chunk c is multiplied, chunks c+1 .. c+NST-1 are on
   // their way; the barrier that ends iteration c tells every wave that chunk c+1 has landed everywhere and that
   // buffer c % NST may be refilled (with chunk c+NST, by the next iteration).
-  int st_load = 0, st = 0;                             // buffers of the next chunk to load and of the current one
-  for (int c = 0; c < NST - 1 && c < nk; ++c) load_chunk(st_load++);
-  wait_vm<0>();
-  __syncthreads();
-  for (int kc = 0; kc < nk; ++kc) {
-    const bool more = kc + NST - 1 < nk;
-    if (more) {
-      load_chunk(st_load);
-      st_load = st_load == NST - 1 ? 0 : st_load + 1;
-    }
-    tile_mma_fwd<T, TM, TN, KB>(acc, As + st * BM * KB, Bs + st * BN * KB, wm, wn, lane);
-    st = st == NST - 1 ? 0 : st + 1;
-    if (more) wait_vm<(NST - 2) * LPT>(); else wait_vm<0>();       // chunk kc + 1 has landed; those behind it may stay in flight
+  floatx16 low[TM][TN];
+  auto k_loop = [&](auto split) __attribute__((always_inline)) {
+    k_part = k_j = k_line = k_cls = 0;
+    k_cnt = MODE == MODE_DENSE ? 1 : cnt_lo;
+    k_set();
+    clear_acc(acc);
+    if constexpr (split.value) clear_acc(low);
+    int st_load = 0, st = 0;                           // buffers of the next chunk to load and of the current one
+    for (int c = 0; c < NST - 1 && c < nk; ++c) load_chunk(st_load++);
+    wait_vm<0>();
     __syncthreads();
+    for (int kc = 0; kc < nk; ++kc) {
+      const bool more = kc + NST - 1 < nk;
+      if (more) {
+        load_chunk(st_load);
+        st_load = st_load == NST - 1 ? 0 : st_load + 1;
+      }
+      if constexpr (split.value) tile_mma_split<TM, TN, KB>(acc, low, As + st * BM * KB, Bs + st * BN * KB, wm, wn, lane);
+      else tile_mma_fwd<T, TM, TN, KB>(acc, As + st * BM * KB, Bs + st * BN * KB, wm, wn, lane);
+      st = st == NST - 1 ? 0 : st + 1;
+      if (more) wait_vm<(NST - 2) * LPT>(); else wait_vm<0>();     // chunk kc + 1 has landed; those behind it may stay in flight
+      __syncthreads();
+    }
+  };
+  if constexpr (SZ == 4) {
+    k_loop(std::true_type{});
+    add_acc(acc, low);
+    if (block_any<TL::NT / 64>(not_finite(acc), smem, wave)) k_loop(std::false_type{});
+  } else {
+    k_loop(std::false_type{});
   }
 
   // ---- epilogue: output row index of every tile row, through LDS (the buffers are free now)
@@ -607,13 +752,15 @@ static void launch_one(ConvArgs a, hipStream_t st) {
 
 template <typename T, int MODE, int EPI>
 static void launch_wide(const ConvArgs& a, hipStream_t st) {
-  switch (a.tile) {
-    case TILE_BIG: return launch_one<T, MODE, EPI, TileBig>(a, st);
-    case TILE_MID: return launch_one<T, MODE, EPI, TileMid>(a, st);
-    case TILE_SMALL: return launch_one<T, MODE, EPI, TileSmall>(a, st);
-    case TILE_NARROW: return launch_one<T, MODE, EPI, TileNarrow>(a, st);
-    case TILE_TINY: return launch_one<T, MODE, EPI, TileTiny>(a, st);
+  typedef FwdTiles<T> Tiles;
+  if constexpr (sizeof(T) == 2) {
+    if (a.tile == TILE_BIG) return launch_one<T, MODE, EPI, typename Tiles::Big>(a, st);
+    if (a.tile == TILE_MID) return launch_one<T, MODE, EPI, typename Tiles::Mid>(a, st);
   }
+  if (a.tile == TILE_SMALL) return launch_one<T, MODE, EPI, typename Tiles::Small>(a, st);
+  if (a.tile == TILE_NARROW) return launch_one<T, MODE, EPI, typename Tiles::Narrow>(a, st);
+  if (a.tile == TILE_TINY) return launch_one<T, MODE, EPI, typename Tiles::Tiny>(a, st);
+  launch_fail("GEMM: a tile that this storage type does not have");
 }
 
 // The (mode, epilogue, tile) combinations the networks use.
@@ -644,7 +791,7 @@ const char* conv_variant_name(int mode, int epi, const ConvArgs& a) {
   static const char* epis[3] = {"", "+actbwd", "+lrelu"};
   static char names[3][3][5][48];
   char* n = names[mode][epi][a.tile];
-  if (!n[0]) snprintf(n, 48, "gemm_%s%s<%s>", modes[mode], epis[epi], tile_info(a.tile).name);
+  if (!n[0]) snprintf(n, 48, "gemm_%s%s<%s>", modes[mode], epis[epi], TILES[0][a.tile].name);
   return n;
 }
 template void launch_conv<float>(int, int, const ConvArgs&, hipStream_t);
@@ -669,10 +816,7 @@ __device__ inline int wgrad_model(const WgradArgs& p, int i) {
 // bf16: ds_read_b64_tr_b16 does the transposition on the way to the registers: within each block of 16 lanes, lane i
 // receives element i%4 of the 8-byte groups addressed by lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4; pointing lane s of a
 // block at row (s/4), channel group (s%4) therefore hands lane i rows 0..3 of channel i.
-// fp32: an operand of v_mfma_f32_32x32x2_f32 is one value per lane, (channel lane%32, row lane/32): a plain 4-byte read
-// of the tile as it lies.  The kernel is bound by the MFMAs (64 cycles each against one such read).  (Its predecessor
-// went global -> registers -> 32 scalar LDS writes per task with two divisions per row: 65-75 TFLOP/s on 128 -> 256
-// channels at side 8, and 11 TFLOP/s at side 7, where nothing was a shift.)
+// fp32: plain 4-byte reads of the tile as it lies, lane r of a half-wave channel r, eight rows a lane for one split step.
 // The 16-byte chunk c of row R sits at position c ^ swz(R), so that the rows one read touches fall into different
 // bank groups.
 template <typename T> constexpr int wg_kr() { return 128 / (int)sizeof(T); }     // rows (reduction index) per chunk: 64 or 32
@@ -688,7 +832,7 @@ __device__ inline uint2 lds_read_tr16(const unsigned char* p) {
 }
 
 template <typename T, typename TL>
-__global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
+__global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void wgrad_kernel(WgradArgs p) {
   constexpr int SZ = (int)sizeof(T), EPV = 16 / SZ, WG_KR = wg_kr<T>();
   constexpr int BM = TL::BM, BN = TL::BN, TM = TL::TM, TN = TL::TN, NT_ = TL::NT;
   constexpr int RBA = BM * SZ, RBB = BN * SZ;               // bytes per LDS row
@@ -784,7 +928,7 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
     else fb_off[i] = (unsigned)((c * Cs + cB) * SZ);
   }
 
-  auto load_chunk = [&](int seg, int k0, int stage) {
+  auto load_chunk = [&](int seg, int k0, int stage) __attribute__((always_inline)) {
     const long long sb = (long long)seg * p.seg_samples + s0;
     const int4v a_rsrc = make_rsrc(static_cast<const T*>(p.Big) + sb * big_per_sample, (unsigned long long)(s1 - s0) * big_per_sample * SZ);
     const int4v b_rsrc = make_rsrc(static_cast<const T*>(p.Small) + sb * rps * Cs, (unsigned long long)R * Cs * SZ);
@@ -838,13 +982,7 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
       load16_to_lds(b_rsrc, (rowB0 + i * RPB < left && okB) ? fb_off[i] + b_delta : NO_ROW, 0u, b_dst + i * NT_ * 16);
   };
 
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  floatx16 acc[TM][TN], low[TM][TN];      // (low: fp32 only)
 
   // ---- fragment addressing: lane = 32 * kgrp + 16 * hb + s ; it points at row 8*kgrp + 4*half + s/4 of the k-step,
   // channels 16*hb + 4*(s%4) .. +3 of the 32-channel fragment
@@ -855,11 +993,11 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
   const int swzA = wg_swz<T, RBA>(frow), swzB = wg_swz<T, RBB>(frow);   // frow % 4 (and (frow/2) % 2) do not change with kstep or half
   // The reads of step ks + 1 are issued in front of the MFMAs of step ks (two register sets; the scheduling barriers keep
   // the compiler from pulling them together, which left every step waiting for its own reads).
-  auto mma_chunk16 = [&](int stage) {
+  auto mma_chunk16 = [&](int stage) __attribute__((always_inline)) {
     const unsigned char* As = smem + stage * STAGE_A;
     const unsigned char* Bs = smem + 2 * STAGE_A + stage * STAGE_B;
     uint4 a[2][TM], b[2][TN];
-    auto fetch = [&](int ks, int set) {
+    auto fetch = [&](int ks, int set) __attribute__((always_inline)) {
 #pragma unroll
       for (int t = 0; t < TM; ++t) {
         const int ch = ((wm * TM + t) * 4 + fch) ^ swzA;
@@ -888,7 +1026,7 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
     }
   };
   // fp32: a step is the row pairs 2 ks, 2 ks + 1 for two values of ks; lane half h reads row 2 ks + h (swz flips with h only)
-  auto mma_chunk32 = [&](int stage) {
+  auto mma_chunk32 = [&](int stage) __attribute__((always_inline)) {
     const int r = lane & 31, h = lane >> 5;
     const unsigned char* As = smem + stage * STAGE_A + h * RBA + (r & 3) * 4;
     const unsigned char* Bs = smem + 2 * STAGE_A + stage * STAGE_B + h * RBB + (r & 3) * 4;
@@ -899,7 +1037,7 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
 #pragma unroll
     for (int t = 0; t < TN; ++t) bp[t] = reinterpret_cast<const float*>(Bs + ((((wn * TN + t) * 8 + (r >> 2)) ^ (8 * h)) * 16));
     float a[2][2][TM], b[2][2][TN];
-    auto fetch = [&](int step, int set) {
+    auto fetch = [&](int step, int set) __attribute__((always_inline)) {
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
 #pragma unroll
@@ -923,9 +1061,26 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto mma_chunk = [&](int stage) {
-    if constexpr (SZ == 2) mma_chunk16(stage);
-    else mma_chunk32(stage);
+  // fp32 through splits: a step is sixteen rows; lane half h reads rows 16 st + 2 j + h, j = 0..7
+  auto mma_chunk_split = [&](int stage) __attribute__((always_inline)) {
+    const int r = lane & 31, h = lane >> 5;
+    const unsigned char* As = smem + stage * STAGE_A + h * RBA + (r & 3) * 4;
+    const unsigned char* Bs = smem + 2 * STAGE_A + stage * STAGE_B + h * RBB + (r & 3) * 4;
+    const auto column = [&](const unsigned char* base, int tile32, int row_bytes, int st) __attribute__((always_inline)) {     // this lane's eight values of one fragment
+      const unsigned char* q = base + ((tile32 * 8 + (r >> 2)) ^ (8 * h)) * 16 + st * 16 * row_bytes;
+      u32x4 lo, hi;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        lo[j] = *reinterpret_cast<const unsigned*>(q + 2 * j * row_bytes);
+        hi[j] = *reinterpret_cast<const unsigned*>(q + 2 * (j + 4) * row_bytes);
+      }
+      return split8(lo, hi);
+    };
+    static_for<0, WG_KR / 16>([&](auto st) __attribute__((always_inline)) {
+      Split8 b[TN];
+      static_for<0, TN>([&](auto t) __attribute__((always_inline)) { b[t.value] = column(Bs, wn * TN + t.value, RBB, st.value); });
+      static_for<0, TM>([&](auto t) __attribute__((always_inline)) { mma_split(acc[t.value], low[t.value], column(As, wm * TM + t.value, RBA, st.value), b); });
+    });
   };
 
   // chunks of all segments as one sequence; in pixel-row-first order the chunks [bad0, bad0 + nbad) of every segment
@@ -940,7 +1095,9 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
   const int per_seg = per_seg_all - nbad;
   const int nchunks = per_seg * p.nseg;
   auto chunk_row = [&](int cin) { return r_lo + (cin < bad0 ? cin : cin + nbad) * WG_KR; };
-  if (nchunks > 0) {
+  auto row_loop = [&](auto mma_chunk) __attribute__((always_inline)) {
+    clear_acc(acc);
+    if (nchunks <= 0) return;
     load_chunk(0, chunk_row(0), 0);
     wait_vm<0>();
     __syncthreads();
@@ -954,6 +1111,14 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
       wait_vm<0>();
       __syncthreads();
     }
+  };
+  if constexpr (SZ == 4) {
+    clear_acc(low);
+    row_loop(mma_chunk_split);
+    add_acc(acc, low);
+    if (block_any<NT_ / 64>(not_finite(acc), smem, wave)) row_loop(mma_chunk32);
+  } else {
+    row_loop(mma_chunk16);
   }
 
   // Epilogue: each wave passes its 32 x (TN*32) blocks through a private LDS patch (the K buffers are free after the
@@ -995,12 +1160,14 @@ __global__ __launch_bounds__(TL::NT) void wgrad_kernel(WgradArgs p) {
 }
 
 // Tiles of the weight gradient.  bf16: the largest tile the output fills, because the loop lives on the CU's path from
-// L2 (operand bytes per product fall with the tile's sides).  fp32: sixteen times the matrix-pipe time per byte, so
-// tiles are small: 128 x 128 with two blocks per CU leaves little of a last round of blocks idle where 256-row tiles
-// (about 1 ms each) idled up to half of it.
+// L2 (operand bytes per product fall with the tile's sides).  fp32: six times the matrix-pipe time, so
+// tiles are small: 128 x 128 with two blocks per CU leaves little of a last round of blocks idle (640 such tiles of 20 models run
+// at 126 TFLOP/s, 256 x 128 ones at 90-106, 256 x 64 at 119).
 typedef Tile<64, 128, 1, 4> TileWgImg;    // patch-matrix layers: 64 packed columns x 128 feature channels
 typedef Tile<64, 64, 2, 2> TileWgImg64;   //   and x 64
 typedef Tile<256, 64, 4, 1> TileWg64;     // 64 channels on the N side, bf16
+typedef Tile<256, 256, 2, 4> TileWgBig;
+typedef Tile<256, 128, 4, 2> TileWgMid;
 typedef Tile<128, 128, 2, 2> TileWgF32;
 typedef Tile<128, 64, 2, 2> TileWgF32N;
 
@@ -1032,9 +1199,9 @@ static void with_wgrad_tile(int ntaps, int Cb, int Cs, F&& f) {
   } else if constexpr (sizeof(T) == 4) {
     if (Cs <= 64) f(TileWgF32N(), "wgrad<128x64>"); else f(TileWgF32(), "wgrad<128x128>");
   } else {
-    if (Cs % 256 == 0) f(TileBig(), "wgrad<256x256>");
+    if (Cs % 256 == 0) f(TileWgBig(), "wgrad<256x256>");
     else if (Cs <= 64) f(TileWg64(), "wgrad<256x64>");
-    else f(TileMid(), "wgrad<256x128>");
+    else f(TileWgMid(), "wgrad<256x128>");
   }
 }
 

@@ -178,3 +178,45 @@ def test_wgrad_row_decoding_and_narrow_tiles(ctxs, prec, cb, cs, hs, groups):
         ref = dW.transpose(2, 3, 1, 0)
         # fp32 sums of up to 4096 products in another order; bf16 inputs are exact here, so only the sums differ too
         assert np.max(np.abs(got[i] - ref)) <= 2e-5 * np.max(np.abs(ref)), "wgrad group %d" % i
+
+
+def test_fp32_values_without_a_bf16_split(ctxs):
+    """fp32 contractions run on sums of bf16 parts.  Infinities, NaN and values that round to a bf16 infinity have no such parts:
+    the results must be what fp32 arithmetic gives, and the other outputs must not notice.  Bounds as in the test above."""
+    torch = U.torch_mod()
+    g = ctxs[binding.FP32]
+    cb, cs, hs, n = 64, 128, 4, 40
+    rng = np.random.default_rng(11)
+    big = rng.normal(0, 1, (n, 2 * hs, 2 * hs, cb)).astype(np.float32)
+    small = rng.normal(0, 1, (n, hs, hs, cs)).astype(np.float32)
+    big[3, 2, 5, 7], big[20, 0, 0, 1], big[31, 7, 7, 63], big[33, 4, 4, 0] = np.inf, -np.inf, np.nan, 3.4e38
+    W = rng.normal(0, 0.05, (cs, cb, 4, 4)).astype(np.float32)
+    offs = U.dev(np.array([0, n], np.int32))
+    d_big, d_small = U.dev(big), U.dev(small)
+    with np.errstate(all="ignore"):
+        ref = O.conv2d(big.transpose(0, 3, 1, 2), W, None).transpose(0, 2, 3, 1)
+        _, dW, _ = O.conv2d_bwd(big.transpose(0, 3, 1, 2), W, small.transpose(0, 3, 1, 2), need_dx=False)
+        dW = dW.transpose(2, 3, 1, 0)
+    for rows in (64, 128, 256):
+        g.op_tile_rows(rows)
+        out = torch.zeros((n, hs, hs, cs), device="cuda")
+        d_w = U.dev(np.ascontiguousarray(W.transpose(2, 3, 0, 1)).reshape(16, cs, cb))
+        g.op_conv_down(d_big.data_ptr(), d_w.data_ptr(), out.data_ptr(), offs.data_ptr(), 1, n, cb, cs, hs)
+        _same_classes(out.cpu().numpy(), ref)
+    g.op_tile_rows(0)
+    dw = torch.zeros((4, 4, cb, cs), device="cuda")
+    g.op_conv_wgrad(d_big.data_ptr(), d_small.data_ptr(), dw.data_ptr(), offs.data_ptr(), 1, n, cb, cs, hs)
+    _same_classes(dw.cpu().numpy(), dW)
+
+
+def _same_classes(got, ref):
+    with np.errstate(over="ignore"):
+        ref = ref.astype(np.float32)                                     # what overflows in fp32 is an infinity there
+    assert not np.isfinite(ref).all()
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(ref))
+    inf = np.isinf(ref)
+    np.testing.assert_array_equal(got[inf], ref[inf])
+    huge = np.isfinite(ref) & (np.abs(ref) > 1e30)
+    assert np.all(np.abs(got[huge] / ref[huge] - 1) <= 2e-5)             # one product dwarfs the others there
+    rest = np.isfinite(ref) & ~huge
+    assert np.max(np.abs(got[rest] - ref[rest])) <= 2e-5 * np.max(np.abs(ref[rest]))
