@@ -31,6 +31,10 @@ inline long long round_up(long long x, long long m) { return (x + m - 1) / m * m
 // many blocks per model, and the partial blocks are added in a fixed order when they are unpacked
 // Row splits of the image-side weight gradients (one or a few output tiles per model): 8 when there are many
 // models, more when the models alone would leave most of the chip idle.  A function of the model count only.
+// Widest patch matrix of D's first convolution that carries the label maps as indicator columns (see gan_create).  Step of one
+// pair, columns -> rows behind the GEMM, in us: 128 columns (28x28, 10 labels, 640 images) 747 -> 759, (32x32, 3 labels, 64) 982 ->
+// 992; 192 (32x32, 10 labels, 1000) 2755 -> 2726; 320 (25 labels, 200) 1310 -> 1260; 960 (100 labels, 64) 1086 -> 999, (1000) 3336 -> 2721.
+constexpr int LABEL_COLUMNS = 128;
 static int img_ksplit_for(int L) { return std::min(std::max(800 / L, 8), 128); }
 constexpr int WG_MAX_KSPLIT = 64;
 
@@ -97,7 +101,10 @@ struct gan_ctx {
   bool paper = false;              // the networks as printed in the paper's tables
   float *dw4 = nullptr, *c3_part = nullptr;   // paper G: k4 weight gradient of one block; row-split partials of the last conv
   int KcD = 0, KcG = 0;
-  int nslot = 1;
+  int nslot = 1;              // class-indicator slots in the patch matrix of D's first conv
+  int labels = 0;             // > 0: the label maps are added as rows behind that GEMM instead (one pair over many labels)
+  void* label_rows = nullptr;
+  float *label_sums = nullptr, *class_part = nullptr;
   int last_n = -1;
   bool shadows_dirty = true;
   std::string err;
@@ -569,6 +576,7 @@ void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, c
   a.C = C; a.N = N; a.Hin = Hin; a.Hr = Hr; a.ub_tiles = ub_tiles(c, n, Hr * Hr, tr);
   a.slope = c->cfg.leaky_slope;
   a.stat_partial = stats ? c->stat_partial : nullptr;
+  if (epi == EPI_LABEL_LRELU) { a.label_rows = c->label_rows; a.sample_slot = c->rb.sample_slot; }
   const int ntaps = mode == MODE_DOWN ? 16 : (mode == MODE_UP ? 4 : 1);
   const int phases = mode == MODE_UP ? 4 : 1;
   const double rows = (double)n * nseg * Hr * Hr * phases;
@@ -698,7 +706,7 @@ void im2col_call(gan_ctx* c, const ConvLayer& cl, const void* img, const float* 
   Im2colArgs a;
   memset(&a, 0, sizeof(a));
   a.img = img; a.real = real; a.perm = c->rb.perm; a.out = out; a.offs = c->rb.offs; a.sample_slot = c->rb.sample_slot;
-  a.L = c->L; a.n = n; a.CB = cl.Cb; a.Hs = cl.Hs; a.Kc = Kc; a.nslot = nslot; a.seg = seg; a.seg_samples = n;
+  a.L = c->L; a.n = n; a.CB = cl.Cb; a.Hs = cl.Hs; a.Kc = Kc; a.nslot = nslot; a.constant = &cl == &c->D.conv[0]; a.seg = seg; a.seg_samples = n;
   const double rows = (double)n * cl.Hs * cl.Hs;
   Scope s(c, "im2col", 0, rows * (4.0 * cl.Cb * (real ? 4 : sizeof(T)) + (double)Kc * sizeof(T)));
   launch_im2col<T>(a, c->st);
@@ -720,8 +728,10 @@ void up_img_call(gan_ctx* c, Net& net, const ConvLayer& cl, const void* feat, vo
 PackArgs pack_args(gan_ctx* c, Net& net, const ConvLayer& cl, int Kc, int nslot, void* wp) {
   PackArgs a;
   memset(&a, 0, sizeof(a));
-  a.w = net.theta + cl.w; a.bias = (nslot > 0 && cl.bias >= 0) ? net.theta + cl.bias : nullptr;
-  a.dw = net.g + cl.w; a.dbias = (nslot > 0 && cl.bias >= 0) ? net.g + cl.bias : nullptr;
+  const bool first = &cl == &c->D.conv[0];       // the constant column carries D's first bias
+  a.w = net.theta + cl.w; a.bias = (first && cl.bias >= 0) ? net.theta + cl.bias : nullptr;
+  a.dw = net.g + cl.w; a.dbias = (first && cl.bias >= 0) ? net.g + cl.bias : nullptr;
+  if (first) { a.labels = c->labels; a.label_rows = c->label_rows; a.label_sums = c->label_sums; }
   a.pstride = net.P; a.wp = wp; a.dwp = c->dwp;
   a.L = c->L; a.CB = cl.Cb; a.CBT = cl.CBT; a.Cs = cl.Cs; a.Kc = Kc; a.nslot = nslot; a.nsplit = c->img_ksplit;
   return a;
@@ -759,8 +769,8 @@ void d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_running) 
   const float slope = c->cfg.leaky_slope;
   // first conv (+label maps, bias, LeakyReLU) as a row-by-row GEMM over the patch matrix
   const ConvLayer& c1 = D.conv[0];
-  conv_call<T>(c, "gemm_dense_img", MODE_DENSE, EPI_LRELU, c->colD, c->wpD, (long long)c1.Cs * c->KcD, c->dact[0], nullptr, c->KcD,
-               c1.Cs, 1, c1.Hs, seg_first, nseg, n, 0, img_flops(c1, n, nseg));
+  conv_call<T>(c, "gemm_dense_img", MODE_DENSE, c->labels > 0 ? EPI_LABEL_LRELU : EPI_LRELU, c->colD, c->wpD, (long long)c1.Cs * c->KcD,
+               c->dact[0], nullptr, c->KcD, c1.Cs, 1, c1.Hs, seg_first, nseg, n, 0, img_flops(c1, n, nseg));
   const int nl = (int)D.conv.size();
   for (int j = 1; j < nl; ++j) {
     const ConvLayer& cl = D.conv[j];
@@ -834,9 +844,16 @@ void d_backward(gan_ctx* c, int n, int seg_first, int nseg, bool param_grads, bo
   }
   const ConvLayer& c1 = D.conv[0];
   if (param_grads) {
-    // taps, label-map class sums and the bias gradient in one GEMM over the patch matrix
+    // taps, the bias gradient and (as indicator columns) the label maps' class sums in one GEMM over the patch matrix
     wgrad_call<T>(c, "gemm_wgrad_img", c->colD, c->bufA, c->dwp, (long long)c->KcD * c1.Cs, c->KcD, c1.Cs, c1.Hs, 1, nseg, n,
                   img_flops(c1, n, nseg), c->img_ksplit);
+    if (c->labels > 0) {
+      ClassSumArgs a;
+      memset(&a, 0, sizeof(a));
+      a.dy = c->bufA; a.part = c->class_part; a.sums = c->label_sums; a.offs = c->rb.offs; a.sample_slot = c->rb.sample_slot;
+      a.L = c->L; a.n = n; a.Hs = c1.Hs; a.Cs = c1.Cs; a.labels = c->labels; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n;
+      launch_class_sums<T>(a, c->st);
+    }
     launch_unpack_dw(pack_args(c, D, c1, c->KcD, c->nslot, c->wpD), c->st);
   }
   if (to_image)   // d cost / d fake, times the tanh derivative (fake segment only)
@@ -1376,6 +1393,15 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
     const ConvLayer& c1 = c->D.conv[0];
     const ConvLayer& gl = c->G.conv.back();
     c->img_ksplit = img_ksplit_for(L);
+    // One pair over many labels: indicator columns for every (label, class) make the patch matrix wide -- written, read by the
+    // GEMM twice and by the weight gradient, nearly all of it zeros.  Beyond LABEL_COLUMNS the maps are added as rows in the
+    // GEMM's epilogue, and their gradient comes from class sums.
+    if (c->nslot > 1 && round_up(16 * c1.Cb + 9 * c->nslot + 1, 64) > LABEL_COLUMNS) {
+      c->labels = c->nslot;
+      c->nslot = 0;
+      ok = ok && dev_alloc(c, &c->label_rows, (size_t)c->labels * 9 * c1.Cs * es) && dev_alloc(c, (void**)&c->label_sums, (size_t)c->labels * 9 * c1.Cs * 4) &&
+           dev_alloc(c, (void**)&c->class_part, (size_t)2 * NB * 9 * c1.Cs * 4);
+    }
     c->KcD = (int)round_up(16 * c1.Cb + 9 * c->nslot + 1, 64);
     c->KcG = (int)round_up(16 * gl.Cb, 64);
     const size_t d1 = (size_t)c->KcD * c1.Cs, g1 = (size_t)c->KcG * gl.Cs;
@@ -1414,7 +1440,7 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
     const ConvLayer& c1 = c->D.conv[0];
     const ConvLayer& gl = c->G.conv.back();
     const long long lim = 1LL << 31;
-    const long long big = std::max({(long long)NB * max_act * (long long)es, (long long)NB * c1.Hs * c1.Hs * c->KcD * (long long)es,
+    const long long big = std::max({(long long)NB * max_act * (long long)es, (long long)NB * c1.Hs * c1.Hs * round_up(16 * c1.Cb + 9 * (c->labels + c->nslot) + 1, 64) * (long long)es,
                                     c->paper ? 0LL : (long long)NB * gl.Hs * gl.Hs * c->KcG * (long long)es});
     if (big >= lim) {
       for (void* p : c->allocs) (void)hipFree(p);

@@ -58,7 +58,7 @@ const char* take_launch_error();   // the first reason recorded on this thread s
 // Block tiles of the forward-type GEMM kernel (rows x columns): conv_gemm.hip
 enum ConvTile { TILE_BIG = 0, TILE_MID = 1, TILE_SMALL = 2, TILE_NARROW = 3, TILE_TINY = 4 };
 enum ConvMode { MODE_DOWN = 0, MODE_UP = 1, MODE_DENSE = 2 };
-enum Epilogue { EPI_NONE = 0, EPI_ACT_BWD = 1, EPI_LRELU = 2 };
+enum Epilogue { EPI_NONE = 0, EPI_ACT_BWD = 1, EPI_LRELU = 2, EPI_LABEL_LRELU = 3 };
 enum Act { ACT_RELU = 0, ACT_LRELU = 1 };
 
 // Arguments of the grouped implicit-GEMM forward-type kernel (down / up / dense).
@@ -67,6 +67,9 @@ struct ConvArgs {
   const void* W;         // weights of model 0, K-contiguous: [tap][N][C] (storage type)
   void* Out;             // output activations (storage type)
   const void* Aux;       // EPI_ACT_BWD: saved forward output at the output position (storage type)
+  const void* label_rows;  // EPI_LABEL_LRELU: [9 * slot + position class][N] (storage type), added to the output rows of the pixels of
+                         // that class in the samples of that slot; slot of the j-th sample: sample_slot[j]
+  const int* sample_slot;
   float* stat_partial;   // if set: per sub-tile (the row block of one wave row of the tile; conv_stat_split of them per tile) the
                          // column sums of the output and of its squared deviations from the sub-tile's column mean,
                          // [(((phase * nseg + segment) * ub_tiles + tile) * split + block) * N + col][2], for the BatchNorm that follows
@@ -104,6 +107,12 @@ struct WgradArgs {
   int hs_shift;          // log2(Hs) or -1 (filled by the launcher)
   unsigned rps_inv, hs_inv;   // sides that are no power of two: reciprocals of Hs*Hs and Hs (filled by the launcher; 0: divide)
 };
+
+// Position class of pixel (y, x) of an Hs-sided map under a k4 s2 p1 filter, by which of its taps lie outside: first, inner and
+// last pixel along either axis.
+__device__ inline int pos_class(int y, int x, int Hs) {
+  return (y == 0 ? 0 : (y == Hs - 1 ? 2 : 1)) * 3 + (x == 0 ? 0 : (x == Hs - 1 ? 2 : 1));
+}
 
 template <typename T> void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st);
 template <typename T> void launch_wgrad(const WgradArgs& a, hipStream_t st);

@@ -333,7 +333,7 @@ __device__ inline int4v make_rsrc(const void* base, unsigned long long bytes) {
 // The wave-uniform part of the offset (which tap, which channels) travels in a scalar register.
 __device__ inline void load16_to_lds(const int4v& rsrc, unsigned byte_off, unsigned uniform_off, unsigned lds_base) {
   asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-               : : "v"(byte_off), "s"(rsrc), "s"(uniform_off), "s"(__builtin_amdgcn_readfirstlane((int)lds_base)) : "memory", "m0");
+               : : "v"(byte_off), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane((int)uniform_off)), "s"(__builtin_amdgcn_readfirstlane((int)lds_base)) : "memory", "m0");
 }
 // wait until at most N loads are still in flight
 template <int N>
@@ -386,7 +386,8 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void conv_gemm_k
   constexpr int BM = TL::BM, BN = TL::BN, TM = TL::TM, TN = TL::TN, PA = TL::PA, PB = TL::PB, RPP = TL::RPP;
   constexpr int KB = TL::KB, NST = TL::NST;
   constexpr int SMEM_RING = NST * (BM + BN) * KB;
-  constexpr int SMEM_EPI = BM * 8 + (TL::NT / 64) * 32 * (TN * 32 * 4 + 16);   // see the epilogue
+  constexpr int ROWTAB = EPI == EPI_LABEL_LRELU ? BM * 12 : BM * 8;            // see the epilogue
+  constexpr int SMEM_EPI = ROWTAB + (TL::NT / 64) * 32 * (TN * 32 * 4 + 16);
   constexpr int SMEM = SMEM_RING > SMEM_EPI ? SMEM_RING : SMEM_EPI;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
   unsigned char* const As = smem;                      // buffer s at As + s * BM * KB
@@ -613,12 +614,18 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void conv_gemm_k
 
   // ---- epilogue: output row index of every tile row, through LDS (the buffers are free now)
   long long* orow = reinterpret_cast<long long*>(smem);
+  int* lrow = reinterpret_cast<int*>(smem + BM * 8);                    // EPI_LABEL_LRELU: the row of label_rows it gets
   for (int t = tid; t < BM; t += TL::NT) {
     const int r = m0 + t;
     long long o = -1;
     if (r < Mrows) {
       if (MODE == MODE_DENSE) {
         o = sample_base * rps + r;
+        if (EPI == EPI_LABEL_LRELU) {
+          int n, y, x;
+          decode_row(r, Hr, rps, p.hr_shift, n, y, x);
+          lrow[t] = p.sample_slot[s0 + n] * 9 + pos_class(y, x, Hr);
+        }
       } else {
         int n, y, x;
         decode_row_yfirst(r, Hr, row_block, p.hr_shift, n, y, x);
@@ -639,8 +646,8 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void conv_gemm_k
     constexpr int WCOLS = TN * 32;
     constexpr int PSTRIDE = WCOLS * 4 + 16;                             // bytes per patch row
     constexpr int CPR = WCOLS / EPV;                                    // 16-byte output chunks per patch row
-    unsigned char* patch = smem + BM * 8 + wave * (32 * PSTRIDE);       // after the row table
-    static_assert(SMEM >= BM * 8 + (TL::NT / 64) * 32 * PSTRIDE && SMEM_EPI == BM * 8 + (TL::NT / 64) * 32 * PSTRIDE, "patch area");
+    unsigned char* patch = smem + ROWTAB + wave * (32 * PSTRIDE);       // after the row tables
+    static_assert(SMEM >= ROWTAB + (TL::NT / 64) * 32 * PSTRIDE && SMEM_EPI == ROWTAB + (TL::NT / 64) * 32 * PSTRIDE, "patch area");
     const int colw = nt * BN + wn * WCOLS;                              // first column of this wave
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
@@ -667,6 +674,16 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void conv_gemm_k
           for (int k = 0; k < EPV; k += 4) {
             const float4 t4 = *reinterpret_cast<const float4*>(patch + pr * PSTRIDE + (pc * EPV + k) * 4);
             vf[k] = t4.x; vf[k + 1] = t4.y; vf[k + 2] = t4.z; vf[k + 3] = t4.w;
+          }
+          if (EPI == EPI_LABEL_LRELU) {
+            const int lr = lrow[wm * TM * 32 + tm * 32 + pr];
+            const uint4 lraw = *reinterpret_cast<const uint4*>(static_cast<const T*>(p.label_rows) + (long long)lr * N + col);
+            const T* ll = reinterpret_cast<const T*>(&lraw);
+#pragma unroll
+            for (int k = 0; k < EPV; ++k) {
+              vf[k] += to_float(ll[k]);
+              if (!(vf[k] > 0.f)) vf[k] *= p.slope;
+            }
           }
           if (EPI == EPI_ACT_BWD) {               // times the activation's derivative, from the saved output
             const uint4 araw = *reinterpret_cast<const uint4*>(Aux + o * N + col);
@@ -768,7 +785,7 @@ template <typename T>
 void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
   // the kernel's assumptions, checked before anything is launched
   if (!a.A || !a.W || !a.Out || !a.offs || !a.tpre || a.N < 1 || a.w_nstride < a.N || a.C % (128 / (int)sizeof(T)) != 0 ||
-      (epi == EPI_ACT_BWD && !a.Aux))
+      (epi == EPI_ACT_BWD && !a.Aux) || (epi == EPI_LABEL_LRELU && (!a.label_rows || !a.sample_slot || a.L != 1)))
     return launch_fail("GEMM: null operand, or channel counts that are not whole 128-byte lines");
   if (a.N < 64) return launch_fail("GEMM: fewer than 64 output channels (image-side outputs have their own kernel)");
   {
@@ -783,13 +800,14 @@ void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
   if (mode == MODE_UP && epi == EPI_ACT_BWD) return launch_wide<T, MODE_UP, EPI_ACT_BWD>(a, st);
   if (mode == MODE_DENSE && epi == EPI_NONE) return launch_wide<T, MODE_DENSE, EPI_NONE>(a, st);
   if (mode == MODE_DENSE && epi == EPI_LRELU) return launch_wide<T, MODE_DENSE, EPI_LRELU>(a, st);
+  if (mode == MODE_DENSE && epi == EPI_LABEL_LRELU) return launch_wide<T, MODE_DENSE, EPI_LABEL_LRELU>(a, st);
   launch_fail("GEMM: (mode, epilogue) combination without an instantiation");
 }
 // Name of the kernel instantiation launch_conv picks (for per-kernel timing): mode, epilogue, tile.
 const char* conv_variant_name(int mode, int epi, const ConvArgs& a) {
   static const char* modes[3] = {"down", "up", "dense"};
-  static const char* epis[3] = {"", "+actbwd", "+lrelu"};
-  static char names[3][3][5][48];
+  static const char* epis[4] = {"", "+actbwd", "+lrelu", "+label+lrelu"};
+  static char names[3][4][5][48];
   char* n = names[mode][epi][a.tile];
   if (!n[0]) snprintf(n, 48, "gemm_%s%s<%s>", modes[mode], epis[epi], TILES[0][a.tile].name);
   return n;

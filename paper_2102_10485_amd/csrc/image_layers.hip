@@ -12,6 +12,8 @@
 // 16*CB tap columns, one indicator column per (label slot, position class) and one constant column: the packed
 // weight holds the summed label-map taps and the bias there, so the forward GEMM adds them and the weight-
 // gradient GEMM returns the class sums and the bias gradient with no extra pass over the feature tensor.
+// One pair over many labels would need a thousand such columns: there the label maps' contributions are rows that the GEMM's
+// epilogue adds (EPI_LABEL_LRELU), and their gradient comes from class sums taken directly (launch_class_sums).
 #include <stdlib.h>
 
 #include <algorithm>
@@ -27,9 +29,6 @@ template <typename T> __device__ inline float ldf(const T* p) { return to_float(
 
 // Position class along one axis: 0 = first output row/col (tap 0 outside), 1 = interior, 2 = last (tap 3 outside).
 __device__ inline bool tap_valid(int cls, int k) { return !((cls == 0 && k == 0) || (cls == 2 && k == 3)); }
-__device__ inline int pos_class(int y, int x, int Hs) {
-  return (y == 0 ? 0 : (y == Hs - 1 ? 2 : 1)) * 3 + (x == 0 ? 0 : (x == Hs - 1 ? 2 : 1));
-}
 
 __device__ inline void store8(float* p, const float (&v)[8]) {
   *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
@@ -71,7 +70,7 @@ __global__ __launch_bounds__(256) void im2col_kernel(Im2colArgs a) {
       const int iy = 2 * y - 1 + (tap >> 2), ix = 2 * x - 1 + (tap & 3);
       if ((unsigned)iy < (unsigned)Hb && (unsigned)ix < (unsigned)Hb)
         val = img ? ldf(img + ((long long)iy * Hb + ix) * a.CB + cb) : real[((long long)cb * Hb + iy) * Hb + ix];
-    } else if (a.nslot > 0) {
+    } else if (a.constant) {
       const int q = m - ntap;
       if (q < 9 * a.nslot) val = (q / 9 == a.sample_slot[j] && q % 9 == pos_class(y, x, a.Hs)) ? 1.f : 0.f;
       else if (q == 9 * a.nslot) val = 1.f;
@@ -138,7 +137,7 @@ __global__ __launch_bounds__(256) void im2col_sample_kernel(Im2colArgs a) {
   for (int t = threadIdx.x; t < 9 * gsp * 8; t += nt) {
     const int cls = t / (gsp * 8), q = t - cls * (gsp * 8);          // q: column - ntap
     float val = 0.f;
-    if (a.nslot > 0) {
+    if (a.constant) {
       if (q < 9 * a.nslot) val = (q / 9 == slot && q % 9 == cls) ? 1.f : 0.f;
       else if (q == 9 * a.nslot) val = 1.f;
     }
@@ -206,6 +205,20 @@ template <typename T> void launch_im2col(const Im2colArgs& a, hipStream_t st) {
 template void launch_im2col<float>(const Im2colArgs&, hipStream_t);
 template void launch_im2col<bf16_t>(const Im2colArgs&, hipStream_t);
 
+// the filter taps of a label's map that lie inside for the pixels of a class, summed
+__device__ inline float label_taps(const PackArgs& a, const float* w, int label, int cls, int cs) {
+  float s = 0.f;
+  for (int tap = 0; tap < 16; ++tap)
+    if (tap_valid(cls / 3, tap >> 2) && tap_valid(cls % 3, tap & 3)) s += w[((long long)tap * a.CBT + a.CB + label) * a.Cs + cs];
+  return s;
+}
+template <typename T>
+__global__ void pack_label_rows_kernel(PackArgs a) {
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= a.labels * 9 * a.Cs) return;
+  const int cs = idx % a.Cs, row = idx / a.Cs;
+  static_cast<T*>(a.label_rows)[idx] = from_float<T>(label_taps(a, a.w, row / 9, row % 9, cs));
+}
 // Wp[l][cs][m]: the taps, then the summed label-map taps per (slot, class), then the bias.
 template <typename T>
 __global__ void pack_w_kernel(PackArgs a) {
@@ -220,16 +233,11 @@ __global__ void pack_w_kernel(PackArgs a) {
   if (m < ntap) {
     const int tap = m / a.CB, cb = m - tap * a.CB;
     val = w[((long long)tap * a.CBT + cb) * a.Cs + cs];
-  } else if (a.nslot > 0) {
+  } else {
     const int q = m - ntap;
     if (q < 9 * a.nslot) {
       const int slot = q / 9, cls = q - slot * 9;
-      if (a.CBT > a.CB) {
-        const int label = (a.L == 1) ? slot : l;
-        for (int tap = 0; tap < 16; ++tap)
-          if (tap_valid(cls / 3, tap >> 2) && tap_valid(cls % 3, tap & 3))
-            val += w[((long long)tap * a.CBT + a.CB + label) * a.Cs + cs];
-      }
+      if (a.CBT > a.CB) val = label_taps(a, w, a.L == 1 ? slot : l, cls, cs);
     } else if (q == 9 * a.nslot && a.bias) {
       val = a.bias[(long long)l * a.pstride + cs];
     }
@@ -239,6 +247,7 @@ __global__ void pack_w_kernel(PackArgs a) {
 template <typename T> void launch_pack_w(const PackArgs& a, hipStream_t st) {
   const long long tot = (long long)a.L * a.Cs * a.Kc;
   hipLaunchKernelGGL((pack_w_kernel<T>), dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, a);
+  if (a.labels > 0) hipLaunchKernelGGL((pack_label_rows_kernel<T>), dim3((unsigned)((a.labels * 9 * a.Cs + 255) / 256)), dim3(256), 0, st, a);
 }
 template void launch_pack_w<float>(const PackArgs&, hipStream_t);
 template void launch_pack_w<bf16_t>(const PackArgs&, hipStream_t);
@@ -256,8 +265,9 @@ __global__ void unpack_dw_kernel(PackArgs a) {
   const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const int Cs = a.Cs;
   const long long n_tap = (long long)a.L * 16 * a.CB * Cs;
-  const long long n_lab = (a.nslot > 0 && a.CBT > a.CB) ? (long long)a.L * a.nslot * 16 * Cs : 0;
-  const long long n_bias = (a.nslot > 0 && a.dbias) ? (long long)a.L * Cs : 0;
+  const int slots = a.labels > 0 ? a.labels : a.nslot;
+  const long long n_lab = a.CBT > a.CB ? (long long)a.L * slots * 16 * Cs : 0;
+  const long long n_bias = a.dbias ? (long long)a.L * Cs : 0;
   const int ntap = 16 * a.CB;
   if (idx < n_tap) {
     const int cs = (int)(idx % Cs);
@@ -271,13 +281,13 @@ __global__ void unpack_dw_kernel(PackArgs a) {
   if (j < n_lab) {
     const int cs = (int)(j % Cs);
     const int tap = (int)((j / Cs) % 16);
-    const int slot = (int)((j / ((long long)Cs * 16)) % a.nslot);
-    const int l = (int)(j / ((long long)Cs * 16 * a.nslot));
+    const int slot = (int)((j / ((long long)Cs * 16)) % slots);
+    const int l = (int)(j / ((long long)Cs * 16 * slots));
     const int label = (a.L == 1) ? slot : l;
     float s = 0.f;
     for (int cls = 0; cls < 9; ++cls)
       if (tap_valid(cls / 3, tap >> 2) && tap_valid(cls % 3, tap & 3))
-        s += dwp_at(a, l, ntap + slot * 9 + cls, cs);
+        s += a.labels > 0 ? a.label_sums[((long long)slot * 9 + cls) * Cs + cs] : dwp_at(a, l, ntap + slot * 9 + cls, cs);
     a.dw[(long long)l * a.pstride + ((long long)tap * a.CBT + a.CB + label) * Cs + cs] = s;
     return;
   }
@@ -320,9 +330,100 @@ void launch_unpack_dw(const PackArgs& a0, hipStream_t st) {
                        a.nsplit);
     a.nsplit = 1;
   }
-  const long long tot = (long long)a.L * a.Cs * (16 * a.CB + (a.nslot > 0 ? a.nslot * 16 + 1 : 0));
+  const long long tot = (long long)a.L * a.Cs * (16 * a.CB + (a.labels > 0 ? a.labels : a.nslot) * 16 + 1);
   hipLaunchKernelGGL(unpack_dw_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, a);
 }
+
+// Class sums of a layer's output gradient, for label maps without indicator columns.  First per sample: a block takes one sample
+// of one segment and up to 128 channels, a thread 8 channels of every 16th pixel row; inner rows meet in LDS, in a fixed order.
+// It reads the tensor once, 16 bytes a lane, and is bound by that.  Then per slot: a thread owns one sum and adds
+// the slot's samples in order.
+template <typename T>
+__global__ __launch_bounds__(256) void class_sums_sample_kernel(ClassSumArgs a) {
+  __shared__ float inner[16][3][128];
+  const int j = blockIdx.x, sidx = blockIdx.y, c0 = blockIdx.z * 128;
+  if (j >= a.offs[a.L]) return;
+  const int g = threadIdx.x & 15, lane = threadIdx.x >> 4;              // channels c0 + 8 g .., pixel rows lane, lane + 16, ..
+  const int c = c0 + 8 * g, H = a.Hs, Cs = a.Cs;
+  const bool have = c < Cs;                                             // Cs is a multiple of 64
+  const T* dy = static_cast<const T*>(a.dy) + ((long long)(a.seg_first + sidx) * a.seg_samples + j) * H * H * Cs + c;
+  float* out = a.part + ((long long)sidx * a.n + j) * 9 * Cs;
+  float mid[3][8] = {};
+  if (have)
+    for (int y = lane; y < H; y += 16) {
+      float s[3][8] = {};
+      const auto add = [&](int x, int cls) __attribute__((always_inline)) {
+        alignas(16) T v[8];
+        const uint4* q = reinterpret_cast<const uint4*>(dy + ((long long)y * H + x) * Cs);
+        uint4* d = reinterpret_cast<uint4*>(v);
+        d[0] = q[0];
+        if constexpr (sizeof(T) == 4) d[sizeof(T) / 4] = q[1];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s[cls][k] += to_float(v[k]);
+      };
+      add(0, 0);
+#pragma unroll 4
+      for (int x = 1; x < H - 1; ++x) add(x, 1);
+      if (H > 1) add(H - 1, 2);
+      const int row = y == 0 ? 0 : (y == H - 1 ? 2 : 1);
+#pragma unroll
+      for (int cls = 0; cls < 3; ++cls)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          if (row == 1) mid[cls][k] += s[cls][k];
+          else out[(row * 3 + cls) * Cs + c + k] = s[cls][k];
+          if (H == 1) out[(6 + cls) * Cs + c + k] = 0.f;                // no last row
+        }
+    }
+#pragma unroll
+  for (int cls = 0; cls < 3; ++cls)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) inner[lane][cls][8 * g + k] = mid[cls][k];
+  __syncthreads();
+  for (int t = threadIdx.x; t < 3 * 128; t += 256) {
+    const int cls = t >> 7, cc = t & 127;
+    float s = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s += inner[r][cls][cc];
+    if (c0 + cc < Cs) out[(3 + cls) * Cs + c0 + cc] = s;
+  }
+}
+__global__ __launch_bounds__(256) void class_sums_slot_kernel(ClassSumArgs a) {
+  __shared__ int list[256];
+  __shared__ int wave_n[4];
+  const int slot = blockIdx.x, per = 9 * a.Cs, e = blockIdx.y * 256 + threadIdx.x;
+  const int n = a.offs[a.L], wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  float s = 0.f;
+  for (int sidx = 0; sidx < a.nseg; ++sidx)
+    for (int j0 = 0; j0 < n; j0 += 256) {
+      const int j = j0 + threadIdx.x;
+      const bool mine = j < n && a.sample_slot[j] == slot;
+      const unsigned long long votes = __ballot(mine);
+      if (lane == 0) wave_n[wave] = __popcll(votes);
+      __syncthreads();
+      int at = 0, total = 0;
+      for (int w = 0; w < 4; ++w) {
+        if (w < wave) at += wave_n[w];
+        total += wave_n[w];
+      }
+      if (mine) list[at + __popcll(votes & ((1ull << lane) - 1))] = j;
+      __syncthreads();
+      if (e < per) {
+        const float* p = a.part + (long long)sidx * a.n * per + e;
+#pragma unroll 4
+        for (int i = 0; i < total; ++i) s += p[(long long)list[i] * per];
+      }
+      __syncthreads();
+    }
+  if (e < per) a.sums[(long long)slot * per + e] = s;
+}
+template <typename T> void launch_class_sums(const ClassSumArgs& a, hipStream_t st) {
+  if (a.n < 1 || a.Cs % 64 != 0) return launch_fail("class sums: no samples, or channels that are no multiple of 64");
+  hipLaunchKernelGGL((class_sums_sample_kernel<T>), dim3((unsigned)a.n, (unsigned)a.nseg, (unsigned)((a.Cs + 127) / 128)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(class_sums_slot_kernel, dim3((unsigned)a.labels, (unsigned)((9 * a.Cs + 255) / 256)), dim3(256), 0, st, a);
+}
+template void launch_class_sums<float>(const ClassSumArgs&, hipStream_t);
+template void launch_class_sums<bf16_t>(const ClassSumArgs&, hipStream_t);
 
 // dbias[cb] = sum over the model's image-side pixels (G's last layer): block (chunk of pixels, model) partial
 // sums, then one small pass adds the chunks in order.

@@ -91,7 +91,8 @@ struct Im2colArgs {
   const int* offs;
   const int* sample_slot;
   int L, n, CB, Hs, Kc;
-  int nslot;                // 0: tap columns only ; > 0: + 9*nslot class indicators + one constant column
+  int nslot;                // class indicators behind the tap columns: 9 * nslot
+  int constant;             // 1: one constant column behind those
   int seg, seg_samples;     // absolute segment of both the source tensor and the output rows
 };
 template <typename T> void launch_im2col(const Im2colArgs& a, hipStream_t st);
@@ -104,8 +105,22 @@ struct PackArgs {
   long long pstride;
   void* wp;                 // pack: [L][Cs][Kc] storage type
   const float* dwp;         // unpack: [nsplit][L][Kc][Cs] fp32 partial blocks
+  // Without indicator columns (nslot == 0, one model): the label maps of `labels` slots as rows to add to the output
+  int labels;
+  void* label_rows;         // pack: [labels][9][Cs] storage type
+  const float* label_sums;  // unpack: [labels][9][Cs], the sums of the layer's output gradient
   int L, CB, CBT, Cs, Kc, nslot, nsplit;
 };
+// sums[slot][class][cs] = sum of dy over the samples of the slot (both segments, in order) and the pixels of the class
+struct ClassSumArgs {
+  const void* dy;           // [rows][Cs] storage type, rows indexed by absolute sample
+  float* part;              // scratch [nseg][n][9][Cs]
+  float* sums;              // [labels][9][Cs]
+  const int* offs;
+  const int* sample_slot;
+  int L, n, Hs, Cs, labels, seg_first, nseg, seg_samples;
+};
+template <typename T> void launch_class_sums(const ClassSumArgs& a, hipStream_t st);
 template <typename T> void launch_pack_w(const PackArgs& a, hipStream_t st);
 void launch_unpack_dw(const PackArgs& a, hipStream_t st);
 

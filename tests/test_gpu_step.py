@@ -189,6 +189,21 @@ def test_single_conditional_pair_over_twenty_labels(prec):
 
 
 @pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+def test_conditional_pair_with_more_samples_than_a_class_sum_takes_at_once(prec):
+    """Twenty labels' maps are rows added behind D's first convolution, their gradient comes from sums per (label, position
+    class) in passes of 256 samples: one pass and a remainder, labels that fill it, occur once, or not at all."""
+    p = Pair("tiny20", 1, 20, 300, prec)
+    rng = np.random.default_rng(9)
+    lab = rng.choice([0, 3, 3, 3, 7, 19], 300)
+    lab[257] = 11
+    p.step(*batch(p.spec, lab, 520))
+    p.compare("300 samples")
+    p.step(*batch(p.spec, np.full(259, 19), 521))
+    p.compare("one label only")
+    p.close()
+
+
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
 def test_single_unconditional_pair(prec):
     """The paper's DC-GAN comparison system (Tables 1 and 2) at test size: one pair, no label anywhere (one label,
     no conditioning), a batch of several hundred so that every weight gradient is split over rows and summed in a
