@@ -15,9 +15,9 @@
 // product, see Split8); accumulation is fp32 in both cases.
 // Forward-type kernel: K-chunks of KB bytes per row travel global -> LDS directly (buffer_load_dwordx4 ... lds, no
 // registers in between) into a ring of NST buffers while the MFMAs of the current chunk run.  In bf16 the 256 x 256 tile uses
-// KB = 128 with two buffers (one block per CU); the 256 x 128 and 128 x 128 tiles use KB = 64 with three, which leaves
-// room for two blocks per CU so that one block's epilogue and barriers hide behind the other's MFMAs; the 256 x 64
-// tile fits two blocks per CU with KB = 128 and two buffers.  The 16-byte chunk c of row
+// KB = 128 with two buffers (one block per CU); the 256 x 128 tile uses KB = 64 with three, which leaves room for two blocks
+// per CU, so that one block's epilogue and barriers hide behind the other's MFMAs; the smaller ones: see FwdTiles.
+// The 16-byte chunk c of row
 // R sits at position c ^ ((R / (256/KB)) % (KB/16)), which keeps both the 1 KiB-per-wave copies and the MFMA operand
 // reads conflict-free.
 // One barrier per chunk in both.
@@ -49,11 +49,17 @@ template <typename T> struct FwdTiles;
 template <> struct FwdTiles<bf16_t> {
   typedef Tile<256, 256, 2, 4, 128, 2> Big;      // 512 threads, wave tile 128 x 64, 128 KiB of LDS
   typedef Tile<256, 128, 4, 2, 64, 3> Mid;       // 512 threads, wave tile 64 x 64, 72 KiB of LDS
-  typedef Tile<128, 128, 2, 2, 64, 3> Small;     // 256 threads, wave tile 64 x 64 (few rows per model), 48 KiB of LDS
+  typedef Tile<128, 128, 2, 2, 128, 2> Small;    // 256 threads, wave tile 64 x 64 (few rows per model), 64 KiB of LDS
   typedef Tile<256, 64, 4, 1, 128, 2> Narrow;    // 256 threads, wave tile 64 x 64, for layers with 64 output channels:
                                                  // 128-byte chunks, two buffers of 40 KiB, so two blocks still share a CU
-  typedef Tile<64, 64, 2, 2, 64, 3> Tiny;        // 256 threads, wave tile 32 x 32, 24 KiB of LDS: workloads so small that
+  typedef Tile<256, 64, 4, 1, 64, 2> NarrowUp;   // the same with two buffers of 20 KiB, for MODE_UP: its reductions are a quarter as
+                                                 // long, and what a block waits for before it can multiply weighs more
+  typedef Tile<64, 64, 2, 2, 128, 2> Tiny;       // 256 threads, wave tile 32 x 32, 32 KiB of LDS: workloads so small that
                                                  // the larger tiles would leave most of the chip without a block
+  // Chunk sizes, in TFLOP/s, 128-byte x 2 against 64-byte x 3: 64x64 down 64 -> 128 channels at side 7, one model of 64 samples, 76
+  // against 63, 64 -> 64 at side 8, 100 models, 453 against 359; 128x128 down 64 -> 128 at side 7, ten models, 541 against 495.
+  // 256x64: up 128 -> 64 at side 16 480 against 582 with 64-byte x 2, up 64 -> 64 at side 8 401 against 438, but down 64 -> 64 at
+  // side 8 586 against 422.
 };
 // fp32 is bound by the matrix and vector pipes together, so more than 128 x 128 brings nothing: 20 x 64 samples, 128 -> 256
 // channels at side 8, in TFLOP/s: 128x128 172, 256x128 162 (eight waves of 64 x 64) and 154 (four of 128 x 64, one wave per SIMD),
@@ -61,6 +67,7 @@ template <> struct FwdTiles<bf16_t> {
 template <> struct FwdTiles<float> {
   typedef Tile<128, 128, 2, 2, 128, 2> Small;    // 256 threads, wave tile 64 x 64, 64 KiB of LDS
   typedef Tile<256, 64, 4, 1, 128, 2> Narrow;    // 256 threads, wave tile 64 x 64, 80 KiB
+  typedef Narrow NarrowUp;
   typedef Tile<64, 64, 2, 2, 128, 2> Tiny;       // 256 threads, wave tile 32 x 32, 32 KiB
 };
 
@@ -72,8 +79,8 @@ template <typename TL> constexpr TileInfo info(ConvTile id, const char* name, in
 }
 static const TileInfo TILES[2][5] = {
     {info<FwdTiles<bf16_t>::Big>(TILE_BIG, "256x256", 1, 1.0), info<FwdTiles<bf16_t>::Mid>(TILE_MID, "256x128", 2, 0.88),
-     info<FwdTiles<bf16_t>::Small>(TILE_SMALL, "128x128", 3, 0.75), info<FwdTiles<bf16_t>::Narrow>(TILE_NARROW, "256x64", 2, 0.70),
-     info<FwdTiles<bf16_t>::Tiny>(TILE_TINY, "64x64", 6, 0.43)},
+     info<FwdTiles<bf16_t>::Small>(TILE_SMALL, "128x128", 2, 0.77), info<FwdTiles<bf16_t>::Narrow>(TILE_NARROW, "256x64", 2, 0.70),
+     info<FwdTiles<bf16_t>::Tiny>(TILE_TINY, "64x64", 5, 0.52)},
     {{TILE_BIG, "", 0, 0, 0, 0, 0}, {TILE_MID, "", 0, 0, 0, 0, 0},
      info<FwdTiles<float>::Small>(TILE_SMALL, "128x128", 2, 1.0), info<FwdTiles<float>::Narrow>(TILE_NARROW, "256x64", 2, 0.95),
      info<FwdTiles<float>::Tiny>(TILE_TINY, "64x64", 5, 0.64)},
@@ -336,8 +343,9 @@ static int log2_or_neg(int v) {
   return -1;
 }
 
-// Waves a SIMD should hold, which bounds the registers: two for fp32 wave tiles of 64 x 64 with their two accumulators.
-template <typename T, typename TL> constexpr int waves_per_simd() { return sizeof(T) == 4 && TL::TM * TL::TN == 4 ? 2 : 1; }
+// Waves a SIMD should hold at least, which bounds the registers.  Wave tiles of 64 x 64: two (fp32 needs about 200 registers for its
+// two accumulators; without the bound bf16 takes 171, half of them accumulation registers, and with it 107, four waves).
+template <typename T, typename TL> constexpr int waves_per_simd() { return TL::TM * TL::TN == 4 ? 2 : 1; }
 template <typename T, int MODE, int EPI, typename TL>
 __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void conv_gemm_kernel(ConvArgs p) {
   constexpr int BM = TL::BM, BN = TL::BN, TM = TL::TM, TN = TL::TN, PA = TL::PA, PB = TL::PB, RPP = TL::RPP;
@@ -732,7 +740,8 @@ static void launch_wide(const ConvArgs& a, hipStream_t st) {
     if (a.tile == TILE_MID) return launch_one<T, MODE, EPI, typename Tiles::Mid>(a, st);
   }
   if (a.tile == TILE_SMALL) return launch_one<T, MODE, EPI, typename Tiles::Small>(a, st);
-  if (a.tile == TILE_NARROW) return launch_one<T, MODE, EPI, typename Tiles::Narrow>(a, st);
+  if (a.tile == TILE_NARROW)
+    return launch_one<T, MODE, EPI, std::conditional_t<MODE == MODE_UP, typename Tiles::NarrowUp, typename Tiles::Narrow>>(a, st);
   if (a.tile == TILE_TINY) return launch_one<T, MODE, EPI, typename Tiles::Tiny>(a, st);
   launch_fail("GEMM: a tile that this storage type does not have");
 }
