@@ -52,8 +52,8 @@ template <> struct FwdTiles<bf16_t> {
   typedef Tile<128, 128, 2, 2, 128, 2> Small;    // 256 threads, wave tile 64 x 64 (few rows per model), 64 KiB of LDS
   typedef Tile<256, 64, 4, 1, 128, 2> Narrow;    // 256 threads, wave tile 64 x 64, for layers with 64 output channels:
                                                  // 128-byte chunks, two buffers of 40 KiB, so two blocks still share a CU
-  typedef Tile<256, 64, 4, 1, 64, 2> NarrowUp;   // the same with two buffers of 20 KiB, for MODE_UP: its reductions are a quarter as
-                                                 // long, and what a block waits for before it can multiply weighs more
+  typedef Tile<256, 64, 4, 1, 64, 2> NarrowShort;  // the same with two buffers of 20 KiB for MODE_UP and MODE_DENSE: their reductions are
+                                                 // short, and what a block waits for before it can multiply weighs more
   typedef Tile<64, 64, 2, 2, 128, 2> Tiny;       // 256 threads, wave tile 32 x 32, 32 KiB of LDS: workloads so small that
                                                  // the larger tiles would leave most of the chip without a block
   // Chunk sizes, in TFLOP/s, 128-byte x 2 against 64-byte x 3: 64x64 down 64 -> 128 channels at side 7, one model of 64 samples, 76
@@ -67,7 +67,7 @@ template <> struct FwdTiles<bf16_t> {
 template <> struct FwdTiles<float> {
   typedef Tile<128, 128, 2, 2, 128, 2> Small;    // 256 threads, wave tile 64 x 64, 64 KiB of LDS
   typedef Tile<256, 64, 4, 1, 128, 2> Narrow;    // 256 threads, wave tile 64 x 64, 80 KiB
-  typedef Narrow NarrowUp;
+  typedef Narrow NarrowShort;
   typedef Tile<64, 64, 2, 2, 128, 2> Tiny;       // 256 threads, wave tile 32 x 32, 32 KiB
 };
 
@@ -741,7 +741,7 @@ static void launch_wide(const ConvArgs& a, hipStream_t st) {
   }
   if (a.tile == TILE_SMALL) return launch_one<T, MODE, EPI, typename Tiles::Small>(a, st);
   if (a.tile == TILE_NARROW)
-    return launch_one<T, MODE, EPI, std::conditional_t<MODE == MODE_UP, typename Tiles::NarrowUp, typename Tiles::Narrow>>(a, st);
+    return launch_one<T, MODE, EPI, std::conditional_t<MODE != MODE_DOWN, typename Tiles::NarrowShort, typename Tiles::Narrow>>(a, st);
   if (a.tile == TILE_TINY) return launch_one<T, MODE, EPI, typename Tiles::Tiny>(a, st);
   launch_fail("GEMM: a tile that this storage type does not have");
 }
