@@ -575,6 +575,7 @@ void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, c
   a.w_stride = wstride; a.L = c->L; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n;
   a.C = C; a.N = N; a.Hin = Hin; a.Hr = Hr; a.ub_tiles = ub_tiles(c, n, Hr * Hr, tr);
   a.slope = c->cfg.leaky_slope;
+  if (epi == EPI_DROP_BWD) a.drop_scale = 1.0f / (1.0f - c->cfg.dropout_p);
   a.stat_partial = stats ? c->stat_partial : nullptr;
   if (epi == EPI_LABEL_LRELU) { a.label_rows = c->label_rows; a.sample_slot = c->rb.sample_slot; }
   const int ntaps = mode == MODE_DOWN ? 16 : (mode == MODE_UP ? 4 : 1);
@@ -913,12 +914,13 @@ PointArgs point_args(gan_ctx* c, void* x, int C, int Cpad, int HW, int seg_first
   a.seed_lo = (unsigned)(c->cfg.seed & 0xffffffffull); a.seed_hi = (unsigned)(c->cfg.seed >> 32);
   return a;
 }
+float dropout_scale(const gan_ctx* c) { return 1.0f / (1.0f - c->cfg.dropout_p); }
 // dropout of D's block `layer` (1-based) in the passes pass0 (first processed segment) and pass0 + 1
 void with_dropout(gan_ctx* c, PointArgs& a, int layer, int pass0, int step_add) {
   const float p = c->cfg.dropout_p;
   if (!(p > 0.f)) return;
   a.thr = (unsigned)ceil((double)p * 16777216.0);
-  a.scale = 1.0f / (1.0f - p);
+  a.scale = dropout_scale(c);
   a.layer = layer; a.pass_of_seg[0] = pass0; a.pass_of_seg[1] = pass0 + 1;
   a.steps = c->D.t; a.step_add = step_add;
 }
@@ -1027,26 +1029,18 @@ void paper_d_backward(gan_ctx* c, int n, int seg_first, int nseg, bool param_gra
     NormArgs na = norm_args<T>(c, D, cl.Cs, cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->d_mean[j], c->d_var[j], c->d_rstd[j],
                                c->d_sums[j], seg_first, nseg, n, 1.f);
     na.eps = f.bn_eps;
-    bn_backward<T>(c, na, c->dpre[j], c->bufA, c->bufB, param_grads);         // -> gradient w.r.t. the dropped activations
-    PointArgs a = point_args(c, c->bufB, cl.cs_real, cl.Cs, cl.Hs * cl.Hs, seg_first, nseg, n);
-    a.saved = c->dpre[j]; a.slope = f.leaky_slope;
-    with_dropout(c, a, j + 1, pass0, step_add);
-    { Scope s(c, "act_dropout_bwd", 0, 3.0 * n * nseg * cl.Hs * cl.Hs * cl.cs_real * sizeof(T)); launch_point_bwd<T>(a, c->st); }
+    na.pre_act = 1; na.pre_slope = f.leaky_slope; na.pre_drop = f.dropout_p > 0.f; na.pre_scale = dropout_scale(c);
+    bn_backward<T>(c, na, c->dpre[j], c->bufA, c->bufB, param_grads);         // -> gradient w.r.t. the convolution's output
     if (param_grads) {
+      const PointArgs a = point_args(c, c->bufB, cl.cs_real, cl.Cs, cl.Hs * cl.Hs, seg_first, nseg, n);
       launch_col_sum<T>(a, D.g + cl.bias, D.P, c->st);
       wgrad_call<T>(c, "gemm_wgrad", c->dact[j - 1], c->bufB, D.g + cl.w, D.P, cl.Cb, cl.Cs, cl.Hs, 16, nseg, n);
     }
-    conv_call<T>(c, "gemm_up", MODE_UP, j == 1 ? EPI_ACT_BWD : EPI_NONE, c->bufB, (const T*)D.shadow_u + cl.w, D.P, c->bufA,
+    const int first = f.dropout_p > 0.f ? EPI_DROP_BWD : EPI_ACT_BWD;         // the first block's LeakyReLU and dropout
+    conv_call<T>(c, "gemm_up", MODE_UP, j == 1 ? first : EPI_NONE, c->bufB, (const T*)D.shadow_u + cl.w, D.P, c->bufA,
                  j == 1 ? c->dact[0] : nullptr, cl.Cs, cl.Cb, cl.Hs, cl.Hs, seg_first, nseg, n);
   }
   const ConvLayer& c1 = D.conv[0];
-  if (f.dropout_p > 0.f) {      // the first block's dropout (its LeakyReLU derivative came with the data gradient above)
-    PointArgs a = point_args(c, c->bufA, c1.cs_real, c1.Cs, c1.Hs * c1.Hs, seg_first, nseg, n);
-    a.saved = c->dact[0];
-    with_dropout(c, a, 1, pass0, step_add);
-    Scope s(c, "act_dropout_bwd", 0, 2.0 * n * nseg * c1.Hs * c1.Hs * c1.cs_real * sizeof(T));
-    launch_point_bwd<T>(a, c->st);
-  }
   if (param_grads) {
     wgrad_call<T>(c, "gemm_wgrad_img", c->colD, c->bufA, c->dwp, (long long)c->KcD * c1.Cs, c->KcD, c1.Cs, c1.Hs, 1, nseg, n,
                   img_flops(c1, n, nseg), c->img_ksplit);
@@ -1092,10 +1086,9 @@ void paper_g_backward(gan_ctx* c, int n) {
   NormArgs na = norm_args<T>(c, G, G.C0, G.h0 * G.h0, G.fc_gamma, G.fc_beta, G.fc_rs, c->g_mean[0], c->g_var[0], c->g_rstd[0],
                              c->g_sums[0], 0, 1, n, 1.f);
   na.eps = f.bn_eps_first;
+  na.pre_act = 1; na.pre_slope = 0.f; na.pre_scale = 1.f;                     // ReLU derivative from the stored output
   bn_backward<T>(c, na, c->gpre[0], c->bufA, c->bufB, true);
-  PointArgs a = point_args(c, c->bufB, G.J, G.J, 1, 0, 1, n);                 // ReLU derivative from the stored output
-  a.saved = c->gpre[0]; a.slope = 0.f;
-  { Scope s(c, "act_dropout_bwd", 0, 3.0 * n * G.J * sizeof(T)); launch_point_bwd<T>(a, c->st); }
+  const PointArgs a = point_args(c, c->bufB, G.J, G.J, 1, 0, 1, n);
   launch_col_sum<T>(a, G.g + G.fc_bias, G.P, c->st);
   wgrad_call<T>(c, "gemm_wgrad_dense", c->bufB, c->zin, G.g + G.fc_w, G.P, G.J, G.Kp, 1, 1, 1, n);
 }

@@ -58,7 +58,7 @@ const char* take_launch_error();   // the first reason recorded on this thread s
 // Block tiles of the forward-type GEMM kernel (rows x columns): conv_gemm.hip
 enum ConvTile { TILE_BIG = 0, TILE_MID = 1, TILE_SMALL = 2, TILE_NARROW = 3, TILE_TINY = 4 };
 enum ConvMode { MODE_DOWN = 0, MODE_UP = 1, MODE_DENSE = 2 };
-enum Epilogue { EPI_NONE = 0, EPI_ACT_BWD = 1, EPI_LRELU = 2, EPI_LABEL_LRELU = 3 };
+enum Epilogue { EPI_NONE = 0, EPI_ACT_BWD = 1, EPI_LRELU = 2, EPI_LABEL_LRELU = 3, EPI_DROP_BWD = 4 };
 enum Act { ACT_RELU = 0, ACT_LRELU = 1 };
 
 // Arguments of the grouped implicit-GEMM forward-type kernel (down / up / dense).
@@ -66,7 +66,7 @@ struct ConvArgs {
   const void* A;         // gathered activations (storage type)
   const void* W;         // weights of model 0, K-contiguous: [tap][N][C] (storage type)
   void* Out;             // output activations (storage type)
-  const void* Aux;       // EPI_ACT_BWD: saved forward output at the output position (storage type)
+  const void* Aux;       // EPI_ACT_BWD, EPI_DROP_BWD: saved forward output at the output position (storage type)
   const void* label_rows;  // EPI_LABEL_LRELU: [9 * slot + position class][N] (storage type), added to the output rows of the pixels of
                          // that class in the samples of that slot; slot of the j-th sample: sample_slot[j]
   const int* sample_slot;
@@ -87,7 +87,8 @@ struct ConvArgs {
   int ub_tiles;          // launched upper bound of M-tiles per (segment, phase)
   ConvTile tile;         // its height is what the prefix array was built for
   int hr_shift;          // log2(Hr) or -1 (filled by the launcher)
-  float slope;           // EPI_ACT_BWD: derivative on the non-positive side
+  float slope;           // EPI_ACT_BWD, EPI_DROP_BWD: derivative on the non-positive side
+  float drop_scale;      // EPI_DROP_BWD: 1 / (1 - p); where the saved output is +0 the element was dropped (see dropped())
 };
 
 // Arguments of the grouped weight-gradient kernel: dW[tap][cb][cs] = sum_rows big(tap)[cb] * small[cs].
@@ -107,6 +108,12 @@ struct WgradArgs {
   int hs_shift;          // log2(Hs) or -1 (filled by the launcher)
   unsigned rps_inv, hs_inv;   // sides that are no power of two: reciprocals of Hs*Hs and Hs (filled by the launcher; 0: divide)
 };
+
+// Dropout writes +0 where it drops; a kept value that is or rounds to zero is stored as -0.  The backward pass reads the mask
+// off the stored tensor.
+__host__ __device__ inline float kept_nonzero(float v) { return v == 0.f ? -0.f : v; }
+__host__ __device__ inline bf16_t kept_nonzero(bf16_t v) { v.v = v.v == 0 ? 0x8000 : v.v; return v; }
+__device__ inline bool dropped(float saved) { return __float_as_uint(saved) == 0; }
 
 // Position class of pixel (y, x) of an Hs-sided map under a k4 s2 p1 filter, by which of its taps lie outside: first, inner and
 // last pixel along either axis.

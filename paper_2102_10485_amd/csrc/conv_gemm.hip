@@ -650,12 +650,16 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void conv_gemm_k
               if (!(vf[k] > 0.f)) vf[k] *= p.slope;
             }
           }
-          if (EPI == EPI_ACT_BWD) {               // times the activation's derivative, from the saved output
+          if (EPI == EPI_ACT_BWD || EPI == EPI_DROP_BWD) {      // times the activation's derivative (and the dropout), from the saved output
             const uint4 araw = *reinterpret_cast<const uint4*>(Aux + o * N + col);
             const T* aa = reinterpret_cast<const T*>(&araw);
 #pragma unroll
             for (int k = 0; k < EPV; ++k)
-              if (!(to_float(aa[k]) > 0.f)) vf[k] *= p.slope;
+            {
+              const float s = to_float(aa[k]);
+              if (!(s > 0.f)) vf[k] *= p.slope;
+              if (EPI == EPI_DROP_BWD) vf[k] = dropped(s) ? 0.f : vf[k] * p.drop_scale;
+            }
           }
           uint4 vraw;
           if constexpr (sizeof(T) == 2) {
@@ -751,7 +755,7 @@ template <typename T>
 void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
   // the kernel's assumptions, checked before anything is launched
   if (!a.A || !a.W || !a.Out || !a.offs || !a.tpre || a.N < 1 || a.w_nstride < a.N || a.C % (128 / (int)sizeof(T)) != 0 ||
-      (epi == EPI_ACT_BWD && !a.Aux) || (epi == EPI_LABEL_LRELU && (!a.label_rows || !a.sample_slot || a.L != 1)))
+      ((epi == EPI_ACT_BWD || epi == EPI_DROP_BWD) && !a.Aux) || (epi == EPI_LABEL_LRELU && (!a.label_rows || !a.sample_slot || a.L != 1)))
     return launch_fail("GEMM: null operand, or channel counts that are not whole 128-byte lines");
   if (a.N < 64) return launch_fail("GEMM: fewer than 64 output channels (image-side outputs have their own kernel)");
   {
@@ -764,6 +768,7 @@ void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
   if (mode == MODE_DOWN && epi == EPI_NONE) return launch_wide<T, MODE_DOWN, EPI_NONE>(a, st);
   if (mode == MODE_UP && epi == EPI_NONE) return launch_wide<T, MODE_UP, EPI_NONE>(a, st);
   if (mode == MODE_UP && epi == EPI_ACT_BWD) return launch_wide<T, MODE_UP, EPI_ACT_BWD>(a, st);
+  if (mode == MODE_UP && epi == EPI_DROP_BWD) return launch_wide<T, MODE_UP, EPI_DROP_BWD>(a, st);
   if (mode == MODE_DENSE && epi == EPI_NONE) return launch_wide<T, MODE_DENSE, EPI_NONE>(a, st);
   if (mode == MODE_DENSE && epi == EPI_LRELU) return launch_wide<T, MODE_DENSE, EPI_LRELU>(a, st);
   if (mode == MODE_DENSE && epi == EPI_LABEL_LRELU) return launch_wide<T, MODE_DENSE, EPI_LABEL_LRELU>(a, st);
@@ -772,8 +777,8 @@ void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
 // Name of the kernel instantiation launch_conv picks (for per-kernel timing): mode, epilogue, tile.
 const char* conv_variant_name(int mode, int epi, const ConvArgs& a) {
   static const char* modes[3] = {"down", "up", "dense"};
-  static const char* epis[4] = {"", "+actbwd", "+lrelu", "+label+lrelu"};
-  static char names[3][4][5][48];
+  static const char* epis[5] = {"", "+actbwd", "+lrelu", "+label+lrelu", "+dropbwd"};
+  static char names[3][5][5][48];
   char* n = names[mode][epi][a.tile];
   if (!n[0]) snprintf(n, 48, "gemm_%s%s<%s>", modes[mode], epis[epi], TILES[0][a.tile].name);
   return n;

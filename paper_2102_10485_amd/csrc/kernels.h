@@ -66,6 +66,10 @@ struct NormArgs {
   int n;                    // samples per segment passed by the caller (upper bound of offs[L])
   int act;                  // ACT_RELU / ACT_LRELU
   float slope, eps, momentum;
+  // bwd apply, networks whose BatchNorm follows an activation: x is that activation's (and dropout's) result, and the gradient goes
+  // on through both, to the convolution's output
+  int pre_act, pre_drop;    // pre_drop: x is +0 where dropped (see dropped())
+  float pre_slope, pre_scale;
   int fold_running;         // statistics from the GEMM's partials, one segment: that kernel also updates the running statistics
   int fold_grads;           // backward reduction, one segment: its last stage also writes dgamma / dbeta
 };
@@ -251,8 +255,7 @@ void launch_dw4_to_dw3(const float* dw4, float* dw3, int n_groups, int cb, int c
 // One pass over a stored NHWC tensor whose samples are grouped by model: rows of sample j (model-major) are HW pixels
 // of Cpad channels, of which the first C are real (the rest is channel padding and is left alone).
 struct PointArgs {
-  void* x;                  // forward: the layer output, in place ; backward: the gradient, in place ; sums: the tensor
-  const void* saved;        // backward: the forward result at the same positions
+  void* x;                  // forward: the layer output, in place ; sums: the tensor
   const float* bias;        // forward: [C] of model 0, pstride between models (may be NULL)
   long long pstride;
   const int* offs;
@@ -269,7 +272,6 @@ struct PointArgs {
   unsigned seed_lo, seed_hi;
 };
 template <typename T> void launch_point_fwd(const PointArgs& a, hipStream_t st);     // x <- dropout(act(x + bias))
-template <typename T> void launch_point_bwd(const PointArgs& a, hipStream_t st);     // g <- g * keep * scale * act'(saved)
 // out[l * out_stride + c] = sum over the segments and rows of model l of x[.., c]
 template <typename T> void launch_col_sum(const PointArgs& a, float* out, long long out_stride, hipStream_t st);
 // batch statistics (mean, biased variance, 1/sqrt(var + eps)) of a stored tensor with Cpad channels per row

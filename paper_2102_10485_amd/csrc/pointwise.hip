@@ -662,7 +662,7 @@ void launch_bn_param_grad(const NormArgs& a, hipStream_t st) {
 }
 
 // dx = gamma * rstd * (g - sum_g / S - xhat * sum_gx / S).  Same block shape as the forward pass.
-template <typename T>
+template <typename T, bool PRE>
 __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(NormArgs a) {
   constexpr int EPV = Vec16<T>::N;
   const int j = blockIdx.x, sidx = blockIdx.y;
@@ -702,14 +702,21 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(NormArgs a) {
       const float xh = (v[k] - mu[k]) * rs[k];
       const float u = ga[k] * xh + be[k];
       const float gg = u > 0.f ? d[k] : d[k] * a.slope;
-      v[k] = ga[k] * rs[k] * (gg - s1[k] - xh * s2[k]);
+      float o = ga[k] * rs[k] * (gg - s1[k] - xh * s2[k]);
+      if (PRE) {
+        if (!(v[k] > 0.f)) o *= a.pre_slope;
+        o = a.pre_drop && dropped(v[k]) ? 0.f : o * a.pre_scale;
+      }
+      v[k] = o;
     }
     storev(dx + (long long)r * a.C + g * EPV, v);
   }
 }
 template <typename T> void launch_bn_bwd_apply(const NormArgs& a, hipStream_t st) {
   if (a.n == 0 || a.nseg == 0) return;
-  hipLaunchKernelGGL((bn_bwd_apply_kernel<T>), dim3((unsigned)a.n, (unsigned)a.nseg), dim3(256), 0, st, a);
+  const dim3 grid((unsigned)a.n, (unsigned)a.nseg);
+  if (a.pre_act) hipLaunchKernelGGL((bn_bwd_apply_kernel<T, true>), grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((bn_bwd_apply_kernel<T, false>), grid, dim3(256), 0, st, a);
 }
 template void launch_bn_bwd_apply<float>(const NormArgs&, hipStream_t);
 template void launch_bn_bwd_apply<bf16_t>(const NormArgs&, hipStream_t);

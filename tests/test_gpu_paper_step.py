@@ -174,3 +174,27 @@ def test_paper_networks_other_image_shapes(prec, spec_name):
         p.step(*batch(p.spec, lab, 500 + s))
         p.compare("step %d" % s)
     p.close()
+
+
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+def test_zero_activations_behind_dropout(prec):
+    """The backward pass reads the dropout mask off the stored activations, where a kept zero is not a dropped one: channels of
+    the first and the second block whose weights and bias are zero have pre-activations of exactly zero, and their bias gradients are
+    the slope times the kept positions' gradients."""
+    p = PaperPair("paper16", 2, 24, prec)
+    names = [n for n, _ in p.shapes[1]]
+    for l in range(2):
+        for j, ch in ((0, [1, 9]), (1, [0, 30])):
+            w, b = [n for n in names if p.orc.D[l][n].ndim == 4][j], [n for n in names if n.endswith("b")][j]
+            p.orc.D[l][w][ch] = 0.0
+            p.orc.D[l][b][ch] = 0.0
+    p.step(*batch(p.spec, np.arange(21) % 2, 620))
+    p.compare("zero channels")
+    if prec == binding.FP32:
+        for l in range(2):
+            got = unflat(p.gpu.get_grads(1, l), p.shapes[1])
+            b = [n for n in names if n.endswith("b")][0]
+            ref = p.orc.grads[l][1][b]
+            assert np.all(np.abs(ref[[1, 9]]) > 0)
+            assert np.max(np.abs(got[b] - ref)) <= 5e-3 * np.max(np.abs(ref))      # the bound of a network's gradient
+    p.close()
