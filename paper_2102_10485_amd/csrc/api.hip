@@ -600,13 +600,15 @@ void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, c
 int wgrad_ksplit(const gan_ctx* c, int Cb, int Cs, int ntaps, int Hs, int nseg) {
   const double blocks = (double)c->L * wgrad_tiles_per_model((int)esize(c), ntaps, Cb, Cs);
   const double rows = (double)c->NB * nseg * Hs * Hs, out = (double)c->L * ntaps * Cb * Cs * 4;
-  const double product = 2.0 * rows * ntaps * Cb * Cs / (c->bf16 ? 900e12 : 150e12);
+  // bf16 tiles fill a CU each.  fp32: a CU holds two blocks, which reach 133 TFLOP/s over the chip where single ones reach 99 (ten
+  // models of 128 samples, 64 -> 128 channels at side 7, 80 tiles: 3 splits 305 us, 4 308, 6 230, 7 291, 8 263, 12 233).
+  const double product = 2.0 * rows * ntaps * Cb * Cs / (c->bf16 ? 900e12 : 133e12), single = c->bf16 ? 1.0 : 1.34;
   const double chunk_rows = 128 / (double)esize(c);
   int best = 1;
   double best_t = 0;
   for (int k = 1; k <= WG_MAX_KSPLIT; ++k) {
     if (k > 1 && rows / nseg / c->L < 2 * chunk_rows * k) break;             // at least two chunks for every block
-    const double b = blocks * k, rounds = (double)(((long long)b + 255) / 256);
+    const double b = blocks * k, full = (double)(((long long)b + 255) / 256), rounds = full > 1 ? full : single;
     const double t = product * rounds * 256 / b + (k > 1 ? 5e-6 + (2 * k + 1) * out / 4e12 : 0);
     if (k == 1 || t < best_t) { best = k; best_t = t; }
   }
