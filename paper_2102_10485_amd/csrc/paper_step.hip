@@ -10,6 +10,8 @@
 // on what else is in the launch.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace gan {
@@ -55,25 +57,42 @@ __global__ __launch_bounds__(256) void point_kernel(PointArgs a) {
   const long long base = ((long long)seg * a.seg_samples + j) * a.HW * a.Cpad;
   T* x = static_cast<T*>(a.x) + base;
   const float* bias = a.bias ? a.bias + (long long)l * a.pstride : nullptr;
-  // (pixel, channel) carried along instead of divided out: the kernel is bound by its vector instructions
-  const int dp = 256 / a.C, dc = 256 - dp * a.C;
-  int pix = (int)threadIdx.x / a.C, c = (int)threadIdx.x - pix * a.C;
   if (a.thr > 0 && (a.HW & 3) == 0) {
-    // a thread takes four consecutive pixels of one channel: consecutive element indices, one generator evaluation
-    const int total = (a.HW >> 2) * a.C;
-    for (int t = threadIdx.x; t < total; t += 256, pix += dp, c += dc) {
-      if (c >= a.C) { c -= a.C; ++pix; }              // pix counts groups of four pixels here
-      unsigned w[4];
-      dropout_words(a, l, ((unsigned long long)n_local * a.C + c) * a.HW + pix * 4, pass_id, step, w);
+    // A thread takes four consecutive pixels of a channel: consecutive element indices, one generator evaluation.  With an even
+    // number of channels it takes two of them, in accesses of two elements (one at a time, the step of 100 such pairs takes 9465 us against 9380).
+    const auto groups = [&](auto width) __attribute__((always_inline)) {
+      constexpr int W = decltype(width)::value;
+      struct alignas(W * sizeof(T)) Group { T v[W]; };
+      const int CG = a.C / W, total = (a.HW >> 2) * CG;
+      const int dp = 256 / CG, dc = 256 - dp * CG;       // (pixel, channel) carried along instead of divided out
+      int pix = (int)threadIdx.x / CG, c = (int)threadIdx.x - pix * CG;      // groups of four pixels, of W channels
+      for (int t = threadIdx.x; t < total; t += 256, pix += dp, c += dc) {
+        if (c >= CG) { c -= CG; ++pix; }
+        Group* const at = reinterpret_cast<Group*>(x + pix * 4 * a.Cpad + W * c);
+        const int row = a.Cpad / W;                      // Cpad is a multiple of 64
+        Group in[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int o = (pix * 4 + k) * a.Cpad + c;
-        const float v = point_value<T>(a, to_float(x[o]), bias, c);
-        x[o] = (w[k] >> 8) >= a.thr ? kept_nonzero(from_float<T>(v * a.scale)) : from_float<T>(0.f);
+        for (int k = 0; k < 4; ++k) in[k] = at[k * row];
+        unsigned w[W][4];
+#pragma unroll
+        for (int q = 0; q < W; ++q) dropout_words(a, l, ((unsigned long long)n_local * a.C + W * c + q) * a.HW + pix * 4, pass_id, step, w[q]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+#pragma unroll
+          for (int q = 0; q < W; ++q) {
+            const float v = point_value<T>(a, to_float(in[k].v[q]), bias, W * c + q);
+            in[k].v[q] = (w[q][k] >> 8) >= a.thr ? kept_nonzero(from_float<T>(v * a.scale)) : from_float<T>(0.f);
+          }
+          at[k * row] = in[k];
+        }
       }
-    }
+    };
+    if ((a.C & 1) == 0) groups(std::integral_constant<int, 2>{});
+    else groups(std::integral_constant<int, 1>{});
     return;
   }
+  const int dp = 256 / a.C, dc = 256 - dp * a.C;
+  int pix = (int)threadIdx.x / a.C, c = (int)threadIdx.x - pix * a.C;
   const int total = a.HW * a.C;
   for (int t = threadIdx.x; t < total; t += 256, pix += dp, c += dc) {
     if (c >= a.C) { c -= a.C; ++pix; }
