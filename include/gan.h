@@ -64,6 +64,8 @@ typedef enum {
   GAN_E_STATE = -6    /* call not valid in the current state (e.g. no step taken yet) */
 } gan_status;
 
+/* GAN_FP32: fp32 storage; contractions take every value as the sum of three bf16 parts (24 significant bits) with fp32 sums, no less
+   accurate than fp32 multiply-adds; infinities and NaN behave as in fp32 arithmetic. */
 typedef enum { GAN_FP32 = 0, GAN_BF16_FP32MASTER = 1 } gan_precision;
 
 #define GAN_MAX_LAYERS 8
@@ -256,7 +258,7 @@ gan_status gan_probe_copy(int64_t bytes, void* hip_stream, double* gbps);
      wgrad: dw[ky,kx,cb,cs]  = sum_{n,y,x} big[n,2y-1+ky,2x-1+kx,cb] * small[n,y,x,cs]
    n_groups models, group g uses weight block g.  n_samples = offs[n_groups] must be given by the caller. */
 /* Which of the forward-type GEMM's tile shapes gan_op_conv_down / gan_op_conv_up use from now on: rows = 64, 128 or
-   256 rows per tile (with 256 the width follows the output channels: 64, 128 or 256 columns), 0 = chosen from the
+   256 rows per tile (with 256 the width follows the output channels: 64, 128 or 256 columns in bf16, always 64 in fp32), 0 = chosen from the
    problem size as inside a training step.  Lets a test run one case through every instantiation. */
 gan_status gan_op_tile_rows(gan_ctx* ctx, int32_t rows);
 gan_status gan_op_conv_down(gan_ctx* ctx, const void* big, const void* w_down, void* small_out, const int32_t* offs,
