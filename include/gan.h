@@ -64,8 +64,9 @@ typedef enum {
   GAN_E_STATE = -6    /* call not valid in the current state (e.g. no step taken yet) */
 } gan_status;
 
-/* GAN_FP32: fp32 storage; contractions take every value as the sum of three bf16 parts (24 significant bits) with fp32 sums, no less
-   accurate than fp32 multiply-adds; infinities and NaN behave as in fp32 arithmetic. */
+/* GAN_FP32: fp32 storage.  The contractions of both families take every value as the sum of three bf16 parts (24 significant bits, over
+   the whole range of fp32) with fp32 sums: error against exact sums below that of a chain of fp32 multiply-adds.  G's last convolution
+   in GAN_FAMILY_PAPER multiplies in fp32.  Infinities and NaN behave as in fp32 arithmetic. */
 typedef enum { GAN_FP32 = 0, GAN_BF16_FP32MASTER = 1 } gan_precision;
 
 #define GAN_MAX_LAYERS 8

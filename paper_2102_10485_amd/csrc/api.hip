@@ -601,7 +601,8 @@ int wgrad_ksplit(const gan_ctx* c, int Cb, int Cs, int ntaps, int Hs, int nseg) 
   const double blocks = (double)c->L * wgrad_tiles_per_model((int)esize(c), ntaps, Cb, Cs);
   const double rows = (double)c->NB * nseg * Hs * Hs, out = (double)c->L * ntaps * Cb * Cs * 4;
   // bf16 tiles fill a CU each.  fp32: a CU holds two blocks, which reach 133 TFLOP/s over the chip where single ones reach 99 (ten
-  // models of 128 samples, 64 -> 128 channels at side 7, 80 tiles: 3 splits 305 us, 4 308, 6 230, 7 291, 8 263, 12 233).
+  // models of 128 samples, 64 -> 128 channels at side 7, 80 tiles: 3 splits 305 us, 4 308, 6 230, 7 291, 8 263, 12 233; taken before
+  // the operands were scaled, which costs every one of them 3 %).
   const double product = 2.0 * rows * ntaps * Cb * Cs / (c->bf16 ? 900e12 : 133e12), single = c->bf16 ? 1.0 : 1.34;
   const double chunk_rows = 128 / (double)esize(c);
   int best = 1;

@@ -63,7 +63,7 @@ template <> struct FwdTiles<bf16_t> {
 };
 // fp32 is bound by the matrix and vector pipes together, so more than 128 x 128 brings nothing: 20 x 64 samples, 128 -> 256
 // channels at side 8, in TFLOP/s: 128x128 172, 256x128 162 (eight waves of 64 x 64) and 154 (four of 128 x 64, one wave per SIMD),
-// 256x64 162; the 64-byte chunks of the bf16 tiles 156-162.
+// 256x64 162; the 64-byte chunks of the bf16 tiles 156-162 (all without the scaling of the operands, see Split8: 128x128 is at 157 with it).
 template <> struct FwdTiles<float> {
   typedef Tile<128, 128, 2, 2, 128, 2> Small;    // 256 threads, wave tile 64 x 64, 64 KiB of LDS
   typedef Tile<256, 64, 4, 1, 128, 2> Narrow;    // 256 threads, wave tile 64 x 64, 80 KiB
@@ -177,6 +177,7 @@ __device__ inline bool block_any(int flag, unsigned char* lds, int wave) {
   __syncthreads();
   return __builtin_amdgcn_readfirstlane(any) != 0;
 }
+// the sum of the products of split operands
 template <int TM, int TN>
 __device__ inline void add_acc(floatx16 (&acc)[TM][TN], const floatx16 (&low)[TM][TN]) {
 #pragma unroll
@@ -184,7 +185,7 @@ __device__ inline void add_acc(floatx16 (&acc)[TM][TN], const floatx16 (&low)[TM
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] += low[i][j][e];
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = (acc[i][j][e] + low[i][j][e]) * SPLIT_UNSCALE;
 }
 template <int TM, int TN>
 __device__ inline void clear_acc(floatx16 (&acc)[TM][TN]) {
@@ -1151,7 +1152,7 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void wgrad_kerne
 // Tiles of the weight gradient.  bf16: the largest tile the output fills, because the loop lives on the CU's path from
 // L2 (operand bytes per product fall with the tile's sides).  fp32: six times the matrix-pipe time, so
 // tiles are small: 128 x 128 with two blocks per CU leaves little of a last round of blocks idle (640 such tiles of 20 models run
-// at 126 TFLOP/s, 256 x 128 ones at 90-106, 256 x 64 at 119).
+// at 126 TFLOP/s, 256 x 128 ones at 90-106, 256 x 64 at 119, all without the scaling of the operands).
 typedef Tile<64, 128, 1, 4> TileWgImg;    // patch-matrix layers: 64 packed columns x 128 feature channels
 typedef Tile<64, 64, 2, 2> TileWgImg64;   //   and x 64
 typedef Tile<256, 64, 4, 1> TileWg64;     // 64 channels on the N side, bf16

@@ -578,7 +578,7 @@ __global__ __launch_bounds__(256) void up_img_kernel(UpImgArgs a) {
       for (int t = 0; t < NCT; ++t)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          acc[t][e] += low[t][e];
+          acc[t][e] = (acc[t][e] + low[t][e]) * SPLIT_UNSCALE;
           z = __builtin_fmaf(acc[t][e], 0.f, z);
         }
       if (__ballot(z != z)) {                               // what has no split: this wave's rows again with the fp32 MFMAs

@@ -17,18 +17,28 @@ __device__ inline void mma16B(floatx16& acc, const uint4& a, const uint4& b, bf1
 // m = bf16(x - h), l = x - h - m: both differences are exact, and l needs eight bits), so a product of two fp32 values is nine
 // bf16 products, each exact in the MFMA.  The six down to 2^-16 of the product are taken, h*h into one fp32 accumulator and the
 // five smaller ones into a second that is added at the end; the three left out are below 2^-24 of it and of either sign.
+// Values are split after a multiplication by 2^24, which the sum is rid of at the end: without it the parts of a value below 2^-109
+// fall under the smallest bf16 (at 1e-36 the error was 2.6e-5); with it the lowest bit of every fp32 value, 2^-149, is a normal bf16.
+// It costs one vector instruction a value (2.5 in 100 of the 10-pair 28x28 step, 4.5 of the 20-pair 32x32 one; a test for
+// small values would cost the same and send them to the fp32 MFMAs).
 // Why: v_mfma_f32_32x32x2_f32 takes sixteen times the matrix-pipe time of the bf16 MFMA, six of which replace it.  Forward-type
-// kernel, 20 x 64 samples, 128 -> 256 channels at side 8: 100 TFLOP/s before, 172 now; weight gradient of the same layer 95 and
-// 126.  What bounds it now is the matrix pipe (1.0 PFLOP/s of bf16) and the 5.5 vector instructions that split a value (without
-// them, 15 % less time).
-// Error against 64-bit sums (relative, 64 .. 512 channels, sides 2 .. 16): 0.31-0.38 of the fp32 MFMA's on normal and on positive
-// inputs, 0.35-0.56 on inputs after a ReLU, because a bf16 MFMA rounds its accumulator once for several products and the small
-// terms have an accumulator of their own.  (All six into one accumulator: 0.85, but 1.1-1.4 after a ReLU, where half the products are zero
-// and the fp32 MFMA has nothing to round; not taken, although its 128 x 64 wave tiles were 8 % faster.)
-// What has no split -- infinities, NaN, values that round to a bf16 infinity -- leaves a NaN in the accumulators; a block that
-// finds one computes its tile again with the fp32 MFMAs.  (Below 2^-110 the parts fall under the smallest bf16 and are lost.)
+// kernel, 20 x 64 samples, 128 -> 256 channels at side 8: 100 TFLOP/s with the fp32 MFMAs, 157 now (168 on two segments, without the
+// scale 168 and 179); weight gradient of the same layer 95 and 152.  What bounds it now is the matrix pipe (1.0 PFLOP/s of bf16)
+// and the 6.5 vector instructions that split a value.
+// Error against 64-bit sums as a share of the fp32 MFMA's (64 .. 512 channels, sides 2 .. 16, six seeds each), 2-norm: 0.31-0.35 on normal
+// and on gradient-sized inputs, 0.16-0.40 on positive ones, 0.34-0.55 on inputs after a ReLU, 0.38-0.44 on inputs spread over many
+// magnitudes, where the weight gradient's is 0.64-0.87; the largest single error there is 0.6-1.0 on average over the seeds, and the
+// worst seed's is up to 1.3 times the fp32 MFMA's worst (8e-5 of the root mean square).  It is this good because a bf16 MFMA
+// rounds its accumulator once for several products and the small terms have an accumulator of their own.  (All six into one
+// accumulator: 0.85, but 1.1-1.4 after a ReLU, where half the products are zero and the fp32 MFMA has nothing to round; not taken,
+// although its 128 x 64 wave tiles were 8 % faster.)
+// What leaves the range -- infinities, NaN, values from 2^104 and sums from 2^80 -- leaves an infinity or NaN in the accumulators; a
+// block that finds one computes its tile again with the fp32 MFMAs.
 struct Split8 { u32x4 h, m, l; };
+constexpr float SPLIT_SCALE = 0x1p24f, SPLIT_UNSCALE = 0x1p-48f;      // of both operands; of their products' sum
 __device__ __forceinline__ void split_pair(float x0, float x1, unsigned& h, unsigned& m, unsigned& l) {
+  x0 *= SPLIT_SCALE;
+  x1 *= SPLIT_SCALE;
   h = pack2_bf16(x0, x1);
   const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
   m = pack2_bf16(r0, r1);

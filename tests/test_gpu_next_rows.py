@@ -56,6 +56,34 @@ def test_sample_small(prec):
     p.close()
 
 
+@pytest.mark.parametrize("channels,g_last", [(1, 64), (3, 128), (4, 64)])
+@pytest.mark.parametrize("size", [1.0, 1e-34, 1e-35])
+def test_small_features_in_front_of_the_image(channels, g_last, size, monkeypatch):
+    """fp32: features so small that their bf16 parts would be lost unscaled, through the kernel onto the image.  Bound: three contractions
+    of up to 5.7e-7 (a chain of 1024 multiply-adds, tests/test_fp32_products.py), their normalisations and tanh, doubled; without the
+    scale the error is 1.6e-5 at 1e-34 and ten times that at 1e-35."""
+    monkeypatch.setitem(synth.SPECS, "faint", dict(cond_g=0, cond_d=0, z_dim=20, img_c=channels, img_hw=16, g_h0=4, g_ch=[64, g_last], d_ch=[64, 64]))
+    p = Pair("faint", 2, 2, 40, binding.FP32)
+    at = synth.param_slices(p.spec, 0)
+    for l in range(2):
+        q = p.gpu.get_params(0, l)
+        q[at["bn1.gamma"][0]] *= np.float32(size)
+        q[at["ct2.w"][0]] *= np.float32(1e-4 / size)             # largest 1e30: within the range of the scaled parts
+        p.gpu.set_params(0, l, q)
+        p.orc.set_params(0, l, q)
+    rng = np.random.default_rng(23)
+    n = 37
+    lab = (np.arange(n) % 2).astype(np.int32)
+    z = rng.normal(size=(n, p.spec["z_dim"])).astype(np.float32)
+    out = U.torch_mod().zeros((n, channels, 16, 16), device="cuda")
+    dl, dz = U.dev(lab), U.dev(z)
+    p.gpu.generate(dl.data_ptr(), dz.data_ptr(), n, out.data_ptr(), 1)
+    rc, ref = p.orc.generate(lab, z.astype(np.float64), 1)
+    assert rc == 0 and np.abs(ref).max() > 0
+    assert U.rel_l2(out.cpu().numpy(), ref) <= 4e-6
+    p.close()
+
+
 def test_sample_config2_full_size_bf16():
     """6400 draws over 100 labels with a rank-Zipf prior: every label bit-exact; images of two labels against the
     oracle (with the running statistics every image depends on its own noise row only)."""

@@ -7,6 +7,7 @@ import pytest
 
 import oracle as O
 from paper_2102_10485_amd import binding, synth
+from tests import fp32_products as F
 from tests import gpu_util as U
 
 pytestmark = pytest.mark.gpu
@@ -207,6 +208,38 @@ def test_fp32_values_without_a_bf16_split(ctxs):
     dw = torch.zeros((4, 4, cb, cs), device="cuda")
     g.op_conv_wgrad(d_big.data_ptr(), d_small.data_ptr(), dw.data_ptr(), offs.data_ptr(), 1, n, cb, cs, hs)
     _same_classes(dw.cpu().numpy(), dW)
+
+
+@pytest.mark.parametrize("scales", [(1.0, 1.0), (1e-34, 1.0), (1.0, 1e-36), (1.2e-38, 1.0), (7e-40, 1e20), (1e-19, 1e-15), (1e15, 1e15)])
+def test_fp32_products_are_no_less_accurate_than_a_chain_of_multiply_adds(ctxs, scales):
+    """Operands of ordinary size, small, subnormal, and with sums beyond the range of the scaled parts.  What the bound tells apart is
+    in tests/test_fp32_products.py."""
+    torch = U.torch_mod()
+    g = ctxs[binding.FP32]
+    cb, cs, hs, n = 64, 64, 4, 3
+    rng = np.random.default_rng(17)
+    big = (rng.normal(size=(n, 2 * hs, 2 * hs, cb)) * scales[0]).astype(np.float32)
+    small = (rng.normal(size=(n, hs, hs, cs)) * scales[0]).astype(np.float32)
+    other = (rng.normal(size=(n, hs, hs, cs)) * scales[1]).astype(np.float32)
+    w = (rng.normal(0, 0.05, (16, cb, cs)) * scales[1]).astype(np.float32)
+    offs = U.dev(np.array([0, n], np.int32))
+    d_big, d_small, d_other, d_wu, d_wd = U.dev(big), U.dev(small), U.dev(other), U.dev(w), U.dev(w.transpose(0, 2, 1))
+    cols = F.columns_down(big)
+    down, down_bound = F.reference(cols, w.reshape(16 * cb, cs))
+    up, up_bound = F.reference(F.columns_up(small), w.transpose(0, 2, 1).reshape(16 * cs, cb))
+    for rows in (64, 128, 256):
+        g.op_tile_rows(rows)
+        out = torch.zeros((n * hs * hs, cs), device="cuda")
+        g.op_conv_down(d_big.data_ptr(), d_wd.data_ptr(), out.data_ptr(), offs.data_ptr(), 1, n, cb, cs, hs)
+        assert F.rel(out.cpu().numpy(), down) <= down_bound, rows
+        out = torch.zeros((n * 4 * hs * hs, cb), device="cuda")
+        g.op_conv_up(d_small.data_ptr(), d_wu.data_ptr(), out.data_ptr(), offs.data_ptr(), 1, n, cb, cs, hs)
+        assert F.rel(out.cpu().numpy(), up) <= up_bound, rows
+    g.op_tile_rows(0)
+    dw, dw_bound = F.reference(np.ascontiguousarray(cols.T), other.reshape(-1, cs))
+    out = torch.zeros((16 * cb, cs), device="cuda")
+    g.op_conv_wgrad(d_big.data_ptr(), d_other.data_ptr(), out.data_ptr(), offs.data_ptr(), 1, n, cb, cs, hs)
+    assert F.rel(out.cpu().numpy(), dw) <= dw_bound
 
 
 def _same_classes(got, ref):
