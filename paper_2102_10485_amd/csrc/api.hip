@@ -1660,6 +1660,7 @@ gan_status gan_anova_f(gan_ctx* c, const int32_t* label_ids, const float* images
   }
   // the results (a few KB) go straight to the host's memory: one wait instead of one and three synchronous copies
   int* gcnt = reinterpret_cast<int*>(c->an_res + 2 * kc);
+  (void)hipGetLastError();      // what an earlier HIP call of the caller's left behind is not this call's failure
   launch_anova(label_ids, images, n, K, C, HW, c->an_x, c->an_res, c->an_res + kc, gcnt, c->st);
   if (hipGetLastError() != hipSuccess || hipStreamSynchronize(c->st) != hipSuccess) return fail(c, GAN_E_HIP, "analysis of variance failed on the device");
   if (!anova_f_from_sums(c->an_res, c->an_res + kc, gcnt, K, C, F))

@@ -177,3 +177,20 @@ def test_anova_f_odd_sizes_and_unaligned_images(hw, n):
         st, F = binding.anova_f_static(dl.data_ptr(), buf.data_ptr() + 4 * shift, n, 5, 3, hw, torch.cuda.current_stream().cuda_stream)
         assert rc == 0 and st == binding.GAN_OK
         np.testing.assert_allclose(F, ref, rtol=1e-9)
+
+
+def test_anova_f_after_a_failed_call_of_the_caller():
+    """An error that some other HIP call of the thread left behind is not the analysis' own."""
+    torch = U.torch_mod()
+    rng = np.random.default_rng(4)
+    n, K = 40, 3
+    lab = (np.arange(n) % K).astype(np.int32)
+    img = np.tanh(rng.normal(size=(n, 3, 16, 16)) + 0.3 * lab[:, None, None, None]).astype(np.float32)
+    g = binding.Gan(binding.make_config(synth.SPECS["tiny3"], K, K, n, binding.FP32), torch.cuda.current_stream().cuda_stream)
+    dl, dx = U.dev(lab), U.dev(img)
+    torch.cuda.synchronize()
+    assert g.lib.hipSetDevice(10000) != 0                    # refused by the runtime: no such device
+    st, F = g.anova_f(dl.data_ptr(), dx.data_ptr(), n, 3)
+    assert st == binding.GAN_OK
+    np.testing.assert_allclose(F, O.anova_f(lab, img, K)[1], rtol=1e-9)
+    g.close()
