@@ -84,6 +84,31 @@ def test_small_features_in_front_of_the_image(channels, g_last, size, monkeypatc
     p.close()
 
 
+@pytest.mark.parametrize("channels,g_last", [(1, 64), (3, 128), (4, 64)])
+def test_values_beyond_the_split_range_through_the_generator(channels, g_last, monkeypatch):
+    """fp32: one sample's noise holds a value whose parts are infinite, and every layer behind it sums far above 2^80.  Linear layer, transposed
+    convolutions and the kernel onto the image compute what fp32 arithmetic gives (pixels of plus or minus one there), and the samples
+    beside it are as accurate as ever."""
+    monkeypatch.setitem(synth.SPECS, "bright", dict(cond_g=0, cond_d=0, z_dim=20, img_c=channels, img_hw=24, g_h0=6, g_ch=[64, g_last],
+                                                    d_ch=[64, 64]))
+    p = Pair("bright", 2, 2, 40, binding.FP32)
+    rng = np.random.default_rng(29)
+    n = 37
+    lab = (np.arange(n) % 2).astype(np.int32)
+    z = rng.normal(size=(n, p.spec["z_dim"])).astype(np.float32)
+    z[8, 3], z[21, 0] = 1e38, -1e38
+    out = U.torch_mod().zeros((n, channels, 24, 24), device="cuda")
+    dl, dz = U.dev(lab), U.dev(z)
+    p.gpu.generate(dl.data_ptr(), dz.data_ptr(), n, out.data_ptr(), 1)
+    rc, ref = p.orc.generate(lab, z.astype(np.float64), 1)
+    got = out.cpu().numpy()
+    loud = np.isin(np.arange(n), [8, 21])
+    assert rc == 0 and np.all(np.abs(ref[loud]) == 1.0)
+    np.testing.assert_array_equal(got[loud], ref[loud])
+    assert U.rel_l2(got[~loud], ref[~loud]) <= 4e-6                 # as for faint features above
+    p.close()
+
+
 def test_sample_config2_full_size_bf16():
     """6400 draws over 100 labels with a rank-Zipf prior: every label bit-exact; images of two labels against the
     oracle (with the running statistics every image depends on its own noise row only)."""
@@ -164,7 +189,7 @@ def test_anova_f_edge_cases():
 
 @pytest.mark.parametrize("hw,n", [(28, 37), (30, 10), (4, 70)])
 def test_anova_f_odd_sizes_and_unaligned_images(hw, n):
-    """Images whose pixel count is no multiple of the 256 floats one trip takes (or of 4), and a buffer off 16-byte alignment."""
+    """Images whose pixel count is no multiple of the 256 floats one trip takes, and a buffer off 16-byte alignment."""
     torch = U.torch_mod()
     rng = np.random.default_rng(hw + n)
     lab = rng.integers(0, 5, n).astype(np.int32)
@@ -177,6 +202,22 @@ def test_anova_f_odd_sizes_and_unaligned_images(hw, n):
         st, F = binding.anova_f_static(dl.data_ptr(), buf.data_ptr() + 4 * shift, n, 5, 3, hw, torch.cuda.current_stream().cuda_stream)
         assert rc == 0 and st == binding.GAN_OK
         np.testing.assert_allclose(F, ref, rtol=1e-9)
+
+
+@pytest.mark.parametrize("hw,n", [(5, 37), (7, 64), (2, 8192 + 37)])
+def test_anova_f_odd_sides_and_more_images_than_one_trip(hw, n):
+    """Pixel counts that are no multiple of 4 in an aligned buffer, and more than the 8192 images whose labels a block takes at once, with
+    a label that occurs behind them only."""
+    torch = U.torch_mod()
+    rng = np.random.default_rng(hw + n)
+    lab = rng.integers(0, 4, n).astype(np.int32)
+    lab[-5:] = 4
+    img = np.tanh(rng.normal(size=(n, 3, hw, hw)) + 0.3 * lab[:, None, None, None]).astype(np.float32)
+    rc, ref = O.anova_f(lab, img, 5)
+    dl, dx = U.dev(lab), U.dev(img)
+    st, F = binding.anova_f_static(dl.data_ptr(), dx.data_ptr(), n, 5, 3, hw, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0 and st == binding.GAN_OK
+    np.testing.assert_allclose(F, ref, rtol=1e-9)
 
 
 def test_anova_f_after_a_failed_call_of_the_caller():

@@ -210,6 +210,27 @@ def test_fp32_values_without_a_bf16_split(ctxs):
     _same_classes(dw.cpu().numpy(), dW)
 
 
+def test_fp32_up_values_without_a_bf16_split(ctxs):
+    """The same for the transposed convolution."""
+    torch = U.torch_mod()
+    g = ctxs[binding.FP32]
+    cb, cs, hs, n = 64, 128, 4, 40
+    rng = np.random.default_rng(12)
+    small = rng.normal(0, 1, (n, hs, hs, cs)).astype(np.float32)
+    small[3, 2, 3, 7], small[20, 0, 0, 1], small[31, 3, 3, 127], small[33, 1, 1, 0] = np.inf, -np.inf, np.nan, 3.4e38
+    W = rng.normal(0, 0.05, (cs, cb, 4, 4)).astype(np.float32)
+    offs = U.dev(np.array([0, n], np.int32))
+    with np.errstate(all="ignore"):
+        ref = O.conv_transpose2d(small.transpose(0, 3, 1, 2), W, None).transpose(0, 2, 3, 1)
+    d_small, d_w = U.dev(small), U.dev(np.ascontiguousarray(W.transpose(2, 3, 1, 0)).reshape(16, cb, cs))
+    for rows in (64, 128, 256):
+        g.op_tile_rows(rows)
+        out = torch.zeros((n, 2 * hs, 2 * hs, cb), device="cuda")
+        g.op_conv_up(d_small.data_ptr(), d_w.data_ptr(), out.data_ptr(), offs.data_ptr(), 1, n, cb, cs, hs)
+        _same_classes(out.cpu().numpy(), ref)
+    g.op_tile_rows(0)
+
+
 @pytest.mark.parametrize("scales", [(1.0, 1.0), (1e-34, 1.0), (1.0, 1e-36), (1.2e-38, 1.0), (7e-40, 1e20), (1e-19, 1e-15), (1e15, 1e15)])
 def test_fp32_products_are_no_less_accurate_than_a_chain_of_multiply_adds(ctxs, scales):
     """Operands of ordinary size, small, subnormal, and with sums beyond the range of the scaled parts.  What the bound tells apart is

@@ -245,14 +245,24 @@ def test_a_step_takes_as_long_however_the_labels_fall():
 @pytest.mark.parametrize("channels,g_last", [(1, 128), (2, 128)])
 def test_image_channels_and_partial_patches(prec, channels, g_last, monkeypatch):
     """The kernel onto the image at every number of (tap, channel) columns the other tests leave out, on a feature map of side 12:
-    whole and partial 8 x 8 patches.  (Four channels are in tests/test_gpu_paper_step.py.  Here, with this batch, model 1 then has a
-    pre-activation within rounding of zero: G's gradients are 1.3e-3 and its parameters 1.4e-4 from the oracle's with fp32 MFMAs and with
-    sums of bf16 parts alike, 5e-7 and 3e-8 with other batches; such a step cannot hold the parameters to 1e-4.)"""
+    whole and partial 8 x 8 patches.  Four channels have a test of their own below."""
     monkeypatch.setitem(synth.SPECS, "side24", dict(cond_g=0, cond_d=2, z_dim=12, img_c=channels, img_hw=24, g_h0=6,
                                                     g_ch=[64, g_last], d_ch=[64, 128]))
     p = Pair("side24", 2, 2, 22, prec)
     p.step(*batch(p.spec, np.arange(19) % 2, 640))
     p.compare("%d channels" % channels)
+    p.close()
+
+
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+def test_four_image_channels_and_partial_patches(prec, monkeypatch):
+    """The same with four channels.  (On the batch above model 1 has a pre-activation within rounding of zero here: G's gradients are 1.3e-3
+    and its parameters 1.4e-4 from the oracle's with fp32 MFMAs and with sums of bf16 parts alike; such a step cannot hold the parameters
+    to 1e-4.)"""
+    monkeypatch.setitem(synth.SPECS, "side24", dict(cond_g=0, cond_d=2, z_dim=12, img_c=4, img_hw=24, g_h0=6, g_ch=[64, 128], d_ch=[64, 128]))
+    p = Pair("side24", 2, 2, 22, prec)
+    p.step(*batch(p.spec, np.arange(19) % 2, 650))
+    p.compare("4 channels")
     p.close()
 
 
