@@ -27,14 +27,13 @@ namespace {
 
 inline long long round_up(long long x, long long m) { return (x + m - 1) / m * m; }
 
-// the weight gradient of a patch-matrix layer has a tiny output and a long reduction: its rows are split over this
-// many blocks per model, and the partial blocks are added in a fixed order when they are unpacked
-// Row splits of the image-side weight gradients (one or a few output tiles per model): 8 when there are many
-// models, more when the models alone would leave most of the chip idle.  A function of the model count only.
 // Widest patch matrix of D's first convolution that carries the label maps as indicator columns (see gan_create).  Step of one
 // pair, columns -> rows behind the GEMM, in us: 128 columns (28x28, 10 labels, 640 images) 747 -> 759, (32x32, 3 labels, 64) 982 ->
 // 992; 192 (32x32, 10 labels, 1000) 2755 -> 2726; 320 (25 labels, 200) 1310 -> 1260; 960 (100 labels, 64) 1086 -> 999, (1000) 3336 -> 2721.
 constexpr int LABEL_COLUMNS = 128;
+// the weight gradient of a patch-matrix layer has a tiny output and a long reduction: its rows are split over this
+// many blocks per model, and the partial blocks are added in a fixed order when they are unpacked.
+// 8 when there are many models, more when the models alone would leave most of the chip idle.  A function of the model count only.
 static int img_ksplit_for(int L) { return std::min(std::max(800 / L, 8), 128); }
 constexpr int WG_MAX_KSPLIT = 64;
 
@@ -1014,7 +1013,7 @@ void paper_d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_run
 }
 
 template <typename T>
-void paper_d_backward(gan_ctx* c, int n, int seg_first, int nseg, bool param_grads, bool to_image, int pass0, int step_add) {
+void paper_d_backward(gan_ctx* c, int n, int seg_first, int nseg, bool param_grads, bool to_image) {
   Net& D = c->D;
   const gan_config& f = c->cfg;
   const int nl = (int)D.conv.size();
@@ -1179,11 +1178,11 @@ void paper_train_step(gan_ctx* c, const int32_t* label_ids, const float* noise, 
   im2col_call<T>(c, c->D.conv[0], c->xd, nullptr, c->colD, c->KcD, c->nslot, 1, n);
   paper_d_forward<T>(c, n, 0, 2, true, 0, 1);                          // D(real), D(fake): dropout passes 0 and 1
   loss_call(c, n, 0);                                                  // Eq. 3
-  paper_d_backward<T>(c, n, 0, 2, true, false, 0, 1);
+  paper_d_backward<T>(c, n, 0, 2, true, false);
   adam_call<T>(c, c->D, false);
   paper_d_forward<T>(c, n, 1, 1, true, 2, 0);                          // updated D on the same fake batch: pass 2
   loss_call(c, n, 1);                                                  // Eq. 4 (negated: minimised)
-  paper_d_backward<T>(c, n, 1, 1, false, true, 2, 0);
+  paper_d_backward<T>(c, n, 1, 1, false, true);
   paper_g_backward<T>(c, n);
   paper_adam_g<T>(c);
 }
