@@ -12,7 +12,8 @@ import time
 
 import numpy as np
 
-# TFLOP/s, TFLOP/s, GB/s (published MI355X figures; an fp32 product is six bf16 MFMAs)
+# TFLOP/s and GB/s, the published MI355X figures; what the GEMM and weight-gradient launches of fp32 storage are held to is derived: an fp32
+# product is six bf16 MFMAs there (the fp32 MFMAs' own published peak is 157.3)
 PEAK = {"mfma_bf16": 2500.0, "mfma_fp32": 2500.0 / 6, "hbm": 8000.0}
 
 # HBM bytes per launch from hardware counters (rocprofv3 --pmc FETCH_SIZE, then WRITE_SIZE, KiB per dispatch, averaged over the
@@ -340,7 +341,7 @@ def main():
         out["elementwise_note"] = ("algorithmic bytes (inputs read once, outputs written once, storage type; Adam 28 B per parameter + "
                                    "storage copies) / HIP-event time, against 8 TB/s; %d steps with events around every launch" % min(args.steps, 5))
         # the same figures against what the simplest kernels reach on this chip (register-only MFMA loop, plain copy)
-        mfma_meas = binding.probe_mfma(w["prec"], torch.cuda.current_stream().cuda_stream)
+        mfma_meas = binding.probe_mfma(binding.BF16, torch.cuda.current_stream().cuda_stream) / (1 if prec_name == "bf16" else 6)
         copy_meas = binding.probe_copy(1 << 30, torch.cuda.current_stream().cuda_stream)
         out["measured_ceilings"] = {"mfma_loop_tflops": mfma_meas, "device_copy_gbps": copy_meas,
                                     "roofline_frac_of_mfma_loop": kern[dom]["tflops"] / mfma_meas,

@@ -28,7 +28,7 @@ namespace {
 inline long long round_up(long long x, long long m) { return (x + m - 1) / m * m; }
 
 // Widest patch matrix of D's first convolution that carries the label maps as indicator columns (see gan_create).  Step of one
-// pair, columns -> rows behind the GEMM, in us: 128 columns (28x28, 10 labels, 640 images) 747 -> 759, (32x32, 3 labels, 64) 982 ->
+// pair, columns -> rows behind the GEMM when the rows were brought in, in us: 128 columns (28x28, 10 labels, 640 images) 747 -> 759, (32x32, 3 labels, 64) 982 ->
 // 992; 192 (32x32, 10 labels, 1000) 2755 -> 2726; 320 (25 labels, 200) 1310 -> 1260; 960 (100 labels, 64) 1086 -> 999, (1000) 3336 -> 2721.
 constexpr int LABEL_COLUMNS = 128;
 // the weight gradient of a patch-matrix layer has a tiny output and a long reduction: its rows are split over this
@@ -599,7 +599,8 @@ void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, c
 int wgrad_ksplit(const gan_ctx* c, int Cb, int Cs, int ntaps, int Hs, int nseg) {
   const double blocks = (double)c->L * wgrad_tiles_per_model((int)esize(c), ntaps, Cb, Cs);
   const double rows = (double)c->NB * nseg * Hs * Hs, out = (double)c->L * ntaps * Cb * Cs * 4;
-  // bf16 tiles fill a CU each.  fp32: a CU holds two blocks, which reach 133 TFLOP/s over the chip where single ones reach 99 (ten
+  // bf16: counted as one block per CU, which the 256x256 and 256x128 tiles are (128 and 96 KiB of LDS); of the 256x64 tile (80 KiB) a CU
+  // holds two, which the estimate does not tell apart.  fp32: a CU holds two blocks, which reach 133 TFLOP/s over the chip where single ones reach 99 (ten
   // models of 128 samples, 64 -> 128 channels at side 7, 80 tiles: 3 splits 305 us, 4 308, 6 230, 7 291, 8 263, 12 233; taken before
   // the operands were scaled, which costs every one of them 3 %).
   const double product = 2.0 * rows * ntaps * Cb * Cs / (c->bf16 ? 900e12 : 133e12), single = c->bf16 ? 1.0 : 1.34;
@@ -855,6 +856,7 @@ void d_backward(gan_ctx* c, int n, int seg_first, int nseg, bool param_grads, bo
       memset(&a, 0, sizeof(a));
       a.dy = c->bufA; a.part = c->class_part; a.sums = c->label_sums; a.offs = c->rb.offs; a.sample_slot = c->rb.sample_slot;
       a.L = c->L; a.n = n; a.Hs = c1.Hs; a.Cs = c1.Cs; a.labels = c->labels; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n;
+      Scope s(c, "class_sums", 0, (double)n * nseg * c1.Hs * c1.Hs * c1.Cs * sizeof(T));
       launch_class_sums<T>(a, c->st);
     }
     launch_unpack_dw(pack_args(c, D, c1, c->KcD, c->nslot, c->wpD), c->st);
@@ -1147,8 +1149,10 @@ void adam_rest_call(gan_ctx* c, Net& net, bool isG, const AdamArgs& a) {
     Scope s(c, "adam", 0, (double)c->L * elems * adam_bytes_per_element(c));
     launch_adam_gaps(a, c->st);
   }
-  if (isG) launch_pack_w<T>(pack_args(c, net, net.conv.back(), c->KcG, 0, c->wpG), c->st);
-  else launch_pack_w<T>(pack_args(c, net, net.conv.front(), c->KcD, c->nslot, c->wpD), c->st);
+  // (with the rows of the label maps, one pair over many labels)
+  const PackArgs pk = isG ? pack_args(c, net, net.conv.back(), c->KcG, 0, c->wpG) : pack_args(c, net, net.conv.front(), c->KcD, c->nslot, c->wpD);
+  Scope s(c, "pack_w", 0, (double)c->L * pk.Cs * pk.Kc * (4.0 + sizeof(T)) + (double)pk.labels * pk.Cs * (64.0 + 9 * sizeof(T)));
+  launch_pack_w<T>(pk, c->st);
 }
 // the whole update on the caller's stream
 template <typename T>
@@ -1431,7 +1435,9 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
     if (c->head_rsplit > 1) ok = ok && dev_alloc(c, (void**)&c->head_part, (size_t)c->head_rsplit * L * (c->D.K + 4) * 4);
   }
   {
-    // the GEMM loaders address one segment of any activation tensor or patch matrix with 32-bit byte offsets
+    // the GEMM loaders address one segment of any activation tensor or patch matrix with 32-bit byte offsets.  Where the label maps are
+    // rows behind the GEMM the patch matrix is counted with their columns all the same: which batches a configuration takes depends on
+    // its shapes alone, not on the way the label maps are held.
     const ConvLayer& c1 = c->D.conv[0];
     const ConvLayer& gl = c->G.conv.back();
     const long long lim = 1LL << 31;

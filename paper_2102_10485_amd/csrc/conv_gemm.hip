@@ -72,7 +72,9 @@ template <> struct FwdTiles<float> {
 };
 
 // What a tile is to the chooser: its shape, the row blocks with statistics of their own, the blocks of it that a CU holds, and
-// the rate a full chip of them reaches against the fastest one of the storage type (0: the storage type has no such tile).
+// the rate a full chip of them reaches against the fastest one of the storage type (0: the storage type has no such tile).  The bf16
+// 256x64 line describes Narrow, which MODE_DOWN runs; MODE_UP and MODE_DENSE run NarrowShort (four blocks per CU, 582 TFLOP/s instead of
+// 480) and are judged by the same line, so the estimate is too high for them.
 struct TileInfo { ConvTile id; const char* name; int rows, cols, split, per_cu; double rate; };
 template <typename TL> constexpr TileInfo info(ConvTile id, const char* name, int per_cu, double rate) {
   return {id, name, TL::BM, TL::BN, TL::WM, per_cu, rate};

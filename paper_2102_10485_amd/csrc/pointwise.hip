@@ -1140,9 +1140,10 @@ __device__ inline double wave_sum_f64(double v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
-// Means of single channel images, one wave each: the whole call is bound by reading the images once (79 MB of 6400 32x32x3
-// images).  VEC: 16-byte loads, four in flight per lane, no barrier; one block per channel image with 4-byte loads and an
-// eight-step tree over LDS took 24 us for the same (3.2 TB/s).
+// Means of single channel images, one wave each.  VEC: 16-byte loads, four in flight per lane, no barrier.  Bound by reading the images
+// once: 79 MB of 6400 32x32x3 images in 14.2 us when they come from memory (5.6 TB/s), 11.9 when a call before left them in the
+// memory-side cache; one block per channel image with 4-byte loads and an eight-step tree over LDS took 31.1 and 24.2.  It is a third
+// of the call (42 us, 40 on repeated images); the label pass below is another.
 template <bool VEC>
 __global__ __launch_bounds__(256) void anova_image_mean_kernel(const float* __restrict__ images, long long count, int HW, double* __restrict__ x) {
   const long long ic = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);      // image * C + channel
