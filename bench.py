@@ -21,20 +21,20 @@ PEAK = {"mfma_bf16": 2500.0, "mfma_fp32": 2500.0 / 6, "hbm": 8000.0}
 # the same counters read for the 1 GiB elementwise probe (fetch x 2.0, write x 1.0).  Valid only for the kernel sources they
 # were taken with: `sources` is the digest of csrc/ at that time, and the roofline reports null traffic when it differs.
 MEASURED_TRAFFIC = {
-    "sources": "1272be6df4352ca9",
+    "sources": "80bd27cfc007764f",
     "workload": "config 2 bf16",
     "fetch_scale": 2.000, "write_scale": 1.000,
     "kib_per_launch": {
-        "gemm_dense<128x128>": (103311, 108800),
-        "gemm_up<256x256>": (453060, 275200),
-        "gemm_up<256x128>": (159017, 435200),
-        "gemm_dense+lrelu<256x128>": (154519, 614758),
-        "gemm_down<256x256>": (498161, 209600),
-        "wgrad<256x256>": (410476, 512076),
-        "gemm_up+actbwd<256x128>": (584743, 614400),
-        "wgrad<64x128>": (460879, 25605),
-        "gemm_dense<256x128>": (103311, 409886),
-        "wgrad<256x128>": (52079, 410066),
+        "gemm_dense<64x64>": (103275, 123122),
+        "gemm_up<256x256>": (455921, 275200),
+        "gemm_up<256x128>": (158978, 435200),
+        "gemm_dense+lrelu<256x128>": (154523, 614741),
+        "gemm_down<256x256>": (501003, 209600),
+        "wgrad<256x256>": (496187, 512053),
+        "gemm_up+actbwd<256x128>": (580143, 614400),
+        "wgrad<64x128>": (460880, 25605),
+        "gemm_dense<256x128>": (103313, 409868),
+        "wgrad<256x128>": (52083, 410049),
     },
 }
 
@@ -162,7 +162,7 @@ def build_workload(args, config, torch, binding, synth, prec_name, single_pair=N
             n_labels = max(work.n_labels, 2)
             spec["cond_g"] = spec["cond_d"] = n_labels
             # one model owns the whole batch, and the library addresses one model's slice of any tensor with 32-bit
-            # byte offsets; the largest slice is the patch matrix of D's first layer
+            # byte offsets; the largest slice is the patch matrix of D's first layer, counted with a column per label and class
             kc = -(-(16 * spec["img_c"] + 9 * n_labels + 1) // 64) * 64
             row_bytes = kc * (2 if prec_name == "bf16" else 4) * (spec["img_hw"] // 2) ** 2
             n = min(n, ((1 << 31) - 1) // row_bytes // 64 * 64)
