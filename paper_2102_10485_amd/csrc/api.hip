@@ -565,7 +565,7 @@ void refresh_shadows(gan_ctx* c) {
 template <typename T>
 void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, const void* W, long long wstride, void* Out,
                const void* Aux, int C, int N, int Hin, int Hr, int seg_first, int nseg, int n, int w_nstride = 0,
-               double flops_alg = -1.0, bool stats = false) {
+               double flops_alg = -1.0, bool stats = false, const NormArgs* known = nullptr, const float* bias = nullptr) {
   ConvArgs a = {};
   a.A = A; a.W = W; a.Out = Out; a.Aux = Aux; a.w_nstride = w_nstride ? w_nstride : N;
   a.tile = layer_tile(c, mode, N, Hr * Hr, nseg);
@@ -574,6 +574,11 @@ void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, c
   a.w_stride = wstride; a.L = c->L; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n;
   a.C = C; a.N = N; a.Hin = Hin; a.Hr = Hr; a.ub_tiles = ub_tiles(c, n, Hr * Hr, tr);
   a.slope = c->cfg.leaky_slope;
+  if (epi == EPI_BN) {
+    a.bn_mean = known->run_mean; a.bn_var = known->run_var; a.bn_rstride = known->rstride;
+    a.bn_gamma = known->gamma; a.bn_beta = known->beta; a.bn_bias = bias; a.bn_pstride = known->pstride;
+    a.bn_C = known->C; a.bn_eps = known->eps; a.slope = known->slope;
+  }
   if (epi == EPI_DROP_BWD) a.drop_scale = 1.0f / (1.0f - c->cfg.dropout_p);
   a.stat_partial = stats ? c->stat_partial : nullptr;
   if (epi == EPI_LABEL_LRELU) { a.label_rows = c->label_rows; a.sample_slot = c->rb.sample_slot; }
@@ -663,16 +668,13 @@ NormArgs norm_args(gan_ctx* c, Net& net, int C, int rps, long long gamma, long l
   return a;
 }
 
-// BatchNorm (batch statistics, or the running ones) + activation: x -> y
+// BatchNorm with batch statistics + activation: x -> y (with running statistics both are part of the GEMM: EPI_BN)
 // gemm_mode / gemm_rps describe the GEMM that produced x and left per-tile column sums in c->stat_partial
 template <typename T>
-void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool use_running, bool update_running, int gemm_mode,
-                int gemm_rps, int col_groups = 1) {
+void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool update_running, int gemm_mode, int gemm_rps, int col_groups = 1) {
   a.x = x; a.y = y;
   const double elems = (double)a.n * a.nseg * a.rps * a.C;
-  if (use_running) {
-    launch_bn_from_running(a, c->st);
-  } else {
+  {
     const ConvTile tile = layer_tile(c, gemm_mode, a.C * col_groups, gemm_rps, a.nseg);   // of the GEMM that left the partials (N = C * col_groups)
     const int tr = conv_tile_rows((int)sizeof(T), tile), gemm_phases = gemm_mode == MODE_UP ? 4 : 1;
     a.fold_running = update_running && a.nseg == 1 && a.run_mean && a.run_var;
@@ -716,15 +718,16 @@ void im2col_call(gan_ctx* c, const ConvLayer& cl, const void* img, const float* 
   launch_im2col<T>(a, c->st);
 }
 
-// transposed conv onto the image side: feat (absolute segment seg) -> out (same segment indexing)
+// transposed conv onto the image side: feat (absolute segment seg) -> out (same segment indexing), or the caller's images
 template <typename T>
-void up_img_call(gan_ctx* c, Net& net, const ConvLayer& cl, const void* feat, void* out, const void* aux, int mode, int seg, int n) {
+void up_img_call(gan_ctx* c, Net& net, const ConvLayer& cl, const void* feat, void* out, const void* aux, int mode, int seg, int n,
+                 float* user = nullptr) {
   UpImgArgs a;
   memset(&a, 0, sizeof(a));
   a.feat = feat; a.w = (const T*)net.shadow_u + cl.w; a.w_stride = net.P; a.out = out; a.aux = aux;
   a.bias = mode == 1 ? net.theta + cl.bias : nullptr; a.bias_stride = net.P;
   a.offs = c->rb.offs; a.sample_model = c->rb.sample_model; a.L = c->L; a.n = n; a.seg = seg; a.seg_samples = n;
-  a.CB = cl.Cb; a.CBT = cl.CBT; a.Cs = cl.Cs; a.Hs = cl.Hs; a.mode = mode;
+  a.CB = cl.Cb; a.CBT = cl.CBT; a.Cs = cl.Cs; a.Hs = cl.Hs; a.mode = mode; a.user = user; a.perm = c->rb.perm;
   Scope s(c, "up_img", img_flops(cl, n, 1), sizeof(T) * (double)n * cl.Hs * cl.Hs * (cl.Cs + 4.0 * cl.Cb * (mode == 2 ? 2 : 1)));
   launch_up_img<T>(a, c->st);
 }
@@ -742,29 +745,30 @@ PackArgs pack_args(gan_ctx* c, Net& net, const ConvLayer& cl, int Kc, int nslot,
 }
 
 // ---- the networks -------------------------------------------------------------------------------------------
+// user: the caller's images (generation), or NULL: into the fake half of D's image buffer
 template <typename T>
-void g_forward(gan_ctx* c, int n, bool use_running, bool update_running) {
+void g_forward(gan_ctx* c, int n, bool use_running, bool update_running, float* user = nullptr) {
   Net& G = c->G;
   const float relu = 0.f;
-  conv_call<T>(c, "gemm_dense", MODE_DENSE, EPI_NONE, c->zin, (const T*)G.shadow_u + G.fc_w, G.P, c->gpre[0], nullptr, G.Kp, G.J,
-               1, 1, 0, 1, n, 0, -1.0, !use_running);
-  bn_forward<T>(c, norm_args<T>(c, G, G.C0, G.h0 * G.h0, G.fc_gamma, G.fc_beta, G.fc_rs, c->g_mean[0], c->g_var[0], c->g_rstd[0],
-                                c->g_sums[0], 0, 1, n, relu),
-                c->gpre[0], c->gact[0], use_running, update_running, MODE_DENSE, 1, G.h0 * G.h0);
+  const NormArgs a0 = norm_args<T>(c, G, G.C0, G.h0 * G.h0, G.fc_gamma, G.fc_beta, G.fc_rs, c->g_mean[0], c->g_var[0], c->g_rstd[0],
+                                   c->g_sums[0], 0, 1, n, relu);
+  conv_call<T>(c, "gemm_dense", MODE_DENSE, use_running ? EPI_BN : EPI_NONE, c->zin, (const T*)G.shadow_u + G.fc_w, G.P,
+               use_running ? c->gact[0] : c->gpre[0], nullptr, G.Kp, G.J, 1, 1, 0, 1, n, 0, -1.0, !use_running, &a0);
+  if (!use_running) bn_forward<T>(c, a0, c->gpre[0], c->gact[0], update_running, MODE_DENSE, 1, G.h0 * G.h0);
   const int nl = (int)G.conv.size();
   for (int i = 0; i + 1 < nl; ++i) {
     const ConvLayer& cl = G.conv[i];
-    conv_call<T>(c, "gemm_up", MODE_UP, EPI_NONE, c->gact[i], (const T*)G.shadow_u + cl.w, G.P, c->gpre[i + 1], nullptr, cl.Cs, cl.Cb,
-                 cl.Hs, cl.Hs, 0, 1, n, 0, -1.0, !use_running);
-    bn_forward<T>(c, norm_args<T>(c, G, cl.Cb, 4 * cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->g_mean[i + 1], c->g_var[i + 1],
-                                  c->g_rstd[i + 1], c->g_sums[i + 1], 0, 1, n, relu),
-                  c->gpre[i + 1], c->gact[i + 1], use_running, update_running, MODE_UP, cl.Hs * cl.Hs);
+    const NormArgs a = norm_args<T>(c, G, cl.Cb, 4 * cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->g_mean[i + 1], c->g_var[i + 1],
+                                    c->g_rstd[i + 1], c->g_sums[i + 1], 0, 1, n, relu);
+    conv_call<T>(c, "gemm_up", MODE_UP, use_running ? EPI_BN : EPI_NONE, c->gact[i], (const T*)G.shadow_u + cl.w, G.P,
+                 use_running ? c->gact[i + 1] : c->gpre[i + 1], nullptr, cl.Cs, cl.Cb, cl.Hs, cl.Hs, 0, 1, n, 0, -1.0, !use_running, &a);
+    if (!use_running) bn_forward<T>(c, a, c->gpre[i + 1], c->gact[i + 1], update_running, MODE_UP, cl.Hs * cl.Hs);
   }
   // last transposed conv (+bias, tanh) straight into the fake half of D's image buffer
   const ConvLayer& cl = G.conv[nl - 1];
   // G's samples sit in segment 0, the fake images in segment 1 of D's image buffer: offset the output pointer
   T* fake = (T*)c->xd + (long long)n * 4 * cl.Hs * cl.Hs * cl.Cb;
-  up_img_call<T>(c, G, cl, c->gact[nl - 1], fake, nullptr, 1, 0, n);
+  up_img_call<T>(c, G, cl, c->gact[nl - 1], fake, nullptr, 1, 0, n, user);
 }
 
 template <typename T>
@@ -782,7 +786,7 @@ void d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_running) 
                  cl.Cs, 2 * cl.Hs, cl.Hs, seg_first, nseg, n, 0, -1.0, true);
     bn_forward<T>(c, norm_args<T>(c, D, cl.Cs, cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->d_mean[j], c->d_var[j], c->d_rstd[j],
                                   c->d_sums[j], seg_first, nseg, n, slope),
-                  c->dpre[j], c->dact[j], false, update_running, MODE_DOWN, cl.Hs * cl.Hs);
+                  c->dpre[j], c->dact[j], update_running, MODE_DOWN, cl.Hs * cl.Hs);
   }
   HeadArgs h;
   memset(&h, 0, sizeof(h));
@@ -929,50 +933,47 @@ void with_dropout(gan_ctx* c, PointArgs& a, int layer, int pass0, int step_add) 
   a.steps = c->D.t; a.step_add = step_add;
 }
 
-// BatchNorm whose statistics are taken from the stored tensor; no activation after it
+// BatchNorm whose batch statistics are taken from the stored tensor; no activation after it
 template <typename T>
-void bn_forward_direct(gan_ctx* c, NormArgs a, const void* x, void* y, float eps, bool use_running, bool update_running) {
+void bn_forward_direct(gan_ctx* c, NormArgs a, const void* x, void* y, float eps, bool update_running) {
   a.x = x; a.y = y; a.eps = eps; a.slope = 1.f;
-  if (use_running) {
-    launch_bn_from_running(a, c->st);
-  } else {
-    launch_bn_stats_direct<T>(a, a.C, c->st);
-    if (update_running) launch_bn_running(a, c->st);
-  }
+  launch_bn_stats_direct<T>(a, a.C, c->st);
+  if (update_running) launch_bn_running(a, c->st);
   Scope s(c, "bn_apply", 0, 2.0 * a.n * a.nseg * a.rps * a.C * sizeof(T));
   launch_bn_apply<T>(a, c->st);
 }
 
 template <typename T>
-void paper_g_forward(gan_ctx* c, int n, bool use_running, bool update_running) {
+void paper_g_forward(gan_ctx* c, int n, bool use_running, bool update_running, float* user = nullptr) {
   Net& G = c->G;
   const gan_config& f = c->cfg;
-  conv_call<T>(c, "gemm_dense", MODE_DENSE, EPI_NONE, c->zin, (const T*)G.shadow_u + G.fc_w, G.P, c->gpre[0], nullptr, G.Kp, G.J,
-               1, 1, 0, 1, n);
-  {
+  NormArgs a0 = norm_args<T>(c, G, G.C0, G.h0 * G.h0, G.fc_gamma, G.fc_beta, G.fc_rs, c->g_mean[0], c->g_var[0], c->g_rstd[0],
+                             c->g_sums[0], 0, 1, n, 1.f);
+  a0.eps = f.bn_eps_first;
+  conv_call<T>(c, "gemm_dense", MODE_DENSE, use_running ? EPI_BN : EPI_NONE, c->zin, (const T*)G.shadow_u + G.fc_w, G.P,
+               use_running ? c->gact[0] : c->gpre[0], nullptr, G.Kp, G.J, 1, 1, 0, 1, n, 0, -1.0, false, &a0, G.theta + G.fc_bias);
+  if (!use_running) {
     PointArgs a = point_args(c, c->gpre[0], G.J, G.J, 1, 0, 1, n);          // + bias, ReLU
     a.bias = G.theta + G.fc_bias; a.pstride = G.P; a.slope = 0.f;
     Scope s(c, "bias_act_dropout", 0, 2.0 * n * G.J * sizeof(T));
     launch_point_fwd<T>(a, c->st);
   }
-  bn_forward_direct<T>(c, norm_args<T>(c, G, G.C0, G.h0 * G.h0, G.fc_gamma, G.fc_beta, G.fc_rs, c->g_mean[0], c->g_var[0], c->g_rstd[0],
-                                       c->g_sums[0], 0, 1, n, 1.f),
-                       c->gpre[0], c->gact[0], f.bn_eps_first, use_running, update_running);
+  if (!use_running) bn_forward_direct<T>(c, a0, c->gpre[0], c->gact[0], f.bn_eps_first, update_running);
   const int nl = (int)G.conv.size();
   for (int i = 0; i + 1 < nl; ++i) {                   // Upsample x2 + Conv k3 as a k4 s2 p1 transposed convolution
     const ConvLayer& cl = G.conv[i];
-    conv_call<T>(c, "gemm_up", MODE_UP, EPI_NONE, c->gact[i], (const T*)G.w4u + cl.w4, G.P4, c->gpre[i + 1], nullptr, cl.Cs, cl.Cb,
-                 cl.Hs, cl.Hs, 0, 1, n, 0, -1.0, !use_running);
-    NormArgs a = norm_args<T>(c, G, cl.Cb, 4 * cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->g_mean[i + 1], c->g_var[i + 1],
-                              c->g_rstd[i + 1], c->g_sums[i + 1], 0, 1, n, f.leaky_slope);
-    bn_forward<T>(c, a, c->gpre[i + 1], c->gact[i + 1], use_running, update_running, MODE_UP, cl.Hs * cl.Hs);
+    const NormArgs a = norm_args<T>(c, G, cl.Cb, 4 * cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->g_mean[i + 1], c->g_var[i + 1],
+                                    c->g_rstd[i + 1], c->g_sums[i + 1], 0, 1, n, f.leaky_slope);
+    conv_call<T>(c, "gemm_up", MODE_UP, use_running ? EPI_BN : EPI_NONE, c->gact[i], (const T*)G.w4u + cl.w4, G.P4,
+                 use_running ? c->gact[i + 1] : c->gpre[i + 1], nullptr, cl.Cs, cl.Cb, cl.Hs, cl.Hs, 0, 1, n, 0, -1.0, !use_running, &a);
+    if (!use_running) bn_forward<T>(c, a, c->gpre[i + 1], c->gact[i + 1], update_running, MODE_UP, cl.Hs * cl.Hs);
   }
-  const ConvLayer& cl = G.conv[nl - 1];                // Conv k3 s1 p1 (+bias) -> tanh, into the fake half of D's image buffer
+  const ConvLayer& cl = G.conv[nl - 1];                // Conv k3 s1 p1 (+bias) -> tanh, into the fake half of D's image buffer or the caller's
   Conv3Args a;
   memset(&a, 0, sizeof(a));
   a.in = c->gact[nl - 1]; a.out = c->xd; a.w = G.theta + cl.w; a.w_stride = G.P; a.bias = G.theta + cl.bias; a.bias_stride = G.P;
   a.offs = c->rb.offs; a.sample_model = c->rb.sample_model; a.L = c->L; a.n = n; a.H = cl.Hs; a.Cin = cl.Cs; a.CO = cl.Cb;
-  a.out_seg = 1; a.seg_samples = n;
+  a.out_seg = 1; a.seg_samples = n; a.user = user; a.perm = c->rb.perm;
   Scope s(c, "conv3_img", 2.0 * n * cl.Hs * cl.Hs * 9 * cl.Cs * cl.Cb, sizeof(T) * (double)n * cl.Hs * cl.Hs * (cl.Cs + cl.Cb));
   launch_conv3_fwd<T>(a, c->st);
 }
@@ -1003,7 +1004,7 @@ void paper_d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_run
     { Scope s(c, "bias_act_dropout", 0, 2.0 * n * nseg * cl.Hs * cl.Hs * cl.cs_real * sizeof(T)); launch_point_fwd<T>(a, c->st); }
     bn_forward_direct<T>(c, norm_args<T>(c, D, cl.Cs, cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->d_mean[j], c->d_var[j], c->d_rstd[j],
                                          c->d_sums[j], seg_first, nseg, n, 1.f),
-                         c->dpre[j], c->dact[j], f.bn_eps, false, update_running);
+                         c->dpre[j], c->dact[j], f.bn_eps, update_running);
   }
   HeadArgs h;
   memset(&h, 0, sizeof(h));
@@ -1601,21 +1602,16 @@ gan_status gan_generate(gan_ctx* c, const int32_t* label_ids, const float* noise
   if (!label_ids || !noise || !out_images) return fail(c, GAN_E_ARG, "null pointer");
   if (c->shadows_dirty) refresh_shadows(c);
   (void)take_launch_error();
-  const gan_config& f = c->cfg;
   const RouteBuffers train_rb = c->rb;         // the launch helpers read c->rb: point them at the generate set
   c->rb = c->rb_gen;
   if (c->bf16) {
     route_and_stage<bf16_t>(c, label_ids, noise, nullptr, n);
-    if (c->paper) paper_g_forward<bf16_t>(c, n, use_running_stats != 0, false); else
-    g_forward<bf16_t>(c, n, use_running_stats != 0, false);
-    launch_unstage<bf16_t>((const bf16_t*)c->xd + (long long)n * f.img_hw * f.img_hw * f.img_c, out_images, n, c->L, f.img_c,
-                           f.img_hw, c->rb, c->st);
+    if (c->paper) paper_g_forward<bf16_t>(c, n, use_running_stats != 0, false, out_images);
+    else g_forward<bf16_t>(c, n, use_running_stats != 0, false, out_images);
   } else {
     route_and_stage<float>(c, label_ids, noise, nullptr, n);
-    if (c->paper) paper_g_forward<float>(c, n, use_running_stats != 0, false); else
-    g_forward<float>(c, n, use_running_stats != 0, false);
-    launch_unstage<float>((const float*)c->xd + (long long)n * f.img_hw * f.img_hw * f.img_c, out_images, n, c->L, f.img_c,
-                          f.img_hw, c->rb, c->st);
+    if (c->paper) paper_g_forward<float>(c, n, use_running_stats != 0, false, out_images);
+    else g_forward<float>(c, n, use_running_stats != 0, false, out_images);
   }
   c->rb = train_rb;
   return launch_status(c);

@@ -147,7 +147,8 @@ __global__ __launch_bounds__(256) void conv3_fwd_kernel(Conv3Args a) {
 #pragma unroll
         for (int tap = 0; tap < 9; ++tap)
           v += *reinterpret_cast<const float*>(rsrc + tap * CO * C3_RTS + ((tap / 3) * C3_HALO + tap % 3) * 4);
-        out[((long long)y * H + x) * CO + oco] = from_float<T>(tanhf(v + bias_o));
+        if (a.user) a.user[((long long)a.perm[j] * CO + oco) * H * H + y * H + x] = tanhf(v + bias_o);
+        else out[((long long)y * H + x) * CO + oco] = from_float<T>(tanhf(v + bias_o));
       }
     }
   }

@@ -511,7 +511,9 @@ constexpr int UP_BLOCKS = 2048;             // blocks that fill the chip (see th
 template <typename T, int CS, int CB>
 constexpr int up_img_lds() { return 16 * CB * ((sizeof(T) == 4 ? 3 : 1) * (CS * 2 + 16) + UP_RROW * 4); }
 
-template <typename T, int CS, int CB>
+// USER: into the caller's images, a channel plane's pixels next to each other (no pass of its own over the images: 37 of 1407 us for
+// 6400 samples of 32x32x3).
+template <typename T, int CS, int CB, bool USER>
 __global__ __launch_bounds__(256) void up_img_kernel(UpImgArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   constexpr int SZ = (int)sizeof(T), NC = 16 * CB, NCT = (NC + 31) / 32, KS = CS / 16;
@@ -622,7 +624,17 @@ __global__ __launch_bounds__(256) void up_img_kernel(UpImgArgs a) {
     constexpr int rowlen = 2 * UP_TS * CB;                    // contiguous output elements per patch row
 #pragma unroll
     for (int i = tid; i < 2 * UP_TS * rowlen; i += 256) {
-      const int Yl = i / rowlen, rem = i % rowlen, Xl = rem / CB, cb = rem % CB;
+      int Yl, Xl, cb;
+      if constexpr (USER) {
+        cb = i / (4 * UP_TS * UP_TS);
+        Yl = i / (2 * UP_TS) % (2 * UP_TS);
+        Xl = i % (2 * UP_TS);
+      } else {
+        const int rem = i % rowlen;
+        Yl = i / rowlen;
+        Xl = rem / CB;
+        cb = rem % CB;
+      }
       const int Y = 2 * y0 + Yl, X = 2 * x0 + Xl;
       if (Y >= Hb || X >= Hb) continue;
       const long long o = ((sample * Hb + Y) * Hb + X) * CB + cb;
@@ -636,6 +648,10 @@ __global__ __launch_bounds__(256) void up_img_kernel(UpImgArgs a) {
         return e0[(ky * 4 + kx) * CB * UP_RROW + dy * UP_HALO + dx];
       };
       float v = (at(0, 0) + at(0, 1)) + (at(1, 0) + at(1, 1));
+      if constexpr (USER) {
+        a.user[(((long long)a.perm[j] * CB + cb) * Hb + Y) * Hb + X] = tanhf(v + a.bias[(long long)l * a.bias_stride + cb]);
+        continue;
+      }
       if (a.mode == 1) v = tanhf(v + a.bias[(long long)l * a.bias_stride + cb]);
       else if (a.mode == 2) { const float yv = to_float(aux[o]); v *= (1.f - yv * yv); }
       out[o] = from_float<T>(v);
@@ -643,22 +659,27 @@ __global__ __launch_bounds__(256) void up_img_kernel(UpImgArgs a) {
     __syncthreads();
   }
 }
-template <typename T, int CS, int CB> static void up_img_one(const UpImgArgs& a, hipStream_t st) {
+template <typename T, int CS, int CB, bool USER> static void up_img_one(const UpImgArgs& a, hipStream_t st) {
   const int tiles = (a.Hs + UP_TS - 1) / UP_TS, np = tiles * tiles;
   // a block per patch while that leaves CUs idle, else several patches per block, for one read of the weights (6400 samples of 4
   // patches: one patch per block 171 us, two 146, four 140; 1024 samples of 16: 89, 86 with two per block, 74 with eight)
   const int blocks = (int)std::min<long long>(np, std::max<long long>(1, (UP_BLOCKS + a.n - 1) / a.n));
   constexpr int lds = up_img_lds<T, CS, CB>();
   if (lds > 48 * 1024)   // above the default dynamic limit: ask for it (idempotent, cheap)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_img_kernel<T, CS, CB>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  hipLaunchKernelGGL((up_img_kernel<T, CS, CB>), dim3((unsigned)blocks, (unsigned)a.n), dim3(256), lds, st, a);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&up_img_kernel<T, CS, CB, USER>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  hipLaunchKernelGGL((up_img_kernel<T, CS, CB, USER>), dim3((unsigned)blocks, (unsigned)a.n), dim3(256), lds, st, a);
 }
 template <typename T> void launch_up_img(const UpImgArgs& a, hipStream_t st) {
   if (a.n == 0) return;
-  if (!a.feat || !a.w || !a.out || a.CB < 1 || a.CB > 4 || (a.Cs != 64 && a.Cs != 128) || (a.mode == 1 && !a.bias) || (a.mode == 2 && !a.aux))
+  if (!a.feat || !a.w || !a.out || a.CB < 1 || a.CB > 4 || (a.Cs != 64 && a.Cs != 128) || (a.mode == 1 && !a.bias) || (a.mode == 2 && !a.aux) ||
+      (a.user && (a.mode != 1 || !a.perm)))
     return launch_fail("image-side transposed convolution: null operand, more than 4 image channels, or feature channels other than 64 / 128");
   const auto with_cs = [&](auto cb) {
-    if (a.Cs == 64) up_img_one<T, 64, cb.value>(a, st); else up_img_one<T, 128, cb.value>(a, st);
+    if (a.user) {
+      if (a.Cs == 64) up_img_one<T, 64, cb.value, true>(a, st); else up_img_one<T, 128, cb.value, true>(a, st);
+    } else {
+      if (a.Cs == 64) up_img_one<T, 64, cb.value, false>(a, st); else up_img_one<T, 128, cb.value, false>(a, st);
+    }
   };
   if (a.CB == 1) with_cs(std::integral_constant<int, 1>{});
   else if (a.CB == 2) with_cs(std::integral_constant<int, 2>{});

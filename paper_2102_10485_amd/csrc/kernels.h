@@ -37,8 +37,6 @@ void launch_route(const int* label_ids, int n, int L, int n_labels, const GeomTa
 template <typename T>
 void launch_stage(const int* label_ids, const float* noise, const float* real, int n, int L, int zdim, int cond_g, int kp,
                   int img_c, int img_hw, const RouteBuffers& rb, T* zin, T* xd, hipStream_t st);
-template <typename T>
-void launch_unstage(const T* fake, float* out, int n, int L, int img_c, int img_hw, const RouteBuffers& rb, hipStream_t st);
 
 // Batch statistics and the normalise+activate passes.  Groups = (segment, model); rows of group (s, l) are the
 // rps rows of each of samples s*seg_samples + offs[l] .. offs[l+1].
@@ -78,7 +76,6 @@ struct NormArgs {
 void launch_bn_stats_from_partial(const NormArgs& a, const float* partial, const int* tpre, int ub_tiles, int nphase,
                                   int groups, int tile_rows, int gemm_rps, int wsplit, hipStream_t st);
 void launch_bn_running(const NormArgs& a, hipStream_t st);
-void launch_bn_from_running(const NormArgs& a, hipStream_t st);   // mean/rstd <- running statistics
 template <typename T> void launch_bn_apply(const NormArgs& a, hipStream_t st);
 constexpr int BN_RED_ROWS = 256;    // rows per block of the backward reduction (tile prefix geometry (rps, BN_RED_ROWS))
 template <typename T>
@@ -142,6 +139,8 @@ struct UpImgArgs {
   int L, n, seg, seg_samples;
   int CB, CBT, Cs, Hs;
   int mode;                 // 0: plain ; 1: + bias, tanh ; 2: times (1 - aux^2)
+  float* user;              // mode 1: the caller's NCHW fp32 images, written in place of out through perm (or NULL)
+  const int* perm;
 };
 template <typename T> void launch_up_img(const UpImgArgs& a, hipStream_t st);
 
@@ -293,6 +292,8 @@ struct Conv3Args {
   const int* sample_model;
   int L, n, H, Cin, CO;
   int out_seg, seg_samples;
+  float* user;              // forward: the caller's NCHW fp32 images, written in place of out through perm (or NULL)
+  const int* perm;
 };
 template <typename T> void launch_conv3_fwd(const Conv3Args& a, hipStream_t st);
 template <typename T> void launch_conv3_dgrad(const Conv3Args& a, hipStream_t st);

@@ -263,27 +263,6 @@ template void launch_stage<float>(const int*, const float*, const float*, int, i
 template void launch_stage<bf16_t>(const int*, const float*, const float*, int, int, int, int, int, int, int,
                                    const RouteBuffers&, bf16_t*, bf16_t*, hipStream_t);
 
-template <typename T>
-__global__ void unstage_kernel(const T* __restrict__ fake, const int* __restrict__ perm, const int* offs, int L, int n, int C,
-                               int HW, float* __restrict__ out) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long long)n * HW) return;
-  const int j = (int)(idx / HW), pix = (int)(idx - (long long)j * HW);
-  if (j >= offs[L]) return;
-  const int dst = perm[j];
-  for (int c = 0; c < C; ++c) out[((long long)dst * C + c) * HW + pix] = to_float(fake[idx * C + c]);
-}
-template <typename T>
-void launch_unstage(const T* fake, float* out, int n, int L, int img_c, int img_hw, const RouteBuffers& rb, hipStream_t st) {
-  if (n == 0) return;
-  const int HW = img_hw * img_hw;
-  const long long tot = (long long)n * HW;
-  hipLaunchKernelGGL((unstage_kernel<T>), dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, fake, rb.perm, rb.offs,
-                     L, n, img_c, HW, out);
-}
-template void launch_unstage<float>(const float*, float*, int, int, int, int, const RouteBuffers&, hipStream_t);
-template void launch_unstage<bf16_t>(const bf16_t*, float*, int, int, int, int, const RouteBuffers&, hipStream_t);
-
 // ---------------------------------------------------------------------------------------------------------
 // BatchNorm
 // ---------------------------------------------------------------------------------------------------------
@@ -441,20 +420,6 @@ __global__ void bn_running_kernel(NormArgs a) {
 }
 void launch_bn_running(const NormArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(bn_running_kernel, dim3((a.L * a.C + 255) / 256), dim3(256), 0, st, a);
-}
-
-__global__ void bn_from_running_kernel(NormArgs a) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= a.L * a.C) return;
-  const int l = idx / a.C, c = idx - l * a.C;
-  const long long o = (long long)(a.seg_first * a.L + l) * a.C + c;
-  const float rv = a.run_var[(long long)l * a.rstride + c];
-  a.mean[o] = a.run_mean[(long long)l * a.rstride + c];
-  a.var[o] = rv;
-  a.rstd[o] = 1.0f / sqrtf(rv + a.eps);
-}
-void launch_bn_from_running(const NormArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(bn_from_running_kernel, dim3((a.L * a.C + 255) / 256), dim3(256), 0, st, a);
 }
 
 // y = act(gamma * (x - mean) * rstd + beta).  One block per (sample, segment): a thread keeps the parameters of its

@@ -198,3 +198,49 @@ def test_zero_activations_behind_dropout(prec):
             assert np.all(np.abs(ref[[1, 9]]) > 0)
             assert np.max(np.abs(got[b] - ref)) <= 5e-3 * np.max(np.abs(ref))      # the bound of a network's gradient
     p.close()
+
+
+class KnownStatistics(PN.PaperNets):
+    """The oracle's generator with BatchNorm on given statistics: known[model][tag] = (mean, variance)."""
+
+    def _bn(self, k, tag, x, gamma, beta, eps, running, update):
+        mean, var = (np.asarray(v, np.float64)[None, :, None, None] for v in running[tag])
+        return (x - mean) / np.sqrt(var + eps) * gamma[None, :, None, None] + beta[None, :, None, None]
+
+
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+@pytest.mark.parametrize("spec_name,n", [("paper16", 1), ("paper16", 37), ("paper28", 21)])
+def test_paper_generator_with_running_statistics(prec, spec_name, n):
+    """Three models with biases, scales, shifts and running statistics of their own, labels in no order, one model with no sample: the
+    BatchNorm (and the ReLU in front of the first one) inside the GEMMs, the images straight into the caller's layout."""
+    torch = U.torch_mod()
+    spec, K = synth.SPECS[spec_name], 3
+    rng = np.random.default_rng(n)
+    gpu = binding.Gan(binding.make_config(spec, K, K, 40, prec, seed=1), torch.cuda.current_stream().cuda_stream)
+    orc = KnownStatistics(spec["img_c"], spec["img_hw"], K, z_dim=spec["z_dim"], g_ch=spec["g_ch"], d_ch=spec["d_ch"], seed=1)
+    known = []
+    for l in range(K):
+        p = np.asarray(synth.init_params(spec, 0, rng), np.float32).astype(np.float64)
+        named = unflat(p, orc.gs)
+        for name in named:
+            if not name.endswith(".w"):
+                named[name] = (named[name] + 0.2 * rng.normal(size=named[name].shape)).astype(np.float32).astype(np.float64)
+        orc.set_params(0, l, named)
+        gpu.set_params(0, l, flat(named, orc.gs))
+        ch = list(spec["g_ch"])
+        mean, var = (0.2 * rng.normal(size=sum(ch))).astype(np.float32), rng.uniform(0.2, 2.0, sum(ch)).astype(np.float32)
+        gpu.set_bn_running(0, l, mean, var)
+        cut = np.cumsum(ch)[:-1]
+        known.append({str(i): mv for i, mv in enumerate(zip(np.split(mean, cut), np.split(var, cut)))})
+    lab = (2 * rng.integers(0, 2, n)).astype(np.int32)
+    z = rng.normal(size=(n, spec["z_dim"])).astype(np.float32)
+    out = torch.full((n, spec["img_c"], spec["img_hw"], spec["img_hw"]), 7.0, device="cuda")
+    dl, dz = torch.from_numpy(lab).cuda(), torch.from_numpy(z).cuda()
+    gpu.generate(dl.data_ptr(), dz.data_ptr(), n, out.data_ptr(), 1)
+    got = out.cpu().numpy()
+    ref = np.empty_like(got)
+    for l in np.unique(lab):
+        ref[lab == l] = orc.g_forward(orc.G[l], z[lab == l].astype(np.float64), known[l])[0]
+    # the stated tolerances: 1e-4 for fp32 storage, 2e-2 for bf16
+    assert U.rel_l2(got, ref) <= (1e-4 if prec == binding.FP32 else 2e-2)
+    gpu.close()
