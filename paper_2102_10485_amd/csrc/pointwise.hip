@@ -1108,7 +1108,7 @@ __device__ inline double wave_sum_f64(double v) {
 // Means of single channel images, one wave each.  VEC: 16-byte loads, four in flight per lane, no barrier.  Bound by reading the images
 // once: 79 MB of 6400 32x32x3 images in 14.2 us when they come from memory (5.6 TB/s), 11.9 when a call before left them in the
 // memory-side cache; one block per channel image with 4-byte loads and an eight-step tree over LDS took 31.1 and 24.2.  It is a third
-// of the call (42 us, 40 on repeated images); the label pass below is another.
+// of the call (33 us on repeated images).
 template <bool VEC>
 __global__ __launch_bounds__(256) void anova_image_mean_kernel(const float* __restrict__ images, long long count, int HW, double* __restrict__ x) {
   const long long ic = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);      // image * C + channel
@@ -1138,63 +1138,91 @@ __global__ __launch_bounds__(256) void anova_image_mean_kernel(const float* __re
   s = wave_sum_f64(s);
   if (lane == 0) x[ic] = s / (double)HW;
 }
-// One block per label: the sum of its images' means and their number, then the squared deviations from the group mean, both
-// over all channels.  The kernel is two chains of memory latencies (labels, then the means of the few that match), so a
-// block is 1024 threads that fetch eight labels each, and the matching means of a trip are in flight together: 6400 labels are
-// one trip.  (256 threads, the means fetched one after the other: 20 us of a 46 us call.)
-constexpr int ANOVA_T = 1024;
+// One block per label: the sum of its images' means and their number, then the squared deviations from the group mean, over all
+// channels.  The kernel is a chain of latencies: the labels, the means of the few that match, two sums across lanes.  So the label's
+// images are first gathered into a list in LDS (eight labels a thread, places from ballots, in a fixed order), then four waves share
+// the list of one channel, so that a sum over lanes is one butterfly and four values, and up to four means a lane stay in registers for
+// the second pass: 6400 images, 100 labels 14.1 -> 6.2 us of a call of 40.1, now 33.1 (before: 1024 threads
+// with eight labels each, every sum over all of them, once per channel).
+constexpr int ANOVA_T = 1024, ANOVA_W = ANOVA_T / 64, ANOVA_E = 8, ANOVA_KEEP = 4;
 __global__ __launch_bounds__(ANOVA_T) void anova_group_kernel(const int* __restrict__ label_ids, const double* __restrict__ x, int n, int C,
                                                               double* __restrict__ gsum, double* __restrict__ ssw, int* __restrict__ gcnt) {
-  __shared__ double sh[5][ANOVA_T / 64];
+  __shared__ int list[ANOVA_E * ANOVA_T];
+  __shared__ int votes_n[ANOVA_E * ANOVA_W];
+  __shared__ double sh[ANOVA_W];
   const int k = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double mean[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int pass = 0; pass < 2; ++pass) {
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
-    int cnt = 0;
-    for (int i0 = threadIdx.x; i0 < n; i0 += 8 * ANOVA_T) {
-      int lab[8];
-      double v[8][4];
+  const int c = wave >> 2, q0 = (wave & 3) * 64 + lane;                // this wave's channel, and its lane's first place in the list
+  // the label's images among ANOVA_E * ANOVA_T from i0 on -> list; returns their number
+  const auto gather = [&](int i0) {
+    int lab[ANOVA_E];
+    unsigned long long votes[ANOVA_E];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) lab[e] = i0 + ANOVA_T * e < n ? label_ids[i0 + ANOVA_T * e] : -1;
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (lab[e] == k) {
-          const double* xi = x + (long long)(i0 + ANOVA_T * e) * C;
-#pragma unroll
-          for (int c = 0; c < 4; ++c) v[e][c] = c < C ? xi[c] : 0.0;
-        }
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (lab[e] == k) {
-          ++cnt;
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const double d = v[e][c] - mean[c];
-            s[c] += pass ? d * d : d;
-          }
-        }
+    for (int e = 0; e < ANOVA_E; ++e) {
+      const int i = i0 + ANOVA_T * e + (int)threadIdx.x;
+      lab[e] = i < n ? label_ids[i] : -1;
     }
-    // per wave, then the waves' sums by every wave alike (16 lanes of a butterfly): all threads need the mean
-    const double all5[5] = {wave_sum_f64(s[0]), wave_sum_f64(s[1]), wave_sum_f64(s[2]), wave_sum_f64(s[3]), wave_sum_f64((double)cnt)};
-    if (lane == 0) {
 #pragma unroll
-      for (int c = 0; c < 5; ++c) sh[c][wave] = all5[c];
+    for (int e = 0; e < ANOVA_E; ++e) {
+      votes[e] = __ballot(lab[e] == k);
+      if (lane == 0) votes_n[e * ANOVA_W + wave] = __popcll(votes[e]);
     }
     __syncthreads();
-    double t[5];
+    // running sums of the 128 counts: two a lane, every wave alike
+    const int a = votes_n[2 * lane], b = votes_n[2 * lane + 1];
+    int run = a + b;
 #pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      t[c] = sh[c][lane & (ANOVA_T / 64 - 1)];
-#pragma unroll
-      for (int o = ANOVA_T / 128; o > 0; o >>= 1) t[c] += __shfl_xor(t[c], o, 64);
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(run, o, 64);
+      if (lane >= o) run += t;
     }
-    __syncthreads();                                                   // sh is written again by the second pass
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      if (threadIdx.x == 0 && c < C) (pass ? ssw : gsum)[(long long)k * C + c] = t[c];
-      if (!pass) mean[c] = t[4] > 0.0 ? t[c] / t[4] : 0.0;
+    for (int e = 0; e < ANOVA_E; ++e) {
+      const int at = e * ANOVA_W + wave;                                // the counts before this one
+      const int before = __shfl(run - a - b, at >> 1, 64) + ((at & 1) ? __shfl(a, at >> 1, 64) : 0);
+      if (lab[e] == k) list[before + __popcll(votes[e] & ((1ull << lane) - 1))] = i0 + ANOVA_T * e + (int)threadIdx.x;
     }
-    if (threadIdx.x == 0 && !pass) gcnt[k] = (int)t[4];
+    const int total = __shfl(run, 63, 64);
+    __syncthreads();
+    return total;
+  };
+  static_assert(ANOVA_E * ANOVA_W == 128, "two counts a lane");
+  double mean = 0.0;
+  double keep[ANOVA_KEEP];
+  int total = 0;
+  long long all = 0;
+  const bool once = n <= ANOVA_E * ANOVA_T;
+  for (int pass = 0; pass < 2; ++pass) {
+    double s = 0.0;
+    for (int i0 = 0; i0 < n; i0 += ANOVA_E * ANOVA_T) {
+      if (!once || pass == 0) {
+        total = gather(i0);
+        if (pass == 0) all += total;
+      }
+      if (c < C) {
+        const auto add = [&](double v) {
+          const double d = v - mean;
+          s += pass ? d * d : d;
+        };
+        if (!once || pass == 0) {
+#pragma unroll
+          for (int e = 0; e < ANOVA_KEEP; ++e) keep[e] = q0 + 256 * e < total ? x[(long long)list[q0 + 256 * e] * C + c] : 0.0;
+        }
+#pragma unroll
+        for (int e = 0; e < ANOVA_KEEP; ++e)
+          if (q0 + 256 * e < total) add(keep[e]);
+#pragma unroll 8
+        for (int i = q0 + 256 * ANOVA_KEEP; i < total; i += 256) add(x[(long long)list[i] * C + c]);
+      }
+      if (!once) __syncthreads();                                       // the list is written again
+    }
+    s = wave_sum_f64(s);
+    if (lane == 0) sh[wave] = s;
+    __syncthreads();
+    const double t = ((sh[4 * c] + sh[4 * c + 1]) + sh[4 * c + 2]) + sh[4 * c + 3];
+    if (!pass) mean = all > 0 ? t / (double)all : 0.0;
+    if ((threadIdx.x & 255) == 0 && c < C) (pass ? ssw : gsum)[(long long)k * C + c] = t;
+    if (threadIdx.x == 0 && !pass) gcnt[k] = (int)all;
+    __syncthreads();                                                    // sh is written again by the second pass
   }
 }
 void launch_anova(const int* label_ids, const float* images, int n, int n_labels, int C, int HW, double* x, double* gsum,

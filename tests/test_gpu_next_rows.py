@@ -220,6 +220,21 @@ def test_anova_f_odd_sides_and_more_images_than_one_trip(hw, n):
     np.testing.assert_allclose(F, ref, rtol=1e-9)
 
 
+@pytest.mark.parametrize("n", [1023, 1025, 5003, 8192])
+def test_anova_f_of_uneven_labels(n):
+    """One label with most of the images (more than the four means a lane keeps between the passes), one with a single image, some with
+    none, in lists that end inside and at the end of a wave."""
+    rng = np.random.default_rng(n)
+    lab = np.where(rng.random(n) < 0.9, 6, rng.integers(0, 4, n)).astype(np.int32)
+    lab[n // 2] = 5
+    img = np.tanh(rng.normal(size=(n, 2, 4, 4)) + 0.3 * lab[:, None, None, None]).astype(np.float32)
+    rc, ref = O.anova_f(lab, img, 8)
+    dl, dx = U.dev(lab), U.dev(img)
+    st, F = binding.anova_f_static(dl.data_ptr(), dx.data_ptr(), n, 8, 2, 4, U.torch_mod().cuda.current_stream().cuda_stream)
+    assert rc == 0 and st == binding.GAN_OK
+    np.testing.assert_allclose(F, ref, rtol=1e-9)            # sums in double on both sides, as above
+
+
 def test_anova_f_after_a_failed_call_of_the_caller():
     """An error that some other HIP call of the thread left behind is not the analysis' own."""
     torch = U.torch_mod()
