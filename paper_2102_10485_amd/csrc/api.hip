@@ -200,6 +200,9 @@ int ub_tiles(const gan_ctx* c, int n, int rps, int tile_rows) {
   return (int)(((long long)n * rps) / tile_rows) + (n < c->L ? n : c->L);
 }
 
+// row blocks of a BatchNorm's backward reduction, from the sizing batch like the tiles
+int red_rows(const gan_ctx* c, int rps) { return bn_red_rows((long long)c->NB * rps, c->L); }
+
 // ---- profiling: two events around a launch ------------------------------------------------------------
 struct Scope {
   gan_ctx* c; int idx = -1; hipStream_t st;
@@ -677,10 +680,9 @@ void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool update_runn
   {
     const ConvTile tile = layer_tile(c, gemm_mode, a.C * col_groups, gemm_rps, a.nseg);   // of the GEMM that left the partials (N = C * col_groups)
     const int tr = conv_tile_rows((int)sizeof(T), tile), gemm_phases = gemm_mode == MODE_UP ? 4 : 1;
-    a.fold_running = update_running && a.nseg == 1 && a.run_mean && a.run_var;
+    a.fold_running = update_running;
     launch_bn_stats_from_partial(a, c->stat_partial, tpre_of(c, gemm_rps, tr), ub_tiles(c, a.n, gemm_rps, tr), gemm_phases, col_groups, tr,
                                  gemm_rps, conv_stat_split((int)sizeof(T), tile), c->st);
-    if (update_running && !a.fold_running) launch_bn_running(a, c->st);
   }
   Scope s(c, "bn_apply", 0, 2 * elems * sizeof(T));
   launch_bn_apply<T>(a, c->st);
@@ -690,14 +692,13 @@ void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool update_runn
 template <typename T>
 void bn_backward(gan_ctx* c, NormArgs a, const void* x, const void* dy, void* dx, bool param_grads) {
   a.x = x; a.dy = dy; a.y = dx;
-  a.fold_grads = param_grads && a.nseg == 1;
+  a.param_grads = param_grads;
   const double elems = (double)a.n * a.nseg * a.rps * a.C;
   {
     Scope s(c, "bn_bwd_reduce", 0, 2 * elems * sizeof(T));
-    launch_bn_bwd_reduce<T>(a, tpre_of(c, a.rps, BN_RED_ROWS), tmodel_of(c, a.rps, BN_RED_ROWS), ub_tiles(c, a.n, a.rps, BN_RED_ROWS),
-                            c->stat_partial, c->st);
+    const int tr = a.red_rows = red_rows(c, a.rps);
+    launch_bn_bwd_reduce<T>(a, tpre_of(c, a.rps, tr), tmodel_of(c, a.rps, tr), ub_tiles(c, a.n, a.rps, tr), c->stat_partial, c->st);
   }
-  if (param_grads && !a.fold_grads) launch_bn_param_grad(a, c->st);
   Scope s(c, "bn_bwd_apply", 0, 3 * elems * sizeof(T));
   launch_bn_bwd_apply<T>(a, c->st);
 }
@@ -1301,10 +1302,11 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
       }
       reg_gemm(MODE_DENSE, d1.Cs, d1.Hs * d1.Hs, nseg);                         // first conv (patch GEMM)
     }
-    // row space of every BatchNorm, in blocks of BN_RED_ROWS rows (backward reduction)
-    reg(c->G.h0 * c->G.h0, BN_RED_ROWS);
-    for (size_t i = 0; i + 1 < c->G.conv.size(); ++i) reg(4 * c->G.conv[i].Hs * c->G.conv[i].Hs, BN_RED_ROWS);
-    for (size_t j = 1; j < c->D.conv.size(); ++j) reg(c->D.conv[j].Hs * c->D.conv[j].Hs, BN_RED_ROWS);
+    // row space of every BatchNorm, in the row blocks of its backward reduction
+    auto reg_bn = [&](int rps) { reg(rps, red_rows(c, rps)); };
+    reg_bn(c->G.h0 * c->G.h0);
+    for (size_t i = 0; i + 1 < c->G.conv.size(); ++i) reg_bn(4 * c->G.conv[i].Hs * c->G.conv[i].Hs);
+    for (size_t j = 1; j < c->D.conv.size(); ++j) reg_bn(c->D.conv[j].Hs * c->D.conv[j].Hs);
   }
   // two sets of routing buffers: the training step's (what gan_get_losses / gan_get_routing report) and one for
   // gan_generate / gan_sample, so that generating between a step and its queries changes nothing they return
@@ -1371,16 +1373,17 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
     }
     // and the BatchNorm backward reduction: segments x row blocks x channels x 2
     {
-      size_t v = (size_t)ub_tiles(c, NB, c->G.h0 * c->G.h0, BN_RED_ROWS) * c->G.C0;
+      const auto red_tiles = [&](int rps) { return ub_tiles(c, NB, rps, red_rows(c, rps)); };
+      size_t v = (size_t)red_tiles(c->G.h0 * c->G.h0) * c->G.C0;
       mx = v > mx ? v : mx;
       for (size_t i = 0; i + 1 < c->G.conv.size(); ++i) {
         const ConvLayer& cl = c->G.conv[i];
-        v = (size_t)ub_tiles(c, NB, 4 * cl.Hs * cl.Hs, BN_RED_ROWS) * cl.Cb;
+        v = (size_t)red_tiles(4 * cl.Hs * cl.Hs) * cl.Cb;
         mx = v > mx ? v : mx;
       }
       for (size_t j = 1; j < c->D.conv.size(); ++j) {
         const ConvLayer& cl = c->D.conv[j];
-        v = (size_t)2 * ub_tiles(c, NB, cl.Hs * cl.Hs, BN_RED_ROWS) * cl.Cs;
+        v = (size_t)2 * red_tiles(cl.Hs * cl.Hs) * cl.Cs;
         mx = v > mx ? v : mx;
       }
     }

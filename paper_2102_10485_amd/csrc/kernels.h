@@ -68,8 +68,9 @@ struct NormArgs {
   // on through both, to the convolution's output
   int pre_act, pre_drop;    // pre_drop: x is +0 where dropped (see dropped())
   float pre_slope, pre_scale;
-  int fold_running;         // statistics from the GEMM's partials, one segment: that kernel also updates the running statistics
-  int fold_grads;           // backward reduction, one segment: its last stage also writes dgamma / dbeta
+  int fold_running;         // statistics from the GEMM's partials: that kernel also updates the running statistics
+  int red_rows;             // backward reduction: rows per block (bn_red_rows)
+  int param_grads;          // backward reduction: its last stage also writes dgamma / dbeta, the segments' sums added in order
 };
 // statistics from the per-tile column sums a GEMM left behind (stat_partial of ConvArgs)
 // (wsplit: sub-tiles per tile, conv_stat_split of the GEMM's tile)
@@ -77,10 +78,9 @@ void launch_bn_stats_from_partial(const NormArgs& a, const float* partial, const
                                   int groups, int tile_rows, int gemm_rps, int wsplit, hipStream_t st);
 void launch_bn_running(const NormArgs& a, hipStream_t st);
 template <typename T> void launch_bn_apply(const NormArgs& a, hipStream_t st);
-constexpr int BN_RED_ROWS = 256;    // rows per block of the backward reduction (tile prefix geometry (rps, BN_RED_ROWS))
+int bn_red_rows(long long rows, int L);     // rows per block of the backward reduction over `rows` rows of L models (its tile prefix geometry)
 template <typename T>
 void launch_bn_bwd_reduce(const NormArgs& a, const int* tpre, const int* tmodel, int ub_tiles, float* partial, hipStream_t st);
-void launch_bn_param_grad(const NormArgs& a, hipStream_t st);
 template <typename T> void launch_bn_bwd_apply(const NormArgs& a, hipStream_t st);
 
 // The layers touching the image (1..4 channels) run as row-by-row GEMMs over an explicit patch matrix.

@@ -2,6 +2,8 @@
 // fused with the activation, D's linear head and the two logistic costs (Eq. 3, Eq. 4), Adam, layout copies.
 // Every reduction has a fixed order that does not depend on the number of models, so results are deterministic
 // and a model's numbers do not change with what else is in the launch.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace gan {
@@ -298,6 +300,14 @@ __device__ inline void loadv(const bf16_t* p, float (&v)[8]) {
   v[4] = __uint_as_float(t.z << 16); v[5] = __uint_as_float(t.z & 0xffff0000u);
   v[6] = __uint_as_float(t.w << 16); v[7] = __uint_as_float(t.w & 0xffff0000u);
 }
+// EPV consecutive per-channel parameters (channel counts and the layout of the parameter blocks keep them 16-byte aligned)
+template <int N> __device__ inline void load_params(const float* p, float (&v)[N]) {
+#pragma unroll
+  for (int k = 0; k < N; k += 4) {
+    const float4 t = *reinterpret_cast<const float4*>(p + k);
+    v[k] = t.x; v[k + 1] = t.y; v[k + 2] = t.z; v[k + 3] = t.w;
+  }
+}
 __device__ inline void storev(float* p, const float (&v)[4]) { store4(p, v); }
 __device__ inline void storev(bf16_t* p, const float (&v)[8]) {
   uint4 t;
@@ -312,93 +322,107 @@ __device__ inline void storev(bf16_t* p, const float (&v)[8]) {
 
 // mean / var / rstd from what the producing GEMM left per sub-tile and column: (sum, sum of squared deviations from
 // the sub-tile's mean); a tile of tile_rows rows is wsplit sub-tiles of tile_rows / wsplit rows, the last ones of a
-// model's last tile possibly empty.  Sub-tiles (and output phases, and column runs) of one (segment, model) are merged
-// in a fixed order with the pairwise update  mean += d n_t/(n+n_t),  M2 += M2_t + d^2 n n_t/(n+n_t),  d = mean_t - mean.
+// model's last tile possibly empty.  Sub-tiles (and output phases, and column runs) of one (segment, model) are added
+// in a fixed order in double:  N mean = sum s_t,  N var = sum (M2_t + s_t^2 / n_t) - (sum s_t)^2 / N.
 // The GEMM's N columns are `groups` runs of the C channels (the linear layer feeding G's first BatchNorm has one
 // run per pixel of the first feature map; the convolutions have one).
-// A block = 16 channels x RED_SLICES slices of the (phase, sub-tile) sequence of one (segment, model): every thread
-// merges its contiguous slice in order, then the slices are merged in order.  The slicing depends on the model's own
-// tile count only.
-constexpr int RED_SLICES = 16;      // slices of the backward reduction's second stage
-// Threads of a block = SL slices x CX channels.  16 x 16 as a rule; 64 x 4 when a model has so many tiles (one pair
-// over the whole batch) that sixteen chains of dependent merges would be the whole kernel.  The choice follows from
+// A block = CX channels x SL slices of one model's entries: phase sl % nphase, of that phase every (SL / nphase)-th (sub-tile, column run)
+// from sl / nphase on; first of the first segment, then of the second: with both in one block it also updates the running statistics.
+// Bound by the latency of the entries' loads, which plain sums leave independent of each other (eight in flight); as a chain of pairwise
+// merges in fp32, a division each, the launches of one step took 135 us of a 2774 us step (one 32x32 pair, 1000 images) and 62 of 574
+// (one 28x28 pair, 64 images), now 54 and 21.
+// Threads of a block: 16 channels x 16 slices as a rule; 64 slices, or 128 of 8 channels, when a model has so many entries that
+// sixteen slices would be long and a launch has few blocks (one pair over the whole batch).  The choice follows from
 // the configuration (tile bound per model), never from a batch.
 template <int SL, int CX>
-__global__ __launch_bounds__(256) void bn_stats_from_partial_kernel(NormArgs a, const float* __restrict__ partial,
-                                                                    const int* __restrict__ tpre, int ub_tiles, int nphase,
-                                                                    int groups, int tile_rows, int gemm_rps, int wsplit) {
-  static_assert(SL * CX == 256, "block shape");
-  __shared__ float sh[SL][CX][3];
+__global__ __launch_bounds__(SL * CX) void bn_stats_from_partial_kernel(NormArgs a, const float* __restrict__ partial,
+                                                                        const int* __restrict__ tpre, int ub_tiles, int nphase,
+                                                                        int groups, unsigned groups_inv, int tile_rows, int gemm_rps, int wsplit) {
+  constexpr int WAVES = SL * CX / 64;
+  __shared__ double sh[2][WAVES][CX][2];
   const int cx = threadIdx.x % CX, sl = threadIdx.x / CX;
   const int cblocks = (a.C + CX - 1) / CX;
   const int c = (blockIdx.x % cblocks) * CX + cx;
-  const int l = (blockIdx.x / cblocks) % a.L;
-  const int sidx = blockIdx.x / (cblocks * a.L);
+  const int l = blockIdx.x / cblocks;
   const int cnt = a.offs[l + 1] - a.offs[l];
   if (cnt == 0) return;                                // block-uniform
   const int rows = cnt * gemm_rps;                     // rows of this model in the GEMM's row space (per phase)
-  const int t0 = tpre[l], nsub = (tpre[l + 1] - t0) * wsplit, sub_rows = tile_rows / wsplit;
-  // the sequence a slice is cut from: (phase, sub-tile, column run), the column runs fastest
-  const int seq = nphase * nsub * groups, per = (seq + SL - 1) / SL;
-  float n = 0.f, mean = 0.f, m2 = 0.f;
-  const float inv_sub = 1.f / (float)sub_rows;
-  if (c < a.C)
-#pragma unroll 4
-    for (int qg = sl * per; qg < min(seq, (sl + 1) * per); ++qg) {  // (unrolled: the loads of four entries are in flight together)
-      const int q = qg / groups, g = qg - q * groups;
-      const int ph = q / nsub, t = q - ph * nsub;
-      const int left = rows - t * sub_rows;
-      if (left <= 0) continue;                         // an empty sub-tile at the end of the model's last tile: never written
-      const float nt = (float)min(sub_rows, left);
-      const long long o = ((((long long)ph * a.nseg + sidx) * ub_tiles * wsplit + (long long)t0 * wsplit + t) * ((long long)a.C * groups) + g * a.C + c) * 2;
-      // one division per merge: a full sub-tile's mean through the reciprocal of its height, the second weight from the first
-      const float d = (left >= sub_rows ? partial[o] * inv_sub : partial[o] / nt) - mean;
-      const float nn = n + nt;
-      const float w = nt / nn;
-      mean += d * w;
-      m2 += partial[o + 1] + d * d * (n * w);
-      n = nn;
+  const int sub_rows = tile_rows / wsplit, nsub = (rows + sub_rows - 1) / sub_rows;      // sub-tiles that hold rows: the others are never written
+  const int seq = nsub * groups;                       // entries of a phase, the column runs fastest
+  const int ph = sl & (nphase - 1), first = sl / nphase, step = SL / nphase;
+  const double inv_sub = 1.0 / (double)sub_rows, inv_last = 1.0 / (double)(rows - (nsub - 1) * sub_rows);
+  const long long row_len = (long long)a.C * groups;
+  for (int sidx = 0; sidx < a.nseg; ++sidx) {
+    const float2* const p = reinterpret_cast<const float2*>(partial) +
+                            (((long long)ph * a.nseg + sidx) * ub_tiles * wsplit + (long long)tpre[l] * wsplit) * row_len + min(c, a.C - 1);
+    double s = 0, q2 = 0;
+    for (int e0 = first; e0 < seq; e0 += 8 * step) {
+      float2 v[8];
+      int t[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int e = min(e0 + k * step, seq - 1);
+        t[k] = groups_inv ? (int)__umulhi((unsigned)e, groups_inv) : e;      // e / groups
+        v[k] = p[t[k] * row_len + (long long)(e - t[k] * groups) * a.C];
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (e0 + k * step < seq) {
+          const double st = v[k].x;
+          s += st;
+          q2 += (double)v[k].y + st * st * (t[k] + 1 < nsub ? inv_sub : inv_last);
+        }
     }
-  sh[sl][cx][0] = n; sh[sl][cx][1] = mean; sh[sl][cx][2] = m2;
+#pragma unroll
+    for (int d = CX; d < 64; d <<= 1) {
+      s += __shfl_xor(s, d, 64);
+      q2 += __shfl_xor(q2, d, 64);
+    }
+    if ((threadIdx.x & 63) < CX) {
+      sh[sidx][threadIdx.x >> 6][cx][0] = s;
+      sh[sidx][threadIdx.x >> 6][cx][1] = q2;
+    }
+  }
   __syncthreads();
   if (sl != 0 || c >= a.C) return;
-  for (int k = 1; k < SL; ++k) {
-    const float nt = sh[k][cx][0];
-    if (nt == 0.f) continue;                           // an empty slice
-    const float d = sh[k][cx][1] - mean;
-    const float nn = n + nt;
-    const float w = nt / nn;
-    mean += d * w;
-    m2 += sh[k][cx][2] + d * d * (n * w);
-    n = nn;
+  const double N = (double)rows * nphase * groups;
+  const long long S = (long long)cnt * a.rps;
+  const long long ro = (long long)l * a.rstride + c;
+  float rm = 0.f, rv = 0.f;
+  if (a.fold_running) { rm = a.run_mean[ro]; rv = a.run_var[ro]; }
+  for (int sidx = 0; sidx < a.nseg; ++sidx) {
+    double s = 0, q2 = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) { s += sh[sidx][w][cx][0]; q2 += sh[sidx][w][cx][1]; }
+    const double m = s / N;
+    const float mean = (float)m, var = (float)fmax((q2 - s * m) / N, 0.0);
+    const long long o = (long long)((a.seg_first + sidx) * a.L + l) * a.C + c;
+    a.mean[o] = mean;
+    a.var[o] = var;
+    a.rstd[o] = 1.0f / sqrtf(var + a.eps);
+    rm = (1.f - a.momentum) * rm + a.momentum * mean;
+    if (S > 1) rv = (1.f - a.momentum) * rv + a.momentum * var * ((float)S / (float)(S - 1));
   }
-  const float var = m2 / n;
-  const long long o = (long long)((a.seg_first + sidx) * a.L + l) * a.C + c;
-  a.mean[o] = mean;
-  a.var[o] = var;
-  a.rstd[o] = 1.0f / sqrtf(var + a.eps);
-  if (a.fold_running) {     // one segment: what bn_running_kernel would do next, without the launch
-    const long long S = (long long)cnt * a.rps;
-    const long long ro = (long long)l * a.rstride + c;
-    a.run_mean[ro] = (1.f - a.momentum) * a.run_mean[ro] + a.momentum * mean;
-    if (S > 1) a.run_var[ro] = (1.f - a.momentum) * a.run_var[ro] + a.momentum * var * ((float)S / (float)(S - 1));
-  }
+  if (a.fold_running) { a.run_mean[ro] = rm; a.run_var[ro] = rv; }     // what bn_running_kernel would do next, without the launch
 }
 void launch_bn_stats_from_partial(const NormArgs& a, const float* partial, const int* tpre, int ub_tiles, int nphase,
                                   int groups, int tile_rows, int gemm_rps, int wsplit, hipStream_t st) {
   if ((long long)a.nseg * a.L * a.C == 0) return;
   if (!tpre || !partial) return launch_fail("BatchNorm statistics: no tile prefix array or no partial sums");
+  if (a.nseg > 2) return launch_fail("BatchNorm statistics: more than two segments");
   if (wsplit < 1 || tile_rows % wsplit) return launch_fail("BatchNorm statistics: the tile height is not a whole number of sub-tiles");
-  const bool many = (long long)ub_tiles * wsplit * nphase * groups > 1024LL * a.L;       // entries per model, by the launch's upper bound
-  if (many) {
-    const long long tot = (long long)a.nseg * a.L * ((a.C + 3) / 4);
-    hipLaunchKernelGGL((bn_stats_from_partial_kernel<64, 4>), dim3((unsigned)tot), dim3(256), 0, st, a, partial, tpre, ub_tiles, nphase,
-                       groups, tile_rows, gemm_rps, wsplit);
-  } else {
-    const long long tot = (long long)a.nseg * a.L * ((a.C + 15) / 16);
-    hipLaunchKernelGGL((bn_stats_from_partial_kernel<16, 16>), dim3((unsigned)tot), dim3(256), 0, st, a, partial, tpre, ub_tiles, nphase,
-                       groups, tile_rows, gemm_rps, wsplit);
-  }
+  if (nphase != 1 && nphase != 4) return launch_fail("BatchNorm statistics: one output phase or four");
+  // ceil(2^32 / groups): the high half of its product with an entry's number is the quotient while number * groups < 2^32
+  if ((double)ub_tiles * wsplit * groups * groups >= 4294967296.0) return launch_fail("BatchNorm statistics: too many column runs");
+  const unsigned inv = groups > 1 ? (unsigned)(((1ULL << 32) + groups - 1) / groups) : 0;
+  const auto go = [&](auto kernel, int sl, int cx) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(a.L * ((a.C + cx - 1) / cx))), dim3(sl * cx), 0, st, a, partial, tpre, ub_tiles, nphase, groups,
+                       inv, tile_rows, gemm_rps, wsplit);
+  };
+  const double entries = (double)ub_tiles * wsplit * nphase * groups / a.L;       // per model, by the launch's upper bound
+  if (entries > 1024) go(&bn_stats_from_partial_kernel<128, 8>, 128, 8);
+  else if (entries > 128) go(&bn_stats_from_partial_kernel<64, 16>, 64, 16);
+  else go(&bn_stats_from_partial_kernel<16, 16>, 16, 16);
 }
 
 // running <- (1 - momentum) running + momentum * batch, once per segment in order; unbiased variance stored.
@@ -422,7 +446,13 @@ void launch_bn_running(const NormArgs& a, hipStream_t st) {
   hipLaunchKernelGGL(bn_running_kernel, dim3((a.L * a.C + 255) / 256), dim3(256), 0, st, a);
 }
 
-// y = act(gamma * (x - mean) * rstd + beta).  One block per (sample, segment): a thread keeps the parameters of its
+// Blocks that share a sample in the two apply passes: one, unless the samples alone are too few blocks to fill the chip.
+// One 28x28 pair of 64 samples, 12544 values each: 64 blocks take 6.8-7.6 us a pass, 4.0-5.0 us with shared samples.
+static unsigned apply_split(const NormArgs& a, int epv) {
+  const long long blocks = (long long)a.n * a.nseg, most = ((long long)a.rps * a.C / epv + 255) / 256;
+  return (unsigned)std::max(1LL, std::min(1024 / blocks, most));
+}
+// y = act(gamma * (x - mean) * rstd + beta).  One block (or gridDim.z of them) per (sample, segment): a thread keeps the parameters of its
 // 16 bytes of channels in registers and walks down the sample's rows.
 template <typename T>
 __global__ __launch_bounds__(256) void bn_apply_kernel(NormArgs a) {
@@ -441,17 +471,17 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(NormArgs a) {
   const int total = a.rps * cg;
   int cur = -1;
   float sc[EPV], mu[EPV], be[EPV];
-  for (int t = threadIdx.x; t < total; t += 256) {
+  for (int t = blockIdx.z * 256 + threadIdx.x; t < total; t += 256 * gridDim.z) {
     const int r = t / cg, g = t - r * cg;
     if (g != cur) {
       cur = g;
+      float rs[EPV];
+      load_params(a.gamma + (long long)l * a.pstride + g * EPV, sc);
+      load_params(a.rstd + so + g * EPV, rs);
+      load_params(a.mean + so + g * EPV, mu);
+      load_params(a.beta + (long long)l * a.pstride + g * EPV, be);
 #pragma unroll
-      for (int k = 0; k < EPV; ++k) {
-        const int c = g * EPV + k;
-        sc[k] = a.gamma[(long long)l * a.pstride + c] * a.rstd[so + c];
-        mu[k] = a.mean[so + c];
-        be[k] = a.beta[(long long)l * a.pstride + c];
-      }
+      for (int k = 0; k < EPV; ++k) sc[k] *= rs[k];
     }
     float v[EPV];
     loadv(x + (long long)r * a.C + g * EPV, v);
@@ -465,14 +495,14 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(NormArgs a) {
 }
 template <typename T> void launch_bn_apply(const NormArgs& a, hipStream_t st) {
   if (a.n == 0 || a.nseg == 0) return;
-  hipLaunchKernelGGL((bn_apply_kernel<T>), dim3((unsigned)a.n, (unsigned)a.nseg), dim3(256), 0, st, a);
+  hipLaunchKernelGGL((bn_apply_kernel<T>), dim3((unsigned)a.n, (unsigned)a.nseg, apply_split(a, Vec16<T>::N)), dim3(256), 0, st, a);
 }
 template void launch_bn_apply<float>(const NormArgs&, hipStream_t);
 template void launch_bn_apply<bf16_t>(const NormArgs&, hipStream_t);
 
 // sums[g][c] = (sum g, sum g * xhat) with g = dy * act'(u), u = gamma * xhat + beta.
-// Stage 1: block (tile of BN_RED_ROWS rows of one model, segment), all channels -> partial[segment][tile][C][2].
-// Stage 2: the tiles of a (segment, model) added in order.
+// Stage 1: block (tile of red_rows rows of one model, segment), all channels -> partial[segment][tile][C][2].
+// Stage 2: the tiles of a (segment, model) added in a fixed order.
 template <typename T>
 __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(NormArgs a, const int* __restrict__ tpre, const int* __restrict__ tmodel,
                                                             int ub_tiles, float* __restrict__ partial) {
@@ -498,19 +528,18 @@ __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(NormArgs a, const in
   const int RL = 256 / cg;                          // row lanes
   const int cl = threadIdx.x % cg, rl = threadIdx.x / cg;
   const long long rows = (long long)cnt * a.rps;
-  const long long r0 = (long long)(tile - tpre[l]) * BN_RED_ROWS;
-  const long long r1 = min(rows, r0 + BN_RED_ROWS);
+  const long long r0 = (long long)(tile - tpre[l]) * a.red_rows;
+  const long long r1 = min(rows, r0 + a.red_rows);
   const long long base = ((long long)seg * a.seg_samples + a.offs[l]) * a.rps * a.C + cl * EPV;
   const T* x = static_cast<const T*>(a.x) + base;
   const T* dy = static_cast<const T*>(a.dy) + base;
   float mu[EPV], rs[EPV], ga[EPV], be[EPV], sg[EPV], sgx[EPV];
+  load_params(a.mean + (long long)g * a.C + cl * EPV, mu);
+  load_params(a.rstd + (long long)g * a.C + cl * EPV, rs);
+  load_params(a.gamma + (long long)l * a.pstride + cl * EPV, ga);
+  load_params(a.beta + (long long)l * a.pstride + cl * EPV, be);
 #pragma unroll
   for (int e = 0; e < EPV; ++e) {
-    const int c = cl * EPV + e;
-    mu[e] = a.mean[(long long)g * a.C + c];
-    rs[e] = a.rstd[(long long)g * a.C + c];
-    ga[e] = a.gamma[(long long)l * a.pstride + c];
-    be[e] = a.beta[(long long)l * a.pstride + c];
     sg[e] = 0.f;
     sgx[e] = 0.f;
   }
@@ -562,69 +591,69 @@ __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(NormArgs a, const in
     partial[(((long long)sidx * ub_tiles + tile) * a.C + c) * 2 + w] = acc;
   }
 }
-__global__ __launch_bounds__(256) void bn_bwd_reduce_final_kernel(NormArgs a, const int* __restrict__ tpre, int ub_tiles,
-                                                                  const float* __restrict__ partial) {
-  __shared__ float sh[RED_SLICES][16][2];
+// (SL slices x 16 channels of one model, slice s adding every SL-th tile from s on: 16, or 64 when a model has many tiles; both segments
+// in one block, which with that also adds them up to the parameters' gradients)
+template <int SL>
+__global__ __launch_bounds__(SL * 16) void bn_bwd_reduce_final_kernel(NormArgs a, const int* __restrict__ tpre, int ub_tiles,
+                                                                      const float* __restrict__ partial) {
+  __shared__ float sh[2][SL / 4][16][2];
   const int cx = threadIdx.x & 15, sl = threadIdx.x >> 4;
   const int cblocks = (a.C + 15) / 16;
   const int c = (blockIdx.x % cblocks) * 16 + cx;
-  const int l = (blockIdx.x / cblocks) % a.L;
-  const int sidx = blockIdx.x / (cblocks * a.L);
+  const int l = blockIdx.x / cblocks;
   if (a.offs[l + 1] == a.offs[l]) return;              // block-uniform
-  const int t0 = tpre[l], ntiles = tpre[l + 1] - t0;
-  const int per = (ntiles + RED_SLICES - 1) / RED_SLICES;
-  float s0 = 0.f, s1 = 0.f;
-  if (c < a.C)
+  const int t0 = tpre[l], t1 = tpre[l + 1];
+  for (int sidx = 0; sidx < a.nseg; ++sidx) {
+    float s0 = 0.f, s1 = 0.f;
+    if (c < a.C)
 #pragma unroll 8
-    for (int t = t0 + sl * per; t < t0 + min(ntiles, (sl + 1) * per); ++t) {     // (eight tiles' loads in flight, added in order)
-      const long long o = (((long long)sidx * ub_tiles + t) * a.C + c) * 2;
-      s0 += partial[o];
-      s1 += partial[o + 1];
+      for (int t = t0 + sl; t < t1; t += SL) {         // (eight tiles' loads in flight, added in order)
+        const float2 e = *reinterpret_cast<const float2*>(partial + (((long long)sidx * ub_tiles + t) * a.C + c) * 2);
+        s0 += e.x;
+        s1 += e.y;
+      }
+#pragma unroll
+    for (int d = 16; d < 64; d <<= 1) {
+      s0 += __shfl_xor(s0, d, 64);
+      s1 += __shfl_xor(s1, d, 64);
     }
-  sh[sl][cx][0] = s0; sh[sl][cx][1] = s1;
+    if ((threadIdx.x & 63) < 16) { sh[sidx][threadIdx.x >> 6][cx][0] = s0; sh[sidx][threadIdx.x >> 6][cx][1] = s1; }
+  }
   __syncthreads();
   if (sl != 0 || c >= a.C) return;
-  for (int k = 1; k < RED_SLICES; ++k) { s0 += sh[k][cx][0]; s1 += sh[k][cx][1]; }
-  const long long o = ((long long)((a.seg_first + sidx) * a.L + l) * a.C + c) * 2;
-  a.sums[o] = s0;
-  a.sums[o + 1] = s1;
-  if (a.fold_grads) {       // one segment: what bn_param_grad_kernel would do next, without the launch
-    a.dbeta[(long long)l * a.pstride + c] = 0.f + s0;
-    a.dgamma[(long long)l * a.pstride + c] = 0.f + s1;
+  float db = 0.f, dg = 0.f;
+  for (int sidx = 0; sidx < a.nseg; ++sidx) {
+    float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+    for (int k = 0; k < SL / 4; ++k) { s0 += sh[sidx][k][cx][0]; s1 += sh[sidx][k][cx][1]; }
+    const long long o = ((long long)((a.seg_first + sidx) * a.L + l) * a.C + c) * 2;
+    a.sums[o] = s0;
+    a.sums[o + 1] = s1;
+    db += s0;
+    dg += s1;
+  }
+  if (a.param_grads) {
+    a.dbeta[(long long)l * a.pstride + c] = db;
+    a.dgamma[(long long)l * a.pstride + c] = dg;
   }
 }
+// Rows a block of the first stage sums: 256, or 64 where those leave the chip short of blocks.  One 32x32 pair of 1000 images, both
+// stages, 256 rows against 64: 16000 rows of 512 channels 28 us and 15, 64000 of 256 20 and 21.  By the sizing batch, never a call's.
+int bn_red_rows(long long rows, int L) { return rows / 256 + L < 192 ? 64 : 256; }
 template <typename T>
 void launch_bn_bwd_reduce(const NormArgs& a, const int* tpre, const int* tmodel, int ub_tiles, float* partial, hipStream_t st) {
   if (a.nseg == 0 || ub_tiles == 0) return;
-  if (!tpre) return launch_fail("BatchNorm backward: no tile prefix array");
+  if (!tpre || a.red_rows < 1 || a.nseg > 2) return launch_fail("BatchNorm backward: no tile prefix array, no tile height, or more than two segments");
   const int cg = a.C / Vec16<T>::N;
   if (cg < 1 || cg > 256) return launch_fail("BatchNorm backward: one thread per 16 bytes of a row needs at most 256 of them");
   const size_t lds = (size_t)2 * (256 / cg) * a.C * sizeof(float);
   hipLaunchKernelGGL((bn_bwd_reduce_kernel<T>), dim3(ub_tiles, a.nseg), dim3(256), lds, st, a, tpre, tmodel, ub_tiles, partial);
-  const long long tot = (long long)a.nseg * a.L * ((a.C + 15) / 16);
-  hipLaunchKernelGGL(bn_bwd_reduce_final_kernel, dim3((unsigned)tot), dim3(256), 0, st, a, tpre, ub_tiles, partial);
+  const long long tot = (long long)a.L * ((a.C + 15) / 16);
+  if (ub_tiles > 64LL * a.L) hipLaunchKernelGGL(bn_bwd_reduce_final_kernel<64>, dim3((unsigned)tot), dim3(1024), 0, st, a, tpre, ub_tiles, partial);
+  else hipLaunchKernelGGL(bn_bwd_reduce_final_kernel<16>, dim3((unsigned)tot), dim3(256), 0, st, a, tpre, ub_tiles, partial);
 }
 template void launch_bn_bwd_reduce<float>(const NormArgs&, const int*, const int*, int, float*, hipStream_t);
 template void launch_bn_bwd_reduce<bf16_t>(const NormArgs&, const int*, const int*, int, float*, hipStream_t);
-
-// dgamma, dbeta: the segments' sums added in order.
-__global__ void bn_param_grad_kernel(NormArgs a) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= a.L * a.C) return;
-  const int l = idx / a.C, c = idx - l * a.C;
-  if (a.offs[l + 1] == a.offs[l]) return;
-  float db = 0.f, dg = 0.f;
-  for (int s = 0; s < a.nseg; ++s) {
-    const long long o = ((long long)((a.seg_first + s) * a.L + l) * a.C + c) * 2;
-    db += a.sums[o];
-    dg += a.sums[o + 1];
-  }
-  a.dbeta[(long long)l * a.pstride + c] = db;
-  a.dgamma[(long long)l * a.pstride + c] = dg;
-}
-void launch_bn_param_grad(const NormArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(bn_param_grad_kernel, dim3((a.L * a.C + 255) / 256), dim3(256), 0, st, a);
-}
 
 // dx = gamma * rstd * (g - sum_g / S - xhat * sum_gx / S).  Same block shape as the forward pass.
 template <typename T, bool PRE>
@@ -644,19 +673,20 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(NormArgs a) {
   const int total = a.rps * cg;
   int cur = -1;
   float rs[EPV], ga[EPV], mu[EPV], be[EPV], s1[EPV], s2[EPV];
-  for (int t = threadIdx.x; t < total; t += 256) {
+  for (int t = blockIdx.z * 256 + threadIdx.x; t < total; t += 256 * gridDim.z) {
     const int r = t / cg, g = t - r * cg;
     if (g != cur) {
       cur = g;
+      float ss[2 * EPV];
+      load_params(a.rstd + so + g * EPV, rs);
+      load_params(a.gamma + (long long)l * a.pstride + g * EPV, ga);
+      load_params(a.mean + so + g * EPV, mu);
+      load_params(a.beta + (long long)l * a.pstride + g * EPV, be);
+      load_params(a.sums + (so + g * EPV) * 2, ss);
 #pragma unroll
       for (int k = 0; k < EPV; ++k) {
-        const int c = g * EPV + k;
-        rs[k] = a.rstd[so + c];
-        ga[k] = a.gamma[(long long)l * a.pstride + c];
-        mu[k] = a.mean[so + c];
-        be[k] = a.beta[(long long)l * a.pstride + c];
-        s1[k] = a.sums[(so + c) * 2] * invS;
-        s2[k] = a.sums[(so + c) * 2 + 1] * invS;
+        s1[k] = ss[2 * k] * invS;
+        s2[k] = ss[2 * k + 1] * invS;
       }
     }
     float v[EPV], d[EPV];
@@ -679,7 +709,7 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(NormArgs a) {
 }
 template <typename T> void launch_bn_bwd_apply(const NormArgs& a, hipStream_t st) {
   if (a.n == 0 || a.nseg == 0) return;
-  const dim3 grid((unsigned)a.n, (unsigned)a.nseg);
+  const dim3 grid((unsigned)a.n, (unsigned)a.nseg, apply_split(a, Vec16<T>::N));
   if (a.pre_act) hipLaunchKernelGGL((bn_bwd_apply_kernel<T, true>), grid, dim3(256), 0, st, a);
   else hipLaunchKernelGGL((bn_bwd_apply_kernel<T, false>), grid, dim3(256), 0, st, a);
 }

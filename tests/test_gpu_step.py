@@ -398,3 +398,38 @@ def test_config0_five_steps_fp32():
         p.step(lab, w.noise(), w.images(lab))
         p.compare("config0 step %d" % s)
     p.close()
+
+
+@pytest.mark.parametrize("n", [5, 60, 300])
+def test_generator_batch_statistics_of_one_pair(n):
+    """BatchNorm statistics merged from few, from hundreds and from thousands of sub-tiles of one model (16, 64 and 128 slices), the
+    linear layer's column runs among them, against 64-bit sums over the whole batch.  Bound: the layers' own rounding (fp32 products of
+    110 and 512 terms, relative 2^-24 times the root of their number) and that of the running update, an order of magnitude apart."""
+    torch = U.torch_mod()
+    spec = synth.SPECS["mnist"]
+    g = binding.Gan(binding.make_config(spec, 1, 10, n, binding.FP32), torch.cuda.current_stream().cuda_stream)
+    rng = np.random.default_rng(n)
+    p = synth.init_params(spec, 0, rng).astype(np.float32)
+    g.set_params(0, 0, p)
+    zeros = np.zeros(g.bn_count(0), np.float32)
+    g.set_bn_running(0, 0, zeros, zeros)
+    lab = rng.integers(0, 10, n).astype(np.int32)
+    z = rng.normal(size=(n, 100)).astype(np.float32)
+    x = np.tanh(rng.normal(size=(n, 1, 28, 28))).astype(np.float32)
+    dl, dz, dx = U.dev(lab), U.dev(z), U.dev(x)
+    g.train_step(dl.data_ptr(), dz.data_ptr(), dx.data_ptr(), n)
+    mean, var = g.get_bn_running(0, 0)
+    g.close()
+    t = torch.from_numpy(p.astype(np.float64))
+    zin = torch.cat([torch.from_numpy(z).double(), torch.nn.functional.one_hot(torch.from_numpy(lab).long(), 10).double()], 1)
+    fc, rest = t[:128 * 49 * 110].view(128 * 49, 110), t[128 * 49 * 110:]
+    pre = [(zin @ fc.T).view(n, 128, 7, 7)]
+    act = torch.relu(torch.nn.functional.batch_norm(pre[0], None, None, rest[:128], rest[128:256], True, 0.0, 1e-5))
+    pre.append(torch.nn.functional.conv_transpose2d(act, rest[256:256 + 128 * 64 * 16].view(128, 64, 4, 4), None, 2, 1))
+    o = 0
+    for q in pre:
+        C, N = q.shape[1], q.numel() // q.shape[1]
+        m, v = q.mean((0, 2, 3)).numpy(), q.var((0, 2, 3), unbiased=False).numpy()
+        assert np.max(np.abs(mean[o:o + C] / 0.1 - m) / np.sqrt(v)) <= 1e-5
+        assert np.max(np.abs(var[o:o + C] / (0.1 * v * N / (N - 1)) - 1)) <= 1e-5
+        o += C
