@@ -34,11 +34,12 @@ namespace gan {
 
 
 // Block tile BM x BN computed by WM x WN waves, each (TM*32) x (TN*32); forward kernel: KB bytes of K per LDS row,
-// NST buffers.
-template <int BM_, int BN_, int WM_, int WN_, int KB_ = 128, int NST_ = 2>
+// NST buffers.  KS (forward kernel): groups of WM x WN waves that share the tile's reduction, chunk c going to group c % KS; each has a
+// ring of buffers of its own, and their sums are added at the end.
+template <int BM_, int BN_, int WM_, int WN_, int KB_ = 128, int NST_ = 2, int KS_ = 1>
 struct Tile {
-  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, KB = KB_, NST = NST_;
-  static constexpr int NT = 64 * WM_ * WN_;
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, KB = KB_, NST = NST_, KS = KS_;
+  static constexpr int NT = 64 * WM_ * WN_;          // threads of a group
   static constexpr int TM = BM_ / (32 * WM_), TN = BN_ / (32 * WN_);
   static constexpr int CPR = KB_ / 16;               // 16-byte chunks per LDS row
   static constexpr int RPP = NT / CPR;               // tile rows filled per loader pass
@@ -56,6 +57,9 @@ template <> struct FwdTiles<bf16_t> {
                                                  // short, and what a block waits for before it can multiply weighs more
   typedef Tile<64, 64, 2, 2, 128, 2> Tiny;       // 256 threads, wave tile 32 x 32, 32 KiB of LDS: workloads so small that
                                                  // the larger tiles would leave most of the chip without a block
+  typedef Tile<64, 64, 2, 2, 128, 2, 2> Pair;    // Tiny with two groups of waves on its reduction: 512 threads, 64 KiB
+  typedef Tile<32, 64, 1, 2, 128, 3, 4> Deep;    // 32 x 64 with four groups: 512 threads, 144 KiB, six or more chunks on their way.  Both
+                                                 // for launches that a CU gets a block or two of, whose time is that of one block: see TILES
   // Chunk sizes, in TFLOP/s, 128-byte x 2 against 64-byte x 3: 64x64 down 64 -> 128 channels at side 7, one model of 64 samples, 76
   // against 63, 64 -> 64 at side 8, 100 models, 453 against 359; 128x128 down 64 -> 128 at side 7, ten models, 541 against 495.
   // 256x64: up 128 -> 64 at side 16 480 against 582 with 64-byte x 2, up 64 -> 64 at side 8 401 against 438, but down 64 -> 64 at
@@ -69,23 +73,33 @@ template <> struct FwdTiles<float> {
   typedef Tile<256, 64, 4, 1, 128, 2> Narrow;    // 256 threads, wave tile 64 x 64, 80 KiB
   typedef Narrow NarrowShort;
   typedef Tile<64, 64, 2, 2, 128, 2> Tiny;       // 256 threads, wave tile 32 x 32, 32 KiB
+  typedef Tile<64, 64, 2, 2, 128, 2, 2> Pair;
+  typedef Tile<32, 64, 1, 2, 128, 3, 4> Deep;
 };
 
 // What a tile is to the chooser: its shape, the row blocks with statistics of their own, the blocks of it that a CU holds, and
 // the rate a full chip of them reaches against the fastest one of the storage type (0: the storage type has no such tile).  The bf16
 // 256x64 line describes Narrow, which MODE_DOWN runs; MODE_UP and MODE_DENSE run NarrowShort (four blocks per CU, 582 TFLOP/s instead of
 // 480) and are judged by the same line, so the estimate is too high for them.
-struct TileInfo { ConvTile id; const char* name; int rows, cols, split, per_cu; double rate; };
-template <typename TL> constexpr TileInfo info(ConvTile id, const char* name, int per_cu, double rate) {
-  return {id, name, TL::BM, TL::BN, TL::WM, per_cu, rate};
+// Deep and Pair take launches of at most `most` tiles.  There a launch takes as long as one block, which waits for each chunk, splits it
+// (fp32) and multiplies it in turn; more waves on the same tile overlap these.  In us, Tiny / Pair / Deep by the number of 64x64 tiles, fp32:
+// down 64 -> 128 channels, side 7: 104 tiles 30.2 / 25.2 / 17.0, 200 31.3 / 26.4 / 31.5, 400 44.1 / 40.4 / 59.5, 800 72.6 / 73.7 / 102;
+// up 256 -> 128, side 4: 104 28.3 / 24.1 / 15.7, 408 41.1 / 38.6 / 56.7, 808 70.0 / 72.0 / 98; bf16: down 128 -> 256, side 4: 104 13.3 /
+// 11.6 / 9.6, 208 13.8 / 12.2 / 16.8, 408 17.6 / 17.3 / 31.7; up 128 -> 64, side 7: 104 6.5 / 6.6 / 6.3, 400 8.1 / 9.0 / 18.3.
+// (Their rates are such that the time of a lone block compares with a lone Tiny's.)
+struct TileInfo { ConvTile id; const char* name; int rows, cols, split, per_cu; double rate; int most; };
+template <typename TL> constexpr TileInfo info(ConvTile id, const char* name, int per_cu, double rate, int most = 1 << 30) {
+  return {id, name, TL::BM, TL::BN, TL::WM, per_cu, rate, most};
 }
-static const TileInfo TILES[2][5] = {
+static const TileInfo TILES[2][7] = {
     {info<FwdTiles<bf16_t>::Big>(TILE_BIG, "256x256", 1, 1.0), info<FwdTiles<bf16_t>::Mid>(TILE_MID, "256x128", 2, 0.88),
      info<FwdTiles<bf16_t>::Small>(TILE_SMALL, "128x128", 2, 0.77), info<FwdTiles<bf16_t>::Narrow>(TILE_NARROW, "256x64", 2, 0.70),
-     info<FwdTiles<bf16_t>::Tiny>(TILE_TINY, "64x64", 5, 0.52)},
-    {{TILE_BIG, "", 0, 0, 0, 0, 0}, {TILE_MID, "", 0, 0, 0, 0, 0},
+     info<FwdTiles<bf16_t>::Tiny>(TILE_TINY, "64x64", 5, 0.52),
+     info<FwdTiles<bf16_t>::Pair>(TILE_PAIR, "64x64 pair", 2, 0.585, 256), info<FwdTiles<bf16_t>::Deep>(TILE_DEEP, "32x64 deep", 1, 0.36, 256)},
+    {{TILE_BIG, "", 0, 0, 0, 0, 0, 0}, {TILE_MID, "", 0, 0, 0, 0, 0, 0},
      info<FwdTiles<float>::Small>(TILE_SMALL, "128x128", 2, 1.0), info<FwdTiles<float>::Narrow>(TILE_NARROW, "256x64", 2, 0.95),
-     info<FwdTiles<float>::Tiny>(TILE_TINY, "64x64", 5, 0.64)},
+     info<FwdTiles<float>::Tiny>(TILE_TINY, "64x64", 5, 0.64),
+     info<FwdTiles<float>::Pair>(TILE_PAIR, "64x64 pair", 2, 0.76, 512), info<FwdTiles<float>::Deep>(TILE_DEEP, "32x64 deep", 1, 0.58, 256)},
 };
 static const TileInfo& tile_info(int esize, ConvTile t) { return TILES[esize == 4][t]; }
 int conv_tile_rows(int esize, ConvTile t) { return tile_info(esize, t).rows; }
@@ -103,6 +117,7 @@ ConvTile conv_choose_tile(int esize, int n_out, double rows_per_model, int n_mod
     if (t.rate == 0) continue;
     if (t.cols > 64 && n_out % t.cols != 0) continue;      // half-filled tiles
     const double tiles = ceil(rows_per_model / t.rows) * n_models * groups * ((n_out + t.cols - 1) / t.cols);
+    if (tiles > t.most) continue;
     const double per_round = 256.0 * t.per_cu, full = floor(tiles / per_round), rest = tiles - full * per_round;
     double blocks = full * t.per_cu;                       // blocks one CU works through
     if (rest > 0) blocks += std::min((double)t.per_cu, ceil(rest / 256.0) + (full > 0 ? 0.5 : 0.0));
@@ -350,21 +365,23 @@ static int log2_or_neg(int v) {
 // two accumulators; without the bound bf16 takes 171, half of them accumulation registers, and with it 107, four waves).
 template <typename T, typename TL> constexpr int waves_per_simd() { return TL::TM * TL::TN == 4 ? 2 : 1; }
 template <typename T, int MODE, int EPI, typename TL>
-__global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void conv_gemm_kernel(ConvArgs p) {
+__global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void conv_gemm_kernel(ConvArgs p) {
   constexpr int BM = TL::BM, BN = TL::BN, TM = TL::TM, TN = TL::TN, PA = TL::PA, PB = TL::PB, RPP = TL::RPP;
-  constexpr int KB = TL::KB, NST = TL::NST;
-  constexpr int SMEM_RING = NST * (BM + BN) * KB;
+  constexpr int KB = TL::KB, NST = TL::NST, KS = TL::KS;
+  constexpr int RING = NST * (BM + BN) * KB;                                   // of one group
+  constexpr int SMEM_RING = KS * RING;
   constexpr int ROWTAB = EPI == EPI_LABEL_LRELU ? BM * 12 : BM * 8;            // see the epilogue
   constexpr int SMEM_EPI = ROWTAB + (TL::NT / 64) * 32 * (TN * 32 * 4 + 16);
   constexpr int SMEM = SMEM_RING > SMEM_EPI ? SMEM_RING : SMEM_EPI;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
-  unsigned char* const As = smem;                      // buffer s at As + s * BM * KB
-  unsigned char* const Bs = smem + NST * BM * KB;      // buffer s at Bs + s * BN * KB
+  const int kgrp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / TL::NT);      // this wave's share of the reduction
+  unsigned char* const As = smem + kgrp * RING;        // buffer s at As + s * BM * KB
+  unsigned char* const Bs = As + NST * BM * KB;        // buffer s at Bs + s * BN * KB
   constexpr int BK = KB / (int)sizeof(T);              // elements of K per chunk
   constexpr int LINES = 128 / KB;                      // chunks per 128-byte line
   constexpr int EPV = 16 / (int)sizeof(T);
   constexpr int LPT = PA + PB;                         // loads per thread per chunk
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = KS == 1 ? (int)threadIdx.x : (int)threadIdx.x - kgrp * TL::NT, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / TL::WN, wn = wave % TL::WN;
 
   // ---- which tile: consecutive virtual ids stay on one XCD (block ids are dealt round-robin to the 8 XCDs).
@@ -491,7 +508,7 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void conv_gemm_k
     bcol[i] = col < N ? (unsigned)((col * C + chunk * EPV) * SZ) : NO_ROW;
   }
 
-  const unsigned lds0 = (unsigned)(uintptr_t)smem;     // LDS byte address of the buffers
+  const unsigned lds0 = (unsigned)(uintptr_t)As;       // LDS byte address of the buffers
   // The next K-chunk to load: which tap it gathers and the wave-uniform byte offsets it adds to the rows' and columns'.
   // K order, fastest first: the chunks of one 128-byte line; the taps whose gathers land on the same input pixels
   // shifted by one (down: the 4 taps of a (ky%2, kx%2) class, up: the phase's 4 taps), which find their rows in
@@ -533,7 +550,7 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void conv_gemm_k
     }
     k_set();
   };
-  auto load_chunk = [&](int stage) {                   // the next chunk, into a buffer
+  auto load_chunk = [&](int stage) {                   // this group's next chunk, into a buffer
     const unsigned a_dst = lds0 + (stage * BM + wave * (1024 / KB)) * KB;        // + pass * RPP rows
     const unsigned b_dst = lds0 + (NST * BM + stage * BN + wave * (1024 / KB)) * KB;
 #pragma unroll
@@ -541,7 +558,8 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void conv_gemm_k
       load16_to_lds(a_rsrc, apix[i] | (unsigned)__builtin_amdgcn_sbfe(outside[i], k_tap, 1), k_aoff, a_dst + i * RPP * KB);
 #pragma unroll
     for (int i = 0; i < PB; ++i) load16_to_lds(w_rsrc, bcol[i], k_woff, b_dst + i * RPP * KB);
-    k_advance();
+#pragma unroll
+    for (int i = 0; i < KS; ++i) k_advance();
   };
   floatx16 acc[TM][TN];
 
@@ -555,18 +573,22 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void conv_gemm_k
     k_set();
     clear_acc(acc);
     if constexpr (split.value) clear_acc(low);
+    for (int i = 0; i < kgrp; ++i) k_advance();
     int st_load = 0, st = 0;                           // buffers of the next chunk to load and of the current one
-    for (int c = 0; c < NST - 1 && c < nk; ++c) load_chunk(st_load++);
-    wait_vm<0>();
+    const int mine = (nk - kgrp + KS - 1) / KS, steps = (nk + KS - 1) / KS;      // this group's chunks; the barriers are everyone's
+    for (int c = 0; c < NST - 1 && c < mine; ++c) load_chunk(st_load++);
+    if (KS > 1 && mine >= NST - 1) wait_vm<(NST - 2) * LPT>(); else wait_vm<0>();
     __syncthreads();
-    for (int kc = 0; kc < nk; ++kc) {
-      const bool more = kc + NST - 1 < nk;
+    for (int kc = 0; kc < steps; ++kc) {
+      const bool more = kc + NST - 1 < mine;
       if (more) {
         load_chunk(st_load);
         st_load = st_load == NST - 1 ? 0 : st_load + 1;
       }
-      if constexpr (split.value) tile_mma_split<TM, TN, KB>(acc, low, As + st * BM * KB, Bs + st * BN * KB, wm, wn, lane);
-      else tile_mma_fwd<T, TM, TN, KB>(acc, As + st * BM * KB, Bs + st * BN * KB, wm, wn, lane);
+      if (KS == 1 || kc < mine) {
+        if constexpr (split.value) tile_mma_split<TM, TN, KB>(acc, low, As + st * BM * KB, Bs + st * BN * KB, wm, wn, lane);
+        else tile_mma_fwd<T, TM, TN, KB>(acc, As + st * BM * KB, Bs + st * BN * KB, wm, wn, lane);
+      }
       st = st == NST - 1 ? 0 : st + 1;
       if (more) wait_vm<(NST - 2) * LPT>(); else wait_vm<0>();     // chunk kc + 1 has landed; those behind it may stay in flight
       __syncthreads();
@@ -575,11 +597,43 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void conv_gemm_k
   if constexpr (SZ == 4) {
     k_loop(std::true_type{});
     add_acc(acc, low);
-    if (block_any<TL::NT / 64>(not_finite(acc), smem, wave)) k_loop(std::false_type{});
+    if (block_any<TL::NT / 64 * KS>(not_finite(acc), smem, kgrp * (TL::NT / 64) + wave)) k_loop(std::false_type{});
   } else {
     k_loop(std::false_type{});
   }
 
+  if constexpr (KS > 1) {
+    // the groups' sums, added in order by the first group, which also does the epilogue (the buffers are free now)
+    constexpr int PER = TM * TN * 16 * 4;                // bytes per thread
+    static_assert((KS - 1) * TL::NT * PER <= SMEM, "the sums fit into the buffers");
+    float4* const sums = reinterpret_cast<float4*>(smem);
+    if (kgrp > 0) {
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            sums[((kgrp - 1) * (PER / 16) + (tm * TN + tn) * 4 + e) * TL::NT + tid] =
+                make_float4(acc[tm][tn][4 * e], acc[tm][tn][4 * e + 1], acc[tm][tn][4 * e + 2], acc[tm][tn][4 * e + 3]);
+    }
+    __syncthreads();
+    if (kgrp == 0) {
+#pragma unroll
+      for (int g = 1; g < KS; ++g)
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+          for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float4 t = sums[((g - 1) * (PER / 16) + (tm * TN + tn) * 4 + e) * TL::NT + tid];
+              acc[tm][tn][4 * e] += t.x; acc[tm][tn][4 * e + 1] += t.y; acc[tm][tn][4 * e + 2] += t.z; acc[tm][tn][4 * e + 3] += t.w;
+            }
+    }
+    __syncthreads();
+    if (kgrp > 0) return;                              // (no barrier below waits for the waves that have ended)
+  }
   // ---- epilogue: output row index of every tile row, through LDS (the buffers are free now)
   long long* orow = reinterpret_cast<long long*>(smem);
   int* lrow = reinterpret_cast<int*>(smem + BM * 8);                    // EPI_LABEL_LRELU: the row of label_rows it gets
@@ -760,7 +814,7 @@ static void launch_one(ConvArgs a, hipStream_t st) {
   const long long blocks = ((long long)a.ub_tiles * NT * a.nseg * (MODE == MODE_UP ? 4 : 1) + 7) / 8 * 8;
   if (blocks == 0 || a.nseg == 0) return;
   dim3 grid((unsigned)blocks, 1, 1);
-  hipLaunchKernelGGL((conv_gemm_kernel<T, MODE, EPI, TL>), grid, dim3(TL::NT), 0, st, a);
+  hipLaunchKernelGGL((conv_gemm_kernel<T, MODE, EPI, TL>), grid, dim3(TL::NT * TL::KS), 0, st, a);
 }
 
 template <typename T, int MODE, int EPI>
@@ -774,6 +828,8 @@ static void launch_wide(const ConvArgs& a, hipStream_t st) {
   if (a.tile == TILE_NARROW)
     return launch_one<T, MODE, EPI, std::conditional_t<MODE != MODE_DOWN, typename Tiles::NarrowShort, typename Tiles::Narrow>>(a, st);
   if (a.tile == TILE_TINY) return launch_one<T, MODE, EPI, typename Tiles::Tiny>(a, st);
+  if (a.tile == TILE_PAIR) return launch_one<T, MODE, EPI, typename Tiles::Pair>(a, st);
+  if (a.tile == TILE_DEEP) return launch_one<T, MODE, EPI, typename Tiles::Deep>(a, st);
   launch_fail("GEMM: a tile that this storage type does not have");
 }
 
@@ -808,7 +864,7 @@ void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
 const char* conv_variant_name(int mode, int epi, const ConvArgs& a) {
   static const char* modes[3] = {"down", "up", "dense"};
   static const char* epis[6] = {"", "+actbwd", "+lrelu", "+label+lrelu", "+dropbwd", "+bn"};
-  static char names[3][6][5][48];
+  static char names[3][6][7][48];
   char* n = names[mode][epi][a.tile];
   if (!n[0]) snprintf(n, 48, "gemm_%s%s<%s>", modes[mode], epis[epi], TILES[0][a.tile].name);
   return n;

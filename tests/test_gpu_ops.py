@@ -274,3 +274,21 @@ def _same_classes(got, ref):
     assert np.all(np.abs(got[huge] / ref[huge] - 1) <= 2e-5)             # one product dwarfs the others there
     rest = np.isfinite(ref) & ~huge
     assert np.max(np.abs(got[rest] - ref[rest])) <= 2e-5 * np.max(np.abs(ref[rest]))
+
+
+@pytest.mark.parametrize("cb,cs,hs,n", [(64, 128, 4, 40), (64, 256, 4, 200)])
+def test_fp32_values_without_a_bf16_split_in_shared_reductions(ctxs, cb, cs, hs, n):
+    """As above, on the tiles whose reduction several groups of waves share (the automatic choice at these sizes: 40 and 200 tiles)."""
+    torch = U.torch_mod()
+    g = ctxs[binding.FP32]
+    g.op_tile_rows(0)
+    rng = np.random.default_rng(13)
+    big = rng.normal(0, 1, (n, 2 * hs, 2 * hs, cb)).astype(np.float32)
+    big[3, 2, 5, 7], big[20, 0, 0, 1], big[31, 7, 7, 63], big[33, 4, 4, 0] = np.inf, -np.inf, np.nan, 3.4e38
+    W = rng.normal(0, 0.05, (cs, cb, 4, 4)).astype(np.float32)
+    with np.errstate(all="ignore"):
+        ref = O.conv2d(big.transpose(0, 3, 1, 2), W, None).transpose(0, 2, 3, 1)
+    out = torch.zeros((n, hs, hs, cs), device="cuda")
+    offs, d_big, d_w = U.dev(np.array([0, n], np.int32)), U.dev(big), U.dev(np.ascontiguousarray(W.transpose(2, 3, 0, 1)).reshape(16, cs, cb))
+    g.op_conv_down(d_big.data_ptr(), d_w.data_ptr(), out.data_ptr(), offs.data_ptr(), 1, n, cb, cs, hs)
+    _same_classes(out.cpu().numpy(), ref)
