@@ -177,6 +177,7 @@ int geom_id(gan_ctx* c, int rps, int tile_rows) {
   return c->geoms.n++;
 }
 const int* tmodel_of(gan_ctx* c, int rps, int tile_rows) {
+  if (c->L == 1) return nullptr;
   for (int i = 0; i < c->geoms.n; ++i)
     if (c->geoms.rps[i] == rps && c->geoms.tile_rows[i] == tile_rows) return c->rb.tmodel + (long long)i * c->rb.tmodel_stride;
   return nullptr;
@@ -798,12 +799,14 @@ void d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_running) 
   launch_head_fwd<T>(h, c->st);
 }
 
-// mode 0: discriminator cost on (real, fake); mode 1: generator cost on the fake segment
+// mode 0: discriminator cost on (real, fake); mode 1: generator cost on the fake segment.  Also advances the player's step counts.
 void loss_call(gan_ctx* c, int n, int mode) {
   HeadArgs h;
   memset(&h, 0, sizeof(h));
   h.logits = c->logits; h.dlogits = c->dlogits; h.loss = mode == 0 ? c->loss_d : c->loss_g;
   h.offs = c->rb.offs; h.L = c->L; h.seg_first = mode == 0 ? 0 : 1; h.nseg = mode == 0 ? 2 : 1; h.seg_samples = n; h.n = n;
+  const Net& net = mode == 0 ? c->D : c->G;
+  h.adam_t = net.t; h.adam_bc = net.bc; h.beta1 = c->cfg.beta1; h.beta2 = c->cfg.beta2;
   h.mode = mode; h.scale = mode == 0 ? c->cfg.d_loss_scale : c->cfg.g_loss_scale;
   launch_loss(h, c->st);
 }
@@ -1160,7 +1163,6 @@ void adam_rest_call(gan_ctx* c, Net& net, bool isG, const AdamArgs& a) {
 template <typename T>
 void adam_call(gan_ctx* c, Net& net, bool isG) {
   const AdamArgs a = adam_args<T>(c, net, isG);
-  launch_adam_prepare(a, c->st);
   adam_region_call<T>(c, a, -1, c->st);
   adam_rest_call<T>(c, net, isG, a);
 }
@@ -1170,8 +1172,7 @@ void route_and_stage(gan_ctx* c, const int32_t* label_ids, const float* noise, c
   launch_route(label_ids, n, c->L, c->cfg.n_labels, c->geoms, c->rb, c->st);
   {
     Scope s(c, "stage", 0, (double)n * c->cfg.z_dim * (4.0 + sizeof(T)));
-    launch_stage<T>(label_ids, noise, nullptr, n, c->L, c->cfg.z_dim, c->cfg.cond_g, c->G.Kp, c->cfg.img_c, c->cfg.img_hw, c->rb,
-                    (T*)c->zin, (T*)c->xd, c->st);
+    launch_stage<T>(label_ids, noise, n, c->L, c->cfg.z_dim, c->cfg.cond_g, c->G.Kp, c->geoms, c->rb, (T*)c->zin, c->st);
   }
   if (real) im2col_call<T>(c, c->D.conv[0], nullptr, real, c->colD, c->KcD, c->nslot, 0, n);   // the real half of D's input
 }
@@ -1205,7 +1206,6 @@ void train_step(gan_ctx* c, const int32_t* label_ids, const float* noise, const 
   c->order_next = 0;
   {
     const AdamArgs aD = adam_args<T>(c, c->D, false);
-    launch_adam_prepare(aD, c->st);
     d_backward<T>(c, n, 0, 2, true, false, &aD);   // weight gradients and the convolutions' updates beside the chain
     adam_rest_call<T>(c, c->D, false, aD);
     order_after(c, c->st, side_stream(c));
@@ -1215,7 +1215,6 @@ void train_step(gan_ctx* c, const int32_t* label_ids, const float* noise, const 
   d_backward<T>(c, n, 1, 1, false, true);          // only data gradients: theta_D is not G's to move
   {
     const AdamArgs aG = adam_args<T>(c, c->G, true);
-    launch_adam_prepare(aG, c->st);
     g_backward<T>(c, n, &aG);
     adam_rest_call<T>(c, c->G, true, aG);
     order_after(c, c->st, side_stream(c));
@@ -1312,7 +1311,7 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
   // gan_generate / gan_sample, so that generating between a step and its queries changes nothing they return
   RouteBuffers& rb = c->rb;
   for (RouteBuffers* r : {&c->rb, &c->rb_gen}) {
-    ok = ok && dev_alloc(c, (void**)&r->cnt, (size_t)ROUTE_CHUNKS * L * 4) && dev_alloc(c, (void**)&r->counts, (size_t)L * 4) &&
+    ok = ok && dev_alloc(c, (void**)&r->cnt, (size_t)ROUTE_WAVES * L * 4) && dev_alloc(c, (void**)&r->counts, (size_t)L * 4) &&
          dev_alloc(c, (void**)&r->offs, (size_t)(L + 1) * 4) && dev_alloc(c, (void**)&r->perm, (size_t)NB * 4) &&
          dev_alloc(c, (void**)&r->sample_model, (size_t)NB * 4) && dev_alloc(c, (void**)&r->sample_slot, (size_t)NB * 4) &&
          dev_alloc(c, (void**)&r->tpre, (size_t)MAX_GEOMS * (L + 1) * 4) && dev_alloc(c, (void**)&r->order, (size_t)L * 4);
@@ -1639,11 +1638,16 @@ gan_status gan_sample(gan_ctx* c, const double* prior, const float* u, const flo
   std::vector<double> cdf((size_t)K);
   double cum = 0.0;
   for (int k = 0; k < K; ++k) { cum += prior[k] / total; cdf[(size_t)k] = cum; }
-  if (!c->cdf && !dev_alloc(c, (void**)&c->cdf, (size_t)K * sizeof(double))) return fail(c, GAN_E_OOM, "cumulative prior");
-  if (hipStreamSynchronize(c->st) != hipSuccess ||      // an earlier call may still read the buffer
-      hipMemcpy(c->cdf, cdf.data(), (size_t)K * sizeof(double), hipMemcpyHostToDevice) != hipSuccess)
-    return fail(c, GAN_E_HIP, "copy of the cumulative prior failed");
-  launch_draw_labels(u, c->cdf, K, last, n, out_labels, c->st);
+  DrawTable table = {};
+  if (K <= DRAW_ARGS) {
+    std::copy(cdf.begin(), cdf.end(), table.cdf);
+  } else {
+    if (!c->cdf && !dev_alloc(c, (void**)&c->cdf, (size_t)K * sizeof(double))) return fail(c, GAN_E_OOM, "cumulative prior");
+    if (hipStreamSynchronize(c->st) != hipSuccess ||      // an earlier call may still read the buffer
+        hipMemcpy(c->cdf, cdf.data(), (size_t)K * sizeof(double), hipMemcpyHostToDevice) != hipSuccess)
+      return fail(c, GAN_E_HIP, "copy of the cumulative prior failed");
+  }
+  launch_draw_labels(u, K <= DRAW_ARGS ? nullptr : c->cdf, table, K, last, n, out_labels, c->st);
   return gan_generate(c, out_labels, noise, n, out_images, use_running_stats);
 }
 

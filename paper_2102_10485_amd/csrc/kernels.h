@@ -6,7 +6,7 @@
 
 namespace gan {
 
-constexpr int ROUTE_CHUNKS = 256;   // sequential chunks of the flat batch, one thread each
+constexpr int ROUTE_WAVES = 16;     // runs of the flat batch, one wave each
 constexpr int MAX_GEOMS = 60;
 
 // One "geometry" = how rows of a layer split into tiles: rows per sample and rows per tile.
@@ -17,14 +17,14 @@ struct GeomTable {
 };
 
 struct RouteBuffers {
-  int* cnt;           // [ROUTE_CHUNKS][L] scratch
+  int* cnt;           // [ROUTE_WAVES][L] scratch
   int* counts;        // [L]
   int* offs;          // [L+1]
   int* perm;          // [n]
   int* sample_model;  // [n] model of the j-th routed sample
   int* sample_slot;   // [n] label-map slot of the j-th routed sample
   int* tpre;          // [MAX_GEOMS][L+1]
-  int* tmodel;        // [MAX_GEOMS][tmodel_stride]: model of every tile of every geometry (built with tpre)
+  int* tmodel;        // [MAX_GEOMS][tmodel_stride]: model of every tile of every geometry (built by the staging; one model: not at all)
   int tmodel_stride;
   int* flags;         // [0]: out-of-range label seen
   int* order;         // [L] models by decreasing sample count (ties by index), for kernels whose work per model
@@ -35,8 +35,8 @@ void launch_route(const int* label_ids, int n, int L, int n_labels, const GeomTa
                   hipStream_t st);
 
 template <typename T>
-void launch_stage(const int* label_ids, const float* noise, const float* real, int n, int L, int zdim, int cond_g, int kp,
-                  int img_c, int img_hw, const RouteBuffers& rb, T* zin, T* xd, hipStream_t st);
+void launch_stage(const int* label_ids, const float* noise, int n, int L, int zdim, int cond_g, int kp, const GeomTable& geoms,
+                  const RouteBuffers& rb, T* zin, hipStream_t st);     // and the model of every tile (rb.tmodel)
 
 // Batch statistics and the normalise+activate passes.  Groups = (segment, model); rows of group (s, l) are the
 // rps rows of each of samples s*seg_samples + offs[l] .. offs[l+1].
@@ -170,6 +170,9 @@ struct HeadArgs {
   const int* offs;
   const int* sample_model;
   int L, K, seg_first, nseg, seg_samples, n;
+  int* adam_t;              // loss: [L] step counts of the update that follows, advanced with the bias corrections adam_bc [L][2]
+  float* adam_bc;
+  float beta1, beta2;
   int mode;                 // loss: 0 = discriminator cost on (real, fake) ; 1 = generator cost on fake
   float scale;
   // head_bwd_w: rsplit > 1 shares every model's rows among rsplit blocks per K chunk; their partial sums go to
@@ -207,7 +210,6 @@ struct AdamArgs {
 // T: storage type of the shadows.  launch_adam does the whole update; the parts below do it piecewise (plan first).
 template <typename T> void launch_adam(AdamArgs a, hipStream_t st);
 bool adam_plan(AdamArgs& a);
-void launch_adam_prepare(const AdamArgs& a, hipStream_t st);
 void launch_adam_gaps(const AdamArgs& a, hipStream_t st);
 template <typename T> void launch_adam_region(AdamArgs a, int region, hipStream_t st);
 template <typename T> void launch_cast_shadow(const float* theta, T* shadow, long long total, hipStream_t st);
@@ -220,11 +222,11 @@ void launch_transpose_w(const S* src, T* dst, long long pstride, int L, int Cb, 
 void launch_sum_splits(const float* part, float* dW, long long dw_stride, long long size, int L, int nsplit, hipStream_t st);
 
 void launch_tile_prefix(const int* offs, int L, int rps, int tile_rows, int* tpre, hipStream_t st);
-// tmodel[t] = model of tile t for t < tpre[L] (cap entries available)
-void launch_tile_models(const int* tpre, int L, int* tmodel, int cap, hipStream_t st);
-
 // Class draws: labels[i] = first k with cdf[k] > (double)u[i]; if none (rounding), `last` .
-void launch_draw_labels(const float* u, const double* cdf, int n_labels, int last, int n, int* labels, hipStream_t st);
+// cdf: device memory, or NULL: in the table (at most DRAW_ARGS labels)
+constexpr int DRAW_ARGS = 256;
+struct DrawTable { double cdf[DRAW_ARGS]; };
+void launch_draw_labels(const float* u, const double* cdf_mem, const DrawTable& table, int n_labels, int last, int n, int* labels, hipStream_t st);
 
 // One-way analysis of variance of the per-image channel means by label; all arithmetic in double, fixed order.
 //   x[i][c]    = mean over the pixels of channel c of image i (images: NCHW fp32)

@@ -51,3 +51,30 @@ def test_more_models_than_the_count_table_has_room_for():
     assert ecnt[7] == 0 and ecnt.min() == 0
     assert np.array_equal(perm, eperm) and np.array_equal(offs, eoffs) and np.array_equal(cnt, ecnt)
     assert np.all(np.isfinite(jd)) and np.all(np.isfinite(jg)) and jd[7] == 0 and jg[7] == 0
+
+
+@pytest.mark.parametrize("L,n", [(1, 1), (3, 64), (64, 1025), (65, 8193), (2200, 5000)])
+def test_shares_of_the_waves_and_tables_beyond_lds(L, n):
+    """Sixteen waves share the batch 64 samples at a time, eight such groups in flight; labels outside the range are dropped wherever
+    they stand; 2200 models' tables are in global memory."""
+    rng = np.random.default_rng(L + n)
+    lab = rng.integers(0, L, n).astype(np.int32)
+    bad = rng.random(n) < 0.05
+    if n > 1:
+        bad[[0, n - 1]] = True
+        lab[bad] = rng.choice([-2, -1, L, 1 << 30], int(bad.sum()))
+    torch = U.torch_mod()
+    spec = dict(synth.SPECS["tiny0"])
+    g = binding.Gan(binding.make_config(spec, L, L, n, binding.BF16), torch.cuda.current_stream().cuda_stream)
+    z = torch.randn((n, spec["z_dim"]), device="cuda")
+    x = torch.randn((n, spec["img_c"], spec["img_hw"], spec["img_hw"]), device="cuda").tanh()
+    dl = torch.from_numpy(lab).cuda()
+    g.train_step(dl.data_ptr(), z.data_ptr(), x.data_ptr(), n)
+    keep = np.flatnonzero(~bad) if n > 1 else np.arange(n)
+    eperm, eoffs, ecnt = _expected(lab[keep], L)
+    _, _, cnt, st = g.get_losses(check=False)
+    perm, offs = g.get_routing(n)
+    g.close()
+    assert st == (binding.GAN_E_LABEL if n > 1 else binding.GAN_OK)
+    assert np.array_equal(offs, eoffs) and np.array_equal(cnt, ecnt)
+    assert np.array_equal(perm[:len(keep)], keep[eperm])
