@@ -66,7 +66,10 @@ struct Net {
   long long fc_bias = -1, P4 = 0;
   void *w4u = nullptr, *w4d = nullptr;
   float *theta = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
-  void *shadow_u = nullptr, *shadow_d = nullptr;   // storage-type copies: [tap][cb][cs] and [tap][cs][cb]
+  void *shadow_u = nullptr, *shadow_d = nullptr;   // bf16 storage: copies [tap][cb][cs] and [tap][cs][cb] (fp32: shadow_u is theta)
+  // fp32 storage: the weights of the convolutions on the GEMM engine (the k4 weights, where there are any) as three bf16 planes in both
+  // layouts, [model][plane][P or P4]
+  unsigned short *split_u = nullptr, *split_d = nullptr;
   float *run_mean = nullptr, *run_var = nullptr;
   int* t = nullptr;
   float* bc = nullptr;
@@ -427,18 +430,22 @@ bool alloc_net(gan_ctx* c, Net& n) {
   const size_t tot = (size_t)c->L * n.P;
   bool ok = dev_alloc(c, (void**)&n.theta, tot * 4) && dev_alloc(c, (void**)&n.m, tot * 4) &&
             dev_alloc(c, (void**)&n.v, tot * 4) && dev_alloc(c, (void**)&n.g, tot * 4) &&
-            dev_alloc(c, &n.shadow_d, tot * esize(c)) &&
             dev_alloc(c, (void**)&n.run_mean, (size_t)c->L * n.nbn * 4) &&
             dev_alloc(c, (void**)&n.run_var, (size_t)c->L * n.nbn * 4) &&
             dev_alloc(c, (void**)&n.t, (size_t)c->L * 4) && dev_alloc(c, (void**)&n.bc, (size_t)c->L * 8);
   if (!ok) return false;
-  if (c->bf16) { if (!dev_alloc(c, &n.shadow_u, tot * 2)) return false; }
-  else n.shadow_u = n.theta;
+  if (c->bf16) {
+    if (!dev_alloc(c, &n.shadow_u, tot * 2) || !dev_alloc(c, &n.shadow_d, tot * 2)) return false;
+    hipMemsetAsync(n.shadow_d, 0, tot * 2, c->st);
+  } else {
+    const size_t parts = (size_t)c->L * (n.P4 ? n.P4 : n.P) * 6;
+    if (!dev_alloc(c, (void**)&n.split_u, parts) || !dev_alloc(c, (void**)&n.split_d, parts)) return false;
+    n.shadow_u = n.theta;
+  }
   hipMemsetAsync(n.theta, 0, tot * 4, c->st);
   hipMemsetAsync(n.m, 0, tot * 4, c->st);
   hipMemsetAsync(n.v, 0, tot * 4, c->st);
   hipMemsetAsync(n.g, 0, tot * 4, c->st);
-  hipMemsetAsync(n.shadow_d, 0, tot * esize(c), c->st);
   hipMemsetAsync(n.run_mean, 0, (size_t)c->L * n.nbn * 4, c->st);
   hipMemsetAsync(n.t, 0, (size_t)c->L * 4, c->st);
   hipMemsetAsync(n.bc, 0, (size_t)c->L * 8, c->st);
@@ -541,7 +548,7 @@ void refresh_transposes(gan_ctx* c, Net& n, bool isG) {
     if (c->bf16)
       launch_transpose_w<bf16_t, bf16_t>((const bf16_t*)n.shadow_u + cl.w, (bf16_t*)n.shadow_d + cl.w, n.P, c->L, cl.Cb, cl.Cs, c->st);
     else
-      launch_transpose_w<float, float>((const float*)n.theta + cl.w, (float*)n.shadow_d + cl.w, n.P, c->L, cl.Cb, cl.Cs, c->st);
+      launch_split_weights({n.theta + cl.w, n.split_u + cl.w, n.split_d + cl.w, n.P, n.P, c->L, cl.Cb, cl.Cs}, c->st);
   }
 }
 // k4 weights with summed taps of G's Upsample + Conv k3 blocks, from the 3 x 3 master weights
@@ -550,7 +557,8 @@ void paper_rebuild_w4(gan_ctx* c) {
   Net& G = c->G;
   for (size_t i = 0; i + 1 < G.conv.size(); ++i) {
     const ConvLayer& cl = G.conv[i];
-    launch_w3_to_w4<T>(G.theta + cl.w, (T*)G.w4u + cl.w4, (T*)G.w4d + cl.w4, c->L, cl.Cb, cl.Cs, c->st, G.P, G.P4);
+    launch_w3_to_w4<T>(G.theta + cl.w, (T*)G.w4u + cl.w4, c->bf16 ? (T*)G.w4d + cl.w4 : nullptr, c->L, cl.Cb, cl.Cs, c->st, G.P, G.P4);
+    if (!c->bf16) launch_split_weights({(const float*)G.w4u + cl.w4, G.split_u + cl.w4, G.split_d + cl.w4, G.P4, G.P4, c->L, cl.Cb, cl.Cs}, c->st);
   }
 }
 void refresh_shadows(gan_ctx* c) {
@@ -566,16 +574,32 @@ void refresh_shadows(gan_ctx* c) {
 }
 
 // ---- launch helpers ---------------------------------------------------------------------------------------
+// The weights of a GEMM launch: see ConvArgs.
+struct Weights {
+  const void* w;
+  long long stride, plane = 0;
+  const float* raw = nullptr;
+  long long raw_stride = 0;
+  int raw_n = 0, raw_k = 0;
+};
+// of a convolution on the engine; up: as G's transposed convolutions and D's data gradients read them
+Weights layer_weights(const gan_ctx* c, const Net& net, const ConvLayer& cl, bool up) {
+  const bool k4 = cl.w4 >= 0;                          // summed taps (the networks of the tables, G)
+  const long long off = k4 ? cl.w4 : cl.w, P = k4 ? net.P4 : net.P;
+  if (c->bf16) return {(const bf16_t*)(k4 ? (up ? net.w4u : net.w4d) : (up ? net.shadow_u : net.shadow_d)) + off, P};
+  return {(up ? net.split_u : net.split_d) + off, 3 * P, P, (k4 ? (const float*)net.w4u : net.theta) + off, P, up ? cl.Cs : 1, up ? 1 : cl.Cs};
+}
 template <typename T>
-void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, const void* W, long long wstride, void* Out,
+void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, const Weights& W, void* Out,
                const void* Aux, int C, int N, int Hin, int Hr, int seg_first, int nseg, int n, int w_nstride = 0,
                double flops_alg = -1.0, bool stats = false, const NormArgs* known = nullptr, const float* bias = nullptr) {
   ConvArgs a = {};
-  a.A = A; a.W = W; a.Out = Out; a.Aux = Aux; a.w_nstride = w_nstride ? w_nstride : N;
+  a.A = A; a.W = W.w; a.Out = Out; a.Aux = Aux; a.w_nstride = w_nstride ? w_nstride : N;
   a.tile = layer_tile(c, mode, N, Hr * Hr, nseg);
   const int tr = conv_tile_rows((int)sizeof(T), a.tile);
   a.offs = c->rb.offs; a.tpre = tpre_of(c, Hr * Hr, tr); a.tmodel = tmodel_of(c, Hr * Hr, tr);
-  a.w_stride = wstride; a.L = c->L; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n;
+  a.w_stride = W.stride; a.w_plane = W.plane; a.w_raw = W.raw; a.raw_stride = W.raw_stride; a.raw_n = W.raw_n; a.raw_k = W.raw_k;
+  a.L = c->L; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n;
   a.C = C; a.N = N; a.Hin = Hin; a.Hr = Hr; a.ub_tiles = ub_tiles(c, n, Hr * Hr, tr);
   a.slope = c->cfg.leaky_slope;
   if (epi == EPI_BN) {
@@ -596,7 +620,7 @@ void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, c
   char detail[64];
   snprintf(detail, sizeof(detail), "[C%d N%d H%d seg%d]", C, N, Hr, nseg);
   (void)name;
-  Scope s(c, conv_variant_name(mode, epi, a), flops, bytes, detail);
+  Scope s(c, conv_variant_name((int)sizeof(T), mode, epi, a), flops, bytes, detail);
   launch_conv<T>(mode, epi, a, c->st);
 }
 
@@ -683,7 +707,7 @@ void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool update_runn
     const int tr = conv_tile_rows((int)sizeof(T), tile), gemm_phases = gemm_mode == MODE_UP ? 4 : 1;
     a.fold_running = update_running;
     launch_bn_stats_from_partial(a, c->stat_partial, tpre_of(c, gemm_rps, tr), ub_tiles(c, a.n, gemm_rps, tr), gemm_phases, col_groups, tr,
-                                 gemm_rps, conv_stat_split((int)sizeof(T), tile), c->st);
+                                 gemm_rps, conv_stat_split((int)sizeof(T), tile, gemm_mode), c->st);
   }
   Scope s(c, "bn_apply", 0, 2 * elems * sizeof(T));
   launch_bn_apply<T>(a, c->st);
@@ -754,7 +778,7 @@ void g_forward(gan_ctx* c, int n, bool use_running, bool update_running, float* 
   const float relu = 0.f;
   const NormArgs a0 = norm_args<T>(c, G, G.C0, G.h0 * G.h0, G.fc_gamma, G.fc_beta, G.fc_rs, c->g_mean[0], c->g_var[0], c->g_rstd[0],
                                    c->g_sums[0], 0, 1, n, relu);
-  conv_call<T>(c, "gemm_dense", MODE_DENSE, use_running ? EPI_BN : EPI_NONE, c->zin, (const T*)G.shadow_u + G.fc_w, G.P,
+  conv_call<T>(c, "gemm_dense", MODE_DENSE, use_running ? EPI_BN : EPI_NONE, c->zin, Weights{(const T*)G.shadow_u + G.fc_w, G.P},
                use_running ? c->gact[0] : c->gpre[0], nullptr, G.Kp, G.J, 1, 1, 0, 1, n, 0, -1.0, !use_running, &a0);
   if (!use_running) bn_forward<T>(c, a0, c->gpre[0], c->gact[0], update_running, MODE_DENSE, 1, G.h0 * G.h0);
   const int nl = (int)G.conv.size();
@@ -762,7 +786,7 @@ void g_forward(gan_ctx* c, int n, bool use_running, bool update_running, float* 
     const ConvLayer& cl = G.conv[i];
     const NormArgs a = norm_args<T>(c, G, cl.Cb, 4 * cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->g_mean[i + 1], c->g_var[i + 1],
                                     c->g_rstd[i + 1], c->g_sums[i + 1], 0, 1, n, relu);
-    conv_call<T>(c, "gemm_up", MODE_UP, use_running ? EPI_BN : EPI_NONE, c->gact[i], (const T*)G.shadow_u + cl.w, G.P,
+    conv_call<T>(c, "gemm_up", MODE_UP, use_running ? EPI_BN : EPI_NONE, c->gact[i], layer_weights(c, G, cl, true),
                  use_running ? c->gact[i + 1] : c->gpre[i + 1], nullptr, cl.Cs, cl.Cb, cl.Hs, cl.Hs, 0, 1, n, 0, -1.0, !use_running, &a);
     if (!use_running) bn_forward<T>(c, a, c->gpre[i + 1], c->gact[i + 1], update_running, MODE_UP, cl.Hs * cl.Hs);
   }
@@ -779,12 +803,12 @@ void d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_running) 
   const float slope = c->cfg.leaky_slope;
   // first conv (+label maps, bias, LeakyReLU) as a row-by-row GEMM over the patch matrix
   const ConvLayer& c1 = D.conv[0];
-  conv_call<T>(c, "gemm_dense_img", MODE_DENSE, c->labels > 0 ? EPI_LABEL_LRELU : EPI_LRELU, c->colD, c->wpD, (long long)c1.Cs * c->KcD,
+  conv_call<T>(c, "gemm_dense_img", MODE_DENSE, c->labels > 0 ? EPI_LABEL_LRELU : EPI_LRELU, c->colD, Weights{c->wpD, (long long)c1.Cs * c->KcD},
                c->dact[0], nullptr, c->KcD, c1.Cs, 1, c1.Hs, seg_first, nseg, n, 0, img_flops(c1, n, nseg));
   const int nl = (int)D.conv.size();
   for (int j = 1; j < nl; ++j) {
     const ConvLayer& cl = D.conv[j];
-    conv_call<T>(c, "gemm_down", MODE_DOWN, EPI_NONE, c->dact[j - 1], (const T*)D.shadow_d + cl.w, D.P, c->dpre[j], nullptr, cl.Cb,
+    conv_call<T>(c, "gemm_down", MODE_DOWN, EPI_NONE, c->dact[j - 1], layer_weights(c, D, cl, false), c->dpre[j], nullptr, cl.Cb,
                  cl.Cs, 2 * cl.Hs, cl.Hs, seg_first, nseg, n, 0, -1.0, true);
     bn_forward<T>(c, norm_args<T>(c, D, cl.Cs, cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->d_mean[j], c->d_var[j], c->d_rstd[j],
                                   c->d_sums[j], seg_first, nseg, n, slope),
@@ -847,7 +871,7 @@ void d_backward(gan_ctx* c, int n, int seg_first, int nseg, bool param_grads, bo
       pending = j - 1;
     }
     // data gradient; for the first conv's output the LeakyReLU derivative is applied in the epilogue
-    conv_call<T>(c, "gemm_up", MODE_UP, j == 1 ? EPI_ACT_BWD : EPI_NONE, dx, (const T*)D.shadow_u + cl.w, D.P, c->bufA,
+    conv_call<T>(c, "gemm_up", MODE_UP, j == 1 ? EPI_ACT_BWD : EPI_NONE, dx, layer_weights(c, D, cl, true), c->bufA,
                  j == 1 ? c->dact[0] : nullptr, cl.Cs, cl.Cb, cl.Hs, cl.Hs, seg_first, nseg, n);
   }
   if (param_grads && adam && pending >= 0) {
@@ -890,7 +914,7 @@ void g_backward(gan_ctx* c, int n, const AdamArgs* adam = nullptr) {
     b.img = dlast; b.partial = c->bias_partial; b.dbias = G.g + last.bias; b.pstride = G.P; b.offs = c->rb.offs;
     b.L = c->L; b.CB = last.Cb; b.HW = 4 * last.Hs * last.Hs;
     launch_img_bias_grad<T>(b, c->st);
-    conv_call<T>(c, "gemm_dense_img", MODE_DENSE, EPI_NONE, c->colG, c->wpG, (long long)last.Cs * c->KcG, c->bufA, nullptr, c->KcG,
+    conv_call<T>(c, "gemm_dense_img", MODE_DENSE, EPI_NONE, c->colG, Weights{c->wpG, (long long)last.Cs * c->KcG}, c->bufA, nullptr, c->KcG,
                  last.Cs, 1, last.Hs, 0, 1, n, 0, img_flops(last, n, 1));
   }
   int pending = -1;
@@ -904,7 +928,7 @@ void g_backward(gan_ctx* c, int n, const AdamArgs* adam = nullptr) {
     if (adam && pending >= 0) adam_region_call<T>(c, *adam, pending, side);      // as in D
     wgrad_call<T>(c, "gemm_wgrad", dx, c->gact[i], G.g + cl.w, G.P, cl.Cb, cl.Cs, cl.Hs, 16, 1, n, -1.0, 0, side);
     pending = i;
-    conv_call<T>(c, "gemm_down", MODE_DOWN, EPI_NONE, dx, (const T*)G.shadow_d + cl.w, G.P, c->bufA, nullptr, cl.Cb, cl.Cs,
+    conv_call<T>(c, "gemm_down", MODE_DOWN, EPI_NONE, dx, layer_weights(c, G, cl, false), c->bufA, nullptr, cl.Cb, cl.Cs,
                  2 * cl.Hs, cl.Hs, 0, 1, n);
   }
   bn_backward<T>(c, norm_args<T>(c, G, G.C0, G.h0 * G.h0, G.fc_gamma, G.fc_beta, G.fc_rs, c->g_mean[0], c->g_var[0], c->g_rstd[0],
@@ -954,7 +978,7 @@ void paper_g_forward(gan_ctx* c, int n, bool use_running, bool update_running, f
   NormArgs a0 = norm_args<T>(c, G, G.C0, G.h0 * G.h0, G.fc_gamma, G.fc_beta, G.fc_rs, c->g_mean[0], c->g_var[0], c->g_rstd[0],
                              c->g_sums[0], 0, 1, n, 1.f);
   a0.eps = f.bn_eps_first;
-  conv_call<T>(c, "gemm_dense", MODE_DENSE, use_running ? EPI_BN : EPI_NONE, c->zin, (const T*)G.shadow_u + G.fc_w, G.P,
+  conv_call<T>(c, "gemm_dense", MODE_DENSE, use_running ? EPI_BN : EPI_NONE, c->zin, Weights{(const T*)G.shadow_u + G.fc_w, G.P},
                use_running ? c->gact[0] : c->gpre[0], nullptr, G.Kp, G.J, 1, 1, 0, 1, n, 0, -1.0, false, &a0, G.theta + G.fc_bias);
   if (!use_running) {
     PointArgs a = point_args(c, c->gpre[0], G.J, G.J, 1, 0, 1, n);          // + bias, ReLU
@@ -968,7 +992,7 @@ void paper_g_forward(gan_ctx* c, int n, bool use_running, bool update_running, f
     const ConvLayer& cl = G.conv[i];
     const NormArgs a = norm_args<T>(c, G, cl.Cb, 4 * cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->g_mean[i + 1], c->g_var[i + 1],
                                     c->g_rstd[i + 1], c->g_sums[i + 1], 0, 1, n, f.leaky_slope);
-    conv_call<T>(c, "gemm_up", MODE_UP, use_running ? EPI_BN : EPI_NONE, c->gact[i], (const T*)G.w4u + cl.w4, G.P4,
+    conv_call<T>(c, "gemm_up", MODE_UP, use_running ? EPI_BN : EPI_NONE, c->gact[i], layer_weights(c, G, cl, true),
                  use_running ? c->gact[i + 1] : c->gpre[i + 1], nullptr, cl.Cs, cl.Cb, cl.Hs, cl.Hs, 0, 1, n, 0, -1.0, !use_running, &a);
     if (!use_running) bn_forward<T>(c, a, c->gpre[i + 1], c->gact[i + 1], update_running, MODE_UP, cl.Hs * cl.Hs);
   }
@@ -989,7 +1013,7 @@ void paper_d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_run
   Net& D = c->D;
   const gan_config& f = c->cfg;
   const ConvLayer& c1 = D.conv[0];
-  conv_call<T>(c, "gemm_dense_img", MODE_DENSE, EPI_LRELU, c->colD, c->wpD, (long long)c1.Cs * c->KcD, c->dact[0], nullptr, c->KcD,
+  conv_call<T>(c, "gemm_dense_img", MODE_DENSE, EPI_LRELU, c->colD, Weights{c->wpD, (long long)c1.Cs * c->KcD}, c->dact[0], nullptr, c->KcD,
                c1.Cs, 1, c1.Hs, seg_first, nseg, n, 0, img_flops(c1, n, nseg));
   if (f.dropout_p > 0.f) {
     PointArgs a = point_args(c, c->dact[0], c1.cs_real, c1.Cs, c1.Hs * c1.Hs, seg_first, nseg, n);
@@ -1000,7 +1024,7 @@ void paper_d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_run
   const int nl = (int)D.conv.size();
   for (int j = 1; j < nl; ++j) {
     const ConvLayer& cl = D.conv[j];
-    conv_call<T>(c, "gemm_down", MODE_DOWN, EPI_NONE, c->dact[j - 1], (const T*)D.shadow_d + cl.w, D.P, c->dpre[j], nullptr, cl.Cb,
+    conv_call<T>(c, "gemm_down", MODE_DOWN, EPI_NONE, c->dact[j - 1], layer_weights(c, D, cl, false), c->dpre[j], nullptr, cl.Cb,
                  cl.Cs, 2 * cl.Hs, cl.Hs, seg_first, nseg, n);
     PointArgs a = point_args(c, c->dpre[j], cl.cs_real, cl.Cs, cl.Hs * cl.Hs, seg_first, nseg, n);
     a.bias = D.theta + cl.bias; a.pstride = D.P; a.slope = f.leaky_slope;
@@ -1046,7 +1070,7 @@ void paper_d_backward(gan_ctx* c, int n, int seg_first, int nseg, bool param_gra
       wgrad_call<T>(c, "gemm_wgrad", c->dact[j - 1], c->bufB, D.g + cl.w, D.P, cl.Cb, cl.Cs, cl.Hs, 16, nseg, n);
     }
     const int first = f.dropout_p > 0.f ? EPI_DROP_BWD : EPI_ACT_BWD;         // the first block's LeakyReLU and dropout
-    conv_call<T>(c, "gemm_up", MODE_UP, j == 1 ? first : EPI_NONE, c->bufB, (const T*)D.shadow_u + cl.w, D.P, c->bufA,
+    conv_call<T>(c, "gemm_up", MODE_UP, j == 1 ? first : EPI_NONE, c->bufB, layer_weights(c, D, cl, true), c->bufA,
                  j == 1 ? c->dact[0] : nullptr, cl.Cs, cl.Cb, cl.Hs, cl.Hs, seg_first, nseg, n);
   }
   const ConvLayer& c1 = D.conv[0];
@@ -1089,7 +1113,7 @@ void paper_g_backward(gan_ctx* c, int n) {
     const long long per = (long long)16 * cl.Cb * cl.Cs;
     wgrad_call<T>(c, "gemm_wgrad", c->bufB, c->gact[i], c->dw4, per, cl.Cb, cl.Cs, cl.Hs, 16, 1, n);
     launch_dw4_to_dw3(c->dw4, G.g + cl.w, c->L, cl.Cb, cl.Cs, c->st, per, G.P);
-    conv_call<T>(c, "gemm_down", MODE_DOWN, EPI_NONE, c->bufB, (const T*)G.w4d + cl.w4, G.P4, c->bufA, nullptr, cl.Cb, cl.Cs,
+    conv_call<T>(c, "gemm_down", MODE_DOWN, EPI_NONE, c->bufB, layer_weights(c, G, cl, false), c->bufA, nullptr, cl.Cb, cl.Cs,
                  2 * cl.Hs, cl.Hs, 0, 1, n);
   }
   NormArgs na = norm_args<T>(c, G, G.C0, G.h0 * G.h0, G.fc_gamma, G.fc_beta, G.fc_rs, c->g_mean[0], c->g_var[0], c->g_rstd[0],
@@ -1124,7 +1148,7 @@ AdamArgs adam_args(gan_ctx* c, Net& net, bool isG) {
   a.theta = net.theta; a.m = net.m; a.v = net.v; a.g = net.g; a.shadow = c->bf16 ? net.shadow_u : nullptr;
   a.P = net.P; a.L = c->L; a.counts = c->rb.counts; a.t = net.t; a.bc = net.bc;
   a.lr = c->cfg.lr; a.beta1 = c->cfg.beta1; a.beta2 = c->cfg.beta2; a.eps = c->cfg.adam_eps;
-  a.shadow_t = net.shadow_d;
+  a.shadow_t = net.shadow_d; a.split_u = net.split_u; a.split_d = net.split_d;
   for (size_t i = 0; i < net.conv.size(); ++i) {
     const bool gemm = isG ? (i + 1 < net.conv.size()) : (i > 0);
     if (!gemm) continue;
@@ -1134,14 +1158,15 @@ AdamArgs adam_args(gan_ctx* c, Net& net, bool isG) {
   adam_plan(a);
   return a;
 }
-// bytes one update moves per element: g, theta, m, v in; theta, m, v out; the storage-type copy
+// bytes one update moves per element: g, theta, m, v in; theta, m, v out; the storage-type copy (tiled regions: and the transposed
+// one; fp32: both as three planes)
 inline double adam_bytes_per_element(const gan_ctx* c) { return 28.0 + (c->bf16 ? 2.0 : 0.0); }
 template <typename T>
 void adam_region_call(gan_ctx* c, const AdamArgs& a, int region, hipStream_t st) {
   double elems = 0;
   for (int r = 0; r < a.nregions; ++r)
     if (region < 0 || r == region) elems += 16.0 * a.reg_cb[r] * a.reg_cs[r];
-  Scope s(c, "adam", 0, (double)c->L * elems * (adam_bytes_per_element(c) + sizeof(T)), nullptr, st);
+  Scope s(c, "adam", 0, (double)c->L * elems * (adam_bytes_per_element(c) + (c->bf16 ? 2.0 : 12.0)), nullptr, st);
   launch_adam_region<T>(a, region, st);
 }
 // what is left of a planned update once the regions are done (or enqueued beside): the gaps, and the packed weights of
@@ -1930,11 +1955,23 @@ static gan_status op_conv(gan_ctx* c, int mode, const void* A, const void* W, vo
   if (s != GAN_OK) return s;
   ConvArgs a = {};
   a.A = A; a.W = W; a.Out = Out; a.Aux = nullptr; a.w_nstride = N; a.offs = offs; a.tpre = tp; a.w_stride = wstride; a.L = n_groups;
+  unsigned short* parts = nullptr;
+  if (!c->bf16) {
+    if (hipMalloc((void**)&parts, (size_t)n_groups * wstride * 6) != hipSuccess) {
+      (void)hipGetLastError();
+      (void)hipFree(tp);
+      return fail(c, GAN_E_OOM, "split weights alloc");
+    }
+    const SplitArgs sp = {(const float*)W, parts, nullptr, wstride, wstride, n_groups, N, C};
+    launch_split_weights(sp, c->st);
+    a.W = parts; a.w_stride = 3 * wstride; a.w_plane = wstride; a.w_raw = (const float*)W; a.raw_stride = wstride; a.raw_n = C; a.raw_k = 1;
+  }
   a.seg_first = 0; a.nseg = 1; a.seg_samples = n_samples; a.C = C; a.N = N; a.Hin = Hin; a.Hr = Hr;
   a.ub_tiles = (int)(((long long)n_samples * Hr * Hr) / tr) + n_groups; a.slope = 0.f; a.tile = tile;
   if (c->bf16) launch_conv<bf16_t>(mode, EPI_NONE, a, c->st); else launch_conv<float>(mode, EPI_NONE, a, c->st);
   s = finish_op(c);
   (void)hipFree(tp);
+  if (parts) (void)hipFree(parts);
   return s;
 }
 

@@ -64,7 +64,12 @@ enum Act { ACT_RELU = 0, ACT_LRELU = 1 };
 // Arguments of the grouped implicit-GEMM forward-type kernel (down / up / dense).
 struct ConvArgs {
   const void* A;         // gathered activations (storage type)
-  const void* W;         // weights of model 0, K-contiguous: [tap][N][C] (storage type)
+  const void* W;         // weights of model 0, K-contiguous: [tap][N][C] (storage type); fp32 convolutions: [3][tap][N][C] bf16, the
+                         // parts of launch_split_weights, planes w_plane elements apart
+  long long w_plane;
+  const float* w_raw;    // the fp32 weights of model 0 themselves, element (tap, n, c) at tap * w_nstride * C + n * raw_n + c * raw_k
+  long long raw_stride;  //   (elements between models), for tiles that have no split (see Split8)
+  int raw_n, raw_k;
   void* Out;             // output activations (storage type)
   const void* Aux;       // EPI_ACT_BWD, EPI_DROP_BWD: saved forward output at the output position (storage type)
   const void* label_rows;  // EPI_LABEL_LRELU: [9 * slot + position class][N] (storage type), added to the output rows of the pixels of
@@ -131,7 +136,7 @@ __device__ inline int pos_class(int y, int x, int Hs) {
 template <typename T> void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st);
 template <typename T> void launch_wgrad(const WgradArgs& a, hipStream_t st);
 // names of the kernel instantiations the two launchers pick (per-kernel timing)
-const char* conv_variant_name(int mode, int epi, const ConvArgs& a);
+const char* conv_variant_name(int esize, int mode, int epi, const ConvArgs& a);
 const char* wgrad_variant_name(int esize, const WgradArgs& a);
 // output tiles per model of the weight-gradient launch for this layer shape (esize: bytes per stored element)
 int wgrad_tiles_per_model(int esize, int ntaps, int Cb, int Cs);
@@ -141,6 +146,6 @@ int wgrad_tiles_per_model(int esize, int ntaps, int Cb, int Cs);
 ConvTile conv_choose_tile(int esize, int n_out, double rows_per_model, int n_models, int groups);
 ConvTile conv_tile_of_rows(int esize, int rows, int n_out);
 int conv_tile_rows(int esize, ConvTile t);
-int conv_stat_split(int esize, ConvTile t);
+int conv_stat_split(int esize, ConvTile t, int mode);
 
 }  // namespace gan

@@ -51,6 +51,7 @@ template <> struct FwdTiles<bf16_t> {
   typedef Tile<256, 256, 2, 4, 128, 2> Big;      // 512 threads, wave tile 128 x 64, 128 KiB of LDS
   typedef Tile<256, 128, 4, 2, 64, 3> Mid;       // 512 threads, wave tile 64 x 64, 72 KiB of LDS
   typedef Tile<128, 128, 2, 2, 128, 2> Small;    // 256 threads, wave tile 64 x 64 (few rows per model), 64 KiB of LDS
+  typedef Small SmallDense;
   typedef Tile<256, 64, 4, 1, 128, 2> Narrow;    // 256 threads, wave tile 64 x 64, for layers with 64 output channels:
                                                  // 128-byte chunks, two buffers of 40 KiB, so two blocks still share a CU
   typedef Tile<256, 64, 4, 1, 64, 2> NarrowShort;  // the same with two buffers of 20 KiB for MODE_UP and MODE_DENSE: their reductions are
@@ -65,16 +66,19 @@ template <> struct FwdTiles<bf16_t> {
   // 256x64: up 128 -> 64 at side 16 480 against 582 with 64-byte x 2, up 64 -> 64 at side 8 401 against 438, but down 64 -> 64 at
   // side 8 586 against 422.
 };
-// fp32 is bound by the matrix and vector pipes together, so more than 128 x 128 brings nothing: 20 x 64 samples, 128 -> 256
-// channels at side 8, in TFLOP/s: 128x128 172, 256x128 162 (eight waves of 64 x 64) and 154 (four of 128 x 64, one wave per SIMD),
-// 256x64 162; the 64-byte chunks of the bf16 tiles 156-162 (all without the scaling of the operands, see Split8: 128x128 is at 157 with it).
+// fp32: a wave splits the rows it reads (its weights are split once, by the update), so wave tiles are one 32-row block and as wide as the
+// tile; two blocks per CU.  20 x 64 samples, us: down 128 -> 256 channels, side 8: 128x128 with 32 x 128 wave tiles 435, 64 x 64 474,
+// 32 x 64 (eight waves) 445, 256x128 (eight waves, one block per CU) 490; up 256 -> 128, side 8: 438, 451, 455, 450; with weights split
+// by every wave 538 and 486 (64 x 64, the best then).  10 x 128 samples, up 128 -> 64, side 7: 128x64 108, 256x64 (one block per CU) 129, before 113.
+// The patch-matrix layers and G's linear one (MODE_DENSE) read their few weights as fp32 and split them too: 64 x 64 wave tiles there.
 template <> struct FwdTiles<float> {
-  typedef Tile<128, 128, 2, 2, 128, 2> Small;    // 256 threads, wave tile 64 x 64, 64 KiB of LDS
-  typedef Tile<256, 64, 4, 1, 128, 2> Narrow;    // 256 threads, wave tile 64 x 64, 80 KiB
+  typedef Tile<128, 128, 4, 1, 128, 2> Small;    // 256 threads, wave tile 32 x 128, 80 KiB of LDS
+  typedef Tile<128, 128, 2, 2, 128, 2> SmallDense;
+  typedef Tile<128, 64, 4, 1, 128, 2> Narrow;    // 256 threads, wave tile 32 x 64, 56 KiB
   typedef Narrow NarrowShort;
-  typedef Tile<64, 64, 2, 2, 128, 2> Tiny;       // 256 threads, wave tile 32 x 32, 32 KiB
-  typedef Tile<64, 64, 2, 2, 128, 2, 2> Pair;
-  typedef Tile<32, 64, 1, 2, 128, 3, 4> Deep;
+  typedef Tile<64, 64, 2, 2, 128, 2> Tiny;       // 256 threads, wave tile 32 x 32, 40 KiB
+  typedef Tile<64, 64, 2, 2, 128, 2, 2> Pair;    // 80 KiB
+  typedef Tile<32, 64, 1, 2, 128, 2, 4> Deep;    // 128 KiB
 };
 
 // What a tile is to the chooser: its shape, the row blocks with statistics of their own, the blocks of it that a CU holds, and
@@ -97,13 +101,16 @@ static const TileInfo TILES[2][7] = {
      info<FwdTiles<bf16_t>::Tiny>(TILE_TINY, "64x64", 5, 0.52),
      info<FwdTiles<bf16_t>::Pair>(TILE_PAIR, "64x64 pair", 2, 0.585, 256), info<FwdTiles<bf16_t>::Deep>(TILE_DEEP, "32x64 deep", 1, 0.36, 256)},
     {{TILE_BIG, "", 0, 0, 0, 0, 0, 0}, {TILE_MID, "", 0, 0, 0, 0, 0, 0},
-     info<FwdTiles<float>::Small>(TILE_SMALL, "128x128", 2, 1.0), info<FwdTiles<float>::Narrow>(TILE_NARROW, "256x64", 2, 0.95),
+     info<FwdTiles<float>::Small>(TILE_SMALL, "128x128", 2, 1.0), info<FwdTiles<float>::Narrow>(TILE_NARROW, "128x64", 2, 0.75),
      info<FwdTiles<float>::Tiny>(TILE_TINY, "64x64", 5, 0.64),
      info<FwdTiles<float>::Pair>(TILE_PAIR, "64x64 pair", 2, 0.76, 512), info<FwdTiles<float>::Deep>(TILE_DEEP, "32x64 deep", 1, 0.58, 256)},
 };
 static const TileInfo& tile_info(int esize, ConvTile t) { return TILES[esize == 4][t]; }
 int conv_tile_rows(int esize, ConvTile t) { return tile_info(esize, t).rows; }
-int conv_stat_split(int esize, ConvTile t) { return tile_info(esize, t).split; }
+int conv_stat_split(int esize, ConvTile t, int mode) {
+  if (esize == 4 && t == TILE_SMALL && mode == MODE_DENSE) return FwdTiles<float>::SmallDense::WM;
+  return tile_info(esize, t).split;
+}
 
 // The tile with the smallest estimated time for a launch of `groups` row spaces (phases x segments) of rows_per_model rows in
 // each of n_models models and n_out output columns: rounds of blocks over the chip's 256 CUs times a block's share of its
@@ -236,6 +243,10 @@ __device__ inline void lds_wait(u32x4 (&a)[TM], u32x4 (&b)[TN]) {
     asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a[0]), "+v"(a[1]), "+v"(b[0]), "+v"(b[1]) : "n"(N) : "memory");
   else if constexpr (TM == 1 && TN == 1)
     asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a[0]), "+v"(b[0]) : "n"(N) : "memory");
+  else if constexpr (TM == 1 && TN == 2)
+    asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(a[0]), "+v"(b[0]), "+v"(b[1]) : "n"(N) : "memory");
+  else if constexpr (TM == 1 && TN == 4)
+    asm volatile("s_waitcnt lgkmcnt(%5)" : "+v"(a[0]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]) : "n"(N) : "memory");
   else
     static_assert(TM == 4 && TN == 2, "add the operand list for this wave tile");
 }
@@ -276,19 +287,27 @@ __device__ __forceinline__ void tile_mma_fwd(floatx16 (&acc)[TM][TN], const unsi
   });
 }
 
-// fp32 through splits: two K-steps (16 values of K per row) are one step here; lane half h supplies the chunks 2 vs + h of both.
-template <int TM, int TN, int KB>
+// fp32 through splits: two K-steps (16 values of K per row) are one step here; lane half h supplies values 8 h .. 8 h + 7 of the step.
+// PRE: the columns are split already, three planes of BN rows of KB / 2 bytes each (swizzled like rows of a bf16 tile).
+template <int TM, int TN, int KB, bool PRE, int BN>
 __device__ __forceinline__ void tile_mma_split(floatx16 (&acc)[TM][TN], floatx16 (&low)[TM][TN], const unsigned char* As,
                                                const unsigned char* Bs, int wm, int wn, int lane) {
   const int r = lane & 31, h = lane >> 5;
-  const int sw = fwd_swz<KB>(r);
+  const int sw = fwd_swz<KB>(r), swb = fwd_swz<KB / 2>(r);
   const unsigned char* const ap = As + (wm * TM * 32 + r) * KB;
-  const unsigned char* const bp = Bs + (wn * TN * 32 + r) * KB;
+  const unsigned char* const bp = Bs + (wn * TN * 32 + r) * (PRE ? KB / 2 : KB);
   static_for<0, KB / 64>([&](auto ps) __attribute__((always_inline)) {
-    const int c0 = ((4 * ps.value + h) ^ sw) * 16, c1 = ((4 * ps.value + 2 + h) ^ sw) * 16;
+    const int c0 = ((4 * ps.value + 2 * h) ^ sw) * 16, c1 = ((4 * ps.value + 2 * h + 1) ^ sw) * 16;
     Split8 b[TN];
     static_for<0, TN>([&](auto t) __attribute__((always_inline)) {
-      b[t.value] = split8(*reinterpret_cast<const u32x4*>(bp + t.value * 32 * KB + c0), *reinterpret_cast<const u32x4*>(bp + t.value * 32 * KB + c1));
+      if constexpr (PRE) {
+        const unsigned char* const q = bp + t.value * 32 * (KB / 2) + ((2 * ps.value + h) ^ swb) * 16;
+        b[t.value].h = *reinterpret_cast<const u32x4*>(q);
+        b[t.value].m = *reinterpret_cast<const u32x4*>(q + BN * (KB / 2));
+        b[t.value].l = *reinterpret_cast<const u32x4*>(q + 2 * BN * (KB / 2));
+      } else {
+        b[t.value] = split8(*reinterpret_cast<const u32x4*>(bp + t.value * 32 * KB + c0), *reinterpret_cast<const u32x4*>(bp + t.value * 32 * KB + c1));
+      }
     });
     static_for<0, TM>([&](auto t) __attribute__((always_inline)) {
       const Split8 a = split8(*reinterpret_cast<const u32x4*>(ap + t.value * 32 * KB + c0), *reinterpret_cast<const u32x4*>(ap + t.value * 32 * KB + c1));
@@ -368,7 +387,10 @@ template <typename T, int MODE, int EPI, typename TL>
 __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void conv_gemm_kernel(ConvArgs p) {
   constexpr int BM = TL::BM, BN = TL::BN, TM = TL::TM, TN = TL::TN, PA = TL::PA, PB = TL::PB, RPP = TL::RPP;
   constexpr int KB = TL::KB, NST = TL::NST, KS = TL::KS;
-  constexpr int RING = NST * (BM + BN) * KB;                                   // of one group
+  // fp32 convolutions get their weights split already (launch_split_weights): three bf16 planes
+  constexpr bool PRE = sizeof(T) == 4 && MODE != MODE_DENSE;
+  constexpr int KBB = PRE ? KB / 2 * 3 : KB;                                   // bytes of a column in LDS
+  constexpr int RING = NST * (BM * KB + BN * KBB);                             // of one group
   constexpr int SMEM_RING = KS * RING;
   constexpr int ROWTAB = EPI == EPI_LABEL_LRELU ? BM * 12 : BM * 8;            // see the epilogue
   constexpr int SMEM_EPI = ROWTAB + (TL::NT / 64) * 32 * (TN * 32 * 4 + 16);
@@ -376,11 +398,12 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
   const int kgrp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / TL::NT);      // this wave's share of the reduction
   unsigned char* const As = smem + kgrp * RING;        // buffer s at As + s * BM * KB
-  unsigned char* const Bs = As + NST * BM * KB;        // buffer s at Bs + s * BN * KB
+  unsigned char* const Bs = As + NST * BM * KB;        // buffer s at Bs + s * BN * KBB
   constexpr int BK = KB / (int)sizeof(T);              // elements of K per chunk
   constexpr int LINES = 128 / KB;                      // chunks per 128-byte line
   constexpr int EPV = 16 / (int)sizeof(T);
-  constexpr int LPT = PA + PB;                         // loads per thread per chunk
+  constexpr int RPB = TL::NT / (KB / 32), PP = BN / RPB;           // PRE: rows of a plane filled per pass, passes per plane
+  constexpr int LPT = PA + (PRE ? 3 * PP : PB);        // loads per thread per chunk
   const int tid = KS == 1 ? (int)threadIdx.x : (int)threadIdx.x - kgrp * TL::NT, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / TL::WN, wn = wave % TL::WN;
 
@@ -457,8 +480,9 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   const unsigned px_bytes = (unsigned)(C * SZ), row_bytes = (unsigned)(Hin * C * SZ), wtap_bytes = (unsigned)(wns * C * SZ);
   const unsigned bias = (MODE == MODE_DENSE) ? 0u : row_bytes + px_bytes;
   const int4v a_rsrc = make_rsrc(reinterpret_cast<const unsigned char*>(a_base) - bias, (unsigned long long)a_elems * SZ + bias);
-  const int4v w_rsrc = make_rsrc(static_cast<const T*>(p.W) + (long long)l * p.w_stride,
-                                 (unsigned long long)(MODE == MODE_DENSE ? 1 : 16) * wns * C * SZ);
+  const int4v w_rsrc = PRE ? make_rsrc(static_cast<const bf16_t*>(p.W) + (long long)l * p.w_stride, (2ull * p.w_plane + 16ull * wns * C) * 2)
+                           : make_rsrc(static_cast<const T*>(p.W) + (long long)l * p.w_stride,
+                                       (unsigned long long)(MODE == MODE_DENSE ? 1 : 16) * wns * C * SZ);
 
   // ---- per-thread load assignment: rows tid/CPR + RPP i, LDS position tid % CPR of the row, which holds the row's
   // 16-byte chunk (tid % CPR) ^ swizzle(row) (RPP is a multiple of the swizzle period, so the same chunk in every
@@ -468,7 +492,7 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   constexpr int CPR = TL::CPR;
   const int row0 = tid / CPR;
   const int chunk = (tid % CPR) ^ fwd_swz<KB>(row0);
-  unsigned apix[PA], bcol[PB];
+  unsigned apix[PA], bcol[PRE ? PP : PB];
   int outside[PA];
 #pragma unroll
   for (int i = 0; i < PA; ++i) {
@@ -502,10 +526,20 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
       }
     }
   }
+  if constexpr (PRE) {
+    static_assert(PP >= 1 && RPB % 16 == 0, "loader shape");
+    const int brow0 = tid / (KB / 32), bchunk = (tid % (KB / 32)) ^ fwd_swz<KB / 2>(brow0);
 #pragma unroll
-  for (int i = 0; i < PB; ++i) {
-    const int col = nt * BN + row0 + RPP * i;
-    bcol[i] = col < N ? (unsigned)((col * C + chunk * EPV) * SZ) : NO_ROW;
+    for (int i = 0; i < PP; ++i) {
+      const int col = nt * BN + brow0 + RPB * i;
+      bcol[i] = col < N ? (unsigned)((col * C + bchunk * 8) * 2) : NO_ROW;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+      const int col = nt * BN + row0 + RPP * i;
+      bcol[i] = col < N ? (unsigned)((col * C + chunk * EPV) * SZ) : NO_ROW;
+    }
   }
 
   const unsigned lds0 = (unsigned)(uintptr_t)As;       // LDS byte address of the buffers
@@ -518,19 +552,22 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   // two left in a class of two are its kx pair at the one valid ky: ky = 2 (top tile, even class) or 1 (bottom, odd).
   int k_part, k_j, k_line, k_cls, k_cnt, k_tap = 0;
   unsigned k_aoff = 0, k_woff = 0;
+  int k_wtap = 0;                                      // the tap's place in the weight block
   auto k_set = [&]() {
     if (MODE == MODE_DOWN) {
       const int j = k_cnt == 4 ? k_j : k_j + (k_cls < 2 ? 2 : 0);
       const int ky = (k_cls >> 1) + 2 * (j >> 1), kx = (k_cls & 1) + 2 * (j & 1);
       k_tap = ky * 4 + kx;
       k_aoff = ky * row_bytes + kx * px_bytes + k_line * 128;
-      k_woff = k_tap * wtap_bytes + k_line * 128;
+      k_wtap = k_tap;
+      k_woff = k_wtap * wtap_bytes + k_line * 128;
     } else if (MODE == MODE_UP) {
       // phase py = 0 gathers rows y and y - 1 through ky = 1 and 3, py = 1 rows y + 1 and y through ky = 0 and 2; likewise x
       k_tap = k_cnt == 4 ? k_j : k_j + (first_gone ? 2 : 0);
       const int a = k_tap >> 1, b = k_tap & 1;
       k_aoff = (py - a + 1) * row_bytes + (px - b + 1) * px_bytes + k_line * 128;
-      k_woff = ((2 * a + 1 - py) * 4 + 2 * b + 1 - px) * wtap_bytes + k_line * 128;
+      k_wtap = (2 * a + 1 - py) * 4 + 2 * b + 1 - px;
+      k_woff = k_wtap * wtap_bytes + k_line * 128;
     } else {
       k_aoff = k_woff = k_line * 128;
     }
@@ -550,14 +587,34 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
     }
     k_set();
   };
-  auto load_chunk = [&](int stage) {                   // this group's next chunk, into a buffer
+  auto load_chunk = [&](int stage, auto split) {       // this group's next chunk, into a buffer
     const unsigned a_dst = lds0 + (stage * BM + wave * (1024 / KB)) * KB;        // + pass * RPP rows
-    const unsigned b_dst = lds0 + (NST * BM + stage * BN + wave * (1024 / KB)) * KB;
+    const unsigned b_dst = lds0 + NST * BM * KB + stage * BN * KBB + wave * 1024;
 #pragma unroll
     for (int i = 0; i < PA; ++i)
       load16_to_lds(a_rsrc, apix[i] | (unsigned)__builtin_amdgcn_sbfe(outside[i], k_tap, 1), k_aoff, a_dst + i * RPP * KB);
+    if constexpr (PRE && split.value) {
 #pragma unroll
-    for (int i = 0; i < PB; ++i) load16_to_lds(w_rsrc, bcol[i], k_woff, b_dst + i * RPP * KB);
+      for (int pl = 0; pl < 3; ++pl)
+#pragma unroll
+        for (int i = 0; i < PP; ++i)
+          load16_to_lds(w_rsrc, bcol[i], (k_woff >> 1) + (unsigned)(pl * p.w_plane * 2), b_dst + (pl * BN + i * RPB) * (KB / 2));
+    } else if constexpr (PRE) {
+      // the weights as they are, value by value (tiles that are computed again: rare)
+      const float* const raw = p.w_raw + (long long)l * p.raw_stride + (long long)k_wtap * wns * C;
+      for (int e = tid; e < BN * CPR; e += TL::NT) {
+        const int row = e / CPR, col = nt * BN + row, kk = k_line * 32 + ((e % CPR) ^ fwd_swz<KB>(row)) * 4;
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (col < N) {
+          const float* const q = raw + (long long)col * p.raw_n + (long long)kk * p.raw_k;
+          v = make_float4(q[0], q[p.raw_k], q[2 * (long long)p.raw_k], q[3 * (long long)p.raw_k]);
+        }
+        *reinterpret_cast<float4*>(Bs + stage * BN * KBB + e * 16) = v;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < PB; ++i) load16_to_lds(w_rsrc, bcol[i], k_woff, b_dst + i * RPP * KB);
+    }
 #pragma unroll
     for (int i = 0; i < KS; ++i) k_advance();
   };
@@ -576,18 +633,18 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
     for (int i = 0; i < kgrp; ++i) k_advance();
     int st_load = 0, st = 0;                           // buffers of the next chunk to load and of the current one
     const int mine = (nk - kgrp + KS - 1) / KS, steps = (nk + KS - 1) / KS;      // this group's chunks; the barriers are everyone's
-    for (int c = 0; c < NST - 1 && c < mine; ++c) load_chunk(st_load++);
+    for (int c = 0; c < NST - 1 && c < mine; ++c) load_chunk(st_load++, split);
     if (KS > 1 && mine >= NST - 1) wait_vm<(NST - 2) * LPT>(); else wait_vm<0>();
     __syncthreads();
     for (int kc = 0; kc < steps; ++kc) {
       const bool more = kc + NST - 1 < mine;
       if (more) {
-        load_chunk(st_load);
+        load_chunk(st_load, split);
         st_load = st_load == NST - 1 ? 0 : st_load + 1;
       }
       if (KS == 1 || kc < mine) {
-        if constexpr (split.value) tile_mma_split<TM, TN, KB>(acc, low, As + st * BM * KB, Bs + st * BN * KB, wm, wn, lane);
-        else tile_mma_fwd<T, TM, TN, KB>(acc, As + st * BM * KB, Bs + st * BN * KB, wm, wn, lane);
+        if constexpr (split.value) tile_mma_split<TM, TN, KB, PRE, BN>(acc, low, As + st * BM * KB, Bs + st * BN * KBB, wm, wn, lane);
+        else tile_mma_fwd<T, TM, TN, KB>(acc, As + st * BM * KB, Bs + st * BN * KBB, wm, wn, lane);
       }
       st = st == NST - 1 ? 0 : st + 1;
       if (more) wait_vm<(NST - 2) * LPT>(); else wait_vm<0>();     // chunk kc + 1 has landed; those behind it may stay in flight
@@ -824,7 +881,8 @@ static void launch_wide(const ConvArgs& a, hipStream_t st) {
     if (a.tile == TILE_BIG) return launch_one<T, MODE, EPI, typename Tiles::Big>(a, st);
     if (a.tile == TILE_MID) return launch_one<T, MODE, EPI, typename Tiles::Mid>(a, st);
   }
-  if (a.tile == TILE_SMALL) return launch_one<T, MODE, EPI, typename Tiles::Small>(a, st);
+  if (a.tile == TILE_SMALL)
+    return launch_one<T, MODE, EPI, std::conditional_t<MODE == MODE_DENSE, typename Tiles::SmallDense, typename Tiles::Small>>(a, st);
   if (a.tile == TILE_NARROW)
     return launch_one<T, MODE, EPI, std::conditional_t<MODE != MODE_DOWN, typename Tiles::NarrowShort, typename Tiles::Narrow>>(a, st);
   if (a.tile == TILE_TINY) return launch_one<T, MODE, EPI, typename Tiles::Tiny>(a, st);
@@ -845,8 +903,10 @@ void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
   {
     // the loaders address one model's slice of A and one weight block with 32-bit byte offsets
     const long long side = mode == MODE_DENSE ? a.Hr : a.Hin;
+    const bool pre = sizeof(T) == 4 && mode != MODE_DENSE;
+    if (pre && (!a.w_raw || a.w_plane < 16LL * a.w_nstride * a.C || a.w_plane % 8)) return launch_fail("GEMM: fp32 weights that are not split");
     if ((long long)a.seg_samples * side * side * a.C * (long long)sizeof(T) >= (1LL << 31) ||
-        16LL * a.w_nstride * a.C * (long long)sizeof(T) >= (1LL << 31))
+        (pre ? (2LL * a.w_plane + 16LL * a.w_nstride * a.C) * 2 : 16LL * a.w_nstride * a.C * (long long)sizeof(T)) >= (1LL << 31))
       return launch_fail("GEMM: one segment of the gathered tensor, or one weight block, is 2 GiB or larger");
   }
   if (mode == MODE_DOWN && epi == EPI_NONE) return launch_wide<T, MODE_DOWN, EPI_NONE>(a, st);
@@ -861,12 +921,12 @@ void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
   launch_fail("GEMM: (mode, epilogue) combination without an instantiation");
 }
 // Name of the kernel instantiation launch_conv picks (for per-kernel timing): mode, epilogue, tile.
-const char* conv_variant_name(int mode, int epi, const ConvArgs& a) {
+const char* conv_variant_name(int esize, int mode, int epi, const ConvArgs& a) {
   static const char* modes[3] = {"down", "up", "dense"};
   static const char* epis[6] = {"", "+actbwd", "+lrelu", "+label+lrelu", "+dropbwd", "+bn"};
-  static char names[3][6][7][48];
-  char* n = names[mode][epi][a.tile];
-  if (!n[0]) snprintf(n, 48, "gemm_%s%s<%s>", modes[mode], epis[epi], TILES[0][a.tile].name);
+  static char names[2][3][6][7][48];
+  char* n = names[esize == 4][mode][epi][a.tile];
+  if (!n[0]) snprintf(n, 48, "gemm_%s%s<%s>", modes[mode], epis[epi], tile_info(esize, a.tile).name);
   return n;
 }
 template void launch_conv<float>(int, int, const ConvArgs&, hipStream_t);

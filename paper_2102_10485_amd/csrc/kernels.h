@@ -190,6 +190,8 @@ struct AdamArgs {
   float* theta; float* m; float* v; const float* g;
   void* shadow;             // storage-type copy of theta (NULL when the storage type is fp32)
   void* shadow_t;           // storage-type copy with every region below transposed: [tap][cs][cb]
+  // fp32 storage, in place of the two copies: the regions as three bf16 planes P elements apart, as they are and transposed (launch_split_weights)
+  unsigned short *split_u, *split_d;
   long long P;              // elements per model
   int L;
   const int* counts;
@@ -216,6 +218,16 @@ template <typename T> void launch_cast_shadow(const float* theta, T* shadow, lon
 // dst[tap][cs][cb] <- src[tap][cb][cs] for every model (src: T or float master)
 template <typename T, typename S>
 void launch_transpose_w(const S* src, T* dst, long long pstride, int L, int Cb, int Cs, hipStream_t st);
+
+// fp32 weights as three bf16 planes (split_mfma.h): the block src[tap][cb][cs] of every model into up[plane][tap][cb][cs] and, transposed,
+// down[plane][tap][cs][cb]; planes `plane`, models src_stride (src) and 3 * plane elements apart.  down may be NULL.
+struct SplitArgs {
+  const float* src;
+  unsigned short *up, *down;
+  long long src_stride, plane;
+  int L, Cb, Cs;
+};
+void launch_split_weights(const SplitArgs& a, hipStream_t st);
 
 // dW[l * dw_stride + i] = part[(0 * L + l) * size + i] + part[(1 * L + l) * size + i] + ... (nsplit terms, in this
 // order), i < size (a multiple of 4), l < L

@@ -5,6 +5,7 @@
 #include <algorithm>
 
 #include "kernels.h"
+#include "split_mfma.h"
 
 namespace gan {
 
@@ -917,11 +918,63 @@ __global__ __launch_bounds__(256) void adam_kernel(AdamArgs a) {
   if (a.shadow) store4(static_cast<bf16_t*>(a.shadow) + o, tt);
 }
 
+// Four (eight) weights as bf16 parts, the planes `plane` elements apart.
+__device__ inline void store_split4(unsigned short* p, long long plane, const float (&t)[4]) {
+  unsigned h0, m0, l0, h1, m1, l1;
+  split_pair(t[0], t[1], h0, m0, l0);
+  split_pair(t[2], t[3], h1, m1, l1);
+  *reinterpret_cast<uint2*>(p) = make_uint2(h0, h1);
+  *reinterpret_cast<uint2*>(p + plane) = make_uint2(m0, m1);
+  *reinterpret_cast<uint2*>(p + 2 * plane) = make_uint2(l0, l1);
+}
+__device__ inline void store_split8(unsigned short* p, long long plane, const uint4& lo, const uint4& hi) {
+  const Split8 s = split8(__builtin_bit_cast(u32x4, lo), __builtin_bit_cast(u32x4, hi));
+  *reinterpret_cast<u32x4*>(p) = s.h;
+  *reinterpret_cast<u32x4*>(p + plane) = s.m;
+  *reinterpret_cast<u32x4*>(p + 2 * plane) = s.l;
+}
+// One 64 (cb) x 64 (cs) tile of one tap of every model, as in the update below (which splits the weights it writes itself).
+__global__ __launch_bounds__(256) void split_weights_kernel(SplitArgs a) {
+  __shared__ __attribute__((aligned(16))) float tile[64][68];
+  const int tcs_n = a.Cs >> 6, tcb_n = a.Cb >> 6, per = 16 * tcs_n * tcb_n;
+  const int l = blockIdx.x / per;
+  int q = blockIdx.x - l * per;
+  const int tcs = q % tcs_n; q /= tcs_n;
+  const int tcb = q % tcb_n, tap = q / tcb_n;
+  const float* src = a.src + (long long)l * a.src_stride;
+  const int c4 = (threadIdx.x & 15) * 4, r0 = threadIdx.x >> 4;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = r0 + 16 * i;
+    const long long o = ((long long)tap * a.Cb + tcb * 64 + row) * a.Cs + tcs * 64 + c4;
+    const float4 v = *reinterpret_cast<const float4*>(src + o);
+    const float t[4] = {v.x, v.y, v.z, v.w};
+    store_split4(a.up + 3 * (long long)l * a.plane + o, a.plane, t);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) tile[c4 + e][row] = t[e];
+  }
+  if (!a.down) return;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int cid = threadIdx.x + 256 * i, cs = cid >> 3, ch = (cid & 7) * 8;
+    store_split8(a.down + 3 * (long long)l * a.plane + ((long long)tap * a.Cs + tcs * 64 + cs) * a.Cb + tcb * 64 + ch, a.plane,
+                 *reinterpret_cast<const uint4*>(&tile[cs][ch]), *reinterpret_cast<const uint4*>(&tile[cs][ch + 4]));
+  }
+}
+void launch_split_weights(const SplitArgs& a, hipStream_t st) {
+  if (!a.src || !a.up || a.Cb % 64 || a.Cs % 64 || a.src_stride % 4 || a.plane % 8) return launch_fail("split of the weights: channel counts or strides");
+  const long long blocks = (long long)a.L * 16 * (a.Cb / 64) * (a.Cs / 64);
+  if (blocks == 0) return;
+  if (blocks >= (1LL << 31)) return launch_fail("split of the weights: more blocks than a launch can have");
+  hipLaunchKernelGGL(split_weights_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
+}
+
 // One 64 (cb) x 64 (cs) tile of one tap of a convolution weight: the update, the storage-type copy, and - through
-// LDS - the transposed storage-type copy, so that the new weights are read from HBM once.
+// LDS - the transposed storage-type copy, so that the new weights are read from HBM once.  fp32 storage: both copies as bf16 parts (a
+// quarter more to write: twenty 32x32 pairs 665 -> 806 us a step), which spares every GEMM block the split of its columns (8.1 -> 7.1 ms).
 template <typename T>
 __global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a) {
-  constexpr int EPV = 16 / (int)sizeof(T);
   constexpr int TSTRIDE = 64 * (int)sizeof(T) + 16;            // bytes per transposed row (64 cb)
   __shared__ __attribute__((aligned(16))) unsigned char tile[64 * TSTRIDE];
   // a block takes the (tile, model) pairs blockIdx.x, blockIdx.x + gridDim.x, ... of this launch (the launcher's
@@ -942,32 +995,38 @@ __global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a) {
     const long long base = (long long)l * a.P + a.reg_w[r];
     const float bc1 = a.bc[2 * l], bc2 = a.bc[2 * l + 1];
     const int c4 = (threadIdx.x & 15) * 4, r0 = threadIdx.x >> 4;
+    const long long o0 = base + ((long long)tap * Cb + tcb * 64 + r0) * Cs + tcs * 64 + c4;
+    float4 gs[4], ths[4], ms[4], vs[4];      // all loads first: a launch of few tiles is one memory latency, not four
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const long long o = o0 + 16LL * i * Cs;
+      gs[i] = ld_stream(a.g + o);
+      ths[i] = ld_stream(a.theta + o);
+      ms[i] = ld_stream(a.m + o);
+      vs[i] = ld_stream(a.v + o);
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = r0 + 16 * i;                                // cb inside the tile
-      const long long o = base + ((long long)tap * Cb + tcb * 64 + row) * Cs + tcs * 64 + c4;
-      const float4 g = ld_stream(a.g + o);
-      float4 th = ld_stream(a.theta + o);
-      float4 m = ld_stream(a.m + o);
-      float4 v = ld_stream(a.v + o);
+      const long long o = o0 + 16LL * i * Cs;
       float tt[4];
-      adam_update4(a, bc1, bc2, g, th, m, v, tt);
-      st_stream(a.theta + o, th);
-      st_stream(a.m + o, m);
-      st_stream(a.v + o, v);
-      if (a.shadow) store4(static_cast<bf16_t*>(a.shadow) + o, tt);
+      adam_update4(a, bc1, bc2, gs[i], ths[i], ms[i], vs[i], tt);
+      st_stream(a.theta + o, ths[i]);
+      st_stream(a.m + o, ms[i]);
+      st_stream(a.v + o, vs[i]);
+      if constexpr (sizeof(T) == 2) store4(static_cast<bf16_t*>(a.shadow) + o, tt);
+      else store_split4(a.split_u + 2 * (long long)l * a.P + o, a.P, tt);
 #pragma unroll
       for (int e = 0; e < 4; ++e) *reinterpret_cast<T*>(tile + (c4 + e) * TSTRIDE + row * (int)sizeof(T)) = from_float<T>(tt[e]);
     }
     __syncthreads();
-    T* dst = static_cast<T*>(a.shadow_t) + base;
-    constexpr int CPR = 64 / EPV;                                 // 16-byte chunks per transposed row
 #pragma unroll
-    for (int i = 0; i < 64 * CPR / 256; ++i) {
-      const int cid = threadIdx.x + 256 * i;
-      const int cs = cid / CPR, ch = cid - cs * CPR;
-      const uint4 val = *reinterpret_cast<const uint4*>(tile + cs * TSTRIDE + ch * 16);
-      *reinterpret_cast<uint4*>(dst + ((long long)tap * Cs + tcs * 64 + cs) * Cb + tcb * 64 + ch * EPV) = val;
+    for (int i = 0; i < 2; ++i) {                                 // eight values of a transposed row at a time
+      const int cid = threadIdx.x + 256 * i, cs = cid >> 3, ch = (cid & 7) * 8;
+      const uint4* src = reinterpret_cast<const uint4*>(tile + cs * TSTRIDE + ch * (int)sizeof(T));
+      const long long o = ((long long)tap * Cs + tcs * 64 + cs) * Cb + tcb * 64 + ch;
+      if constexpr (sizeof(T) == 2) *reinterpret_cast<uint4*>(static_cast<T*>(a.shadow_t) + base + o) = src[0];
+      else store_split8(a.split_d + 2 * (long long)l * a.P + base + o, a.P, src[0], src[1]);
     }
     __syncthreads();                                              // the tile is rewritten by the next pair
   }
@@ -994,7 +1053,7 @@ bool adam_plan(AdamArgs& a) {
       ++a.ngaps;
     }
     if (r < a.nregions) {
-      if (a.reg_cb[r] % 64 || a.reg_cs[r] % 64 || !a.shadow_t) {
+      if (a.reg_cb[r] % 64 || a.reg_cs[r] % 64 || (a.shadow ? !a.shadow_t : !a.split_u || !a.split_d)) {
         launch_fail("Adam: tiled regions need channel counts that are multiples of 64");
         return false;
       }

@@ -292,3 +292,31 @@ def test_fp32_values_without_a_bf16_split_in_shared_reductions(ctxs, cb, cs, hs,
     offs, d_big, d_w = U.dev(np.array([0, n], np.int32)), U.dev(big), U.dev(np.ascontiguousarray(W.transpose(2, 3, 0, 1)).reshape(16, cs, cb))
     g.op_conv_down(d_big.data_ptr(), d_w.data_ptr(), out.data_ptr(), offs.data_ptr(), 1, n, cb, cs, hs)
     _same_classes(out.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("rows", [0, 64, 128, 256])
+def test_fp32_weights_without_a_bf16_split(ctxs, rows):
+    """The weights' parts are made once and not where they are multiplied: weights beyond the parts' range must give what fp32 arithmetic
+    gives (finite values and, with activations above one, infinities), in their columns and nowhere else, in both layouts."""
+    torch = U.torch_mod()
+    g = ctxs[binding.FP32]
+    g.op_tile_rows(rows)
+    cb, cs, hs, n = 64, 128, 4, 40
+    rng = np.random.default_rng(14)
+    big = rng.normal(0, 1, (n, 2 * hs, 2 * hs, cb)).astype(np.float32)
+    small = rng.normal(0, 1, (n, hs, hs, cs)).astype(np.float32)
+    W = rng.normal(0, 0.05, (cs, cb, 4, 4)).astype(np.float32)
+    W[3, 5, 1, 2], W[70, 0, 0, 0], W[127, 63, 3, 3] = 3.3e38, 1e33, -3.3e38
+    offs = U.dev(np.array([0, n], np.int32))
+    with np.errstate(all="ignore"):
+        down = O.conv2d(big.transpose(0, 3, 1, 2), W, None).transpose(0, 2, 3, 1)
+        up = O.conv_transpose2d(small.transpose(0, 3, 1, 2), W, None).transpose(0, 2, 3, 1)
+    d_big, d_small = U.dev(big), U.dev(small)
+    d_wd, d_wu = U.dev(np.ascontiguousarray(W.transpose(2, 3, 0, 1))), U.dev(np.ascontiguousarray(W.transpose(2, 3, 1, 0)))
+    out = torch.zeros((n, hs, hs, cs), device="cuda")
+    g.op_conv_down(d_big.data_ptr(), d_wd.data_ptr(), out.data_ptr(), offs.data_ptr(), 1, n, cb, cs, hs)
+    _same_classes(out.cpu().numpy(), down)
+    out = torch.zeros((n, 2 * hs, 2 * hs, cb), device="cuda")
+    g.op_conv_up(d_small.data_ptr(), d_wu.data_ptr(), out.data_ptr(), offs.data_ptr(), 1, n, cb, cs, hs)
+    g.op_tile_rows(0)
+    _same_classes(out.cpu().numpy(), up)
