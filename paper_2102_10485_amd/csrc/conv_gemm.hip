@@ -36,9 +36,14 @@ namespace gan {
 // Block tile BM x BN computed by WM x WN waves, each (TM*32) x (TN*32); forward kernel: KB bytes of K per LDS row,
 // NST buffers.  KS (forward kernel): groups of WM x WN waves that share the tile's reduction, chunk c going to group c % KS; each has a
 // ring of buffers of its own, and their sums are added at the end.
-template <int BM_, int BN_, int WM_, int WN_, int KB_ = 128, int NST_ = 2, int KS_ = 1>
+// SLOTS > 0, SHARE (forward kernel, MODE_UP): the two taps of a filter row gather the same pixels one column apart, and share one stage of
+// them; NST buffers of weights, two of SLOTS pixels.
+template <int BM_, int BN_, int WM_, int WN_, int KB_ = 128, int NST_ = 2, int KS_ = 1, int SLOTS_ = 0>
 struct Tile {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, KB = KB_, NST = NST_, KS = KS_;
+  static constexpr bool SHARE = SLOTS_ > 0;
+  // An output pixel's one tap reads the pixel that its neighbour's other tap reads, so a stage holds H + 1 pixels for every H rows of the tile.
+  static constexpr int SLOTS = SLOTS_;
   static constexpr int NT = 64 * WM_ * WN_;          // threads of a group
   static constexpr int TM = BM_ / (32 * WM_), TN = BN_ / (32 * WN_);
   static constexpr int CPR = KB_ / 16;               // 16-byte chunks per LDS row
@@ -58,6 +63,14 @@ template <> struct FwdTiles<bf16_t> {
                                                  // short, and what a block waits for before it can multiply weighs more
   typedef Tile<64, 64, 2, 2, 128, 2> Tiny;       // 256 threads, wave tile 32 x 32, 32 KiB of LDS: workloads so small that
                                                  // the larger tiles would leave most of the chip without a block
+  // MODE_UP with shared pixels, for sides from 4 up (share_fits): the loop lives on the CU's load path, and a pair of taps brings in half the
+  // pixels and a bit.  us: 256 -> 128 channels, side 8, 6400 samples 433 -> 413; 128 -> 64, side 16, 1024 samples 106 -> 91; 512 -> 256, side 4,
+  // 6400 samples 372 -> 365.  MODE_DOWN gained nothing (256x256 401 and 402, 256x128 78.6 and 79.3, 256x64 77 and 78), nor did side 7, whose
+  // runs need padding against bank conflicts (57.7 and 58.8).
+  typedef Tile<256, 256, 2, 4, 128, 2, 1, 320> BigShare;       // 144 KiB
+  typedef Tile<256, 128, 4, 2, 64, 3, 1, 320> MidShare;        // 64 KiB
+  typedef Tile<128, 128, 2, 2, 128, 2, 1, 160> SmallShare;     // 72 KiB
+  typedef Tile<256, 64, 4, 1, 64, 3, 1, 320> NarrowShare;      // 52 KiB, three blocks per CU
   typedef Tile<64, 64, 2, 2, 128, 2, 2> Pair;    // Tiny with two groups of waves on its reduction: 512 threads, 64 KiB
   typedef Tile<32, 64, 1, 2, 128, 3, 4> Deep;    // 32 x 64 with four groups: 512 threads, 144 KiB, six or more chunks on their way.  Both
                                                  // for launches that a CU gets a block or two of, whose time is that of one block: see TILES
@@ -80,6 +93,20 @@ template <> struct FwdTiles<float> {
   typedef Tile<64, 64, 2, 2, 128, 2, 2> Pair;    // 80 KiB
   typedef Tile<32, 64, 1, 2, 128, 2, 4> Deep;    // 128 KiB
 };
+
+// SHARE: the xor of the 16-byte chunks of the pixel p = 0 .. H of a run of H columns.  Sixteen rows that are read together lie in G = 256 / KB
+// places of the bank period; what a read of them must not do is meet twice in a place with the same xor, be it the rows' first pixels
+// (p = 0 .. H - 1 of each run) or their second ones (1 .. H).  With sides that are multiples of G the pixels of one place have H / G values in turn,
+// which p = 0 and p = H, never read together, share.  (The usual xor of the slot number doubled the time of the reads.)
+__device__ inline int share_xor(int H, int G, int run, int p) {
+  const int per = H / G, k = p / G;
+  return run * per + (k >= per ? k - per : k);
+}
+// whether the kernel can (side, and the slots that a tile of BM rows reads; tiles start at multiples of BM rows)
+template <typename TL> static bool share_fits(int H) {
+  const int runs = (TL::BM - 1 + (TL::BM % H ? H - 1 : 0)) / H;
+  return H % (256 / TL::KB) == 0 && TL::BM + runs + 1 <= TL::SLOTS;
+}
 
 // What a tile is to the chooser: its shape, the row blocks with statistics of their own, the blocks of it that a CU holds, and
 // the rate a full chip of them reaches against the fastest one of the storage type (0: the storage type has no such tile).  The bf16
@@ -287,6 +314,36 @@ __device__ __forceinline__ void tile_mma_fwd(floatx16 (&acc)[TM][TN], const unsi
   });
 }
 
+// The same with the address of every fragment's row given (SHARE).
+template <typename T, int TM, int TN, int KB>
+__device__ __forceinline__ void tile_mma_rows(floatx16 (&acc)[TM][TN], const unsigned (&arow)[TM], unsigned a_stage, const unsigned char* Bs, int wn,
+                                              int lane) {
+  const int r = lane & 31, h = lane >> 5;
+  constexpr int NV = KB / 32;
+  const unsigned b0 = (unsigned)(uintptr_t)Bs + (wn * TN * 32 + r) * KB + ((h ^ fwd_swz<KB>(r)) << 4);
+  unsigned a0[TM];
+#pragma unroll
+  for (int t = 0; t < TM; ++t) a0[t] = arow[t] + a_stage;
+  u32x4 a[2][TM], b[2][TN];
+  auto fetch = [&](auto vs, auto set) __attribute__((always_inline)) {
+    const unsigned bb = b0 ^ (vs.value << 5);
+    static_for<0, TM>([&](auto t) __attribute__((always_inline)) { lds_read16<0>(a[set.value][t.value], a0[t.value] ^ (vs.value << 5)); });
+    static_for<0, TN>([&](auto t) __attribute__((always_inline)) { lds_read16<t.value * 32 * KB>(b[set.value][t.value], bb); });
+  };
+  fetch(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+  static_for<0, NV>([&](auto vs) __attribute__((always_inline)) {
+    constexpr int cur = vs.value & 1;
+    if constexpr (vs.value + 1 < NV) {
+      fetch(std::integral_constant<int, vs.value + 1>{}, std::integral_constant<int, cur ^ 1>{});
+      lds_wait<TM + TN>(a[cur], b[cur]);
+    } else {
+      lds_wait<0>(a[cur], b[cur]);
+    }
+    mma_step(acc, a[cur], b[cur], T());
+    __builtin_amdgcn_sched_barrier(0);       // keep these MFMAs in front of the next K-step's wait
+  });
+}
+
 // fp32 through splits: two K-steps (16 values of K per row) are one step here; lane half h supplies values 8 h .. 8 h + 7 of the step.
 // PRE: the columns are split already, three planes of BN rows of KB / 2 bytes each (swizzled like rows of a bf16 tile).
 template <int TM, int TN, int KB, bool PRE, int BN>
@@ -390,7 +447,11 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   // fp32 convolutions get their weights split already (launch_split_weights): three bf16 planes
   constexpr bool PRE = sizeof(T) == 4 && MODE != MODE_DENSE;
   constexpr int KBB = PRE ? KB / 2 * 3 : KB;                                   // bytes of a column in LDS
-  constexpr int RING = NST * (BM * KB + BN * KBB);                             // of one group
+  constexpr bool SHARE = TL::SHARE;
+  static_assert(!SHARE || (sizeof(T) == 2 && MODE == MODE_UP && KS == 1), "shared pixels: bf16, MODE_UP");
+  constexpr int SLOTS = TL::SLOTS;
+  constexpr int A_RING = SHARE ? 2 * SLOTS * KB : NST * BM * KB;               // of one group
+  constexpr int RING = A_RING + NST * BN * KBB;
   constexpr int SMEM_RING = KS * RING;
   constexpr int ROWTAB = EPI == EPI_LABEL_LRELU ? BM * 12 : BM * 8;            // see the epilogue
   constexpr int SMEM_EPI = ROWTAB + (TL::NT / 64) * 32 * (TN * 32 * 4 + 16);
@@ -398,7 +459,7 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
   const int kgrp = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / TL::NT);      // this wave's share of the reduction
   unsigned char* const As = smem + kgrp * RING;        // buffer s at As + s * BM * KB
-  unsigned char* const Bs = As + NST * BM * KB;        // buffer s at Bs + s * BN * KBB
+  unsigned char* const Bs = As + A_RING;               // buffer s at Bs + s * BN * KBB
   constexpr int BK = KB / (int)sizeof(T);              // elements of K per chunk
   constexpr int LINES = 128 / KB;                      // chunks per 128-byte line
   constexpr int EPV = 16 / (int)sizeof(T);
@@ -492,8 +553,42 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   constexpr int CPR = TL::CPR;
   const int row0 = tid / CPR;
   const int chunk = (tid % CPR) ^ fwd_swz<KB>(row0);
-  unsigned apix[PA], bcol[PRE ? PP : PB];
-  int outside[PA];
+  constexpr int PS = SHARE ? (SLOTS + RPP - 1) / RPP : PA;       // passes over the pixels
+  unsigned apix[PS], bcol[PRE ? PP : PB];
+  int outside[PS];
+  // SHARE: slot t of a stage is pixel p = u % (H + 1), column p - 1 + px, of run u / (H + 1) of H rows, u = t + x0, the first run being the
+  // one that the tile's first row lies in, x0 columns behind its start.  Tile row r reads the slots p = x (tap b = 1) and x + 1 (b = 0).
+  // Per slot the filter rows whose pixel is outside the map.
+  constexpr int G = 256 / KB;
+  const int q0 = SHARE ? m0 / Hr : 0, x0 = m0 - q0 * Hr;
+  const int need = BM + (BM - 1 + x0) / Hr + 1;                  // slots that the tile's rows read
+  unsigned arow[2][TM];
+  if constexpr (SHARE) {
+    const float inv_run = 1.f / (float)(Hr + 1), inv_n = 1.f / (float)nsamp;
+#pragma unroll
+    for (int i = 0; i < PS; ++i) {
+      const int u = row0 + RPP * i + x0, run = (int)(((float)u + 0.5f) * inv_run), p_ = u - run * (Hr + 1);      // (exact: u < 1024)
+      const int q = q0 + run;
+      int y = (int)((float)q * inv_n);
+      y -= y * nsamp > q ? 1 : 0;
+      y += (y + 1) * nsamp <= q ? 1 : 0;
+      const int n = q - y * nsamp;
+      outside[i] = -1;
+      if (y < Hr && (unsigned)(p_ + px - 1) < (unsigned)Hin)
+        outside[i] = ~(((unsigned)(y + py) < (unsigned)Hin ? 1 : 0) | ((unsigned)(y + py - 1) < (unsigned)Hin ? 2 : 0));
+      const int chunk_ = (tid % CPR) ^ (share_xor(Hr, G, run, p_) & (CPR - 1));
+      apix[i] = (unsigned)((((n * Hin + y) * Hin + p_) * C + chunk_ * EPV) * SZ);
+    }
+#pragma unroll
+    for (int t = 0; t < TM; ++t) {
+      const int v = x0 + wm * TM * 32 + t * 32 + (lane & 31), run = v / Hr, x = v - run * Hr;
+#pragma unroll
+      for (int sft = 0; sft < 2; ++sft) {
+        const int slot = run * (Hr + 1) + x + sft - x0;
+        arow[sft][t] = (unsigned)(uintptr_t)As + slot * KB + (((lane >> 5) ^ (share_xor(Hr, G, run, x + sft) & (CPR - 1))) << 4);
+      }
+    }
+  } else
 #pragma unroll
   for (int i = 0; i < PA; ++i) {
     const int r = m0 + row0 + RPP * i;
@@ -651,7 +746,79 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
       __syncthreads();
     }
   };
-  if constexpr (SZ == 4) {
+  // SHARE: stages of pixels and, two to a stage, chunks of weights.  Stage order, fastest first: the halves of a 128-byte line (KB = 64), the
+  // filter rows, which read the same pixels shifted by a row, the channel line.  The next stage's pixels are requested at the start of a stage, its
+  // weights NST - 1 chunks ahead.
+  struct Stage { int part = 0, j = 0, line = 0; };
+  const int frows = cnt_lo >> 1;                       // filter rows a = 0, 1 (y + py - a), or the one that is inside the map
+  auto stage_row = [&](const Stage& g) { return frows == 2 ? g.j : (first_gone ? 1 : 0); };
+  auto stage_next = [&](Stage& g) {
+    if (LINES == 2) {
+      g.part ^= 1;
+      if (g.part) return;
+    }
+    if (++g.j < frows) return;
+    g.j = 0;
+    ++g.line;
+  };
+  auto load_pixels = [&](const Stage& g, int buf) {
+    const int a = stage_row(g);
+    const unsigned off = (py - a + 1) * row_bytes + px * px_bytes + g.line * 128 + g.part * KB;
+    const unsigned dst = lds0 + buf * SLOTS * KB + wave * 1024;
+#pragma unroll
+    for (int i = 0; i < PS; ++i)
+      if (i < PA || RPP * i + wave * (1024 / KB) < need)          // (a wave's copy fills 1024 / KB slots; the last passes may have none)
+        load16_to_lds(a_rsrc, apix[i] | (unsigned)__builtin_amdgcn_sbfe(outside[i], a, 1), off, dst + i * RPP * KB);
+  };
+  auto load_weights = [&](const Stage& g, int sft, int buf) {
+    const int tap = (2 * stage_row(g) + 1 - py) * 4 + 2 * (1 - sft) + 1 - px;
+    const unsigned off = tap * wtap_bytes + g.line * 128 + g.part * KB;
+    const unsigned dst = lds0 + A_RING + buf * BN * KBB + wave * 1024;
+#pragma unroll
+    for (int i = 0; i < PB; ++i) load16_to_lds(w_rsrc, bcol[i], off, dst + i * RPP * KB);
+  };
+  auto share_loop = [&]() __attribute__((always_inline)) {
+    clear_acc(acc);
+    const int stages = nk >> 1;
+    Stage ga, gb;                                                 // of the next pixels and of the next weights to load
+    int sb = 0, b_load = 0, b_cur = 0;
+    auto next_weights = [&]() {
+      load_weights(gb, sb, b_load);
+      b_load = b_load == NST - 1 ? 0 : b_load + 1;
+      sb ^= 1;
+      if (!sb) stage_next(gb);
+    };
+    load_pixels(ga, 0);
+    stage_next(ga);
+    for (int c = 0; c < NST - 1; ++c) next_weights();             // (a stage has two)
+    wait_vm<0>();
+    __syncthreads();
+    for (int i = 0; i < stages; ++i) {
+      const bool more = i + 1 < stages;
+      const unsigned a_stage = (i & 1) * (SLOTS * KB);
+      // first tap.  More stages: two chunks of weights at least are not loaded yet
+      if (NST == 2 || more) next_weights();
+      if (more) {
+        load_pixels(ga, (i + 1) & 1);
+        stage_next(ga);
+      }
+      tile_mma_rows<T, TM, TN, KB>(acc, arow[0], a_stage, Bs + b_cur * BN * KBB, wn, lane);
+      b_cur = b_cur == NST - 1 ? 0 : b_cur + 1;
+      // the second tap's weights have landed; what was requested after them may stay in flight: later weights and the pixels, PA or more copies
+      if (more) wait_vm<(NST - 2) * PB + PA>(); else wait_vm<0>();
+      __syncthreads();
+      if (more) next_weights();
+      tile_mma_rows<T, TM, TN, KB>(acc, arow[1], a_stage, Bs + b_cur * BN * KBB, wn, lane);
+      b_cur = b_cur == NST - 1 ? 0 : b_cur + 1;
+      // the next stage's pixels and first weights have landed
+      if (more && NST > 2) wait_vm<PB>(); else wait_vm<0>();
+      __syncthreads();
+    }
+  };
+  if constexpr (SHARE) {
+    static_assert(NST == 2 || NST == 3, "the waits count for these");
+    share_loop();
+  } else if constexpr (SZ == 4) {
     k_loop(std::true_type{});
     add_acc(acc, low);
     if (block_any<TL::NT / 64 * KS>(not_finite(acc), smem, kgrp * (TL::NT / 64) + wave)) k_loop(std::false_type{});
@@ -877,6 +1044,19 @@ static void launch_one(ConvArgs a, hipStream_t st) {
 template <typename T, int MODE, int EPI>
 static void launch_wide(const ConvArgs& a, hipStream_t st) {
   typedef FwdTiles<T> Tiles;
+  if constexpr (sizeof(T) == 2 && MODE == MODE_UP) {
+    bool done = false;
+    const auto shared = [&](ConvTile id, auto tile) {
+      if (done || a.tile != id || !share_fits<decltype(tile)>(a.Hr)) return;
+      launch_one<T, MODE, EPI, decltype(tile)>(a, st);
+      done = true;
+    };
+    shared(TILE_BIG, typename Tiles::BigShare());
+    shared(TILE_MID, typename Tiles::MidShare());
+    shared(TILE_SMALL, typename Tiles::SmallShare());
+    shared(TILE_NARROW, typename Tiles::NarrowShare());
+    if (done) return;
+  }
   if constexpr (sizeof(T) == 2) {
     if (a.tile == TILE_BIG) return launch_one<T, MODE, EPI, typename Tiles::Big>(a, st);
     if (a.tile == TILE_MID) return launch_one<T, MODE, EPI, typename Tiles::Mid>(a, st);

@@ -320,3 +320,26 @@ def test_fp32_weights_without_a_bf16_split(ctxs, rows):
     g.op_conv_up(d_small.data_ptr(), d_wu.data_ptr(), out.data_ptr(), offs.data_ptr(), 1, n, cb, cs, hs)
     g.op_tile_rows(0)
     _same_classes(out.cpu().numpy(), up)
+
+
+@pytest.mark.parametrize("tile_rows", [128, 256])
+@pytest.mark.parametrize("cb,cs,hs,groups", [(128, 64, 12, [3, 0, 2]), (64, 64, 20, [2, 1]), (256, 64, 12, [4]), (64, 128, 28, [1, 1]), (256, 64, 5, [9])])
+def test_conv_up_shared_pixels(ctxs, cb, cs, hs, groups, tile_rows):
+    """Taps that share a stage of gathered pixels: sides that are no power of two, so that tiles start and end inside a row, and one side
+    that the shared form does not take."""
+    torch = U.torch_mod()
+    g = ctxs[binding.BF16]
+    g.op_tile_rows(tile_rows)
+    rng = np.random.default_rng(cb + hs)
+    n, G = int(sum(groups)), len(groups)
+    offs = np.concatenate([[0], np.cumsum(groups)]).astype(np.int32)
+    W = U.round_to(rng.normal(0, 0.05, (G, cs, cb, 4, 4)), True)
+    small = U.round_to(rng.normal(0, 1, (n, cs, hs, hs)), True)
+    d_offs, d_small = U.dev(offs), U.dev(U.pack(small.transpose(0, 2, 3, 1), True))
+    d_w = U.dev(U.pack(np.ascontiguousarray(W.transpose(0, 3, 4, 2, 1)).reshape(G, 16, cb, cs), True))
+    out = torch.zeros(n * 4 * hs * hs * cb, dtype=torch.int16, device="cuda")
+    g.op_conv_up(d_small.data_ptr(), d_w.data_ptr(), out.data_ptr(), d_offs.data_ptr(), G, n, cb, cs, hs)
+    g.op_tile_rows(0)
+    got = U.unpack(out, True, (n, 2 * hs, 2 * hs, cb)).transpose(0, 3, 1, 2)
+    ref = np.concatenate([O.conv_transpose2d(small[offs[i]:offs[i + 1]], W[i], None) for i in range(G) if groups[i]])
+    assert np.max(np.abs(got - ref)) <= tolerance(binding.BF16) * np.max(np.abs(ref))
