@@ -699,7 +699,7 @@ NormArgs norm_args(gan_ctx* c, Net& net, int C, int rps, long long gamma, long l
 // BatchNorm with batch statistics + activation: x -> y (with running statistics both are part of the GEMM: EPI_BN)
 // gemm_mode / gemm_rps describe the GEMM that produced x and left per-tile column sums in c->stat_partial
 template <typename T>
-void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool update_running, int gemm_mode, int gemm_rps, int col_groups = 1) {
+void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool update_running, int gemm_mode, int gemm_rps, int col_groups = 1) {      // y NULL: the statistics only
   a.x = x; a.y = y;
   const double elems = (double)a.n * a.nseg * a.rps * a.C;
   {
@@ -709,6 +709,7 @@ void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool update_runn
     launch_bn_stats_from_partial(a, c->stat_partial, tpre_of(c, gemm_rps, tr), ub_tiles(c, a.n, gemm_rps, tr), gemm_phases, col_groups, tr,
                                  gemm_rps, conv_stat_split((int)sizeof(T), tile, gemm_mode), c->st);
   }
+  if (!y) return;
   Scope s(c, "bn_apply", 0, 2 * elems * sizeof(T));
   launch_bn_apply<T>(a, c->st);
 }
@@ -971,6 +972,16 @@ void bn_forward_direct(gan_ctx* c, NormArgs a, const void* x, void* y, float eps
   launch_bn_apply<T>(a, c->st);
 }
 
+// G's last convolution reads the block in front of it before its BatchNorm and activation
+void paper_last_norm(gan_ctx* c, Conv3Args& a) {
+  const Net& G = c->G;
+  const int last = (int)G.conv.size() - 1;
+  const ConvLayer& cl = G.conv[last - 1];
+  a.in = c->gpre[last];
+  a.bn_mean = c->g_mean[last]; a.bn_rstd = c->g_rstd[last]; a.bn_gamma = G.theta + cl.gamma; a.bn_beta = G.theta + cl.beta;
+  a.bn_pstride = G.P; a.bn_slope = c->cfg.leaky_slope;
+}
+
 template <typename T>
 void paper_g_forward(gan_ctx* c, int n, bool use_running, bool update_running, float* user = nullptr) {
   Net& G = c->G;
@@ -994,7 +1005,8 @@ void paper_g_forward(gan_ctx* c, int n, bool use_running, bool update_running, f
                                     c->g_rstd[i + 1], c->g_sums[i + 1], 0, 1, n, f.leaky_slope);
     conv_call<T>(c, "gemm_up", MODE_UP, use_running ? EPI_BN : EPI_NONE, c->gact[i], layer_weights(c, G, cl, true),
                  use_running ? c->gact[i + 1] : c->gpre[i + 1], nullptr, cl.Cs, cl.Cb, cl.Hs, cl.Hs, 0, 1, n, 0, -1.0, !use_running, &a);
-    if (!use_running) bn_forward<T>(c, a, c->gpre[i + 1], c->gact[i + 1], update_running, MODE_UP, cl.Hs * cl.Hs);
+    // (the last block's BatchNorm and activation are part of the kernels that read its output)
+    if (!use_running) bn_forward<T>(c, a, c->gpre[i + 1], i + 2 < nl ? c->gact[i + 1] : nullptr, update_running, MODE_UP, cl.Hs * cl.Hs);
   }
   const ConvLayer& cl = G.conv[nl - 1];                // Conv k3 s1 p1 (+bias) -> tanh, into the fake half of D's image buffer or the caller's
   Conv3Args a;
@@ -1002,6 +1014,7 @@ void paper_g_forward(gan_ctx* c, int n, bool use_running, bool update_running, f
   a.in = c->gact[nl - 1]; a.out = c->xd; a.w = G.theta + cl.w; a.w_stride = G.P; a.bias = G.theta + cl.bias; a.bias_stride = G.P;
   a.offs = c->rb.offs; a.sample_model = c->rb.sample_model; a.L = c->L; a.n = n; a.H = cl.Hs; a.Cin = cl.Cs; a.CO = cl.Cb;
   a.out_seg = 1; a.seg_samples = n; a.user = user; a.perm = c->rb.perm;
+  if (!use_running) paper_last_norm(c, a);
   Scope s(c, "conv3_img", 2.0 * n * cl.Hs * cl.Hs * 9 * cl.Cs * cl.Cb, sizeof(T) * (double)n * cl.Hs * cl.Hs * (cl.Cs + cl.Cb));
   launch_conv3_fwd<T>(a, c->st);
 }
@@ -1093,23 +1106,37 @@ void paper_g_backward(gan_ctx* c, int n) {
   {
     Conv3Args a;
     memset(&a, 0, sizeof(a));
-    a.in = c->gact[nl - 1]; a.dout = c->dimg; a.din = c->bufA; a.w = G.theta + last.w; a.w_stride = G.P;
+    a.dout = c->dimg; a.din = c->bufB; a.w = G.theta + last.w; a.w_stride = G.P;
     a.offs = c->rb.offs; a.sample_model = c->rb.sample_model; a.L = c->L; a.n = n; a.H = last.Hs; a.Cin = last.Cs; a.CO = last.Cb;
     a.out_seg = 1; a.seg_samples = n;
+    paper_last_norm(c, a);
     { Scope s(c, "conv3_img_wgrad", 2.0 * n * last.Hs * last.Hs * 9 * last.Cs * last.Cb, sizeof(T) * (double)n * last.Hs * last.Hs * (last.Cs + last.Cb));
       launch_conv3_wgrad<T>(a, c->c3_part, G.g + last.w, G.P, c->st); }
     ImgBiasArgs b;
     b.img = dlast; b.partial = c->bias_partial; b.dbias = G.g + last.bias; b.pstride = G.P; b.offs = c->rb.offs;
     b.L = c->L; b.CB = last.Cb; b.HW = last.Hs * last.Hs;
     launch_img_bias_grad<T>(b, c->st);
-    Scope s(c, "conv3_img_dgrad", 2.0 * n * last.Hs * last.Hs * 9 * last.Cs * last.Cb, sizeof(T) * (double)n * last.Hs * last.Hs * (last.Cs + last.Cb));
+    // the data gradient twice, for the sums of BatchNorm's backward pass and for its result (bufB)
+    const ConvLayer& cl = G.conv[nl - 2];
+    NormArgs na = norm_args<T>(c, G, cl.Cb, 4 * cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->g_mean[nl - 1], c->g_var[nl - 1], c->g_rstd[nl - 1],
+                               c->g_sums[nl - 1], 0, 1, n, f.leaky_slope);
+    na.param_grads = 1;
+    a.bn_part = c->stat_partial;
+    const double flops = 2.0 * n * last.Hs * last.Hs * 9 * last.Cs * last.Cb, elems = (double)n * last.Hs * last.Hs;
+    {
+      Scope s(c, "conv3_img_dgrad_sums", flops, sizeof(T) * elems * (last.Cs + last.Cb));
+      launch_conv3_dgrad<T>(a, c->st);
+      launch_bn_bwd_final(na, c->rb.offs, n, c->stat_partial, c->st);
+    }
+    a.bn_sums = c->g_sums[nl - 1];
+    Scope s(c, "conv3_img_dgrad", flops, sizeof(T) * elems * (2 * last.Cs + last.Cb));
     launch_conv3_dgrad<T>(a, c->st);
   }
   for (int i = nl - 2; i >= 0; --i) {
     const ConvLayer& cl = G.conv[i];
     NormArgs na = norm_args<T>(c, G, cl.Cb, 4 * cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->g_mean[i + 1], c->g_var[i + 1],
                                c->g_rstd[i + 1], c->g_sums[i + 1], 0, 1, n, f.leaky_slope);
-    bn_backward<T>(c, na, c->gpre[i + 1], c->bufA, c->bufB, true);
+    if (i < nl - 2) bn_backward<T>(c, na, c->gpre[i + 1], c->bufA, c->bufB, true);
     const long long per = (long long)16 * cl.Cb * cl.Cs;
     wgrad_call<T>(c, "gemm_wgrad", c->bufB, c->gact[i], c->dw4, per, cl.Cb, cl.Cs, cl.Hs, 16, 1, n);
     launch_dw4_to_dw3(c->dw4, G.g + cl.w, c->L, cl.Cb, cl.Cs, c->st, per, G.P);
@@ -1411,6 +1438,7 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
         mx = v > mx ? v : mx;
       }
     }
+    if (c->paper) mx = std::max(mx, (size_t)NB * c->G.conv.back().Cs);        // the same from G's last layer: samples x channels x 2
     ok = ok && dev_alloc(c, (void**)&c->stat_partial, mx * 2 * 4);
   }
   ok = ok && dev_alloc(c, &c->bufA, (size_t)2 * NB * max_act * es) && dev_alloc(c, &c->bufB, (size_t)2 * NB * max_act * es) &&

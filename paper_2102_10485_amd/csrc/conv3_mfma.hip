@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -40,6 +41,43 @@ __device__ inline void c3_mma(c3_f16& acc, const uint4& a, const uint4& b, float
 // (e / 4) * 8 + h * 4 + e % 4 of column r
 __device__ inline int c3_acc_row(int e, int h) { return (e >> 2) * 8 + h * 4 + (e & 3); }
 
+// BatchNorm (batch statistics) and activation of 16 bytes of consecutive channels of the feature tensor, for the kernels that read it as it is
+// in front of them: the features are then never stored (a read and a write of the largest tensor of the step), and the pass rounds as the stored
+// tensor did.  6400 samples of 32 x 32 x 64, bf16: the pass's 345 us are gone, forward 225 -> 317 and weight gradient 220 -> 315, both now
+// bound by their vector instructions.
+template <typename T> struct C3Norm {
+  static constexpr int EPV = 16 / (int)sizeof(T);
+  float mu[EPV], rs[EPV], ga[EPV], be[EPV], sc[EPV], slope;
+  __device__ void load(const Conv3Args& a, int l, int ch) {      // ch: which 16 bytes of a pixel
+    const long long po = (long long)l * a.bn_pstride + ch * EPV, so = (long long)l * a.Cin + ch * EPV;
+    slope = a.bn_slope;
+#pragma unroll
+    for (int k = 0; k < EPV; ++k) {
+      mu[k] = a.bn_mean[so + k];
+      rs[k] = a.bn_rstd[so + k];
+      ga[k] = a.bn_gamma[po + k];
+      be[k] = a.bn_beta[po + k];
+      sc[k] = ga[k] * rs[k];
+    }
+  }
+  __device__ uint4 apply(const uint4& raw) const {
+    uint4 out;
+    const T* x = reinterpret_cast<const T*>(&raw);
+    float v[EPV];
+#pragma unroll
+    for (int k = 0; k < EPV; ++k) {
+      const float u = (to_float(x[k]) - mu[k]) * sc[k] + be[k];
+      v[k] = u > 0.f ? u : u * slope;
+    }
+    pack(v, out);
+    return out;
+  }
+  __device__ static void pack(const float (&v)[EPV], uint4& out) {
+    if constexpr (sizeof(T) == 2) out = make_uint4(pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3]), pack2_bf16(v[4], v[5]), pack2_bf16(v[6], v[7]));
+    else out = make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
+  }
+};
+
 constexpr int C3_TS = 8;                 // patch side
 constexpr int C3_HALO = C3_TS + 2;
 constexpr int C3_MAXCO = 4;
@@ -53,7 +91,8 @@ constexpr int C3_MAX_SPLITS = 32;
 // neighbours' entries, one per tap.  (Multiplying per output pixel instead, with K = (neighbour, channel), needs 4.5
 // times the MFMAs for the same result and was bound by them and by the partial sums' way through LDS.)
 constexpr int C3_RTS = 128 * 4 + 16;     // bytes per row of the transposed product: 128 halo-pixel slots of fp32
-template <typename T, int CIN>
+// NORM: the features are the input's BatchNorm and activation, applied on the way into LDS (a thread's channels are the same in every copy).
+template <typename T, int CIN, bool NORM>
 __global__ __launch_bounds__(256) void conv3_fwd_kernel(Conv3Args a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   constexpr int SZ = (int)sizeof(T);
@@ -74,15 +113,22 @@ __global__ __launch_bounds__(256) void conv3_fwd_kernel(Conv3Args a) {
   T* out = static_cast<T*>(a.out) + ((long long)a.out_seg * a.seg_samples + j) * H * H * CO;
   constexpr int NF = (C3_HALO * C3_HALO * cpr + 255) / 256;
   uint4 fv[NF];
+  unsigned inside = 0;                                         // the copies that lie inside the image
+  static_assert(256 % cpr == 0 && NF <= 32, "a thread's channels");
+  C3Norm<T> norm;
+  if constexpr (NORM) norm.load(a, l, tid % cpr);
   auto fetch = [&](int tile) {
     const int y0 = (tile / tiles) * C3_TS, x0 = (tile % tiles) * C3_TS;
+    inside = 0;
 #pragma unroll
     for (int k = 0; k < NF; ++k) {
       const int i = tid + 256 * k;
       const int hr = i / cpr, ch = i - hr * cpr;
       const int y = y0 - 1 + hr / C3_HALO, x = x0 - 1 + hr % C3_HALO;
       fv[k] = make_uint4(0, 0, 0, 0);
-      if (i < C3_HALO * C3_HALO * cpr && (unsigned)y < (unsigned)H && (unsigned)x < (unsigned)H)
+      const bool in_image = i < C3_HALO * C3_HALO * cpr && (unsigned)y < (unsigned)H && (unsigned)x < (unsigned)H;
+      inside |= (in_image ? 1u : 0u) << k;
+      if (in_image)
         fv[k] = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(in + ((long long)y * H + x) * CIN) + ch * 16);
     }
   };
@@ -110,6 +156,7 @@ __global__ __launch_bounds__(256) void conv3_fwd_kernel(Conv3Args a) {
     for (int k = 0; k < NF; ++k) {
       const int i = tid + 256 * k;
       const int hr = i / cpr, ch = i - hr * cpr;
+      if (NORM && (inside >> k & 1)) fv[k] = norm.apply(fv[k]);
       if (i < C3_HALO * C3_HALO * cpr) *reinterpret_cast<uint4*>(Fl + hr * rowB + ch * 16) = fv[k];
     }
     if (tile + 1 < tiles * tiles) fetch(tile + 1);
@@ -176,7 +223,12 @@ __device__ inline T c3_patch_value(const T* D, int q, int tap, int co) {
 // ---- data gradient ---------------------------------------------------------------------------------------------------
 // One block per sample, the weights (transposed, rounded to T) in LDS once, the next patch's dout halo on its way while
 // the current patch is multiplied.
-template <typename T, int CIN>
+// With BatchNorm and activation between the feature tensor x and this layer, the gradient is not stored (it takes two MFMA steps to make)
+// but made twice: C3_SUMS reads x and leaves the sample's sums of g and g xhat for BatchNorm's backward pass, g being the gradient times the
+// activation's derivative; C3_APPLY reads x and writes the gradient with respect to it.  6400 samples of 32 x 32 x 64, bf16: 263 us
+// and 376, where storing it (233), reducing it (275) and applying it (476) took 984.
+enum { C3_PLAIN = 0, C3_SUMS = 1, C3_APPLY = 2 };
+template <typename T, int CIN, int WHAT>
 __global__ __launch_bounds__(256) void conv3_dgrad_kernel(Conv3Args a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   constexpr int SZ = (int)sizeof(T);
@@ -224,9 +276,36 @@ __global__ __launch_bounds__(256) void conv3_dgrad_kernel(Conv3Args a) {
   const int r = lane & 31, h = lane >> 5;
   const int mt = wave & 1;
   const int ksteps = (9 * CO * SZ + 31) / 32;
-  constexpr int cpr = CIN * SZ / 16;
+  constexpr int cpr = CIN * SZ / 16, EPV = 16 / SZ, NX = 64 * cpr / 256;
+  static_assert(64 * cpr % 256 == 0 && 256 % cpr == 0, "a thread's channels");
+  C3Norm<T> norm;
+  float s1[EPV], s2[EPV];                                      // C3_SUMS: the sums ; C3_APPLY: the model's means of them
+  if constexpr (WHAT != C3_PLAIN) {
+    norm.load(a, l, tid % cpr);
+    const float inv = 1.0f / ((float)(a.offs[l + 1] - a.offs[l]) * (float)(H * H));
+#pragma unroll
+    for (int k = 0; k < EPV; ++k) {
+      const long long o = ((long long)l * CIN + (tid % cpr) * EPV + k) * 2;
+      s1[k] = WHAT == C3_APPLY ? a.bn_sums[o] * inv : 0.f;
+      s2[k] = WHAT == C3_APPLY ? a.bn_sums[o + 1] * inv : 0.f;
+    }
+  }
+  const T* xs = static_cast<const T*>(a.in) + (long long)j * H * H * CIN;
+  uint4 xv[NX];
   for (int tile = 0; tile < tiles * tiles; ++tile) {
     const int y0 = (tile / tiles) * C3_TS, x0 = (tile % tiles) * C3_TS;
+    if constexpr (WHAT != C3_PLAIN)                            // this patch's x, on its way while the gradient is made
+#pragma unroll
+      for (int k = 0; k < NX; ++k) {
+        const int i = tid + 256 * k, q = i / cpr, ch = i - q * cpr;
+        const int y = y0 + q / C3_TS, x = x0 + q % C3_TS;
+        xv[k] = make_uint4(0, 0, 0, 0);
+        if (y < H && x < H) {
+          typedef unsigned u4 __attribute__((ext_vector_type(4)));
+          const u4 t = __builtin_nontemporal_load(reinterpret_cast<const u4*>(reinterpret_cast<const unsigned char*>(xs + ((long long)y * H + x) * CIN) + ch * 16));
+          xv[k] = make_uint4(t.x, t.y, t.z, t.w);
+        }
+      }
     __syncthreads();                                           // the previous patch: multiplied and written out
 #pragma unroll
     for (int k = 0; k < ND; ++k) {
@@ -262,18 +341,53 @@ __global__ __launch_bounds__(256) void conv3_dgrad_kernel(Conv3Args a) {
         *reinterpret_cast<T*>(OUT + (mt * 32 + c3_acc_row(e, h)) * orow + (nt * 32 + r) * SZ) = from_float<T>(acc[i][e]);
     }
     __syncthreads();
-    for (int i = tid; i < 64 * cpr; i += 256) {
-      const int q = i / cpr, ch = i - q * cpr;
+#pragma unroll
+    for (int k = 0; k < NX; ++k) {
+      const int i = tid + 256 * k, q = i / cpr, ch = i - q * cpr;
       const int y = y0 + q / C3_TS, x = x0 + q % C3_TS;
       if (y >= H || x >= H) continue;
-      *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(din + ((long long)y * H + x) * CIN) + ch * 16) =
-          *reinterpret_cast<const uint4*>(OUT + q * orow + ch * 16);
+      uint4 d = *reinterpret_cast<const uint4*>(OUT + q * orow + ch * 16);
+      if constexpr (WHAT != C3_PLAIN) {
+        const T* xe = reinterpret_cast<const T*>(&xv[k]);
+        const T* de = reinterpret_cast<const T*>(&d);
+        float v[EPV];
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) {
+          const float xh = (to_float(xe[e]) - norm.mu[e]) * norm.rs[e];
+          const float u = norm.ga[e] * xh + norm.be[e], dd = to_float(de[e]);
+          const float g = u > 0.f ? dd : dd * norm.slope;
+          if (WHAT == C3_SUMS) { s1[e] += g; s2[e] += g * xh; }
+          else v[e] = norm.sc[e] * (g - s1[e] - xh * s2[e]);
+        }
+        if (WHAT == C3_SUMS) continue;
+        C3Norm<T>::pack(v, d);
+      }
+      typedef unsigned u4 __attribute__((ext_vector_type(4)));
+      u4 o; o.x = d.x; o.y = d.y; o.z = d.z; o.w = d.w;
+      u4* dst = reinterpret_cast<u4*>(reinterpret_cast<unsigned char*>(din + ((long long)y * H + x) * CIN) + ch * 16);
+      if constexpr (WHAT == C3_APPLY) __builtin_nontemporal_store(o, dst); else *dst = o;
+    }
+  }
+  if constexpr (WHAT == C3_SUMS) {
+    // the 256 / cpr threads of each channel group, added in order
+    __syncthreads();
+    float* red = reinterpret_cast<float*>(lds);                // [256 / cpr][CIN][2], over the operands
+#pragma unroll
+    for (int e = 0; e < EPV; ++e)
+      *reinterpret_cast<float2*>(red + (((tid / cpr) * CIN + (tid % cpr) * EPV + e) * 2)) = make_float2(s1[e], s2[e]);
+    __syncthreads();
+    for (int t = tid; t < 2 * CIN; t += 256) {
+      float s = 0.f;
+#pragma unroll 8
+      for (int k = 0; k < 256 / cpr; ++k) s += red[k * CIN * 2 + t];
+      a.bn_part[(long long)j * CIN * 2 + t] = s;
     }
   }
 }
 
 // ---- weight gradient -------------------------------------------------------------------------------------------------
-template <typename T, int CIN>
+// NORM: as in the forward kernel
+template <typename T, int CIN, bool NORM>
 __global__ __launch_bounds__(256) void conv3_wgrad_kernel(Conv3Args a, float* __restrict__ part, int splits) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   constexpr int SZ = (int)sizeof(T);
@@ -311,6 +425,7 @@ __global__ __launch_bounds__(256) void conv3_wgrad_kernel(Conv3Args a, float* __
   static_assert(64 * cpr % 256 == 0, "feature tile chunks per thread");
   T dreg[ND];
   uint4 ireg[NI];
+  unsigned inside = 0;
   const int per_sample = tiles * tiles, npatch = (n_hi - n_lo) * per_sample;
   auto fetch = [&](int idx) {
     const int n = n_lo + idx / per_sample, tile = idx % per_sample;
@@ -329,12 +444,14 @@ __global__ __launch_bounds__(256) void conv3_wgrad_kernel(Conv3Args a, float* __
     // a wave takes one 16-byte channel group of all 64 pixels: its lanes then write 64 consecutive elements of a
     // row of IT (rows a multiple of 16 bytes apart would all fall into one bank if a lane's neighbours held the
     // other channel groups of the same pixel); the tile's lines come out of the L1 for the other groups
+    inside = 0;
 #pragma unroll
     for (int k = 0; k < NI; ++k) {
       const int i = tid + 256 * k;
       const int ch = i >> 6, q = i & 63;
       const int y = y0 + q / C3_TS, x = x0 + q % C3_TS;
       ireg[k] = make_uint4(0, 0, 0, 0);
+      inside |= (y < H && x < H ? 1u : 0u) << k;
       if (y < H && x < H) ireg[k] = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(in + ((long long)y * H + x) * CIN) + ch * 16);
     }
   };
@@ -350,6 +467,11 @@ __global__ __launch_bounds__(256) void conv3_wgrad_kernel(Conv3Args a, float* __
     for (int k = 0; k < NI; ++k) {
       const int i = tid + 256 * k;
       const int ch = i >> 6, q = i & 63;
+      if (NORM && (inside >> k & 1)) {
+        C3Norm<T> norm;                                        // (a wave's channels: the parameters come out of the caches)
+        norm.load(a, l, ch);
+        ireg[k] = norm.apply(ireg[k]);
+      }
       const T* e = reinterpret_cast<const T*>(&ireg[k]);
 #pragma unroll
       for (int kk = 0; kk < EPV; ++kk) *reinterpret_cast<T*>(IT + (ch * EPV + kk) * krow + q * SZ) = e[kk];
@@ -407,7 +529,7 @@ __device__ inline uint2 c3_read_tr16(const unsigned char* p) {
   const c3_short4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) c3_short4*)(p));
   return __builtin_bit_cast(uint2, v);
 }
-template <int CIN>
+template <int CIN, bool NORM>
 __global__ __launch_bounds__(256) void conv3_wgrad_tr_kernel(Conv3Args a, float* __restrict__ part, int splits) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   typedef bf16_t T;
@@ -454,6 +576,10 @@ __global__ __launch_bounds__(256) void conv3_wgrad_tr_kernel(Conv3Args a, float*
   static_assert(64 * cpr % 256 == 0, "feature tile chunks per thread");
   T dreg[ND];
   uint4 ireg[NI];
+  unsigned inside = 0;
+  static_assert(256 % cpr == 0, "a thread's channels");
+  C3Norm<T> norm;
+  if constexpr (NORM) norm.load(a, l, tid % cpr);
   const int per_sample = tiles * tiles, npatch = (n_hi - n_lo) * per_sample;
   auto fetch = [&](int idx) {
     const int n = n_lo + idx / per_sample, tile = idx % per_sample;
@@ -469,12 +595,14 @@ __global__ __launch_bounds__(256) void conv3_wgrad_tr_kernel(Conv3Args a, float*
       if (t < C3_HALO * C3_HALO * C3_MAXCO && co < CO && (unsigned)y < (unsigned)H && (unsigned)x < (unsigned)H)
         dreg[k] = dout[((long long)y * H + x) * CO + co];
     }
+    inside = 0;
 #pragma unroll
     for (int k = 0; k < NI; ++k) {
       const int i = tid + 256 * k;
       const int q = i / cpr, ch = i - q * cpr;
       const int y = y0 + q / C3_TS, x = x0 + q % C3_TS;
       ireg[k] = make_uint4(0, 0, 0, 0);
+      inside |= (y < H && x < H ? 1u : 0u) << k;
       if (y < H && x < H) ireg[k] = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(in + ((long long)y * H + x) * CIN) + ch * 16);
     }
   };
@@ -490,6 +618,7 @@ __global__ __launch_bounds__(256) void conv3_wgrad_tr_kernel(Conv3Args a, float*
     for (int k = 0; k < NI; ++k) {
       const int i = tid + 256 * k;
       const int q = i / cpr, ch = i - q * cpr;
+      if (NORM && (inside >> k & 1)) ireg[k] = norm.apply(ireg[k]);
       *reinterpret_cast<uint4*>(Fq + q * rowB + ch * 16) = ireg[k];
     }
     if (idx + 1 < npatch) fetch(idx + 1);
@@ -552,42 +681,64 @@ template <typename K> static void c3_allow_lds(K kernel, size_t lds) {
   if (lds > 48 * 1024)   // above the default dynamic limit: ask for it (idempotent, cheap)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
+// kernel(std::integral_constant<int, Cin>, std::integral_constant<bool, NORM>) for this call
+template <typename F> static void c3_pick(const Conv3Args& a, F&& f) {
+  const bool norm = a.bn_mean != nullptr;
+  if (a.Cin == 64) { if (norm) f(std::integral_constant<int, 64>(), std::true_type()); else f(std::integral_constant<int, 64>(), std::false_type()); }
+  else { if (norm) f(std::integral_constant<int, 128>(), std::true_type()); else f(std::integral_constant<int, 128>(), std::false_type()); }
+}
+static bool c3_norm_ok(const Conv3Args& a) { return !a.bn_mean || (a.bn_rstd && a.bn_gamma && a.bn_beta); }
 template <typename T> void launch_conv3_fwd(const Conv3Args& a, hipStream_t st) {
   if (a.n == 0) return;
-  if (!conv3_ok(a) || !a.in || !a.out || !a.bias) return launch_fail("image-side k3 convolution: unsupported shape or null operand");
+  if (!conv3_ok(a) || !a.in || !a.out || !a.bias || !c3_norm_ok(a)) return launch_fail("image-side k3 convolution: unsupported shape or null operand");
   const int nct = 9 * a.CO > 32 ? 2 : 1;
   const size_t lds = (size_t)(C3_HALO * C3_HALO + 32 * nct) * (a.Cin * sizeof(T) + 16) + (size_t)32 * nct * C3_RTS;
-  const dim3 grid(a.n);
-  if (a.Cin == 64) { c3_allow_lds(&conv3_fwd_kernel<T, 64>, lds); hipLaunchKernelGGL((conv3_fwd_kernel<T, 64>), grid, dim3(256), lds, st, a); }
-  else { c3_allow_lds(&conv3_fwd_kernel<T, 128>, lds); hipLaunchKernelGGL((conv3_fwd_kernel<T, 128>), grid, dim3(256), lds, st, a); }
+  c3_pick(a, [&](auto cin, auto norm) {
+    const auto kernel = &conv3_fwd_kernel<T, decltype(cin)::value, decltype(norm)::value>;
+    c3_allow_lds(kernel, lds);
+    hipLaunchKernelGGL(kernel, dim3(a.n), dim3(256), lds, st, a);
+  });
 }
+// with bn_mean: the sums (bn_part, per sample) without bn_sums, else the gradient with respect to a.in, the tensor in front of the BatchNorm
 template <typename T> void launch_conv3_dgrad(const Conv3Args& a, hipStream_t st) {
   if (a.n == 0) return;
-  if (!conv3_ok(a) || !a.dout || !a.din) return launch_fail("image-side k3 convolution: unsupported shape or null operand");
+  const bool sums = a.bn_mean && !a.bn_sums;
+  if (!conv3_ok(a) || !a.dout || (!sums && !a.din) || !c3_norm_ok(a) || (a.bn_mean && !a.in) || (sums && !a.bn_part))
+    return launch_fail("image-side k3 convolution: unsupported shape or null operand");
   const int SZ = (int)sizeof(T);
   const size_t prow = (size_t)(9 * C3_MAXCO * SZ + 31) / 32 * 32 + 16;
-  const size_t lds = (size_t)((C3_HALO * C3_HALO * C3_MAXCO * SZ + 15) & ~15) + (64 + a.Cin) * prow + (size_t)64 * (a.Cin * SZ + 16);
-  const dim3 grid(a.n);
-  if (a.Cin == 64) { c3_allow_lds(&conv3_dgrad_kernel<T, 64>, lds); hipLaunchKernelGGL((conv3_dgrad_kernel<T, 64>), grid, dim3(256), lds, st, a); }
-  else { c3_allow_lds(&conv3_dgrad_kernel<T, 128>, lds); hipLaunchKernelGGL((conv3_dgrad_kernel<T, 128>), grid, dim3(256), lds, st, a); }
+  const size_t lds = std::max((size_t)((C3_HALO * C3_HALO * C3_MAXCO * SZ + 15) & ~15) + (64 + a.Cin) * prow + (size_t)64 * (a.Cin * SZ + 16),
+                              sums ? (size_t)256 * (16 / SZ) * 8 : (size_t)0);
+  c3_pick(a, [&](auto cin, auto norm) {
+    const auto go = [&](auto kernel) {
+      c3_allow_lds(kernel, lds);
+      hipLaunchKernelGGL(kernel, dim3(a.n), dim3(256), lds, st, a);
+    };
+    constexpr int C = decltype(cin)::value;
+    if constexpr (!decltype(norm)::value) go(&conv3_dgrad_kernel<T, C, C3_PLAIN>);
+    else if (sums) go(&conv3_dgrad_kernel<T, C, C3_SUMS>);
+    else go(&conv3_dgrad_kernel<T, C, C3_APPLY>);
+  });
 }
 template <typename T> void launch_conv3_wgrad(const Conv3Args& a, float* part, float* dw, long long dw_stride, hipStream_t st) {
   if (a.n == 0) return;
-  if (!conv3_ok(a) || !a.dout || !a.in || !part || !dw) return launch_fail("image-side k3 convolution: unsupported shape or null operand");
+  if (!conv3_ok(a) || !a.dout || !a.in || !part || !dw || !c3_norm_ok(a)) return launch_fail("image-side k3 convolution: unsupported shape or null operand");
   const int splits = conv3_wgrad_splits(a.L);
   const int SZ = (int)sizeof(T);
   const size_t krow = (size_t)64 * SZ + 16;
   const int MT = (9 * C3_MAXCO + 31) / 32;
-  const size_t lds = (size_t)((C3_HALO * C3_HALO * C3_MAXCO * SZ + 15) & ~15) + std::max((MT * 32 + a.Cin) * krow, (size_t)MT * 32 * a.Cin * 4);
-  const dim3 grid(splits, a.L);
-  if constexpr (sizeof(T) == 2) {
-    const size_t lds_tr = std::max((size_t)((C3_HALO * C3_HALO * C3_MAXCO * SZ + 15) & ~15) + (size_t)64 * (a.Cin * SZ + 16), (size_t)MT * 32 * a.Cin * 4);
-    if (a.Cin == 64) { c3_allow_lds(&conv3_wgrad_tr_kernel<64>, lds_tr); hipLaunchKernelGGL((conv3_wgrad_tr_kernel<64>), grid, dim3(256), lds_tr, st, a, part, splits); }
-    else { c3_allow_lds(&conv3_wgrad_tr_kernel<128>, lds_tr); hipLaunchKernelGGL((conv3_wgrad_tr_kernel<128>), grid, dim3(256), lds_tr, st, a, part, splits); }
-  } else {
-    if (a.Cin == 64) { c3_allow_lds(&conv3_wgrad_kernel<T, 64>, lds); hipLaunchKernelGGL((conv3_wgrad_kernel<T, 64>), grid, dim3(256), lds, st, a, part, splits); }
-    else { c3_allow_lds(&conv3_wgrad_kernel<T, 128>, lds); hipLaunchKernelGGL((conv3_wgrad_kernel<T, 128>), grid, dim3(256), lds, st, a, part, splits); }
-  }
+  const size_t halo = (C3_HALO * C3_HALO * C3_MAXCO * SZ + 15) & ~15;
+  const size_t lds = SZ == 2 ? std::max(halo + (size_t)64 * (a.Cin * SZ + 16), (size_t)MT * 32 * a.Cin * 4)
+                             : halo + std::max((MT * 32 + a.Cin) * krow, (size_t)MT * 32 * a.Cin * 4);
+  c3_pick(a, [&](auto cin, auto norm) {
+    constexpr int C = decltype(cin)::value;
+    constexpr bool NORM = decltype(norm)::value;
+    const auto go = [&](auto kernel) {
+      c3_allow_lds(kernel, lds);
+      hipLaunchKernelGGL(kernel, dim3(splits, a.L), dim3(256), lds, st, a, part, splits);
+    };
+    if constexpr (sizeof(T) == 2) go(&conv3_wgrad_tr_kernel<C, NORM>); else go(&conv3_wgrad_kernel<T, C, NORM>);
+  });
   const long long tot = (long long)a.L * 9 * a.CO * a.Cin;
   hipLaunchKernelGGL(conv3_wgrad_final_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, a, part, dw, dw_stride, splits);
 }

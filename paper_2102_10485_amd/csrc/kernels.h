@@ -81,6 +81,8 @@ template <typename T> void launch_bn_apply(const NormArgs& a, hipStream_t st);
 int bn_red_rows(long long rows, int L);     // rows per block of the backward reduction over `rows` rows of L models (its tile prefix geometry)
 template <typename T>
 void launch_bn_bwd_reduce(const NormArgs& a, const int* tpre, const int* tmodel, int ub_tiles, float* partial, hipStream_t st);
+// its second stage on partial sums [segment][ub_tiles][C][2] of tiles tpre[l] .. tpre[l + 1]
+void launch_bn_bwd_final(const NormArgs& a, const int* tpre, int ub_tiles, const float* partial, hipStream_t st);
 template <typename T> void launch_bn_bwd_apply(const NormArgs& a, hipStream_t st);
 
 // The layers touching the image (1..4 channels) run as row-by-row GEMMs over an explicit patch matrix.
@@ -308,6 +310,13 @@ struct Conv3Args {
   int out_seg, seg_samples;
   float* user;              // forward: the caller's NCHW fp32 images, written in place of out through perm (or NULL)
   const int* perm;
+  // with bn_mean: `in` is the tensor in front of the BatchNorm (batch statistics [L][Cin]; gamma, beta of model 0, bn_pstride between models) and
+  // the activation (slope below zero) whose result the features are
+  const float *bn_mean, *bn_rstd, *bn_gamma, *bn_beta;
+  long long bn_pstride;
+  float bn_slope;
+  float* bn_part;           // data gradient without bn_sums: [n][Cin][2], the sums of every sample that BatchNorm's backward pass wants
+  const float* bn_sums;     // [L][Cin][2]: with them the data gradient is that of `in`
 };
 template <typename T> void launch_conv3_fwd(const Conv3Args& a, hipStream_t st);
 template <typename T> void launch_conv3_dgrad(const Conv3Args& a, hipStream_t st);

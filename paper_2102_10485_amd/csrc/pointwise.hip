@@ -613,6 +613,13 @@ __global__ __launch_bounds__(SL * 16) void bn_bwd_reduce_final_kernel(NormArgs a
 // Rows a block of the first stage sums: 256, or 64 where those leave the chip short of blocks.  One 32x32 pair of 1000 images, both
 // stages, 256 rows against 64: 16000 rows of 512 channels 28 us and 15, 64000 of 256 20 and 21.  By the sizing batch, never a call's.
 int bn_red_rows(long long rows, int L) { return rows / 256 + L < 192 ? 64 : 256; }
+void launch_bn_bwd_final(const NormArgs& a, const int* tpre, int ub_tiles, const float* partial, hipStream_t st) {
+  if (a.nseg == 0 || ub_tiles == 0) return;
+  if (!tpre || !partial || a.nseg > 2) return launch_fail("BatchNorm backward: no tile prefix array, no partial sums, or more than two segments");
+  const long long tot = (long long)a.L * ((a.C + 15) / 16);
+  if (ub_tiles > 64LL * a.L) hipLaunchKernelGGL(bn_bwd_reduce_final_kernel<64>, dim3((unsigned)tot), dim3(1024), 0, st, a, tpre, ub_tiles, partial);
+  else hipLaunchKernelGGL(bn_bwd_reduce_final_kernel<16>, dim3((unsigned)tot), dim3(256), 0, st, a, tpre, ub_tiles, partial);
+}
 template <typename T>
 void launch_bn_bwd_reduce(const NormArgs& a, const int* tpre, const int* tmodel, int ub_tiles, float* partial, hipStream_t st) {
   if (a.nseg == 0 || ub_tiles == 0) return;
@@ -621,9 +628,7 @@ void launch_bn_bwd_reduce(const NormArgs& a, const int* tpre, const int* tmodel,
   if (cg < 1 || cg > 256) return launch_fail("BatchNorm backward: one thread per 16 bytes of a row needs at most 256 of them");
   const size_t lds = (size_t)2 * (256 / cg) * a.C * sizeof(float);
   hipLaunchKernelGGL((bn_bwd_reduce_kernel<T>), dim3(ub_tiles, a.nseg), dim3(256), lds, st, a, tpre, tmodel, ub_tiles, partial);
-  const long long tot = (long long)a.L * ((a.C + 15) / 16);
-  if (ub_tiles > 64LL * a.L) hipLaunchKernelGGL(bn_bwd_reduce_final_kernel<64>, dim3((unsigned)tot), dim3(1024), 0, st, a, tpre, ub_tiles, partial);
-  else hipLaunchKernelGGL(bn_bwd_reduce_final_kernel<16>, dim3((unsigned)tot), dim3(256), 0, st, a, tpre, ub_tiles, partial);
+  launch_bn_bwd_final(a, tpre, ub_tiles, partial, st);
 }
 template void launch_bn_bwd_reduce<float>(const NormArgs&, const int*, const int*, int, float*, hipStream_t);
 template void launch_bn_bwd_reduce<bf16_t>(const NormArgs&, const int*, const int*, int, float*, hipStream_t);
