@@ -1221,10 +1221,9 @@ void adam_call(gan_ctx* c, Net& net, bool isG) {
 
 template <typename T>
 void route_and_stage(gan_ctx* c, const int32_t* label_ids, const float* noise, const float* real, int n) {
-  launch_route(label_ids, n, c->L, c->cfg.n_labels, c->geoms, c->rb, c->st);
   {
     Scope s(c, "stage", 0, (double)n * c->cfg.z_dim * (4.0 + sizeof(T)));
-    launch_stage<T>(label_ids, noise, n, c->L, c->cfg.z_dim, c->cfg.cond_g, c->G.Kp, c->geoms, c->rb, (T*)c->zin, c->st);
+    launch_route_stage<T>(label_ids, noise, n, c->L, c->cfg.n_labels, c->cfg.z_dim, c->cfg.cond_g, c->G.Kp, c->geoms, c->rb, (T*)c->zin, c->st);
   }
   if (real) im2col_call<T>(c, c->D.conv[0], nullptr, real, c->colD, c->KcD, c->nslot, 0, n);   // the real half of D's input
 }

@@ -209,9 +209,12 @@ template void launch_im2col<bf16_t>(const Im2colArgs&, hipStream_t);
 
 // the filter taps of a label's map that lie inside for the pixels of a class, summed
 __device__ inline float label_taps(const PackArgs& a, const float* w, int label, int cls, int cs) {
-  float s = 0.f;
+  float v[16], s = 0.f;      // (all loads first: the kernel is bound by their latency)
+#pragma unroll
+  for (int tap = 0; tap < 16; ++tap) v[tap] = w[((long long)tap * a.CBT + a.CB + label) * a.Cs + cs];
+#pragma unroll
   for (int tap = 0; tap < 16; ++tap)
-    if (tap_valid(cls / 3, tap >> 2) && tap_valid(cls % 3, tap & 3)) s += w[((long long)tap * a.CBT + a.CB + label) * a.Cs + cs];
+    if (tap_valid(cls / 3, tap >> 2) && tap_valid(cls % 3, tap & 3)) s += v[tap];
   return s;
 }
 template <typename T>
@@ -300,17 +303,18 @@ __global__ void unpack_dw_kernel(PackArgs a) {
   }
 }
 // part[0][i] <- part[0][i] + part[1][i] + ... (nsplit blocks of size4 float4 each), in a fixed order: lane group q of
-// a block adds the blocks q, q + 4, ... in turn, then (q0 + q1) + (q2 + q3).  One thread per element would walk the
-// splits one load after the other: with one model and 128 splits that chain alone took 0.13 ms.
+// a block adds the blocks q, q + 16, ... in turn, eight loads in flight, then the groups' sums are added in order.  One thread per element
+// would walk the splits one load after the other: with one model and 128 splits that chain alone took 0.13 ms, and four groups
+// with four loads in flight 6.5-7.9 us (sixteen: 3.2-4.8).
 __global__ __launch_bounds__(256) void reduce_splits_kernel(float* __restrict__ part, long long size4, int nsplit) {
-  __shared__ float4 red[4][64];
-  const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const long long i = (long long)blockIdx.x * 64 + c;
+  __shared__ float4 red[16][16];
+  const int c = threadIdx.x & 15, q = threadIdx.x >> 4;
+  const long long i = (long long)blockIdx.x * 16 + c;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   if (i < size4) {
     const float4* p = reinterpret_cast<const float4*>(part) + i;
-#pragma unroll 4
-    for (int k = q; k < nsplit; k += 4) {
+#pragma unroll 8
+    for (int k = q; k < nsplit; k += 16) {
       const float4 t = p[(long long)k * size4];
       acc.x += t.x; acc.y += t.y; acc.z += t.z; acc.w += t.w;
     }
@@ -318,9 +322,12 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(float* __restrict__ 
   red[q][c] = acc;
   __syncthreads();
   if (q == 0 && i < size4) {
-    const float4 a0 = red[0][c], a1 = red[1][c], a2 = red[2][c], a3 = red[3][c];
-    reinterpret_cast<float4*>(part)[i] = make_float4((a0.x + a1.x) + (a2.x + a3.x), (a0.y + a1.y) + (a2.y + a3.y),
-                                                      (a0.z + a1.z) + (a2.z + a3.z), (a0.w + a1.w) + (a2.w + a3.w));
+#pragma unroll
+    for (int g = 1; g < 16; ++g) {
+      const float4 t = red[g][c];
+      acc.x += t.x; acc.y += t.y; acc.z += t.z; acc.w += t.w;
+    }
+    reinterpret_cast<float4*>(part)[i] = acc;
   }
 }
 void launch_unpack_dw(const PackArgs& a0, hipStream_t st) {
@@ -328,7 +335,7 @@ void launch_unpack_dw(const PackArgs& a0, hipStream_t st) {
   const long long block = (long long)a.L * a.Kc * a.Cs;       // floats per split
   if (a.nsplit > 4 && block % 4 == 0) {
     // many row splits: add them up with a kernel that has enough threads, in place into the first block
-    hipLaunchKernelGGL(reduce_splits_kernel, dim3((unsigned)((block / 4 + 63) / 64)), dim3(256), 0, st, const_cast<float*>(a.dwp), block / 4,
+    hipLaunchKernelGGL(reduce_splits_kernel, dim3((unsigned)((block / 4 + 15) / 16)), dim3(256), 0, st, const_cast<float*>(a.dwp), block / 4,
                        a.nsplit);
     a.nsplit = 1;
   }

@@ -31,12 +31,10 @@ struct RouteBuffers {
                       //     follows the count (may be NULL)
 };
 
-void launch_route(const int* label_ids, int n, int L, int n_labels, const GeomTable& geoms, const RouteBuffers& rb,
-                  hipStream_t st);
-
+// the partition, G's input rows (noise | one-hot label | zeros, kp values a row) in its order, and the model of every tile (rb.tmodel)
 template <typename T>
-void launch_stage(const int* label_ids, const float* noise, int n, int L, int zdim, int cond_g, int kp, const GeomTable& geoms,
-                  const RouteBuffers& rb, T* zin, hipStream_t st);     // and the model of every tile (rb.tmodel)
+void launch_route_stage(const int* label_ids, const float* noise, int n, int L, int n_labels, int zdim, int cond_g, int kp, const GeomTable& geoms,
+                        const RouteBuffers& rb, T* zin, hipStream_t st);
 
 // Batch statistics and the normalise+activate passes.  Groups = (segment, model); rows of group (s, l) are the
 // rps rows of each of samples s*seg_samples + offs[l] .. offs[l+1].

@@ -27,9 +27,18 @@ constexpr int ROUTE_THREADS = 64 * ROUTE_WAVES;
 constexpr int ROUTE_LDS_BYTES = 152 * 1024;
 // (the placement is a template parameter so that every access is known to be an LDS or a global one: through
 // pointers that may be either, each LDS access took several times as long)
-template <bool in_lds>
+template <typename T>
+__device__ inline T staged_noise(const float* __restrict__ noise, const int* __restrict__ label_ids, int src, int k, int zdim, int cond_g) {
+  float v = 0.f;
+  if (k < zdim) v = noise[(long long)src * zdim + k];
+  else if (k < zdim + cond_g) v = (k - zdim == label_ids[src]) ? 1.f : 0.f;
+  return from_float<T>(v);
+}
+// The staging of one model's few rows as a tail of the routing (STAGE_INSIDE): another launch costs more than one block's pass over them.
+template <typename T> struct StageTail { const float* noise; T* zin; int zdim, cond_g, kp; };      // noise NULL: none
+template <bool in_lds, typename T>
 __global__ __launch_bounds__(ROUTE_THREADS) void route_kernel(const int* __restrict__ label_ids, int n, int L, int n_labels, int bits,
-                                                              GeomTable geoms, RouteBuffers rb) {
+                                                              GeomTable geoms, RouteBuffers rb, StageTail<T> tail) {
   extern __shared__ int route_lds[];
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   int* cl = in_lds ? route_lds : rb.counts;                    // [L]
@@ -134,6 +143,14 @@ __global__ __launch_bounds__(ROUTE_THREADS) void route_kernel(const int* __restr
       rb.sample_slot[pos] = (L == 1) ? y : 0;
     }
   });
+  if (tail.noise) {
+    __syncthreads();
+    const int rows = ol[L];
+    for (int i = t; i < rows * tail.kp; i += ROUTE_THREADS) {
+      const int j = i / tail.kp;
+      tail.zin[i] = staged_noise<T>(tail.noise, label_ids, rb.perm[j], i - j * tail.kp, tail.zdim, tail.cond_g);
+    }
+  }
 }
 
 // model of tile t of a geometry
@@ -146,41 +163,48 @@ __device__ inline void tile_model(const int* __restrict__ tpre, int L, int* __re
   }
   tmodel[t] = lo;
 }
+// Q threads share an element's splits, thread q adding q, q + Q, ..., then the threads' sums are added in order.
+template <int Q>
 __global__ __launch_bounds__(256) void sum_splits_kernel(const float* __restrict__ part, float* __restrict__ dW, long long dw_stride,
                                                           long long size4, int L, int nsplit) {
-  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= size4 * L) return;
-  const int l = (int)(idx / size4);
+  __shared__ float4 sh[Q][256 / Q];
+  const int c = threadIdx.x % (256 / Q), q = threadIdx.x / (256 / Q);
+  const long long idx = (long long)blockIdx.x * (256 / Q) + c;
+  const bool have = idx < size4 * L;
+  const int l = have ? (int)(idx / size4) : 0;
   const long long i = idx - (long long)l * size4;
   const float4* p = reinterpret_cast<const float4*>(part) + (long long)l * size4 + i;
-  float4 s = p[0];
-#pragma unroll 8
-  for (int k = 1; k < nsplit; ++k) {
-    const float4 t = p[(long long)k * L * size4];
-    s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  // eight loads in flight, added in order (written out: a loop of fewer trips than it is unrolled by loads one after the other)
+  if (have)
+    for (int k0 = q; k0 < nsplit; k0 += 8 * Q) {
+      float4 t[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (k0 + k * Q < nsplit) t[k] = p[(long long)(k0 + k * Q) * L * size4];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (k0 + k * Q < nsplit) { s.x += t[k].x; s.y += t[k].y; s.z += t[k].z; s.w += t[k].w; }
+    }
+  if constexpr (Q > 1) {
+    sh[q][c] = s;
+    __syncthreads();
+    if (q > 0) return;
+#pragma unroll
+    for (int k = 1; k < Q; ++k) { const float4 t = sh[k][c]; s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w; }
   }
-  *reinterpret_cast<float4*>(dW + (long long)l * dw_stride + 4 * i) = s;
+  if (have) *reinterpret_cast<float4*>(dW + (long long)l * dw_stride + 4 * i) = s;
 }
 void launch_sum_splits(const float* part, float* dW, long long dw_stride, long long size, int L, int nsplit, hipStream_t st) {
   if (size % 4 != 0 || dw_stride % 4 != 0 || ((uintptr_t)dW & 15) != 0 || ((uintptr_t)part & 15) != 0)
     return launch_fail("sum of row splits: sizes and pointers must be multiples of 16 bytes");
   const long long tot = size / 4 * L;
   if (tot == 0) return;
-  hipLaunchKernelGGL(sum_splits_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, part, dW, dw_stride, size / 4, L, nsplit);
-}
-
-void launch_route(const int* label_ids, int n, int L, int n_labels, const GeomTable& geoms, const RouteBuffers& rb,
-                  hipStream_t st) {
-  int bits = 0;
-  while (bits < 31 && (1 << bits) < L) ++bits;
-  const size_t lds = ((size_t)(2 + ROUTE_WAVES) * L + 1) * 4;
-  const auto go = [&](auto kernel, size_t bytes) {
-    if (bytes > 48 * 1024)   // above the default dynamic limit: ask for it (idempotent, cheap)
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    hipLaunchKernelGGL(kernel, dim3(1), dim3(ROUTE_THREADS), bytes, st, label_ids, n, L, n_labels, bits, geoms, rb);
-  };
-  if (lds <= (size_t)ROUTE_LDS_BYTES) go(&route_kernel<true>, lds);
-  else go(&route_kernel<false>, 0);
+  // (few elements: four threads each.  16 taps of 64 x 128 in 32 splits 8.0 -> 5.5 us)
+  if (tot < 256 * 256 && nsplit >= 16)
+    hipLaunchKernelGGL(sum_splits_kernel<4>, dim3((unsigned)((tot + 63) / 64)), dim3(256), 0, st, part, dW, dw_stride, size / 4, L, nsplit);
+  else
+    hipLaunchKernelGGL(sum_splits_kernel<1>, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, part, dW, dw_stride, size / 4, L, nsplit);
 }
 
 __global__ void tile_prefix_kernel(const int* offs, int L, int rps, int tile_rows, int* tpre) {
@@ -217,17 +241,28 @@ __global__ __launch_bounds__(256) void stage_noise_kernel(const float* __restric
   if (idx >= (long long)n * kp) return;
   const int j = (int)(idx / kp), k = (int)(idx - (long long)j * kp);
   if (j >= rb.offs[L]) return;
-  const int src = rb.perm[j];
-  float v = 0.f;
-  if (k < zdim) v = noise[(long long)src * zdim + k];
-  else if (k < zdim + cond_g) v = (k - zdim == label_ids[src]) ? 1.f : 0.f;
-  zin[idx] = from_float<T>(v);
+  zin[idx] = staged_noise<T>(noise, label_ids, rb.perm[j], k, zdim, cond_g);
 }
 
+// Elements of one model's noise rows up to which the routing's block stages them itself: four a thread.  2048 elements: 5.6 us for both,
+// 4.2 and 3.0 in launches of their own; 8192 elements: 11.5, 4.8 and 3.5.
+constexpr int STAGE_INSIDE = 4 * ROUTE_THREADS;
 template <typename T>
-void launch_stage(const int* label_ids, const float* noise, int n, int L, int zdim, int cond_g, int kp, const GeomTable& geoms,
-                  const RouteBuffers& rb, T* zin, hipStream_t st) {
-  if (n == 0) return;
+void launch_route_stage(const int* label_ids, const float* noise, int n, int L, int n_labels, int zdim, int cond_g, int kp, const GeomTable& geoms,
+                        const RouteBuffers& rb, T* zin, hipStream_t st) {
+  int bits = 0;
+  while (bits < 31 && (1 << bits) < L) ++bits;
+  const bool inside = L == 1 && (long long)n * kp <= STAGE_INSIDE;
+  const StageTail<T> tail = {inside ? noise : nullptr, zin, zdim, cond_g, kp};
+  const size_t lds = ((size_t)(2 + ROUTE_WAVES) * L + 1) * 4;
+  const auto go = [&](auto kernel, size_t bytes) {
+    if (bytes > 48 * 1024)   // above the default dynamic limit: ask for it (idempotent, cheap)
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(ROUTE_THREADS), bytes, st, label_ids, n, L, n_labels, bits, geoms, rb, tail);
+  };
+  if (lds <= (size_t)ROUTE_LDS_BYTES) go(&route_kernel<true, T>, lds);
+  else go(&route_kernel<false, T>, 0);
+  if (n == 0 || inside) return;
   const long long noise_blocks = ((long long)n * kp + 255) / 256;
   const int tile_blocks = (rb.tmodel_stride + 255) / 256;
   const long long blocks = noise_blocks + (L > 1 ? (long long)tile_blocks * geoms.n : 0);      // (one model's tiles need no table)
@@ -235,8 +270,8 @@ void launch_stage(const int* label_ids, const float* noise, int n, int L, int zd
   hipLaunchKernelGGL((stage_noise_kernel<T>), dim3((unsigned)blocks), dim3(256), 0, st, noise, label_ids, n, L, zdim, cond_g, kp, zin, rb,
                      (int)noise_blocks, tile_blocks);
 }
-template void launch_stage<float>(const int*, const float*, int, int, int, int, int, const GeomTable&, const RouteBuffers&, float*, hipStream_t);
-template void launch_stage<bf16_t>(const int*, const float*, int, int, int, int, int, const GeomTable&, const RouteBuffers&, bf16_t*, hipStream_t);
+template void launch_route_stage<float>(const int*, const float*, int, int, int, int, int, int, const GeomTable&, const RouteBuffers&, float*, hipStream_t);
+template void launch_route_stage<bf16_t>(const int*, const float*, int, int, int, int, int, int, const GeomTable&, const RouteBuffers&, bf16_t*, hipStream_t);
 
 // ---------------------------------------------------------------------------------------------------------
 // BatchNorm
@@ -578,13 +613,19 @@ __global__ __launch_bounds__(SL * 16) void bn_bwd_reduce_final_kernel(NormArgs a
   const int t0 = tpre[l], t1 = tpre[l + 1];
   for (int sidx = 0; sidx < a.nseg; ++sidx) {
     float s0 = 0.f, s1 = 0.f;
-    if (c < a.C)
-#pragma unroll 8
-      for (int t = t0 + sl; t < t1; t += SL) {         // (eight tiles' loads in flight, added in order)
-        const float2 e = *reinterpret_cast<const float2*>(partial + (((long long)sidx * ub_tiles + t) * a.C + c) * 2);
-        s0 += e.x;
-        s1 += e.y;
-      }
+    const float2* const p = reinterpret_cast<const float2*>(partial) + (long long)sidx * ub_tiles * a.C + min(c, a.C - 1);
+    for (int t = t0 + sl; t < t1; t += 8 * SL) {       // (eight tiles' loads in flight, added in order)
+      float2 e[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (t + k * SL < t1) e[k] = p[(long long)(t + k * SL) * a.C];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (t + k * SL < t1) {
+          s0 += e[k].x;
+          s1 += e[k].y;
+        }
+    }
 #pragma unroll
     for (int d = 16; d < 64; d <<= 1) {
       s0 += __shfl_xor(s0, d, 64);
