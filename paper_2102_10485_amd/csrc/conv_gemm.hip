@@ -110,8 +110,8 @@ template <typename TL> static bool share_fits(int H) {
 
 // What a tile is to the chooser: its shape, the row blocks with statistics of their own, the blocks of it that a CU holds, and
 // the rate a full chip of them reaches against the fastest one of the storage type (0: the storage type has no such tile).  The bf16
-// 256x64 line describes Narrow, which MODE_DOWN runs; MODE_UP and MODE_DENSE run NarrowShort (four blocks per CU, 582 TFLOP/s instead of
-// 480) and are judged by the same line, so the estimate is too high for them.
+// 256x64 line describes Narrow, which MODE_DOWN runs; MODE_DENSE and MODE_UP run NarrowShort and, with sides that allow it, NarrowShare (four and
+// three blocks per CU; 582 and 670 TFLOP/s where Narrow reaches 480) and are judged by the same line, so the estimate is too high for them.
 // Deep and Pair take launches of at most `most` tiles.  There a launch takes as long as one block, which waits for each chunk, splits it
 // (fp32) and multiplies it in turn; more waves on the same tile overlap these.  In us, Tiny / Pair / Deep by the number of 64x64 tiles, fp32:
 // down 64 -> 128 channels, side 7: 104 tiles 30.2 / 25.2 / 17.0, 200 31.3 / 26.4 / 31.5, 400 44.1 / 40.4 / 59.5, 800 72.6 / 73.7 / 102;
