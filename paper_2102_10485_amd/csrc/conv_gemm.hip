@@ -1024,7 +1024,8 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
         if (lane < 32 && col < N) {
           const float nf = (float)nvalid;
           p.stat_partial[(tix * N + col) * 2] = K * nf + s1;
-          p.stat_partial[(tix * N + col) * 2 + 1] = fmaxf(s2 - s1 * s1 / nf, 0.f);
+          const float m2 = s2 - s1 * s1 / nf;
+          p.stat_partial[(tix * N + col) * 2 + 1] = m2 < 0.f ? 0.f : m2;      // (a NaN, from squares beyond fp32 for one, stays a NaN)
         }
       }
     }

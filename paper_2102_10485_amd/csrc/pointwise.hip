@@ -403,7 +403,8 @@ __global__ __launch_bounds__(SL * CX) void bn_stats_from_partial_kernel(NormArgs
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) { s += sh[sidx][w][cx][0]; q2 += sh[sidx][w][cx][1]; }
     const double m = s / N;
-    const float mean = (float)m, var = (float)fmax((q2 - s * m) / N, 0.0);
+    const double dev = (q2 - s * m) / N;
+    const float mean = (float)m, var = (float)(dev < 0.0 ? 0.0 : dev);     // (a NaN stays one: fmax would make it 0)
     const long long o = (long long)((a.seg_first + sidx) * a.L + l) * a.C + c;
     a.mean[o] = mean;
     a.var[o] = var;

@@ -433,3 +433,37 @@ def test_generator_batch_statistics_of_one_pair(n):
         assert np.max(np.abs(mean[o:o + C] / 0.1 - m) / np.sqrt(v)) <= 1e-5
         assert np.max(np.abs(var[o:o + C] / (0.1 * v * N / (N - 1)) - 1)) <= 1e-5
         o += C
+
+
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+@pytest.mark.parametrize("spec_name", ["tiny3", "paper16"])
+@pytest.mark.parametrize("what", ["infinity", "squares"])
+def test_values_without_a_finite_variance_show_in_the_statistics(prec, spec_name, what):
+    """An infinity (its deviations are NaN), or values whose squares are beyond fp32, in one model's batch: that model's running variances
+    are not finite, its images with batch statistics are NaN and not a finite -1 or 1; the model beside it notices nothing."""
+    torch = U.torch_mod()
+    spec, n = synth.SPECS[spec_name], 20 if what == "infinity" else 4              # (four: one wave's rows hold a whole layer of the model)
+    g = binding.Gan(binding.make_config(spec, 3, 3, n, prec), torch.cuda.current_stream().cuda_stream)
+    lab, z, x = batch(spec, np.arange(n) % 2, 91)
+    if what == "infinity":
+        z[4, 3], x[6, 0, 5, 5] = np.inf, np.inf
+    else:
+        z[0::4] *= 1e24
+        x[0::4] *= 1e24
+    dl, dz, dx = U.dev(lab), U.dev(z), U.dev(x)
+    out = torch.zeros((n, spec["img_c"], spec["img_hw"], spec["img_hw"]), device="cuda")
+    g.generate(dl.data_ptr(), dz.data_ptr(), n, out.data_ptr(), 0)
+    g.train_step(dl.data_ptr(), dz.data_ptr(), dx.data_ptr(), n)
+    var = [[g.get_bn_running(w, l)[1] for l in (0, 1)] for w in (0, 1)]
+    grads = [g.get_grads(w, 1) for w in (0, 1)]
+    img = out.cpu().numpy()
+    g.close()
+    first = spec["g_ch"][0], spec["d_ch"][1]
+    for w in (0, 1):
+        # later layers: NaN follows NaN; behind a variance of infinity the values are zero
+        seen = var[w][0] if what == "infinity" else var[w][0][:first[w]]
+        assert not np.isfinite(seen).any(), (w, seen)
+        assert np.isfinite(var[w][1]).all() and np.isfinite(grads[w]).all()
+    if what == "infinity":
+        assert np.isnan(img[lab == 0]).all()
+    assert np.isfinite(img[lab == 1]).all()
