@@ -723,6 +723,7 @@ void bn_backward(gan_ctx* c, NormArgs a, const void* x, const void* dy, void* dx
   {
     Scope s(c, "bn_bwd_reduce", 0, 2 * elems * sizeof(T));
     const int tr = a.red_rows = red_rows(c, a.rps);
+    a.red_tiles = ub_tiles(c, c->NB, a.rps, tr);
     launch_bn_bwd_reduce<T>(a, tpre_of(c, a.rps, tr), tmodel_of(c, a.rps, tr), ub_tiles(c, a.n, a.rps, tr), c->stat_partial, c->st);
   }
   Scope s(c, "bn_bwd_apply", 0, 3 * elems * sizeof(T));
@@ -1120,7 +1121,7 @@ void paper_g_backward(gan_ctx* c, int n) {
     const ConvLayer& cl = G.conv[nl - 2];
     NormArgs na = norm_args<T>(c, G, cl.Cb, 4 * cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->g_mean[nl - 1], c->g_var[nl - 1], c->g_rstd[nl - 1],
                                c->g_sums[nl - 1], 0, 1, n, f.leaky_slope);
-    na.param_grads = 1;
+    na.param_grads = 1; na.red_tiles = c->NB;
     a.bn_part = c->stat_partial;
     const double flops = 2.0 * n * last.Hs * last.Hs * 9 * last.Cs * last.Cb, elems = (double)n * last.Hs * last.Hs;
     {

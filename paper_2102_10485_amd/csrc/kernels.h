@@ -68,6 +68,7 @@ struct NormArgs {
   float pre_slope, pre_scale;
   int fold_running;         // statistics from the GEMM's partials: that kernel also updates the running statistics
   int red_rows;             // backward reduction: rows per block (bn_red_rows)
+  int red_tiles;            // and its tiles at the sizing batch, which decide how its second stage adds them
   int param_grads;          // backward reduction: its last stage also writes dgamma / dbeta, the segments' sums added in order
 };
 // statistics from the per-tile column sums a GEMM left behind (stat_partial of ConvArgs)

@@ -600,7 +600,8 @@ __global__ __launch_bounds__(256) void bn_bwd_reduce_kernel(NormArgs a, const in
     partial[(((long long)sidx * ub_tiles + tile) * a.C + c) * 2 + w] = acc;
   }
 }
-// (SL slices x 16 channels of one model, slice s adding every SL-th tile from s on: 16, or 64 when a model has many tiles; both segments
+// (SL slices x 16 channels of one model, slice s adding every SL-th tile from s on: 16, or 64 when a model has many tiles at the sizing
+// batch (the call's own batch may not decide, or the order of a model's sums would follow the other models' samples); both segments
 // in one block, which with that also adds them up to the parameters' gradients)
 template <int SL>
 __global__ __launch_bounds__(SL * 16) void bn_bwd_reduce_final_kernel(NormArgs a, const int* __restrict__ tpre, int ub_tiles,
@@ -657,9 +658,10 @@ __global__ __launch_bounds__(SL * 16) void bn_bwd_reduce_final_kernel(NormArgs a
 int bn_red_rows(long long rows, int L) { return rows / 256 + L < 192 ? 64 : 256; }
 void launch_bn_bwd_final(const NormArgs& a, const int* tpre, int ub_tiles, const float* partial, hipStream_t st) {
   if (a.nseg == 0 || ub_tiles == 0) return;
-  if (!tpre || !partial || a.nseg > 2) return launch_fail("BatchNorm backward: no tile prefix array, no partial sums, or more than two segments");
+  if (!tpre || !partial || a.red_tiles < ub_tiles || a.nseg > 2)
+    return launch_fail("BatchNorm backward: no tile prefix array, no partial sums, more tiles than at the sizing batch, or more than two segments");
   const long long tot = (long long)a.L * ((a.C + 15) / 16);
-  if (ub_tiles > 64LL * a.L) hipLaunchKernelGGL(bn_bwd_reduce_final_kernel<64>, dim3((unsigned)tot), dim3(1024), 0, st, a, tpre, ub_tiles, partial);
+  if (a.red_tiles > 64LL * a.L) hipLaunchKernelGGL(bn_bwd_reduce_final_kernel<64>, dim3((unsigned)tot), dim3(1024), 0, st, a, tpre, ub_tiles, partial);
   else hipLaunchKernelGGL(bn_bwd_reduce_final_kernel<16>, dim3((unsigned)tot), dim3(256), 0, st, a, tpre, ub_tiles, partial);
 }
 template <typename T>

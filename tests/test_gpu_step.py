@@ -467,3 +467,54 @@ def test_values_without_a_finite_variance_show_in_the_statistics(prec, spec_name
     if what == "infinity":
         assert np.isnan(img[lab == 0]).all()
     assert np.isfinite(img[lab == 1]).all()
+
+
+def _ten_pairs(prec, cap, keep, others, seed, z_keep=None):
+    """One step of ten 28x28 pairs in a context for `cap` samples: model 3 gets `keep` samples, the others `others` between them."""
+    torch = U.torch_mod()
+    spec = synth.SPECS["mnist"]
+    rng = np.random.default_rng(seed)
+    lab, z, x = batch(spec, np.full(keep, 3), seed)
+    if z_keep is not None:
+        z = z_keep(z)
+    lab2, z2, x2 = batch(spec, rng.choice([0, 1, 2, 4, 5, 6, 7, 8, 9], others), seed + others + 1)
+    order = rng.permutation(keep + others)
+    order[np.sort(np.flatnonzero(order < keep))] = np.arange(keep)                 # model 3's samples in their own order
+    lab, z, x = (np.concatenate(p)[order] for p in ((lab, lab2), (z, z2), (x, x2)))
+    g = binding.Gan(binding.make_config(spec, 10, 10, cap, prec, seed=2), torch.cuda.current_stream().cuda_stream)
+    dl, dz, dx = U.dev(lab), U.dev(z), U.dev(x)
+    g.train_step(dl.data_ptr(), dz.data_ptr(), dx.data_ptr(), len(lab))
+    out = [g.get_grads(w, 3) for w in (0, 1)] + [g.get_params(w, 3) for w in (0, 1)] + [v for w in (0, 1) for v in g.get_bn_running(w, 3)]
+    g.close()
+    return out
+
+
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+@pytest.mark.parametrize("others", [300, 1100])
+def test_backward_sums_do_not_depend_on_the_other_models_samples(prec, others):
+    """The same hundred samples of one model (77 row blocks of 256 rows at side 14) alone and beside few and many samples of
+    nine other models, in contexts of one size: the sums of BatchNorm's backward pass are added in the same order, bit for bit."""
+    alone = _ten_pairs(prec, 1280, 100, 0, 31)
+    for a, b in zip(alone, _ten_pairs(prec, 1280, 100, others, 31)):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+def test_table_networks_sums_do_not_depend_on_the_other_models_samples(prec):
+    """The same for the sums that the image-side layer of the tables' generator leaves per sample: sixty samples of one of three models,
+    beside 60 and beside 400 others."""
+    torch = U.torch_mod()
+    spec = synth.SPECS["paper16"]
+    res = []
+    for others in (60, 400):
+        lab, z, x = batch(spec, np.concatenate([np.full(60, 1), np.arange(others) % 2 * 2]), 33)
+        z, x = z.copy(), x.copy()
+        z2, x2 = batch(spec, np.full(60, 1), 34)[1:]
+        z[:60], x[:60] = z2, x2
+        g = binding.Gan(binding.make_config(spec, 3, 3, 600, prec, seed=2), torch.cuda.current_stream().cuda_stream)
+        dl, dz, dx = U.dev(lab), U.dev(z), U.dev(x)
+        g.train_step(dl.data_ptr(), dz.data_ptr(), dx.data_ptr(), len(lab))
+        res.append([g.get_grads(w, 1) for w in (0, 1)] + [g.get_params(w, 1) for w in (0, 1)])
+        g.close()
+    for a, b in zip(*res):
+        assert np.array_equal(a, b)
