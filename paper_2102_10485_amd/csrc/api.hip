@@ -706,8 +706,8 @@ void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool update_runn
     const ConvTile tile = layer_tile(c, gemm_mode, a.C * col_groups, gemm_rps, a.nseg);   // of the GEMM that left the partials (N = C * col_groups)
     const int tr = conv_tile_rows((int)sizeof(T), tile), gemm_phases = gemm_mode == MODE_UP ? 4 : 1;
     a.fold_running = update_running;
-    launch_bn_stats_from_partial(a, c->stat_partial, tpre_of(c, gemm_rps, tr), ub_tiles(c, a.n, gemm_rps, tr), gemm_phases, col_groups, tr,
-                                 gemm_rps, conv_stat_split((int)sizeof(T), tile, gemm_mode), c->st);
+    launch_bn_stats_from_partial(a, c->stat_partial, tpre_of(c, gemm_rps, tr), ub_tiles(c, a.n, gemm_rps, tr), ub_tiles(c, c->NB, gemm_rps, tr),
+                                 gemm_phases, col_groups, tr, gemm_rps, conv_stat_split((int)sizeof(T), tile, gemm_mode), c->st);
   }
   if (!y) return;
   Scope s(c, "bn_apply", 0, 2 * elems * sizeof(T));

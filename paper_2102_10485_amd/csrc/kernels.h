@@ -72,8 +72,8 @@ struct NormArgs {
   int param_grads;          // backward reduction: its last stage also writes dgamma / dbeta, the segments' sums added in order
 };
 // statistics from the per-tile column sums a GEMM left behind (stat_partial of ConvArgs)
-// (wsplit: sub-tiles per tile, conv_stat_split of the GEMM's tile)
-void launch_bn_stats_from_partial(const NormArgs& a, const float* partial, const int* tpre, int ub_tiles, int nphase,
+// (wsplit: sub-tiles per tile, conv_stat_split of the GEMM's tile; size_tiles: the tiles at the sizing batch, which decide the order of the sums)
+void launch_bn_stats_from_partial(const NormArgs& a, const float* partial, const int* tpre, int ub_tiles, int size_tiles, int nphase,
                                   int groups, int tile_rows, int gemm_rps, int wsplit, hipStream_t st);
 void launch_bn_running(const NormArgs& a, hipStream_t st);
 template <typename T> void launch_bn_apply(const NormArgs& a, hipStream_t st);

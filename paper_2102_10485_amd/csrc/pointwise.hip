@@ -341,7 +341,7 @@ __device__ inline void storev(bf16_t* p, const float (&v)[8]) {
 // (one 28x28 pair, 64 images), now 54 and 21.
 // Threads of a block: 16 channels x 16 slices as a rule; 64 slices, or 128 of 8 channels, when a model has so many entries that
 // sixteen slices would be long and a launch has few blocks (one pair over the whole batch).  The choice follows from
-// the configuration (tile bound per model), never from a batch.
+// the configuration (tile bound per model at the sizing batch), never from a call's batch.
 template <int SL, int CX>
 __global__ __launch_bounds__(SL * CX) void bn_stats_from_partial_kernel(NormArgs a, const float* __restrict__ partial,
                                                                         const int* __restrict__ tpre, int ub_tiles, int nphase,
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(SL * CX) void bn_stats_from_partial_kernel(NormArgs
   }
   if (a.fold_running) { a.run_mean[ro] = rm; a.run_var[ro] = rv; }     // what bn_running_kernel would do next, without the launch
 }
-void launch_bn_stats_from_partial(const NormArgs& a, const float* partial, const int* tpre, int ub_tiles, int nphase,
+void launch_bn_stats_from_partial(const NormArgs& a, const float* partial, const int* tpre, int ub_tiles, int size_tiles, int nphase,
                                   int groups, int tile_rows, int gemm_rps, int wsplit, hipStream_t st) {
   if ((long long)a.nseg * a.L * a.C == 0) return;
   if (!tpre || !partial) return launch_fail("BatchNorm statistics: no tile prefix array or no partial sums");
@@ -428,7 +428,7 @@ void launch_bn_stats_from_partial(const NormArgs& a, const float* partial, const
     hipLaunchKernelGGL(kernel, dim3((unsigned)(a.L * ((a.C + cx - 1) / cx))), dim3(sl * cx), 0, st, a, partial, tpre, ub_tiles, nphase, groups,
                        inv, tile_rows, gemm_rps, wsplit);
   };
-  const double entries = (double)ub_tiles * wsplit * nphase * groups / a.L;       // per model, by the launch's upper bound
+  const double entries = (double)size_tiles * wsplit * nphase * groups / a.L;     // per model, at the sizing batch
   if (entries > 1024) go(&bn_stats_from_partial_kernel<128, 8>, 128, 8);
   else if (entries > 128) go(&bn_stats_from_partial_kernel<64, 16>, 64, 16);
   else go(&bn_stats_from_partial_kernel<16, 16>, 16, 16);

@@ -518,3 +518,18 @@ def test_table_networks_sums_do_not_depend_on_the_other_models_samples(prec):
         g.close()
     for a, b in zip(*res):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+def test_statistics_do_not_depend_on_the_other_models_samples(prec):
+    """BatchNorm's statistics are sums in double, whose order shows where they cancel: two samples whose values are 2^55 and
+    -2^55 times the others', so that what a slice adds between them (the 64 rows between theirs) loses its last bits.  The sums come out bit
+    for bit the same alone and beside 1000 samples of nine other models."""
+    def z_keep(z):
+        z = z.copy()
+        z[7] *= 2.0 ** 55
+        z[135] = -z[7]
+        return z
+    alone, beside = (_ten_pairs(prec, 1280, 192, others, 35, z_keep) for others in (0, 1000))
+    for a, b in zip(alone[4:6], beside[4:6]):                                      # the generator's running mean and variance
+        assert np.array_equal(a, b)
