@@ -541,9 +541,15 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   const unsigned px_bytes = (unsigned)(C * SZ), row_bytes = (unsigned)(Hin * C * SZ), wtap_bytes = (unsigned)(wns * C * SZ);
   const unsigned bias = (MODE == MODE_DENSE) ? 0u : row_bytes + px_bytes;
   const int4v a_rsrc = make_rsrc(reinterpret_cast<const unsigned char*>(a_base) - bias, (unsigned long long)a_elems * SZ + bias);
-  const int4v w_rsrc = PRE ? make_rsrc(static_cast<const bf16_t*>(p.W) + (long long)l * p.w_stride, (2ull * p.w_plane + 16ull * wns * C) * 2)
-                           : make_rsrc(static_cast<const T*>(p.W) + (long long)l * p.w_stride,
-                                       (unsigned long long)(MODE == MODE_DENSE ? 1 : 16) * wns * C * SZ);
+  // PRE: a descriptor for every plane, so that a 32-bit offset need only reach over one of them
+  int4v w_rsrc[PRE ? 3 : 1];
+  if constexpr (PRE) {
+#pragma unroll
+    for (int pl = 0; pl < 3; ++pl)
+      w_rsrc[pl] = make_rsrc(static_cast<const bf16_t*>(p.W) + (long long)l * p.w_stride + pl * p.w_plane, 32ull * wns * C);
+  } else {
+    w_rsrc[0] = make_rsrc(static_cast<const T*>(p.W) + (long long)l * p.w_stride, (unsigned long long)(MODE == MODE_DENSE ? 1 : 16) * wns * C * SZ);
+  }
 
   // ---- per-thread load assignment: rows tid/CPR + RPP i, LDS position tid % CPR of the row, which holds the row's
   // 16-byte chunk (tid % CPR) ^ swizzle(row) (RPP is a multiple of the swizzle period, so the same chunk in every
@@ -693,7 +699,7 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
       for (int pl = 0; pl < 3; ++pl)
 #pragma unroll
         for (int i = 0; i < PP; ++i)
-          load16_to_lds(w_rsrc, bcol[i], (k_woff >> 1) + (unsigned)(pl * p.w_plane * 2), b_dst + (pl * BN + i * RPB) * (KB / 2));
+          load16_to_lds(w_rsrc[pl], bcol[i], k_woff >> 1, b_dst + (pl * BN + i * RPB) * (KB / 2));
     } else if constexpr (PRE) {
       // the weights as they are, value by value (tiles that are computed again: rare)
       const float* const raw = p.w_raw + (long long)l * p.raw_stride + (long long)k_wtap * wns * C;
@@ -708,7 +714,7 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < PB; ++i) load16_to_lds(w_rsrc, bcol[i], k_woff, b_dst + i * RPP * KB);
+      for (int i = 0; i < PB; ++i) load16_to_lds(w_rsrc[0], bcol[i], k_woff, b_dst + i * RPP * KB);
     }
 #pragma unroll
     for (int i = 0; i < KS; ++i) k_advance();
@@ -775,7 +781,7 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
     const unsigned off = tap * wtap_bytes + g.line * 128 + g.part * KB;
     const unsigned dst = lds0 + A_RING + buf * BN * KBB + wave * 1024;
 #pragma unroll
-    for (int i = 0; i < PB; ++i) load16_to_lds(w_rsrc, bcol[i], off, dst + i * RPP * KB);
+    for (int i = 0; i < PB; ++i) load16_to_lds(w_rsrc[0], bcol[i], off, dst + i * RPP * KB);
   };
   auto share_loop = [&]() __attribute__((always_inline)) {
     clear_acc(acc);
@@ -1087,7 +1093,7 @@ void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
     const bool pre = sizeof(T) == 4 && mode != MODE_DENSE;
     if (pre && (!a.w_raw || a.w_plane < 16LL * a.w_nstride * a.C || a.w_plane % 8)) return launch_fail("GEMM: fp32 weights that are not split");
     if ((long long)a.seg_samples * side * side * a.C * (long long)sizeof(T) >= (1LL << 31) ||
-        (pre ? (2LL * a.w_plane + 16LL * a.w_nstride * a.C) * 2 : 16LL * a.w_nstride * a.C * (long long)sizeof(T)) >= (1LL << 31))
+        16LL * a.w_nstride * a.C * (long long)sizeof(T) >= (1LL << 31))
       return launch_fail("GEMM: one segment of the gathered tensor, or one weight block, is 2 GiB or larger");
   }
   if (mode == MODE_DOWN && epi == EPI_NONE) return launch_wide<T, MODE_DOWN, EPI_NONE>(a, st);

@@ -343,3 +343,32 @@ def test_conv_up_shared_pixels(ctxs, cb, cs, hs, groups, tile_rows):
     got = U.unpack(out, True, (n, 2 * hs, 2 * hs, cb)).transpose(0, 3, 1, 2)
     ref = np.concatenate([O.conv_transpose2d(small[offs[i]:offs[i + 1]], W[i], None) for i in range(G) if groups[i]])
     assert np.max(np.abs(got - ref)) <= tolerance(binding.BF16) * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("mode", ["down", "up"])
+def test_fp32_weights_up_to_two_gibibytes(ctxs, mode):
+    """A weight block of 1.45 GB: its three bf16 planes together are beyond what a 32-bit byte offset reaches, each by itself is not."""
+    torch = U.torch_mod()
+    g = ctxs[binding.FP32]
+    g.op_tile_rows(0)
+    C, N, n = 4736, 4800, 3
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    W = torch.randn((16, N, C), device="cuda", generator=gen) * 0.02
+    offs = U.dev(np.array([0, n], np.int32))
+    side = 2 if mode == "down" else 1
+    x = torch.randn((n, side, side, C), device="cuda", generator=gen)
+    out = torch.zeros((n, 3 - side, 3 - side, N), device="cuda")
+    if mode == "down":
+        g.op_conv_down(x.data_ptr(), W.data_ptr(), out.data_ptr(), offs.data_ptr(), 1, n, C, N, 1)
+    else:
+        g.op_conv_up(x.data_ptr(), W.data_ptr(), out.data_ptr(), offs.data_ptr(), 1, n, N, C, 1)
+    x, got = x.cpu().double(), out.cpu().double()
+    ref = torch.zeros_like(got)
+    for ky in (1, 2):                                                  # side 1: the inner taps, one pixel each
+        for kx in (1, 2):
+            w = W[ky * 4 + kx].cpu().double()
+            if mode == "down":
+                ref[:, 0, 0] += x[:, ky - 1, kx - 1] @ w.T
+            else:
+                ref[:, ky - 1, kx - 1] = x[:, 0, 0] @ w.T
+    assert float((got - ref).abs().max()) <= tolerance(binding.FP32) * float(ref.abs().max())
