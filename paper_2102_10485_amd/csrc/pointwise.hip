@@ -370,7 +370,8 @@ __global__ __launch_bounds__(SL * CX) void bn_stats_from_partial_kernel(NormArgs
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         const int e = min(e0 + k * step, seq - 1);
-        t[k] = groups_inv ? (int)__umulhi((unsigned)e, groups_inv) : e;      // e / groups
+        t[k] = groups_inv ? (int)__umulhi((unsigned)e, groups_inv) : e;      // e / groups, or one more
+        if (t[k] * groups > e) --t[k];
         v[k] = p[t[k] * row_len + (long long)(e - t[k] * groups) * a.C];
       }
 #pragma unroll
@@ -421,8 +422,7 @@ void launch_bn_stats_from_partial(const NormArgs& a, const float* partial, const
   if (a.nseg > 2) return launch_fail("BatchNorm statistics: more than two segments");
   if (wsplit < 1 || tile_rows % wsplit) return launch_fail("BatchNorm statistics: the tile height is not a whole number of sub-tiles");
   if (nphase != 1 && nphase != 4) return launch_fail("BatchNorm statistics: one output phase or four");
-  // ceil(2^32 / groups): the high half of its product with an entry's number is the quotient while number * groups < 2^32
-  if ((double)ub_tiles * wsplit * groups * groups >= 4294967296.0) return launch_fail("BatchNorm statistics: too many column runs");
+  // ceil(2^32 / groups): the high half of its product with an entry's number is the quotient, or one more from number * groups = 2^32 on
   const unsigned inv = groups > 1 ? (unsigned)(((1ULL << 32) + groups - 1) / groups) : 0;
   const auto go = [&](auto kernel, int sl, int cx) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)(a.L * ((a.C + cx - 1) / cx))), dim3(sl * cx), 0, st, a, partial, tpre, ub_tiles, nphase, groups,

@@ -533,3 +533,32 @@ def test_statistics_do_not_depend_on_the_other_models_samples(prec):
     alone, beside = (_ten_pairs(prec, 1280, 192, others, 35, z_keep) for others in (0, 1000))
     for a, b in zip(alone[4:6], beside[4:6]):                                      # the generator's running mean and variance
         assert np.array_equal(a, b)
+
+
+def test_generate_with_a_first_map_of_many_pixels():
+    """A 112 x 112 first feature map (12544 column runs behind the linear layer) for sixteen models: BatchNorm statistics of the batch
+    against 64-bit sums."""
+    torch = U.torch_mod()
+    spec = dict(cond_g=0, cond_d=0, z_dim=8, img_c=1, img_hw=448, g_h0=112, g_ch=[64, 64], d_ch=[64] * 6)
+    L, n = 16, 20
+    g = binding.Gan(binding.make_config(spec, L, L, n, binding.BF16, seed=4), torch.cuda.current_stream().cuda_stream)
+    rng = np.random.default_rng(5)
+    lab = np.concatenate([np.arange(L), [5, 5, 15, 0]]).astype(np.int32)
+    z = rng.normal(size=(n, 8)).astype(np.float32)
+    dl, dz = U.dev(lab), U.dev(z)
+    out = torch.zeros((n, 1, 448, 448), device="cuda")
+    g.generate(dl.data_ptr(), dz.data_ptr(), n, out.data_ptr(), 0)
+    got = out.cpu().numpy()
+    for l in (5, 15):
+        p = torch.from_numpy(g.get_params(0, l).astype(np.float64))
+        sel = np.flatnonzero(lab == l)
+        fc, rest = p[:64 * 112 * 112 * 8].view(-1, 8), p[64 * 112 * 112 * 8:]
+        h = (torch.from_numpy(z[sel]).double() @ fc.T).view(len(sel), 64, 112, 112)
+        h = torch.relu(torch.nn.functional.batch_norm(h, None, None, rest[:64], rest[64:128], True, 0.0, 1e-5))
+        rest = rest[128:]
+        h = torch.nn.functional.conv_transpose2d(h, rest[:65536].view(64, 64, 4, 4), None, 2, 1)
+        h = torch.relu(torch.nn.functional.batch_norm(h, None, None, rest[65536:65600], rest[65600:65664], True, 0.0, 1e-5))
+        rest = rest[65664:]
+        ref = torch.tanh(torch.nn.functional.conv_transpose2d(h, rest[:1024].view(64, 1, 4, 4), rest[1024:1025], 2, 1)).numpy()
+        assert U.rel_l2(got[sel], ref) <= TOL[binding.BF16]
+    g.close()
