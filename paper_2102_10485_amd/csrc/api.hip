@@ -49,6 +49,7 @@ struct ConvLayer {
   // summed-tap k4 weights in the storage-type arenas
   int cs_real = 0, cb_real = 0;
   long long w4 = -1;
+  long long part = -1;                                  // fp32 storage, layers on the GEMM engine: offset into a plane of the split weights
 };
 
 struct Net {
@@ -62,13 +63,14 @@ struct Net {
   std::vector<long long> ext2int;  // documented index -> internal index
   std::vector<long long> bn_ext2int;   // documented running-statistics index -> internal (empty: identical)
   std::vector<int> ext_kind;       // per documented element: 0 weight, 1 gamma, 2 zero-initialised (built-in initialiser)
-  // networks as printed in the paper's tables (G): k4 weights with summed taps, [tap][cb][cs] and [tap][cs][cb]
+  // networks as printed in the paper's tables (G): k4 weights with summed taps, [tap][cb][cs] and (bf16 storage) [tap][cs][cb]
   long long fc_bias = -1, P4 = 0;
   void *w4u = nullptr, *w4d = nullptr;
   float *theta = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
   void *shadow_u = nullptr, *shadow_d = nullptr;   // bf16 storage: copies [tap][cb][cs] and [tap][cs][cb] (fp32: shadow_u is theta)
   // fp32 storage: the weights of the convolutions on the GEMM engine (the k4 weights, where there are any) as three bf16 planes in both
-  // layouts, [model][plane][P or P4]
+  // layouts, [model][plane][PS]
+  long long PS = 0;
   unsigned short *split_u = nullptr, *split_d = nullptr;
   float *run_mean = nullptr, *run_var = nullptr;
   int* t = nullptr;
@@ -426,6 +428,9 @@ void build_layout_paper(gan_ctx* c) {
   }
 }
 
+// whether the GEMM engine runs this convolution (all but the ones next to the image)
+bool on_engine(const gan_ctx* c, const Net& n, size_t i) { return &n == &c->G ? i + 1 < n.conv.size() : i > 0; }
+
 bool alloc_net(gan_ctx* c, Net& n) {
   const size_t tot = (size_t)c->L * n.P;
   bool ok = dev_alloc(c, (void**)&n.theta, tot * 4) && dev_alloc(c, (void**)&n.m, tot * 4) &&
@@ -438,7 +443,13 @@ bool alloc_net(gan_ctx* c, Net& n) {
     if (!dev_alloc(c, &n.shadow_u, tot * 2) || !dev_alloc(c, &n.shadow_d, tot * 2)) return false;
     hipMemsetAsync(n.shadow_d, 0, tot * 2, c->st);
   } else {
-    const size_t parts = (size_t)c->L * (n.P4 ? n.P4 : n.P) * 6;
+    for (size_t i = 0; i < n.conv.size(); ++i) {
+      ConvLayer& cl = n.conv[i];
+      if (!on_engine(c, n, i)) continue;
+      cl.part = n.PS;
+      n.PS += (long long)16 * cl.Cb * cl.Cs;
+    }
+    const size_t parts = (size_t)c->L * n.PS * 6;
     if (!dev_alloc(c, (void**)&n.split_u, parts) || !dev_alloc(c, (void**)&n.split_d, parts)) return false;
     n.shadow_u = n.theta;
   }
@@ -542,13 +553,12 @@ void refresh_transposes(gan_ctx* c, Net& n, bool isG) {
   // layers run by the GEMM engine in "down" form need [tap][cs][cb]
   for (size_t i = 0; i < n.conv.size(); ++i) {
     const ConvLayer& cl = n.conv[i];
-    const bool gemm = isG ? (i + 1 < n.conv.size()) : (i > 0);
-    if (!gemm) continue;
+    if (!on_engine(c, n, i)) continue;
     Scope s(c, "transpose_w", 0, (double)c->L * 16 * cl.Cb * cl.Cs * 2 * sizeof(T));
     if (c->bf16)
       launch_transpose_w<bf16_t, bf16_t>((const bf16_t*)n.shadow_u + cl.w, (bf16_t*)n.shadow_d + cl.w, n.P, c->L, cl.Cb, cl.Cs, c->st);
     else
-      launch_split_weights({n.theta + cl.w, n.split_u + cl.w, n.split_d + cl.w, n.P, n.P, c->L, cl.Cb, cl.Cs}, c->st);
+      launch_split_weights({n.theta + cl.w, n.split_u + cl.part, n.split_d + cl.part, n.P, n.PS, c->L, cl.Cb, cl.Cs}, c->st);
   }
 }
 // k4 weights with summed taps of G's Upsample + Conv k3 blocks, from the 3 x 3 master weights
@@ -558,7 +568,7 @@ void paper_rebuild_w4(gan_ctx* c) {
   for (size_t i = 0; i + 1 < G.conv.size(); ++i) {
     const ConvLayer& cl = G.conv[i];
     launch_w3_to_w4<T>(G.theta + cl.w, (T*)G.w4u + cl.w4, c->bf16 ? (T*)G.w4d + cl.w4 : nullptr, c->L, cl.Cb, cl.Cs, c->st, G.P, G.P4);
-    if (!c->bf16) launch_split_weights({(const float*)G.w4u + cl.w4, G.split_u + cl.w4, G.split_d + cl.w4, G.P4, G.P4, c->L, cl.Cb, cl.Cs}, c->st);
+    if (!c->bf16) launch_split_weights({(const float*)G.w4u + cl.w4, G.split_u + cl.part, G.split_d + cl.part, G.P4, G.PS, c->L, cl.Cb, cl.Cs}, c->st);
   }
 }
 void refresh_shadows(gan_ctx* c) {
@@ -587,7 +597,7 @@ Weights layer_weights(const gan_ctx* c, const Net& net, const ConvLayer& cl, boo
   const bool k4 = cl.w4 >= 0;                          // summed taps (the networks of the tables, G)
   const long long off = k4 ? cl.w4 : cl.w, P = k4 ? net.P4 : net.P;
   if (c->bf16) return {(const bf16_t*)(k4 ? (up ? net.w4u : net.w4d) : (up ? net.shadow_u : net.shadow_d)) + off, P};
-  return {(up ? net.split_u : net.split_d) + off, 3 * P, P, (k4 ? (const float*)net.w4u : net.theta) + off, P, up ? cl.Cs : 1, up ? 1 : cl.Cs};
+  return {(up ? net.split_u : net.split_d) + cl.part, 3 * net.PS, net.PS, (k4 ? (const float*)net.w4u : net.theta) + off, P, up ? cl.Cs : 1, up ? 1 : cl.Cs};
 }
 template <typename T>
 void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, const Weights& W, void* Out,
@@ -1171,16 +1181,15 @@ void paper_adam_g(gan_ctx* c) {
 // The planned update of one network: every convolution weight the GEMM engine also reads in "down" form is a tiled
 // region (the update writes that transposed copy too), in layer order; the rest of the block is the gaps.
 template <typename T>
-AdamArgs adam_args(gan_ctx* c, Net& net, bool isG) {
+AdamArgs adam_args(gan_ctx* c, Net& net) {
   AdamArgs a = {};
   a.theta = net.theta; a.m = net.m; a.v = net.v; a.g = net.g; a.shadow = c->bf16 ? net.shadow_u : nullptr;
   a.P = net.P; a.L = c->L; a.counts = c->rb.counts; a.t = net.t; a.bc = net.bc;
   a.lr = c->cfg.lr; a.beta1 = c->cfg.beta1; a.beta2 = c->cfg.beta2; a.eps = c->cfg.adam_eps;
-  a.shadow_t = net.shadow_d; a.split_u = net.split_u; a.split_d = net.split_d;
+  a.shadow_t = net.shadow_d; a.split_u = net.split_u; a.split_d = net.split_d; a.plane = net.PS;
   for (size_t i = 0; i < net.conv.size(); ++i) {
-    const bool gemm = isG ? (i + 1 < net.conv.size()) : (i > 0);
-    if (!gemm) continue;
-    a.reg_w[a.nregions] = net.conv[i].w; a.reg_cb[a.nregions] = net.conv[i].Cb; a.reg_cs[a.nregions] = net.conv[i].Cs;
+    if (!on_engine(c, net, i)) continue;
+    a.reg_w[a.nregions] = net.conv[i].w; a.reg_part[a.nregions] = net.conv[i].part; a.reg_cb[a.nregions] = net.conv[i].Cb; a.reg_cs[a.nregions] = net.conv[i].Cs;
     ++a.nregions;
   }
   adam_plan(a);
@@ -1215,7 +1224,7 @@ void adam_rest_call(gan_ctx* c, Net& net, bool isG, const AdamArgs& a) {
 // the whole update on the caller's stream
 template <typename T>
 void adam_call(gan_ctx* c, Net& net, bool isG) {
-  const AdamArgs a = adam_args<T>(c, net, isG);
+  const AdamArgs a = adam_args<T>(c, net);
   adam_region_call<T>(c, a, -1, c->st);
   adam_rest_call<T>(c, net, isG, a);
 }
@@ -1257,7 +1266,7 @@ void train_step(gan_ctx* c, const int32_t* label_ids, const float* noise, const 
   loss_call(c, n, 0);                              // Eq. 3
   c->order_next = 0;
   {
-    const AdamArgs aD = adam_args<T>(c, c->D, false);
+    const AdamArgs aD = adam_args<T>(c, c->D);
     d_backward<T>(c, n, 0, 2, true, false, &aD);   // weight gradients and the convolutions' updates beside the chain
     adam_rest_call<T>(c, c->D, false, aD);
     order_after(c, c->st, side_stream(c));
@@ -1266,7 +1275,7 @@ void train_step(gan_ctx* c, const int32_t* label_ids, const float* noise, const 
   loss_call(c, n, 1);                              // Eq. 4 (negated: minimised)
   d_backward<T>(c, n, 1, 1, false, true);          // only data gradients: theta_D is not G's to move
   {
-    const AdamArgs aG = adam_args<T>(c, c->G, true);
+    const AdamArgs aG = adam_args<T>(c, c->G);
     g_backward<T>(c, n, &aG);
     adam_rest_call<T>(c, c->G, true, aG);
     order_after(c, c->st, side_stream(c));
@@ -1482,7 +1491,7 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
       size_t per = 0;
       for (size_t i = 0; i + 1 < c->G.conv.size(); ++i) per = std::max(per, (size_t)16 * c->G.conv[i].Cb * c->G.conv[i].Cs);
       const ConvLayer& last = c->G.conv.back();
-      ok = ok && dev_alloc(c, &c->G.w4u, (size_t)L * c->G.P4 * es) && dev_alloc(c, &c->G.w4d, (size_t)L * c->G.P4 * es) &&
+      ok = ok && dev_alloc(c, &c->G.w4u, (size_t)L * c->G.P4 * es) && (!c->bf16 || dev_alloc(c, &c->G.w4d, (size_t)L * c->G.P4 * es)) &&
            dev_alloc(c, (void**)&c->dw4, (size_t)L * per * 4) &&
            dev_alloc(c, (void**)&c->c3_part, (size_t)conv3_wgrad_splits(L) * L * 9 * last.Cb * last.Cs * 4);
     }

@@ -191,8 +191,10 @@ struct AdamArgs {
   float* theta; float* m; float* v; const float* g;
   void* shadow;             // storage-type copy of theta (NULL when the storage type is fp32)
   void* shadow_t;           // storage-type copy with every region below transposed: [tap][cs][cb]
-  // fp32 storage, in place of the two copies: the regions as three bf16 planes P elements apart, as they are and transposed (launch_split_weights)
+  // fp32 storage, in place of the two copies: the regions, from element reg_part of a plane on, as three bf16 planes, as they are and
+  // transposed (launch_split_weights; models 3 * plane elements apart)
   unsigned short *split_u, *split_d;
+  long long plane;
   long long P;              // elements per model
   int L;
   const int* counts;
@@ -202,7 +204,7 @@ struct AdamArgs {
   // Convolution weights [16][Cb][Cs] (Cb, Cs multiples of 64) that need the transposed copy: updated tile by tile.
   // Everything else is the list of gaps between them, updated as flat ranges.
   int nregions;
-  long long reg_w[ADAM_MAX_REGIONS];
+  long long reg_w[ADAM_MAX_REGIONS], reg_part[ADAM_MAX_REGIONS];
   int reg_cb[ADAM_MAX_REGIONS], reg_cs[ADAM_MAX_REGIONS];
   int reg_tile0[ADAM_MAX_REGIONS + 1];    // prefix of 64 x 64 tiles (filled by the launcher)
   int ngaps;

@@ -1041,7 +1041,7 @@ __global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a) {
     const int tcs = q % tcs_n; q /= tcs_n;
     const int tcb = q % tcb_n;
     const int tap = q / tcb_n;
-    const long long base = (long long)l * a.P + a.reg_w[r];
+    const long long base = (long long)l * a.P + a.reg_w[r], part = 3 * (long long)l * a.plane + a.reg_part[r];
     const float bc1 = a.bc[2 * l], bc2 = a.bc[2 * l + 1];
     const int c4 = (threadIdx.x & 15) * 4, r0 = threadIdx.x >> 4;
     const long long o0 = base + ((long long)tap * Cb + tcb * 64 + r0) * Cs + tcs * 64 + c4;
@@ -1064,7 +1064,7 @@ __global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a) {
       st_stream(a.m + o, ms[i]);
       st_stream(a.v + o, vs[i]);
       if constexpr (sizeof(T) == 2) store4(static_cast<bf16_t*>(a.shadow) + o, tt);
-      else store_split4(a.split_u + 2 * (long long)l * a.P + o, a.P, tt);
+      else store_split4(a.split_u + part + (o - base), a.plane, tt);
 #pragma unroll
       for (int e = 0; e < 4; ++e) *reinterpret_cast<T*>(tile + (c4 + e) * TSTRIDE + row * (int)sizeof(T)) = from_float<T>(tt[e]);
     }
@@ -1075,7 +1075,7 @@ __global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a) {
       const uint4* src = reinterpret_cast<const uint4*>(tile + cs * TSTRIDE + ch * (int)sizeof(T));
       const long long o = ((long long)tap * Cs + tcs * 64 + cs) * Cb + tcb * 64 + ch;
       if constexpr (sizeof(T) == 2) *reinterpret_cast<uint4*>(static_cast<T*>(a.shadow_t) + base + o) = src[0];
-      else store_split8(a.split_d + 2 * (long long)l * a.P + base + o, a.P, src[0], src[1]);
+      else store_split8(a.split_d + part + o, a.plane, src[0], src[1]);
     }
     __syncthreads();                                              // the tile is rewritten by the next pair
   }
@@ -1102,7 +1102,7 @@ bool adam_plan(AdamArgs& a) {
       ++a.ngaps;
     }
     if (r < a.nregions) {
-      if (a.reg_cb[r] % 64 || a.reg_cs[r] % 64 || (a.shadow ? !a.shadow_t : !a.split_u || !a.split_d)) {
+      if (a.reg_cb[r] % 64 || a.reg_cs[r] % 64 || (a.shadow ? !a.shadow_t : !a.split_u || !a.split_d || a.plane % 8)) {
         launch_fail("Adam: tiled regions need channel counts that are multiples of 64");
         return false;
       }

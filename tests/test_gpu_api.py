@@ -110,3 +110,29 @@ def test_checkpoint_calls_restore_a_context_bit_for_bit(prec):
     assert np.array_equal(a.get_losses()[0], b.get_losses()[0])
     a.close()
     b.close()
+
+
+def _bytes_held(spec, n_models, n):
+    """Device memory that a context takes."""
+    torch = U.torch_mod()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    g = binding.Gan(binding.make_config(spec, n_models, n_models, n, binding.FP32), torch.cuda.current_stream().cuda_stream)
+    held = before - torch.cuda.mem_get_info()[0]
+    g.close()
+    return held
+
+
+def test_memory_of_parameters_in_fp32():
+    """A parameter of a linear layer takes its value, its gradient and two moments, 16 bytes; one of a convolution between feature maps
+    two times three bf16 parts besides.  The tables' generator holds its convolutions' summed taps (16 for every 9 weights) once."""
+    wide = lambda z: dict(cond_g=0, cond_d=0, z_dim=z, img_c=1, img_hw=16, g_h0=4, g_ch=[1024, 64], d_ch=[64, 64])
+    per = (_bytes_held(wide(1024), 1, 2) - _bytes_held(wide(64), 1, 2)) / (1024 * 16 * 960)
+    assert 15.5 <= per <= 16.5
+    # one more model of 512 -> 512 -> 64 channels: theta, m, v, g of 9 weights, k4 values, their parts twice and one k4 gradient
+    spec = dict(family="paper", cond_g=0, cond_d=0, z_dim=16, img_c=1, img_hw=16, g_h0=4, g_ch=[512, 512, 64], d_ch=[16, 16])
+    per = (_bytes_held(spec, 24, 24) - _bytes_held(spec, 16, 24)) / 8
+    w = 512 * 512 + 512 * 64
+    linear = 16 * 512 * (64 + 1)
+    want = 16 * (9 * w + linear) + 16 * w * (4 + 12) + 16 * 512 * 512 * 4
+    assert 0.97 * want <= per <= 1.05 * want, (per, want)
