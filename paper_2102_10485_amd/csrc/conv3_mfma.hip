@@ -223,11 +223,11 @@ __device__ inline T c3_patch_value(const T* D, int q, int tap, int co) {
 // ---- data gradient ---------------------------------------------------------------------------------------------------
 // One block per sample, the weights (transposed, rounded to T) in LDS once, the next patch's dout halo on its way while
 // the current patch is multiplied.
-// With BatchNorm and activation between the feature tensor x and this layer, the gradient is not stored (it takes two MFMA steps to make)
+// BatchNorm and activation lie between the feature tensor x and this layer, and the gradient is not stored (it takes two MFMA steps to make)
 // but made twice: C3_SUMS reads x and leaves the sample's sums of g and g xhat for BatchNorm's backward pass, g being the gradient times the
 // activation's derivative; C3_APPLY reads x and writes the gradient with respect to it.  6400 samples of 32 x 32 x 64, bf16: 263 us
 // and 376, where storing it (233), reducing it (275) and applying it (476) took 984.
-enum { C3_PLAIN = 0, C3_SUMS = 1, C3_APPLY = 2 };
+enum { C3_SUMS = 0, C3_APPLY = 1 };
 template <typename T, int CIN, int WHAT>
 __global__ __launch_bounds__(256) void conv3_dgrad_kernel(Conv3Args a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -280,32 +280,29 @@ __global__ __launch_bounds__(256) void conv3_dgrad_kernel(Conv3Args a) {
   static_assert(64 * cpr % 256 == 0 && 256 % cpr == 0, "a thread's channels");
   C3Norm<T> norm;
   float s1[EPV], s2[EPV];                                      // C3_SUMS: the sums ; C3_APPLY: the model's means of them
-  if constexpr (WHAT != C3_PLAIN) {
-    norm.load(a, l, tid % cpr);
-    const float inv = 1.0f / ((float)(a.offs[l + 1] - a.offs[l]) * (float)(H * H));
+  norm.load(a, l, tid % cpr);
+  const float inv = 1.0f / ((float)(a.offs[l + 1] - a.offs[l]) * (float)(H * H));
 #pragma unroll
-    for (int k = 0; k < EPV; ++k) {
-      const long long o = ((long long)l * CIN + (tid % cpr) * EPV + k) * 2;
-      s1[k] = WHAT == C3_APPLY ? a.bn_sums[o] * inv : 0.f;
-      s2[k] = WHAT == C3_APPLY ? a.bn_sums[o + 1] * inv : 0.f;
-    }
+  for (int k = 0; k < EPV; ++k) {
+    const long long o = ((long long)l * CIN + (tid % cpr) * EPV + k) * 2;
+    s1[k] = WHAT == C3_APPLY ? a.bn_sums[o] * inv : 0.f;
+    s2[k] = WHAT == C3_APPLY ? a.bn_sums[o + 1] * inv : 0.f;
   }
   const T* xs = static_cast<const T*>(a.in) + (long long)j * H * H * CIN;
   uint4 xv[NX];
   for (int tile = 0; tile < tiles * tiles; ++tile) {
     const int y0 = (tile / tiles) * C3_TS, x0 = (tile % tiles) * C3_TS;
-    if constexpr (WHAT != C3_PLAIN)                            // this patch's x, on its way while the gradient is made
 #pragma unroll
-      for (int k = 0; k < NX; ++k) {
-        const int i = tid + 256 * k, q = i / cpr, ch = i - q * cpr;
-        const int y = y0 + q / C3_TS, x = x0 + q % C3_TS;
-        xv[k] = make_uint4(0, 0, 0, 0);
-        if (y < H && x < H) {
-          typedef unsigned u4 __attribute__((ext_vector_type(4)));
-          const u4 t = __builtin_nontemporal_load(reinterpret_cast<const u4*>(reinterpret_cast<const unsigned char*>(xs + ((long long)y * H + x) * CIN) + ch * 16));
-          xv[k] = make_uint4(t.x, t.y, t.z, t.w);
-        }
+    for (int k = 0; k < NX; ++k) {                             // this patch's x, on its way while the gradient is made
+      const int i = tid + 256 * k, q = i / cpr, ch = i - q * cpr;
+      const int y = y0 + q / C3_TS, x = x0 + q % C3_TS;
+      xv[k] = make_uint4(0, 0, 0, 0);
+      if (y < H && x < H) {
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        const u4 t = __builtin_nontemporal_load(reinterpret_cast<const u4*>(reinterpret_cast<const unsigned char*>(xs + ((long long)y * H + x) * CIN) + ch * 16));
+        xv[k] = make_uint4(t.x, t.y, t.z, t.w);
       }
+    }
     __syncthreads();                                           // the previous patch: multiplied and written out
 #pragma unroll
     for (int k = 0; k < ND; ++k) {
@@ -347,25 +344,23 @@ __global__ __launch_bounds__(256) void conv3_dgrad_kernel(Conv3Args a) {
       const int y = y0 + q / C3_TS, x = x0 + q % C3_TS;
       if (y >= H || x >= H) continue;
       uint4 d = *reinterpret_cast<const uint4*>(OUT + q * orow + ch * 16);
-      if constexpr (WHAT != C3_PLAIN) {
-        const T* xe = reinterpret_cast<const T*>(&xv[k]);
-        const T* de = reinterpret_cast<const T*>(&d);
-        float v[EPV];
+      const T* xe = reinterpret_cast<const T*>(&xv[k]);
+      const T* de = reinterpret_cast<const T*>(&d);
+      float v[EPV];
 #pragma unroll
-        for (int e = 0; e < EPV; ++e) {
-          const float xh = (to_float(xe[e]) - norm.mu[e]) * norm.rs[e];
-          const float u = norm.ga[e] * xh + norm.be[e], dd = to_float(de[e]);
-          const float g = u > 0.f ? dd : dd * norm.slope;
-          if (WHAT == C3_SUMS) { s1[e] += g; s2[e] += g * xh; }
-          else v[e] = norm.sc[e] * (g - s1[e] - xh * s2[e]);
-        }
-        if (WHAT == C3_SUMS) continue;
-        C3Norm<T>::pack(v, d);
+      for (int e = 0; e < EPV; ++e) {
+        const float xh = (to_float(xe[e]) - norm.mu[e]) * norm.rs[e];
+        const float u = norm.ga[e] * xh + norm.be[e], dd = to_float(de[e]);
+        const float g = u > 0.f ? dd : dd * norm.slope;
+        if (WHAT == C3_SUMS) { s1[e] += g; s2[e] += g * xh; }
+        else v[e] = norm.sc[e] * (g - s1[e] - xh * s2[e]);
       }
+      if (WHAT == C3_SUMS) continue;
+      C3Norm<T>::pack(v, d);
       typedef unsigned u4 __attribute__((ext_vector_type(4)));
       u4 o; o.x = d.x; o.y = d.y; o.z = d.z; o.w = d.w;
       u4* dst = reinterpret_cast<u4*>(reinterpret_cast<unsigned char*>(din + ((long long)y * H + x) * CIN) + ch * 16);
-      if constexpr (WHAT == C3_APPLY) __builtin_nontemporal_store(o, dst); else *dst = o;
+      __builtin_nontemporal_store(o, dst);
     }
   }
   if constexpr (WHAT == C3_SUMS) {
@@ -386,8 +381,8 @@ __global__ __launch_bounds__(256) void conv3_dgrad_kernel(Conv3Args a) {
 }
 
 // ---- weight gradient -------------------------------------------------------------------------------------------------
-// NORM: as in the forward kernel
-template <typename T, int CIN, bool NORM>
+// The features are the input's BatchNorm and activation, as in the forward kernel.
+template <typename T, int CIN>
 __global__ __launch_bounds__(256) void conv3_wgrad_kernel(Conv3Args a, float* __restrict__ part, int splits) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   constexpr int SZ = (int)sizeof(T);
@@ -467,7 +462,7 @@ __global__ __launch_bounds__(256) void conv3_wgrad_kernel(Conv3Args a, float* __
     for (int k = 0; k < NI; ++k) {
       const int i = tid + 256 * k;
       const int ch = i >> 6, q = i & 63;
-      if (NORM && (inside >> k & 1)) {
+      if (inside >> k & 1) {
         C3Norm<T> norm;                                        // (a wave's channels: the parameters come out of the caches)
         norm.load(a, l, ch);
         ireg[k] = norm.apply(ireg[k]);
@@ -529,7 +524,7 @@ __device__ inline uint2 c3_read_tr16(const unsigned char* p) {
   const c3_short4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) c3_short4*)(p));
   return __builtin_bit_cast(uint2, v);
 }
-template <int CIN, bool NORM>
+template <int CIN>
 __global__ __launch_bounds__(256) void conv3_wgrad_tr_kernel(Conv3Args a, float* __restrict__ part, int splits) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   typedef bf16_t T;
@@ -579,7 +574,7 @@ __global__ __launch_bounds__(256) void conv3_wgrad_tr_kernel(Conv3Args a, float*
   unsigned inside = 0;
   static_assert(256 % cpr == 0, "a thread's channels");
   C3Norm<T> norm;
-  if constexpr (NORM) norm.load(a, l, tid % cpr);
+  norm.load(a, l, tid % cpr);
   const int per_sample = tiles * tiles, npatch = (n_hi - n_lo) * per_sample;
   auto fetch = [&](int idx) {
     const int n = n_lo + idx / per_sample, tile = idx % per_sample;
@@ -618,7 +613,7 @@ __global__ __launch_bounds__(256) void conv3_wgrad_tr_kernel(Conv3Args a, float*
     for (int k = 0; k < NI; ++k) {
       const int i = tid + 256 * k;
       const int q = i / cpr, ch = i - q * cpr;
-      if (NORM && (inside >> k & 1)) ireg[k] = norm.apply(ireg[k]);
+      if (inside >> k & 1) ireg[k] = norm.apply(ireg[k]);
       *reinterpret_cast<uint4*>(Fq + q * rowB + ch * 16) = ireg[k];
     }
     if (idx + 1 < npatch) fetch(idx + 1);
@@ -681,42 +676,42 @@ template <typename K> static void c3_allow_lds(K kernel, size_t lds) {
   if (lds > 48 * 1024)   // above the default dynamic limit: ask for it (idempotent, cheap)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
-// kernel(std::integral_constant<int, Cin>, std::integral_constant<bool, NORM>) for this call
+// f(std::integral_constant<int, Cin>) for this call
 template <typename F> static void c3_pick(const Conv3Args& a, F&& f) {
-  const bool norm = a.bn_mean != nullptr;
-  if (a.Cin == 64) { if (norm) f(std::integral_constant<int, 64>(), std::true_type()); else f(std::integral_constant<int, 64>(), std::false_type()); }
-  else { if (norm) f(std::integral_constant<int, 128>(), std::true_type()); else f(std::integral_constant<int, 128>(), std::false_type()); }
+  if (a.Cin == 64) f(std::integral_constant<int, 64>()); else f(std::integral_constant<int, 128>());
 }
-static bool c3_norm_ok(const Conv3Args& a) { return !a.bn_mean || (a.bn_rstd && a.bn_gamma && a.bn_beta); }
+static bool c3_norm_ok(const Conv3Args& a) { return a.bn_mean && a.bn_rstd && a.bn_gamma && a.bn_beta; }
+// without bn_mean: `in` are the features themselves (generation with running statistics, which are part of the GEMM that makes them)
 template <typename T> void launch_conv3_fwd(const Conv3Args& a, hipStream_t st) {
   if (a.n == 0) return;
-  if (!conv3_ok(a) || !a.in || !a.out || !a.bias || !c3_norm_ok(a)) return launch_fail("image-side k3 convolution: unsupported shape or null operand");
+  if (!conv3_ok(a) || !a.in || !a.out || !a.bias || (a.bn_mean && !c3_norm_ok(a))) return launch_fail("image-side k3 convolution: unsupported shape or null operand");
   const int nct = 9 * a.CO > 32 ? 2 : 1;
   const size_t lds = (size_t)(C3_HALO * C3_HALO + 32 * nct) * (a.Cin * sizeof(T) + 16) + (size_t)32 * nct * C3_RTS;
-  c3_pick(a, [&](auto cin, auto norm) {
-    const auto kernel = &conv3_fwd_kernel<T, decltype(cin)::value, decltype(norm)::value>;
-    c3_allow_lds(kernel, lds);
-    hipLaunchKernelGGL(kernel, dim3(a.n), dim3(256), lds, st, a);
+  c3_pick(a, [&](auto cin) {
+    const auto go = [&](auto kernel) {
+      c3_allow_lds(kernel, lds);
+      hipLaunchKernelGGL(kernel, dim3(a.n), dim3(256), lds, st, a);
+    };
+    if (a.bn_mean) go(&conv3_fwd_kernel<T, decltype(cin)::value, true>); else go(&conv3_fwd_kernel<T, decltype(cin)::value, false>);
   });
 }
-// with bn_mean: the sums (bn_part, per sample) without bn_sums, else the gradient with respect to a.in, the tensor in front of the BatchNorm
+// without bn_sums: the sums (bn_part, per sample), else the gradient with respect to a.in, the tensor in front of the BatchNorm
 template <typename T> void launch_conv3_dgrad(const Conv3Args& a, hipStream_t st) {
   if (a.n == 0) return;
-  const bool sums = a.bn_mean && !a.bn_sums;
-  if (!conv3_ok(a) || !a.dout || (!sums && !a.din) || !c3_norm_ok(a) || (a.bn_mean && !a.in) || (sums && !a.bn_part))
+  const bool sums = !a.bn_sums;
+  if (!conv3_ok(a) || !a.dout || (sums ? !a.bn_part : !a.din) || !c3_norm_ok(a) || !a.in)
     return launch_fail("image-side k3 convolution: unsupported shape or null operand");
   const int SZ = (int)sizeof(T);
   const size_t prow = (size_t)(9 * C3_MAXCO * SZ + 31) / 32 * 32 + 16;
   const size_t lds = std::max((size_t)((C3_HALO * C3_HALO * C3_MAXCO * SZ + 15) & ~15) + (64 + a.Cin) * prow + (size_t)64 * (a.Cin * SZ + 16),
                               sums ? (size_t)256 * (16 / SZ) * 8 : (size_t)0);
-  c3_pick(a, [&](auto cin, auto norm) {
+  c3_pick(a, [&](auto cin) {
     const auto go = [&](auto kernel) {
       c3_allow_lds(kernel, lds);
       hipLaunchKernelGGL(kernel, dim3(a.n), dim3(256), lds, st, a);
     };
     constexpr int C = decltype(cin)::value;
-    if constexpr (!decltype(norm)::value) go(&conv3_dgrad_kernel<T, C, C3_PLAIN>);
-    else if (sums) go(&conv3_dgrad_kernel<T, C, C3_SUMS>);
+    if (sums) go(&conv3_dgrad_kernel<T, C, C3_SUMS>);
     else go(&conv3_dgrad_kernel<T, C, C3_APPLY>);
   });
 }
@@ -730,14 +725,13 @@ template <typename T> void launch_conv3_wgrad(const Conv3Args& a, float* part, f
   const size_t halo = (C3_HALO * C3_HALO * C3_MAXCO * SZ + 15) & ~15;
   const size_t lds = SZ == 2 ? std::max(halo + (size_t)64 * (a.Cin * SZ + 16), (size_t)MT * 32 * a.Cin * 4)
                              : halo + std::max((MT * 32 + a.Cin) * krow, (size_t)MT * 32 * a.Cin * 4);
-  c3_pick(a, [&](auto cin, auto norm) {
+  c3_pick(a, [&](auto cin) {
     constexpr int C = decltype(cin)::value;
-    constexpr bool NORM = decltype(norm)::value;
     const auto go = [&](auto kernel) {
       c3_allow_lds(kernel, lds);
       hipLaunchKernelGGL(kernel, dim3(splits, a.L), dim3(256), lds, st, a, part, splits);
     };
-    if constexpr (sizeof(T) == 2) go(&conv3_wgrad_tr_kernel<C, NORM>); else go(&conv3_wgrad_kernel<T, C, NORM>);
+    if constexpr (sizeof(T) == 2) go(&conv3_wgrad_tr_kernel<C>); else go(&conv3_wgrad_kernel<T, C>);
   });
   const long long tot = (long long)a.L * 9 * a.CO * a.Cin;
   hipLaunchKernelGGL(conv3_wgrad_final_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, a, part, dw, dw_stride, splits);

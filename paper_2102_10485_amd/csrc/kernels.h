@@ -300,7 +300,7 @@ struct Conv3Args {
   const void* in;           // features [samples][H][H][Cin] (segment 0)
   void* out;                // forward: tanh(conv + bias) into segment out_seg of the image buffer
   const void* dout;         // backward: gradient w.r.t. the pre-tanh output, segment out_seg of the image-gradient buffer
-  void* din;                // backward: gradient w.r.t. the features
+  void* din;                // backward: gradient w.r.t. `in`
   const float* w;           // [9][CO][Cin] of model 0, w_stride between models
   long long w_stride;
   const float* bias;        // [CO] of model 0
@@ -311,13 +311,13 @@ struct Conv3Args {
   int out_seg, seg_samples;
   float* user;              // forward: the caller's NCHW fp32 images, written in place of out through perm (or NULL)
   const int* perm;
-  // with bn_mean: `in` is the tensor in front of the BatchNorm (batch statistics [L][Cin]; gamma, beta of model 0, bn_pstride between models) and
+  // with bn_mean (the backward kernels always): `in` is the tensor in front of the BatchNorm (batch statistics [L][Cin]; gamma, beta of model 0, bn_pstride between models) and
   // the activation (slope below zero) whose result the features are
   const float *bn_mean, *bn_rstd, *bn_gamma, *bn_beta;
   long long bn_pstride;
   float bn_slope;
   float* bn_part;           // data gradient without bn_sums: [n][Cin][2], the sums of every sample that BatchNorm's backward pass wants
-  const float* bn_sums;     // [L][Cin][2]: with them the data gradient is that of `in`
+  const float* bn_sums;     // [L][Cin][2], their sums by model: with them the data gradient itself
 };
 template <typename T> void launch_conv3_fwd(const Conv3Args& a, hipStream_t st);
 template <typename T> void launch_conv3_dgrad(const Conv3Args& a, hipStream_t st);
