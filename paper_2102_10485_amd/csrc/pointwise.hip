@@ -1258,16 +1258,17 @@ __global__ __launch_bounds__(256) void anova_image_mean_kernel(const float* __re
 // images are first gathered into a list in LDS (eight labels a thread, places from ballots, in a fixed order), then four waves share
 // the list of one channel, so that a sum over lanes is one butterfly and four values, and up to four means a lane stay in registers for
 // the second pass: 6400 images, 100 labels 14.1 -> 6.2 us of a call of 40.1, now 33.1 (before: 1024 threads
-// with eight labels each, every sum over all of them, once per channel).
-constexpr int ANOVA_T = 1024, ANOVA_W = ANOVA_T / 64, ANOVA_E = 8, ANOVA_KEEP = 4;
+// with eight labels each, every sum over all of them, once per channel).  What loses is one label with nearly all of a full trip, whose list
+// four waves walk: 8192 images, 34 us of a call against 30.
+constexpr int ANOVA_T = 1024, ANOVA_W = ANOVA_T / 64, ANOVA_E = 8, ANOVA_TRIP = ANOVA_E * ANOVA_T, ANOVA_KEEP = 4;
 __global__ __launch_bounds__(ANOVA_T) void anova_group_kernel(const int* __restrict__ label_ids, const double* __restrict__ x, int n, int C,
                                                               double* __restrict__ gsum, double* __restrict__ ssw, int* __restrict__ gcnt) {
-  __shared__ int list[ANOVA_E * ANOVA_T];
+  __shared__ int list[ANOVA_TRIP];
   __shared__ int votes_n[ANOVA_E * ANOVA_W];
   __shared__ double sh[ANOVA_W];
   const int k = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int c = wave >> 2, q0 = (wave & 3) * 64 + lane;                // this wave's channel, and its lane's first place in the list
-  // the label's images among ANOVA_E * ANOVA_T from i0 on -> list; returns their number
+  // the label's images among ANOVA_TRIP from i0 on -> list; returns their number
   const auto gather = [&](int i0) {
     int lab[ANOVA_E];
     unsigned long long votes[ANOVA_E];
@@ -1305,10 +1306,10 @@ __global__ __launch_bounds__(ANOVA_T) void anova_group_kernel(const int* __restr
   double keep[ANOVA_KEEP];
   int total = 0;
   long long all = 0;
-  const bool once = n <= ANOVA_E * ANOVA_T;
+  const bool once = n <= ANOVA_TRIP;
   for (int pass = 0; pass < 2; ++pass) {
     double s = 0.0;
-    for (int i0 = 0; i0 < n; i0 += ANOVA_E * ANOVA_T) {
+    for (int i0 = 0; i0 < n; i0 += ANOVA_TRIP) {
       if (!once || pass == 0) {
         total = gather(i0);
         if (pass == 0) all += total;
@@ -1340,6 +1341,65 @@ __global__ __launch_bounds__(ANOVA_T) void anova_group_kernel(const int* __restr
     __syncthreads();                                                    // sh is written again by the second pass
   }
 }
+// The same without lists, for many images: every thread adds the means of its own images that match, over all channels at once, and keeps
+// nothing, so a trip over 8192 labels waits for nobody.  With lists every further trip costs two barriers and is gathered again in the second
+// pass, and a long list has four waves of sixteen on it.  us of a call, lists / without (4x4 images, one channel): 65536 images 116 / 69 with
+// two labels, 67 / 58 with 100, 186 / 120 with 1000; 32768 67 / 46, 43 / 42, 113 / 94; 16384 43 / 35, 31 / 34, 76 / 81; one trip, 8192
+// images, 27 / 30, 23 / 31, 48 / 75.
+__global__ __launch_bounds__(ANOVA_T) void anova_group_many_kernel(const int* __restrict__ label_ids, const double* __restrict__ x, int n, int C,
+                                                                   double* __restrict__ gsum, double* __restrict__ ssw, int* __restrict__ gcnt) {
+  __shared__ double sh[5][ANOVA_W];
+  const int k = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double mean[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int pass = 0; pass < 2; ++pass) {
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    int cnt = 0;
+    for (int i0 = threadIdx.x; i0 < n; i0 += ANOVA_TRIP) {
+      int lab[ANOVA_E];
+      double v[ANOVA_E][4];
+#pragma unroll
+      for (int e = 0; e < ANOVA_E; ++e) lab[e] = i0 + ANOVA_T * e < n ? label_ids[i0 + ANOVA_T * e] : -1;
+#pragma unroll
+      for (int e = 0; e < ANOVA_E; ++e)
+        if (lab[e] == k) {
+          const double* xi = x + (long long)(i0 + ANOVA_T * e) * C;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) v[e][c] = c < C ? xi[c] : 0.0;
+        }
+#pragma unroll
+      for (int e = 0; e < ANOVA_E; ++e)
+        if (lab[e] == k) {
+          ++cnt;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const double d = v[e][c] - mean[c];
+            s[c] += pass ? d * d : d;
+          }
+        }
+    }
+    // per wave, then the waves' sums by every wave alike (16 lanes of a butterfly): all threads need the mean
+    const double all5[5] = {wave_sum_f64(s[0]), wave_sum_f64(s[1]), wave_sum_f64(s[2]), wave_sum_f64(s[3]), wave_sum_f64((double)cnt)};
+    if (lane == 0) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) sh[c][wave] = all5[c];
+    }
+    __syncthreads();
+    double t[5];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+      t[c] = sh[c][lane & (ANOVA_W - 1)];
+#pragma unroll
+      for (int o = ANOVA_W / 2; o > 0; o >>= 1) t[c] += __shfl_xor(t[c], o, 64);
+    }
+    __syncthreads();                                                   // sh is written again by the second pass
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (threadIdx.x == 0 && c < C) (pass ? ssw : gsum)[(long long)k * C + c] = t[c];
+      if (!pass) mean[c] = t[4] > 0.0 ? t[c] / t[4] : 0.0;
+    }
+    if (threadIdx.x == 0 && !pass) gcnt[k] = (int)t[4];
+  }
+}
 void launch_anova(const int* label_ids, const float* images, int n, int n_labels, int C, int HW, double* x, double* gsum,
                   double* ssw, int* gcnt, hipStream_t st) {
   if (n == 0) return;
@@ -1349,7 +1409,9 @@ void launch_anova(const int* label_ids, const float* images, int n, int n_labels
     hipLaunchKernelGGL(anova_image_mean_kernel<true>, grid, dim3(256), 0, st, images, count, HW, x);
   else
     hipLaunchKernelGGL(anova_image_mean_kernel<false>, grid, dim3(256), 0, st, images, count, HW, x);
-  hipLaunchKernelGGL(anova_group_kernel, dim3(n_labels), dim3(ANOVA_T), 0, st, label_ids, x, n, C, gsum, ssw, gcnt);
+  // lists for one trip, and for two or three where a label has 2048 images or fewer on average (see the second kernel)
+  const bool lists = n <= ANOVA_TRIP || (n <= 3 * ANOVA_TRIP && n <= 2048LL * n_labels);
+  hipLaunchKernelGGL(lists ? &anova_group_kernel : &anova_group_many_kernel, dim3(n_labels), dim3(ANOVA_T), 0, st, label_ids, x, n, C, gsum, ssw, gcnt);
 }
 
 }  // namespace gan

@@ -235,6 +235,20 @@ def test_anova_f_of_uneven_labels(n):
     np.testing.assert_allclose(F, ref, rtol=1e-9)            # sums in double on both sides, as above
 
 
+@pytest.mark.parametrize("n,K", [(8193, 3), (8193, 5), (24576, 12), (24577, 12), (40000, 2), (30000, 700)])
+def test_anova_f_of_several_trips(n, K):
+    """On both sides of the lines between lists of a label's images and sums without them: 8192 images, 2048 to a label, 24576 images."""
+    rng = np.random.default_rng(n + K)
+    lab = rng.integers(0, K, n).astype(np.int32)
+    lab[rng.random(n) < 0.01] = K + 1                        # ignored
+    img = np.tanh(rng.normal(size=(n, 2, 2, 2)) + 0.1 * (lab % 7)[:, None, None, None]).astype(np.float32)
+    rc, ref = O.anova_f(lab, img, K)
+    dl, dx = U.dev(lab), U.dev(img)
+    st, F = binding.anova_f_static(dl.data_ptr(), dx.data_ptr(), n, K, 2, 2, U.torch_mod().cuda.current_stream().cuda_stream)
+    assert rc == 0 and st == binding.GAN_OK
+    np.testing.assert_allclose(F, ref, rtol=1e-9)            # sums in double on both sides, as above
+
+
 def test_anova_f_after_a_failed_call_of_the_caller():
     """An error that some other HIP call of the thread left behind is not the analysis' own."""
     torch = U.torch_mod()
