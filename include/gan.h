@@ -260,7 +260,8 @@ gan_status gan_probe_copy(int64_t bytes, void* hip_stream, double* gbps);
    n_groups models, group g uses weight block g.  n_samples = offs[n_groups] must be given by the caller. */
 /* Which of the forward-type GEMM's tile shapes gan_op_conv_down / gan_op_conv_up use from now on: rows = 64, 128 or
    256 rows per tile (with 256 the width follows the output channels: 64, 128 or 256 columns; fp32 takes its 64-column tile, of 128 rows), 0 = chosen from the
-   problem size as inside a training step.  Lets a test run one case through every instantiation. */
+   problem size as inside a training step, which for a few hundred tiles is one whose reduction several groups of waves share (no height names those).
+   Lets a test run one case through the instantiations. */
 gan_status gan_op_tile_rows(gan_ctx* ctx, int32_t rows);
 gan_status gan_op_conv_down(gan_ctx* ctx, const void* big, const void* w_down, void* small_out, const int32_t* offs,
                             int32_t n_groups, int32_t n_samples, int32_t cb, int32_t cs, int32_t hs);

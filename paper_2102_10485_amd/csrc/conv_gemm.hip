@@ -991,9 +991,9 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   }
   if (p.stat_partial) {
     // For the BatchNorm that follows.  Every wave's (TM*32)-row block of the tile is a sub-tile of its own: per column
-    // the sum of its fp32 results and the sum of their squared deviations from the sub-tile's column mean, which the
-    // statistics kernel merges across sub-tiles with the pairwise-update formula (no E[x^2] - mean^2 over a whole
-    // channel).  One pass over the accumulators with the sub-tile's first row as the shift K:
+    // the sum s of its fp32 results and the sum M2 of their squared deviations from the sub-tile's column mean, from which the
+    // statistics kernel gets the channel's as sum(M2 + s^2 / n) - (sum s)^2 / N, in double (whose bits pay for what cancels).
+    // One pass over the accumulators with the sub-tile's first row as the shift K:
     //   sum = K n + sum(x - K),   M2 = sum((x - K)^2) - (sum(x - K))^2 / n
     // (a sample of the column is as good a shift as its mean up to a few units of the last place), no block-wide
     // barrier and nothing shared between the waves, so a wave is done when its own stores and sums are.

@@ -1,7 +1,7 @@
 // Bandwidth-bound kernels of the training step: label routing, staging, BatchNorm statistics / apply / backward
 // fused with the activation, D's linear head and the two logistic costs (Eq. 3, Eq. 4), Adam, layout copies.
-// Every reduction has a fixed order that does not depend on the number of models, so results are deterministic
-// and a model's numbers do not change with what else is in the launch.
+// Every reduction has an order that follows from the configuration (models, sizing batch, layer shapes) and the model's own samples, so results are
+// deterministic and a model's numbers do not change with what else is in the launch.
 #include <algorithm>
 
 #include "kernels.h"

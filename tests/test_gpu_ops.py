@@ -41,6 +41,7 @@ CASES = [
     (256, 64, 8, [2, 7]),          # up: the same, per output phase
     (64, 256, 16, [2, 1]),         # down: one sample per 256-row tile
     (256, 64, 16, [1, 2]),         # up: one sample per tile
+    (128, 64, 7, [3, 0, 6]),       # up: 256 x 128 tiles that do not share pixels
 ]
 
 
@@ -52,9 +53,10 @@ def tolerance(prec):
 @pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
 @pytest.mark.parametrize("cb,cs,hs,groups", CASES)
 def test_conv_down_up_wgrad(ctxs, prec, cb, cs, hs, groups, tile_rows):
-    """tile_rows: the forward-type kernel's tile height (0: as a training step would choose for this size, which is
-    the smallest tile at these sizes); with 256 the width follows the output channels (64, 128 or 256 columns), so the
-    cases together run every tile instantiation."""
+    """tile_rows: the forward-type kernel's tile height; with 256 the width follows the output channels (64, 128 or 256
+    columns), and transposed convolutions in bf16 share the gathered pixels of two taps where the side allows it (not 2 and 7).  0: as a training step
+    would choose for this size: 32 x 64 tiles with four groups of waves on a reduction, or 64 x 64 with two (256 -> 512 channels at side 4 down, 256 <- 64
+    at sides 8 and 16 up).  Together the cases run every tile of the kernel without an epilogue, down and up."""
     torch = U.torch_mod()
     g = ctxs[prec]
     g.op_tile_rows(tile_rows)

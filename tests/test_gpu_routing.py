@@ -1,5 +1,4 @@
-"""The routing kernel (GPU) where its tables do not all live in LDS: a batch too large for the label copy, and more
-models than the count table has room for.  The expected result is the definition itself, written out with numpy: a
+"""The routing kernel (GPU): large batches, many models, tables in LDS and beyond it.  The expected result is the definition itself, written out with numpy: a
 stable partition of the flat batch by model (Eq. 5: pair k sees the samples of label k, in their order)."""
 import numpy as np
 import pytest
@@ -32,17 +31,17 @@ def _expected(lab, n_models):
     return np.argsort(model, kind="stable").astype(np.int32), np.concatenate([[0], np.cumsum(counts)]).astype(np.int32), counts
 
 
-def test_one_pair_with_a_batch_larger_than_the_label_copy():
+def test_one_pair_with_a_large_batch():
     rng = np.random.default_rng(1)
-    lab = rng.integers(0, 4, 40000).astype(np.int32)                  # 160 kB of labels: read from global memory
+    lab = rng.integers(0, 4, 40000).astype(np.int32)                  # five trips of 512 samples for every wave
     perm, offs, cnt, jd, jg = _step_and_routing("tiny", 1, 4, lab, 2)
     eperm, eoffs, ecnt = _expected(lab, 1)
     assert np.array_equal(perm, eperm) and np.array_equal(offs, eoffs) and np.array_equal(cnt, ecnt)
     assert np.all(np.isfinite(jd)) and np.all(np.isfinite(jg))
 
 
-def test_more_models_than_the_count_table_has_room_for():
-    L = 130                                                            # 256 x 130 counts: kept in global memory
+def test_many_models_and_one_without_samples():
+    L = 130                                                            # three trips of 64 models in the prefix scans
     rng = np.random.default_rng(3)
     lab = rng.integers(0, L, 1000).astype(np.int32)
     lab[lab == 7] = 8                                                  # one model without samples
@@ -53,10 +52,10 @@ def test_more_models_than_the_count_table_has_room_for():
     assert np.all(np.isfinite(jd)) and np.all(np.isfinite(jg)) and jd[7] == 0 and jg[7] == 0
 
 
-@pytest.mark.parametrize("L,n", [(1, 1), (3, 64), (64, 1025), (65, 8193), (2200, 5000)])
+@pytest.mark.parametrize("L,n", [(1, 1), (3, 64), (64, 1025), (65, 8193), (2161, 3000), (2162, 3000), (2200, 5000)])
 def test_shares_of_the_waves_and_tables_beyond_lds(L, n):
     """Sixteen waves share the batch 64 samples at a time, eight such groups in flight; labels outside the range are dropped wherever
-    they stand; 2200 models' tables are in global memory."""
+    they stand; the tables of 2161 models are the largest that fit LDS (18 L + 1 integers in 152 KiB), those of more are in global memory."""
     rng = np.random.default_rng(L + n)
     lab = rng.integers(0, L, n).astype(np.int32)
     bad = rng.random(n) < 0.05

@@ -278,6 +278,17 @@ def test_single_unconditional_pair(prec):
     p.close()
 
 
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+@pytest.mark.parametrize("n", [5, 33])
+def test_row_splits_without_rows(prec, n):
+    """One 28x28 pair sized for 64 samples, whose weight gradients are split 15 to 32 ways between feature maps and 128 ways at the image
+    (four threads an element add 16 or more of the former, sixteen the latter): few samples leave splits a part of a chunk, or nothing."""
+    p = Pair("mnist", 1, 10, 64, prec)
+    p.step(*batch(p.spec, np.full(n, 3), 710 + n))
+    p.compare("%d samples" % n)
+    p.close()
+
+
 def test_free_running_steps_keep_the_stated_tolerance_while_it_means_something():
     """Three steps with no state reloaded in between, fp32 storage: the costs and parameters stay within 1e-4 of the
     fp64 oracle for the first two steps (the third is past where the oracle's own single-precision build holds it)."""
