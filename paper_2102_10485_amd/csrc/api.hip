@@ -49,7 +49,7 @@ struct ConvLayer {
   // summed-tap k4 weights in the storage-type arenas
   int cs_real = 0, cb_real = 0;
   long long w4 = -1;
-  long long part = -1;                                  // fp32 storage, layers on the GEMM engine: offset into a plane of the split weights
+  long long part = -1;                                  // fp32 storage, layers on the GEMM engine: offset into a plane of the split weights, or into shadow_d
 };
 
 struct Net {
@@ -69,7 +69,7 @@ struct Net {
   float *theta = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
   void *shadow_u = nullptr, *shadow_d = nullptr;   // bf16 storage: copies [tap][cb][cs] and [tap][cs][cb] (fp32: shadow_u is theta)
   // fp32 storage: the weights of the convolutions on the GEMM engine (the k4 weights, where there are any) as three bf16 planes in both
-  // layouts, [model][plane][PS]
+  // layouts, [model][plane][PS] (without presplit: shadow_d, the second layout in fp32, [model][PS])
   long long PS = 0;
   unsigned short *split_u = nullptr, *split_d = nullptr;
   float *run_mean = nullptr, *run_var = nullptr;
@@ -103,6 +103,7 @@ struct gan_ctx {
   int head_rsplit = 1;
   float* wg_part = nullptr;        // row-split partial weight gradients (few models only)
   bool paper = false;              // the networks as printed in the paper's tables
+  bool presplit = false;           // fp32 storage: the convolutions on the GEMM engine read weights that the update has split (see presplit_pays)
   float *dw4 = nullptr, *c3_part = nullptr;   // paper G: k4 weight gradient of one block; row-split partials of the last conv
   int KcD = 0, KcG = 0;
   int nslot = 1;              // class-indicator slots in the patch matrix of D's first conv
@@ -431,6 +432,25 @@ void build_layout_paper(gan_ctx* c) {
 // whether the GEMM engine runs this convolution (all but the ones next to the image)
 bool on_engine(const gan_ctx* c, const Net& n, size_t i) { return &n == &c->G ? i + 1 < n.conv.size() : i > 0; }
 
+// fp32 storage: whether the update writes the convolutions' weights split.  That is 40 bytes an update and weight where the weights and a
+// transposed copy are 32, and 6 bytes instead of 4 in every GEMM; it spares the GEMMs splits for every row they multiply.  The line is on the rows a
+// weight meets per model at the sizing batch (never a call's).  us a step, split / whole: a hundred 32x32 pairs, 102 rows 11357 / 9945, 205 rows 14830 /
+// 14047, 410 rows 21633 / 21364, 819 rows 35735 / 36922; ten of them 102 rows 1694 / 1599, 205 rows 2249 / 2270, 410 rows 3130 / 3255; eight 64x64
+// pairs 146 rows 1948 / 1850, 293 rows 2429 / 2487; a thousand 16x16 pairs 43 rows 9219 / 7865, 87 rows 11277 / 10155.  The networks of the
+// tables, whose generator's k4 weights are made anew in any case, always have them split.
+bool presplit_pays(const gan_ctx* c) {
+  if (c->paper) return true;
+  double weights = 0, rows = 0;
+  for (const Net* n : {&c->G, &c->D})
+    for (size_t i = 0; i < n->conv.size(); ++i) {
+      const ConvLayer& cl = n->conv[i];
+      if (!on_engine(c, *n, i)) continue;
+      weights += (double)cl.Cb * cl.Cs;
+      rows += (double)cl.Cb * cl.Cs * cl.Hs * cl.Hs;
+    }
+  return rows * c->NB >= 256.0 * c->L * weights;
+}
+
 bool alloc_net(gan_ctx* c, Net& n) {
   const size_t tot = (size_t)c->L * n.P;
   bool ok = dev_alloc(c, (void**)&n.theta, tot * 4) && dev_alloc(c, (void**)&n.m, tot * 4) &&
@@ -450,7 +470,8 @@ bool alloc_net(gan_ctx* c, Net& n) {
       n.PS += (long long)16 * cl.Cb * cl.Cs;
     }
     const size_t parts = (size_t)c->L * n.PS * 6;
-    if (!dev_alloc(c, (void**)&n.split_u, parts) || !dev_alloc(c, (void**)&n.split_d, parts)) return false;
+    if (c->presplit ? !dev_alloc(c, (void**)&n.split_u, parts) || !dev_alloc(c, (void**)&n.split_d, parts)
+                    : !dev_alloc(c, &n.shadow_d, (size_t)c->L * n.PS * 4)) return false;
     n.shadow_u = n.theta;
   }
   hipMemsetAsync(n.theta, 0, tot * 4, c->st);
@@ -556,7 +577,9 @@ void refresh_transposes(gan_ctx* c, Net& n, bool isG) {
     if (!on_engine(c, n, i)) continue;
     Scope s(c, "transpose_w", 0, (double)c->L * 16 * cl.Cb * cl.Cs * 2 * sizeof(T));
     if (c->bf16)
-      launch_transpose_w<bf16_t, bf16_t>((const bf16_t*)n.shadow_u + cl.w, (bf16_t*)n.shadow_d + cl.w, n.P, c->L, cl.Cb, cl.Cs, c->st);
+      launch_transpose_w<bf16_t, bf16_t>((const bf16_t*)n.shadow_u + cl.w, (bf16_t*)n.shadow_d + cl.w, n.P, n.P, c->L, cl.Cb, cl.Cs, c->st);
+    else if (!c->presplit)
+      launch_transpose_w<float, float>(n.theta + cl.w, (float*)n.shadow_d + cl.part, n.P, n.PS, c->L, cl.Cb, cl.Cs, c->st);
     else
       launch_split_weights({n.theta + cl.w, n.split_u + cl.part, n.split_d + cl.part, n.P, n.PS, c->L, cl.Cb, cl.Cs}, c->st);
   }
@@ -597,6 +620,10 @@ Weights layer_weights(const gan_ctx* c, const Net& net, const ConvLayer& cl, boo
   const bool k4 = cl.w4 >= 0;                          // summed taps (the networks of the tables, G)
   const long long off = k4 ? cl.w4 : cl.w, P = k4 ? net.P4 : net.P;
   if (c->bf16) return {(const bf16_t*)(k4 ? (up ? net.w4u : net.w4d) : (up ? net.shadow_u : net.shadow_d)) + off, P};
+  if (!c->presplit) {
+    if (up) return {net.theta + cl.w, net.P};
+    return {(const float*)net.shadow_d + cl.part, net.PS};
+  }
   return {(up ? net.split_u : net.split_d) + cl.part, 3 * net.PS, net.PS, (k4 ? (const float*)net.w4u : net.theta) + off, P, up ? cl.Cs : 1, up ? 1 : cl.Cs};
 }
 template <typename T>
@@ -717,7 +744,7 @@ void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool update_runn
     const int tr = conv_tile_rows((int)sizeof(T), tile), gemm_phases = gemm_mode == MODE_UP ? 4 : 1;
     a.fold_running = update_running;
     launch_bn_stats_from_partial(a, c->stat_partial, tpre_of(c, gemm_rps, tr), ub_tiles(c, a.n, gemm_rps, tr), ub_tiles(c, c->NB, gemm_rps, tr),
-                                 gemm_phases, col_groups, tr, gemm_rps, conv_stat_split((int)sizeof(T), tile, gemm_mode), c->st);
+                                 gemm_phases, col_groups, tr, gemm_rps, conv_stat_split((int)sizeof(T), tile, c->presplit && gemm_mode != MODE_DENSE), c->st);
   }
   if (!y) return;
   Scope s(c, "bn_apply", 0, 2 * elems * sizeof(T));
@@ -1203,7 +1230,7 @@ void adam_region_call(gan_ctx* c, const AdamArgs& a, int region, hipStream_t st)
   double elems = 0;
   for (int r = 0; r < a.nregions; ++r)
     if (region < 0 || r == region) elems += 16.0 * a.reg_cb[r] * a.reg_cs[r];
-  Scope s(c, "adam", 0, (double)c->L * elems * (adam_bytes_per_element(c) + (c->bf16 ? 2.0 : 12.0)), nullptr, st);
+  Scope s(c, "adam", 0, (double)c->L * elems * (adam_bytes_per_element(c) + (c->bf16 ? 2.0 : c->presplit ? 12.0 : 4.0)), nullptr, st);
   launch_adam_region<T>(a, region, st);
 }
 // what is left of a planned update once the regions are done (or enqueued beside): the gaps, and the packed weights of
@@ -1338,6 +1365,7 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
   c->geoms.n = 0;
   c->paper = cfg->family == GAN_FAMILY_PAPER;
   if (c->paper) build_layout_paper(c); else build_layout(c);
+  c->presplit = !c->bf16 && presplit_pays(c);
   const int L = c->L, NB = c->NB;
   const size_t es = esize(c);
   bool ok = alloc_net(c, c->G) && alloc_net(c, c->D);

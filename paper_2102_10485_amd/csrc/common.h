@@ -64,9 +64,9 @@ enum Act { ACT_RELU = 0, ACT_LRELU = 1 };
 // Arguments of the grouped implicit-GEMM forward-type kernel (down / up / dense).
 struct ConvArgs {
   const void* A;         // gathered activations (storage type)
-  const void* W;         // weights of model 0, K-contiguous: [tap][N][C] (storage type); fp32 convolutions: [3][tap][N][C] bf16, the
+  const void* W;         // weights of model 0, K-contiguous: [tap][N][C] (storage type); fp32 convolutions with w_plane: [3][tap][N][C] bf16, the
                          // parts of launch_split_weights, planes w_plane elements apart
-  long long w_plane;
+  long long w_plane;     // 0: W in the storage type
   const float* w_raw;    // the fp32 weights of model 0 themselves, element (tap, n, c) at tap * w_nstride * C + n * raw_n + c * raw_k
   long long raw_stride;  //   (elements between models), for tiles that have no split (see Split8)
   int raw_n, raw_k;
@@ -146,6 +146,6 @@ int wgrad_tiles_per_model(int esize, int ntaps, int Cb, int Cs);
 ConvTile conv_choose_tile(int esize, int n_out, double rows_per_model, int n_models, int groups);
 ConvTile conv_tile_of_rows(int esize, int rows, int n_out);
 int conv_tile_rows(int esize, ConvTile t);
-int conv_stat_split(int esize, ConvTile t, int mode);
+int conv_stat_split(int esize, ConvTile t, bool split_weights);      // split_weights: fp32 convolutions, see ConvArgs
 
 }  // namespace gan

@@ -56,7 +56,7 @@ template <> struct FwdTiles<bf16_t> {
   typedef Tile<256, 256, 2, 4, 128, 2> Big;      // 512 threads, wave tile 128 x 64, 128 KiB of LDS
   typedef Tile<256, 128, 4, 2, 64, 3> Mid;       // 512 threads, wave tile 64 x 64, 72 KiB of LDS
   typedef Tile<128, 128, 2, 2, 128, 2> Small;    // 256 threads, wave tile 64 x 64 (few rows per model), 64 KiB of LDS
-  typedef Small SmallDense;
+  typedef Small SmallWhole;
   typedef Tile<256, 64, 4, 1, 128, 2> Narrow;    // 256 threads, wave tile 64 x 64, for layers with 64 output channels:
                                                  // 128-byte chunks, two buffers of 40 KiB, so two blocks still share a CU
   typedef Tile<256, 64, 4, 1, 64, 2> NarrowShort;  // the same with two buffers of 20 KiB for MODE_UP and MODE_DENSE: their reductions are
@@ -83,10 +83,11 @@ template <> struct FwdTiles<bf16_t> {
 // tile; two blocks per CU.  20 x 64 samples, us: down 128 -> 256 channels, side 8: 128x128 with 32 x 128 wave tiles 435, 64 x 64 474,
 // 32 x 64 (eight waves) 445, 256x128 (eight waves, one block per CU) 490; up 256 -> 128, side 8: 438, 451, 455, 450; with weights split
 // by every wave 538 and 486 (64 x 64, the best then).  10 x 128 samples, up 128 -> 64, side 7: 128x64 108, 256x64 (one block per CU) 129, before 113.
-// The patch-matrix layers and G's linear one (MODE_DENSE) read their few weights as fp32 and split them too: 64 x 64 wave tiles there.
+// The patch-matrix layers and G's linear one (MODE_DENSE), and convolutions of contexts whose weights the update does not split, read the weights as
+// fp32 and split them too: 64 x 64 wave tiles there (SmallWhole).
 template <> struct FwdTiles<float> {
   typedef Tile<128, 128, 4, 1, 128, 2> Small;    // 256 threads, wave tile 32 x 128, 80 KiB of LDS
-  typedef Tile<128, 128, 2, 2, 128, 2> SmallDense;
+  typedef Tile<128, 128, 2, 2, 128, 2> SmallWhole;
   typedef Tile<128, 64, 4, 1, 128, 2> Narrow;    // 256 threads, wave tile 32 x 64, 56 KiB
   typedef Narrow NarrowShort;
   typedef Tile<64, 64, 2, 2, 128, 2> Tiny;       // 256 threads, wave tile 32 x 32, 40 KiB
@@ -134,8 +135,8 @@ static const TileInfo TILES[2][7] = {
 };
 static const TileInfo& tile_info(int esize, ConvTile t) { return TILES[esize == 4][t]; }
 int conv_tile_rows(int esize, ConvTile t) { return tile_info(esize, t).rows; }
-int conv_stat_split(int esize, ConvTile t, int mode) {
-  if (esize == 4 && t == TILE_SMALL && mode == MODE_DENSE) return FwdTiles<float>::SmallDense::WM;
+int conv_stat_split(int esize, ConvTile t, bool split_weights) {
+  if (esize == 4 && t == TILE_SMALL && !split_weights) return FwdTiles<float>::SmallWhole::WM;
   return tile_info(esize, t).split;
 }
 
@@ -440,12 +441,12 @@ static int log2_or_neg(int v) {
 // Waves a SIMD should hold at least, which bounds the registers.  Wave tiles of 64 x 64: two (fp32 needs about 200 registers for its
 // two accumulators; without the bound bf16 takes 171, half of them accumulation registers, and with it 107, four waves).
 template <typename T, typename TL> constexpr int waves_per_simd() { return TL::TM * TL::TN == 4 ? 2 : 1; }
-template <typename T, int MODE, int EPI, typename TL>
+// PRE: fp32 convolutions whose weights come split (launch_split_weights), as three bf16 planes
+template <typename T, int MODE, int EPI, typename TL, bool PRE>
 __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void conv_gemm_kernel(ConvArgs p) {
   constexpr int BM = TL::BM, BN = TL::BN, TM = TL::TM, TN = TL::TN, PA = TL::PA, PB = TL::PB, RPP = TL::RPP;
   constexpr int KB = TL::KB, NST = TL::NST, KS = TL::KS;
-  // fp32 convolutions get their weights split already (launch_split_weights): three bf16 planes
-  constexpr bool PRE = sizeof(T) == 4 && MODE != MODE_DENSE;
+  static_assert(!PRE || (sizeof(T) == 4 && MODE != MODE_DENSE), "split weights: fp32 convolutions");
   constexpr int KBB = PRE ? KB / 2 * 3 : KB;                                   // bytes of a column in LDS
   constexpr bool SHARE = TL::SHARE;
   static_assert(!SHARE || (sizeof(T) == 2 && MODE == MODE_UP && KS == 1), "shared pixels: bf16, MODE_UP");
@@ -1038,24 +1039,24 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   }
 }
 
-template <typename T, int MODE, int EPI, typename TL>
+template <typename T, int MODE, int EPI, typename TL, bool PRE>
 static void launch_one(ConvArgs a, hipStream_t st) {
   a.hr_shift = log2_or_neg(a.Hr);
   const int NT = (a.N + TL::BN - 1) / TL::BN;
   const long long blocks = ((long long)a.ub_tiles * NT * a.nseg * (MODE == MODE_UP ? 4 : 1) + 7) / 8 * 8;
   if (blocks == 0 || a.nseg == 0) return;
   dim3 grid((unsigned)blocks, 1, 1);
-  hipLaunchKernelGGL((conv_gemm_kernel<T, MODE, EPI, TL>), grid, dim3(TL::NT * TL::KS), 0, st, a);
+  hipLaunchKernelGGL((conv_gemm_kernel<T, MODE, EPI, TL, PRE>), grid, dim3(TL::NT * TL::KS), 0, st, a);
 }
 
-template <typename T, int MODE, int EPI>
+template <typename T, int MODE, int EPI, bool PRE>
 static void launch_wide(const ConvArgs& a, hipStream_t st) {
   typedef FwdTiles<T> Tiles;
   if constexpr (sizeof(T) == 2 && MODE == MODE_UP) {
     bool done = false;
     const auto shared = [&](ConvTile id, auto tile) {
       if (done || a.tile != id || !share_fits<decltype(tile)>(a.Hr)) return;
-      launch_one<T, MODE, EPI, decltype(tile)>(a, st);
+      launch_one<T, MODE, EPI, decltype(tile), PRE>(a, st);
       done = true;
     };
     shared(TILE_BIG, typename Tiles::BigShare());
@@ -1065,17 +1066,24 @@ static void launch_wide(const ConvArgs& a, hipStream_t st) {
     if (done) return;
   }
   if constexpr (sizeof(T) == 2) {
-    if (a.tile == TILE_BIG) return launch_one<T, MODE, EPI, typename Tiles::Big>(a, st);
-    if (a.tile == TILE_MID) return launch_one<T, MODE, EPI, typename Tiles::Mid>(a, st);
+    if (a.tile == TILE_BIG) return launch_one<T, MODE, EPI, typename Tiles::Big, PRE>(a, st);
+    if (a.tile == TILE_MID) return launch_one<T, MODE, EPI, typename Tiles::Mid, PRE>(a, st);
   }
   if (a.tile == TILE_SMALL)
-    return launch_one<T, MODE, EPI, std::conditional_t<MODE == MODE_DENSE, typename Tiles::SmallDense, typename Tiles::Small>>(a, st);
+    return launch_one<T, MODE, EPI, std::conditional_t<PRE || sizeof(T) == 2, typename Tiles::Small, typename Tiles::SmallWhole>, PRE>(a, st);
   if (a.tile == TILE_NARROW)
-    return launch_one<T, MODE, EPI, std::conditional_t<MODE != MODE_DOWN, typename Tiles::NarrowShort, typename Tiles::Narrow>>(a, st);
-  if (a.tile == TILE_TINY) return launch_one<T, MODE, EPI, typename Tiles::Tiny>(a, st);
-  if (a.tile == TILE_PAIR) return launch_one<T, MODE, EPI, typename Tiles::Pair>(a, st);
-  if (a.tile == TILE_DEEP) return launch_one<T, MODE, EPI, typename Tiles::Deep>(a, st);
+    return launch_one<T, MODE, EPI, std::conditional_t<MODE != MODE_DOWN, typename Tiles::NarrowShort, typename Tiles::Narrow>, PRE>(a, st);
+  if (a.tile == TILE_TINY) return launch_one<T, MODE, EPI, typename Tiles::Tiny, PRE>(a, st);
+  if (a.tile == TILE_PAIR) return launch_one<T, MODE, EPI, typename Tiles::Pair, PRE>(a, st);
+  if (a.tile == TILE_DEEP) return launch_one<T, MODE, EPI, typename Tiles::Deep, PRE>(a, st);
   launch_fail("GEMM: a tile that this storage type does not have");
+}
+
+template <typename T, int MODE, int EPI>
+static void launch_mode(const ConvArgs& a, hipStream_t st) {
+  if constexpr (sizeof(T) == 4 && MODE != MODE_DENSE)
+    if (a.w_plane != 0) return launch_wide<T, MODE, EPI, true>(a, st);
+  launch_wide<T, MODE, EPI, false>(a, st);
 }
 
 // The (mode, epilogue, tile) combinations the networks use.
@@ -1087,24 +1095,25 @@ void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
       (epi == EPI_BN && (!a.bn_mean || !a.bn_var || !a.bn_gamma || !a.bn_beta || a.bn_C < 1)))
     return launch_fail("GEMM: null operand, or channel counts that are not whole 128-byte lines");
   if (a.N < 64) return launch_fail("GEMM: fewer than 64 output channels (image-side outputs have their own kernel)");
+  const bool pre = a.w_plane != 0;
   {
     // the loaders address one model's slice of A and one weight block with 32-bit byte offsets
     const long long side = mode == MODE_DENSE ? a.Hr : a.Hin;
-    const bool pre = sizeof(T) == 4 && mode != MODE_DENSE;
-    if (pre && (!a.w_raw || a.w_plane < 16LL * a.w_nstride * a.C || a.w_plane % 8)) return launch_fail("GEMM: fp32 weights that are not split");
+    if (pre && (sizeof(T) != 4 || mode == MODE_DENSE || !a.w_raw || a.w_plane < 16LL * a.w_nstride * a.C || a.w_plane % 8))
+      return launch_fail("GEMM: split weights are those of fp32 convolutions");
     if ((long long)a.seg_samples * side * side * a.C * (long long)sizeof(T) >= (1LL << 31) ||
         16LL * a.w_nstride * a.C * (long long)sizeof(T) >= (1LL << 31))
       return launch_fail("GEMM: one segment of the gathered tensor, or one weight block, is 2 GiB or larger");
   }
-  if (mode == MODE_DOWN && epi == EPI_NONE) return launch_wide<T, MODE_DOWN, EPI_NONE>(a, st);
-  if (mode == MODE_UP && epi == EPI_NONE) return launch_wide<T, MODE_UP, EPI_NONE>(a, st);
-  if (mode == MODE_UP && epi == EPI_ACT_BWD) return launch_wide<T, MODE_UP, EPI_ACT_BWD>(a, st);
-  if (mode == MODE_UP && epi == EPI_BN) return launch_wide<T, MODE_UP, EPI_BN>(a, st);
-  if (mode == MODE_DENSE && epi == EPI_BN) return launch_wide<T, MODE_DENSE, EPI_BN>(a, st);
-  if (mode == MODE_UP && epi == EPI_DROP_BWD) return launch_wide<T, MODE_UP, EPI_DROP_BWD>(a, st);
-  if (mode == MODE_DENSE && epi == EPI_NONE) return launch_wide<T, MODE_DENSE, EPI_NONE>(a, st);
-  if (mode == MODE_DENSE && epi == EPI_LRELU) return launch_wide<T, MODE_DENSE, EPI_LRELU>(a, st);
-  if (mode == MODE_DENSE && epi == EPI_LABEL_LRELU) return launch_wide<T, MODE_DENSE, EPI_LABEL_LRELU>(a, st);
+  if (mode == MODE_DOWN && epi == EPI_NONE) return launch_mode<T, MODE_DOWN, EPI_NONE>(a, st);
+  if (mode == MODE_UP && epi == EPI_NONE) return launch_mode<T, MODE_UP, EPI_NONE>(a, st);
+  if (mode == MODE_UP && epi == EPI_ACT_BWD) return launch_mode<T, MODE_UP, EPI_ACT_BWD>(a, st);
+  if (mode == MODE_UP && epi == EPI_BN) return launch_mode<T, MODE_UP, EPI_BN>(a, st);
+  if (mode == MODE_DENSE && epi == EPI_BN) return launch_mode<T, MODE_DENSE, EPI_BN>(a, st);
+  if (mode == MODE_UP && epi == EPI_DROP_BWD) return launch_mode<T, MODE_UP, EPI_DROP_BWD>(a, st);
+  if (mode == MODE_DENSE && epi == EPI_NONE) return launch_mode<T, MODE_DENSE, EPI_NONE>(a, st);
+  if (mode == MODE_DENSE && epi == EPI_LRELU) return launch_mode<T, MODE_DENSE, EPI_LRELU>(a, st);
+  if (mode == MODE_DENSE && epi == EPI_LABEL_LRELU) return launch_mode<T, MODE_DENSE, EPI_LABEL_LRELU>(a, st);
   launch_fail("GEMM: (mode, epilogue) combination without an instantiation");
 }
 // Name of the kernel instantiation launch_conv picks (for per-kernel timing): mode, epilogue, tile.

@@ -192,7 +192,8 @@ struct AdamArgs {
   void* shadow;             // storage-type copy of theta (NULL when the storage type is fp32)
   void* shadow_t;           // storage-type copy with every region below transposed: [tap][cs][cb]
   // fp32 storage, in place of the two copies: the regions, from element reg_part of a plane on, as three bf16 planes, as they are and
-  // transposed (launch_split_weights; models 3 * plane elements apart)
+  // transposed (launch_split_weights; models 3 * plane elements apart).  Or both NULL, and shadow_t has the regions only, from reg_part on, models
+  // plane elements apart.
   unsigned short *split_u, *split_d;
   long long plane;
   long long P;              // elements per model
@@ -220,7 +221,7 @@ template <typename T> void launch_adam_region(AdamArgs a, int region, hipStream_
 template <typename T> void launch_cast_shadow(const float* theta, T* shadow, long long total, hipStream_t st);
 // dst[tap][cs][cb] <- src[tap][cb][cs] for every model (src: T or float master)
 template <typename T, typename S>
-void launch_transpose_w(const S* src, T* dst, long long pstride, int L, int Cb, int Cs, hipStream_t st);
+void launch_transpose_w(const S* src, T* dst, long long src_stride, long long dst_stride, int L, int Cb, int Cs, hipStream_t st);
 
 // fp32 weights as three bf16 planes (split_mfma.h): the block src[tap][cb][cs] of every model into up[plane][tap][cb][cs] and, transposed,
 // down[plane][tap][cs][cb]; planes `plane`, models src_stride (src) and 3 * plane elements apart.  down may be NULL.

@@ -105,7 +105,7 @@ void launch_w3_to_w4(const float* w3, T* w4, T* w4t, int n_groups, int cb, int c
   hipLaunchKernelGGL((w3_to_w4_kernel<T>), dim3((unsigned)((cb * cs + 255) / 256), 16, (unsigned)n_groups), dim3(256), 0, st, w3, w4, cb, cs,
                      w3_stride ? w3_stride : (long long)9 * cb * cs, s4);
   if (w4t) {
-    if (cb % 32 == 0) launch_transpose_w<T, T>(w4, w4t, s4, n_groups, cb, cs, st);      // 32 x 32 tiles through LDS
+    if (cb % 32 == 0) launch_transpose_w<T, T>(w4, w4t, s4, s4, n_groups, cb, cs, st);      // 32 x 32 tiles through LDS
     else hipLaunchKernelGGL((transpose_plain_kernel<T>), dim3((unsigned)((cb * cs + 255) / 256), 16, (unsigned)n_groups), dim3(256), 0, st, w4, w4t, cb, cs, s4);
   }
 }

@@ -1021,7 +1021,8 @@ void launch_split_weights(const SplitArgs& a, hipStream_t st) {
 
 // One 64 (cb) x 64 (cs) tile of one tap of a convolution weight: the update, the storage-type copy, and - through
 // LDS - the transposed storage-type copy, so that the new weights are read from HBM once.  fp32 storage: both copies as bf16 parts (a
-// quarter more to write: twenty 32x32 pairs 665 -> 806 us a step), which spares every GEMM block the split of its columns (8.1 -> 7.1 ms).
+// quarter more to write: twenty 32x32 pairs 665 -> 806 us a step), which spares every GEMM block the split of its columns (8.1 -> 7.1 ms); with few rows
+// a model the transposed copy in fp32 alone.
 template <typename T>
 __global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a) {
   constexpr int TSTRIDE = 64 * (int)sizeof(T) + 16;            // bytes per transposed row (64 cb)
@@ -1064,7 +1065,7 @@ __global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a) {
       st_stream(a.m + o, ms[i]);
       st_stream(a.v + o, vs[i]);
       if constexpr (sizeof(T) == 2) store4(static_cast<bf16_t*>(a.shadow) + o, tt);
-      else store_split4(a.split_u + part + (o - base), a.plane, tt);
+      else if (a.split_u) store_split4(a.split_u + part + (o - base), a.plane, tt);
 #pragma unroll
       for (int e = 0; e < 4; ++e) *reinterpret_cast<T*>(tile + (c4 + e) * TSTRIDE + row * (int)sizeof(T)) = from_float<T>(tt[e]);
     }
@@ -1075,7 +1076,12 @@ __global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a) {
       const uint4* src = reinterpret_cast<const uint4*>(tile + cs * TSTRIDE + ch * (int)sizeof(T));
       const long long o = ((long long)tap * Cs + tcs * 64 + cs) * Cb + tcb * 64 + ch;
       if constexpr (sizeof(T) == 2) *reinterpret_cast<uint4*>(static_cast<T*>(a.shadow_t) + base + o) = src[0];
-      else store_split8(a.split_d + part + o, a.plane, src[0], src[1]);
+      else if (a.split_u) store_split8(a.split_d + part + o, a.plane, src[0], src[1]);
+      else {
+        uint4* dst = reinterpret_cast<uint4*>(static_cast<T*>(a.shadow_t) + (long long)l * a.plane + a.reg_part[r] + o);
+        dst[0] = src[0];
+        dst[1] = src[1];
+      }
     }
     __syncthreads();                                              // the tile is rewritten by the next pair
   }
@@ -1102,7 +1108,7 @@ bool adam_plan(AdamArgs& a) {
       ++a.ngaps;
     }
     if (r < a.nregions) {
-      if (a.reg_cb[r] % 64 || a.reg_cs[r] % 64 || (a.shadow ? !a.shadow_t : !a.split_u || !a.split_d || a.plane % 8)) {
+      if (a.reg_cb[r] % 64 || a.reg_cs[r] % 64 || (a.split_u ? !a.split_d : !a.shadow_t) || a.plane % 8) {
         launch_fail("Adam: tiled regions need channel counts that are multiples of 64");
         return false;
       }
@@ -1154,29 +1160,30 @@ template void launch_cast_shadow<float>(const float*, float*, long long, hipStre
 
 // dst[tap][cs][cb] <- src[tap][cb][cs]; block = 32 x 32 tile, grid (tiles, 16 taps, L)
 template <typename T, typename S>
-__global__ void transpose_w_kernel(const S* __restrict__ src, T* __restrict__ dst, long long pstride, int Cb, int Cs) {
+__global__ void transpose_w_kernel(const S* __restrict__ src, T* __restrict__ dst, long long src_stride, long long dst_stride, int Cb, int Cs) {
   __shared__ float tile[32][33];
   const int tb = Cb / 32;
   const int tcs = blockIdx.x / tb, tcb = blockIdx.x - tcs * tb;
-  const long long base = (long long)blockIdx.z * pstride + (long long)blockIdx.y * Cb * Cs;
+  src += (long long)blockIdx.z * src_stride + (long long)blockIdx.y * Cb * Cs;
+  dst += (long long)blockIdx.z * dst_stride + (long long)blockIdx.y * Cb * Cs;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 256 threads: 8 rows per pass
   for (int r = ty; r < 32; r += 8) {
     const int cb = tcb * 32 + r, cs = tcs * 32 + tx;
-    tile[r][tx] = (cs < Cs) ? to_float(src[base + (long long)cb * Cs + cs]) : 0.f;
+    tile[r][tx] = (cs < Cs) ? to_float(src[(long long)cb * Cs + cs]) : 0.f;
   }
   __syncthreads();
   for (int r = ty; r < 32; r += 8) {
     const int cs = tcs * 32 + r, cb = tcb * 32 + tx;
-    if (cs < Cs) dst[base + (long long)cs * Cb + cb] = from_float<T>(tile[tx][r]);
+    if (cs < Cs) dst[(long long)cs * Cb + cb] = from_float<T>(tile[tx][r]);
   }
 }
 template <typename T, typename S>
-void launch_transpose_w(const S* src, T* dst, long long pstride, int L, int Cb, int Cs, hipStream_t st) {
+void launch_transpose_w(const S* src, T* dst, long long src_stride, long long dst_stride, int L, int Cb, int Cs, hipStream_t st) {
   dim3 grid((Cb / 32) * ((Cs + 31) / 32), 16, L);
-  hipLaunchKernelGGL((transpose_w_kernel<T, S>), grid, dim3(256), 0, st, src, dst, pstride, Cb, Cs);
+  hipLaunchKernelGGL((transpose_w_kernel<T, S>), grid, dim3(256), 0, st, src, dst, src_stride, dst_stride, Cb, Cs);
 }
-template void launch_transpose_w<float, float>(const float*, float*, long long, int, int, int, hipStream_t);
-template void launch_transpose_w<bf16_t, bf16_t>(const bf16_t*, bf16_t*, long long, int, int, int, hipStream_t);
+template void launch_transpose_w<float, float>(const float*, float*, long long, long long, int, int, int, hipStream_t);
+template void launch_transpose_w<bf16_t, bf16_t>(const bf16_t*, bf16_t*, long long, long long, int, int, int, hipStream_t);
 
 // ---------------------------------------------------------------------------------------------------------
 // Mixture sampling (Eq. 5): class draws from the prior.  The cumulative probabilities come from the host in

@@ -125,7 +125,7 @@ def _bytes_held(spec, n_models, n):
 
 def test_memory_of_parameters_in_fp32():
     """A parameter of a linear layer takes its value, its gradient and two moments, 16 bytes; one of a convolution between feature maps
-    two times three bf16 parts besides.  The tables' generator holds its convolutions' summed taps (16 for every 9 weights) once."""
+    two times three bf16 parts besides (contexts of many rows a model and all of the tables' networks).  The tables' generator holds its convolutions' summed taps (16 for every 9 weights) once."""
     wide = lambda z: dict(cond_g=0, cond_d=0, z_dim=z, img_c=1, img_hw=16, g_h0=4, g_ch=[1024, 64], d_ch=[64, 64])
     per = (_bytes_held(wide(1024), 1, 2) - _bytes_held(wide(64), 1, 2)) / (1024 * 16 * 960)
     assert 15.5 <= per <= 16.5

@@ -289,6 +289,36 @@ def test_row_splits_without_rows(prec, n):
     p.close()
 
 
+@pytest.mark.parametrize("cap", [47, 48])
+def test_fp32_weights_split_by_the_update_or_by_the_gemm(cap):
+    """Two 16x16 pairs on both sides of 256 rows to a weight and model at the sizing batch (10.86 a sample): below, the GEMMs split the weights
+    themselves and the update writes a transposed copy.  A step against the oracle; then two steps in a row against two between which the copies are made
+    anew, bit for bit; images with running statistics against the oracle."""
+    torch = U.torch_mod()
+    p = Pair("tiny0", 2, 2, cap, binding.FP32)
+    lab, z, x = batch(p.spec, np.arange(40) % 2, 720)
+    p.step(lab, z, x)
+    p.compare("sized for %d" % cap)
+    dl, dz, dx = U.dev(lab), U.dev(z), U.dev(x)
+    res = []
+    for again in (False, True):
+        g = binding.Gan(binding.make_config(p.spec, 2, 2, cap, binding.FP32, seed=6), torch.cuda.current_stream().cuda_stream)
+        g.train_step(dl.data_ptr(), dz.data_ptr(), dx.data_ptr(), 40)
+        if again:
+            for w in (0, 1):
+                g.set_params(w, 1, g.get_params(w, 1))
+        g.train_step(dl.data_ptr(), dz.data_ptr(), dx.data_ptr(), 40)
+        res.append([g.get_params(w, l) for w in (0, 1) for l in (0, 1)])
+        g.close()
+    for a, b in zip(*res):
+        assert np.array_equal(a, b)
+    out = torch.zeros((40, 3, 16, 16), device="cuda")
+    p.gpu.generate(dl.data_ptr(), dz.data_ptr(), 40, out.data_ptr(), 1)
+    rc, ref = p.orc.generate(lab, z.astype(np.float64), use_running_stats=1)
+    assert rc == 0 and U.rel_l2(out.cpu().numpy(), ref, floor=0.1 * np.sqrt(ref.size)) <= TOL[binding.FP32]
+    p.close()
+
+
 def test_free_running_steps_keep_the_stated_tolerance_while_it_means_something():
     """Three steps with no state reloaded in between, fp32 storage: the costs and parameters stay within 1e-4 of the
     fp64 oracle for the first two steps (the third is past where the oracle's own single-precision build holds it)."""
