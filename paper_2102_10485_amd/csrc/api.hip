@@ -1223,7 +1223,7 @@ AdamArgs adam_args(gan_ctx* c, Net& net) {
   return a;
 }
 // bytes one update moves per element: g, theta, m, v in; theta, m, v out; the storage-type copy (tiled regions: and the transposed
-// one; fp32: both as three planes)
+// one; fp32: both as three planes, or with few rows a model the transposed one alone)
 inline double adam_bytes_per_element(const gan_ctx* c) { return 28.0 + (c->bf16 ? 2.0 : 0.0); }
 template <typename T>
 void adam_region_call(gan_ctx* c, const AdamArgs& a, int region, hipStream_t st) {
