@@ -20,7 +20,7 @@
 // The 16-byte chunk c of row
 // R sits at position c ^ ((R / (256/KB)) % (KB/16)), which keeps both the 1 KiB-per-wave copies and the MFMA operand
 // reads conflict-free.
-// One barrier per chunk in both.
+// One barrier per chunk in both; the 256 x 256 tile of the convolutions has one per quarter of a chunk (quad_loop).
 #include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -38,8 +38,10 @@ namespace gan {
 // ring of buffers of its own, and their sums are added at the end.
 // SLOTS > 0, SHARE (forward kernel, MODE_UP): the two taps of a filter row gather the same pixels one column apart, and share one stage of
 // them; NST buffers of weights, two of SLOTS pixels.
-template <int BM_, int BN_, int WM_, int WN_, int KB_ = 128, int NST_ = 2, int KS_ = 1, int SLOTS_ = 0>
+// QUAD (forward kernel, MODE_DOWN and MODE_UP): a chunk is multiplied in four quarters, half the rows by half the columns, see quad_loop.
+template <int BM_, int BN_, int WM_, int WN_, int KB_ = 128, int NST_ = 2, int KS_ = 1, int SLOTS_ = 0, bool QUAD_ = false>
 struct Tile {
+  static constexpr bool QUAD = QUAD_;
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, KB = KB_, NST = NST_, KS = KS_;
   static constexpr bool SHARE = SLOTS_ > 0;
   // An output pixel's one tap reads the pixel that its neighbour's other tap reads, so a stage holds H + 1 pixels for every H rows of the tile.
@@ -54,6 +56,8 @@ struct Tile {
 template <typename T> struct FwdTiles;
 template <> struct FwdTiles<bf16_t> {
   typedef Tile<256, 256, 2, 4, 128, 2> Big;      // 512 threads, wave tile 128 x 64, 128 KiB of LDS
+                                                 // (MODE_DENSE, whose reductions are a few chunks)
+  typedef Tile<256, 256, 2, 4, 128, 2, 1, 0, true> BigQuad;      // the same in quarters, MODE_DOWN and MODE_UP
   typedef Tile<256, 128, 4, 2, 64, 3> Mid;       // 512 threads, wave tile 64 x 64, 72 KiB of LDS
   typedef Tile<128, 128, 2, 2, 128, 2> Small;    // 256 threads, wave tile 64 x 64 (few rows per model), 64 KiB of LDS
   typedef Small SmallWhole;
@@ -64,10 +68,9 @@ template <> struct FwdTiles<bf16_t> {
   typedef Tile<64, 64, 2, 2, 128, 2> Tiny;       // 256 threads, wave tile 32 x 32, 32 KiB of LDS: workloads so small that
                                                  // the larger tiles would leave most of the chip without a block
   // MODE_UP with shared pixels, for sides from 4 up (share_fits): the loop lives on the CU's load path, and a pair of taps brings in half the
-  // pixels and a bit.  us: 256 -> 128 channels, side 8, 6400 samples 433 -> 413; 128 -> 64, side 16, 1024 samples 106 -> 91; 512 -> 256, side 4,
-  // 6400 samples 372 -> 365.  MODE_DOWN gained nothing (256x256 401 and 402, 256x128 78.6 and 79.3, 256x64 77 and 78), nor did side 7, whose
-  // runs need padding against bank conflicts (57.7 and 58.8).
-  typedef Tile<256, 256, 2, 4, 128, 2, 1, 320> BigShare;       // 144 KiB
+  // pixels and a bit.  us: 256 -> 128 channels, side 8, 6400 samples 433 -> 413; 128 -> 64, side 16, 1024 samples 106 -> 91.  MODE_DOWN gained
+  // nothing (256x128 78.6 and 79.3, 256x64 77 and 78), nor did side 7, whose runs need padding against bank conflicts (57.7 and 58.8), and on
+  // 256x256 tiles the quarters gain more than the sharing did (512 -> 256, side 4, 6400 samples: 372 plain, 365 shared, 331 in quarters).
   typedef Tile<256, 128, 4, 2, 64, 3, 1, 320> MidShare;        // 64 KiB
   typedef Tile<128, 128, 2, 2, 128, 2, 1, 160> SmallShare;     // 72 KiB
   typedef Tile<256, 64, 4, 1, 64, 3, 1, 320> NarrowShare;      // 52 KiB, three blocks per CU
@@ -278,6 +281,20 @@ __device__ inline void lds_wait(u32x4 (&a)[TM], u32x4 (&b)[TN]) {
   else
     static_assert(TM == 4 && TN == 2, "add the operand list for this wave tile");
 }
+// the end of a quarter of a chunk (QUAD): the operands requested in it are here, at most N loads are still in flight, and so say all waves
+template <int N>
+__device__ __forceinline__ void quad_wait(u32x4 (&a)[2][4]) {
+  asm volatile("s_waitcnt vmcnt(%8) lgkmcnt(0)\n\ts_barrier" : "+v"(a[0][0]), "+v"(a[0][1]), "+v"(a[0][2]), "+v"(a[0][3]), "+v"(a[1][0]), "+v"(a[1][1]),
+               "+v"(a[1][2]), "+v"(a[1][3]) : "n"(N) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void quad_wait(u32x4 (&b)[4]) {
+  asm volatile("s_waitcnt vmcnt(%4) lgkmcnt(0)\n\ts_barrier" : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]) : "n"(N) : "memory");
+}
+// QUAD: the column of the tile that row R of a buffer of weights holds: first the 32 columns of each of the four waves' first blocks, then
+// those of their second ones
+__device__ inline int quad_col(int R) { return ((R >> 5) & 3) * 64 + (R >> 7) * 32 + (R & 31); }
+
 template <int I, int N, typename F>
 __device__ __forceinline__ void static_for(F&& f) {
   if constexpr (I < N) {
@@ -394,6 +411,12 @@ __device__ inline void load16_to_lds(const int4v& rsrc, unsigned byte_off, unsig
   asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
                : : "v"(byte_off), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane((int)uniform_off)), "s"(__builtin_amdgcn_readfirstlane((int)lds_base)) : "memory", "m0");
 }
+// The same with the LDS address as a scalar base and a constant, which then takes no register of its own.
+template <int LDS_OFF>
+__device__ inline void load16_to_lds_at(const int4v& rsrc, unsigned byte_off, unsigned uniform_off, int lds_base) {
+  asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               : : "v"(byte_off), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane((int)uniform_off)), "s"(lds_base), "n"(LDS_OFF) : "memory", "m0", "scc");
+}
 // wait until at most N loads are still in flight
 template <int N>
 __device__ inline void wait_vm() {
@@ -448,7 +471,9 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   constexpr int KB = TL::KB, NST = TL::NST, KS = TL::KS;
   static_assert(!PRE || (sizeof(T) == 4 && MODE != MODE_DENSE), "split weights: fp32 convolutions");
   constexpr int KBB = PRE ? KB / 2 * 3 : KB;                                   // bytes of a column in LDS
-  constexpr bool SHARE = TL::SHARE;
+  constexpr bool SHARE = TL::SHARE, QUAD = TL::QUAD;
+  static_assert(!QUAD || (sizeof(T) == 2 && MODE != MODE_DENSE && KB == 128 && NST == 2 && KS == 1 && !SHARE && TM == 4 && TN == 2 && PA == 4 && PB == 4),
+                "quadrants: bf16, 256 x 256");
   static_assert(!SHARE || (sizeof(T) == 2 && MODE == MODE_UP && KS == 1), "shared pixels: bf16, MODE_UP");
   constexpr int SLOTS = TL::SLOTS;
   constexpr int A_RING = SHARE ? 2 * SLOTS * KB : NST * BM * KB;               // of one group
@@ -466,7 +491,8 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   constexpr int EPV = 16 / (int)sizeof(T);
   constexpr int RPB = TL::NT / (KB / 32), PP = BN / RPB;           // PRE: rows of a plane filled per pass, passes per plane
   constexpr int LPT = PA + (PRE ? 3 * PP : PB);        // loads per thread per chunk
-  const int tid = KS == 1 ? (int)threadIdx.x : (int)threadIdx.x - kgrp * TL::NT, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tid = KS == 1 ? (int)threadIdx.x : (int)threadIdx.x - kgrp * TL::NT, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / TL::WN, wn = wave % TL::WN;
 
   // ---- which tile: consecutive virtual ids stay on one XCD (block ids are dealt round-robin to the 8 XCDs).
@@ -516,7 +542,9 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   int cnt_lo = 4, cnt_hi = 4;     // down: valid taps of the classes with ky even / odd ; up: cnt_lo = valid taps
   bool first_gone = false;        // the skipped taps are the first ones of their group (otherwise the last ones)
   if (MODE != MODE_DENSE) {
-    const int y_lo = m0 / row_block, y_hi = (min(m0 + BM, Mrows) - 1) / row_block;
+    // (scalar registers: the divisions are vector instructions, and the K order that follows from them would stay in vector registers)
+    const int y_lo = __builtin_amdgcn_readfirstlane(m0 / row_block);
+    const int y_hi = __builtin_amdgcn_readfirstlane((min(m0 + BM, Mrows) - 1) / row_block);
     const bool top_only = y_hi == 0, bottom_only = y_lo == Hr - 1;          // only the first / last pixel row
     if (MODE == MODE_DOWN) {
       if (top_only) cnt_lo = 2;                      // ky = 0 reads row -1
@@ -639,7 +667,7 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   } else {
 #pragma unroll
     for (int i = 0; i < PB; ++i) {
-      const int col = nt * BN + row0 + RPP * i;
+      const int col = nt * BN + (QUAD ? quad_col(row0 + RPP * i) : row0 + RPP * i);
       bcol[i] = col < N ? (unsigned)((col * C + chunk * EPV) * SZ) : NO_ROW;
     }
   }
@@ -686,6 +714,10 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
         ++k_cls;
         k_cnt = k_cls < 2 ? cnt_lo : cnt_hi;
       }
+    }
+    if constexpr (QUAD) {        // (kept out of the vector registers, of which none is left)
+      k_j = __builtin_amdgcn_readfirstlane(k_j);
+      k_line = __builtin_amdgcn_readfirstlane(k_line);
     }
     k_set();
   };
@@ -822,7 +854,119 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
       __syncthreads();
     }
   };
-  if constexpr (SHARE) {
+  // QUAD.  With whole chunks in two buffers a buffer is free when its last K-step has been read and has to be full one chunk later, so a
+  // chunk took at least as long as its 64 copies: 1100 to 1400 cycles to issue, in which the waves stand in front of the first products, and the
+  // slowest one's way to memory, 3500 in all for 2048 of MFMAs.  Here a wave multiplies half its rows by half its columns at a time, in
+  // the order (0, f) (0, s) (1, s) (1, f) with the operands of all four K-steps in registers, f and s being the halves of columns, f = 0 in even
+  // chunks and 1 in odd ones.  A quarter needs one half of an operand that the previous ones did not, which is read in the
+  // quarter before it; the quarter after that, the half's place in LDS is filled with that of the chunk after the next.  So every half has seven
+  // quarters to arrive in, two copies a wave go out in each, between the products, and one barrier a quarter says both that the next half is here and that
+  // the last one is free.  Cycles of a launch, 128 -> 256 channels at side 8, two segments of 6400 samples: 1538k -> 1274k, 256 -> 512 at side 4
+  // 1391k -> 1123k (matrix pipe busy 0.50 -> 0.60 and 0.52 -> 0.64 of them).  The clock goes down with the power the pipe takes, 2.05 -> 1.86 GHz, which
+  // leaves 769 -> 688 and 701 -> 616 us; 512 -> 256 transposed, side 4, one segment 363 -> 331.  Issuing the copies in front of the reads
+  // or between them, or at a raised wave priority: +-0.5 %.
+  auto quad_loop = [&](auto) __attribute__((always_inline)) {      // (a template, so that only the tiles that call it compile it)
+    clear_acc(acc);
+    k_part = k_j = k_line = k_cls = 0;
+    k_cnt = cnt_lo;
+    k_set();
+    const int a_bytes = a_rsrc.z, w_bytes = w_rsrc[0].z;
+    int4v ra = a_rsrc, rw = w_rsrc[0];
+    int to_load = nk;
+    // 128 of 256 registers are accumulators and 96 operands, so the rest is kept few: the masks of taps outside the map, 16 bits a row,
+    // of passes i and i + 2 share one, and a lane's four columns, a whole number of columns apart, one offset
+    const int out2[2] = {(outside[0] & 0xffff) | (outside[2] << 16), (outside[1] & 0xffff) | (outside[3] << 16)};
+    const int lds_wave = __builtin_amdgcn_readfirstlane((int)lds0 + wave * 1024);
+    // (the offsets come out of 64-bit multiply-adds, whose upper halves would stay in registers)
+    unsigned pix[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) asm volatile("v_mov_b32 %0, %1" : "=v"(pix[i]) : "v"(apix[i]));
+    auto load_a = [&](auto half, auto buf) __attribute__((always_inline)) {
+      static_for<0, 2>([&](auto i) __attribute__((always_inline)) {
+        load16_to_lds_at<buf.value * 32768 + half.value * 8192 + i.value * 16384>(
+            ra, pix[half.value + 2 * i.value] | (unsigned)__builtin_amdgcn_sbfe(out2[half.value], k_tap + 16 * i.value, 1), k_aoff, lds_wave);
+      });
+    };
+    auto load_b = [&](auto half, auto buf) __attribute__((always_inline)) {
+      static_for<0, 2>([&](auto i) __attribute__((always_inline)) {
+        load16_to_lds_at<65536 + buf.value * 32768 + half.value * 16384 + i.value * 8192>(
+            rw, bcol[0], k_woff + (unsigned)((half.value * 32 + i.value * 128) * C * SZ), lds_wave);
+      });
+    };
+    auto next_chunk = [&]() __attribute__((always_inline)) {
+      k_advance();
+      --to_load;
+      ra.z = to_load > 0 ? a_bytes : 0;
+      rw.z = to_load > 0 ? w_bytes : 0;
+    };
+    const int r = lane & 31, h = lane >> 5, sw = fwd_swz<KB>(r);
+    const unsigned a0 = lds0 + (wm * 128 + r) * 128 + ((h ^ sw) << 4);
+    const unsigned b0 = lds0 + 65536 + (wn * 32 + r) * 128 + ((h ^ sw) << 4);
+    u32x4 a[2][2][4], b[2][4];
+    auto read_a = [&](auto half, auto buf, auto k) __attribute__((always_inline)) {
+      lds_read16<buf.value * 32768 + half.value * 8192>(a[half.value][0][k.value], a0 ^ (k.value << 5));
+      lds_read16<buf.value * 32768 + half.value * 8192 + 4096>(a[half.value][1][k.value], a0 ^ (k.value << 5));
+    };
+    auto read_b = [&](auto half, auto buf, auto k) __attribute__((always_inline)) {
+      lds_read16<buf.value * 32768 + half.value * 16384>(b[half.value][k.value], b0 ^ (k.value << 5));
+    };
+    const std::integral_constant<int, 0> c0{};
+    const std::integral_constant<int, 1> c1{};
+    // the first two chunks, and the registers that the first quarter multiplies; the copies of chunk j go out in the order A half 0, first B,
+    // second B, A half 1, the first of them a quarter earlier than the others.  (Behind the last chunk the descriptors are empty and the
+    // copies write zeros, which nothing multiplies, so that the count in flight stays the same.)
+    load_a(c0, c0); load_b(c0, c0); load_b(c1, c0); load_a(c1, c0);
+    next_chunk();
+    load_a(c0, c1); load_b(c1, c1); load_b(c0, c1); load_a(c1, c1);
+    next_chunk();
+    wait_vm<12>();
+    __syncthreads();
+    static_for<0, 4>([&](auto k) __attribute__((always_inline)) { read_a(c0, c0, k); read_b(c0, c0, k); });
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[0][2]), "+v"(b[0][3]) : : "memory");
+    quad_wait<10>(a[0]);
+    load_a(c0, c0);
+    // a quarter of a chunk: rows ah, columns bh; reads(k) and loads(k) go between its four K-steps
+    auto quarter = [&](auto ah, auto bh, auto&& reads, auto&& loads) __attribute__((always_inline)) {
+      static_for<0, 4>([&](auto k) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          mma16B(acc[ah.value * 2 + t][bh.value], __builtin_bit_cast(uint4, a[ah.value][t][k.value]), __builtin_bit_cast(uint4, b[bh.value][k.value]), bf16_t());
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (k.value < 2) {
+          reads(std::integral_constant<int, 2 * k.value>{});
+          reads(std::integral_constant<int, 2 * k.value + 1>{});
+        }
+        if constexpr (k.value == 2) loads();
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    // chunk in buffer BUF, whose first columns are half BUF, its second ones the other half
+    auto chunk = [&](auto buf) __attribute__((always_inline)) {
+      constexpr int B = buf.value;
+      const std::integral_constant<int, B> first{};
+      const std::integral_constant<int, 1 - B> second{};
+      quarter(c0, first, [&](auto k) __attribute__((always_inline)) { read_b(second, buf, k); }, [&]() __attribute__((always_inline)) { load_b(first, buf); });
+      quad_wait<12>(b[1 - B]);
+      quarter(c0, second, [&](auto k) __attribute__((always_inline)) { read_a(c1, buf, k); }, [&]() __attribute__((always_inline)) { load_b(second, buf); });
+      quad_wait<12>(a[1]);
+      quarter(c1, second, [&](auto k) __attribute__((always_inline)) { read_a(c0, second, k); }, [&]() __attribute__((always_inline)) { load_a(c1, buf); });
+      quad_wait<12>(a[0]);
+      quarter(c1, first, [&](auto k) __attribute__((always_inline)) { read_b(second, second, k); },
+              [&]() __attribute__((always_inline)) { next_chunk(); load_a(c0, second); });
+      quad_wait<12>(b[1 - B]);
+    };
+    for (int c = 0; c < nk; c += 2) {
+      chunk(c0);
+      chunk(c1);
+    }
+    wait_vm<0>();
+    __syncthreads();
+  };
+  if constexpr (QUAD) {
+    quad_loop(0);
+    lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));      // (not kept through the loop)
+    tid = wave * 64 + lane;
+  } else if constexpr (SHARE) {
     static_assert(NST == 2 || NST == 3, "the waits count for these");
     share_loop();
   } else if constexpr (SZ == 4) {
@@ -1059,14 +1203,13 @@ static void launch_wide(const ConvArgs& a, hipStream_t st) {
       launch_one<T, MODE, EPI, decltype(tile), PRE>(a, st);
       done = true;
     };
-    shared(TILE_BIG, typename Tiles::BigShare());
     shared(TILE_MID, typename Tiles::MidShare());
     shared(TILE_SMALL, typename Tiles::SmallShare());
     shared(TILE_NARROW, typename Tiles::NarrowShare());
     if (done) return;
   }
   if constexpr (sizeof(T) == 2) {
-    if (a.tile == TILE_BIG) return launch_one<T, MODE, EPI, typename Tiles::Big, PRE>(a, st);
+    if (a.tile == TILE_BIG) return launch_one<T, MODE, EPI, std::conditional_t<MODE != MODE_DENSE, typename Tiles::BigQuad, typename Tiles::Big>, PRE>(a, st);
     if (a.tile == TILE_MID) return launch_one<T, MODE, EPI, typename Tiles::Mid, PRE>(a, st);
   }
   if (a.tile == TILE_SMALL)
@@ -1094,6 +1237,7 @@ void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
       ((epi == EPI_ACT_BWD || epi == EPI_DROP_BWD) && !a.Aux) || (epi == EPI_LABEL_LRELU && (!a.label_rows || !a.sample_slot || a.L != 1)) ||
       (epi == EPI_BN && (!a.bn_mean || !a.bn_var || !a.bn_gamma || !a.bn_beta || a.bn_C < 1)))
     return launch_fail("GEMM: null operand, or channel counts that are not whole 128-byte lines");
+  if (a.tile == TILE_BIG && a.N % 256 != 0) return launch_fail("GEMM: 256 x 256 tiles need whole tiles of columns");
   if (a.N < 64) return launch_fail("GEMM: fewer than 64 output channels (image-side outputs have their own kernel)");
   const bool pre = a.w_plane != 0;
   {

@@ -347,6 +347,37 @@ def test_conv_up_shared_pixels(ctxs, cb, cs, hs, groups, tile_rows):
     assert np.max(np.abs(got - ref)) <= tolerance(binding.BF16) * np.max(np.abs(ref))
 
 
+@pytest.mark.parametrize("up,cin,cout,hs,groups", [
+    (True, 64, 256, 4, [130]),             # tiles inside the first or last pixel row: two chunks, the fewest there are
+    (True, 64, 512, 2, [1, 0, 70]),        # two and four chunks, a model of four rows
+    (True, 192, 256, 5, [9, 2]),           # three channel lines, tiles that start inside a row
+    (False, 64, 256, 4, [130, 1]),         # twelve chunks in tiles of the first and last pixel rows, sixteen in the others
+    (False, 192, 512, 3, [30]),            # three channel lines
+])
+def test_tiles_multiplied_in_quarters(ctxs, up, cin, cout, hs, groups):
+    """256 x 256 tiles in bf16: the smallest and odd numbers of chunks, rows past a model's end, exact products.  Inputs are small whole
+    numbers, so sums are exact in fp32 and the result is the rounded exact one."""
+    torch = U.torch_mod()
+    g = ctxs[binding.BF16]
+    g.op_tile_rows(256)
+    rng = np.random.default_rng(cin + hs)
+    n, G = int(sum(groups)), len(groups)
+    offs = np.concatenate([[0], np.cumsum(groups)]).astype(np.int32)
+    cb, cs, side = (cout, cin, hs) if up else (cin, cout, 2 * hs)
+    W = rng.integers(-3, 4, (G, cs, cb, 4, 4)).astype(np.float32)
+    x = rng.integers(-3, 4, (n, cin, side, side)).astype(np.float32)
+    d_offs, d_x = U.dev(offs), U.dev(U.pack(x.transpose(0, 2, 3, 1), True))
+    d_w = U.dev(U.pack(np.ascontiguousarray(W.transpose(0, 3, 4, 2, 1) if up else W.transpose(0, 3, 4, 1, 2)).reshape(G, 16, cout, cin), True))
+    out_side = 2 * hs if up else hs
+    out = torch.zeros(n * out_side * out_side * cout, dtype=torch.int16, device="cuda")
+    (g.op_conv_up if up else g.op_conv_down)(d_x.data_ptr(), d_w.data_ptr(), out.data_ptr(), d_offs.data_ptr(), G, n, cb, cs, hs)
+    g.op_tile_rows(0)
+    got = U.unpack(out, True, (n, out_side, out_side, cout)).transpose(0, 3, 1, 2)
+    op = O.conv_transpose2d if up else O.conv2d
+    ref = np.concatenate([op(x[offs[i]:offs[i + 1]], W[i], None) for i in range(G) if groups[i]])
+    assert np.array_equal(got, U.round_to(ref, True))
+
+
 @pytest.mark.parametrize("mode", ["down", "up"])
 def test_fp32_weights_up_to_two_gibibytes(ctxs, mode):
     """A weight block of 1.45 GB: its three bf16 planes together are beyond what a 32-bit byte offset reaches, each by itself is not."""
