@@ -1558,9 +1558,167 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void wgrad_kerne
     });
   };
 
+  // QUAD: the forward-type kernel's quarters, with halves of channels on both sides.  A half of an operand is 64 rows of 128 channels in LDS.
+  // Cycles of a launch, 128 -> 256 channels at side 8, two segments of 6400 samples: 1911k -> 1639k, 256 -> 512 at side 4 1674k -> 1472k; clock
+  // 2.19 -> 2.04 GHz, 877 -> 817 and 800 -> 780 us (one segment 451 -> 433, 472 -> 446).  What is left there are the stores of dW (256 KiB a
+  // tile after 16 to 128 chunks) and the last round of blocks (800 tiles on 256 CUs).
+  const int chunks_of_share = r_hi > r_lo ? (r_hi - r_lo + WG_KR - 1) / WG_KR : 0;
+  auto quad_loop = [&](int bad0, int nbad, int nchunks) __attribute__((always_inline)) {
+    clear_acc(acc);
+    if (nchunks <= 0) return;
+    const int per_seg = chunks_of_share - nbad, sh = p.hs_shift;
+    // ---- loader: rows tid / 16 and + 32 of a chunk, 16 bytes: of A channels 128 (chunk / 8) + 64 half + 8 (chunk % 8), of B 64 (chunk / 4) +
+    // 32 half + 8 (chunk % 4) of the tile.  What rows 32 further down and the other half add is wave-uniform.
+    const int row = tid >> 4, chunk = (tid & 15) ^ (4 * (row & 3));
+    const int m = mt * BM + (chunk >> 3) * 128 + (chunk & 7) * 8, tap = m / Cb, ky = tap >> 2, kx = tap & 3;
+    const int ni = yfirst ? row >> sh : row >> (2 * sh), yi = yfirst ? 0 : (row & (rps - 1)) >> sh, xi = row & (Hs - 1);
+    const int ix = 2 * xi - 1 + kx;
+    const bool whole_rows = !yfirst && rps > 32;                 // 32 rows are some pixel rows of the same sample, otherwise some samples
+    const unsigned px = (unsigned)(Cb * SZ), line = (unsigned)Hb * px, bias = line + px;      // (row -1, column -1 have offset 0)
+    int iy = (unsigned)ix < (unsigned)Hb ? 2 * yi - 1 + ky : 1 << 20;
+    unsigned aoff = (unsigned)(ni * Hb * Hb) * px + (unsigned)(2 * yi + ky) * line + (unsigned)(ix + 1) * px + (unsigned)(m - tap * Cb) * SZ;
+    unsigned boff = (unsigned)(((yfirst ? (row >> sh) * rps + xi : row) * Cs + nt * BN + (chunk >> 2) * 64 + (chunk & 3) * 8) * SZ);
+    const int rows32 = 32 >> sh;                                 // 32 rows in pixel rows of one sample
+    const unsigned a32 = whole_rows ? 2 * rows32 * line : (yfirst ? rows32 : 32 >> (2 * sh)) * (unsigned)(Hb * Hb) * px;
+    const unsigned b32 = (unsigned)((yfirst ? rows32 * rps : 32) * Cs * SZ);
+    const int dy32 = whole_rows ? 2 * rows32 : 0;
+    // ---- the chunk to load next
+    const unsigned long long a_bytes = (unsigned long long)(s1 - s0) * big_per_sample * SZ + bias, b_bytes = (unsigned long long)R * Cs * SZ;
+    const T* a_base = reinterpret_cast<const T*>(reinterpret_cast<const unsigned char*>(static_cast<const T*>(p.Big) + s0 * big_per_sample) - bias);
+    const T* b_base = static_cast<const T*>(p.Small) + (long long)s0 * rps * Cs;
+    int4v ra = make_rsrc(a_base, a_bytes), rb_ = make_rsrc(b_base, b_bytes);
+    int cin = 0, to_load = __builtin_amdgcn_readfirstlane(nchunks), k0, y0 = 0, rem = 0, left, y2;
+    unsigned a_delta, b_delta;
+    auto place = [&]() __attribute__((always_inline)) {
+      k0 = r_lo + (cin < bad0 ? cin : cin + nbad) * WG_KR;
+      if (yfirst) {
+        y0 = __builtin_amdgcn_readfirstlane(k0 / rb);
+        rem = k0 - y0 * rb;
+      }
+    };
+    auto set = [&]() __attribute__((always_inline)) {
+      left = r_hi - k0;
+      const int n0 = yfirst ? rem >> sh : k0 >> (2 * sh), y = yfirst ? y0 : (k0 & (rps - 1)) >> sh;
+      y2 = 2 * y;
+      a_delta = (unsigned)((n0 * Hb + y2) * Hb) * px;
+      b_delta = yfirst ? (unsigned)(((n0 * Hs + y0) * Hs) * Cs * SZ) : (unsigned)(k0 * Cs * SZ);
+    };
+    auto next_chunk = [&]() __attribute__((always_inline)) {
+      if (--to_load <= 0) {                                      // behind the last chunk: copies of zeros
+        ra.z = rb_.z = 0;
+        return;
+      }
+      if (++cin == per_seg) {
+        cin = 0;
+        a_base += (long long)p.seg_samples * big_per_sample;
+        b_base += (long long)p.seg_samples * rps * Cs;
+        ra = make_rsrc(a_base, a_bytes);
+        rb_ = make_rsrc(b_base, b_bytes);
+        place();
+      } else if (cin == bad0 && nbad > 0) {
+        place();
+      } else {
+        k0 += WG_KR;
+        rem += WG_KR;
+        if (rem == rb) { rem = 0; ++y0; }
+      }
+      // (kept out of the vector registers, of which none is left)
+      cin = __builtin_amdgcn_readfirstlane(cin);
+      k0 = __builtin_amdgcn_readfirstlane(k0);
+      rem = __builtin_amdgcn_readfirstlane(rem);
+      y0 = __builtin_amdgcn_readfirstlane(y0);
+      set();
+    };
+    const int lds_wave = __builtin_amdgcn_readfirstlane((int)lds0 + wave * 1024);
+    auto load_a = [&](auto half, auto buf) __attribute__((always_inline)) {
+      static_for<0, 2>([&](auto i) __attribute__((always_inline)) {
+        const bool ok = row + 32 * i.value < left && (unsigned)(iy + y2 + i.value * dy32) < (unsigned)Hb;
+        load16_to_lds_at<buf.value * 32768 + half.value * 16384 + i.value * 8192>(ra, ok ? aoff : NO_ROW, a_delta + i.value * a32 + half.value * 128, lds_wave);
+      });
+    };
+    auto load_b = [&](auto half, auto buf) __attribute__((always_inline)) {
+      static_for<0, 2>([&](auto i) __attribute__((always_inline)) {
+        load16_to_lds_at<65536 + buf.value * 32768 + half.value * 16384 + i.value * 8192>(rb_, row + 32 * i.value < left ? boff : NO_ROW,
+                                                                                        b_delta + i.value * b32 + half.value * 64, lds_wave);
+      });
+    };
+    // ---- operands: rows of 128 channels (256 bytes); the two fragments of a half of A differ in bit 2 of the chunk
+    const unsigned char* ap[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) ap[t] = smem + frow * 256 + ((wm * 8 + t * 4 + fch) ^ (4 * (frow & 3))) * 16 + fbyte;
+    const unsigned char* const bp = smem + 65536 + frow * 256 + ((wn * 4 + fch) ^ (4 * (frow & 3))) * 16 + fbyte;
+    u32x4 a[2][2][4], b[2][4];
+    auto fragment = [&](const unsigned char* q) __attribute__((always_inline)) {
+      const uint2 lo = lds_read_tr16(q), hi = lds_read_tr16(q + 4 * 256);
+      u32x4 v;
+      v.x = lo.x; v.y = lo.y; v.z = hi.x; v.w = hi.y;
+      return v;
+    };
+    auto read_a = [&](auto half, auto buf, auto k) __attribute__((always_inline)) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) a[half.value][t][k.value] = fragment(ap[t] + buf.value * 32768 + half.value * 16384 + k.value * 4096);
+    };
+    auto read_b = [&](auto half, auto buf, auto k) __attribute__((always_inline)) {
+      b[half.value][k.value] = fragment(bp + buf.value * 32768 + half.value * 16384 + k.value * 4096);
+    };
+    const std::integral_constant<int, 0> c0{};
+    const std::integral_constant<int, 1> c1{};
+    // (the waits as builtins: the compiler counts these reads, and would count them beyond the waits otherwise)
+    auto next_quarter = [](auto in_flight) __attribute__((always_inline)) {
+      asm volatile("" : : : "memory");
+      __builtin_amdgcn_s_waitcnt(0x70 | in_flight.value);       // vmcnt(in_flight) lgkmcnt(0)
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" : : : "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    const std::integral_constant<int, 12> six{};                 // quarters' copies
+    place();
+    set();
+    load_a(c0, c0); load_b(c0, c0); load_b(c1, c0); load_a(c1, c0);
+    next_chunk();
+    load_a(c0, c1); load_b(c1, c1); load_b(c0, c1); load_a(c1, c1);
+    next_chunk();
+    next_quarter(six);
+    static_for<0, 4>([&](auto k) __attribute__((always_inline)) { read_a(c0, c0, k); read_b(c0, c0, k); });
+    next_quarter(std::integral_constant<int, 10>{});
+    load_a(c0, c0);
+    auto quarter = [&](auto ah, auto bh, auto&& reads, auto&& loads) __attribute__((always_inline)) {
+      static_for<0, 4>([&](auto k) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          mma16B(acc[ah.value * 2 + t][bh.value], __builtin_bit_cast(uint4, a[ah.value][t][k.value]), __builtin_bit_cast(uint4, b[bh.value][k.value]), bf16_t());
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (k.value < 2) {
+          reads(std::integral_constant<int, 2 * k.value>{});
+          reads(std::integral_constant<int, 2 * k.value + 1>{});
+        }
+        if constexpr (k.value == 2) loads();
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      next_quarter(six);
+    };
+    auto chunk_mma = [&](auto buf) __attribute__((always_inline)) {
+      constexpr int B = buf.value;
+      const std::integral_constant<int, B> first{};
+      const std::integral_constant<int, 1 - B> second{};
+      quarter(c0, first, [&](auto k) __attribute__((always_inline)) { read_b(second, buf, k); }, [&]() __attribute__((always_inline)) { load_b(first, buf); });
+      quarter(c0, second, [&](auto k) __attribute__((always_inline)) { read_a(c1, buf, k); }, [&]() __attribute__((always_inline)) { load_b(second, buf); });
+      quarter(c1, second, [&](auto k) __attribute__((always_inline)) { read_a(c0, second, k); }, [&]() __attribute__((always_inline)) { load_a(c1, buf); });
+      quarter(c1, first, [&](auto k) __attribute__((always_inline)) { read_b(second, second, k); },
+              [&]() __attribute__((always_inline)) { next_chunk(); load_a(c0, second); });
+    };
+    for (int c = 0; c < nchunks; c += 2) {
+      chunk_mma(c0);
+      if (c + 1 == nchunks) break;
+      chunk_mma(c1);
+    }
+    wait_vm<0>();
+    __syncthreads();
+  };
+
   // chunks of all segments as one sequence; in pixel-row-first order the chunks [bad0, bad0 + nbad) of every segment
   // (the pixel row whose tap row is outside the map) are left out
-  const int per_seg_all = r_hi > r_lo ? (r_hi - r_lo + WG_KR - 1) / WG_KR : 0;
+  const int per_seg_all = chunks_of_share;
   int bad0 = 0, nbad = 0;
   if (yfirst && per_seg_all > 0 && (ky_tile == 0 || ky_tile == 3)) {
     const int yb = ky_tile == 0 ? 0 : Hs - 1;
@@ -1592,6 +1750,8 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void wgrad_kerne
     row_loop(mma_chunk_split);
     add_acc(acc, low);
     if (block_any<NT_ / 64>(not_finite(acc), smem, wave)) row_loop(mma_chunk32);
+  } else if constexpr (TL::QUAD) {
+    quad_loop(bad0, nbad, nchunks);
   } else {
     row_loop(mma_chunk16);
   }
@@ -1642,6 +1802,7 @@ typedef Tile<64, 128, 1, 4> TileWgImg;    // patch-matrix layers: 64 packed colu
 typedef Tile<64, 64, 2, 2> TileWgImg64;   //   and x 64
 typedef Tile<256, 64, 4, 1> TileWg64;     // 64 channels on the N side, bf16
 typedef Tile<256, 256, 2, 4> TileWgBig;
+typedef Tile<256, 256, 2, 4, 128, 2, 1, 0, true> TileWgQuad;      // in quarters, see quad_loop
 typedef Tile<256, 128, 4, 2> TileWgMid;
 typedef Tile<128, 128, 2, 2> TileWgF32;
 typedef Tile<128, 64, 2, 2> TileWgF32N;
@@ -1662,6 +1823,14 @@ static void launch_wgrad_one(WgradArgs a, hipStream_t st) {
   if (a.hs_shift < 0 && a.seg_samples * rps * rps < (1LL << 32)) {
     a.rps_inv = (unsigned)(((1ULL << 32) + rps - 1) / rps);
     a.hs_inv = (unsigned)(((1ULL << 32) + a.Hs - 1) / a.Hs);
+  }
+  if constexpr (std::is_same_v<TL, TileWgBig>) {
+    // What the quarters' loader assumes: both halves of a tile's big channels under the same tap, whole tiles, and 32 rows of a chunk a fixed
+    // distance from the other 32.  Other shapes have no registers left for their rows.
+    if (a.ntaps == 16 && a.Cb % 128 == 0 && a.Cs % 256 == 0 && a.hs_shift >= 0 && a.Hs <= 32) {
+      hipLaunchKernelGGL((wgrad_kernel<T, TileWgQuad>), dim3((unsigned)blocks), dim3(TL::NT), 0, st, a);
+      return;
+    }
   }
   hipLaunchKernelGGL((wgrad_kernel<T, TL>), dim3((unsigned)blocks), dim3(TL::NT), 0, st, a);
 }

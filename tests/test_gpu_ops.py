@@ -378,6 +378,38 @@ def test_tiles_multiplied_in_quarters(ctxs, up, cin, cout, hs, groups):
     assert np.array_equal(got, U.round_to(ref, True))
 
 
+@pytest.mark.parametrize("cb,cs,hs,groups", [
+    (128, 256, 1, [3, 0, 130]),            # one chunk and three, the last one of two rows
+    (128, 256, 2, [5, 16, 32, 33]),        # pixel rows in turn (16, 32 samples) and samples in turn
+    (256, 512, 8, [1, 8, 9]),              # the same, one chunk a sample
+    (384, 256, 4, [16, 7]),                # a tile over two taps
+    (128, 512, 16, [1, 4]),                # chunks of four pixel rows; the top or bottom row's chunks left out
+    (128, 256, 32, [2, 1]),                # the largest side
+    (128, 256, 64, [1]), (192, 256, 4, [9]),       # not multiplied in quarters
+])
+def test_weight_gradient_in_quarters(ctxs, cb, cs, hs, groups):
+    """256 x 256 tiles of the bf16 weight gradient: small whole numbers, so that every sum is exact in fp32."""
+    torch = U.torch_mod()
+    g = ctxs[binding.BF16]
+    rng = np.random.default_rng(cb + hs)
+    n, G = int(sum(groups)), len(groups)
+    offs = np.concatenate([[0], np.cumsum(groups)]).astype(np.int32)
+    big = rng.integers(-3, 4, (n, 2 * hs, 2 * hs, cb)).astype(np.float32)
+    small = rng.integers(-3, 4, (n, hs, hs, cs)).astype(np.float32)
+    d_offs, d_big, d_small = U.dev(offs), U.dev(U.pack(big, True)), U.dev(U.pack(small, True))
+    dw = torch.full((G, 4, 4, cb, cs), 7.0, dtype=torch.float32, device="cuda")
+    g.op_conv_wgrad(d_big.data_ptr(), d_small.data_ptr(), dw.data_ptr(), d_offs.data_ptr(), G, n, cb, cs, hs)
+    got = dw.cpu().numpy()
+    pad = np.pad(big, ((0, 0), (1, 1), (1, 1), (0, 0)))
+    for i in range(G):
+        part = slice(offs[i], offs[i + 1])
+        y = small[part].reshape(-1, cs)
+        for ky in range(4):
+            for kx in range(4):
+                x = pad[part, ky:ky + 2 * hs:2, kx:kx + 2 * hs:2].reshape(-1, cb)
+                assert np.array_equal(got[i, ky, kx], x.T @ y), (i, ky, kx)
+
+
 @pytest.mark.parametrize("mode", ["down", "up"])
 def test_fp32_weights_up_to_two_gibibytes(ctxs, mode):
     """A weight block of 1.45 GB: its three bf16 planes together are beyond what a 32-bit byte offset reaches, each by itself is not."""
