@@ -406,6 +406,9 @@ __device__ inline int4v make_rsrc(const void* base, unsigned long long bytes) {
   r.w = 0x00020000;
   return r;
 }
+__device__ inline __amdgpu_buffer_rsrc_t buffer_of(const void* base, unsigned long long bytes) {      // the same for the load builtins
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)(unsigned)(bytes > 0xfffffff0ull ? 0xfffffff0ull : bytes), 0x00020000);
+}
 // The wave-uniform part of the offset (which tap, which channels) travels in a scalar register.
 __device__ inline void load16_to_lds(const int4v& rsrc, unsigned byte_off, unsigned uniform_off, unsigned lds_base) {
   asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
@@ -1403,12 +1406,8 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void wgrad_kerne
     else fb_off[i] = (unsigned)((c * Cs + cB) * SZ);
   }
 
-  auto load_chunk = [&](int seg, int k0, int stage) __attribute__((always_inline)) {
-    const long long sb = (long long)seg * p.seg_samples + s0;
-    const int4v a_rsrc = make_rsrc(static_cast<const T*>(p.Big) + sb * big_per_sample, (unsigned long long)(s1 - s0) * big_per_sample * SZ);
-    const int4v b_rsrc = make_rsrc(static_cast<const T*>(p.Small) + sb * rps * Cs, (unsigned long long)R * Cs * SZ);
-    const unsigned a_dst = lds0 + stage * STAGE_A + wave * 1024;
-    const unsigned b_dst = lds0 + 2 * STAGE_A + stage * STAGE_B + wave * 1024;
+  // this thread's byte offsets of a chunk, as a_load(pass, offset) and b_load(pass, offset)
+  auto chunk_offsets = [&](int k0, auto&& a_load, auto&& b_load) __attribute__((always_inline)) {
     const int left = r_hi - k0;                 // rows of this chunk that exist
     unsigned b_delta = (unsigned)(k0 * Cs * SZ);
     if (fast) {
@@ -1429,7 +1428,7 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void wgrad_kerne
 #pragma unroll
       for (int i = 0; i < PA; ++i) {
         const bool ok = rowA0 + i * RPA < left && (unsigned)(fa_iy[i] + y2) < (unsigned)Hb;
-        load16_to_lds(a_rsrc, ok ? fa_off[i] + a_delta : NO_ROW, 0u, a_dst + i * NT_ * 16);
+        a_load(i, ok ? fa_off[i] + a_delta : NO_ROW);
       }
     } else {
 #pragma unroll
@@ -1449,12 +1448,21 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void wgrad_kerne
           const int iy = 2 * y - 1 + kyA, ix = 2 * x - 1 + kxA;
           if ((unsigned)iy < (unsigned)Hb && (unsigned)ix < (unsigned)Hb) off = (unsigned)((((n * Hb + iy) * Hb + ix) * Cb + cA) * SZ);
         }
-        load16_to_lds(a_rsrc, off, 0u, a_dst + i * NT_ * 16);
+        a_load(i, off);
       }
     }
 #pragma unroll
-    for (int i = 0; i < PB; ++i)
-      load16_to_lds(b_rsrc, (rowB0 + i * RPB < left && okB) ? fb_off[i] + b_delta : NO_ROW, 0u, b_dst + i * NT_ * 16);
+    for (int i = 0; i < PB; ++i) b_load(i, (rowB0 + i * RPB < left && okB) ? fb_off[i] + b_delta : NO_ROW);
+  };
+  auto a_slice = [&](int seg) { return static_cast<const T*>(p.Big) + ((long long)seg * p.seg_samples + s0) * big_per_sample; };
+  auto b_slice = [&](int seg) { return static_cast<const T*>(p.Small) + ((long long)seg * p.seg_samples + s0) * rps * Cs; };
+  const unsigned long long a_slice_bytes = (unsigned long long)(s1 - s0) * big_per_sample * SZ, b_slice_bytes = (unsigned long long)R * Cs * SZ;
+  auto load_chunk = [&](int seg, int k0, int stage) __attribute__((always_inline)) {
+    const int4v a_rsrc = make_rsrc(a_slice(seg), a_slice_bytes), b_rsrc = make_rsrc(b_slice(seg), b_slice_bytes);
+    const unsigned a_dst = lds0 + stage * STAGE_A + wave * 1024;
+    const unsigned b_dst = lds0 + 2 * STAGE_A + stage * STAGE_B + wave * 1024;
+    chunk_offsets(k0, [&](int i, unsigned off) __attribute__((always_inline)) { load16_to_lds(a_rsrc, off, 0u, a_dst + i * NT_ * 16); },
+                  [&](int i, unsigned off) __attribute__((always_inline)) { load16_to_lds(b_rsrc, off, 0u, b_dst + i * NT_ * 16); });
   };
 
   floatx16 acc[TM][TN], low[TM][TN];      // (low: fp32 only)
@@ -1536,26 +1544,69 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void wgrad_kerne
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // fp32 through splits: a step is sixteen rows; lane half h reads rows 16 st + 2 j + h, j = 0..7
-  auto mma_chunk_split = [&](int stage) __attribute__((always_inline)) {
-    const int r = lane & 31, h = lane >> 5;
-    const unsigned char* As = smem + stage * STAGE_A + h * RBA + (r & 3) * 4;
-    const unsigned char* Bs = smem + 2 * STAGE_A + stage * STAGE_B + h * RBB + (r & 3) * 4;
-    const auto column = [&](const unsigned char* base, int tile32, int row_bytes, int st) __attribute__((always_inline)) {     // this lane's eight values of one fragment
-      const unsigned char* q = base + ((tile32 * 8 + (r >> 2)) ^ (8 * h)) * 16 + st * 16 * row_bytes;
-      u32x4 lo, hi;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        lo[j] = *reinterpret_cast<const unsigned*>(q + 2 * j * row_bytes);
-        hi[j] = *reinterpret_cast<const unsigned*>(q + 2 * (j + 4) * row_bytes);
-      }
-      return split8(lo, hi);
+  // fp32 through splits: the chunk comes into registers, is split there, once a block, and goes to LDS as three planes of bf16 rows, which are then
+  // read like a bf16 chunk.  Split by the waves that multiply, every value was split twice in a 128 x 128 tile, and the vector instructions of that took
+  // longer (830 cycles a 16-row step) than the MFMAs (770): 128 -> 256 channels, side 8, two segments of 20 x 64 samples 1035 -> 942 us,
+  // 256 -> 512, side 4 1060 -> 949, patch-matrix layer 156 -> 137; 10 x 128 samples, 64 -> 128, side 7 256 -> 229.  The matrix pipe is busy 0.57 of the
+  // time a CU has blocks.  PLANE: bytes of one; buffers are not doubled, the next chunk waits in the registers.
+  constexpr int PLANE_A = WG_KR * BM * 2, PLANE_B = WG_KR * BN * 2;
+  auto split_loop = [&](auto chunk_row, int per_seg, int nchunks) __attribute__((always_inline)) {
+    clear_acc(acc);
+    clear_acc(low);
+    if (nchunks <= 0) return;
+    static_assert(sizeof(T) == 2 || 3 * (PLANE_A + PLANE_B) <= 2 * (STAGE_A + STAGE_B), "the planes fit into the buffers");
+    u32x4 va[PA], vb[PB];
+    auto fetch = [&](int seg, int k0) __attribute__((always_inline)) {
+      const __amdgpu_buffer_rsrc_t ra = buffer_of(a_slice(seg), a_slice_bytes), rb_ = buffer_of(b_slice(seg), b_slice_bytes);
+      chunk_offsets(k0, [&](int i, unsigned off) __attribute__((always_inline)) { va[i] = __builtin_amdgcn_raw_buffer_load_b128(ra, off, 0, 0); },
+                    [&](int i, unsigned off) __attribute__((always_inline)) { vb[i] = __builtin_amdgcn_raw_buffer_load_b128(rb_, off, 0, 0); });
     };
-    static_for<0, WG_KR / 16>([&](auto st) __attribute__((always_inline)) {
-      Split8 b[TN];
-      static_for<0, TN>([&](auto t) __attribute__((always_inline)) { b[t.value] = column(Bs, wn * TN + t.value, RBB, st.value); });
-      static_for<0, TM>([&](auto t) __attribute__((always_inline)) { mma_split(acc[t.value], low[t.value], column(As, wm * TM + t.value, RBA, st.value), b); });
-    });
+    // four channels of a row into the three planes
+    auto put = [&](unsigned char* plane0, int plane_bytes, int row_bytes, int row, int ch, int swz, const u32x4& v) __attribute__((always_inline)) {
+      const Split4 q = split4(v);
+      unsigned char* const at = plane0 + row * row_bytes + (((ch >> 1) ^ swz) << 4) + (ch & 1) * 8;
+      *reinterpret_cast<uint2*>(at) = q.h;
+      *reinterpret_cast<uint2*>(at + plane_bytes) = q.m;
+      *reinterpret_cast<uint2*>(at + 2 * plane_bytes) = q.l;
+    };
+    unsigned char* const Ap = smem;
+    unsigned char* const Bp = smem + 3 * PLANE_A;
+    auto fragment = [&](const unsigned char* base, int plane_bytes, int row_bytes, int tile32, int swz, int ks) __attribute__((always_inline)) {
+      const unsigned char* q = base + (ks * 16 + frow) * row_bytes + ((tile32 * 4 + fch) ^ swz) * 16 + fbyte;
+      Split8 v;
+      const auto one = [&](u32x4& d, const unsigned char* a) __attribute__((always_inline)) {
+        const uint2 lo = lds_read_tr16(a), hi = lds_read_tr16(a + 4 * row_bytes);
+        d.x = lo.x; d.y = lo.y; d.z = hi.x; d.w = hi.y;
+      };
+      one(v.h, q);
+      one(v.m, q + plane_bytes);
+      one(v.l, q + 2 * plane_bytes);
+      return v;
+    };
+    const int sa = wg_swz<bf16_t, BM * 2>(frow), sb = wg_swz<bf16_t, BN * 2>(frow);
+    fetch(0, chunk_row(0));
+    int seg = 0, cin = 0;
+    for (int c = 0; c < nchunks; ++c) {
+      if (c > 0) __syncthreads();                                // the previous chunk has been read
+#pragma unroll
+      for (int i = 0; i < PA; ++i) put(Ap, PLANE_A, BM * 2, rowA0 + i * RPA, chA, wg_swz<bf16_t, BM * 2>(rowA0 + i * RPA), va[i]);
+#pragma unroll
+      for (int i = 0; i < PB; ++i) put(Bp, PLANE_B, BN * 2, rowB0 + i * RPB, chB, wg_swz<bf16_t, BN * 2>(rowB0 + i * RPB), vb[i]);
+      if (c + 1 < nchunks) {
+        if (++cin == per_seg) { cin = 0; ++seg; }
+        fetch(seg, chunk_row(cin));
+      }
+      __syncthreads();
+#pragma unroll
+      for (int ks = 0; ks < WG_KR / 16; ++ks) {
+        Split8 b[TN];
+#pragma unroll
+        for (int t = 0; t < TN; ++t) b[t] = fragment(Bp, PLANE_B, BN * 2, wn * TN + t, sb, ks);
+#pragma unroll
+        for (int t = 0; t < TM; ++t) mma_split(acc[t], low[t], fragment(Ap, PLANE_A, BM * 2, wm * TM + t, sa, ks), b);
+      }
+    }
+    __syncthreads();
   };
 
   // QUAD: the forward-type kernel's quarters, with halves of channels on both sides.  A half of an operand is 64 rows of 128 channels in LDS.
@@ -1746,8 +1797,7 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void wgrad_kerne
     }
   };
   if constexpr (SZ == 4) {
-    clear_acc(low);
-    row_loop(mma_chunk_split);
+    split_loop(chunk_row, per_seg, nchunks);
     add_acc(acc, low);
     if (block_any<NT_ / 64>(not_finite(acc), smem, wave)) row_loop(mma_chunk32);
   } else if constexpr (TL::QUAD) {

@@ -57,6 +57,14 @@ __device__ __forceinline__ Split8 split8(const u32x4& lo, const u32x4& hi) {
   }
   return s;
 }
+// four neighbouring values of a row
+struct Split4 { uint2 h, m, l; };
+__device__ __forceinline__ Split4 split4(const u32x4& v) {
+  Split4 s;
+  split_pair(__uint_as_float(v[0]), __uint_as_float(v[1]), s.h.x, s.m.x, s.l.x);
+  split_pair(__uint_as_float(v[2]), __uint_as_float(v[3]), s.h.y, s.m.y, s.l.y);
+  return s;
+}
 __device__ inline void mma_u4(floatx16& acc, const u32x4& a, const u32x4& b) {
   mma16B(acc, __builtin_bit_cast(uint4, a), __builtin_bit_cast(uint4, b), bf16_t());
 }
