@@ -244,7 +244,7 @@ def mfma_summary(kern, peak):
 
 # the bandwidth-bound kernel families reported against the HBM peak (algorithmic bytes: every input read once, every
 # output written once, in the storage type; Adam: 28 B per parameter plus the storage-type copies)
-ELEMENTWISE = ("adam", "bn_apply", "bn_bwd_reduce", "bn_bwd_apply", "im2col", "up_img", "head_fwd", "head_bwd_data", "head_bwd_w",
+ELEMENTWISE = ("adam", "bn_apply", "bn_bwd_reduce", "bn_bwd_apply", "im2col", "up_img", "head_fwd", "head_bwd",
                "stage", "transpose_w")
 
 

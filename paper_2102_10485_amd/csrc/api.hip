@@ -809,6 +809,24 @@ PackArgs pack_args(gan_ctx* c, Net& net, const ConvLayer& cl, int Kc, int nslot,
   return a;
 }
 
+// D's linear head.  Both segments: the discriminator's cost on (real, fake); the fake one alone: the generator's.
+HeadArgs head_args(gan_ctx* c, int n, int seg_first, int nseg) {
+  Net& D = c->D;
+  HeadArgs h;
+  memset(&h, 0, sizeof(h));
+  h.feat = c->dact[D.conv.size() - 1]; h.dfeat = c->bufA; h.w = D.theta + D.fc_w; h.b = D.theta + D.fc_b;
+  h.dw = D.g + D.fc_w; h.db = D.g + D.fc_b; h.pstride = D.P; h.logits = c->logits; h.dlogits = c->dlogits;
+  h.part = c->head_part; h.rsplit = c->head_rsplit;
+  h.offs = c->rb.offs; h.sample_model = c->rb.sample_model; h.L = c->L; h.K = D.K;
+  h.seg_first = seg_first; h.nseg = nseg; h.seg_samples = n; h.n = n;
+  h.mode = nseg == 2 ? 0 : 1;
+  h.loss = h.mode == 0 ? c->loss_d : c->loss_g;
+  h.scale = h.mode == 0 ? c->cfg.d_loss_scale : c->cfg.g_loss_scale;
+  const Net& net = h.mode == 0 ? c->D : c->G;      // whose update follows
+  h.adam_t = net.t; h.adam_bc = net.bc; h.beta1 = c->cfg.beta1; h.beta2 = c->cfg.beta2;
+  return h;
+}
+
 // ---- the networks -------------------------------------------------------------------------------------------
 // user: the caller's images (generation), or NULL: into the fake half of D's image buffer
 template <typename T>
@@ -853,25 +871,8 @@ void d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_running) 
                                   c->d_sums[j], seg_first, nseg, n, slope),
                   c->dpre[j], c->dact[j], update_running, MODE_DOWN, cl.Hs * cl.Hs);
   }
-  HeadArgs h;
-  memset(&h, 0, sizeof(h));
-  h.feat = c->dact[nl - 1]; h.w = D.theta + D.fc_w; h.b = D.theta + D.fc_b; h.pstride = D.P; h.logits = c->logits;
-  h.offs = c->rb.offs; h.sample_model = c->rb.sample_model; h.L = c->L; h.K = D.K;
-  h.seg_first = seg_first; h.nseg = nseg; h.seg_samples = n; h.n = n;
   Scope s(c, "head_fwd", 0, sizeof(T) * (double)n * nseg * D.K);
-  launch_head_fwd<T>(h, c->st);
-}
-
-// mode 0: discriminator cost on (real, fake); mode 1: generator cost on the fake segment.  Also advances the player's step counts.
-void loss_call(gan_ctx* c, int n, int mode) {
-  HeadArgs h;
-  memset(&h, 0, sizeof(h));
-  h.logits = c->logits; h.dlogits = c->dlogits; h.loss = mode == 0 ? c->loss_d : c->loss_g;
-  h.offs = c->rb.offs; h.L = c->L; h.seg_first = mode == 0 ? 0 : 1; h.nseg = mode == 0 ? 2 : 1; h.seg_samples = n; h.n = n;
-  const Net& net = mode == 0 ? c->D : c->G;
-  h.adam_t = net.t; h.adam_bc = net.bc; h.beta1 = c->cfg.beta1; h.beta2 = c->cfg.beta2;
-  h.mode = mode; h.scale = mode == 0 ? c->cfg.d_loss_scale : c->cfg.g_loss_scale;
-  launch_loss(h, c->st);
+  launch_head_fwd<T>(head_args(c, n, seg_first, nseg), c->st);
 }
 
 // Backward through D.  param_grads: fill D's gradient block (both segments summed).  to_image: continue down to
@@ -884,15 +885,10 @@ void d_backward(gan_ctx* c, int n, int seg_first, int nseg, bool param_grads, bo
   hipStream_t side = side_stream(c);
   const float slope = c->cfg.leaky_slope;
   const int nl = (int)D.conv.size();
-  HeadArgs h;
-  memset(&h, 0, sizeof(h));
-  h.feat = c->dact[nl - 1]; h.dfeat = c->bufA; h.w = D.theta + D.fc_w; h.b = D.theta + D.fc_b;
-  h.dw = D.g + D.fc_w; h.db = D.g + D.fc_b; h.pstride = D.P; h.dlogits = c->dlogits;
-  h.part = c->head_part; h.rsplit = c->head_rsplit;
-  h.offs = c->rb.offs; h.sample_model = c->rb.sample_model; h.L = c->L; h.K = D.K;
-  h.seg_first = seg_first; h.nseg = nseg; h.seg_samples = n; h.n = n;
-  { Scope s(c, "head_bwd_data", 0, sizeof(T) * (double)n * nseg * D.K); launch_head_bwd_data<T>(h, c->st); }
-  if (param_grads) { Scope s(c, "head_bwd_w", 0, sizeof(T) * (double)n * nseg * D.K); launch_head_bwd_w<T>(h, c->st); }
+  {
+    Scope s(c, "head_bwd", 0, sizeof(T) * (double)n * nseg * D.K * (param_grads ? 2 : 1));
+    launch_head_bwd<T>(head_args(c, n, seg_first, nseg), param_grads, c->st);
+  }
   int pending = -1;                // region of D's planned update whose turn comes next
   for (int j = nl - 1; j >= 1; --j) {
     const ConvLayer& cl = D.conv[j];
@@ -1085,13 +1081,8 @@ void paper_d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_run
                                          c->d_sums[j], seg_first, nseg, n, 1.f),
                          c->dpre[j], c->dact[j], f.bn_eps, update_running);
   }
-  HeadArgs h;
-  memset(&h, 0, sizeof(h));
-  h.feat = c->dact[nl - 1]; h.w = D.theta + D.fc_w; h.b = D.theta + D.fc_b; h.pstride = D.P; h.logits = c->logits;
-  h.offs = c->rb.offs; h.sample_model = c->rb.sample_model; h.L = c->L; h.K = D.K;
-  h.seg_first = seg_first; h.nseg = nseg; h.seg_samples = n; h.n = n;
   Scope s(c, "head_fwd", 0, sizeof(T) * (double)n * nseg * D.K);
-  launch_head_fwd<T>(h, c->st);
+  launch_head_fwd<T>(head_args(c, n, seg_first, nseg), c->st);
 }
 
 template <typename T>
@@ -1099,15 +1090,10 @@ void paper_d_backward(gan_ctx* c, int n, int seg_first, int nseg, bool param_gra
   Net& D = c->D;
   const gan_config& f = c->cfg;
   const int nl = (int)D.conv.size();
-  HeadArgs h;
-  memset(&h, 0, sizeof(h));
-  h.feat = c->dact[nl - 1]; h.dfeat = c->bufA; h.w = D.theta + D.fc_w; h.b = D.theta + D.fc_b;
-  h.dw = D.g + D.fc_w; h.db = D.g + D.fc_b; h.pstride = D.P; h.dlogits = c->dlogits;
-  h.part = c->head_part; h.rsplit = c->head_rsplit;
-  h.offs = c->rb.offs; h.sample_model = c->rb.sample_model; h.L = c->L; h.K = D.K;
-  h.seg_first = seg_first; h.nseg = nseg; h.seg_samples = n; h.n = n;
-  { Scope s(c, "head_bwd_data", 0, sizeof(T) * (double)n * nseg * D.K); launch_head_bwd_data<T>(h, c->st); }
-  if (param_grads) { Scope s(c, "head_bwd_w", 0, sizeof(T) * (double)n * nseg * D.K); launch_head_bwd_w<T>(h, c->st); }
+  {
+    Scope s(c, "head_bwd", 0, sizeof(T) * (double)n * nseg * D.K * (param_grads ? 2 : 1));
+    launch_head_bwd<T>(head_args(c, n, seg_first, nseg), param_grads, c->st);
+  }
   for (int j = nl - 1; j >= 1; --j) {
     const ConvLayer& cl = D.conv[j];
     NormArgs na = norm_args<T>(c, D, cl.Cs, cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->d_mean[j], c->d_var[j], c->d_rstd[j],
@@ -1272,12 +1258,10 @@ void paper_train_step(gan_ctx* c, const int32_t* label_ids, const float* noise, 
   paper_g_forward<T>(c, n, false, true);                               // fake = G(z)
   im2col_call<T>(c, c->D.conv[0], c->xd, nullptr, c->colD, c->KcD, c->nslot, 1, n);
   paper_d_forward<T>(c, n, 0, 2, true, 0, 1);                          // D(real), D(fake): dropout passes 0 and 1
-  loss_call(c, n, 0);                                                  // Eq. 3
-  paper_d_backward<T>(c, n, 0, 2, true, false);
+  paper_d_backward<T>(c, n, 0, 2, true, false);                        // Eq. 3
   adam_call<T>(c, c->D, false);
   paper_d_forward<T>(c, n, 1, 1, true, 2, 0);                          // updated D on the same fake batch: pass 2
-  loss_call(c, n, 1);                                                  // Eq. 4 (negated: minimised)
-  paper_d_backward<T>(c, n, 1, 1, false, true);
+  paper_d_backward<T>(c, n, 1, 1, false, true);                        // Eq. 4 (negated: minimised)
   paper_g_backward<T>(c, n);
   paper_adam_g<T>(c);
 }
@@ -1290,17 +1274,15 @@ void train_step(gan_ctx* c, const int32_t* label_ids, const float* noise, const 
   g_forward<T>(c, n, false, true);                 // fake = G(z)
   im2col_call<T>(c, c->D.conv[0], c->xd, nullptr, c->colD, c->KcD, c->nslot, 1, n);   // the fake half of D's input
   d_forward<T>(c, n, 0, 2, true);                  // D(real), D(fake): separate batch statistics per segment
-  loss_call(c, n, 0);                              // Eq. 3
   c->order_next = 0;
   {
     const AdamArgs aD = adam_args<T>(c, c->D);
-    d_backward<T>(c, n, 0, 2, true, false, &aD);   // weight gradients and the convolutions' updates beside the chain
+    d_backward<T>(c, n, 0, 2, true, false, &aD);   // Eq. 3; weight gradients and the convolutions' updates beside the chain
     adam_rest_call<T>(c, c->D, false, aD);
     order_after(c, c->st, side_stream(c));
   }
   d_forward<T>(c, n, 1, 1, true);                  // updated D on the same fake batch
-  loss_call(c, n, 1);                              // Eq. 4 (negated: minimised)
-  d_backward<T>(c, n, 1, 1, false, true);          // only data gradients: theta_D is not G's to move
+  d_backward<T>(c, n, 1, 1, false, true);          // Eq. 4 (negated: minimised); only data gradients: theta_D is not G's to move
   {
     const AdamArgs aG = adam_args<T>(c, c->G);
     g_backward<T>(c, n, &aG);

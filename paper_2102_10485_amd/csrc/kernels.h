@@ -171,20 +171,19 @@ struct HeadArgs {
   const int* offs;
   const int* sample_model;
   int L, K, seg_first, nseg, seg_samples, n;
-  int* adam_t;              // loss: [L] step counts of the update that follows, advanced with the bias corrections adam_bc [L][2]
+  int* adam_t;              // with the costs: [L] step counts of the update that follows, advanced with the bias corrections adam_bc [L][2]
   float* adam_bc;
   float beta1, beta2;
-  int mode;                 // loss: 0 = discriminator cost on (real, fake) ; 1 = generator cost on fake
+  int mode;                 // 0 = discriminator cost on (real, fake) ; 1 = generator cost on fake
   float scale;
-  // head_bwd_w: rsplit > 1 shares every model's rows among rsplit blocks per K chunk; their partial sums go to
+  // weight gradient: rsplit > 1 shares every model's rows among rsplit blocks per K chunk; their partial sums go to
   // part[rsplit][L][K + 4] (the bias term at index K) and are added in order by a second kernel
   float* part;
   int rsplit;
 };
 template <typename T> void launch_head_fwd(const HeadArgs& a, hipStream_t st);
-void launch_loss(const HeadArgs& a, hipStream_t st);
-template <typename T> void launch_head_bwd_data(const HeadArgs& a, hipStream_t st);
-template <typename T> void launch_head_bwd_w(const HeadArgs& a, hipStream_t st);
+// the costs and the data gradient; weights: the weight gradient too
+template <typename T> void launch_head_bwd(const HeadArgs& a, bool weights, hipStream_t st);
 
 constexpr int ADAM_MAX_REGIONS = 8;
 struct AdamArgs {

@@ -748,7 +748,18 @@ __device__ inline float wave_sum(float v) {
   return v;
 }
 
-// one wave per row: logit = <feat[row], w[model]> + b[model]
+__device__ inline float softplus_f(float u) { return fmaxf(u, 0.f) + log1pf(expf(-fabsf(u))); }
+__device__ inline float sigmoid_f(float u) {
+  if (u >= 0.f) return 1.f / (1.f + expf(-u));
+  const float e = expf(u);
+  return e / (1.f + e);
+}
+
+// mode 0 (Eq. 3): J_D = scale*mean softplus(-s_real) + scale*mean softplus(s_fake), segments (0, 1).  mode 1 (Eq. 4, negated):
+// scale*mean softplus(-s_fake') on segment seg_first.
+__device__ inline float head_sign(const HeadArgs& a, int seg) { return a.mode == 0 && seg == 1 ? 1.f : -1.f; }
+
+// one wave per row: logit = <feat[row], w[model]> + b[model], and the cost's derivative by it
 template <typename T>
 __global__ __launch_bounds__(256) void head_fwd_kernel(HeadArgs a) {
   const int lane = threadIdx.x & 63;
@@ -769,7 +780,11 @@ __global__ __launch_bounds__(256) void head_fwd_kernel(HeadArgs a) {
     acc += v[0] * ww.x + v[1] * ww.y + v[2] * ww.z + v[3] * ww.w;
   }
   acc = wave_sum(acc);
-  if (lane == 0) a.logits[r] = acc + a.b[(long long)l * a.pstride];
+  if (lane == 0) {
+    const float logit = acc + a.b[(long long)l * a.pstride], sign = head_sign(a, a.seg_first + sidx);
+    a.logits[r] = logit;
+    a.dlogits[r] = a.scale * sign * sigmoid_f(sign * logit) * (1.f / (float)(a.offs[l + 1] - a.offs[l]));
+  }
 }
 template <typename T> void launch_head_fwd(const HeadArgs& a, hipStream_t st) {
   const long long rows = (long long)a.n * a.nseg;
@@ -779,31 +794,17 @@ template <typename T> void launch_head_fwd(const HeadArgs& a, hipStream_t st) {
 template void launch_head_fwd<float>(const HeadArgs&, hipStream_t);
 template void launch_head_fwd<bf16_t>(const HeadArgs&, hipStream_t);
 
-__device__ inline float softplus_f(float u) { return fmaxf(u, 0.f) + log1pf(expf(-fabsf(u))); }
-__device__ inline float sigmoid_f(float u) {
-  if (u >= 0.f) return 1.f / (1.f + expf(-u));
-  const float e = expf(u);
-  return e / (1.f + e);
-}
-
-// One block per model.  mode 0 (Eq. 3): J_D = scale*mean softplus(-s_real) + scale*mean softplus(s_fake),
-// segments (0, 1).  mode 1 (Eq. 4, negated): scale*mean softplus(-s_fake') on segment seg_first.
-__global__ __launch_bounds__(256) void loss_kernel(HeadArgs a) {
+// One block per model: its cost, and the step count of the update that follows.
+__device__ inline void head_loss(const HeadArgs& a, int l) {
   __shared__ float red[256];
-  const int l = blockIdx.x;
   const int s0 = a.offs[l], cnt = a.offs[l + 1] - s0;
   if (cnt == 0) { if (threadIdx.x == 0) a.loss[l] = 0.f; return; }
   const float inv = 1.f / (float)cnt;
   float acc = 0.f;
   for (int s = 0; s < a.nseg; ++s) {
     const int seg = a.seg_first + s;
-    const float sign = (a.mode == 0 && seg == 1) ? 1.f : -1.f;
-    for (int i = threadIdx.x; i < cnt; i += 256) {
-      const long long r = (long long)seg * a.seg_samples + s0 + i;
-      const float u = sign * a.logits[r];
-      acc += softplus_f(u);
-      a.dlogits[r] = a.scale * sign * sigmoid_f(u) * inv;
-    }
+    const float sign = head_sign(a, seg);
+    for (int i = threadIdx.x; i < cnt; i += 256) acc += softplus_f(sign * a.logits[(long long)seg * a.seg_samples + s0 + i]);
   }
   red[threadIdx.x] = acc;
   __syncthreads();
@@ -813,28 +814,24 @@ __global__ __launch_bounds__(256) void loss_kernel(HeadArgs a) {
   }
   if (threadIdx.x == 0) {
     a.loss[l] = a.scale * red[0] * inv;
-    // the step count of the update that follows, and its bias corrections (a launch of their own took 4.6 us)
+    // and its bias corrections (a launch of their own took 4.6 us)
     const int t = a.adam_t[l] + 1;
     a.adam_t[l] = t;
     a.adam_bc[2 * l] = (float)(1.0 - pow((double)a.beta1, (double)t));
     a.adam_bc[2 * l + 1] = (float)(1.0 - pow((double)a.beta2, (double)t));
   }
 }
-void launch_loss(const HeadArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(loss_kernel, dim3(a.L), dim3(256), 0, st, a);
-}
 
 // dfeat[row][k] = dlogit[row] * w[model][k]; a thread takes 8 consecutive k of one row (K is a multiple of 8: the
-// feature maps have whole 64-channel lines), blockIdx.y the segment; 32-bit index arithmetic (the launcher checks).
+// feature maps have whole 64-channel lines); 32-bit index arithmetic (the launcher checks).
 template <typename T>
-__global__ __launch_bounds__(256) void head_bwd_data_kernel(HeadArgs a) {
+__device__ inline void head_data(const HeadArgs& a, int sidx, unsigned idx) {
   const unsigned k8 = (unsigned)a.K >> 3;
-  const unsigned idx = blockIdx.x * 256u + threadIdx.x;
   const unsigned j = idx / k8;
   if (j >= (unsigned)a.n || (int)j >= a.offs[a.L]) return;
   const int k = (int)(idx - j * k8) * 8;
   const int l = a.sample_model[j];
-  const long long r = (long long)(a.seg_first + (int)blockIdx.y) * a.seg_samples + j;
+  const long long r = (long long)(a.seg_first + sidx) * a.seg_samples + j;
   const float d = a.dlogits[r];
   const float* w = a.w + (long long)l * a.pstride + k;
   const float4 w0 = *reinterpret_cast<const float4*>(w), w1 = *reinterpret_cast<const float4*>(w + 4);
@@ -847,23 +844,14 @@ __global__ __launch_bounds__(256) void head_bwd_data_kernel(HeadArgs a) {
     *reinterpret_cast<float4*>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
   }
 }
-template <typename T> void launch_head_bwd_data(const HeadArgs& a, hipStream_t st) {
-  const long long tot = (long long)a.n * (a.K / 8);
-  if (tot == 0 || a.nseg == 0) return;
-  if (a.K % 8 != 0 || tot + 256 >= (1LL << 32)) return launch_fail("head data gradient: K must be a multiple of 8 and n * K / 8 below 2^32");
-  hipLaunchKernelGGL((head_bwd_data_kernel<T>), dim3((unsigned)((tot + 255) / 256), (unsigned)a.nseg), dim3(256), 0, st, a);
-}
-template void launch_head_bwd_data<float>(const HeadArgs&, hipStream_t);
-template void launch_head_bwd_data<bf16_t>(const HeadArgs&, hipStream_t);
 
-// dw[model][k] = sum_rows dlogit[row] * feat[row][k] ; db = sum_rows dlogit.  Block (k chunk of 1024, model).
+// dw[model][k] = sum_rows dlogit[row] * feat[row][k] ; db = sum_rows dlogit.  Block (k chunk of 1024, model, row split).
 template <typename T>
-__global__ __launch_bounds__(256) void head_bwd_w_kernel(HeadArgs a) {
-  const int l = blockIdx.y;
+__device__ inline void head_weights(const HeadArgs& a, int kc, int l, int sp) {
   const int s0 = a.offs[l], cnt = a.offs[l + 1] - s0;
   if (cnt == 0) return;
-  const int k = blockIdx.x * 1024 + threadIdx.x * 4;
-  const int rsplit = a.rsplit > 1 ? a.rsplit : 1, sp = blockIdx.z;
+  const int k = kc * 1024 + threadIdx.x * 4;
+  const int rsplit = a.rsplit > 1 ? a.rsplit : 1;
   const int per = (cnt + rsplit - 1) / rsplit;
   const int i0 = sp * per, i1 = min(cnt, i0 + per);
   float acc[4] = {0, 0, 0, 0}, accb = 0.f;
@@ -884,11 +872,28 @@ __global__ __launch_bounds__(256) void head_bwd_w_kernel(HeadArgs a) {
   if (rsplit > 1) {
     float* part = a.part + ((long long)sp * a.L + l) * (a.K + 4);
     if (k < a.K) *reinterpret_cast<float4*>(part + k) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    if (blockIdx.x == 0 && threadIdx.x == 0) part[a.K] = accb;
+    if (kc == 0 && threadIdx.x == 0) part[a.K] = accb;
     return;
   }
   if (k < a.K) *reinterpret_cast<float4*>(a.dw + (long long)l * a.pstride + k) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.db[(long long)l * a.pstride] = accb;
+  if (kc == 0 && threadIdx.x == 0) a.db[(long long)l * a.pstride] = accb;
+}
+
+// Everything that needs nothing but the logits and their derivatives, which the forward kernel leaves: the weight gradient's blocks first (they
+// take longest), the costs', the data gradient's.  In small configurations every launch is 4 to 6 us whatever it does, and these
+// were three: one 28x28 pair 425 -> 417 us a step, ten in bf16 1.8 % less, a hundred 32x32 pairs 0.5 %.
+template <typename T>
+__global__ __launch_bounds__(256) void head_bwd_kernel(HeadArgs a, int w_blocks, unsigned data_blocks) {
+  const int b = (int)blockIdx.x;
+  if (b < w_blocks) {
+    const int kcs = (a.K + 1023) / 1024, q = b / kcs;
+    head_weights<T>(a, b - q * kcs, q % a.L, q / a.L);
+  } else if (b < w_blocks + a.L) {
+    head_loss(a, b - w_blocks);
+  } else {
+    const unsigned q = (unsigned)(b - w_blocks - a.L), sidx = q / data_blocks;
+    head_data<T>(a, (int)sidx, (q - sidx * data_blocks) * 256u + threadIdx.x);
+  }
 }
 // the row splits' partial sums, added in order (index K: the bias term)
 __global__ void head_bwd_w_final_kernel(HeadArgs a) {
@@ -902,17 +907,22 @@ __global__ void head_bwd_w_final_kernel(HeadArgs a) {
   if (k < a.K) a.dw[(long long)l * a.pstride + k] = s;
   else a.db[(long long)l * a.pstride] = s;
 }
-template <typename T> void launch_head_bwd_w(const HeadArgs& a, hipStream_t st) {
-  if (a.K % 4 != 0 || (a.rsplit > 1 && !a.part)) return launch_fail("linear head: feature count not a multiple of 4, or no buffer for the row splits");
+template <typename T> void launch_head_bwd(const HeadArgs& a, bool weights, hipStream_t st) {
+  if (a.nseg == 0 || a.L == 0) return;
+  const long long tot = (long long)a.n * (a.K / 8), data_blocks = (tot + 255) / 256;
+  if (a.K % 8 != 0 || tot + 256 >= (1LL << 32)) return launch_fail("head data gradient: K must be a multiple of 8 and n * K / 8 below 2^32");
+  if (weights && a.rsplit > 1 && !a.part) return launch_fail("linear head: no buffer for the row splits");
   const int rsplit = a.rsplit > 1 ? a.rsplit : 1;
-  hipLaunchKernelGGL((head_bwd_w_kernel<T>), dim3((a.K + 1023) / 1024, a.L, rsplit), dim3(256), 0, st, a);
-  if (rsplit > 1) {
-    const long long tot = (long long)a.L * (a.K + 1);
-    hipLaunchKernelGGL(head_bwd_w_final_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, a);
+  const long long w_blocks = weights ? (long long)((a.K + 1023) / 1024) * a.L * rsplit : 0, blocks = w_blocks + a.L + data_blocks * a.nseg;
+  if (blocks >= (1LL << 31)) return launch_fail("linear head: more blocks than a launch can have");
+  hipLaunchKernelGGL((head_bwd_kernel<T>), dim3((unsigned)blocks), dim3(256), 0, st, a, (int)w_blocks, (unsigned)data_blocks);
+  if (weights && rsplit > 1) {
+    const long long fin = (long long)a.L * (a.K + 1);
+    hipLaunchKernelGGL(head_bwd_w_final_kernel, dim3((unsigned)((fin + 255) / 256)), dim3(256), 0, st, a);
   }
 }
-template void launch_head_bwd_w<float>(const HeadArgs&, hipStream_t);
-template void launch_head_bwd_w<bf16_t>(const HeadArgs&, hipStream_t);
+template void launch_head_bwd<float>(const HeadArgs&, bool, hipStream_t);
+template void launch_head_bwd<bf16_t>(const HeadArgs&, bool, hipStream_t);
 
 // ---------------------------------------------------------------------------------------------------------
 // Adam (bias-corrected, epsilon outside the root), all models and tensors of one network in one sweep
@@ -1118,7 +1128,7 @@ bool adam_plan(AdamArgs& a) {
   }
   return true;
 }
-// The parts of one update of a planned AdamArgs, in any order after the cost's kernel, which advances the step counts and bias
+// The parts of one update of a planned AdamArgs, in any order after head_bwd_kernel, which advances the step counts and bias
 // corrections: the gaps; one tiled region (or all of them, region < 0).  Each element is updated by exactly one part.
 void launch_adam_gaps(const AdamArgs& a, hipStream_t st) {
   if (a.ngaps > 0) hipLaunchKernelGGL(adam_kernel, dim3((unsigned)a.gap_blk0[a.ngaps], a.L), dim3(256), 0, st, a);
