@@ -996,11 +996,11 @@ void with_dropout(gan_ctx* c, PointArgs& a, int layer, int pass0, int step_add) 
   a.steps = c->D.t; a.step_add = step_add;
 }
 
-// BatchNorm whose batch statistics are taken from the stored tensor; no activation after it
+// BatchNorm whose batch statistics are taken from the stored tensor (`real` channels and padding); no activation after it
 template <typename T>
-void bn_forward_direct(gan_ctx* c, NormArgs a, const void* x, void* y, float eps, bool update_running) {
+void bn_forward_direct(gan_ctx* c, NormArgs a, int real, const void* x, void* y, float eps, bool update_running) {
   a.x = x; a.y = y; a.eps = eps; a.slope = 1.f;
-  launch_bn_stats_direct<T>(a, a.C, c->st);
+  launch_bn_stats_direct<T>(a, real, c->st);
   if (update_running) launch_bn_running(a, c->st);
   Scope s(c, "bn_apply", 0, 2.0 * a.n * a.nseg * a.rps * a.C * sizeof(T));
   launch_bn_apply<T>(a, c->st);
@@ -1031,7 +1031,7 @@ void paper_g_forward(gan_ctx* c, int n, bool use_running, bool update_running, f
     Scope s(c, "bias_act_dropout", 0, 2.0 * n * G.J * sizeof(T));
     launch_point_fwd<T>(a, c->st);
   }
-  if (!use_running) bn_forward_direct<T>(c, a0, c->gpre[0], c->gact[0], f.bn_eps_first, update_running);
+  if (!use_running) bn_forward_direct<T>(c, a0, a0.C, c->gpre[0], c->gact[0], f.bn_eps_first, update_running);
   const int nl = (int)G.conv.size();
   for (int i = 0; i + 1 < nl; ++i) {                   // Upsample x2 + Conv k3 as a k4 s2 p1 transposed convolution
     const ConvLayer& cl = G.conv[i];
@@ -1079,7 +1079,7 @@ void paper_d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_run
     { Scope s(c, "bias_act_dropout", 0, 2.0 * n * nseg * cl.Hs * cl.Hs * cl.cs_real * sizeof(T)); launch_point_fwd<T>(a, c->st); }
     bn_forward_direct<T>(c, norm_args<T>(c, D, cl.Cs, cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->d_mean[j], c->d_var[j], c->d_rstd[j],
                                          c->d_sums[j], seg_first, nseg, n, 1.f),
-                         c->dpre[j], c->dact[j], f.bn_eps, update_running);
+                         cl.cs_real, c->dpre[j], c->dact[j], f.bn_eps, update_running);
   }
   Scope s(c, "head_fwd", 0, sizeof(T) * (double)n * nseg * D.K);
   launch_head_fwd<T>(head_args(c, n, seg_first, nseg), c->st);

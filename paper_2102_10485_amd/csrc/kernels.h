@@ -290,8 +290,8 @@ struct PointArgs {
 template <typename T> void launch_point_fwd(const PointArgs& a, hipStream_t st);     // x <- dropout(act(x + bias))
 // out[l * out_stride + c] = sum over the segments and rows of model l of x[.., c]
 template <typename T> void launch_col_sum(const PointArgs& a, float* out, long long out_stride, hipStream_t st);
-// batch statistics (mean, biased variance, 1/sqrt(var + eps)) of a stored tensor with Cpad channels per row
-template <typename T> void launch_bn_stats_direct(const NormArgs& a, int Cpad, hipStream_t st);
+// batch statistics (mean, biased variance, 1/sqrt(var + eps)) of a stored tensor with C channels per row, of which those from `real` on are padding
+template <typename T> void launch_bn_stats_direct(const NormArgs& a, int real, hipStream_t st);
 // zero the gradient entries of the fourth tap row and column of a k3 filter held as [16][Cb][Cs]
 void launch_clear_fourth_taps(float* dw, long long pstride, int L, int Cb, int Cs, hipStream_t st);
 

@@ -117,9 +117,15 @@ template void launch_point_fwd<float>(const PointArgs&, hipStream_t);
 template void launch_point_fwd<bf16_t>(const PointArgs&, hipStream_t);
 
 // Rows of (segment, model): samples offs[l] .. offs[l+1] of segment seg, HW rows each, Cpad channels per row.
-// Block = CB_ channels of one (segment,) model: CB_ / EPV channel lanes of 16 bytes x 256 / lanes row lanes; every row
-// lane adds its rows (rl, rl + RL, ...) in order, then the lanes are added in order -- whole 16-byte loads of 64 or
-// 128 contiguous bytes per row instead of one element per thread.
+// Block = PS_CH channels of one (segment,) model: PS_CH / EPV channel lanes of 16 bytes x NTH * EPV / PS_CH row lanes; every row
+// lane adds its rows (rl, rl + RL, ...) in order, then the lanes are added in order, a few to a thread and then these sums --
+// whole 16-byte loads of 64 or 128 contiguous bytes per row instead of one element per thread.
+// What bounds it is how many rows a block has on their way: a model's rows belong to one block (its sums do not depend on other models'
+// samples then), a hundred models of 64 channels are 200 blocks, and with 256 threads they left most of the chip's loads unused.
+// 64 rows of a sample, a hundred models of 64 samples in bf16, us with 256 and with 1024 threads: column sums (two segments) 68 and 27, statistics (one
+// segment) 55 and 25; 16 rows 20 and 11, 14 and 10.  Statistics of 4 rows: 7.5 and 11, so 256 threads there.  (Statistics that kept a lane's first
+// sixteen rows in registers between the passes: 62 registers spilled, 73 us for 61.)
+// One row a sample (G's linear layer, whose 8192 columns are blocks enough): 256 threads.  The number follows from the layer's shape alone.
 constexpr int PS_CH = 32;                     // channels per block
 template <typename T> struct PsVec { static constexpr int N = 16 / (int)sizeof(T); };
 template <typename T> __device__ inline void ps_load(const T* p, float (&v)[PsVec<T>::N]) {
@@ -135,25 +141,32 @@ template <typename T> __device__ inline void ps_load(const T* p, float (&v)[PsVe
 }
 // sum over the row lanes, in lane order, of every lane's EPV values; result for channel cx (< PS_CH) in the threads
 // with threadIdx.x < PS_CH
-template <int EPV>
-__device__ inline float ps_lanes_sum(const float (&v)[EPV], float* sh, int cl, int rl, int RL) {
+template <int NTH, int EPV>
+__device__ inline float ps_lanes_sum(const float (&v)[EPV], float* sh, int cl, int rl) {
+  constexpr int PER = EPV, GROUPS = NTH / PS_CH;     // NTH * EPV / PS_CH lanes: PER of them to each group of threads
   __syncthreads();                                   // the buffer's previous use is over
 #pragma unroll
   for (int e = 0; e < EPV; ++e) sh[rl * PS_CH + cl * EPV + e] = v[e];
   __syncthreads();
+  const int c = (int)threadIdx.x % PS_CH, g = (int)threadIdx.x / PS_CH;
   float s = 0.f;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) s += sh[(g * PER + k) * PS_CH + c];
+  sh[g * PER * PS_CH + c] = s;                       // (this thread alone reads and writes the group's lanes of its channel)
+  __syncthreads();
+  s = 0.f;
   if ((int)threadIdx.x < PS_CH)
-    for (int k = 0; k < RL; ++k) s += sh[k * PS_CH + threadIdx.x];
+    for (int k = 0; k < GROUPS; ++k) s += sh[k * PER * PS_CH + threadIdx.x];
   return s;
 }
 
 // dbias[l][c] = sum over the segments and rows of g (the segments are added in order inside the block)
-template <typename T>
-__global__ __launch_bounds__(256) void col_sum_kernel(PointArgs a, float* __restrict__ out, long long out_stride) {
-  constexpr int EPV = PsVec<T>::N, CG = PS_CH / EPV, RL = 256 / CG;
+template <typename T, int NTH>
+__global__ __launch_bounds__(NTH) void col_sum_kernel(PointArgs a, float* __restrict__ out, long long out_stride) {
+  constexpr int EPV = PsVec<T>::N, CG = PS_CH / EPV, RL = NTH / CG;
   __shared__ float sh[RL * PS_CH];
   const int cl = threadIdx.x % CG, rl = threadIdx.x / CG;
-  const int cblocks = (a.Cpad + PS_CH - 1) / PS_CH;
+  const int cblocks = (a.C + PS_CH - 1) / PS_CH;     // (padded channels have no bias)
   const int c0 = (blockIdx.x % cblocks) * PS_CH;
   const int l = blockIdx.x / cblocks;
   const int cnt = a.offs[l + 1] - a.offs[l];
@@ -167,80 +180,81 @@ __global__ __launch_bounds__(256) void col_sum_kernel(PointArgs a, float* __rest
 #pragma unroll
     for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
     if (live)
+#pragma unroll 4
       for (long long r = rl; r < rows; r += RL) {
         float v[EPV];
         ps_load<T>(g + r * a.Cpad, v);
 #pragma unroll
         for (int e = 0; e < EPV; ++e) acc[e] += v[e];
       }
-    tot += ps_lanes_sum<EPV>(acc, sh, cl, rl, RL);
+    tot += ps_lanes_sum<NTH, EPV>(acc, sh, cl, rl);
   }
   const int c = c0 + (int)threadIdx.x;
   if ((int)threadIdx.x < PS_CH && c < a.C) out[(long long)l * out_stride + c] = tot;
 }
 template <typename T> void launch_col_sum(const PointArgs& a, float* out, long long out_stride, hipStream_t st) {
-  if (a.nseg == 0) return;
+  if (a.nseg == 0 || a.L == 0 || a.C == 0) return;
   if (a.Cpad % 8 != 0) return launch_fail("column sums: the channel count of a row must be a multiple of 8");
-  hipLaunchKernelGGL((col_sum_kernel<T>), dim3((unsigned)(a.L * ((a.Cpad + PS_CH - 1) / PS_CH))), dim3(256), 0, st, a, out, out_stride);
+  const dim3 grid((unsigned)(a.L * ((a.C + PS_CH - 1) / PS_CH)));
+  if (a.HW > 1) hipLaunchKernelGGL((col_sum_kernel<T, 1024>), grid, dim3(1024), 0, st, a, out, out_stride);
+  else hipLaunchKernelGGL((col_sum_kernel<T, 256>), grid, dim3(256), 0, st, a, out, out_stride);
 }
 template void launch_col_sum<float>(const PointArgs&, float*, long long, hipStream_t);
 template void launch_col_sum<bf16_t>(const PointArgs&, float*, long long, hipStream_t);
 
 // Batch statistics of a stored tensor per (segment, model, channel): mean, biased variance (from the deviations, second
 // pass), 1 / sqrt(var + eps); written where the BatchNorm passes expect them ([(segment) * L + model][C]).
-template <typename T>
-__global__ __launch_bounds__(256) void bn_stats_direct_kernel(NormArgs a, int Cpad) {
-  constexpr int EPV = PsVec<T>::N, CG = PS_CH / EPV, RL = 256 / CG;
+// Of channels from `real` on, which are padding and hold zeros, nothing is read.
+template <typename T, int NTH>
+__global__ __launch_bounds__(NTH) void bn_stats_direct_kernel(NormArgs a, int real) {
+  constexpr int EPV = PsVec<T>::N, CG = PS_CH / EPV, RL = NTH / CG;
   __shared__ float sh[RL * PS_CH];
   __shared__ float mean_sh[PS_CH];
   const int cl = threadIdx.x % CG, rl = threadIdx.x / CG;
-  const int cblocks = (Cpad + PS_CH - 1) / PS_CH;
+  const int cblocks = (a.C + PS_CH - 1) / PS_CH;
   const int c0 = (blockIdx.x % cblocks) * PS_CH;
   const int l = (blockIdx.x / cblocks) % a.L;
   const int sidx = blockIdx.x / (cblocks * a.L);
   const int cnt = a.offs[l + 1] - a.offs[l];
   if (cnt == 0) return;
-  const long long rows = (long long)cnt * a.rps;
-  const bool live = c0 + cl * EPV < Cpad;
-  const T* x = static_cast<const T*>(a.x) + ((long long)(a.seg_first + sidx) * a.seg_samples + a.offs[l]) * a.rps * Cpad + c0 + cl * EPV;
-  float acc[EPV];
+  const long long all = (long long)cnt * a.rps, rows = c0 + cl * EPV < real ? all : 0;       // of the model; those this lane has a part of
+  const T* x = static_cast<const T*>(a.x) + ((long long)(a.seg_first + sidx) * a.seg_samples + a.offs[l]) * a.rps * a.C + c0 + cl * EPV;
+  float acc[EPV], mean[EPV], v[EPV];
 #pragma unroll
   for (int e = 0; e < EPV; ++e) acc[e] = 0.f;
-  if (live)
-    for (long long r = rl; r < rows; r += RL) {
-      float v[EPV];
-      ps_load<T>(x + r * Cpad, v);
+#pragma unroll 4
+  for (long long r = rl; r < rows; r += RL) {
+    ps_load<T>(x + r * a.C, v);
 #pragma unroll
-      for (int e = 0; e < EPV; ++e) acc[e] += v[e];
-    }
-  const float s1 = ps_lanes_sum<EPV>(acc, sh, cl, rl, RL);
-  if ((int)threadIdx.x < PS_CH) mean_sh[threadIdx.x] = s1 / (float)rows;
+    for (int e = 0; e < EPV; ++e) acc[e] += v[e];
+  }
+  const float s1 = ps_lanes_sum<NTH, EPV>(acc, sh, cl, rl);
+  if ((int)threadIdx.x < PS_CH) mean_sh[threadIdx.x] = s1 / (float)all;
   __syncthreads();
-  float mean[EPV];
 #pragma unroll
   for (int e = 0; e < EPV; ++e) { mean[e] = mean_sh[cl * EPV + e]; acc[e] = 0.f; }
-  if (live)
-    for (long long r = rl; r < rows; r += RL) {
-      float v[EPV];
-      ps_load<T>(x + r * Cpad, v);
+#pragma unroll 4
+  for (long long r = rl; r < rows; r += RL) {
+    ps_load<T>(x + r * a.C, v);
 #pragma unroll
-      for (int e = 0; e < EPV; ++e) { const float d = v[e] - mean[e]; acc[e] += d * d; }
-    }
-  const float s2 = ps_lanes_sum<EPV>(acc, sh, cl, rl, RL);
+    for (int e = 0; e < EPV; ++e) { const float d = v[e] - mean[e]; acc[e] += d * d; }
+  }
+  const float s2 = ps_lanes_sum<NTH, EPV>(acc, sh, cl, rl);
   const int c = c0 + (int)threadIdx.x;
   if ((int)threadIdx.x < PS_CH && c < a.C) {
-    const float var = s2 / (float)rows;
+    const float var = s2 / (float)all;
     const long long o = (long long)((a.seg_first + sidx) * a.L + l) * a.C + c;
     a.mean[o] = mean_sh[threadIdx.x];
     a.var[o] = var;
     a.rstd[o] = 1.0f / sqrtf(var + a.eps);
   }
 }
-template <typename T> void launch_bn_stats_direct(const NormArgs& a, int Cpad, hipStream_t st) {
-  const long long tot = (long long)a.nseg * a.L * ((Cpad + PS_CH - 1) / PS_CH);
+template <typename T> void launch_bn_stats_direct(const NormArgs& a, int real, hipStream_t st) {
+  const long long tot = (long long)a.nseg * a.L * ((a.C + PS_CH - 1) / PS_CH);
   if (tot == 0) return;
-  if (Cpad % 8 != 0) return launch_fail("batch statistics: the channel count of a row must be a multiple of 8");
-  hipLaunchKernelGGL((bn_stats_direct_kernel<T>), dim3((unsigned)tot), dim3(256), 0, st, a, Cpad);
+  if (a.C % 8 != 0) return launch_fail("batch statistics: the channel count of a row must be a multiple of 8");
+  if (a.rps >= 16) hipLaunchKernelGGL((bn_stats_direct_kernel<T, 1024>), dim3((unsigned)tot), dim3(1024), 0, st, a, real);
+  else hipLaunchKernelGGL((bn_stats_direct_kernel<T, 256>), dim3((unsigned)tot), dim3(256), 0, st, a, real);
 }
 template void launch_bn_stats_direct<float>(const NormArgs&, int, hipStream_t);
 template void launch_bn_stats_direct<bf16_t>(const NormArgs&, int, hipStream_t);
