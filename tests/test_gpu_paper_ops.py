@@ -81,3 +81,40 @@ def test_summed_taps_and_their_adjoint(ctxs, prec, G, cb, cs):
     ref3 = np.einsum("ak,gacbs,cl->gklbs", A, d4.astype(np.float64), A)
     assert np.max(np.abs(got3 - ref3)) <= 1e-6 * np.max(np.abs(ref3))
     assert abs(np.sum(ref * d4) - np.sum(w3 * ref3)) <= 1e-9 * abs(np.sum(ref * d4))
+
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+@pytest.mark.parametrize("G,cb,cs,shift", [(2, 32, 64, 0),      # one tile of channels
+                                           (2, 96, 192, 0),     # several both ways
+                                           (2, 32, 96, 0),      # half a tile: the general kernels
+                                           (2, 64, 64, 1),      # buffers that start off a 16-byte boundary
+                                           (2, 7, 5, 0)])       # planes that are no whole number of 16-byte runs
+def test_summed_taps_by_tiles(ctxs, prec, G, cb, cs, shift):
+    """Small whole numbers: every sum is exact in both storage types, and what lies behind the results stays as it was."""
+    torch = U.torch_mod()
+    g = ctxs[prec]
+    bf = prec == binding.BF16
+    rng = np.random.default_rng(G * 1000 + cb + cs)
+    plane, dt = cb * cs, torch.int16 if bf else torch.float32
+
+    def put(values):
+        t = torch.zeros(values.size + shift + 8, dtype=torch.float32, device="cuda")
+        t[shift:shift + values.size] = U.dev(values.reshape(-1))
+        return t
+
+    w3 = rng.integers(-8, 9, (G, 3, 3, cb, cs)).astype(np.float32)
+    d_w3 = put(w3)
+    d_w4, d_w4t = (torch.full((G * 16 * plane + shift + 8,), 77, dtype=dt, device="cuda") for _ in range(2))
+    g.op_w3_to_w4(d_w3[shift:].data_ptr(), d_w4[shift:].data_ptr(), d_w4t[shift:].data_ptr(), G, cb, cs)
+    ref = np.einsum("ak,gklbs,cl->gacbs", A, w3.astype(np.float64), A)
+    end = shift + G * 16 * plane
+    assert np.array_equal(U.unpack(d_w4[shift:end].clone(), bf, (G, 4, 4, cb, cs)), ref)
+    assert np.array_equal(U.unpack(d_w4t[shift:end].clone(), bf, (G, 4, 4, cs, cb)), ref.transpose(0, 1, 2, 4, 3))
+    for t in (d_w4, d_w4t):
+        assert torch.all(t[:shift] == 77) and torch.all(t[end:] == 77)
+    d4 = rng.integers(-8, 9, (G, 4, 4, cb, cs)).astype(np.float32)
+    d_d4, d_d3 = put(d4), torch.full((G * 9 * plane + shift + 8,), 77.0, device="cuda")
+    g.op_dw4_to_dw3(d_d4[shift:].data_ptr(), d_d3[shift:].data_ptr(), G, cb, cs)
+    end = shift + G * 9 * plane
+    assert np.array_equal(d_d3[shift:end].cpu().numpy().reshape(G, 3, 3, cb, cs), np.einsum("ak,gacbs,cl->gklbs", A, d4.astype(np.float64), A))
+    assert torch.all(d_d3[:shift] == 77) and torch.all(d_d3[end:] == 77)
+
