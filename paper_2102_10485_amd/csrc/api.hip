@@ -644,6 +644,7 @@ void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, c
     a.bn_gamma = known->gamma; a.bn_beta = known->beta; a.bn_bias = bias; a.bn_pstride = known->pstride;
     a.bn_C = known->C; a.bn_eps = known->eps; a.slope = known->slope;
   }
+  if (epi == EPI_BIAS_ACT) { a.bn_bias = bias; a.bn_pstride = known->pstride; a.slope = 0.f; }
   if (epi == EPI_DROP_BWD) a.drop_scale = 1.0f / (1.0f - c->cfg.dropout_p);
   a.stat_partial = stats ? c->stat_partial : nullptr;
   if (epi == EPI_LABEL_LRELU) { a.label_rows = c->label_rows; a.sample_slot = c->rb.sample_slot; }
@@ -1023,14 +1024,8 @@ void paper_g_forward(gan_ctx* c, int n, bool use_running, bool update_running, f
   NormArgs a0 = norm_args<T>(c, G, G.C0, G.h0 * G.h0, G.fc_gamma, G.fc_beta, G.fc_rs, c->g_mean[0], c->g_var[0], c->g_rstd[0],
                              c->g_sums[0], 0, 1, n, 1.f);
   a0.eps = f.bn_eps_first;
-  conv_call<T>(c, "gemm_dense", MODE_DENSE, use_running ? EPI_BN : EPI_NONE, c->zin, Weights{(const T*)G.shadow_u + G.fc_w, G.P},
-               use_running ? c->gact[0] : c->gpre[0], nullptr, G.Kp, G.J, 1, 1, 0, 1, n, 0, -1.0, false, &a0, G.theta + G.fc_bias);
-  if (!use_running) {
-    PointArgs a = point_args(c, c->gpre[0], G.J, G.J, 1, 0, 1, n);          // + bias, ReLU
-    a.bias = G.theta + G.fc_bias; a.pstride = G.P; a.slope = 0.f;
-    Scope s(c, "bias_act_dropout", 0, 2.0 * n * G.J * sizeof(T));
-    launch_point_fwd<T>(a, c->st);
-  }
+  conv_call<T>(c, "gemm_dense", MODE_DENSE, use_running ? EPI_BN : EPI_BIAS_ACT, c->zin, Weights{(const T*)G.shadow_u + G.fc_w, G.P},
+               use_running ? c->gact[0] : c->gpre[0], nullptr, G.Kp, G.J, 1, 1, 0, 1, n, 0, -1.0, false, &a0, G.theta + G.fc_bias);   // + bias, ReLU
   if (!use_running) bn_forward_direct<T>(c, a0, a0.C, c->gpre[0], c->gact[0], f.bn_eps_first, update_running);
   const int nl = (int)G.conv.size();
   for (int i = 0; i + 1 < nl; ++i) {                   // Upsample x2 + Conv k3 as a k4 s2 p1 transposed convolution

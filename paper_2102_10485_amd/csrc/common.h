@@ -58,7 +58,7 @@ const char* take_launch_error();   // the first reason recorded on this thread s
 // Block tiles of the forward-type GEMM kernel (rows x columns): conv_gemm.hip
 enum ConvTile { TILE_BIG = 0, TILE_MID = 1, TILE_SMALL = 2, TILE_NARROW = 3, TILE_TINY = 4, TILE_PAIR = 5, TILE_DEEP = 6 };
 enum ConvMode { MODE_DOWN = 0, MODE_UP = 1, MODE_DENSE = 2 };
-enum Epilogue { EPI_NONE = 0, EPI_ACT_BWD = 1, EPI_LRELU = 2, EPI_LABEL_LRELU = 3, EPI_DROP_BWD = 4, EPI_BN = 5 };
+enum Epilogue { EPI_NONE = 0, EPI_ACT_BWD = 1, EPI_LRELU = 2, EPI_LABEL_LRELU = 3, EPI_DROP_BWD = 4, EPI_BN = 5, EPI_BIAS_ACT = 6 };
 enum Act { ACT_RELU = 0, ACT_LRELU = 1 };
 
 // Arguments of the grouped implicit-GEMM forward-type kernel (down / up / dense).
@@ -92,11 +92,11 @@ struct ConvArgs {
   int ub_tiles;          // launched upper bound of M-tiles per (segment, phase)
   ConvTile tile;         // its height is what the prefix array was built for
   int hr_shift;          // log2(Hr) or -1 (filled by the launcher)
-  float slope;           // EPI_ACT_BWD, EPI_DROP_BWD: derivative on the non-positive side; EPI_BN: factor there
+  float slope;           // EPI_ACT_BWD, EPI_DROP_BWD: derivative on the non-positive side; EPI_BN, EPI_BIAS_ACT: factor there
   // EPI_BN: BatchNorm with known statistics (gamma (x - mean) / sqrt(var + eps) + beta) and the activation (slope below zero) of every
   // output; column col is channel col % bn_C.  Vectors of model 0; strides between models.
   const float *bn_mean, *bn_var, *bn_gamma, *bn_beta;
-  const float* bn_bias;  // [N] added first, then a ReLU (a layer whose activation comes before its BatchNorm), or NULL
+  const float* bn_bias;  // [N] added first, then a ReLU (a layer whose activation comes before its BatchNorm), or NULL; EPI_BIAS_ACT: [N] added
   long long bn_rstride, bn_pstride;
   int bn_C;
   float bn_eps;

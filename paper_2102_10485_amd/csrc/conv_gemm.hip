@@ -1053,7 +1053,13 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
     // launch that prepares its parameters, are not needed (6400 samples of a hundred 32x32 generators, bf16, 1407 -> 1172 us with the
     // images' own pass gone too; sixteen 28x28 digits, fp32, 62 -> 42).  Applied to the accumulators, where a lane has TN columns: in the
     // store loop it has 16 / sizeof(T) of them, whose parameters' registers cost the 256x128 tile its second block per CU (1422 us).
+    // EPI_BIAS_ACT: what is stored is what a pass over the stored products would make of them (which are rounded to the storage type first);
+    // that pass took 130 us for 6400 samples of 8192 columns in bf16, and the GEMM takes the 87 that it took without this.
     float bn_sc[TN], bn_mu[TN], bn_be[TN], bn_bi[TN];
+    if constexpr (EPI == EPI_BIAS_ACT) {
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn) bn_bi[tn] = p.bn_bias[(long long)l * p.bn_pstride + min(colw + tn * 32 + (lane & 31), N - 1)];
+    }
     if constexpr (EPI == EPI_BN) {
 #pragma unroll
       for (int tn = 0; tn < TN; ++tn) {
@@ -1074,6 +1080,10 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
           const int pr = (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
           float val = acc[tm][tn][e];
           if (EPI == EPI_LRELU) val = val > 0.f ? val : val * p.slope;
+          if constexpr (EPI == EPI_BIAS_ACT) {
+            val = to_float(from_float<T>(val)) + bn_bi[tn];
+            val = val > 0.f ? val : val * p.slope;
+          }
           if constexpr (EPI == EPI_BN) {
             if (p.bn_bias) {
               val += bn_bi[tn];
@@ -1238,7 +1248,7 @@ void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
   // the kernel's assumptions, checked before anything is launched
   if (!a.A || !a.W || !a.Out || !a.offs || !a.tpre || a.N < 1 || a.w_nstride < a.N || a.C % (128 / (int)sizeof(T)) != 0 ||
       ((epi == EPI_ACT_BWD || epi == EPI_DROP_BWD) && !a.Aux) || (epi == EPI_LABEL_LRELU && (!a.label_rows || !a.sample_slot || a.L != 1)) ||
-      (epi == EPI_BN && (!a.bn_mean || !a.bn_var || !a.bn_gamma || !a.bn_beta || a.bn_C < 1)))
+      (epi == EPI_BIAS_ACT && !a.bn_bias) || (epi == EPI_BN && (!a.bn_mean || !a.bn_var || !a.bn_gamma || !a.bn_beta || a.bn_C < 1)))
     return launch_fail("GEMM: null operand, or channel counts that are not whole 128-byte lines");
   if (a.tile == TILE_BIG && a.N % 256 != 0) return launch_fail("GEMM: 256 x 256 tiles need whole tiles of columns");
   if (a.N < 64) return launch_fail("GEMM: fewer than 64 output channels (image-side outputs have their own kernel)");
@@ -1259,6 +1269,7 @@ void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
   if (mode == MODE_DENSE && epi == EPI_BN) return launch_mode<T, MODE_DENSE, EPI_BN>(a, st);
   if (mode == MODE_UP && epi == EPI_DROP_BWD) return launch_mode<T, MODE_UP, EPI_DROP_BWD>(a, st);
   if (mode == MODE_DENSE && epi == EPI_NONE) return launch_mode<T, MODE_DENSE, EPI_NONE>(a, st);
+  if (mode == MODE_DENSE && epi == EPI_BIAS_ACT) return launch_mode<T, MODE_DENSE, EPI_BIAS_ACT>(a, st);
   if (mode == MODE_DENSE && epi == EPI_LRELU) return launch_mode<T, MODE_DENSE, EPI_LRELU>(a, st);
   if (mode == MODE_DENSE && epi == EPI_LABEL_LRELU) return launch_mode<T, MODE_DENSE, EPI_LABEL_LRELU>(a, st);
   launch_fail("GEMM: (mode, epilogue) combination without an instantiation");
@@ -1266,8 +1277,8 @@ void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
 // Name of the kernel instantiation launch_conv picks (for per-kernel timing): mode, epilogue, tile.
 const char* conv_variant_name(int esize, int mode, int epi, const ConvArgs& a) {
   static const char* modes[3] = {"down", "up", "dense"};
-  static const char* epis[6] = {"", "+actbwd", "+lrelu", "+label+lrelu", "+dropbwd", "+bn"};
-  static char names[2][3][6][7][48];
+  static const char* epis[7] = {"", "+actbwd", "+lrelu", "+label+lrelu", "+dropbwd", "+bn", "+bias+act"};
+  static char names[2][3][7][7][48];
   char* n = names[esize == 4][mode][epi][a.tile];
   if (!n[0]) snprintf(n, 48, "gemm_%s%s<%s>", modes[mode], epis[epi], tile_info(esize, a.tile).name);
   return n;

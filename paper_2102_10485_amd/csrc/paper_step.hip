@@ -4,7 +4,7 @@
 //            the engine as a k4 s2 p1 one whose fourth tap row and column are zero, channel counts padded to 64;
 //            bias, activation and dropout are one pass over its output, BatchNorm takes its statistics from the
 //            stored tensor (they cannot come from the GEMM: the activation and the dropout sit in between);
-//   G input: Linear (+bias) -> ReLU -> BatchNorm(eps 1e-5)                                 -- same pass, no dropout;
+//   G input: Linear (+bias) -> ReLU -> BatchNorm(eps 1e-5)                                 -- bias and ReLU in the GEMM (EPI_BIAS_ACT);
 //   G last : Conv k3 s1 p1 (+bias) -> tanh onto the image, and its two gradients: conv3_mfma.hip.
 // All sums run in a fixed order (thread-strided partial sums, then ordered merges), so a model's result does not depend
 // on what else is in the launch.
