@@ -1071,6 +1071,22 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
         bn_bi[tn] = p.bn_bias ? p.bn_bias[po + col] : 0.f;
       }
     }
+    // EPI_ACT_BWD, EPI_DROP_BWD: the saved outputs of a 32-row block are requested while the block in front of it is stored.  Requested in the store
+    // loop, each in its row's branch, they were waited for one by one, the whole way to memory every time.  us, two segments: bf16 256 -> 128
+    // channels, side 8, 6400 samples 933 -> 873, 128 -> 64, side 16, 1024 samples 249 -> 227, with dropout 64 -> 64, side 8, 6400 samples 280 -> 233;
+    // fp32 128 -> 64, side 7, 1280 samples 244 -> 225.  (A second set of registers, for a whole block ahead, costs the 256x128 tile its second
+    // block per CU.)
+    constexpr bool AUX = EPI == EPI_ACT_BWD || EPI == EPI_DROP_BWD;
+    constexpr int PASSES = 32 * CPR / 64;
+    uint4 aux[AUX ? PASSES : 1];
+    auto request_aux = [&](int tm, int i) __attribute__((always_inline)) {
+      const int cid = lane + 64 * i, pr = cid / CPR, col = colw + (cid - pr * CPR) * EPV;
+      const long long o = orow[wm * TM * 32 + tm * 32 + pr];
+      aux[i] = *reinterpret_cast<const uint4*>(Aux + (o < 0 ? 0 : o) * N + (col < N ? col : 0));      // (any place for what is not stored)
+    };
+    if constexpr (AUX)
+#pragma unroll
+      for (int i = 0; i < PASSES; ++i) request_aux(0, i);
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
 #pragma unroll
@@ -1097,7 +1113,7 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int i = 0; i < 32 * CPR / 64; ++i) {
+      for (int i = 0; i < PASSES; ++i) {
         const int cid = lane + 64 * i;
         const int pr = cid / CPR, pc = cid - pr * CPR;
         const long long o = orow[wm * TM * 32 + tm * 32 + pr];
@@ -1119,9 +1135,8 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
               if (!(vf[k] > 0.f)) vf[k] *= p.slope;
             }
           }
-          if (EPI == EPI_ACT_BWD || EPI == EPI_DROP_BWD) {      // times the activation's derivative (and the dropout), from the saved output
-            const uint4 araw = *reinterpret_cast<const uint4*>(Aux + o * N + col);
-            const T* aa = reinterpret_cast<const T*>(&araw);
+          if constexpr (AUX) {      // times the activation's derivative (and the dropout), from the saved output
+            const T* aa = reinterpret_cast<const T*>(&aux[i]);
 #pragma unroll
             for (int k = 0; k < EPV; ++k)
             {
@@ -1142,6 +1157,8 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
             __builtin_nontemporal_store(q, reinterpret_cast<u4*>(Out + o * N + col));      // read next by another kernel, never by this one
           }
         }
+        if constexpr (AUX)
+          if (tm + 1 < TM) request_aux(tm + 1, i);
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       __builtin_amdgcn_wave_barrier();
