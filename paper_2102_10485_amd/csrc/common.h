@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "k_order.h"
+
 namespace gan {
 
 // bf16 storage: upper half of an fp32, round-to-nearest-even on conversion.
@@ -57,7 +59,6 @@ const char* take_launch_error();   // the first reason recorded on this thread s
 
 // Block tiles of the forward-type GEMM kernel (rows x columns): conv_gemm.hip
 enum ConvTile { TILE_BIG = 0, TILE_MID = 1, TILE_SMALL = 2, TILE_NARROW = 3, TILE_TINY = 4, TILE_PAIR = 5, TILE_DEEP = 6 };
-enum ConvMode { MODE_DOWN = 0, MODE_UP = 1, MODE_DENSE = 2 };
 enum Epilogue { EPI_NONE = 0, EPI_ACT_BWD = 1, EPI_LRELU = 2, EPI_LABEL_LRELU = 3, EPI_DROP_BWD = 4, EPI_BN = 5, EPI_BIAS_ACT = 6 };
 enum Act { ACT_RELU = 0, ACT_LRELU = 1 };
 

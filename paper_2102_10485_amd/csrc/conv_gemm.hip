@@ -676,71 +676,27 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   }
 
   const unsigned lds0 = (unsigned)(uintptr_t)As;       // LDS byte address of the buffers
-  // The next K-chunk to load: which tap it gathers and the wave-uniform byte offsets it adds to the rows' and columns'.
-  // K order, fastest first: the chunks of one 128-byte line; the taps whose gathers land on the same input pixels
-  // shifted by one (down: the 4 taps of a (ky%2, kx%2) class, up: the phase's 4 taps), which find their rows in
-  // L2; the channel line; (down) the class.  Carried along chunk by chunk: decoding the chunk's number took 90 scalar
-  // instructions a chunk, more issue time than the 8 MFMAs per wave of a 64-byte chunk.
-  // down: classes 0, 1 hold the taps with ky in {0, 2}, classes 2, 3 those with ky in {1, 3}; a class keeps cnt taps, and the
-  // two left in a class of two are its kx pair at the one valid ky: ky = 2 (top tile, even class) or 1 (bottom, odd).
-  int k_part, k_j, k_line, k_cls, k_cnt, k_tap = 0;
-  unsigned k_aoff = 0, k_woff = 0;
-  int k_wtap = 0;                                      // the tap's place in the weight block
-  auto k_set = [&]() {
-    if (MODE == MODE_DOWN) {
-      const int j = k_cnt == 4 ? k_j : k_j + (k_cls < 2 ? 2 : 0);
-      const int ky = (k_cls >> 1) + 2 * (j >> 1), kx = (k_cls & 1) + 2 * (j & 1);
-      k_tap = ky * 4 + kx;
-      k_aoff = ky * row_bytes + kx * px_bytes + k_line * 128;
-      k_wtap = k_tap;
-      k_woff = k_wtap * wtap_bytes + k_line * 128;
-    } else if (MODE == MODE_UP) {
-      // phase py = 0 gathers rows y and y - 1 through ky = 1 and 3, py = 1 rows y + 1 and y through ky = 0 and 2; likewise x
-      k_tap = k_cnt == 4 ? k_j : k_j + (first_gone ? 2 : 0);
-      const int a = k_tap >> 1, b = k_tap & 1;
-      k_aoff = (py - a + 1) * row_bytes + (px - b + 1) * px_bytes + k_line * 128;
-      k_wtap = (2 * a + 1 - py) * 4 + 2 * b + 1 - px;
-      k_woff = k_wtap * wtap_bytes + k_line * 128;
-    } else {
-      k_aoff = k_woff = k_line * 128;
-    }
-  };
-  auto k_advance = [&]() {
-    if (LINES == 2) {
-      k_part ^= 1;
-      if (k_part) { k_aoff += KB; k_woff += KB; return; }
-    }
-    if (++k_j == k_cnt) {
-      k_j = 0;
-      if (++k_line == cpl && MODE == MODE_DOWN) {
-        k_line = 0;
-        ++k_cls;
-        k_cnt = k_cls < 2 ? cnt_lo : cnt_hi;
-      }
-    }
-    if constexpr (QUAD) {        // (kept out of the vector registers, of which none is left)
-      k_j = __builtin_amdgcn_readfirstlane(k_j);
-      k_line = __builtin_amdgcn_readfirstlane(k_line);
-    }
-    k_set();
-  };
+  // The next K-chunk to load
+  KOrder<MODE, KB, QUAD> order;
+  order.cpl = cpl; order.cnt_lo = cnt_lo; order.cnt_hi = cnt_hi; order.first_gone = first_gone; order.py = py; order.px = px;
+  order.row_bytes = row_bytes; order.px_bytes = px_bytes; order.wtap_bytes = wtap_bytes;
   auto load_chunk = [&](int stage, auto split) {       // this group's next chunk, into a buffer
     const unsigned a_dst = lds0 + (stage * BM + wave * (1024 / KB)) * KB;        // + pass * RPP rows
     const unsigned b_dst = lds0 + NST * BM * KB + stage * BN * KBB + wave * 1024;
 #pragma unroll
     for (int i = 0; i < PA; ++i)
-      load16_to_lds(a_rsrc, apix[i] | (unsigned)__builtin_amdgcn_sbfe(outside[i], k_tap, 1), k_aoff, a_dst + i * RPP * KB);
+      load16_to_lds(a_rsrc, apix[i] | (unsigned)__builtin_amdgcn_sbfe(outside[i], order.tap, 1), order.aoff, a_dst + i * RPP * KB);
     if constexpr (PRE && split.value) {
 #pragma unroll
       for (int pl = 0; pl < 3; ++pl)
 #pragma unroll
         for (int i = 0; i < PP; ++i)
-          load16_to_lds(w_rsrc[pl], bcol[i], k_woff >> 1, b_dst + (pl * BN + i * RPB) * (KB / 2));
+          load16_to_lds(w_rsrc[pl], bcol[i], order.woff >> 1, b_dst + (pl * BN + i * RPB) * (KB / 2));
     } else if constexpr (PRE) {
       // the weights as they are, value by value (tiles that are computed again: rare)
-      const float* const raw = p.w_raw + (long long)l * p.raw_stride + (long long)k_wtap * wns * C;
+      const float* const raw = p.w_raw + (long long)l * p.raw_stride + (long long)order.wtap * wns * C;
       for (int e = tid; e < BN * CPR; e += TL::NT) {
-        const int row = e / CPR, col = nt * BN + row, kk = k_line * 32 + ((e % CPR) ^ fwd_swz<KB>(row)) * 4;
+        const int row = e / CPR, col = nt * BN + row, kk = order.line * 32 + ((e % CPR) ^ fwd_swz<KB>(row)) * 4;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (col < N) {
           const float* const q = raw + (long long)col * p.raw_n + (long long)kk * p.raw_k;
@@ -750,10 +706,10 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < PB; ++i) load16_to_lds(w_rsrc[0], bcol[i], k_woff, b_dst + i * RPP * KB);
+      for (int i = 0; i < PB; ++i) load16_to_lds(w_rsrc[0], bcol[i], order.woff, b_dst + i * RPP * KB);
     }
 #pragma unroll
-    for (int i = 0; i < KS; ++i) k_advance();
+    for (int i = 0; i < KS; ++i) order.advance();
   };
   floatx16 acc[TM][TN];
 
@@ -762,12 +718,10 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   // buffer c % NST may be refilled (with chunk c+NST, by the next iteration).
   floatx16 low[TM][TN];
   auto k_loop = [&](auto split) __attribute__((always_inline)) {
-    k_part = k_j = k_line = k_cls = 0;
-    k_cnt = MODE == MODE_DENSE ? 1 : cnt_lo;
-    k_set();
+    order.start();
     clear_acc(acc);
     if constexpr (split.value) clear_acc(low);
-    for (int i = 0; i < kgrp; ++i) k_advance();
+    for (int i = 0; i < kgrp; ++i) order.advance();
     int st_load = 0, st = 0;                           // buffers of the next chunk to load and of the current one
     const int mine = (nk - kgrp + KS - 1) / KS, steps = (nk + KS - 1) / KS;      // this group's chunks; the barriers are everyone's
     for (int c = 0; c < NST - 1 && c < mine; ++c) load_chunk(st_load++, split);
@@ -870,9 +824,7 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   // or between them, or at a raised wave priority: +-0.5 %.
   auto quad_loop = [&](auto) __attribute__((always_inline)) {      // (a template, so that only the tiles that call it compile it)
     clear_acc(acc);
-    k_part = k_j = k_line = k_cls = 0;
-    k_cnt = cnt_lo;
-    k_set();
+    order.start();
     const int a_bytes = a_rsrc.z, w_bytes = w_rsrc[0].z;
     int4v ra = a_rsrc, rw = w_rsrc[0];
     int to_load = nk;
@@ -887,20 +839,19 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
     auto load_a = [&](auto half, auto buf) __attribute__((always_inline)) {
       static_for<0, 2>([&](auto i) __attribute__((always_inline)) {
         load16_to_lds_at<buf.value * 32768 + half.value * 8192 + i.value * 16384>(
-            ra, pix[half.value + 2 * i.value] | (unsigned)__builtin_amdgcn_sbfe(out2[half.value], k_tap + 16 * i.value, 1), k_aoff, lds_wave);
+            ra, pix[half.value + 2 * i.value] | (unsigned)__builtin_amdgcn_sbfe(out2[half.value], order.tap + 16 * i.value, 1), order.aoff, lds_wave);
       });
     };
     auto load_b = [&](auto half, auto buf) __attribute__((always_inline)) {
       static_for<0, 2>([&](auto i) __attribute__((always_inline)) {
         load16_to_lds_at<65536 + buf.value * 32768 + half.value * 16384 + i.value * 8192>(
-            rw, bcol[0], k_woff + (unsigned)((half.value * 32 + i.value * 128) * C * SZ), lds_wave);
+            rw, bcol[0], order.woff + (unsigned)((half.value * 32 + i.value * 128) * C * SZ), lds_wave);
       });
     };
     auto next_chunk = [&]() __attribute__((always_inline)) {
-      k_advance();
-      --to_load;
-      ra.z = to_load > 0 ? a_bytes : 0;
-      rw.z = to_load > 0 ? w_bytes : 0;
+      const bool more = order.next(to_load);
+      ra.z = more ? a_bytes : 0;
+      rw.z = more ? w_bytes : 0;
     };
     const int r = lane & 31, h = lane >> 5, sw = fwd_swz<KB>(r);
     const unsigned a0 = lds0 + (wm * 128 + r) * 128 + ((h ^ sw) << 4);
