@@ -257,39 +257,16 @@ __device__ inline void clear_acc(floatx16 (&acc)[TM][TN]) {
 // sixteen different 16-byte slots of the 256-byte bank period, and so do the rows one wave-wide copy fills.
 template <int KB>
 __device__ inline int fwd_swz(int row) { return (row / (256 / KB)) % (KB / 16); }
-// The operand reads of the forward-type kernel are issued by hand so that the reads of K-step vs+1 are in flight
-// while the MFMAs of K-step vs run (two register sets).  The compiler does not count these reads, so the waits are
-// explicit; each wait names the registers it makes valid, which orders the MFMAs behind it.
-template <int OFF>
-__device__ inline void lds_read16(u32x4& d, unsigned addr) {
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF) : "memory");
-}
-template <int N, int TM, int TN>
-__device__ inline void lds_wait(u32x4 (&a)[TM], u32x4 (&b)[TN]) {
-  static_assert(TM <= 4 && TN <= 4, "operand list below");
-  // at most N reads still in flight; all of a[] and b[] were issued before those
-  if constexpr (TM == 4 && TN == 2)
-    asm volatile("s_waitcnt lgkmcnt(%6)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]) : "n"(N) : "memory");
-  else if constexpr (TM == 2 && TN == 2)
-    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a[0]), "+v"(a[1]), "+v"(b[0]), "+v"(b[1]) : "n"(N) : "memory");
-  else if constexpr (TM == 1 && TN == 1)
-    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a[0]), "+v"(b[0]) : "n"(N) : "memory");
-  else if constexpr (TM == 1 && TN == 2)
-    asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(a[0]), "+v"(b[0]), "+v"(b[1]) : "n"(N) : "memory");
-  else if constexpr (TM == 1 && TN == 4)
-    asm volatile("s_waitcnt lgkmcnt(%5)" : "+v"(a[0]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]) : "n"(N) : "memory");
-  else
-    static_assert(TM == 4 && TN == 2, "add the operand list for this wave tile");
-}
-// the end of a quarter of a chunk (QUAD): the operands requested in it are here, at most N loads are still in flight, and so say all waves
+// The end of a quarter of a chunk (QUAD): the operands requested in it are here, at most N copies are still in flight, and so say all waves.  The
+// compiler counts the operands' reads and sees this wait, so that no register is read, moved or used again before its operand is there.
 template <int N>
-__device__ __forceinline__ void quad_wait(u32x4 (&a)[2][4]) {
-  asm volatile("s_waitcnt vmcnt(%8) lgkmcnt(0)\n\ts_barrier" : "+v"(a[0][0]), "+v"(a[0][1]), "+v"(a[0][2]), "+v"(a[0][3]), "+v"(a[1][0]), "+v"(a[1][1]),
-               "+v"(a[1][2]), "+v"(a[1][3]) : "n"(N) : "memory");
-}
-template <int N>
-__device__ __forceinline__ void quad_wait(u32x4 (&b)[4]) {
-  asm volatile("s_waitcnt vmcnt(%4) lgkmcnt(0)\n\ts_barrier" : "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]) : "n"(N) : "memory");
+__device__ __forceinline__ void quad_wait() {
+  static_assert(N < 16, "the counter's low bits");
+  asm volatile("" : : : "memory");
+  __builtin_amdgcn_s_waitcnt(0x70 | N);       // vmcnt(N) lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" : : : "memory");
+  __builtin_amdgcn_sched_barrier(0);
 }
 // QUAD: the column of the tile that row R of a buffer of weights holds: first the 32 columns of each of the four waves' first blocks, then
 // those of their second ones
@@ -308,55 +285,50 @@ __device__ __forceinline__ void tile_mma_fwd(floatx16 (&acc)[TM][TN], const unsi
   const int r = lane & 31, h = lane >> 5;
   const int sw = fwd_swz<KB>(r);   // tile rows start at multiples of 32, a multiple of the swizzle period
   constexpr int NV = KB / 32;
-  // LDS byte address of this lane's 16 bytes of K-step 0 in its first A / B row; K-step vs sits at the same
-  // address with bit 5 .. flipped by vs (chunk index (2 vs + h) ^ sw = (2 vs) ^ (h ^ sw): no carries)
-  const unsigned a0 = (unsigned)(uintptr_t)As + (wm * TM * 32 + r) * KB + ((h ^ sw) << 4);
-  const unsigned b0 = (unsigned)(uintptr_t)Bs + (wn * TN * 32 + r) * KB + ((h ^ sw) << 4);
+  // `at`: this lane's 16 bytes of K-step 0 in its rows; K-step vs sits there with bit 5 .. flipped by vs (chunk index
+  // (2 vs + h) ^ sw = (2 vs) ^ (h ^ sw): no carries).  The reads of K-step vs + 1 are in flight while the MFMAs of K-step vs run (two register
+  // sets), which the scheduling barriers keep in this order.
+  const unsigned char* const a0 = As + (wm * TM * 32 + r) * KB;
+  const unsigned char* const b0 = Bs + (wn * TN * 32 + r) * KB;
+  const int at = (h ^ sw) << 4;
   u32x4 a[2][TM], b[2][TN];
   auto fetch = [&](auto vs, auto set) __attribute__((always_inline)) {
-    const unsigned aa = a0 ^ (vs.value << 5), bb = b0 ^ (vs.value << 5);
-    static_for<0, TM>([&](auto t) __attribute__((always_inline)) { lds_read16<t.value * 32 * KB>(a[set.value][t.value], aa); });
-    static_for<0, TN>([&](auto t) __attribute__((always_inline)) { lds_read16<t.value * 32 * KB>(b[set.value][t.value], bb); });
+    const int k = at ^ (vs.value << 5);
+#pragma unroll
+    for (int t = 0; t < TM; ++t) a[set.value][t] = *reinterpret_cast<const u32x4*>(a0 + k + t * 32 * KB);
+#pragma unroll
+    for (int t = 0; t < TN; ++t) b[set.value][t] = *reinterpret_cast<const u32x4*>(b0 + k + t * 32 * KB);
+    __builtin_amdgcn_sched_barrier(0);
   };
   fetch(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
   static_for<0, NV>([&](auto vs) __attribute__((always_inline)) {
     constexpr int cur = vs.value & 1;
-    if constexpr (vs.value + 1 < NV) {
-      fetch(std::integral_constant<int, vs.value + 1>{}, std::integral_constant<int, cur ^ 1>{});
-      lds_wait<TM + TN>(a[cur], b[cur]);
-    } else {
-      lds_wait<0>(a[cur], b[cur]);
-    }
+    if constexpr (vs.value + 1 < NV) fetch(std::integral_constant<int, vs.value + 1>{}, std::integral_constant<int, cur ^ 1>{});
     mma_step(acc, a[cur], b[cur], T());
     __builtin_amdgcn_sched_barrier(0);       // keep these MFMAs in front of the next K-step's wait
   });
 }
 
-// The same with the address of every fragment's row given (SHARE).
+// The same with the offset of every fragment's row in its stage given (SHARE).
 template <typename T, int TM, int TN, int KB>
-__device__ __forceinline__ void tile_mma_rows(floatx16 (&acc)[TM][TN], const unsigned (&arow)[TM], unsigned a_stage, const unsigned char* Bs, int wn,
-                                              int lane) {
+__device__ __forceinline__ void tile_mma_rows(floatx16 (&acc)[TM][TN], const unsigned (&arow)[TM], unsigned a_stage, const unsigned char* As,
+                                              const unsigned char* Bs, int wn, int lane) {
   const int r = lane & 31, h = lane >> 5;
   constexpr int NV = KB / 32;
-  const unsigned b0 = (unsigned)(uintptr_t)Bs + (wn * TN * 32 + r) * KB + ((h ^ fwd_swz<KB>(r)) << 4);
-  unsigned a0[TM];
-#pragma unroll
-  for (int t = 0; t < TM; ++t) a0[t] = arow[t] + a_stage;
+  const unsigned char* const b0 = Bs + (wn * TN * 32 + r) * KB;
+  const int at = (h ^ fwd_swz<KB>(r)) << 4;
   u32x4 a[2][TM], b[2][TN];
   auto fetch = [&](auto vs, auto set) __attribute__((always_inline)) {
-    const unsigned bb = b0 ^ (vs.value << 5);
-    static_for<0, TM>([&](auto t) __attribute__((always_inline)) { lds_read16<0>(a[set.value][t.value], a0[t.value] ^ (vs.value << 5)); });
-    static_for<0, TN>([&](auto t) __attribute__((always_inline)) { lds_read16<t.value * 32 * KB>(b[set.value][t.value], bb); });
+#pragma unroll
+    for (int t = 0; t < TM; ++t) a[set.value][t] = *reinterpret_cast<const u32x4*>(As + ((arow[t] + a_stage) ^ (vs.value << 5)));
+#pragma unroll
+    for (int t = 0; t < TN; ++t) b[set.value][t] = *reinterpret_cast<const u32x4*>(b0 + (at ^ (vs.value << 5)) + t * 32 * KB);
+    __builtin_amdgcn_sched_barrier(0);
   };
   fetch(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
   static_for<0, NV>([&](auto vs) __attribute__((always_inline)) {
     constexpr int cur = vs.value & 1;
-    if constexpr (vs.value + 1 < NV) {
-      fetch(std::integral_constant<int, vs.value + 1>{}, std::integral_constant<int, cur ^ 1>{});
-      lds_wait<TM + TN>(a[cur], b[cur]);
-    } else {
-      lds_wait<0>(a[cur], b[cur]);
-    }
+    if constexpr (vs.value + 1 < NV) fetch(std::integral_constant<int, vs.value + 1>{}, std::integral_constant<int, cur ^ 1>{});
     mma_step(acc, a[cur], b[cur], T());
     __builtin_amdgcn_sched_barrier(0);       // keep these MFMAs in front of the next K-step's wait
   });
@@ -623,7 +595,7 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
 #pragma unroll
       for (int sft = 0; sft < 2; ++sft) {
         const int slot = run * (Hr + 1) + x + sft - x0;
-        arow[sft][t] = (unsigned)(uintptr_t)As + slot * KB + (((lane >> 5) ^ (share_xor(Hr, G, run, x + sft) & (CPR - 1))) << 4);
+        arow[sft][t] = slot * KB + (((lane >> 5) ^ (share_xor(Hr, G, run, x + sft) & (CPR - 1))) << 4);
       }
     }
   } else
@@ -798,13 +770,13 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
         load_pixels(ga, (i + 1) & 1);
         stage_next(ga);
       }
-      tile_mma_rows<T, TM, TN, KB>(acc, arow[0], a_stage, Bs + b_cur * BN * KBB, wn, lane);
+      tile_mma_rows<T, TM, TN, KB>(acc, arow[0], a_stage, As, Bs + b_cur * BN * KBB, wn, lane);
       b_cur = b_cur == NST - 1 ? 0 : b_cur + 1;
       // the second tap's weights have landed; what was requested after them may stay in flight: later weights and the pixels, PA or more copies
       if (more) wait_vm<(NST - 2) * PB + PA>(); else wait_vm<0>();
       __syncthreads();
       if (more) next_weights();
-      tile_mma_rows<T, TM, TN, KB>(acc, arow[1], a_stage, Bs + b_cur * BN * KBB, wn, lane);
+      tile_mma_rows<T, TM, TN, KB>(acc, arow[1], a_stage, As, Bs + b_cur * BN * KBB, wn, lane);
       b_cur = b_cur == NST - 1 ? 0 : b_cur + 1;
       // the next stage's pixels and first weights have landed
       if (more && NST > 2) wait_vm<PB>(); else wait_vm<0>();
@@ -854,15 +826,15 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
       rw.z = more ? w_bytes : 0;
     };
     const int r = lane & 31, h = lane >> 5, sw = fwd_swz<KB>(r);
-    const unsigned a0 = lds0 + (wm * 128 + r) * 128 + ((h ^ sw) << 4);
-    const unsigned b0 = lds0 + 65536 + (wn * 32 + r) * 128 + ((h ^ sw) << 4);
+    const int a0 = (wm * 128 + r) * 128 + ((h ^ sw) << 4), b0 = 65536 + (wn * 32 + r) * 128 + ((h ^ sw) << 4);
     u32x4 a[2][2][4], b[2][4];
     auto read_a = [&](auto half, auto buf, auto k) __attribute__((always_inline)) {
-      lds_read16<buf.value * 32768 + half.value * 8192>(a[half.value][0][k.value], a0 ^ (k.value << 5));
-      lds_read16<buf.value * 32768 + half.value * 8192 + 4096>(a[half.value][1][k.value], a0 ^ (k.value << 5));
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        a[half.value][t][k.value] = *reinterpret_cast<const u32x4*>(smem + (a0 ^ (k.value << 5)) + buf.value * 32768 + half.value * 8192 + t * 4096);
     };
     auto read_b = [&](auto half, auto buf, auto k) __attribute__((always_inline)) {
-      lds_read16<buf.value * 32768 + half.value * 16384>(b[half.value][k.value], b0 ^ (k.value << 5));
+      b[half.value][k.value] = *reinterpret_cast<const u32x4*>(smem + (b0 ^ (k.value << 5)) + buf.value * 32768 + half.value * 16384);
     };
     const std::integral_constant<int, 0> c0{};
     const std::integral_constant<int, 1> c1{};
@@ -873,11 +845,9 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
     next_chunk();
     load_a(c0, c1); load_b(c1, c1); load_b(c0, c1); load_a(c1, c1);
     next_chunk();
-    wait_vm<12>();
-    __syncthreads();
+    quad_wait<12>();
     static_for<0, 4>([&](auto k) __attribute__((always_inline)) { read_a(c0, c0, k); read_b(c0, c0, k); });
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[0][2]), "+v"(b[0][3]) : : "memory");
-    quad_wait<10>(a[0]);
+    quad_wait<10>();
     load_a(c0, c0);
     // a quarter of a chunk: rows ah, columns bh; reads(k) and loads(k) go between its four K-steps
     auto quarter = [&](auto ah, auto bh, auto&& reads, auto&& loads) __attribute__((always_inline)) {
@@ -900,14 +870,14 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
       const std::integral_constant<int, B> first{};
       const std::integral_constant<int, 1 - B> second{};
       quarter(c0, first, [&](auto k) __attribute__((always_inline)) { read_b(second, buf, k); }, [&]() __attribute__((always_inline)) { load_b(first, buf); });
-      quad_wait<12>(b[1 - B]);
+      quad_wait<12>();
       quarter(c0, second, [&](auto k) __attribute__((always_inline)) { read_a(c1, buf, k); }, [&]() __attribute__((always_inline)) { load_b(second, buf); });
-      quad_wait<12>(a[1]);
+      quad_wait<12>();
       quarter(c1, second, [&](auto k) __attribute__((always_inline)) { read_a(c0, second, k); }, [&]() __attribute__((always_inline)) { load_a(c1, buf); });
-      quad_wait<12>(a[0]);
+      quad_wait<12>();
       quarter(c1, first, [&](auto k) __attribute__((always_inline)) { read_b(second, second, k); },
               [&]() __attribute__((always_inline)) { next_chunk(); load_a(c0, second); });
-      quad_wait<12>(b[1 - B]);
+      quad_wait<12>();
     };
     for (int c = 0; c < nk; c += 2) {
       chunk(c0);
@@ -1693,24 +1663,15 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void wgrad_kerne
     };
     const std::integral_constant<int, 0> c0{};
     const std::integral_constant<int, 1> c1{};
-    // (the waits as builtins: the compiler counts these reads, and would count them beyond the waits otherwise)
-    auto next_quarter = [](auto in_flight) __attribute__((always_inline)) {
-      asm volatile("" : : : "memory");
-      __builtin_amdgcn_s_waitcnt(0x70 | in_flight.value);       // vmcnt(in_flight) lgkmcnt(0)
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" : : : "memory");
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    const std::integral_constant<int, 12> six{};                 // quarters' copies
     place();
     set();
     load_a(c0, c0); load_b(c0, c0); load_b(c1, c0); load_a(c1, c0);
     next_chunk();
     load_a(c0, c1); load_b(c1, c1); load_b(c0, c1); load_a(c1, c1);
     next_chunk();
-    next_quarter(six);
+    quad_wait<12>();
     static_for<0, 4>([&](auto k) __attribute__((always_inline)) { read_a(c0, c0, k); read_b(c0, c0, k); });
-    next_quarter(std::integral_constant<int, 10>{});
+    quad_wait<10>();
     load_a(c0, c0);
     auto quarter = [&](auto ah, auto bh, auto&& reads, auto&& loads) __attribute__((always_inline)) {
       static_for<0, 4>([&](auto k) __attribute__((always_inline)) {
@@ -1725,7 +1686,7 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void wgrad_kerne
         if constexpr (k.value == 2) loads();
         __builtin_amdgcn_sched_barrier(0);
       });
-      next_quarter(six);
+      quad_wait<12>();
     };
     auto chunk_mma = [&](auto buf) __attribute__((always_inline)) {
       constexpr int B = buf.value;
