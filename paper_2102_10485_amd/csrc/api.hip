@@ -810,8 +810,12 @@ PackArgs pack_args(gan_ctx* c, Net& net, const ConvLayer& cl, int Kc, int nslot,
   return a;
 }
 
-// D's linear head.  Both segments: the discriminator's cost on (real, fake); the fake one alone: the generator's.
-HeadArgs head_args(gan_ctx* c, int n, int seg_first, int nseg) {
+// A pass through D belongs to one of the two costs, and that says which segments it runs over.
+struct Segments { int first, count; };
+Segments segments_of(Cost cost) { return cost == COST_D ? Segments{0, 2} : Segments{1, 1}; }
+
+// D's linear head
+HeadArgs head_args(gan_ctx* c, int n, Cost cost) {
   Net& D = c->D;
   HeadArgs h;
   memset(&h, 0, sizeof(h));
@@ -819,11 +823,12 @@ HeadArgs head_args(gan_ctx* c, int n, int seg_first, int nseg) {
   h.dw = D.g + D.fc_w; h.db = D.g + D.fc_b; h.pstride = D.P; h.logits = c->logits; h.dlogits = c->dlogits;
   h.part = c->head_part; h.rsplit = c->head_rsplit;
   h.offs = c->rb.offs; h.sample_model = c->rb.sample_model; h.L = c->L; h.K = D.K;
-  h.seg_first = seg_first; h.nseg = nseg; h.seg_samples = n; h.n = n;
-  h.mode = nseg == 2 ? 0 : 1;
-  h.loss = h.mode == 0 ? c->loss_d : c->loss_g;
-  h.scale = h.mode == 0 ? c->cfg.d_loss_scale : c->cfg.g_loss_scale;
-  const Net& net = h.mode == 0 ? c->D : c->G;      // whose update follows
+  const Segments seg = segments_of(cost);
+  h.seg_first = seg.first; h.nseg = seg.count; h.seg_samples = n; h.n = n;
+  h.cost = cost;
+  h.loss = cost == COST_D ? c->loss_d : c->loss_g;
+  h.scale = cost == COST_D ? c->cfg.d_loss_scale : c->cfg.g_loss_scale;
+  const Net& net = cost == COST_D ? c->D : c->G;      // whose update follows
   h.adam_t = net.t; h.adam_bc = net.bc; h.beta1 = c->cfg.beta1; h.beta2 = c->cfg.beta2;
   return h;
 }
@@ -856,8 +861,9 @@ void g_forward(gan_ctx* c, int n, bool use_running, bool update_running, float* 
 }
 
 template <typename T>
-void d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_running) {
+void d_forward(gan_ctx* c, int n, Cost cost, bool update_running) {
   Net& D = c->D;
+  const int seg_first = segments_of(cost).first, nseg = segments_of(cost).count;
   const float slope = c->cfg.leaky_slope;
   // first conv (+label maps, bias, LeakyReLU) as a row-by-row GEMM over the patch matrix
   const ConvLayer& c1 = D.conv[0];
@@ -873,22 +879,24 @@ void d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_running) 
                   c->dpre[j], c->dact[j], update_running, MODE_DOWN, cl.Hs * cl.Hs);
   }
   Scope s(c, "head_fwd", 0, sizeof(T) * (double)n * nseg * D.K);
-  launch_head_fwd<T>(head_args(c, n, seg_first, nseg), c->st);
+  launch_head_fwd<T>(head_args(c, n, cost), c->st);
 }
 
 // Backward through D.  param_grads: fill D's gradient block (both segments summed).  to_image: continue down to
 // d cost / d fake, multiplied by the tanh derivative, into dimg.
-// adam (with param_grads): D's planned update, whose step counts are already advanced; the update of a convolution's
-// weights is enqueued beside the chain as soon as its gradient is complete and its data gradient has read the old ones.
+// adam (with param_grads): D's planned update, whose step counts and bias corrections the head's launch here advances, in front of
+// every part of it; the update of a convolution's weights is enqueued beside the chain as soon as its gradient is complete and its
+// data gradient has read the old ones.
 template <typename T>
-void d_backward(gan_ctx* c, int n, int seg_first, int nseg, bool param_grads, bool to_image, const AdamArgs* adam = nullptr) {
+void d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_image, const AdamArgs* adam = nullptr) {
   Net& D = c->D;
+  const int seg_first = segments_of(cost).first, nseg = segments_of(cost).count;
   hipStream_t side = side_stream(c);
   const float slope = c->cfg.leaky_slope;
   const int nl = (int)D.conv.size();
   {
     Scope s(c, "head_bwd", 0, sizeof(T) * (double)n * nseg * D.K * (param_grads ? 2 : 1));
-    launch_head_bwd<T>(head_args(c, n, seg_first, nseg), param_grads, c->st);
+    launch_head_bwd<T>(head_args(c, n, cost), param_grads, c->st);
   }
   int pending = -1;                // region of D's planned update whose turn comes next
   for (int j = nl - 1; j >= 1; --j) {
@@ -1051,8 +1059,9 @@ void paper_g_forward(gan_ctx* c, int n, bool use_running, bool update_running, f
 // pass0: dropout pass id of the first processed segment (real 0, fake 1, fake through the updated D 2);
 // step_add: 1 before D's update of this iteration, 0 after it (the iteration number is D's step count + step_add)
 template <typename T>
-void paper_d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_running, int pass0, int step_add) {
+void paper_d_forward(gan_ctx* c, int n, Cost cost, bool update_running, int pass0, int step_add) {
   Net& D = c->D;
+  const int seg_first = segments_of(cost).first, nseg = segments_of(cost).count;
   const gan_config& f = c->cfg;
   const ConvLayer& c1 = D.conv[0];
   conv_call<T>(c, "gemm_dense_img", MODE_DENSE, EPI_LRELU, c->colD, Weights{c->wpD, (long long)c1.Cs * c->KcD}, c->dact[0], nullptr, c->KcD,
@@ -1077,17 +1086,18 @@ void paper_d_forward(gan_ctx* c, int n, int seg_first, int nseg, bool update_run
                          cl.cs_real, c->dpre[j], c->dact[j], f.bn_eps, update_running);
   }
   Scope s(c, "head_fwd", 0, sizeof(T) * (double)n * nseg * D.K);
-  launch_head_fwd<T>(head_args(c, n, seg_first, nseg), c->st);
+  launch_head_fwd<T>(head_args(c, n, cost), c->st);
 }
 
 template <typename T>
-void paper_d_backward(gan_ctx* c, int n, int seg_first, int nseg, bool param_grads, bool to_image) {
+void paper_d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_image) {
   Net& D = c->D;
+  const int seg_first = segments_of(cost).first, nseg = segments_of(cost).count;
   const gan_config& f = c->cfg;
   const int nl = (int)D.conv.size();
   {
     Scope s(c, "head_bwd", 0, sizeof(T) * (double)n * nseg * D.K * (param_grads ? 2 : 1));
-    launch_head_bwd<T>(head_args(c, n, seg_first, nseg), param_grads, c->st);
+    launch_head_bwd<T>(head_args(c, n, cost), param_grads, c->st);
   }
   for (int j = nl - 1; j >= 1; --j) {
     const ConvLayer& cl = D.conv[j];
@@ -1252,11 +1262,11 @@ void paper_train_step(gan_ctx* c, const int32_t* label_ids, const float* noise, 
   route_and_stage<T>(c, label_ids, noise, real, n);
   paper_g_forward<T>(c, n, false, true);                               // fake = G(z)
   im2col_call<T>(c, c->D.conv[0], c->xd, nullptr, c->colD, c->KcD, c->nslot, 1, n);
-  paper_d_forward<T>(c, n, 0, 2, true, 0, 1);                          // D(real), D(fake): dropout passes 0 and 1
-  paper_d_backward<T>(c, n, 0, 2, true, false);                        // Eq. 3
+  paper_d_forward<T>(c, n, COST_D, true, 0, 1);                        // D(real), D(fake): dropout passes 0 and 1
+  paper_d_backward<T>(c, n, COST_D, true, false);                      // Eq. 3
   adam_call<T>(c, c->D, false);
-  paper_d_forward<T>(c, n, 1, 1, true, 2, 0);                          // updated D on the same fake batch: pass 2
-  paper_d_backward<T>(c, n, 1, 1, false, true);                        // Eq. 4 (negated: minimised)
+  paper_d_forward<T>(c, n, COST_G, true, 2, 0);                        // updated D on the same fake batch: pass 2
+  paper_d_backward<T>(c, n, COST_G, false, true);                      // Eq. 4 (negated: minimised)
   paper_g_backward<T>(c, n);
   paper_adam_g<T>(c);
 }
@@ -1268,16 +1278,16 @@ void train_step(gan_ctx* c, const int32_t* label_ids, const float* noise, const 
   route_and_stage<T>(c, label_ids, noise, real, n);
   g_forward<T>(c, n, false, true);                 // fake = G(z)
   im2col_call<T>(c, c->D.conv[0], c->xd, nullptr, c->colD, c->KcD, c->nslot, 1, n);   // the fake half of D's input
-  d_forward<T>(c, n, 0, 2, true);                  // D(real), D(fake): separate batch statistics per segment
+  d_forward<T>(c, n, COST_D, true);                // D(real), D(fake): separate batch statistics per segment
   c->order_next = 0;
   {
     const AdamArgs aD = adam_args<T>(c, c->D);
-    d_backward<T>(c, n, 0, 2, true, false, &aD);   // Eq. 3; weight gradients and the convolutions' updates beside the chain
+    d_backward<T>(c, n, COST_D, true, false, &aD); // Eq. 3; weight gradients and the convolutions' updates beside the chain
     adam_rest_call<T>(c, c->D, false, aD);
     order_after(c, c->st, side_stream(c));
   }
-  d_forward<T>(c, n, 1, 1, true);                  // updated D on the same fake batch
-  d_backward<T>(c, n, 1, 1, false, true);          // Eq. 4 (negated: minimised); only data gradients: theta_D is not G's to move
+  d_forward<T>(c, n, COST_G, true);                // updated D on the same fake batch
+  d_backward<T>(c, n, COST_G, false, true);        // Eq. 4 (negated: minimised); only data gradients: theta_D is not G's to move
   {
     const AdamArgs aG = adam_args<T>(c, c->G);
     g_backward<T>(c, n, &aG);

@@ -157,6 +157,7 @@ struct ImgBiasArgs {
 template <typename T> void launch_img_bias_grad(const ImgBiasArgs& a, hipStream_t st);
 
 // D's final linear layer (one logit), the two costs, and their gradients.
+enum Cost { COST_D = 0, COST_G = 1 };      // the discriminator's, on (real, fake); the generator's, on fake
 struct HeadArgs {
   const void* feat;         // [rows][K] last feature map, flattened (h,w,c)
   void* dfeat;              // gradient w.r.t. it
@@ -174,7 +175,7 @@ struct HeadArgs {
   int* adam_t;              // with the costs: [L] step counts of the update that follows, advanced with the bias corrections adam_bc [L][2]
   float* adam_bc;
   float beta1, beta2;
-  int mode;                 // 0 = discriminator cost on (real, fake) ; 1 = generator cost on fake
+  Cost cost;
   float scale;
   // weight gradient: rsplit > 1 shares every model's rows among rsplit blocks per K chunk; their partial sums go to
   // part[rsplit][L][K + 4] (the bias term at index K) and are added in order by a second kernel

@@ -780,9 +780,9 @@ __device__ inline float sigmoid_f(float u) {
   return e / (1.f + e);
 }
 
-// mode 0 (Eq. 3): J_D = scale*mean softplus(-s_real) + scale*mean softplus(s_fake), segments (0, 1).  mode 1 (Eq. 4, negated):
+// COST_D (Eq. 3): J_D = scale*mean softplus(-s_real) + scale*mean softplus(s_fake), segments (0, 1).  COST_G (Eq. 4, negated):
 // scale*mean softplus(-s_fake') on segment seg_first.
-__device__ inline float head_sign(const HeadArgs& a, int seg) { return a.mode == 0 && seg == 1 ? 1.f : -1.f; }
+__device__ inline float head_sign(const HeadArgs& a, int seg) { return a.cost == COST_D && seg == 1 ? 1.f : -1.f; }
 
 // one wave per row: logit = <feat[row], w[model]> + b[model], and the cost's derivative by it
 template <typename T>
