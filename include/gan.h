@@ -263,6 +263,10 @@ gan_status gan_probe_copy(int64_t bytes, void* hip_stream, double* gbps);
    problem size as inside a training step, which for a few hundred tiles is one whose reduction several groups of waves share (no height names those).
    Lets a test run one case through the instantiations. */
 gan_status gan_op_tile_rows(gan_ctx* ctx, int32_t rows);
+/* What gan_op_conv_wgrad reduces over from now on (1 and 1 at first): `segments` batches of n_samples each, one behind the other in both operands
+   and with the same offs, as the discriminator's real and fake halves are; and into how many parts it splits every group's rows, 1 to 64, whose
+   partial results it leaves one behind the other, dw [splits][n_groups][4*4][cb][cs]. */
+gan_status gan_op_wgrad_parts(gan_ctx* ctx, int32_t segments, int32_t splits);
 gan_status gan_op_conv_down(gan_ctx* ctx, const void* big, const void* w_down, void* small_out, const int32_t* offs,
                             int32_t n_groups, int32_t n_samples, int32_t cb, int32_t cs, int32_t hs);
 gan_status gan_op_conv_up(gan_ctx* ctx, const void* small_in, const void* w_up, void* big_out, const int32_t* offs,

@@ -76,6 +76,7 @@ def load_library():
     L.gan_profile_enable.argtypes = [_VP, C.c_int32]
     L.gan_use_graphs.argtypes = [_VP, C.c_int32]
     L.gan_op_tile_rows.argtypes = [_VP, C.c_int32]
+    L.gan_op_wgrad_parts.argtypes = [_VP, C.c_int32, C.c_int32]
     L.gan_use_second_stream.argtypes = [_VP, C.c_int32]
     L.gan_graph_replays.argtypes = [_VP, C.POINTER(C.c_int64)]
     L.gan_profile_read.argtypes = [_VP, C.c_int32, C.POINTER(C.c_char_p), _I64P, C.POINTER(C.c_double),
@@ -287,6 +288,9 @@ class Gan:
     # single operations (device pointers as integers)
     def op_tile_rows(self, rows):
         self._check(self.lib.gan_op_tile_rows(self.h, rows))
+
+    def op_wgrad_parts(self, segments, splits):
+        self._check(self.lib.gan_op_wgrad_parts(self.h, segments, splits))
 
     def op_conv_down(self, big, w_down, small_out, offs, n_groups, n_samples, cb, cs, hs):
         self._check(self.lib.gan_op_conv_down(self.h, big, w_down, small_out, offs, n_groups, n_samples, cb, cs, hs))

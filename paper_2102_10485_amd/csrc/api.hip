@@ -147,6 +147,7 @@ struct gan_ctx {
   std::vector<StepArgs> seen;      // the last eight distinct argument sets that ran as plain launches
   unsigned long long calls = 0, replays = 0;
   int op_tile_rows = 0;            // single-operation entry points: tile height forced by the caller (0: chosen as in a step)
+  int op_segments = 1, op_splits = 1;      // of gan_op_conv_wgrad
 };
 
 namespace {
@@ -2034,6 +2035,14 @@ gan_status gan_op_tile_rows(gan_ctx* c, int32_t rows) {
   return GAN_OK;
 }
 
+gan_status gan_op_wgrad_parts(gan_ctx* c, int32_t segments, int32_t splits) {
+  if (!c) return GAN_E_ARG;
+  if (segments < 1 || segments > 2 || splits < 1 || splits > WG_MAX_KSPLIT) return fail(c, GAN_E_ARG, "one or two segments, and as many row splits as a step may take");
+  c->op_segments = segments;
+  c->op_splits = splits;
+  return GAN_OK;
+}
+
 gan_status gan_op_conv_down(gan_ctx* c, const void* big, const void* w_down, void* small_out, const int32_t* offs,
                             int32_t n_groups, int32_t n_samples, int32_t cb, int32_t cs, int32_t hs) {
   return op_conv(c, MODE_DOWN, big, w_down, small_out, offs, n_groups, n_samples, cb, cs, 2 * hs, hs, (long long)16 * cb * cs);
@@ -2051,7 +2060,8 @@ gan_status gan_op_conv_wgrad(gan_ctx* c, const void* big, const void* small_in, 
   (void)take_launch_error();
   WgradArgs a = {};
   a.Big = big; a.Small = small_in; a.dW = dw; a.offs = offs; a.dw_stride = (long long)16 * cb * cs;
-  a.L = n_groups; a.nseg = 1; a.seg_samples = n_samples; a.Cb = cb; a.Cs = cs; a.Hs = hs; a.ntaps = 16; a.ksplit = 1;
+  a.L = n_groups; a.nseg = c->op_segments; a.seg_samples = n_samples; a.Cb = cb; a.Cs = cs; a.Hs = hs; a.ntaps = 16; a.ksplit = c->op_splits;
+  a.split_stride = n_groups * a.dw_stride;
   if (c->bf16) launch_wgrad<bf16_t>(a, c->st); else launch_wgrad<float>(a, c->st);
   return finish_op(c);
 }

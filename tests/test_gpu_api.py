@@ -37,6 +37,9 @@ def test_single_operations_refuse_shapes_the_kernels_do_not_support():
     assert g.lib.gan_op_conv_down(g.h, p, p, p, o, 1, -1, 64, 64, 4) == binding.GAN_E_ARG
     # a tile height the kernels do not have
     assert g.lib.gan_op_tile_rows(g.h, 96) == binding.GAN_E_ARG
+    # segments and row splits that no step has
+    for parts in ((0, 1), (3, 1), (1, 0), (1, 65)):
+        assert g.lib.gan_op_wgrad_parts(g.h, *parts) == binding.GAN_E_ARG
     # and the context still works afterwards, with every tile height there is
     for rows in (64, 128, 256, 0):
         g.op_tile_rows(rows)

@@ -410,6 +410,47 @@ def test_weight_gradient_in_quarters(ctxs, cb, cs, hs, groups):
                 assert np.array_equal(got[i, ky, kx], x.T @ y), (i, ky, kx)
 
 
+@pytest.mark.parametrize("prec,cb,cs,hs,groups,segments,splits", [
+    (binding.BF16, 128, 256, 8, [1, 3, 0], 2, 1),      # in quarters: one and three chunks to a segment
+    (binding.BF16, 256, 256, 8, [8, 16], 2, 1),        # pixel rows in turn, seven and fourteen chunks, the first or last pixel row's left out
+    (binding.BF16, 128, 256, 4, [16, 1], 2, 3),        # a share without rows; one of three of a chunk each
+    (binding.BF16, 128, 256, 8, [16], 1, 2),           # the row that is left out at the start of a share and at the end of one
+    (binding.BF16, 128, 512, 8, [16, 3], 2, 8),        # shares that are a pixel row, all of it left out
+    (binding.BF16, 128, 256, 8, [16], 2, 16),          # shares that are half of one
+    (binding.BF16, 128, 256, 8, [24], 2, 5),           # shares that start inside a pixel row
+    (binding.BF16, 128, 256, 32, [2], 2, 7),
+    (binding.BF16, 64, 256, 8, [8, 3], 2, 3), (binding.BF16, 128, 128, 4, [16, 5], 2, 2), (binding.BF16, 128, 64, 7, [5], 2, 3),       # other tiles
+    (binding.FP32, 128, 256, 8, [8, 1], 2, 3), (binding.FP32, 128, 64, 7, [4, 0, 2], 2, 2), (binding.FP32, 64, 128, 4, [9], 2, 1),
+])
+def test_weight_gradient_of_segments_and_row_splits(ctxs, prec, cb, cs, hs, groups, segments, splits):
+    """What a step's weight gradients run and the cases above do not: two segments, and rows shared among blocks.  Small whole numbers, so
+    that every sum is exact in fp32, the parts' sum included."""
+    torch = U.torch_mod()
+    g, bf = ctxs[prec], prec == binding.BF16
+    rng = np.random.default_rng(cb + cs + hs + splits)
+    n, G = int(sum(groups)), len(groups)
+    offs = np.concatenate([[0], np.cumsum(groups)]).astype(np.int32)
+    big = rng.integers(-3, 4, (segments, n, 2 * hs, 2 * hs, cb)).astype(np.float32)
+    small = rng.integers(-3, 4, (segments, n, hs, hs, cs)).astype(np.float32)
+    d_offs, d_big, d_small = U.dev(offs), U.dev(U.pack(big, bf)), U.dev(U.pack(small, bf))
+    dw = torch.full((splits, G, 4, 4, cb, cs), 7.0, dtype=torch.float32, device="cuda")
+    g.op_wgrad_parts(segments, splits)
+    try:
+        g.op_conv_wgrad(d_big.data_ptr(), d_small.data_ptr(), dw.data_ptr(), d_offs.data_ptr(), G, n, cb, cs, hs)
+    finally:
+        g.op_wgrad_parts(1, 1)
+    got = dw.cpu().numpy().astype(np.float64)
+    got = got.sum(axis=0)
+    pad = np.pad(big, ((0, 0), (0, 0), (1, 1), (1, 1), (0, 0)))
+    for i in range(G):
+        part = slice(offs[i], offs[i + 1])
+        y = small[:, part].reshape(-1, cs)
+        for ky in range(4):
+            for kx in range(4):
+                x = pad[:, part, ky:ky + 2 * hs:2, kx:kx + 2 * hs:2].reshape(-1, cb)
+                assert np.array_equal(got[i, ky, kx], x.T @ y), (i, ky, kx)
+
+
 @pytest.mark.parametrize("mode", ["down", "up"])
 def test_fp32_weights_up_to_two_gibibytes(ctxs, mode):
     """A weight block of 1.45 GB: its three bf16 planes together are beyond what a 32-bit byte offset reaches, each by itself is not."""
