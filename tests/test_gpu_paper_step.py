@@ -177,6 +177,18 @@ def test_paper_networks_other_image_shapes(prec, spec_name):
 
 
 @pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+def test_paper_channels_that_do_not_divide_the_threads(prec, monkeypatch):
+    """136 channels, held as 192: 24 or 48 groups of 16 bytes a row, which do not divide the 256 threads of BatchNorm's apply passes (here with the
+    activation and the dropout in front of it); 300 samples, so that a block goes round two or three times."""
+    monkeypatch.setitem(synth.SPECS, "paper136", dict(family="paper", cond_g=0, cond_d=0, z_dim=16, img_c=1, img_hw=16, g_h0=4, g_ch=[192, 64, 64],
+                                                      d_ch=[16, 136]))
+    p = PaperPair("paper136", 1, 300, prec)
+    p.step(*batch(p.spec, np.zeros(300), 630))
+    p.compare("136 channels")
+    p.close()
+
+
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
 def test_zero_activations_behind_dropout(prec):
     """The backward pass reads the dropout mask off the stored activations, where a kept zero is not a dropped one: channels of
     the first and the second block whose weights and bias are zero have pre-activations of exactly zero, and their bias gradients are

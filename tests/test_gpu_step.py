@@ -267,6 +267,33 @@ def test_four_image_channels_and_partial_patches(prec, monkeypatch):
 
 
 @pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+@pytest.mark.parametrize("n", [11, 520])
+def test_channels_that_do_not_divide_the_threads(prec, n, monkeypatch):
+    """192 channels, whose 24 or 48 groups of 16 bytes do not divide the 256 threads of BatchNorm's apply passes: a thread's channels change
+    from row to row.  520 samples: one block each, which goes round two or three times; 11: several blocks a sample."""
+    monkeypatch.setitem(synth.SPECS, "wide192", dict(cond_g=0, cond_d=0, z_dim=12, img_c=1, img_hw=16, g_h0=2, g_ch=[64, 192, 64],
+                                                     d_ch=[64, 192]))
+    p = Pair("wide192", 1, 1, n, prec)
+    p.step(*batch(p.spec, np.zeros(n), 660))
+    p.compare("192 channels, %d samples" % n)
+    p.close()
+
+
+def test_layers_on_tiles_of_256_columns(monkeypatch):
+    """A step whose layers get 256 x 256 tiles in bf16: the statistics of G's and D's feature maps come out of those tiles, the weight gradients
+    of D have two segments.  One of sixteen models against the oracle."""
+    monkeypatch.setitem(synth.SPECS, "wide", dict(cond_g=0, cond_d=0, z_dim=20, img_c=3, img_hw=32, g_h0=4, g_ch=[64, 512, 64], d_ch=[128, 256]))
+    p = Pair("wide", 16, 16, 512, binding.BF16, oracle_models=[3])
+    p.gpu.profile_enable(True)
+    p.step(*batch(p.spec, np.random.default_rng(5).permutation(np.arange(512) % 16), 670))
+    names = set(p.gpu.profile_read())
+    p.gpu.profile_enable(False)
+    assert {"gemm_down<256x256>", "gemm_up<256x256>", "wgrad<256x256>"} <= names, names
+    p.compare("256 x 256")
+    p.close()
+
+
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
 def test_single_unconditional_pair(prec):
     """The paper's DC-GAN comparison system (Tables 1 and 2) at test size: one pair, no label anywhere (one label,
     no conditioning), a batch of several hundred so that every weight gradient is split over rows and summed in a
