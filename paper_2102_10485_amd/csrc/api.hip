@@ -672,9 +672,11 @@ int wgrad_ksplit(const gan_ctx* c, int Cb, int Cs, int ntaps, int Hs, int nseg) 
   const double blocks = (double)c->L * wgrad_tiles_per_model((int)esize(c), ntaps, Cb, Cs);
   const double rows = (double)c->NB * nseg * Hs * Hs, out = (double)c->L * ntaps * Cb * Cs * 4;
   // bf16: counted as one block per CU, which the 256x256 and 256x128 tiles are (128 and 96 KiB of LDS); of the 256x64 tile (80 KiB) a CU
-  // holds two, which the estimate does not tell apart.  fp32: a CU holds two blocks, which reach 133 TFLOP/s over the chip where single ones reach 99 (ten
-  // models of 128 samples, 64 -> 128 channels at side 7, 80 tiles: 3 splits 305 us, 4 308, 6 230, 7 291, 8 263, 12 233; taken before
-  // the operands were scaled, which costs every one of them 3 %).
+  // holds two, which the estimate does not tell apart.  fp32: a CU holds two blocks, which reached 133 TFLOP/s over the chip where single ones reached 99
+  // when every wave split what it multiplied (ten models of 128 samples, 64 -> 128 channels at side 7, two segments, 80 tiles); with chunks split once a block
+  // 156 and 106: 3 splits 310 us, 4 287, 6 211, 7 279, 8 254, 12 213.  The bf16 256x256 tile in quarters reaches 900 to 1020.  Of 99 shapes, batches and
+  // numbers of models two (fp32) and eleven (bf16) would be split otherwise with these rates, ten of the thirteen by a tenth at most, so the rates
+  // stand as they were taken.
   const double product = 2.0 * rows * ntaps * Cb * Cs / (c->bf16 ? 900e12 : 133e12), single = c->bf16 ? 1.0 : 1.34;
   const double chunk_rows = 128 / (double)esize(c);
   int best = 1;

@@ -20,7 +20,8 @@
 // The 16-byte chunk c of row
 // R sits at position c ^ ((R / (256/KB)) % (KB/16)), which keeps both the 1 KiB-per-wave copies and the MFMA operand
 // reads conflict-free.
-// One barrier per chunk in both; the 256 x 256 tile of the convolutions has one per quarter of a chunk (quad_loop).
+// One barrier per chunk in both, except that the 256 x 256 tiles of the convolutions and of the weight gradient have one per quarter of a
+// chunk (their quad_loops), tiles that share pixels one per tap of a stage, and the fp32 weight gradient two per chunk (split_loop).
 #include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -122,6 +123,11 @@ template <typename TL> static bool share_fits(int H) {
 // up 256 -> 128, side 4: 104 28.3 / 24.1 / 15.7, 408 41.1 / 38.6 / 56.7, 808 70.0 / 72.0 / 98; bf16: down 128 -> 256, side 4: 104 13.3 /
 // 11.6 / 9.6, 208 13.8 / 12.2 / 16.8, 408 17.6 / 17.3 / 31.7; up 128 -> 64, side 7: 104 6.5 / 6.6 / 6.3, 400 8.1 / 9.0 / 18.3.
 // (Their rates are such that the time of a lone block compares with a lone Tiny's.)
+// The bf16 rates were taken when the 256x256 tile multiplied whole chunks, as MODE_DENSE still does.  With chunks in quarters, a hundred models of
+// 64 samples, us of 256x256, 128x128 and 64x64: down 128 -> 256 channels, side 8, 367, 498, 714; 256 -> 512, side 4, 338, 421, 632; up 512 -> 256,
+// side 4, 351, 414, 662; 128 -> 256, side 8, 438, 506, 730: 128x128 at 0.74 to 0.87, 64x64 at 0.51 to 0.60.  256x128 and 128x128: down 256 -> 128,
+// side 8, 450 and 433; up 256 -> 128, side 8, 414 and 460: 0.77 to 0.95 for 256x128.
+// So the lines still lie inside what their tiles reach; what differs is the mode, which they do not tell apart.
 struct TileInfo { ConvTile id; const char* name; int rows, cols, split, per_cu; double rate; int most; };
 template <typename TL> constexpr TileInfo info(ConvTile id, const char* name, int per_cu, double rate, int most = 1 << 30) {
   return {id, name, TL::BM, TL::BN, TL::WM, per_cu, rate, most};
@@ -783,17 +789,17 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
       __syncthreads();
     }
   };
-  // QUAD.  With whole chunks in two buffers a buffer is free when its last K-step has been read and has to be full one chunk later, so a
-  // chunk took at least as long as its 64 copies: 1100 to 1400 cycles to issue, in which the waves stand in front of the first products, and the
-  // slowest one's way to memory, 3500 in all for 2048 of MFMAs.  Here a wave multiplies half its rows by half its columns at a time, in
-  // the order (0, f) (0, s) (1, s) (1, f) with the operands of all four K-steps in registers, f and s being the halves of columns, f = 0 in even
-  // chunks and 1 in odd ones.  A quarter needs one half of an operand that the previous ones did not, which is read in the
-  // quarter before it; the quarter after that, the half's place in LDS is filled with that of the chunk after the next.  So every half has seven
-  // quarters to arrive in, two copies a wave go out in each, between the products, and one barrier a quarter says both that the next half is here and that
-  // the last one is free.  Cycles of a launch, 128 -> 256 channels at side 8, two segments of 6400 samples: 1538k -> 1274k, 256 -> 512 at side 4
-  // 1391k -> 1123k (matrix pipe busy 0.50 -> 0.60 and 0.52 -> 0.64 of them).  The clock goes down with the power the pipe takes, 2.05 -> 1.86 GHz, which
-  // leaves 769 -> 688 and 701 -> 616 us; 512 -> 256 transposed, side 4, one segment 363 -> 331.  Issuing the copies in front of the reads
-  // or between them, or at a raised wave priority: +-0.5 %.
+  // QUAD.  With whole chunks in two buffers a buffer is free when its last K-step has been read and has to be full one chunk later, so a chunk took
+  // at least as long as its 64 copies: 1100 to 1400 cycles to issue, in which the waves stand in front of the first products, and the slowest one's
+  // way to memory, 3500 to 3900 in all (a launch's cycles over the chunks of its rounds of blocks) for 2048 of MFMAs.  Here a wave multiplies half
+  // its rows by half its columns at a time, in the order (0, f) (0, s) (1, s) (1, f) with the operands of all four K-steps in registers, f and s
+  // being the halves of columns, f = 0 in even chunks and 1 in odd ones.  A quarter needs one half of an operand that the previous ones did not,
+  // which is read in the quarter before it; the quarter after that, the half's place in LDS is filled with that of the chunk after the next.  So
+  // every half has six quarters and a part of one to arrive in, two copies a wave go out in each, between the products, and one barrier a quarter
+  // says both that the next half is here and that the last one is free.  Cycles of a launch, 128 -> 256 channels at side 8, two segments of 6400
+  // samples: 1538k -> 1276k, 256 -> 512 at side 4 1391k -> 1146k (matrix pipe busy 0.50 -> 0.60 and 0.52 -> 0.63 of them).  The clock goes down with
+  // the power the pipe takes, 2.05 -> 1.8 GHz, which leaves 769 -> 688 and 701 -> 616 us; 512 -> 256 transposed, side 4, one segment 363 -> 331.
+  // Issuing the copies in front of the reads or between them, or at a raised wave priority: +-0.5 %.
   auto quad_loop = [&](auto) __attribute__((always_inline)) {      // (a template, so that only the tiles that call it compile it)
     clear_acc(acc);
     order.start();
@@ -1243,7 +1249,8 @@ __device__ inline int wgrad_model(const WgradArgs& p, int i) {
 // bf16: ds_read_b64_tr_b16 does the transposition on the way to the registers: within each block of 16 lanes, lane i
 // receives element i%4 of the 8-byte groups addressed by lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4; pointing lane s of a
 // block at row (s/4), channel group (s%4) therefore hands lane i rows 0..3 of channel i.
-// fp32: plain 4-byte reads of the tile as it lies, lane r of a half-wave channel r, eight rows a lane for one split step.
+// fp32: the chunk is split on the way into LDS (split_loop) and its bf16 planes are read like a bf16 chunk; only a tile that is computed
+// again with the fp32 MFMAs (infinities, NaN) has the chunk itself there and reads it four bytes at a time, lane r of a half-wave channel r.
 // The 16-byte chunk c of row R sits at position c ^ swz(R), so that the rows one read touches fall into different
 // bank groups.
 template <typename T> constexpr int wg_kr() { return 128 / (int)sizeof(T); }     // rows (reduction index) per chunk: 64 or 32

@@ -123,8 +123,9 @@ template void launch_point_fwd<bf16_t>(const PointArgs&, hipStream_t);
 // What bounds it is how many rows a block has on their way: a model's rows belong to one block (its sums do not depend on other models'
 // samples then), a hundred models of 64 channels are 200 blocks, and with 256 threads they left most of the chip's loads unused.
 // 64 rows of a sample, a hundred models of 64 samples in bf16, us with 256 and with 1024 threads: column sums (two segments) 68 and 27, statistics (one
-// segment) 55 and 25; 16 rows 20 and 11, 14 and 10.  Statistics of 4 rows: 7.5 and 11, so 256 threads there.  (Statistics that kept a lane's first
-// sixteen rows in registers between the passes: 62 registers spilled, 73 us for 61.)
+// segment) 55 and 25; 16 rows 20 and 11, 14 and 10.  Statistics of 4 rows: 7.5 and 11, so 256 threads there; column sums of 4 rows: 6.9 and 7.8,
+// but for one model of 150 samples 8.0 and 7.2, of 1000 samples 26 and 21, for eight of 100 7.7 and 6.1, so 1024.  (Statistics that kept a lane's
+// first sixteen rows in registers between the passes: 62 registers spilled, 73 us for 61.)
 // One row a sample (G's linear layer, whose 8192 columns are blocks enough): 256 threads.  The number follows from the layer's shape alone.
 constexpr int PS_CH = 32;                     // channels per block
 template <typename T> struct PsVec { static constexpr int N = 16 / (int)sizeof(T); };

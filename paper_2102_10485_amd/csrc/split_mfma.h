@@ -23,7 +23,8 @@ __device__ inline void mma16B(floatx16& acc, const uint4& a, const uint4& b, bf1
 // small values would cost the same and send them to the fp32 MFMAs).
 // Why: v_mfma_f32_32x32x2_f32 takes sixteen times the matrix-pipe time of the bf16 MFMA, six of which replace it.  Forward-type
 // kernel, 20 x 64 samples, 128 -> 256 channels at side 8: 100 TFLOP/s with the fp32 MFMAs, 157 when every block splits both
-// operands, 180 with the weights split once by the update that writes them; weight gradient of the same layer 95 and 152.  What bounds it now is
+// operands, 180 with the weights split once by the update that writes them; weight gradient of the same layer 95, 152 when every wave
+// splits what it multiplies, a tenth more with each chunk split once by its block (1035 -> 942 us).  What bounds the forward-type kernel now is
 // the matrix pipe (1.1 PFLOP/s of bf16) together with the 6.5 vector instructions that split a value of the rows and the loads (6 bytes a weight).
 // Error against 64-bit sums as a share of the fp32 MFMA's (64 .. 512 channels, sides 2 .. 16, six seeds each), 2-norm: 0.31-0.35 on normal
 // and on gradient-sized inputs, 0.16-0.40 on positive ones, 0.34-0.55 on inputs after a ReLU, 0.38-0.44 on inputs spread over many
