@@ -21,20 +21,20 @@ PEAK = {"mfma_bf16": 2500.0, "mfma_fp32": 2500.0 / 6, "hbm": 8000.0}
 # the same counters read for the 1 GiB elementwise probe (fetch x 2.0, write x 1.0).  Valid only for the kernel sources they
 # were taken with: `sources` is the digest of csrc/ at that time, and the roofline reports null traffic when it differs.
 MEASURED_TRAFFIC = {
-    "sources": "96db69e269425cfe",
+    "sources": "2e3eecddaf4a79b8",
     "workload": "config 2 bf16",
     "fetch_scale": 2.000, "write_scale": 1.000,
     "kib_per_launch": {
-        "gemm_dense<64x64>": (103274, 123227),
-        "gemm_up<256x256>": (462896, 275201),
-        "gemm_up<256x128>": (158340, 435200),
-        "gemm_dense+lrelu<256x128>": (154515, 614674),
-        "gemm_down<256x256>": (499557, 209600),
-        "wgrad<256x256>": (496001, 512055),
-        "gemm_up+actbwd<256x128>": (580557, 614400),
-        "wgrad<64x128>": (460883, 25607),
-        "gemm_dense<256x128>": (103313, 409910),
-        "wgrad<256x128>": (52090, 410086),
+        "gemm_dense<64x64>": (103269, 122591),
+        "gemm_up<256x256>": (459345, 275238),
+        "gemm_up<256x128>": (158402, 435200),
+        "gemm_dense+lrelu<256x128>": (154523, 614621),
+        "gemm_down<256x256>": (504764, 209601),
+        "wgrad<256x256>": (476166, 512101),
+        "gemm_up+actbwd<256x128>": (591148, 614400),
+        "wgrad<64x128>": (460881, 25605),
+        "gemm_dense<256x128>": (103307, 409868),
+        "wgrad<256x128>": (52088, 409945),
     },
 }
 
