@@ -27,14 +27,6 @@ namespace {
 
 inline long long round_up(long long x, long long m) { return (x + m - 1) / m * m; }
 
-// Widest patch matrix of D's first convolution that carries the label maps as indicator columns (see gan_create).  Step of one
-// pair, columns -> rows behind the GEMM when the rows were brought in, in us: 128 columns (28x28, 10 labels, 640 images) 747 -> 759, (32x32, 3 labels, 64) 982 ->
-// 992; 192 (32x32, 10 labels, 1000) 2755 -> 2726; 320 (25 labels, 200) 1310 -> 1260; 960 (100 labels, 64) 1086 -> 999, (1000) 3336 -> 2721.
-constexpr int LABEL_COLUMNS = 128;
-// the weight gradient of a patch-matrix layer has a tiny output and a long reduction: its rows are split over this
-// many blocks per model, and the partial blocks are added in a fixed order when they are unpacked.
-// 8 when there are many models, more when the models alone would leave most of the chip idle.  A function of the model count only.
-static int img_ksplit_for(int L) { return std::min(std::max(800 / L, 8), 128); }
 constexpr int WG_MAX_KSPLIT = 64;
 
 // A (transposed) convolution between a "big" tensor (Cb channels, side 2*Hs) and a "small" one (Cs, side Hs).
@@ -95,20 +87,17 @@ struct gan_ctx {
   std::vector<void*> gpre, gact, dpre, dact;
   std::vector<float*> g_mean, g_var, g_rstd, g_sums, d_mean, d_var, d_rstd, d_sums;
   float *logits = nullptr, *dlogits = nullptr, *loss_d = nullptr, *loss_g = nullptr;
-  // image-side layers: patch matrices, packed weights, packed weight gradients
-  void *colD = nullptr, *colG = nullptr, *wpD = nullptr, *wpG = nullptr;
-  float *dwp = nullptr, *bias_partial = nullptr, *stat_partial = nullptr;
-  int img_ksplit = 8;
+  // image-side layers: packed weights (and what the label maps and the bias add, by position class), partial weight gradients
+  void *wpD = nullptr, *wpG = nullptr;
+  float *addD = nullptr, *img_part = nullptr, *img_sums = nullptr, *bias_partial = nullptr, *stat_partial = nullptr;
+  int img_tile = 1;                // samples of a tile of their weight gradients
   float* head_part = nullptr;      // row-split partial sums of the linear head's weight gradient (few models only)
   int head_rsplit = 1;
   float* wg_part = nullptr;        // row-split partial weight gradients (few models only)
   bool paper = false;              // the networks as printed in the paper's tables
   bool presplit = false;           // fp32 storage: the convolutions on the GEMM engine read weights that the update has split (see presplit_pays)
   float *dw4 = nullptr, *c3_part = nullptr;   // paper G: k4 weight gradient of one block; row-split partials of the last conv
-  int KcD = 0, KcG = 0;
-  int nslot = 1;              // class-indicator slots in the patch matrix of D's first conv
-  int labels = 0;             // > 0: the label maps are added as rows behind that GEMM instead (one pair over many labels)
-  void* label_rows = nullptr;
+  int labels = 0;             // > 0: one pair over that many labels, whose maps' gradients come from class sums
   float *label_sums = nullptr, *class_part = nullptr;
   int last_n = -1;
   bool shadows_dirty = true;
@@ -249,6 +238,7 @@ void order_after(gan_ctx* c, hipStream_t later, hipStream_t earlier) {
 }
 
 template <typename T> void adam_region_call(gan_ctx* c, const AdamArgs& a, int region, hipStream_t st);
+template <typename T> void pack_image_call(gan_ctx* c, const Net& net);
 
 double valid_tap_fraction(int Hs) {   // k4 s2 p1: per axis 2 of the 4*Hs (row, tap) pairs fall outside
   const double f = (4.0 * Hs - 2.0) / (4.0 * Hs);
@@ -565,13 +555,10 @@ bool builtin_init_paper(gan_ctx* c) {
 }
 
 // ---- storage-type copies of the weights ------------------------------------------------------------------
-PackArgs pack_args(gan_ctx* c, Net& net, const ConvLayer& cl, int Kc, int nslot, void* wp);
 
 template <typename T>
-void refresh_transposes(gan_ctx* c, Net& n, bool isG) {
-  // the image-side layer multiplies a patch matrix: [cs][Kc] with the label-map sums and the bias folded in
-  if (isG) launch_pack_w<T>(pack_args(c, n, n.conv.back(), c->KcG, 0, c->wpG), c->st);
-  else launch_pack_w<T>(pack_args(c, n, n.conv.front(), c->KcD, c->nslot, c->wpD), c->st);
+void refresh_transposes(gan_ctx* c, Net& n) {
+  pack_image_call<T>(c, n);                             // the image-side layer
   // layers run by the GEMM engine in "down" form need [tap][cs][cb]
   for (size_t i = 0; i < n.conv.size(); ++i) {
     const ConvLayer& cl = n.conv[i];
@@ -602,7 +589,7 @@ void refresh_shadows(gan_ctx* c) {
       if (c->bf16) paper_rebuild_w4<bf16_t>(c); else paper_rebuild_w4<float>(c);
       continue;
     }
-    if (c->bf16) refresh_transposes<bf16_t>(c, *n, n == &c->G); else refresh_transposes<float>(c, *n, n == &c->G);
+    if (c->bf16) refresh_transposes<bf16_t>(c, *n); else refresh_transposes<float>(c, *n);
   }
   c->shadows_dirty = false;
 }
@@ -648,7 +635,6 @@ void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, c
   if (epi == EPI_BIAS_ACT) { a.bn_bias = bias; a.bn_pstride = known->pstride; a.slope = 0.f; }
   if (epi == EPI_DROP_BWD) a.drop_scale = 1.0f / (1.0f - c->cfg.dropout_p);
   a.stat_partial = stats ? c->stat_partial : nullptr;
-  if (epi == EPI_LABEL_LRELU) { a.label_rows = c->label_rows; a.sample_slot = c->rb.sample_slot; }
   const int ntaps = mode == MODE_DOWN ? 16 : (mode == MODE_UP ? 4 : 1);
   const int phases = mode == MODE_UP ? 4 : 1;
   const double rows = (double)n * nseg * Hr * Hr * phases;
@@ -775,18 +761,6 @@ double img_flops(const ConvLayer& cl, int n, int nseg) {
   return 2.0 * n * nseg * cl.Hs * cl.Hs * 16 * cl.Cb * cl.Cs * valid_tap_fraction(cl.Hs);
 }
 
-// Patch matrix of an image-side tensor (or of the caller's real batch when img == NULL).
-template <typename T>
-void im2col_call(gan_ctx* c, const ConvLayer& cl, const void* img, const float* real, void* out, int Kc, int nslot, int seg, int n) {
-  Im2colArgs a;
-  memset(&a, 0, sizeof(a));
-  a.img = img; a.real = real; a.perm = c->rb.perm; a.out = out; a.offs = c->rb.offs; a.sample_slot = c->rb.sample_slot;
-  a.L = c->L; a.n = n; a.CB = cl.Cb; a.Hs = cl.Hs; a.Kc = Kc; a.nslot = nslot; a.constant = &cl == &c->D.conv[0]; a.seg = seg; a.seg_samples = n;
-  const double rows = (double)n * cl.Hs * cl.Hs;
-  Scope s(c, "im2col", 0, rows * (4.0 * cl.Cb * (real ? 4 : sizeof(T)) + (double)Kc * sizeof(T)));
-  launch_im2col<T>(a, c->st);
-}
-
 // transposed conv onto the image side: feat (absolute segment seg) -> out (same segment indexing), or the caller's images
 template <typename T>
 void up_img_call(gan_ctx* c, Net& net, const ConvLayer& cl, const void* feat, void* out, const void* aux, int mode, int seg, int n,
@@ -801,16 +775,58 @@ void up_img_call(gan_ctx* c, Net& net, const ConvLayer& cl, const void* feat, vo
   launch_up_img<T>(a, c->st);
 }
 
-PackArgs pack_args(gan_ctx* c, Net& net, const ConvLayer& cl, int Kc, int nslot, void* wp) {
-  PackArgs a;
-  memset(&a, 0, sizeof(a));
-  const bool first = &cl == &c->D.conv[0];       // the constant column carries D's first bias
-  a.w = net.theta + cl.w; a.bias = (first && cl.bias >= 0) ? net.theta + cl.bias : nullptr;
-  a.dw = net.g + cl.w; a.dbias = (first && cl.bias >= 0) ? net.g + cl.bias : nullptr;
-  if (first) { a.labels = c->labels; a.label_rows = c->label_rows; a.label_sums = c->label_sums; }
-  a.pstride = net.P; a.wp = wp; a.dwp = c->dwp;
-  a.L = c->L; a.CB = cl.Cb; a.CBT = cl.CBT; a.Cs = cl.Cs; a.Kc = Kc; a.nslot = nslot; a.nsplit = c->img_ksplit;
-  return a;
+// packed weights of an image-side layer
+template <typename T>
+void pack_image_call(gan_ctx* c, const Net& net) {
+  const bool first = &net == &c->D;                 // (G's last layer: as its gradients read it)
+  const ConvLayer& cl = first ? net.conv.front() : net.conv.back();
+  ImagePackArgs a = {};
+  a.w = net.theta + cl.w; a.bias = first ? net.theta + cl.bias : nullptr; a.packed = first ? c->wpD : c->wpG; a.add = first ? c->addD : nullptr;
+  a.pstride = net.P; a.L = c->L; a.CB = cl.Cb; a.CBT = cl.CBT; a.Cs = cl.Cs; a.P = image_values(cl.Cb); a.tables = c->labels > 0 ? c->labels : c->L;
+  Scope s(c, "pack_w", 0, (double)c->L * cl.Cs * 16 * (4.0 * cl.CBT + a.P * sizeof(T)));
+  launch_pack_image_w<T>(a, c->st);
+}
+// The strided convolution of images: D's first layer (label maps, bias, LeakyReLU), or with `grad` the data gradient of G's last layer from
+// the gradient of its images.  real: the caller's batch in place of segment 0.
+template <typename T>
+void image_conv_call(gan_ctx* c, const ConvLayer& cl, const void* img, const float* real, void* out, bool grad, int seg_first, int nseg, int n) {
+  ImageConvArgs a = {};
+  a.img = img; a.real = real; a.perm = c->rb.perm; a.w = grad ? c->wpG : c->wpD; a.add = grad ? nullptr : c->addD;
+  a.sample_slot = !grad && c->labels > 0 ? c->rb.sample_slot : nullptr;
+  a.out = out; a.offs = c->rb.offs; a.sample_model = c->rb.sample_model;
+  a.L = c->L; a.n = n; a.CB = cl.Cb; a.Hs = cl.Hs; a.Cs = cl.Cs; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n;
+  a.slope = grad ? 1.f : c->cfg.leaky_slope;
+  const double rows = (double)n * nseg * cl.Hs * cl.Hs;
+  Scope s(c, grad ? "gemm_image_grad" : "gemm_image", img_flops(cl, n, nseg), sizeof(T) * rows * (4.0 * cl.Cb + cl.Cs));
+  launch_image_conv<T>(a, c->st);
+}
+// Its weight gradient, into the network's gradient block: the taps, the label maps and the bias of D's first layer, the taps and the bias of G's last.
+template <typename T>
+void image_wgrad_call(gan_ctx* c, Net& net, const ConvLayer& cl, const void* img, const float* real, const void* dy, int seg_first, int nseg, int n) {
+  const bool first = &net == &c->D;
+  ImageWgradArgs a = {};
+  a.img = img; a.real = real; a.perm = c->rb.perm; a.dy = dy; a.part = c->img_part; a.pixel_sums = first ? nullptr : c->img_sums;
+  a.offs = c->rb.offs; a.tpre = tpre_of(c, 1, c->img_tile); a.tmodel = tmodel_of(c, 1, c->img_tile);
+  a.L = c->L; a.CB = cl.Cb; a.Hs = cl.Hs; a.Cs = cl.Cs; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n; a.tile_samples = c->img_tile;
+  const double rows = (double)n * nseg * cl.Hs * cl.Hs;
+  {
+    Scope s(c, "wgrad_image", img_flops(cl, n, nseg), sizeof(T) * rows * (4.0 * cl.Cb + cl.Cs));
+    launch_image_wgrad<T>(a, ub_tiles(c, n, 1, c->img_tile), c->st);
+  }
+  if (first && c->labels > 0) {
+    ClassSumArgs b;
+    memset(&b, 0, sizeof(b));
+    b.dy = dy; b.part = c->class_part; b.sums = c->label_sums; b.offs = c->rb.offs; b.sample_slot = c->rb.sample_slot;
+    b.L = c->L; b.n = n; b.Hs = cl.Hs; b.Cs = cl.Cs; b.labels = c->labels; b.seg_first = seg_first; b.nseg = nseg; b.seg_samples = n;
+    Scope s(c, "class_sums", 0, rows * cl.Cs * sizeof(T));
+    launch_class_sums<T>(b, c->st);
+  }
+  ImageGradArgs g = {};
+  g.part = c->img_part; g.pixel_sums = a.pixel_sums; g.tpre = a.tpre; g.dw = net.g + cl.w;
+  g.dbias = first ? net.g + cl.bias : nullptr; g.image_bias = first ? nullptr : net.g + cl.bias;
+  g.labels = first ? c->labels : 0; g.label_sums = c->label_sums; g.plane_labels = first && cl.CBT > cl.Cb && c->labels == 0;
+  g.pstride = net.P; g.L = c->L; g.CB = cl.Cb; g.CBT = cl.CBT; g.Cs = cl.Cs; g.P = image_values(cl.Cb);
+  launch_image_wgrad_final(g, c->st);
 }
 
 // A pass through D belongs to one of the two costs, and that says which segments it runs over.
@@ -864,14 +880,11 @@ void g_forward(gan_ctx* c, int n, bool use_running, bool update_running, float* 
 }
 
 template <typename T>
-void d_forward(gan_ctx* c, int n, Cost cost, bool update_running) {
+void d_forward(gan_ctx* c, int n, Cost cost, bool update_running, const float* real = nullptr) {
   Net& D = c->D;
   const int seg_first = segments_of(cost).first, nseg = segments_of(cost).count;
   const float slope = c->cfg.leaky_slope;
-  // first conv (+label maps, bias, LeakyReLU) as a row-by-row GEMM over the patch matrix
-  const ConvLayer& c1 = D.conv[0];
-  conv_call<T>(c, "gemm_dense_img", MODE_DENSE, c->labels > 0 ? EPI_LABEL_LRELU : EPI_LRELU, c->colD, Weights{c->wpD, (long long)c1.Cs * c->KcD},
-               c->dact[0], nullptr, c->KcD, c1.Cs, 1, c1.Hs, seg_first, nseg, n, 0, img_flops(c1, n, nseg));
+  image_conv_call<T>(c, D.conv[0], c->xd, real, c->dact[0], false, seg_first, nseg, n);      // first conv (+label maps, bias, LeakyReLU)
   const int nl = (int)D.conv.size();
   for (int j = 1; j < nl; ++j) {
     const ConvLayer& cl = D.conv[j];
@@ -891,7 +904,7 @@ void d_forward(gan_ctx* c, int n, Cost cost, bool update_running) {
 // every part of it; the update of a convolution's weights is enqueued beside the chain as soon as its gradient is complete and its
 // data gradient has read the old ones.
 template <typename T>
-void d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_image, const AdamArgs* adam = nullptr) {
+void d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_image, const float* real = nullptr, const AdamArgs* adam = nullptr) {
   Net& D = c->D;
   const int seg_first = segments_of(cost).first, nseg = segments_of(cost).count;
   hipStream_t side = side_stream(c);
@@ -926,20 +939,7 @@ void d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_image, c
     adam_region_call<T>(c, *adam, pending, side);
   }
   const ConvLayer& c1 = D.conv[0];
-  if (param_grads) {
-    // taps, the bias gradient and (as indicator columns) the label maps' class sums in one GEMM over the patch matrix
-    wgrad_call<T>(c, "gemm_wgrad_img", c->colD, c->bufA, c->dwp, (long long)c->KcD * c1.Cs, c->KcD, c1.Cs, c1.Hs, 1, nseg, n,
-                  img_flops(c1, n, nseg), c->img_ksplit);
-    if (c->labels > 0) {
-      ClassSumArgs a;
-      memset(&a, 0, sizeof(a));
-      a.dy = c->bufA; a.part = c->class_part; a.sums = c->label_sums; a.offs = c->rb.offs; a.sample_slot = c->rb.sample_slot;
-      a.L = c->L; a.n = n; a.Hs = c1.Hs; a.Cs = c1.Cs; a.labels = c->labels; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n;
-      Scope s(c, "class_sums", 0, (double)n * nseg * c1.Hs * c1.Hs * c1.Cs * sizeof(T));
-      launch_class_sums<T>(a, c->st);
-    }
-    launch_unpack_dw(pack_args(c, D, c1, c->KcD, c->nslot, c->wpD), c->st);
-  }
+  if (param_grads) image_wgrad_call<T>(c, D, c1, c->xd, real, c->bufA, seg_first, nseg, n);
   if (to_image)   // d cost / d fake, times the tanh derivative (fake segment only)
     up_img_call<T>(c, D, c1, c->bufA, c->dimg, c->xd, 2, 1, n);
 }
@@ -952,18 +952,8 @@ void g_backward(gan_ctx* c, int n, const AdamArgs* adam = nullptr) {
   const int nl = (int)G.conv.size();
   const ConvLayer& last = G.conv[nl - 1];
   const T* dlast = (const T*)c->dimg + (long long)n * 4 * last.Hs * last.Hs * last.Cb;
-  {
-    im2col_call<T>(c, last, dlast, nullptr, c->colG, c->KcG, 0, 0, n);
-    wgrad_call<T>(c, "gemm_wgrad_img", c->colG, c->gact[nl - 1], c->dwp, (long long)c->KcG * last.Cs, c->KcG, last.Cs, last.Hs, 1, 1, n,
-                  img_flops(last, n, 1), c->img_ksplit);
-    launch_unpack_dw(pack_args(c, G, last, c->KcG, 0, c->wpG), c->st);
-    ImgBiasArgs b;
-    b.img = dlast; b.partial = c->bias_partial; b.dbias = G.g + last.bias; b.pstride = G.P; b.offs = c->rb.offs;
-    b.L = c->L; b.CB = last.Cb; b.HW = 4 * last.Hs * last.Hs;
-    launch_img_bias_grad<T>(b, c->st);
-    conv_call<T>(c, "gemm_dense_img", MODE_DENSE, EPI_NONE, c->colG, Weights{c->wpG, (long long)last.Cs * c->KcG}, c->bufA, nullptr, c->KcG,
-                 last.Cs, 1, last.Hs, 0, 1, n, 0, img_flops(last, n, 1));
-  }
+  image_wgrad_call<T>(c, G, last, dlast, nullptr, c->gact[nl - 1], 0, 1, n);
+  image_conv_call<T>(c, last, dlast, nullptr, c->bufA, true, 0, 1, n);
   int pending = -1;
   for (int i = nl - 2; i >= 0; --i) {
     const ConvLayer& cl = G.conv[i];
@@ -1062,13 +1052,12 @@ void paper_g_forward(gan_ctx* c, int n, bool use_running, bool update_running, f
 // pass0: dropout pass id of the first processed segment (real 0, fake 1, fake through the updated D 2);
 // step_add: 1 before D's update of this iteration, 0 after it (the iteration number is D's step count + step_add)
 template <typename T>
-void paper_d_forward(gan_ctx* c, int n, Cost cost, bool update_running, int pass0, int step_add) {
+void paper_d_forward(gan_ctx* c, int n, Cost cost, bool update_running, int pass0, int step_add, const float* real = nullptr) {
   Net& D = c->D;
   const int seg_first = segments_of(cost).first, nseg = segments_of(cost).count;
   const gan_config& f = c->cfg;
   const ConvLayer& c1 = D.conv[0];
-  conv_call<T>(c, "gemm_dense_img", MODE_DENSE, EPI_LRELU, c->colD, Weights{c->wpD, (long long)c1.Cs * c->KcD}, c->dact[0], nullptr, c->KcD,
-               c1.Cs, 1, c1.Hs, seg_first, nseg, n, 0, img_flops(c1, n, nseg));
+  image_conv_call<T>(c, c1, c->xd, real, c->dact[0], false, seg_first, nseg, n);
   if (f.dropout_p > 0.f) {
     PointArgs a = point_args(c, c->dact[0], c1.cs_real, c1.Cs, c1.Hs * c1.Hs, seg_first, nseg, n);
     with_dropout(c, a, 1, pass0, step_add);
@@ -1093,7 +1082,7 @@ void paper_d_forward(gan_ctx* c, int n, Cost cost, bool update_running, int pass
 }
 
 template <typename T>
-void paper_d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_image) {
+void paper_d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_image, const float* real = nullptr) {
   Net& D = c->D;
   const int seg_first = segments_of(cost).first, nseg = segments_of(cost).count;
   const gan_config& f = c->cfg;
@@ -1120,9 +1109,7 @@ void paper_d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_im
   }
   const ConvLayer& c1 = D.conv[0];
   if (param_grads) {
-    wgrad_call<T>(c, "gemm_wgrad_img", c->colD, c->bufA, c->dwp, (long long)c->KcD * c1.Cs, c->KcD, c1.Cs, c1.Hs, 1, nseg, n,
-                  img_flops(c1, n, nseg), c->img_ksplit);
-    launch_unpack_dw(pack_args(c, D, c1, c->KcD, c->nslot, c->wpD), c->st);
+    image_wgrad_call<T>(c, D, c1, c->xd, real, c->bufA, seg_first, nseg, n);
     for (const ConvLayer& cl : D.conv) launch_clear_fourth_taps(D.g + cl.w, D.P, c->L, cl.CBT, cl.Cs, c->st);
   }
   if (to_image) up_img_call<T>(c, D, c1, c->bufA, c->dimg, c->xd, 2, 1, n);
@@ -1230,44 +1217,37 @@ void adam_region_call(gan_ctx* c, const AdamArgs& a, int region, hipStream_t st)
 // what is left of a planned update once the regions are done (or enqueued beside): the gaps, and the packed weights of
 // the image-side layer, rebuilt from the new master weights
 template <typename T>
-void adam_rest_call(gan_ctx* c, Net& net, bool isG, const AdamArgs& a) {
+void adam_rest_call(gan_ctx* c, Net& net, const AdamArgs& a) {
   {
     double elems = 0;
     for (int r = 0; r < a.ngaps; ++r) elems += (double)(a.gap_hi[r] - a.gap_lo[r]);
     Scope s(c, "adam", 0, (double)c->L * elems * adam_bytes_per_element(c));
     launch_adam_gaps(a, c->st);
   }
-  // (with the rows of the label maps, one pair over many labels)
-  const PackArgs pk = isG ? pack_args(c, net, net.conv.back(), c->KcG, 0, c->wpG) : pack_args(c, net, net.conv.front(), c->KcD, c->nslot, c->wpD);
-  Scope s(c, "pack_w", 0, (double)c->L * pk.Cs * pk.Kc * (4.0 + sizeof(T)) + (double)pk.labels * pk.Cs * (64.0 + 9 * sizeof(T)));
-  launch_pack_w<T>(pk, c->st);
+  pack_image_call<T>(c, net);
 }
 // the whole update on the caller's stream
 template <typename T>
-void adam_call(gan_ctx* c, Net& net, bool isG) {
+void adam_call(gan_ctx* c, Net& net) {
   const AdamArgs a = adam_args<T>(c, net);
   adam_region_call<T>(c, a, -1, c->st);
-  adam_rest_call<T>(c, net, isG, a);
+  adam_rest_call<T>(c, net, a);
 }
 
 template <typename T>
-void route_and_stage(gan_ctx* c, const int32_t* label_ids, const float* noise, const float* real, int n) {
-  {
-    Scope s(c, "stage", 0, (double)n * c->cfg.z_dim * (4.0 + sizeof(T)));
-    launch_route_stage<T>(label_ids, noise, n, c->L, c->cfg.n_labels, c->cfg.z_dim, c->cfg.cond_g, c->G.Kp, c->geoms, c->rb, (T*)c->zin, c->st);
-  }
-  if (real) im2col_call<T>(c, c->D.conv[0], nullptr, real, c->colD, c->KcD, c->nslot, 0, n);   // the real half of D's input
+void route_and_stage(gan_ctx* c, const int32_t* label_ids, const float* noise, int n) {
+  Scope s(c, "stage", 0, (double)n * c->cfg.z_dim * (4.0 + sizeof(T)));
+  launch_route_stage<T>(label_ids, noise, n, c->L, c->cfg.n_labels, c->cfg.z_dim, c->cfg.cond_g, c->G.Kp, c->geoms, c->rb, (T*)c->zin, c->st);
 }
 
 template <typename T>
 void paper_train_step(gan_ctx* c, const int32_t* label_ids, const float* noise, const float* real, int n) {
   if (c->shadows_dirty) refresh_shadows(c);
-  route_and_stage<T>(c, label_ids, noise, real, n);
+  route_and_stage<T>(c, label_ids, noise, n);
   paper_g_forward<T>(c, n, false, true);                               // fake = G(z)
-  im2col_call<T>(c, c->D.conv[0], c->xd, nullptr, c->colD, c->KcD, c->nslot, 1, n);
-  paper_d_forward<T>(c, n, COST_D, true, 0, 1);                        // D(real), D(fake): dropout passes 0 and 1
-  paper_d_backward<T>(c, n, COST_D, true, false);                      // Eq. 3
-  adam_call<T>(c, c->D, false);
+  paper_d_forward<T>(c, n, COST_D, true, 0, 1, real);                   // D(real), D(fake): dropout passes 0 and 1
+  paper_d_backward<T>(c, n, COST_D, true, false, real);                 // Eq. 3
+  adam_call<T>(c, c->D);
   paper_d_forward<T>(c, n, COST_G, true, 2, 0);                        // updated D on the same fake batch: pass 2
   paper_d_backward<T>(c, n, COST_G, false, true);                      // Eq. 4 (negated: minimised)
   paper_g_backward<T>(c, n);
@@ -1278,15 +1258,14 @@ template <typename T>
 void train_step(gan_ctx* c, const int32_t* label_ids, const float* noise, const float* real, int n) {
   if (c->paper) return paper_train_step<T>(c, label_ids, noise, real, n);
   if (c->shadows_dirty) refresh_shadows(c);
-  route_and_stage<T>(c, label_ids, noise, real, n);
+  route_and_stage<T>(c, label_ids, noise, n);
   g_forward<T>(c, n, false, true);                 // fake = G(z)
-  im2col_call<T>(c, c->D.conv[0], c->xd, nullptr, c->colD, c->KcD, c->nslot, 1, n);   // the fake half of D's input
-  d_forward<T>(c, n, COST_D, true);                // D(real), D(fake): separate batch statistics per segment
+  d_forward<T>(c, n, COST_D, true, real);              // D(real), D(fake): separate batch statistics per segment
   c->order_next = 0;
   {
     const AdamArgs aD = adam_args<T>(c, c->D);
-    d_backward<T>(c, n, COST_D, true, false, &aD); // Eq. 3; weight gradients and the convolutions' updates beside the chain
-    adam_rest_call<T>(c, c->D, false, aD);
+    d_backward<T>(c, n, COST_D, true, false, real, &aD); // Eq. 3; weight gradients and the convolutions' updates beside the chain
+    adam_rest_call<T>(c, c->D, aD);
     order_after(c, c->st, side_stream(c));
   }
   d_forward<T>(c, n, COST_G, true);                // updated D on the same fake batch
@@ -1294,7 +1273,7 @@ void train_step(gan_ctx* c, const int32_t* label_ids, const float* noise, const 
   {
     const AdamArgs aG = adam_args<T>(c, c->G);
     g_backward<T>(c, n, &aG);
-    adam_rest_call<T>(c, c->G, true, aG);
+    adam_rest_call<T>(c, c->G, aG);
     order_after(c, c->st, side_stream(c));
   }
 }
@@ -1351,7 +1330,6 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
   c->st = (hipStream_t)hip_stream;
   c->bf16 = cfg->precision == GAN_BF16_FP32MASTER;
   c->L = cfg->n_models; c->NB = cfg->max_total_batch;
-  c->nslot = (cfg->cond_d > 0 && c->L == 1) ? cfg->cond_d : 1;
   c->geoms.n = 0;
   c->paper = cfg->family == GAN_FAMILY_PAPER;
   if (c->paper) build_layout_paper(c); else build_layout(c);
@@ -1363,22 +1341,20 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
   {
     auto reg = [&](int rps, int tile_rows) { if (geom_id(c, rps, tile_rows) < 0) ok = false; };
     auto reg_gemm = [&](int mode, int n_out, int rps, int nseg) { reg(rps, conv_tile_rows((int)es, layer_tile(c, mode, n_out, rps, nseg))); };
-    const ConvLayer& gl = c->G.conv.back();
-    const ConvLayer& d1 = c->D.conv.front();
     reg_gemm(MODE_DENSE, c->G.J, 1, 1);                                         // G's linear layer
     for (size_t i = 0; i + 1 < c->G.conv.size(); ++i) {
       const ConvLayer& cl = c->G.conv[i];
       reg_gemm(MODE_UP, cl.Cb, cl.Hs * cl.Hs, 1);                               // forward
       reg_gemm(MODE_DOWN, cl.Cs, cl.Hs * cl.Hs, 1);                             // data gradient
     }
-    reg_gemm(MODE_DENSE, gl.Cs, gl.Hs * gl.Hs, 1);                              // G's last layer: its data gradient (patch GEMM)
+    c->img_tile = image_tile_samples((int)es, NB);
+    reg(1, c->img_tile);                                                        // the weight gradients of the image-side layers
     for (int nseg = 1; nseg <= 2; ++nseg) {                                     // D runs on one segment and on both
       for (size_t j = 1; j < c->D.conv.size(); ++j) {
         const ConvLayer& cl = c->D.conv[j];
         reg_gemm(MODE_DOWN, cl.Cs, cl.Hs * cl.Hs, nseg);                        // forward
         reg_gemm(MODE_UP, cl.Cb, cl.Hs * cl.Hs, nseg);                          // data gradient
       }
-      reg_gemm(MODE_DENSE, d1.Cs, d1.Hs * d1.Hs, nseg);                         // first conv (patch GEMM)
     }
     // row space of every BatchNorm, in the row blocks of its backward reduction
     auto reg_bn = [&](int rps) { reg(rps, red_rows(c, rps)); };
@@ -1474,23 +1450,15 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
   {
     const ConvLayer& c1 = c->D.conv[0];
     const ConvLayer& gl = c->G.conv.back();
-    c->img_ksplit = img_ksplit_for(L);
-    // One pair over many labels: indicator columns for every (label, class) make the patch matrix wide -- written, read by the
-    // GEMM twice and by the weight gradient, nearly all of it zeros.  Beyond LABEL_COLUMNS the maps are added as rows in the
-    // GEMM's epilogue, and their gradient comes from class sums.
-    if (c->nslot > 1 && round_up(16 * c1.Cb + 9 * c->nslot + 1, 64) > LABEL_COLUMNS) {
-      c->labels = c->nslot;
-      c->nslot = 0;
-      ok = ok && dev_alloc(c, &c->label_rows, (size_t)c->labels * 9 * c1.Cs * es) && dev_alloc(c, (void**)&c->label_sums, (size_t)c->labels * 9 * c1.Cs * 4) &&
-           dev_alloc(c, (void**)&c->class_part, (size_t)2 * NB * 9 * c1.Cs * 4);
+    if (L == 1 && cfg->cond_d > 1) {
+      c->labels = cfg->cond_d;
+      ok = ok && dev_alloc(c, (void**)&c->label_sums, (size_t)c->labels * 9 * c1.Cs * 4) && dev_alloc(c, (void**)&c->class_part, (size_t)2 * NB * 9 * c1.Cs * 4);
     }
-    c->KcD = (int)round_up(16 * c1.Cb + 9 * c->nslot + 1, 64);
-    c->KcG = (int)round_up(16 * gl.Cb, 64);
-    const size_t d1 = (size_t)c->KcD * c1.Cs, g1 = (size_t)c->KcG * gl.Cs;
-    ok = ok && dev_alloc(c, &c->colD, (size_t)2 * NB * c1.Hs * c1.Hs * c->KcD * es) &&
-         dev_alloc(c, &c->colG, c->paper ? 16 : (size_t)NB * gl.Hs * gl.Hs * c->KcG * es) && dev_alloc(c, &c->wpD, (size_t)L * d1 * es) &&
-         dev_alloc(c, &c->wpG, (size_t)L * g1 * es) && dev_alloc(c, (void**)&c->dwp, (size_t)c->img_ksplit * L * (d1 > g1 ? d1 : g1) * 4) &&
-         dev_alloc(c, (void**)&c->bias_partial, (size_t)L * img_bias_chunks(L) * 4 * 4);
+    const size_t d1 = (size_t)16 * image_values(c1.Cb) * c1.Cs, g1 = c->paper ? 0 : (size_t)16 * image_values(gl.Cb) * gl.Cs, tiles = ub_tiles(c, NB, 1, c->img_tile);
+    ok = ok && dev_alloc(c, &c->wpD, (size_t)L * d1 * es) && dev_alloc(c, &c->wpG, (size_t)L * g1 * es) &&
+         dev_alloc(c, (void**)&c->addD, (size_t)(c->labels > 0 ? c->labels : L) * 9 * c1.Cs * 4) &&
+         dev_alloc(c, (void**)&c->img_part, tiles * std::max(d1, g1) * 4) && dev_alloc(c, (void**)&c->img_sums, tiles * 4 * 4) &&
+         dev_alloc(c, (void**)&c->bias_partial, c->paper ? (size_t)L * img_bias_chunks(L) * 4 * 4 : 0);
   }
   {
     // partial blocks of the weight gradients that are split over rows (few models only)
@@ -1518,14 +1486,14 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
     if (c->head_rsplit > 1) ok = ok && dev_alloc(c, (void**)&c->head_part, (size_t)c->head_rsplit * L * (c->D.K + 4) * 4);
   }
   {
-    // the GEMM loaders address one segment of any activation tensor or patch matrix with 32-bit byte offsets.  Where the label maps are
-    // rows behind the GEMM the patch matrix is counted with their columns all the same: which batches a configuration takes depends on
-    // its shapes alone, not on the way the label maps are held.
+    // the GEMM loaders address one segment of any activation tensor with 32-bit byte offsets.  The image-side layers count with 16 columns an
+    // image channel and 9 a label of one pair, in lines of 64: which batches a configuration takes follows from its shapes alone, not from
+    // the way those layers are computed.
     const ConvLayer& c1 = c->D.conv[0];
     const ConvLayer& gl = c->G.conv.back();
-    const long long lim = 1LL << 31;
-    const long long big = std::max({(long long)NB * max_act * (long long)es, (long long)NB * c1.Hs * c1.Hs * round_up(16 * c1.Cb + 9 * (c->labels + c->nslot) + 1, 64) * (long long)es,
-                                    c->paper ? 0LL : (long long)NB * gl.Hs * gl.Hs * c->KcG * (long long)es});
+    const long long lim = 1LL << 31, slots = cfg->cond_d > 0 && L == 1 ? cfg->cond_d : 1;
+    const long long big = std::max({(long long)NB * max_act * (long long)es, (long long)NB * c1.Hs * c1.Hs * round_up(16 * c1.Cb + 9 * slots + 1, 64) * (long long)es,
+                                    c->paper ? 0LL : (long long)NB * gl.Hs * gl.Hs * round_up(16 * gl.Cb, 64) * (long long)es});
     if (big >= lim) {
       for (void* p : c->allocs) (void)hipFree(p);
       delete c;
@@ -1687,11 +1655,11 @@ gan_status gan_generate(gan_ctx* c, const int32_t* label_ids, const float* noise
   const RouteBuffers train_rb = c->rb;         // the launch helpers read c->rb: point them at the generate set
   c->rb = c->rb_gen;
   if (c->bf16) {
-    route_and_stage<bf16_t>(c, label_ids, noise, nullptr, n);
+    route_and_stage<bf16_t>(c, label_ids, noise, n);
     if (c->paper) paper_g_forward<bf16_t>(c, n, use_running_stats != 0, false, out_images);
     else g_forward<bf16_t>(c, n, use_running_stats != 0, false, out_images);
   } else {
-    route_and_stage<float>(c, label_ids, noise, nullptr, n);
+    route_and_stage<float>(c, label_ids, noise, n);
     if (c->paper) paper_g_forward<float>(c, n, use_running_stats != 0, false, out_images);
     else g_forward<float>(c, n, use_running_stats != 0, false, out_images);
   }

@@ -59,7 +59,7 @@ const char* take_launch_error();   // the first reason recorded on this thread s
 
 // Block tiles of the forward-type GEMM kernel (rows x columns): conv_gemm.hip
 enum ConvTile { TILE_BIG = 0, TILE_MID = 1, TILE_SMALL = 2, TILE_NARROW = 3, TILE_TINY = 4, TILE_PAIR = 5, TILE_DEEP = 6 };
-enum Epilogue { EPI_NONE = 0, EPI_ACT_BWD = 1, EPI_LRELU = 2, EPI_LABEL_LRELU = 3, EPI_DROP_BWD = 4, EPI_BN = 5, EPI_BIAS_ACT = 6 };
+enum Epilogue { EPI_NONE = 0, EPI_ACT_BWD = 1, EPI_DROP_BWD = 2, EPI_BN = 3, EPI_BIAS_ACT = 4 };
 enum Act { ACT_RELU = 0, ACT_LRELU = 1 };
 
 // Arguments of the grouped implicit-GEMM forward-type kernel (down / up / dense).
@@ -73,9 +73,6 @@ struct ConvArgs {
   int raw_n, raw_k;
   void* Out;             // output activations (storage type)
   const void* Aux;       // EPI_ACT_BWD, EPI_DROP_BWD: saved forward output at the output position (storage type)
-  const void* label_rows;  // EPI_LABEL_LRELU: [9 * slot + position class][N] (storage type), added to the output rows of the pixels of
-                         // that class in the samples of that slot; slot of the j-th sample: sample_slot[j]
-  const int* sample_slot;
   float* stat_partial;   // if set: per sub-tile (the row block of one wave row of the tile; conv_stat_split of them per tile) the
                          // column sums of the output and of its squared deviations from the sub-tile's column mean,
                          // [(((phase * nseg + segment) * ub_tiles + tile) * split + block) * N + col][2], for the BatchNorm that follows
@@ -133,6 +130,9 @@ __device__ inline bool dropped(float saved) { return __float_as_uint(saved) == 0
 __device__ inline int pos_class(int y, int x, int Hs) {
   return (y == 0 ? 0 : (y == Hs - 1 ? 2 : 1)) * 3 + (x == 0 ? 0 : (x == Hs - 1 ? 2 : 1));
 }
+
+// Whether the tap k (one axis) of the pixels of class cls along it (0 first, 1 inner, 2 last) lies inside the map.
+__device__ inline bool tap_inside(int cls, int k) { return !((cls == 0 && k == 0) || (cls == 2 && k == 3)); }
 
 template <typename T> void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st);
 template <typename T> void launch_wgrad(const WgradArgs& a, hipStream_t st);

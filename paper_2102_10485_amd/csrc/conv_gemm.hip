@@ -6,7 +6,7 @@
 // Forward-type kernel (conv_gemm_kernel): C[row][n] = sum_{tap, c} A(row, tap)[c] * W[tap][n][c]
 //   down : rows are output pixels of the small tensor, 16 taps gathered from the big tensor at (2y-1+ky, 2x-1+kx)
 //   up   : rows are the pixels of one output phase (Y%2, X%2) of the big tensor, 4 taps gathered from the small one
-//   dense: one tap, rows are read directly (linear layer, patch-matrix layers)
+//   dense: one tap, rows are read directly (linear layer)
 // Weight-gradient kernel (wgrad_kernel): dW[tap][cb][cs] = sum_rows Big(row, tap)[cb] * Small(row)[cs]; the
 //   reduction index is the slow memory index of both operands: tiles go into LDS as they lie in memory, and the operand
 //   reads do the transposition.
@@ -28,6 +28,7 @@
 
 #include <algorithm>
 
+#include "lds_copy.h"
 #include "split_mfma.h"
 #include <type_traits>
 
@@ -87,7 +88,7 @@ template <> struct FwdTiles<bf16_t> {
 // tile; two blocks per CU.  20 x 64 samples, us: down 128 -> 256 channels, side 8: 128x128 with 32 x 128 wave tiles 435, 64 x 64 474,
 // 32 x 64 (eight waves) 445, 256x128 (eight waves, one block per CU) 490; up 256 -> 128, side 8: 438, 451, 455, 450; with weights split
 // by every wave 538 and 486 (64 x 64, the best then).  10 x 128 samples, up 128 -> 64, side 7: 128x64 108, 256x64 (one block per CU) 129, before 113.
-// The patch-matrix layers and G's linear one (MODE_DENSE), and convolutions of contexts whose weights the update does not split, read the weights as
+// G's linear layer (MODE_DENSE), and convolutions of contexts whose weights the update does not split, read the weights as
 // fp32 and split them too: 64 x 64 wave tiles there (SmallWhole).
 template <> struct FwdTiles<float> {
   typedef Tile<128, 128, 4, 1, 128, 2> Small;    // 256 threads, wave tile 32 x 128, 80 KiB of LDS
@@ -278,13 +279,6 @@ __device__ __forceinline__ void quad_wait() {
 // those of their second ones
 __device__ inline int quad_col(int R) { return ((R >> 5) & 3) * 64 + (R >> 7) * 32 + (R & 31); }
 
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
-}
 template <typename T, int TM, int TN, int KB>
 __device__ __forceinline__ void tile_mma_fwd(floatx16 (&acc)[TM][TN], const unsigned char* As, const unsigned char* Bs, int wm, int wn,
                                     int lane) {
@@ -369,42 +363,6 @@ __device__ __forceinline__ void tile_mma_split(floatx16 (&acc)[TM][TN], floatx16
   });
 }
 
-// 16 bytes per lane from a buffer straight into LDS: the wave's 64 lanes fill the 1 KiB starting at lds_base
-// (wave-uniform) in lane order; a lane whose byte offset lies outside the buffer (NO_ROW below) delivers zeros,
-// which is how padding taps, rows past a model's end and columns past N are filled.  Completion is counted by
-// vmcnt like any vector load.
-typedef int int4v __attribute__((ext_vector_type(4)));
-constexpr unsigned NO_ROW = 0xffffffffu;
-__device__ inline int4v make_rsrc(const void* base, unsigned long long bytes) {
-  const unsigned long long p = (unsigned long long)base;
-  int4v r;
-  r.x = __builtin_amdgcn_readfirstlane((int)(unsigned)p);
-  r.y = __builtin_amdgcn_readfirstlane((int)((unsigned)(p >> 32) & 0xffffu));                 // stride 0: raw buffer
-  r.z = __builtin_amdgcn_readfirstlane((int)(unsigned)(bytes > 0xfffffff0ull ? 0xfffffff0ull : bytes));
-  r.w = 0x00020000;
-  return r;
-}
-__device__ inline __amdgpu_buffer_rsrc_t buffer_of(const void* base, unsigned long long bytes) {      // the same for the load builtins
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)(unsigned)(bytes > 0xfffffff0ull ? 0xfffffff0ull : bytes), 0x00020000);
-}
-// The wave-uniform part of the offset (which tap, which channels) travels in a scalar register.
-__device__ inline void load16_to_lds(const int4v& rsrc, unsigned byte_off, unsigned uniform_off, unsigned lds_base) {
-  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-               : : "v"(byte_off), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane((int)uniform_off)), "s"(__builtin_amdgcn_readfirstlane((int)lds_base)) : "memory", "m0");
-}
-// The same with the LDS address as a scalar base and a constant, which then takes no register of its own.
-template <int LDS_OFF>
-__device__ inline void load16_to_lds_at(const int4v& rsrc, unsigned byte_off, unsigned uniform_off, int lds_base) {
-  asm volatile("s_add_u32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-               : : "v"(byte_off), "s"(rsrc), "s"(__builtin_amdgcn_readfirstlane((int)uniform_off)), "s"(lds_base), "n"(LDS_OFF) : "memory", "m0", "scc");
-}
-// wait until at most N loads are still in flight
-template <int N>
-__device__ inline void wait_vm() {
-  static_assert(N <= 63, "vmcnt range");
-  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
-
 __device__ inline void store_out(float* p, float v) { *p = v; }
 __device__ inline void store_out(bf16_t* p, float v) { *p = from_float<bf16_t>(v); }
 
@@ -460,7 +418,7 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   constexpr int A_RING = SHARE ? 2 * SLOTS * KB : NST * BM * KB;               // of one group
   constexpr int RING = A_RING + NST * BN * KBB;
   constexpr int SMEM_RING = KS * RING;
-  constexpr int ROWTAB = EPI == EPI_LABEL_LRELU ? BM * 12 : BM * 8;            // see the epilogue
+  constexpr int ROWTAB = BM * 8;                                               // see the epilogue
   constexpr int SMEM_EPI = ROWTAB + (TL::NT / 64) * 32 * (TN * 32 * 4 + 16);
   constexpr int SMEM = SMEM_RING > SMEM_EPI ? SMEM_RING : SMEM_EPI;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[SMEM];
@@ -941,18 +899,12 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
   }
   // ---- epilogue: output row index of every tile row, through LDS (the buffers are free now)
   long long* orow = reinterpret_cast<long long*>(smem);
-  int* lrow = reinterpret_cast<int*>(smem + BM * 8);                    // EPI_LABEL_LRELU: the row of label_rows it gets
   for (int t = tid; t < BM; t += TL::NT) {
     const int r = m0 + t;
     long long o = -1;
     if (r < Mrows) {
       if (MODE == MODE_DENSE) {
         o = sample_base * rps + r;
-        if (EPI == EPI_LABEL_LRELU) {
-          int n, y, x;
-          decode_row(r, Hr, rps, p.hr_shift, n, y, x);
-          lrow[t] = p.sample_slot[s0 + n] * 9 + pos_class(y, x, Hr);
-        }
       } else {
         int n, y, x;
         decode_row_yfirst(r, Hr, row_block, p.hr_shift, n, y, x);
@@ -1022,7 +974,6 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
         for (int e = 0; e < 16; ++e) {
           const int pr = (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
           float val = acc[tm][tn][e];
-          if (EPI == EPI_LRELU) val = val > 0.f ? val : val * p.slope;
           if constexpr (EPI == EPI_BIAS_ACT) {
             val = to_float(from_float<T>(val)) + bn_bi[tn];
             val = val > 0.f ? val : val * p.slope;
@@ -1051,16 +1002,6 @@ __global__ __launch_bounds__(TL::NT * TL::KS, (waves_per_simd<T, TL>())) void co
           for (int k = 0; k < EPV; k += 4) {
             const float4 t4 = *reinterpret_cast<const float4*>(patch + pr * PSTRIDE + (pc * EPV + k) * 4);
             vf[k] = t4.x; vf[k + 1] = t4.y; vf[k + 2] = t4.z; vf[k + 3] = t4.w;
-          }
-          if (EPI == EPI_LABEL_LRELU) {
-            const int lr = lrow[wm * TM * 32 + tm * 32 + pr];
-            const uint4 lraw = *reinterpret_cast<const uint4*>(static_cast<const T*>(p.label_rows) + (long long)lr * N + col);
-            const T* ll = reinterpret_cast<const T*>(&lraw);
-#pragma unroll
-            for (int k = 0; k < EPV; ++k) {
-              vf[k] += to_float(ll[k]);
-              if (!(vf[k] > 0.f)) vf[k] *= p.slope;
-            }
           }
           if constexpr (AUX) {      // times the activation's derivative (and the dropout), from the saved output
             const T* aa = reinterpret_cast<const T*>(&aux[i]);
@@ -1191,7 +1132,7 @@ template <typename T>
 void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
   // the kernel's assumptions, checked before anything is launched
   if (!a.A || !a.W || !a.Out || !a.offs || !a.tpre || a.N < 1 || a.w_nstride < a.N || a.C % (128 / (int)sizeof(T)) != 0 ||
-      ((epi == EPI_ACT_BWD || epi == EPI_DROP_BWD) && !a.Aux) || (epi == EPI_LABEL_LRELU && (!a.label_rows || !a.sample_slot || a.L != 1)) ||
+      ((epi == EPI_ACT_BWD || epi == EPI_DROP_BWD) && !a.Aux) ||
       (epi == EPI_BIAS_ACT && !a.bn_bias) || (epi == EPI_BN && (!a.bn_mean || !a.bn_var || !a.bn_gamma || !a.bn_beta || a.bn_C < 1)))
     return launch_fail("GEMM: null operand, or channel counts that are not whole 128-byte lines");
   if (a.tile == TILE_BIG && a.N % 256 != 0) return launch_fail("GEMM: 256 x 256 tiles need whole tiles of columns");
@@ -1214,15 +1155,13 @@ void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st) {
   if (mode == MODE_UP && epi == EPI_DROP_BWD) return launch_mode<T, MODE_UP, EPI_DROP_BWD>(a, st);
   if (mode == MODE_DENSE && epi == EPI_NONE) return launch_mode<T, MODE_DENSE, EPI_NONE>(a, st);
   if (mode == MODE_DENSE && epi == EPI_BIAS_ACT) return launch_mode<T, MODE_DENSE, EPI_BIAS_ACT>(a, st);
-  if (mode == MODE_DENSE && epi == EPI_LRELU) return launch_mode<T, MODE_DENSE, EPI_LRELU>(a, st);
-  if (mode == MODE_DENSE && epi == EPI_LABEL_LRELU) return launch_mode<T, MODE_DENSE, EPI_LABEL_LRELU>(a, st);
   launch_fail("GEMM: (mode, epilogue) combination without an instantiation");
 }
 // Name of the kernel instantiation launch_conv picks (for per-kernel timing): mode, epilogue, tile.
 const char* conv_variant_name(int esize, int mode, int epi, const ConvArgs& a) {
   static const char* modes[3] = {"down", "up", "dense"};
-  static const char* epis[7] = {"", "+actbwd", "+lrelu", "+label+lrelu", "+dropbwd", "+bn", "+bias+act"};
-  static char names[2][3][7][7][48];
+  static const char* epis[5] = {"", "+actbwd", "+dropbwd", "+bn", "+bias+act"};
+  static char names[2][3][5][7][48];
   char* n = names[esize == 4][mode][epi][a.tile];
   if (!n[0]) snprintf(n, 48, "gemm_%s%s<%s>", modes[mode], epis[epi], tile_info(esize, a.tile).name);
   return n;
@@ -1258,11 +1197,6 @@ template <typename T, int ROWB>
 __device__ inline int wg_swz(int row) {   // in 16-byte chunks
   if (sizeof(T) == 4) return 8 * (row & 1);
   return ROWB >= 256 ? 4 * (row & 3) : 4 * ((row >> 1) & 1);
-}
-typedef short short4v __attribute__((ext_vector_type(4)));
-__device__ inline uint2 lds_read_tr16(const unsigned char* p) {
-  const short4v v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v*)(p));
-  return __builtin_bit_cast(uint2, v);
 }
 
 template <typename T, typename TL>
@@ -1503,7 +1437,7 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void wgrad_kerne
   // fp32 through splits: the chunk comes into registers, is split there, once a block, and goes to LDS as three planes of bf16 rows, which are then
   // read like a bf16 chunk.  Split by the waves that multiply, every value was split twice in a 128 x 128 tile, and the vector instructions of that took
   // longer (830 cycles a 16-row step) than the MFMAs (770): 128 -> 256 channels, side 8, two segments of 20 x 64 samples 1035 -> 942 us,
-  // 256 -> 512, side 4 1060 -> 949, patch-matrix layer 156 -> 137; 10 x 128 samples, 64 -> 128, side 7 256 -> 229.  The matrix pipe is busy 0.57 of the
+  // 256 -> 512, side 4 1060 -> 949; 10 x 128 samples, 64 -> 128, side 7 256 -> 229.  The matrix pipe is busy 0.57 of the
   // time a CU has blocks.  PLANE: bytes of one; buffers are not doubled, the next chunk waits in the registers.
   constexpr int PLANE_A = WG_KR * BM * 2, PLANE_B = WG_KR * BN * 2;
   auto split_loop = [&](auto chunk_row, int per_seg, int nchunks) __attribute__((always_inline)) {
@@ -1795,8 +1729,6 @@ __global__ __launch_bounds__(TL::NT, (waves_per_simd<T, TL>())) void wgrad_kerne
 // L2 (operand bytes per product fall with the tile's sides).  fp32: six times the matrix-pipe time, so
 // tiles are small: 128 x 128 with two blocks per CU leaves little of a last round of blocks idle (640 such tiles of 20 models run
 // at 126 TFLOP/s, 256 x 128 ones at 90-106, 256 x 64 at 119, all without the scaling of the operands).
-typedef Tile<64, 128, 1, 4> TileWgImg;    // patch-matrix layers: 64 packed columns x 128 feature channels
-typedef Tile<64, 64, 2, 2> TileWgImg64;   //   and x 64
 typedef Tile<256, 64, 4, 1> TileWg64;     // 64 channels on the N side, bf16
 typedef Tile<256, 256, 2, 4> TileWgBig;
 typedef Tile<256, 256, 2, 4, 128, 2, 1, 0, true> TileWgQuad;      // in quarters, see quad_loop
@@ -1835,9 +1767,7 @@ static void launch_wgrad_one(WgradArgs a, hipStream_t st) {
 // Which tile a layer's weight gradient uses, as f(tile, name)
 template <typename T, typename F>
 static void with_wgrad_tile(int ntaps, int Cb, int Cs, F&& f) {
-  if (ntaps * Cb <= 64) {
-    if (Cs <= 64) f(TileWgImg64(), "wgrad<64x64>"); else f(TileWgImg(), "wgrad<64x128>");
-  } else if constexpr (sizeof(T) == 4) {
+  if constexpr (sizeof(T) == 4) {
     if (Cs <= 64) f(TileWgF32N(), "wgrad<128x64>"); else f(TileWgF32(), "wgrad<128x128>");
   } else {
     if (Cs % 256 == 0) f(TileWgBig(), "wgrad<256x256>");

@@ -1,0 +1,768 @@
+// The strided convolutions that read an image of 1..4 channels: D's first layer, and the gradients of G's last transposed
+// convolution, whose output gradient is such an image.  k4 s2 p1, Cs = 64 or 128 feature channels.
+//   out[pixel][cs]  = act(sum over (tap, c) of patch(pixel)[tap][c] * w[tap][c][cs] + add[position class][cs])
+//   dw[tap][c][cs]  = sum over pixels of patch(pixel)[tap][c] * dy[pixel][cs]
+// Both are contractions over 16 taps of a few channels, bound by the feature tensor that they write or read once.  No patch matrix
+// exists: an image tile lies in LDS with P = 2, 4 or 8 values a pixel (the channels, a one inside the image, zeros), and the operand reads
+// pick the patches out of it.  Forward: a lane's eight values of K are neighbouring pixels of a tile row, 16 bytes.  Weight gradient: the
+// transposing LDS read takes an address of 8 bytes per lane, so that its rows are pixels and its columns the (tap, channel) of the patch.
+//
+// A one-hot label map is a constant plane.  Forward, it and the bias are a row per position class (3 x 3: which taps lie outside), added
+// behind the product.  Its gradient is that of the ones inside the image, and the bias's is the same at a tap that is never outside.
+// One pair over many labels takes its label maps' gradients from class sums instead (launch_class_sums).
+//
+// fp32 storage: the tile, the weights and dy are split into three bf16 parts (split_mfma.h).
+//
+// What it replaced: patch matrices in memory, written by one kernel and read as the operand of a row-by-row GEMM and weight gradient.  us, before
+// -> now.  A hundred 32x32 pairs of 64 samples, 128 channels, bf16: both segments 388 -> 217 (now 4.4 TB/s of the 0.96 GB that have to move; 179
+// without the image's loads, 107 without the stores), one 129 -> 112, their weight gradients 320 -> 259 and 243 -> 113, which now includes the bias;
+// eight 64x64 pairs, 64 channels, 191 -> 88, 51 -> 40, 112 -> 80, 122 -> 48; twenty 32x32 pairs in fp32 184 -> 108, 68 -> 55, 144 -> 127, 105 -> 73; ten
+// 28x28 pairs in fp32 93 -> 45, 31 -> 25, 69 -> 57, 62 -> 33.  Whole steps: +10 % (ten 28x28 pairs, bf16) to +2 % (twenty 32x32 pairs, fp32).
+#include <algorithm>
+
+#include "kernels.h"
+#include "lds_copy.h"
+#include "split_mfma.h"
+
+namespace gan {
+
+namespace {
+
+constexpr int IMG_SIDE = 16;                 // outputs along x of a unit, at most
+constexpr int conv_side_y(int esize) { return esize == 4 ? 8 : 16; }      // along y: forward
+constexpr int WG_SIDE_Y = 8;                                              // and weight gradient, where one wave's registers hold the next unit's image
+constexpr int ZERO_ROWS = 4;                 // behind the weight gradient's tiles: what pixels outside the map read
+
+constexpr int img_values(int CB) { return CB == 1 ? 2 : (CB < 4 ? 4 : 8); }
+// Units of a map of side Hs: ph x pw outputs, their tile rows `pitch` bytes apart.  A pitch of 80 to 176 bytes modulo 256 keeps the rows that one
+// transposing read touches apart.
+struct Units { int pw, ph, nx, ny, pitch; };
+Units img_units(int Hs, int CB, int side_y) {
+  Units u;
+  u.nx = (Hs + IMG_SIDE - 1) / IMG_SIDE;
+  u.pw = (Hs + u.nx - 1) / u.nx;
+  u.ny = (Hs + side_y - 1) / side_y;
+  u.ph = (Hs + u.ny - 1) / u.ny;
+  u.pitch = ((2 * u.pw + 2) * 2 * img_values(CB) + 15) / 16 * 16;
+  while (u.pitch % 256 < 80 || u.pitch % 256 > 176) u.pitch += 16;
+  return u;
+}
+
+// one pixel of the tile: P values, fp32 in three planes `plane` bytes apart
+template <typename T, int CB>
+__device__ __forceinline__ void put_pixel(unsigned char* at, int plane, const float (&v)[CB], bool in) {
+  constexpr int P = img_values(CB);
+  float f[P];
+#pragma unroll
+  for (int i = 0; i < P; ++i) f[i] = i < CB ? v[i] : (i == CB && in ? 1.f : 0.f);
+  unsigned q[sizeof(T) == 4 ? 3 : 1][P / 2];
+#pragma unroll
+  for (int i = 0; i < P / 2; ++i) {
+    if constexpr (sizeof(T) == 4) split_pair(f[2 * i], f[2 * i + 1], q[0][i], q[1][i], q[2][i]);
+    else q[0][i] = pack2_bf16(f[2 * i], f[2 * i + 1]);
+  }
+#pragma unroll
+  for (int pl = 0; pl < (sizeof(T) == 4 ? 3 : 1); ++pl) {
+    unsigned char* const d = at + pl * plane;
+    if constexpr (P == 2) *reinterpret_cast<unsigned*>(d) = q[pl][0];
+    else if constexpr (P == 4) *reinterpret_cast<uint2*>(d) = make_uint2(q[pl][0], q[pl][1]);
+    else *reinterpret_cast<uint4*>(d) = make_uint4(q[pl][0], q[pl][1], q[pl][2], q[pl][3]);
+  }
+}
+// The image under the outputs (y0 .., x0 ..) of a unit: tile pixel (ty, tx) is image pixel (2 y0 - 1 + ty, 2 x0 - 1 + tx), zeros outside.  A thread's
+// U pairs of neighbouring pixels are all on their way together (no branch and no conversion between the loads, either of which would wait for
+// them), and the tile is written later (put).  own: put also adds up the pixels of the unit's own 2 ph x 2 pw.
+template <typename T, int CB, int U>
+struct Stager {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  u2 v[U][CB];                                                 // as loaded.  NCHW: channel c of both pixels in v[c]; NHWC: the pair's 2 CB values in a row
+  unsigned in;                                                 // bit k: pair k lies inside the image
+  bool nchw;
+  template <typename F>
+  static __device__ __forceinline__ void pairs(const Units& u, int tid, int nt, F&& f) {
+    const int per = u.pw + 2, total = (2 * u.ph + 2) * per;
+    const float inv = 1.f / (float)per;
+    static_for<0, U>([&](auto k) __attribute__((always_inline)) {
+      const int q = tid + k.value * nt, ty = (int)(((float)q + 0.5f) * inv);       // (exact: q < 1024)
+      f(k, ty, q - ty * per - 1, q < total);
+    });
+  }
+  __device__ __forceinline__ void fetch(const Units& u, const T* img, const float* real, int Hb, int y0, int x0, int tid, int nt) {
+    in = 0;
+    nchw = img == nullptr;
+    const int npix = Hb * Hb;
+    const __amdgpu_buffer_rsrc_t rs = buffer_of(nchw ? (const void*)real : (const void*)img, (unsigned)npix * CB * (nchw ? 4u : (unsigned)sizeof(T)));
+    const unsigned pixel = nchw ? 4u : (unsigned)sizeof(T) * CB, step = nchw ? 4u * npix : 8u;      // bytes
+    pairs(u, tid, nt, [&](auto k, int ty, int pr, bool there) __attribute__((always_inline)) {
+      const int iy = 2 * y0 - 1 + ty, ix = 2 * (x0 + pr);
+      const bool inside = there && (unsigned)iy < (unsigned)Hb && (unsigned)ix < (unsigned)Hb;
+      in |= inside ? 1u << k.value : 0u;
+      const unsigned at = (unsigned)(iy * Hb + ix) * pixel;
+      static_for<0, CB>([&](auto c) __attribute__((always_inline)) {
+        const bool needed = sizeof(T) == 4 || nchw || 2 * c.value < CB;      // (bf16 NHWC: CB words)
+        v[k.value][c.value] = __builtin_amdgcn_raw_buffer_load_b64(rs, inside && needed ? at + c.value * step : NO_ROW, 0, 0);
+      });
+    });
+  }
+  template <int P, int C, int K> __device__ __forceinline__ float value() const {      // channel C of pixel P of pair K
+    constexpr int e = P * CB + C;
+    if constexpr (sizeof(T) == 2) {
+      const unsigned w = v[K][e / 4][e / 2 % 2], half = e & 1 ? w & 0xffff0000u : w << 16;
+      return __uint_as_float(nchw ? v[K][C][P] : half);
+    } else {
+      return __uint_as_float(nchw ? v[K][C][P] : v[K][e / 2][e % 2]);
+    }
+  }
+  __device__ __forceinline__ void put(unsigned char* tile, int plane, const Units& u, int tid, int nt, float (*own)[CB]) const {
+    constexpr int PB = 2 * img_values(CB);
+    pairs(u, tid, nt, [&](auto k, int ty, int pr, bool there) __attribute__((always_inline)) {
+      unsigned char* const at = tile + ty * u.pitch + (2 * pr + 1) * PB;
+      const bool inside = (in >> k.value) & 1;
+      float a[CB], b[CB];
+      static_for<0, CB>([&](auto c) __attribute__((always_inline)) {
+        a[c.value] = value<0, c.value, k.value>();
+        b[c.value] = value<1, c.value, k.value>();
+      });
+      if (there && pr >= 0) put_pixel<T, CB>(at, plane, a, inside);
+      if (there && pr < u.pw) put_pixel<T, CB>(at + PB, plane, b, inside);
+      if (own) {
+        const bool mine = there && ty > 0 && ty <= 2 * u.ph && pr >= 0 && pr < u.pw;
+        static_for<0, CB>([&](auto c) __attribute__((always_inline)) { (*own)[c.value] += mine ? a[c.value] + b[c.value] : 0.f; });
+      }
+    });
+  }
+};
+// pairs of the largest unit
+constexpr int unit_pairs(int side_y) { return (2 * side_y + 2) * (IMG_SIDE + 2); }
+
+__device__ inline bool any_not_finite(const floatx16& a) {
+  float z = 0.f;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) z = __builtin_fmaf(a[e], 0.f, z);
+  return __ballot(z != z) != 0;
+}
+
+// The value of patch column m = tap * P + c at output pixel (y, x), from memory
+template <typename T, int CB>
+__device__ inline float patch_value(const T* img, const float* real, int Hb, int y, int x, int m) {
+  constexpr int P = img_values(CB);
+  const int tap = m / P, c = m - tap * P, iy = 2 * y - 1 + (tap >> 2), ix = 2 * x - 1 + (tap & 3);
+  if (c > CB || (unsigned)iy >= (unsigned)Hb || (unsigned)ix >= (unsigned)Hb) return 0.f;
+  if (c == CB) return 1.f;
+  return img ? to_float(img[((long long)iy * Hb + ix) * CB + c]) : real[((long long)c * Hb + iy) * Hb + ix];
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Forward: a block per (unit, sample, segment), bound by its stores.  A wave owns 128 bytes of channels (64 in bf16, 32 in fp32), whose weights stay in its registers, and
+// multiplies them with 32 pixels at a time; the result's columns are pixels, so that a lane has 16 channels of its pixel from every product.  They
+// go through a patch of LDS of the wave's own, so that a store writes whole 128-byte lines of eight pixels (16 bytes a lane straight from the
+// registers, 32 or 64 in a row: 294 and 265 us for 217; past the caches 302).
+// ---------------------------------------------------------------------------------------------------------
+constexpr int OUT_ROW = 128 + 16;            // bytes of a pixel in the patch
+template <typename T, int CB, int CS>
+__global__ __launch_bounds__(256) void image_conv_kernel(ImageConvArgs a, Units u) {
+  constexpr int P = img_values(CB), PB = 2 * P, KS = P, PL = sizeof(T) == 4 ? 3 : 1;
+  constexpr int NB = PL == 1 ? 2 : 1, GROUPS = CS / (32 * NB), TURNS = 4 / GROUPS;      // blocks of 32 channels a wave, waves across the channels, and along the pixels
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const int per_sample = u.nx * u.ny, j = (int)blockIdx.x / per_sample, unit = (int)blockIdx.x - j * per_sample;
+  if (j >= a.offs[a.L]) return;
+  const int l = a.sample_model[j], seg = a.seg_first + (int)blockIdx.y;
+  const int Hs = a.Hs, Hb = 2 * Hs, plane = (2 * u.ph + 2) * u.pitch;
+  const int uy = unit / u.nx, y0 = uy * u.ph, x0 = (unit - uy * u.nx) * u.pw;
+  const int ph = min(u.ph, Hs - y0), pw = min(u.pw, Hs - x0), px = ph * pw;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 31, h = lane >> 5, cg = wave % GROUPS, c0 = cg * 32 * NB;
+  const bool nchw = a.real && seg == 0;
+  const T* img = nchw ? nullptr : static_cast<const T*>(a.img) + ((long long)seg * a.seg_samples + j) * Hb * Hb * CB;
+  const float* real = nchw ? a.real + (long long)a.perm[j] * CB * Hb * Hb : nullptr;
+  Stager<T, CB, (unit_pairs(conv_side_y((int)sizeof(T))) + 255) / 256> image;
+  image.fetch(u, img, real, Hb, y0, x0, tid, 256);
+  // this lane's row of weights: channel 8 h' + e of the first sixteen, of the second, so that the results come out eight channels at a time
+  const int e_ = (r >> 3) * 4 + (r & 3), ch = (e_ >> 3) * 16 + ((r >> 2) & 1) * 8 + (e_ & 7);
+  u32x4 w[NB][PL][KS];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const T* wr = static_cast<const T*>(a.w) + ((long long)l * CS + c0 + 32 * b + ch) * 16 * P + 8 * h;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const u32x4* q = reinterpret_cast<const u32x4*>(wr + 16 * s);
+      if constexpr (PL == 3) {
+        const Split8 t = split8(q[0], q[1]);
+        w[b][0][s] = t.h; w[b][1][s] = t.m; w[b][2][s] = t.l;
+      } else {
+        w[b][0][s] = q[0];
+      }
+    }
+  }
+  float* const add = reinterpret_cast<float*>(lds + PL * plane);
+  unsigned char* const patch = lds + PL * plane + 9 * CS * 4 + wave * (32 * OUT_ROW);
+  if (a.add) {
+    const float* src = a.add + (long long)(a.sample_slot ? a.sample_slot[j] : l) * 9 * CS;
+    for (int i = tid; i < 9 * CS / 4; i += 256) reinterpret_cast<float4*>(add)[i] = reinterpret_cast<const float4*>(src)[i];
+  } else {
+    for (int i = tid; i < 9 * CS / 4; i += 256) reinterpret_cast<float4*>(add)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  image.put(lds, plane, u, tid, 256, nullptr);
+  __syncthreads();
+  // K-step s, lane half h: pixels of the patch row ky = s (P = 4: columns 2 h, 2 h + 1), 2 s + h (P = 2: all four) or s / 2 (P = 8: column 2 (s % 2) + h)
+  const int hoff = P == 2 ? h * u.pitch : (P == 4 ? 2 * h * PB : h * PB);
+  T* const out = static_cast<T*>(a.out) + ((long long)seg * a.seg_samples + j) * Hs * Hs * CS + c0;
+  const float inv_pw = 1.f / (float)pw;
+  const auto row_of = [&](int q) __attribute__((always_inline)) { return (int)(((float)q + 0.5f) * inv_pw); };      // (exact: at most 16 x 16 pixels)
+  for (int p0 = wave / GROUPS * 32; p0 < px; p0 += TURNS * 32) {
+    const int pc = min(p0 + r, px - 1), yl = row_of(pc), xl = pc - yl * pw, y = y0 + yl, x = x0 + xl;
+    const unsigned char* const q = lds + 2 * yl * u.pitch + 2 * xl * PB + hoff;
+    const float* const ad = add + pos_class(y, x, Hs) * CS + c0 + h * 8;
+    floatx16 acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int e = 0; e < 16; e += 4) {
+        const float4 t = *reinterpret_cast<const float4*>(ad + 32 * b + (e >> 3) * 16 + (e & 7));
+        acc[b][e] = t.x; acc[b][e + 1] = t.y; acc[b][e + 2] = t.z; acc[b][e + 3] = t.w;
+      }
+    const auto pixels = [&](int s, int pl) __attribute__((always_inline)) {
+      const unsigned char* const at = q + pl * plane + (P == 2 ? 2 * s * u.pitch : (P == 4 ? s * u.pitch : (s >> 1) * u.pitch + (s & 1) * 2 * PB));
+      if constexpr (P == 2) {                          // 8-byte aligned
+        const uint2 lo = *reinterpret_cast<const uint2*>(at), hi = *reinterpret_cast<const uint2*>(at + 8);
+        return u32x4{lo.x, lo.y, hi.x, hi.y};
+      } else {
+        return *reinterpret_cast<const u32x4*>(at);
+      }
+    };
+    if constexpr (PL == 1) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const u32x4 f = pixels(s, 0);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) mma_u4(acc[b], w[b][0][s], f);
+      }
+    } else {
+      floatx16 sum = {}, low = {};
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const u32x4 fh = pixels(s, 0), fm = pixels(s, 1), fl = pixels(s, 2);
+        mma_u4(low, w[0][2][s], fh);
+        mma_u4(sum, w[0][0][s], fh);
+        mma_u4(low, w[0][0][s], fl);
+        mma_u4(low, w[0][1][s], fm);
+        mma_u4(low, w[0][1][s], fh);
+        mma_u4(low, w[0][0][s], fm);
+      }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sum[e] = (sum[e] + low[e]) * SPLIT_UNSCALE;
+      if (any_not_finite(sum)) {                       // what has no split: these 32 pixels again, value by value
+        const T* w0 = static_cast<const T*>(a.w) + ((long long)l * CS + c0 + h * 8) * 16 * P;
+        sum = floatx16{};
+        for (int m = 0; m < 16 * P; ++m) {
+          if (m % P >= CB) continue;
+          const float v = patch_value<T, CB>(img, real, Hb, y, x, m);
+#pragma unroll
+          for (int e = 0; e < 16; ++e) sum[e] = __builtin_fmaf(v, to_float(w0[((e >> 3) * 16 + (e & 7)) * 16 * P + m]), sum[e]);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[0][e] += sum[e];
+    }
+    // into the patch: pixel r, channels 32 b + 16 g + 8 h .. + 7
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[b][e] = acc[b][e] > 0.f ? acc[b][e] : acc[b][e] * a.slope;
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        unsigned char* const d = patch + r * OUT_ROW + (32 * b + 16 * g + 8 * h) * (int)sizeof(T);
+        if constexpr (PL == 1) {
+          *reinterpret_cast<u32x4*>(d) = u32x4{pack2_bf16(acc[b][8 * g], acc[b][8 * g + 1]), pack2_bf16(acc[b][8 * g + 2], acc[b][8 * g + 3]),
+                                               pack2_bf16(acc[b][8 * g + 4], acc[b][8 * g + 5]), pack2_bf16(acc[b][8 * g + 6], acc[b][8 * g + 7])};
+        } else {
+#pragma unroll
+          for (int k = 0; k < 8; k += 4)
+            *reinterpret_cast<float4*>(d + 4 * k) = make_float4(acc[b][8 * g + k], acc[b][8 * g + k + 1], acc[b][8 * g + k + 2], acc[b][8 * g + k + 3]);
+        }
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = 8 * i + (lane >> 3), pg = p0 + row, yg = row_of(pg);
+      const u32x4 v = *reinterpret_cast<const u32x4*>(patch + row * OUT_ROW + (lane & 7) * 16);
+      if (pg < px) *reinterpret_cast<u32x4*>(out + ((y0 + yg) * Hs + x0 + pg - yg * pw) * CS + (lane & 7) * (16 / (int)sizeof(T))) = v;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+template <typename T, int CB, int CS>
+void conv_one(const ImageConvArgs& a, hipStream_t st) {
+  const Units u = img_units(a.Hs, CB, conv_side_y((int)sizeof(T)));
+  const size_t lds = (size_t)(sizeof(T) == 4 ? 3 : 1) * (2 * u.ph + 2) * u.pitch + 9 * CS * 4 + 4 * 32 * OUT_ROW;
+  if (lds > 48 * 1024)   // above the default dynamic limit: ask for it (idempotent, cheap)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&image_conv_kernel<T, CB, CS>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const long long blocks = (long long)a.n * u.nx * u.ny;
+  if (blocks >= (1LL << 31)) return launch_fail("image-side convolution: more blocks than a launch can have");
+  hipLaunchKernelGGL((image_conv_kernel<T, CB, CS>), dim3((unsigned)blocks, (unsigned)a.nseg), dim3(256), lds, st, a, u);
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Weight gradient: a block takes the samples of one tile of a model (both segments), unit by unit, and leaves partial sums; what adds them
+// follows below.  Four waves multiply, each its own 32 feature channels (64 of them: two waves share 32, a K-step of 16 pixels each in turn), so
+// that dy needs no barrier: its pixels come into the wave's own ring of LDS (fp32: of registers) K-steps ahead.  A fifth wave stages the next
+// unit's image tile meanwhile.
+// ---------------------------------------------------------------------------------------------------------
+constexpr int wg_ring(int esize) { return esize == 4 ? 3 : 6; }      // K-steps of dy on their way, a wave (bf16: 1 KiB each, fp32: 2)
+constexpr int WG_THREADS = 320;
+
+// EVEN: units of sixteen columns that the map is a whole number of, so that a K-step is (part of) a row and the next one a fixed distance away;
+// every lane's addresses are then its own constants and wave-uniform offsets.
+template <typename T, int CB, int CS, bool EVEN>
+__global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? 4 : 3)) void image_wgrad_kernel(ImageWgradArgs a, Units u) {
+  constexpr int P = img_values(CB), PB = 2 * P, NC = CS / 32, TURNS = 4 / NC, MF = P == 2 ? 1 : P / 2, PL = sizeof(T) == 4 ? 3 : 1;
+  constexpr int WG_RING = wg_ring((int)sizeof(T));
+  constexpr int RING_BYTES = PL == 1 ? WG_RING * 1024 : 3 * 1024;      // of a wave
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+  const int tile = blockIdx.x;
+  if (tile >= a.tpre[a.L]) return;
+  const int l = a.tmodel ? a.tmodel[tile] : 0;
+  const int j0 = a.offs[l] + (tile - a.tpre[l]) * a.tile_samples, j1 = min(a.offs[l + 1], j0 + a.tile_samples);
+  const int Hs = a.Hs, Hb = 2 * Hs, npix = Hb * Hb;
+  const int units = (j1 - j0) * u.nx * u.ny * a.nseg;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int trows = 2 * u.ph + 2, plane = (trows + ZERO_ROWS) * u.pitch, buf = PL * plane;
+  unsigned char* const tiles = lds + 4 * RING_BYTES;                   // two
+  struct At { int seg, j, y0, x0; };
+  const auto next_unit = [&](At& t) __attribute__((always_inline)) {     // along x, along y, the next sample, the next segment
+    if ((t.x0 += u.pw) < Hs) return;
+    t.x0 = 0;
+    if ((t.y0 += u.ph) < Hs) return;
+    t.y0 = 0;
+    if (++t.j < j1) return;
+    t.j = j0;
+    ++t.seg;
+  };
+  const At first = {a.seg_first, j0, 0, 0};
+  float own[CB];
+#pragma unroll
+  for (int c = 0; c < CB; ++c) own[c] = 0.f;
+  Stager<T, CB, (unit_pairs(WG_SIDE_Y) + 63) / 64> image;
+  At ahead = first;
+  int place = a.real ? a.perm[j0] : 0;                                   // of the sample `ahead`, known a unit before it is needed
+  const auto fetch = [&]() __attribute__((always_inline)) {
+    const bool nchw = a.real && ahead.seg == 0;
+    image.fetch(u, nchw ? nullptr : static_cast<const T*>(a.img) + ((long long)ahead.seg * a.seg_samples + ahead.j) * npix * CB,
+                nchw ? a.real + (long long)place * CB * npix : nullptr, Hb, ahead.y0, ahead.x0, lane, 64);
+    next_unit(ahead);
+    if (a.real) place = a.perm[ahead.j];
+  };
+  const auto put = [&](int i) __attribute__((always_inline)) { image.put(tiles + (i & 1) * buf, plane, u, lane, 64, a.pixel_sums ? &own : nullptr); };
+  if (wave == 4) fetch();
+  // the rows that pixels outside the map read
+  for (int i = tid; i < 2 * PL * ZERO_ROWS * u.pitch / 16; i += WG_THREADS) {
+    const int per = ZERO_ROWS * u.pitch / 16, q = i / per;
+    *reinterpret_cast<uint4*>(tiles + q * plane + trows * u.pitch + (i - q * per) * 16) = make_uint4(0, 0, 0, 0);
+  }
+
+  const int cb = wave % NC, turn = wave / NC % TURNS;
+  const int steps = ((u.ph * u.pw + 15) / 16 + TURNS - 1) / TURNS;     // K-steps of a unit, each of 16 pixels in row order, that this wave takes
+  floatx16 acc[MF] = {}, low[PL == 3 ? MF : 1] = {};
+  // ---- dy: lane -> pixel and 16 bytes of this wave's 32 channels, K-steps in the order of the units
+  constexpr int LPP = PL == 1 ? 4 : 8, LOADS = PL == 1 ? 1 : 2;        // lanes a pixel, loads a K-step
+  const int dx16 = 16 * TURNS % u.pw, dy16 = 16 * TURNS / u.pw;
+  int at_unit = 0, at_step = 0, ly[LOADS], lx[LOADS];
+  At at = first;
+  const auto first_pixel = [&](int p, int& y, int& x) __attribute__((always_inline)) { y = p / u.pw; x = p - y * u.pw; };
+  int y_first[LOADS], x_first[LOADS];
+#pragma unroll
+  for (int i = 0; i < LOADS; ++i) {
+    first_pixel(16 * turn + lane / LPP + i * (64 / LPP), y_first[i], x_first[i]);
+    ly[i] = y_first[i]; lx[i] = x_first[i];
+  }
+  const T* dy_sample = static_cast<const T*>(a.dy) + ((long long)at.seg * a.seg_samples + at.j) * Hs * Hs * CS;
+  const unsigned dy_bytes = (unsigned)(Hs * Hs * CS * (int)sizeof(T));
+  bool live = wave < 4;
+  const unsigned row_bytes = (unsigned)(Hs * CS * (int)sizeof(T));
+  const auto unit_off = [&](const At& t) __attribute__((always_inline)) { return (unsigned)t.y0 * row_bytes + (unsigned)(t.x0 * CS * (int)sizeof(T)); };
+  unsigned uoff = EVEN ? unit_off(at) : 0u;            // EVEN: of the K-step to load
+  unsigned lane_off[LOADS];
+#pragma unroll
+  for (int i = 0; i < LOADS; ++i)
+    lane_off[i] = (unsigned)turn * row_bytes + (unsigned)(((lane / LPP + i * (64 / LPP)) * CS + cb * 32 + lane % LPP * (16 / (int)sizeof(T))) * (int)sizeof(T));
+  const auto offset = [&](int i) __attribute__((always_inline)) {
+    if constexpr (EVEN) return lane_off[i];
+    const int y = at.y0 + ly[i], x = at.x0 + lx[i];
+    const bool ok = ly[i] < u.ph && y < Hs && x < Hs;
+    return ok ? (unsigned)(((y * Hs + x) * CS + cb * 32 + lane % LPP * (16 / (int)sizeof(T))) * (int)sizeof(T)) : NO_ROW;
+  };
+  const auto advance = [&]() __attribute__((always_inline)) {
+    if (++at_step < steps) {
+      if constexpr (EVEN) { uoff += TURNS * row_bytes; return; }
+#pragma unroll
+      for (int i = 0; i < LOADS; ++i) {
+        lx[i] += dx16; ly[i] += dy16;
+        if (lx[i] >= u.pw) { lx[i] -= u.pw; ++ly[i]; }
+      }
+      return;
+    }
+    at_step = 0;
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) { ly[i] = y_first[i]; lx[i] = x_first[i]; }
+    if (++at_unit < units) {
+      next_unit(at);
+      if constexpr (EVEN) uoff = unit_off(at);
+      dy_sample = static_cast<const T*>(a.dy) + ((long long)at.seg * a.seg_samples + at.j) * Hs * Hs * CS;
+    } else {
+      live = false;                                    // behind the last unit: an empty buffer, zeros
+    }
+  };
+  // ---- operands: lane = 32 kgrp + 16 hb + s reads, for rows 8 kgrp + 4 half + s / 4 of a K-step (pixels), the 8 bytes s % 4 of the 16 columns hb
+  const int s16 = lane & 15, hb = (lane >> 4) & 1, kgrp = lane >> 5, frow = 8 * kgrp + (s16 >> 2), sg = s16 & 3;
+  // column group 4 hb + sg of fragment t: P = 4: tap (2 t + hb, sg); P = 2: taps (2 hb + sg / 2, 2 (sg % 2) ..); P = 8: half sg % 2 of tap (t, 2 hb + sg / 2)
+  const int goff = P == 4 ? hb * u.pitch + sg * PB : (P == 2 ? (2 * hb + (sg >> 1)) * u.pitch + (sg & 1) * 2 * PB : (2 * hb + (sg >> 1)) * PB + (sg & 1) * 8);
+  const int tstep = P == 4 ? 2 * u.pitch : u.pitch;
+  int py_first[2], px_first[2], py[2], px[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) first_pixel(16 * turn + frow + 4 * i, py_first[i], px_first[i]);
+  unsigned char* const ring = lds + wave * RING_BYTES;
+  const unsigned ring_lds = (unsigned)(uintptr_t)ring;
+  const unsigned char* const bq = ring + frow * 64 + hb * 32 + sg * 8;
+  u32x4 v[PL == 3 ? WG_RING : 1][2];
+  const auto request = [&](auto slot) __attribute__((always_inline)) {
+    if constexpr (PL == 1) {
+      load16_to_lds(make_rsrc(dy_sample, live ? dy_bytes : 0), offset(0), uoff, ring_lds + slot.value * 1024);
+    } else {
+      const __amdgpu_buffer_rsrc_t rs = buffer_of(dy_sample, live ? dy_bytes : 0);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) v[slot.value][i] = __builtin_amdgcn_raw_buffer_load_b128(rs, offset(i), uoff, 0);
+    }
+    advance();
+  };
+  At cur = first;
+  const int even_first = 2 * turn * u.pitch;
+  int even_row = even_first;                           // EVEN: tile row of the K-step to multiply, in bytes
+  const auto multiply = [&](auto slot, const unsigned char* tb, bool there) __attribute__((always_inline)) {
+    u32x4 b[PL], f[MF][PL];
+    if constexpr (PL == 1) {
+      wait_vm<WG_RING - 1>();
+    } else {
+      // split into the planes [part][pixel][32 channels], which this wave alone reads and writes
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const Split4 q = split4(v[slot.value][i]);
+        unsigned char* const d = ring + (lane / 8 + 8 * i) * 64 + lane % 8 * 8;
+        *reinterpret_cast<uint2*>(d) = q.h;
+        *reinterpret_cast<uint2*>(d + 1024) = q.m;
+        *reinterpret_cast<uint2*>(d + 2048) = q.l;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    const unsigned char* pa[2];
+    if constexpr (EVEN) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) pa[i] = tb + even_row + 2 * (frow + 4 * i) * PB + goff;
+      even_row += 2 * TURNS * u.pitch;
+    } else
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const bool ok = py[i] < u.ph && cur.y0 + py[i] < Hs && cur.x0 + px[i] < Hs;
+      pa[i] = tb + (ok ? 2 * py[i] * u.pitch + 2 * px[i] * PB : trows * u.pitch) + goff;
+      px[i] += dx16; py[i] += dy16;
+      if (px[i] >= u.pw) { px[i] -= u.pw; ++py[i]; }
+    }
+#pragma unroll
+    for (int pl = 0; pl < PL; ++pl) {
+      const unsigned char* const q = bq + (PL == 1 ? slot.value * 1024 : pl * 1024);
+      const uint2 lo = lds_read_tr16(q), hi = lds_read_tr16(q + 4 * 64);
+      b[pl] = u32x4{lo.x, lo.y, hi.x, hi.y};
+#pragma unroll
+      for (int t = 0; t < MF; ++t) {
+        const uint2 p0 = lds_read_tr16(pa[0] + pl * plane + t * tstep), p1 = lds_read_tr16(pa[1] + pl * plane + t * tstep);
+        f[t][pl] = u32x4{p0.x, p0.y, p1.x, p1.y};
+      }
+    }
+    if constexpr (PL == 1) {
+      __builtin_amdgcn_s_waitcnt(0xc07f);                // lgkmcnt(0): the slot has been read and may be filled again
+      asm volatile("" : : : "memory");
+      request(slot);
+      if (there)
+#pragma unroll
+        for (int t = 0; t < MF; ++t) mma_u4(acc[t], f[t][0], b[0]);
+    } else {
+      request(slot);
+      if (there)
+#pragma unroll
+      for (int t = 0; t < MF; ++t) {
+        mma_u4(low[t], f[t][2], b[0]);
+        mma_u4(acc[t], f[t][0], b[0]);
+        mma_u4(low[t], f[t][0], b[2]);
+        mma_u4(low[t], f[t][1], b[1]);
+        mma_u4(low[t], f[t][1], b[0]);
+        mma_u4(low[t], f[t][0], b[1]);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+  };
+  if (wave == 4) {
+    put(0);
+    if (units > 1) fetch();
+    __syncthreads();
+    for (int i = 0; i < units; ++i) {
+      if (i + 1 < units) put(i + 1);
+      if (i + 2 < units) fetch();
+      __syncthreads();
+    }
+  } else {
+    static_for<0, WG_RING>([&](auto k) __attribute__((always_inline)) { request(k); });
+    __syncthreads();
+    int i = 0, s = 0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) { py[k] = py_first[k]; px[k] = px_first[k]; }
+    // (whole rounds of the ring, whose slots are registers or constant offsets: behind the last unit nothing is multiplied, for which the other tile may never have been written)
+    for (int g = 0; g < units * steps; g += WG_RING)
+      static_for<0, WG_RING>([&](auto k) __attribute__((always_inline)) {
+        multiply(k, tiles + (i & 1) * buf, i < units);
+        if (++s == steps && i < units) {
+          __syncthreads();
+          s = 0;
+          ++i;
+          next_unit(cur);
+          even_row = even_first;
+#pragma unroll
+          for (int q = 0; q < 2; ++q) { py[q] = py_first[q]; px[q] = px_first[q]; }
+        }
+      });
+  }
+  wait_vm<0>();
+  __syncthreads();
+  // ---- partial sums [tile][16 P][CS]
+  float* const part = a.part + (long long)tile * 16 * P * CS;
+  if constexpr (PL == 3) {
+#pragma unroll
+    for (int t = 0; t < MF; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[t][e] = (acc[t][e] + low[t][e]) * SPLIT_UNSCALE;
+    bool bad = false;
+    if (wave < 4) {
+#pragma unroll
+      for (int t = 0; t < MF; ++t) bad = any_not_finite(acc[t]) || bad;
+    }
+    if (bad) {                                         // what has no split: this wave's sums again with the fp32 MFMAs, from memory
+#pragma unroll
+      for (int t = 0; t < MF; ++t) acc[t] = floatx16{};
+      At q = first;
+      for (int i = 0; i < units; ++i, next_unit(q)) {
+        const bool nchw = a.real && q.seg == 0;
+        const T* img = nchw ? nullptr : static_cast<const T*>(a.img) + ((long long)q.seg * a.seg_samples + q.j) * npix * CB;
+        const float* real = nchw ? a.real + (long long)a.perm[q.j] * CB * npix : nullptr;
+        const T* dys = static_cast<const T*>(a.dy) + ((long long)q.seg * a.seg_samples + q.j) * Hs * Hs * CS;
+        for (int k = 0; k < 16 * steps; k += 2) {      // the pixels of its own K-steps
+          const int p = ((k >> 4) * TURNS + turn) * 16 + (k & 15) + kgrp, yl = p / u.pw, y = q.y0 + yl, x = q.x0 + p - yl * u.pw;
+          const bool ok = yl < u.ph && y < Hs && x < Hs;
+          const float d = ok ? to_float(dys[(long long)(y * Hs + x) * CS + cb * 32 + (lane & 31)]) : 0.f;
+#pragma unroll
+          for (int t = 0; t < MF; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(ok ? patch_value<T, CB>(img, real, Hb, y, x, 32 * t + (lane & 31)) : 0.f, d, acc[t], 0, 0, 0);
+        }
+      }
+    }
+  }
+  if constexpr (TURNS > 1) {                           // the second wave's sums onto the first's (the rings and tiles are free)
+    static_assert(TURNS == 2, "two waves");
+    float* const sums = reinterpret_cast<float*>(lds) + cb * MF * 16 * 64;
+    if (wave < 4 && turn == 1)
+#pragma unroll
+      for (int t = 0; t < MF; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sums[(t * 16 + e) * 64 + lane] = acc[t][e];
+    __syncthreads();
+    if (wave < 4 && turn == 0)
+#pragma unroll
+      for (int t = 0; t < MF; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[t][e] += sums[(t * 16 + e) * 64 + lane];
+  }
+  if (wave < 4 && turn == 0) {
+#pragma unroll
+    for (int t = 0; t < MF; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) part[(32 * t + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)) * CS + cb * 32 + (lane & 31)] = acc[t][e];
+  }
+  if (wave == 4 && a.pixel_sums) {
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+      float s = own[c];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+      if (lane == 0) a.pixel_sums[tile * 4 + c] = s;
+    }
+  }
+}
+template <typename T, int CB, int CS>
+void wgrad_one(const ImageWgradArgs& a, int tiles, hipStream_t st) {
+  const Units u = img_units(a.Hs, CB, WG_SIDE_Y);
+  constexpr int PL = sizeof(T) == 4 ? 3 : 1, MF = img_values(CB) == 2 ? 1 : img_values(CB) / 2;
+  const size_t lds = std::max<size_t>(4 * (PL == 1 ? wg_ring((int)sizeof(T)) * 1024 : 3 * 1024) + (size_t)2 * PL * (2 * u.ph + 2 + ZERO_ROWS) * u.pitch, CS == 64 ? 2 * MF * 16 * 64 * 4 : 0);
+  const bool even = u.pw == 16 && u.nx * u.pw == a.Hs && u.ny * u.ph == a.Hs && u.ph % (128 / CS) == 0;
+  const void* const kernel = even ? reinterpret_cast<const void*>(&image_wgrad_kernel<T, CB, CS, true>) : reinterpret_cast<const void*>(&image_wgrad_kernel<T, CB, CS, false>);
+  if (lds > 48 * 1024)   // above the default dynamic limit: ask for it (idempotent, cheap)
+    (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (even) hipLaunchKernelGGL((image_wgrad_kernel<T, CB, CS, true>), dim3((unsigned)tiles), dim3(WG_THREADS), lds, st, a, u);
+  else hipLaunchKernelGGL((image_wgrad_kernel<T, CB, CS, false>), dim3((unsigned)tiles), dim3(WG_THREADS), lds, st, a, u);
+}
+
+// The tiles' partial sums of every model, added in a fixed order, where the gradients belong.  A block takes 16 groups of four columns of one
+// model; lane group q adds the tiles q, q + 16, ... in turn, eight loads in flight, then the groups' sums are added in order.
+// Blocks behind those: a model's pixel sums (the bias of G's last layer), or the label maps' gradients from class sums.
+__global__ __launch_bounds__(256) void image_wgrad_final_kernel(ImageGradArgs a, int col_blocks, int main_blocks, int sum_blocks) {
+  const int b = (int)blockIdx.x;
+  const int P = a.P, Cs = a.Cs;
+  if (b < main_blocks) {
+    __shared__ float4 red[16][16];
+    const int l = b / col_blocks, c = threadIdx.x & 15, q = threadIdx.x >> 4;
+    const int t0 = a.tpre[l], t1 = a.tpre[l + 1], i = (b - l * col_blocks) * 16 + c;      // 16 P Cs / 4 is a multiple of 16
+    const long long size4 = (long long)16 * P * Cs / 4;
+    const float4* p = reinterpret_cast<const float4*>(a.part) + i;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int k0 = t0 + q; k0 < t1; k0 += 8 * 16) {
+      float4 t[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (k0 + 16 * k < t1) t[k] = p[(long long)(k0 + 16 * k) * size4];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (k0 + 16 * k < t1) { s.x += t[k].x; s.y += t[k].y; s.z += t[k].z; s.w += t[k].w; }
+    }
+    red[q][c] = s;
+    __syncthreads();
+    if (q > 0) return;
+#pragma unroll
+    for (int g = 1; g < 16; ++g) {
+      const float4 t = red[g][c];
+      s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+    }
+    const int m = 4 * i / Cs, cs = 4 * i - m * Cs, tap = m / P, ch = m - tap * P;
+    float* const dw = a.dw + (long long)l * a.pstride + ((long long)tap * a.CBT + ch) * Cs + cs;
+    if (ch < a.CB) *reinterpret_cast<float4*>(dw) = s;
+    if (ch == a.CB) {
+      if (a.plane_labels) *reinterpret_cast<float4*>(dw + (long long)(a.L == 1 ? 0 : l) * Cs) = s;
+      if (tap == 5 && a.dbias) *reinterpret_cast<float4*>(a.dbias + (long long)l * a.pstride + cs) = s;
+    }
+    return;
+  }
+  if (b < main_blocks + sum_blocks) {
+    __shared__ float sh[256];
+    const int l = b - main_blocks, t0 = a.tpre[l], t1 = a.tpre[l + 1];
+    if (t0 == t1) return;
+    for (int c = 0; c < a.CB; ++c) {
+      float s = 0.f;
+      for (int t = t0 + (int)threadIdx.x; t < t1; t += 256) s += a.pixel_sums[t * 4 + c];
+      sh[threadIdx.x] = s;
+      __syncthreads();
+      for (int o = 128; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
+        __syncthreads();
+      }
+      if (threadIdx.x == 0) a.image_bias[(long long)l * a.pstride + c] = sh[0];
+      __syncthreads();
+    }
+    return;
+  }
+  const int e = (b - main_blocks - sum_blocks) * 256 + (int)threadIdx.x;      // (label, tap, cs), one model
+  if (e >= a.labels * 16 * Cs) return;
+  const int cs = e % Cs, tap = e / Cs % 16, label = e / (16 * Cs);
+  float s = 0.f;
+  for (int cls = 0; cls < 9; ++cls)
+    if (tap_inside(cls / 3, tap >> 2) && tap_inside(cls % 3, tap & 3)) s += a.label_sums[((long long)label * 9 + cls) * Cs + cs];
+  a.dw[((long long)tap * a.CBT + a.CB + label) * Cs + cs] = s;
+}
+
+// w[l][cs][tap * P + c] and, behind them, the rows to add: add[table][class][cs] = sum of the label map's taps inside + bias, each as stored
+template <typename T>
+__global__ __launch_bounds__(256) void pack_image_w_kernel(ImagePackArgs a, int w_blocks) {
+  const int P = a.P, Cs = a.Cs;
+  if ((int)blockIdx.x < w_blocks) {
+    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= (long long)a.L * 16 * P * Cs) return;
+    const int m = (int)(idx % (16 * P)), cs = (int)(idx / (16 * P) % Cs), l = (int)(idx / ((long long)16 * P * Cs));
+    const int tap = m / P, c = m - tap * P;
+    static_cast<T*>(a.packed)[idx] = from_float<T>(c < a.CB ? a.w[(long long)l * a.pstride + ((long long)tap * a.CBT + c) * Cs + cs] : 0.f);
+    return;
+  }
+  const int idx = ((int)blockIdx.x - w_blocks) * 256 + (int)threadIdx.x;
+  if (idx >= a.tables * 9 * Cs) return;
+  const int cs = idx % Cs, cls = idx / Cs % 9, t = idx / (9 * Cs), l = a.L == 1 ? 0 : t;
+  const float* w = a.w + (long long)l * a.pstride;
+  float v[16], s = 0.f;                                // (all loads first: the kernel is bound by their latency)
+  if (a.CBT > a.CB) {
+#pragma unroll
+    for (int tap = 0; tap < 16; ++tap) v[tap] = w[((long long)tap * a.CBT + a.CB + t) * Cs + cs];
+#pragma unroll
+    for (int tap = 0; tap < 16; ++tap)
+      if (tap_inside(cls / 3, tap >> 2) && tap_inside(cls % 3, tap & 3)) s += v[tap];
+  }
+  a.add[idx] = to_float(from_float<T>(s)) + (a.bias ? to_float(from_float<T>(a.bias[(long long)l * a.pstride + cs])) : 0.f);
+}
+
+// f(channels of the image, feature channels) as types
+template <typename F> bool with_channels(int CB, int Cs, F&& f) {
+  const auto cs = [&](auto cb) {
+    if (Cs == 64) f(cb, std::integral_constant<int, 64>{}); else f(cb, std::integral_constant<int, 128>{});
+  };
+  if (Cs != 64 && Cs != 128) return false;
+  if (CB == 1) cs(std::integral_constant<int, 1>{});
+  else if (CB == 2) cs(std::integral_constant<int, 2>{});
+  else if (CB == 3) cs(std::integral_constant<int, 3>{});
+  else if (CB == 4) cs(std::integral_constant<int, 4>{});
+  else return false;
+  return true;
+}
+
+}  // namespace
+
+int image_values(int CB) { return img_values(CB); }
+// Samples of a tile of the weight gradient: a round of blocks at the sizing batch, three a CU in bf16 and two in fp32.
+int image_tile_samples(int esize, int size_samples) { const int tiles = esize == 4 ? 480 : 700; return std::max(1, (size_samples + tiles - 1) / tiles); }
+
+template <typename T> void launch_image_conv(const ImageConvArgs& a, hipStream_t st) {
+  if (a.n == 0 || a.nseg == 0) return;
+  if (!a.img || !a.w || !a.out || !a.offs || !a.sample_model || (a.real && !a.perm) || a.Hs < 1)
+    return launch_fail("image-side convolution: null operand");
+  if ((long long)a.Hs * a.Hs * a.Cs * (long long)sizeof(T) >= (1LL << 31)) return launch_fail("image-side convolution: a sample of 2 GiB or larger");
+  if (!with_channels(a.CB, a.Cs, [&](auto cb, auto cs) { conv_one<T, cb.value, cs.value>(a, st); }))
+    launch_fail("image-side convolution: more than 4 image channels, or feature channels other than 64 / 128");
+}
+template void launch_image_conv<float>(const ImageConvArgs&, hipStream_t);
+template void launch_image_conv<bf16_t>(const ImageConvArgs&, hipStream_t);
+
+template <typename T> void launch_image_wgrad(const ImageWgradArgs& a, int ub_tiles, hipStream_t st) {
+  if (ub_tiles == 0 || a.nseg == 0) return;
+  if (!a.img || !a.dy || !a.part || !a.offs || !a.tpre || (a.L > 1 && !a.tmodel) || (a.real && !a.perm) || a.tile_samples < 1 || a.Hs < 1)
+    return launch_fail("image-side weight gradient: null operand");
+  if ((long long)a.Hs * a.Hs * a.Cs * (long long)sizeof(T) >= (1LL << 31)) return launch_fail("image-side weight gradient: a sample of 2 GiB or larger");
+  if (!with_channels(a.CB, a.Cs, [&](auto cb, auto cs) { wgrad_one<T, cb.value, cs.value>(a, ub_tiles, st); }))
+    launch_fail("image-side weight gradient: more than 4 image channels, or feature channels other than 64 / 128");
+}
+template void launch_image_wgrad<float>(const ImageWgradArgs&, int, hipStream_t);
+template void launch_image_wgrad<bf16_t>(const ImageWgradArgs&, int, hipStream_t);
+
+void launch_image_wgrad_final(const ImageGradArgs& a, hipStream_t st) {
+  if (!a.part || !a.dw || !a.tpre || a.pstride % 4 != 0 || ((uintptr_t)a.dw & 15) != 0 || ((uintptr_t)a.dbias & 15) != 0 || (a.labels > 0 && (!a.label_sums || a.L != 1)))
+    return launch_fail("image-side weight gradient: null operand, or gradients that are not 16-byte aligned");
+  const int cols = 16 * a.P * a.Cs / 64;
+  const long long main_blocks = (long long)a.L * cols, sum_blocks = a.image_bias ? a.L : 0, label_blocks = ((long long)a.labels * 16 * a.Cs + 255) / 256;
+  if (main_blocks + sum_blocks + label_blocks >= (1LL << 31)) return launch_fail("image-side weight gradient: more blocks than a launch can have");
+  hipLaunchKernelGGL(image_wgrad_final_kernel, dim3((unsigned)(main_blocks + sum_blocks + label_blocks)), dim3(256), 0, st, a, cols, (int)main_blocks,
+                     (int)sum_blocks);
+}
+
+template <typename T> void launch_pack_image_w(const ImagePackArgs& a, hipStream_t st) {
+  const long long w_blocks = ((long long)a.L * 16 * a.P * a.Cs + 255) / 256, add_blocks = a.add ? ((long long)a.tables * 9 * a.Cs + 255) / 256 : 0;
+  if (w_blocks + add_blocks >= (1LL << 31)) return launch_fail("image-side weights: more blocks than a launch can have");
+  hipLaunchKernelGGL((pack_image_w_kernel<T>), dim3((unsigned)(w_blocks + add_blocks)), dim3(256), 0, st, a, (int)w_blocks);
+}
+template void launch_pack_image_w<float>(const ImagePackArgs&, hipStream_t);
+template void launch_pack_image_w<bf16_t>(const ImagePackArgs&, hipStream_t);
+
+}  // namespace gan

@@ -1,19 +1,6 @@
-// The two layers that touch the image (1..4 channels): D's first convolution and G's last transposed
-// convolution.  With so few image channels their implicit-GEMM K (16 taps x channels) is tiny, so the image
-// side is expanded once into an explicit patch matrix ("im2col") of 64-column rows and the layers run on the
-// same MFMA engine as everything else, as plain row-by-row GEMMs:
-//   forward of D's first conv      : feat = patches x Wp^T
-//   its weight gradient            : dWp  = patches^T x dfeat
-//   data gradient of G's last convT: dfeat = patches(d image) x Wp^T ; its weight gradient likewise.
-//
-// A one-hot label map is a constant plane: its contribution to D's first convolution is a per-position bias
-// that only differs at the border (3 x 3 position classes), and its weight gradient is the sum of dfeat over the
-// positions where the tap falls inside the image.  Both are exact.  The patch matrix therefore carries, after the
-// 16*CB tap columns, one indicator column per (label slot, position class) and one constant column: the packed
-// weight holds the summed label-map taps and the bias there, so the forward GEMM adds them and the weight-
-// gradient GEMM returns the class sums and the bias gradient with no extra pass over the feature tensor.
-// One pair over many labels would need a thousand such columns: there the label maps' contributions are rows that the GEMM's
-// epilogue adds (EPI_LABEL_LRELU), and their gradient comes from class sums taken directly (launch_class_sums).
+// The layers that write an image of 1..4 channels, or sums over one: the transposed convolution onto the image (G's last layer, the data
+// gradient of D's first), the class sums that give the label maps of one pair over many labels their gradient, and the sums of an image's pixels.
+// The layers that read an image: image_conv.hip.
 #include <stdlib.h>
 
 #include <algorithm>
@@ -27,323 +14,7 @@ namespace gan {
 
 template <typename T> __device__ inline float ldf(const T* p) { return to_float(*p); }
 
-// Position class along one axis: 0 = first output row/col (tap 0 outside), 1 = interior, 2 = last (tap 3 outside).
-__device__ inline bool tap_valid(int cls, int k) { return !((cls == 0 && k == 0) || (cls == 2 && k == 3)); }
-
-__device__ inline void store8(float* p, const float (&v)[8]) {
-  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-  *reinterpret_cast<float4*>(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
-}
-__device__ inline void store8(bf16_t* p, const float (&v)[8]) {
-  uint4 t;
-  t.x = pack2_bf16(v[0], v[1]);
-  t.y = pack2_bf16(v[2], v[3]);
-  t.z = pack2_bf16(v[4], v[5]);
-  t.w = pack2_bf16(v[6], v[7]);
-  *reinterpret_cast<uint4*>(p) = t;
-}
-
-// One thread per 8 columns of one patch row.
-template <typename T>
-__global__ __launch_bounds__(256) void im2col_kernel(Im2colArgs a) {
-  const int g8 = a.Kc >> 3;
-  const int rps = a.Hs * a.Hs, Hb = 2 * a.Hs;
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long long)a.n * rps * g8) return;
-  const long long row = idx / g8;
-  const int m0 = (int)(idx - row * g8) * 8;
-  const int j = (int)(row / rps), pix = (int)(row - (long long)j * rps);
-  if (j >= a.offs[a.L]) return;
-  const int y = pix / a.Hs, x = pix - y * a.Hs;
-  const int ntap = 16 * a.CB;
-  const T* img = nullptr;
-  const float* real = nullptr;
-  if (a.img) img = static_cast<const T*>(a.img) + ((long long)a.seg * a.seg_samples + j) * Hb * Hb * a.CB;
-  else real = a.real + (long long)a.perm[j] * a.CB * Hb * Hb;
-  float v[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int m = m0 + e;
-    float val = 0.f;
-    if (m < ntap) {
-      const int tap = m / a.CB, cb = m - tap * a.CB;
-      const int iy = 2 * y - 1 + (tap >> 2), ix = 2 * x - 1 + (tap & 3);
-      if ((unsigned)iy < (unsigned)Hb && (unsigned)ix < (unsigned)Hb)
-        val = img ? ldf(img + ((long long)iy * Hb + ix) * a.CB + cb) : real[((long long)cb * Hb + iy) * Hb + ix];
-    } else if (a.constant) {
-      const int q = m - ntap;
-      if (q < 9 * a.nslot) val = (q / 9 == a.sample_slot[j] && q % 9 == pos_class(y, x, a.Hs)) ? 1.f : 0.f;
-      else if (q == 9 * a.nslot) val = 1.f;
-    }
-    v[e] = val;
-  }
-  store8(static_cast<T*>(a.out) + (((long long)a.seg * a.seg_samples + j) * rps + pix) * a.Kc + m0, v);
-}
-// Same result, one block per sample (small batches: several, each with its share of the patch rows): the sample's image goes through LDS once (NHWC, storage type, with a one-pixel
-// border of zeros so that no tap needs a bounds test), and every thread keeps the decoding of its 8 columns -- for a
-// tap column the offset of its element from the patch's first one -- while it walks down the sample's patch rows.
-template <typename T>
-__global__ __launch_bounds__(256) void im2col_sample_kernel(Im2colArgs a) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  T* tile = reinterpret_cast<T*>(lds_raw);                       // [Hb + 2][Hb + 2][CB]
-  const int j = blockIdx.x;
-  if (j >= a.offs[a.L]) return;
-  const int g8 = a.Kc >> 3;
-  const int nt = blockDim.x;                                      // a multiple of g8 (the launcher's choice), at most 256
-  const int rps = a.Hs * a.Hs, Hb = 2 * a.Hs, CB = a.CB;
-  const int npix = Hb * Hb, Hp = Hb + 2;
-  // the border: rows 0 and Hp - 1, columns 0 and Hp - 1
-  for (int t = threadIdx.x; t < 4 * Hp * CB; t += nt) {
-    const int side = t / (Hp * CB), r = t - side * (Hp * CB);
-    const int q = r / CB, cb = r - q * CB;
-    const int py = side == 0 ? 0 : (side == 1 ? Hp - 1 : q), px = side < 2 ? q : (side == 2 ? 0 : Hp - 1);
-    tile[(py * Hp + px) * CB + cb] = from_float<T>(0.f);
-  }
-  if (a.img) {
-    const T* img = static_cast<const T*>(a.img) + ((long long)a.seg * a.seg_samples + j) * npix * CB;
-    for (int t = threadIdx.x; t < npix * CB; t += nt) {
-      const int pxl = t / CB, cb = t - pxl * CB;
-      const int py = pxl / Hb, px = pxl - py * Hb;
-      tile[((py + 1) * Hp + px + 1) * CB + cb] = img[t];
-    }
-  } else {
-    const float* real = a.real + (long long)a.perm[j] * CB * npix;     // NCHW fp32; npix is a multiple of 4
-    const int nq = npix >> 2;
-    if ((reinterpret_cast<uintptr_t>(a.real) & 15) != 0) {             // caller's buffer not 16-byte aligned: scalar loads
-      for (int t = threadIdx.x; t < npix * CB; t += nt) {
-        const int cb = t / npix, pxl = t - cb * npix;
-        const int py = pxl / Hb, px = pxl - py * Hb;
-        tile[((py + 1) * Hp + px + 1) * CB + cb] = from_float<T>(real[t]);
-      }
-    } else
-    for (int t = threadIdx.x; t < CB * nq; t += nt) {
-      const int cb = t / nq, pxl = 4 * (t - cb * nq);
-      const float4 v = reinterpret_cast<const float4*>(real)[t];
-      const float vv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {                                    // (four pixels of a row, unless Hb % 4 == 2)
-        const int py = (pxl + k) / Hb, px = pxl + k - py * Hb;
-        tile[((py + 1) * Hp + px + 1) * CB + cb] = from_float<T>(vv[k]);
-      }
-    }
-  }
-  const int ntap = 16 * CB;                        // a multiple of 8: a group of 8 columns is all taps or none
-  const int slot = a.nslot > 0 ? a.sample_slot[j] : 0;
-  T* out = static_cast<T*>(a.out) + ((long long)a.seg * a.seg_samples + j) * rps * a.Kc;
-  // The columns after the taps (label-map indicators, the constant one, padding) depend on the pixel only through its
-  // position class: their 9 possible rows are written once, behind the image tile.
-  const int gtap = ntap >> 3, gsp = g8 - gtap;     // groups of tap columns, of the others
-  T* special = tile + Hp * Hp * CB + ((16 - ((Hp * Hp * CB * (int)sizeof(T)) & 15)) & 15) / (int)sizeof(T);   // 16-byte aligned; [9][gsp * 8]
-  for (int t = threadIdx.x; t < 9 * gsp * 8; t += nt) {
-    const int cls = t / (gsp * 8), q = t - cls * (gsp * 8);          // q: column - ntap
-    float val = 0.f;
-    if (a.constant) {
-      if (q < 9 * a.nslot) val = (q / 9 == slot && q % 9 == cls) ? 1.f : 0.f;
-      else if (q == 9 * a.nslot) val = 1.f;
-    }
-    special[t] = from_float<T>(val);
-  }
-  __syncthreads();
-  // A thread keeps its group of 8 columns (the block's thread count is a multiple of the groups per row) and walks
-  // down the patch rows in steps of threads / g8; the row's (y, x) is carried along instead of divided out, and the values
-  // travel as stored (no conversion): the kernel is bound by its vector instructions otherwise.
-  const int g = (int)threadIdx.x % g8, pstep = nt / g8 * (int)gridDim.y;
-  int off[8];                                      // tap columns: element offset from the patch's corner
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int m = g * 8 + e;
-    const int tap = m / CB, cb = m - tap * CB;
-    off[e] = m < ntap ? ((tap >> 2) * Hp + (tap & 3)) * CB + cb : 0;
-  }
-  const bool taps = g < gtap;
-  constexpr int VB = 8 * (int)sizeof(T);           // bytes of a group
-  int pix = ((int)blockIdx.y * nt + (int)threadIdx.x) / g8;
-  int y = pix / a.Hs, x = pix - y * a.Hs;
-  for (; pix < rps; pix += pstep) {
-    uint4 pk[VB / 16];
-    if (taps) {
-      const T* corner = tile + (2 * y * Hp + 2 * x) * CB;      // padded position of input pixel (2y - 1, 2x - 1)
-      T v[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = corner[off[e]];
-      if constexpr (sizeof(T) == 2) {
-        pk[0].x = (unsigned)v[0].v | ((unsigned)v[1].v << 16);
-        pk[0].y = (unsigned)v[2].v | ((unsigned)v[3].v << 16);
-        pk[0].z = (unsigned)v[4].v | ((unsigned)v[5].v << 16);
-        pk[0].w = (unsigned)v[6].v | ((unsigned)v[7].v << 16);
-      } else {
-        const unsigned* u = reinterpret_cast<const unsigned*>(v);
-        pk[0] = make_uint4(u[0], u[1], u[2], u[3]);
-        pk[VB / 16 - 1] = make_uint4(u[4], u[5], u[6], u[7]);
-      }
-    } else {
-      const uint4* src = reinterpret_cast<const uint4*>(special + (pos_class(y, x, a.Hs) * gsp + (g - gtap)) * 8);
-#pragma unroll
-      for (int k = 0; k < VB / 16; ++k) pk[k] = src[k];
-    }
-    uint4* dst = reinterpret_cast<uint4*>(out + (long long)pix * a.Kc + g * 8);
-#pragma unroll
-    for (int k = 0; k < VB / 16; ++k) dst[k] = pk[k];
-    x += pstep;
-    while (x >= a.Hs) { x -= a.Hs; ++y; }
-  }
-}
-template <typename T> void launch_im2col(const Im2colArgs& a, hipStream_t st) {
-  const long long tot = (long long)a.n * a.Hs * a.Hs * (a.Kc / 8);
-  if (tot == 0) return;
-  // the zero-bordered image tile, then (16-byte aligned) the 9 possible rows of the columns behind the taps
-  const size_t lds = (size_t)(2 * a.Hs + 2) * (2 * a.Hs + 2) * a.CB * sizeof(T) + 16 + (size_t)9 * (a.Kc - 16 * a.CB) * sizeof(T);
-  const int g8 = a.Kc / 8;
-  if (lds <= 64 * 1024 && g8 >= 1 && g8 <= 256 && a.Kc >= 16 * a.CB) {
-    if (lds > 48 * 1024)   // above the default dynamic limit: ask for it (idempotent, cheap)
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&im2col_sample_kernel<T>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    // blocks per sample: as many as bring a small batch to 512 (64 images of 28x28: 8.2 us with one, 6.7 with eight)
-    const unsigned split = (unsigned)std::max(1, std::min(512 / a.n, a.Hs * a.Hs / 16));
-    hipLaunchKernelGGL((im2col_sample_kernel<T>), dim3((unsigned)a.n, split), dim3((unsigned)(256 / g8 * g8)), lds, st, a);
-    return;
-  }
-  hipLaunchKernelGGL((im2col_kernel<T>), dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, a);
-}
-template void launch_im2col<float>(const Im2colArgs&, hipStream_t);
-template void launch_im2col<bf16_t>(const Im2colArgs&, hipStream_t);
-
-// the filter taps of a label's map that lie inside for the pixels of a class, summed
-__device__ inline float label_taps(const PackArgs& a, const float* w, int label, int cls, int cs) {
-  float v[16], s = 0.f;      // (all loads first: the kernel is bound by their latency)
-#pragma unroll
-  for (int tap = 0; tap < 16; ++tap) v[tap] = w[((long long)tap * a.CBT + a.CB + label) * a.Cs + cs];
-#pragma unroll
-  for (int tap = 0; tap < 16; ++tap)
-    if (tap_valid(cls / 3, tap >> 2) && tap_valid(cls % 3, tap & 3)) s += v[tap];
-  return s;
-}
-template <typename T>
-__global__ void pack_label_rows_kernel(PackArgs a) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= a.labels * 9 * a.Cs) return;
-  const int cs = idx % a.Cs, row = idx / a.Cs;
-  static_cast<T*>(a.label_rows)[idx] = from_float<T>(label_taps(a, a.w, row / 9, row % 9, cs));
-}
-// Wp[l][cs][m]: the taps, then the summed label-map taps per (slot, class), then the bias.
-template <typename T>
-__global__ void pack_w_kernel(PackArgs a) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long long)a.L * a.Cs * a.Kc) return;
-  const int m = (int)(idx % a.Kc);
-  const int cs = (int)((idx / a.Kc) % a.Cs);
-  const int l = (int)(idx / ((long long)a.Kc * a.Cs));
-  const float* w = a.w + (long long)l * a.pstride;
-  const int ntap = 16 * a.CB;
-  float val = 0.f;
-  if (m < ntap) {
-    const int tap = m / a.CB, cb = m - tap * a.CB;
-    val = w[((long long)tap * a.CBT + cb) * a.Cs + cs];
-  } else {
-    const int q = m - ntap;
-    if (q < 9 * a.nslot) {
-      const int slot = q / 9, cls = q - slot * 9;
-      if (a.CBT > a.CB) val = label_taps(a, w, a.L == 1 ? slot : l, cls, cs);
-    } else if (q == 9 * a.nslot && a.bias) {
-      val = a.bias[(long long)l * a.pstride + cs];
-    }
-  }
-  static_cast<T*>(a.wp)[idx] = from_float<T>(val);
-}
-template <typename T> void launch_pack_w(const PackArgs& a, hipStream_t st) {
-  const long long tot = (long long)a.L * a.Cs * a.Kc;
-  hipLaunchKernelGGL((pack_w_kernel<T>), dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, a);
-  if (a.labels > 0) hipLaunchKernelGGL((pack_label_rows_kernel<T>), dim3((unsigned)((a.labels * 9 * a.Cs + 255) / 256)), dim3(256), 0, st, a);
-}
-template void launch_pack_w<float>(const PackArgs&, hipStream_t);
-template void launch_pack_w<bf16_t>(const PackArgs&, hipStream_t);
-
-// dWp[l][m][cs] (fp32) -> the gradient block: taps, label-map channels (class sums over the positions where the
-// tap is inside), bias.
-// element (l, m, cs) of the packed gradient: the split partial blocks added in order
-__device__ inline float dwp_at(const PackArgs& a, int l, int m, int cs) {
-  float s = 0.f;
-  for (int k = 0; k < a.nsplit; ++k) s += a.dwp[(((long long)k * a.L + l) * a.Kc + m) * a.Cs + cs];
-  return s;
-}
-
-__global__ void unpack_dw_kernel(PackArgs a) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int Cs = a.Cs;
-  const long long n_tap = (long long)a.L * 16 * a.CB * Cs;
-  const int slots = a.labels > 0 ? a.labels : a.nslot;
-  const long long n_lab = a.CBT > a.CB ? (long long)a.L * slots * 16 * Cs : 0;
-  const long long n_bias = a.dbias ? (long long)a.L * Cs : 0;
-  const int ntap = 16 * a.CB;
-  if (idx < n_tap) {
-    const int cs = (int)(idx % Cs);
-    const int m = (int)((idx / Cs) % ntap);
-    const int l = (int)(idx / ((long long)Cs * ntap));
-    const int tap = m / a.CB, cb = m - tap * a.CB;
-    a.dw[(long long)l * a.pstride + ((long long)tap * a.CBT + cb) * Cs + cs] = dwp_at(a, l, m, cs);
-    return;
-  }
-  long long j = idx - n_tap;
-  if (j < n_lab) {
-    const int cs = (int)(j % Cs);
-    const int tap = (int)((j / Cs) % 16);
-    const int slot = (int)((j / ((long long)Cs * 16)) % slots);
-    const int l = (int)(j / ((long long)Cs * 16 * slots));
-    const int label = (a.L == 1) ? slot : l;
-    float s = 0.f;
-    for (int cls = 0; cls < 9; ++cls)
-      if (tap_valid(cls / 3, tap >> 2) && tap_valid(cls % 3, tap & 3))
-        s += a.labels > 0 ? a.label_sums[((long long)slot * 9 + cls) * Cs + cs] : dwp_at(a, l, ntap + slot * 9 + cls, cs);
-    a.dw[(long long)l * a.pstride + ((long long)tap * a.CBT + a.CB + label) * Cs + cs] = s;
-    return;
-  }
-  j -= n_lab;
-  if (j < n_bias) {
-    const int l = (int)(j / Cs), cs = (int)(j - (long long)l * Cs);
-    a.dbias[(long long)l * a.pstride + cs] = dwp_at(a, l, ntap + 9 * a.nslot, cs);
-  }
-}
-// part[0][i] <- part[0][i] + part[1][i] + ... (nsplit blocks of size4 float4 each), in a fixed order: lane group q of
-// a block adds the blocks q, q + 16, ... in turn, eight loads in flight, then the groups' sums are added in order.  One thread per element
-// would walk the splits one load after the other: with one model and 128 splits that chain alone took 0.13 ms, and four groups
-// with four loads in flight 6.5-7.9 us (sixteen: 3.2-4.8).
-__global__ __launch_bounds__(256) void reduce_splits_kernel(float* __restrict__ part, long long size4, int nsplit) {
-  __shared__ float4 red[16][16];
-  const int c = threadIdx.x & 15, q = threadIdx.x >> 4;
-  const long long i = (long long)blockIdx.x * 16 + c;
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (i < size4) {
-    const float4* p = reinterpret_cast<const float4*>(part) + i;
-#pragma unroll 8
-    for (int k = q; k < nsplit; k += 16) {
-      const float4 t = p[(long long)k * size4];
-      acc.x += t.x; acc.y += t.y; acc.z += t.z; acc.w += t.w;
-    }
-  }
-  red[q][c] = acc;
-  __syncthreads();
-  if (q == 0 && i < size4) {
-#pragma unroll
-    for (int g = 1; g < 16; ++g) {
-      const float4 t = red[g][c];
-      acc.x += t.x; acc.y += t.y; acc.z += t.z; acc.w += t.w;
-    }
-    reinterpret_cast<float4*>(part)[i] = acc;
-  }
-}
-void launch_unpack_dw(const PackArgs& a0, hipStream_t st) {
-  PackArgs a = a0;
-  const long long block = (long long)a.L * a.Kc * a.Cs;       // floats per split
-  if (a.nsplit > 4 && block % 4 == 0) {
-    // many row splits: add them up with a kernel that has enough threads, in place into the first block
-    hipLaunchKernelGGL(reduce_splits_kernel, dim3((unsigned)((block / 4 + 15) / 16)), dim3(256), 0, st, const_cast<float*>(a.dwp), block / 4,
-                       a.nsplit);
-    a.nsplit = 1;
-  }
-  const long long tot = (long long)a.L * a.Cs * (16 * a.CB + (a.labels > 0 ? a.labels : a.nslot) * 16 + 1);
-  hipLaunchKernelGGL(unpack_dw_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, a);
-}
-
-// Class sums of a layer's output gradient, for label maps without indicator columns.  First per sample: a block takes one sample
+// Class sums of a layer's output gradient, for one pair's label maps.  First per sample: a block takes one sample
 // of one segment and up to 128 channels, a thread 8 channels of every 16th pixel row; inner rows meet in LDS, in a fixed order.
 // It reads the tensor once, 16 bytes a lane, and is bound by that.  Then per slot: a block owns 64 sums of a slot; of every 1024 samples
 // its sixteen waves take the slot's in turn, eight loads in flight, and the waves' sums meet in LDS in order.  That bounds the chain of

@@ -84,35 +84,6 @@ void launch_bn_bwd_reduce(const NormArgs& a, const int* tpre, const int* tmodel,
 void launch_bn_bwd_final(const NormArgs& a, const int* tpre, int ub_tiles, const float* partial, hipStream_t st);
 template <typename T> void launch_bn_bwd_apply(const NormArgs& a, hipStream_t st);
 
-// The layers touching the image (1..4 channels) run as row-by-row GEMMs over an explicit patch matrix.
-struct Im2colArgs {
-  const void* img;          // NHWC image-side tensor (storage type), side 2*Hs, indexed by absolute sample; or NULL
-  const float* real;        // caller's NCHW fp32 batch, gathered through perm (used when img == NULL)
-  const int* perm;
-  void* out;                // [rows][Kc] (storage type), rows indexed by absolute sample
-  const int* offs;
-  const int* sample_slot;
-  int L, n, CB, Hs, Kc;
-  int nslot;                // class indicators behind the tap columns: 9 * nslot
-  int constant;             // 1: one constant column behind those
-  int seg, seg_samples;     // absolute segment of both the source tensor and the output rows
-};
-template <typename T> void launch_im2col(const Im2colArgs& a, hipStream_t st);
-
-struct PackArgs {
-  const float* w;           // model 0 master weights [16][CBT][Cs]; per-model stride pstride
-  const float* bias;        // [Cs] (may be NULL)
-  float* dw;                // unpack: gradient block of model 0, same layout as w
-  float* dbias;             // unpack: may be NULL
-  long long pstride;
-  void* wp;                 // pack: [L][Cs][Kc] storage type
-  const float* dwp;         // unpack: [nsplit][L][Kc][Cs] fp32 partial blocks
-  // Without indicator columns (nslot == 0, one model): the label maps of `labels` slots as rows to add to the output
-  int labels;
-  void* label_rows;         // pack: [labels][9][Cs] storage type
-  const float* label_sums;  // unpack: [labels][9][Cs], the sums of the layer's output gradient
-  int L, CB, CBT, Cs, Kc, nslot, nsplit;
-};
 // sums[slot][class][cs] = sum of dy over the samples of the slot (both segments, in order) and the pixels of the class
 struct ClassSumArgs {
   const void* dy;           // [rows][Cs] storage type, rows indexed by absolute sample
@@ -123,8 +94,6 @@ struct ClassSumArgs {
   int L, n, Hs, Cs, labels, seg_first, nseg, seg_samples;
 };
 template <typename T> void launch_class_sums(const ClassSumArgs& a, hipStream_t st);
-template <typename T> void launch_pack_w(const PackArgs& a, hipStream_t st);
-void launch_unpack_dw(const PackArgs& a, hipStream_t st);
 
 // Transposed convolution onto the image side (G's last layer; data gradient of D's first layer).
 struct UpImgArgs {
@@ -144,6 +113,60 @@ struct UpImgArgs {
   const int* perm;
 };
 template <typename T> void launch_up_img(const UpImgArgs& a, hipStream_t st);
+
+// The strided convolutions that read an image (image_conv.hip): D's first layer, and the gradients of G's last, whose output gradient is an image.
+// Images: NHWC in the storage type, indexed by absolute sample; segment 0 may be the caller's NCHW fp32 batch instead, gathered through perm.
+int image_values(int CB);                    // values a pixel has in a tile: 2, 4 or 8; packed weights have 16 times as many a feature channel
+struct ImageConvArgs {
+  const void* img;
+  const float* real;
+  const int* perm;
+  const void* w;            // [L][Cs][16 P], launch_pack_image_w
+  const float* add;         // [tables][9][Cs]: added to the outputs by position class, or NULL
+  const int* sample_slot;   // the table of a sample, or NULL: its model's
+  void* out;                // [rows][Cs], rows indexed by absolute sample
+  const int* offs;
+  const int* sample_model;
+  int L, n, CB, Hs, Cs, seg_first, nseg, seg_samples;
+  float slope;              // factor below zero
+};
+template <typename T> void launch_image_conv(const ImageConvArgs& a, hipStream_t st);
+int image_tile_samples(int esize, int size_samples);    // samples of a model that a tile of the weight gradient takes
+struct ImageWgradArgs {
+  const void* img;
+  const float* real;
+  const int* perm;
+  const void* dy;           // [rows][Cs], rows indexed by absolute sample
+  float* part;              // [tiles][16 P][Cs], partial sums of every tile of tile_samples samples
+  float* pixel_sums;        // [tiles][4]: the sums of the image's pixels, or NULL
+  const int* offs;
+  const int* tpre;          // the prefix array and models of the tiles (tmodel NULL: one model)
+  const int* tmodel;
+  int L, CB, Hs, Cs, seg_first, nseg, seg_samples, tile_samples;
+};
+template <typename T> void launch_image_wgrad(const ImageWgradArgs& a, int ub_tiles, hipStream_t st);
+struct ImageGradArgs {      // the tiles' sums into the gradient blocks
+  const float* part;
+  const float* pixel_sums;
+  const int* tpre;
+  float* dw;                // model 0 [16][CBT][Cs]; pstride between models
+  float* dbias;             // [Cs], or NULL
+  float* image_bias;        // [CB], from the pixel sums, or NULL
+  const float* label_sums;  // labels > 0 (one model): [labels][9][Cs], the class sums of the layer's output gradient
+  long long pstride;
+  int L, CB, CBT, Cs, P, labels;
+  int plane_labels;         // the model's one label map has the gradient of the ones
+};
+void launch_image_wgrad_final(const ImageGradArgs& a, hipStream_t st);
+struct ImagePackArgs {
+  const float* w;           // model 0 master weights [16][CBT][Cs]; pstride between models
+  const float* bias;        // [Cs], or NULL
+  void* packed;             // [L][Cs][16 P] storage type
+  float* add;               // [tables][9][Cs], or NULL
+  long long pstride;
+  int L, CB, CBT, Cs, P, tables;
+};
+template <typename T> void launch_pack_image_w(const ImagePackArgs& a, hipStream_t st);
 
 int img_bias_chunks(int L);          // pixel chunks per model of the image-side bias gradient
 struct ImgBiasArgs {
