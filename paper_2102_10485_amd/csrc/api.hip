@@ -824,6 +824,7 @@ void image_wgrad_call(gan_ctx* c, Net& net, const ConvLayer& cl, const void* img
   ImageGradArgs g = {};
   g.part = c->img_part; g.pixel_sums = a.pixel_sums; g.tpre = a.tpre; g.dw = net.g + cl.w;
   g.dbias = first ? net.g + cl.bias : nullptr; g.image_bias = first ? nullptr : net.g + cl.bias;
+  g.k3 = c->paper;
   g.labels = first ? c->labels : 0; g.label_sums = c->label_sums; g.plane_labels = first && cl.CBT > cl.Cb && c->labels == 0;
   g.pstride = net.P; g.L = c->L; g.CB = cl.Cb; g.CBT = cl.CBT; g.Cs = cl.Cs; g.P = image_values(cl.Cb);
   launch_image_wgrad_final(g, c->st);
@@ -1110,7 +1111,6 @@ void paper_d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_im
   const ConvLayer& c1 = D.conv[0];
   if (param_grads) {
     image_wgrad_call<T>(c, D, c1, c->xd, real, c->bufA, seg_first, nseg, n);
-    for (const ConvLayer& cl : D.conv) launch_clear_fourth_taps(D.g + cl.w, D.P, c->L, cl.CBT, cl.Cs, c->st);
   }
   if (to_image) up_img_call<T>(c, D, c1, c->bufA, c->dimg, c->xd, 2, 1, n);
 }
@@ -1197,9 +1197,12 @@ AdamArgs adam_args(gan_ctx* c, Net& net) {
   a.shadow_t = net.shadow_d; a.split_u = net.split_u; a.split_d = net.split_d; a.plane = net.PS;
   for (size_t i = 0; i < net.conv.size(); ++i) {
     if (!on_engine(c, net, i)) continue;
-    a.reg_w[a.nregions] = net.conv[i].w; a.reg_part[a.nregions] = net.conv[i].part; a.reg_cb[a.nregions] = net.conv[i].Cb; a.reg_cs[a.nregions] = net.conv[i].Cs;
+    const ConvLayer& cl = net.conv[i];
+    a.reg_w[a.nregions] = cl.w; a.reg_part[a.nregions] = cl.part; a.reg_cb[a.nregions] = cl.Cb; a.reg_cs[a.nregions] = cl.Cs;
+    a.reg_cb_real[a.nregions] = c->paper ? cl.cb_real : cl.Cb; a.reg_cs_real[a.nregions] = c->paper ? cl.cs_real : cl.Cs;
     ++a.nregions;
   }
+  a.k3 = c->paper;                                 // (D: its k3 filters are held as k4 ones)
   adam_plan(a);
   return a;
 }

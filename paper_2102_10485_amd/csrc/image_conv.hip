@@ -643,6 +643,7 @@ __global__ __launch_bounds__(256) void image_wgrad_final_kernel(ImageGradArgs a,
       s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
     }
     const int m = 4 * i / Cs, cs = 4 * i - m * Cs, tap = m / P, ch = m - tap * P;
+    if (a.k3 && ((tap >> 2) == 3 || (tap & 3) == 3)) return;
     float* const dw = a.dw + (long long)l * a.pstride + ((long long)tap * a.CBT + ch) * Cs + cs;
     if (ch < a.CB) *reinterpret_cast<float4*>(dw) = s;
     if (ch == a.CB) {

@@ -156,6 +156,7 @@ struct ImageGradArgs {      // the tiles' sums into the gradient blocks
   long long pstride;
   int L, CB, CBT, Cs, P, labels;
   int plane_labels;         // the model's one label map has the gradient of the ones
+  int k3;                   // the taps of the fourth row and column are no parameters: not written
 };
 void launch_image_wgrad_final(const ImageGradArgs& a, hipStream_t st);
 struct ImagePackArgs {
@@ -230,6 +231,8 @@ struct AdamArgs {
   int nregions;
   long long reg_w[ADAM_MAX_REGIONS], reg_part[ADAM_MAX_REGIONS];
   int reg_cb[ADAM_MAX_REGIONS], reg_cs[ADAM_MAX_REGIONS];
+  int reg_cb_real[ADAM_MAX_REGIONS], reg_cs_real[ADAM_MAX_REGIONS];      // channels from here on are padding: zeros that no update moves
+  int k3;                                 // the taps of the fourth row and column are no parameters (zeros likewise, whatever their gradients hold)
   int reg_tile0[ADAM_MAX_REGIONS + 1];    // prefix of 64 x 64 tiles (filled by the launcher)
   int ngaps;
   long long gap_lo[ADAM_MAX_REGIONS + 1], gap_hi[ADAM_MAX_REGIONS + 1];
@@ -316,8 +319,6 @@ template <typename T> void launch_point_fwd(const PointArgs& a, hipStream_t st);
 template <typename T> void launch_col_sum(const PointArgs& a, float* out, long long out_stride, hipStream_t st);
 // batch statistics (mean, biased variance, 1/sqrt(var + eps)) of a stored tensor with C channels per row, of which those from `real` on are padding
 template <typename T> void launch_bn_stats_direct(const NormArgs& a, int real, hipStream_t st);
-// zero the gradient entries of the fourth tap row and column of a k3 filter held as [16][Cb][Cs]
-void launch_clear_fourth_taps(float* dw, long long pstride, int L, int Cb, int Cs, hipStream_t st);
 
 // Conv k3 s1 p1 between Cin feature channels (64 or 128) and CO image channels (1..4), side H, NHWC, rows model-major.
 struct Conv3Args {

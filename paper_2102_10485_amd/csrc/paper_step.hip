@@ -260,21 +260,4 @@ template <typename T> void launch_bn_stats_direct(const NormArgs& a, int real, h
 template void launch_bn_stats_direct<float>(const NormArgs&, int, hipStream_t);
 template void launch_bn_stats_direct<bf16_t>(const NormArgs&, int, hipStream_t);
 
-// A k3 convolution held in the engine's k4 layout [16][Cb][Cs]: the fourth tap row and column are not parameters.
-// Their gradient entries (the engine computes all 16) are cleared before Adam, so they stay exactly zero.
-__global__ void clear_fourth_taps_kernel(float* __restrict__ dw, long long pstride, int L, int per_tap) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;      // (l, 7 taps, per_tap)
-  if (idx >= (long long)L * 7 * per_tap) return;
-  const int e = (int)(idx % per_tap);
-  const int k = (int)((idx / per_tap) % 7);
-  const int l = (int)(idx / ((long long)per_tap * 7));
-  const int tap = k < 4 ? 12 + k : 3 + 4 * (k - 4);       // ky = 3 (taps 12..15), then kx = 3 for ky = 0, 1, 2
-  dw[(long long)l * pstride + (long long)tap * per_tap + e] = 0.f;
-}
-void launch_clear_fourth_taps(float* dw, long long pstride, int L, int Cb, int Cs, hipStream_t st) {
-  const long long tot = (long long)L * 7 * Cb * Cs;
-  if (tot == 0) return;
-  hipLaunchKernelGGL(clear_fourth_taps_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, dw, pstride, L, Cb * Cs);
-}
-
 }  // namespace gan

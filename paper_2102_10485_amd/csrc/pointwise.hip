@@ -1058,6 +1058,9 @@ void launch_split_weights(const SplitArgs& a, hipStream_t st) {
 // LDS - the transposed storage-type copy, so that the new weights are read from HBM once.  fp32 storage: both copies as bf16 parts (a
 // quarter more to write: twenty 32x32 pairs 665 -> 806 us a step), which spares every GEMM block the split of its columns (8.1 -> 7.1 ms); with few rows
 // a model the transposed copy in fp32 alone.
+// The tables' discriminator, whose k3 filters of 16 and 32 channels are held as k4 ones of 64: nothing of the fourth taps and of the padded channels
+// is read or written (a hundred pairs 136 -> 83 us a launch, and the four launches that cleared their gradients, 37 us, are gone).  The
+// same for the padded columns of G's linear layer, 28 of every 128, is slower than updating them: 566 -> 633 us for the holes in the lines.
 template <typename T>
 __global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a) {
   constexpr int TSTRIDE = 64 * (int)sizeof(T) + 16;            // bytes per transposed row (64 cb)
@@ -1077,6 +1080,8 @@ __global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a) {
     const int tcs = q % tcs_n; q /= tcs_n;
     const int tcb = q % tcb_n;
     const int tap = q / tcb_n;
+    if (a.k3 && ((tap >> 2) == 3 || (tap & 3) == 3)) continue;
+    const int cb_real = a.reg_cb_real[r] - tcb * 64, cs_real = a.reg_cs_real[r] - tcs * 64;      // inside the tile
     const long long base = (long long)l * a.P + a.reg_w[r], part = 3 * (long long)l * a.plane + a.reg_part[r];
     const float bc1 = a.bc[2 * l], bc2 = a.bc[2 * l + 1];
     const int c4 = (threadIdx.x & 15) * 4, r0 = threadIdx.x >> 4;
@@ -1085,6 +1090,7 @@ __global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const long long o = o0 + 16LL * i * Cs;
+      if (r0 + 16 * i >= cb_real || c4 >= cs_real) continue;
       gs[i] = ld_stream(a.g + o);
       ths[i] = ld_stream(a.theta + o);
       ms[i] = ld_stream(a.m + o);
@@ -1093,6 +1099,7 @@ __global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = r0 + 16 * i;                                // cb inside the tile
+      if (row >= cb_real || c4 >= cs_real) continue;
       const long long o = o0 + 16LL * i * Cs;
       float tt[4];
       adam_update4(a, bc1, bc2, gs[i], ths[i], ms[i], vs[i], tt);
@@ -1108,6 +1115,20 @@ __global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {                                 // eight values of a transposed row at a time
       const int cid = threadIdx.x + 256 * i, cs = cid >> 3, ch = (cid & 7) * 8;
+      if (ch + 8 > cb_real || cs >= cs_real) {                    // padding, or the last real channels one by one
+        for (int k = 0; k < 8 && ch + k < cb_real && cs < cs_real; ++k) {
+          const T v = *reinterpret_cast<const T*>(tile + cs * TSTRIDE + (ch + k) * (int)sizeof(T));
+          const long long o = ((long long)tap * Cs + tcs * 64 + cs) * Cb + tcb * 64 + ch + k;
+          if constexpr (sizeof(T) == 2) static_cast<T*>(a.shadow_t)[base + o] = v;
+          else if (a.split_u) {
+            unsigned h, m, l_;
+            split_pair(v, 0.f, h, m, l_);
+            unsigned short* const d = a.split_d + part + o;
+            d[0] = (unsigned short)h; d[a.plane] = (unsigned short)m; d[2 * a.plane] = (unsigned short)l_;
+          } else static_cast<T*>(a.shadow_t)[(long long)l * a.plane + a.reg_part[r] + o] = v;
+        }
+        continue;
+      }
       const uint4* src = reinterpret_cast<const uint4*>(tile + cs * TSTRIDE + ch * (int)sizeof(T));
       const long long o = ((long long)tap * Cs + tcs * 64 + cs) * Cb + tcb * 64 + ch;
       if constexpr (sizeof(T) == 2) *reinterpret_cast<uint4*>(static_cast<T*>(a.shadow_t) + base + o) = src[0];
@@ -1143,7 +1164,7 @@ bool adam_plan(AdamArgs& a) {
       ++a.ngaps;
     }
     if (r < a.nregions) {
-      if (a.reg_cb[r] % 64 || a.reg_cs[r] % 64 || (a.split_u ? !a.split_d : !a.shadow_t) || a.plane % 8) {
+      if (a.reg_cb[r] % 64 || a.reg_cs[r] % 64 || a.reg_cb_real[r] > a.reg_cb[r] || a.reg_cs_real[r] > a.reg_cs[r] || (a.split_u ? !a.split_d : !a.shadow_t) || a.plane % 8) {
         launch_fail("Adam: tiled regions need channel counts that are multiples of 64");
         return false;
       }
