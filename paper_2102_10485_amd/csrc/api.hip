@@ -725,10 +725,18 @@ NormArgs norm_args(gan_ctx* c, Net& net, int C, int rps, long long gamma, long l
 
 // BatchNorm with batch statistics + activation: x -> y (with running statistics both are part of the GEMM: EPI_BN)
 // gemm_mode / gemm_rps describe the GEMM that produced x and left per-tile column sums in c->stat_partial
+// the normalised and activated tensor; head: and D's head behind it
 template <typename T>
-void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool update_running, int gemm_mode, int gemm_rps, int col_groups = 1) {      // y NULL: the statistics only
-  a.x = x; a.y = y;
+void apply_call(gan_ctx* c, const NormArgs& a, const HeadArgs* head) {
   const double elems = (double)a.n * a.nseg * a.rps * a.C;
+  Scope s(c, head ? "bn_apply_head" : "bn_apply", 0, 2 * elems * sizeof(T));
+  if (head) launch_bn_apply_head<T>(a, *head, c->st);
+  else launch_bn_apply<T>(a, c->st);
+}
+template <typename T>
+void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool update_running, int gemm_mode, int gemm_rps, int col_groups = 1,
+                const HeadArgs* head = nullptr) {      // y NULL: the statistics only
+  a.x = x; a.y = y;
   {
     const ConvTile tile = layer_tile(c, gemm_mode, a.C * col_groups, gemm_rps, a.nseg);   // of the GEMM that left the partials (N = C * col_groups)
     const int tr = conv_tile_rows((int)sizeof(T), tile), gemm_phases = gemm_mode == MODE_UP ? 4 : 1;
@@ -736,9 +744,7 @@ void bn_forward(gan_ctx* c, NormArgs a, const void* x, void* y, bool update_runn
     launch_bn_stats_from_partial(a, c->stat_partial, tpre_of(c, gemm_rps, tr), ub_tiles(c, a.n, gemm_rps, tr), ub_tiles(c, c->NB, gemm_rps, tr),
                                  gemm_phases, col_groups, tr, gemm_rps, conv_stat_split((int)sizeof(T), tile, c->presplit && gemm_mode != MODE_DENSE), c->st);
   }
-  if (!y) return;
-  Scope s(c, "bn_apply", 0, 2 * elems * sizeof(T));
-  launch_bn_apply<T>(a, c->st);
+  if (y) apply_call<T>(c, a, head);
 }
 
 // dy (w.r.t. the activated output) -> dx (w.r.t. the pre-normalisation tensor), plus dgamma / dbeta
@@ -825,6 +831,7 @@ void image_wgrad_call(gan_ctx* c, Net& net, const ConvLayer& cl, const void* img
   g.part = c->img_part; g.pixel_sums = a.pixel_sums; g.tpre = a.tpre; g.dw = net.g + cl.w;
   g.dbias = first ? net.g + cl.bias : nullptr; g.image_bias = first ? nullptr : net.g + cl.bias;
   g.k3 = c->paper;
+  if (first && c->head_rsplit > 1) g.head = {c->head_part, net.g + net.fc_w, net.g + net.fc_b, net.K, c->head_rsplit};
   g.labels = first ? c->labels : 0; g.label_sums = c->label_sums; g.plane_labels = first && cl.CBT > cl.Cb && c->labels == 0;
   g.pstride = net.P; g.L = c->L; g.CB = cl.Cb; g.CBT = cl.CBT; g.Cs = cl.Cs; g.P = image_values(cl.Cb);
   launch_image_wgrad_final(g, c->st);
@@ -887,16 +894,15 @@ void d_forward(gan_ctx* c, int n, Cost cost, bool update_running, const float* r
   const float slope = c->cfg.leaky_slope;
   image_conv_call<T>(c, D.conv[0], c->xd, real, c->dact[0], false, seg_first, nseg, n);      // first conv (+label maps, bias, LeakyReLU)
   const int nl = (int)D.conv.size();
+  const HeadArgs head = head_args(c, n, cost);
   for (int j = 1; j < nl; ++j) {
     const ConvLayer& cl = D.conv[j];
     conv_call<T>(c, "gemm_down", MODE_DOWN, EPI_NONE, c->dact[j - 1], layer_weights(c, D, cl, false), c->dpre[j], nullptr, cl.Cb,
                  cl.Cs, 2 * cl.Hs, cl.Hs, seg_first, nseg, n, 0, -1.0, true);
     bn_forward<T>(c, norm_args<T>(c, D, cl.Cs, cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->d_mean[j], c->d_var[j], c->d_rstd[j],
                                   c->d_sums[j], seg_first, nseg, n, slope),
-                  c->dpre[j], c->dact[j], update_running, MODE_DOWN, cl.Hs * cl.Hs);
+                  c->dpre[j], c->dact[j], update_running, MODE_DOWN, cl.Hs * cl.Hs, 1, j == nl - 1 ? &head : nullptr);
   }
-  Scope s(c, "head_fwd", 0, sizeof(T) * (double)n * nseg * D.K);
-  launch_head_fwd<T>(head_args(c, n, cost), c->st);
 }
 
 // Backward through D.  param_grads: fill D's gradient block (both segments summed).  to_image: continue down to
@@ -1001,12 +1007,11 @@ void with_dropout(gan_ctx* c, PointArgs& a, int layer, int pass0, int step_add) 
 
 // BatchNorm whose batch statistics are taken from the stored tensor (`real` channels and padding); no activation after it
 template <typename T>
-void bn_forward_direct(gan_ctx* c, NormArgs a, int real, const void* x, void* y, float eps, bool update_running) {
+void bn_forward_direct(gan_ctx* c, NormArgs a, int real, const void* x, void* y, float eps, bool update_running, const HeadArgs* head = nullptr) {
   a.x = x; a.y = y; a.eps = eps; a.slope = 1.f;
   launch_bn_stats_direct<T>(a, real, c->st);
   if (update_running) launch_bn_running(a, c->st);
-  Scope s(c, "bn_apply", 0, 2.0 * a.n * a.nseg * a.rps * a.C * sizeof(T));
-  launch_bn_apply<T>(a, c->st);
+  apply_call<T>(c, a, head);
 }
 
 // G's last convolution reads the block in front of it before its BatchNorm and activation
@@ -1066,6 +1071,7 @@ void paper_d_forward(gan_ctx* c, int n, Cost cost, bool update_running, int pass
     launch_point_fwd<T>(a, c->st);
   }
   const int nl = (int)D.conv.size();
+  const HeadArgs head = head_args(c, n, cost);
   for (int j = 1; j < nl; ++j) {
     const ConvLayer& cl = D.conv[j];
     conv_call<T>(c, "gemm_down", MODE_DOWN, EPI_NONE, c->dact[j - 1], layer_weights(c, D, cl, false), c->dpre[j], nullptr, cl.Cb,
@@ -1076,10 +1082,8 @@ void paper_d_forward(gan_ctx* c, int n, Cost cost, bool update_running, int pass
     { Scope s(c, "bias_act_dropout", 0, 2.0 * n * nseg * cl.Hs * cl.Hs * cl.cs_real * sizeof(T)); launch_point_fwd<T>(a, c->st); }
     bn_forward_direct<T>(c, norm_args<T>(c, D, cl.Cs, cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->d_mean[j], c->d_var[j], c->d_rstd[j],
                                          c->d_sums[j], seg_first, nseg, n, 1.f),
-                         cl.cs_real, c->dpre[j], c->dact[j], f.bn_eps, update_running);
+                         cl.cs_real, c->dpre[j], c->dact[j], f.bn_eps, update_running, j == nl - 1 ? &head : nullptr);
   }
-  Scope s(c, "head_fwd", 0, sizeof(T) * (double)n * nseg * D.K);
-  launch_head_fwd<T>(head_args(c, n, cost), c->st);
 }
 
 template <typename T>
@@ -1484,8 +1488,9 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
            dev_alloc(c, (void**)&c->dw4, (size_t)L * per * 4) &&
            dev_alloc(c, (void**)&c->c3_part, (size_t)conv3_wgrad_splits(L) * L * 9 * last.Cb * last.Cs * 4);
     }
-    // the linear head's weight gradient: blocks of 1024 columns per model, rows split when that leaves the chip idle
-    c->head_rsplit = (int)std::min<long long>(std::max<long long>(512 / ((long long)L * ((c->D.K + 1023) / 1024)), 1), 64);
+    // the linear head's weight gradient: blocks of 1024 columns per model, rows split when that leaves the chip idle.  A block is a chain of waits for its
+    // rows; 512 and 1024 blocks: twenty 32x32 pairs in fp32 47 and 36 us, ten 28x28 pairs 37 and 28, eight 64x64 pairs in bf16 27 and 19 (2048: 32, 26, 21).
+    c->head_rsplit = (int)std::min<long long>(std::max<long long>(1024 / ((long long)L * ((c->D.K + 1023) / 1024)), 1), 64);
     if (c->head_rsplit > 1) ok = ok && dev_alloc(c, (void**)&c->head_part, (size_t)c->head_rsplit * L * (c->D.K + 4) * 4);
   }
   {

@@ -614,8 +614,9 @@ void wgrad_one(const ImageWgradArgs& a, int tiles, hipStream_t st) {
 
 // The tiles' partial sums of every model, added in a fixed order, where the gradients belong.  A block takes 16 groups of four columns of one
 // model; lane group q adds the tiles q, q + 16, ... in turn, eight loads in flight, then the groups' sums are added in order.
-// Blocks behind those: a model's pixel sums (the bias of G's last layer), or the label maps' gradients from class sums.
-__global__ __launch_bounds__(256) void image_wgrad_final_kernel(ImageGradArgs a, int col_blocks, int main_blocks, int sum_blocks) {
+// Blocks behind those: a model's pixel sums (the bias of G's last layer), the label maps' gradients from class sums, the row splits of the linear
+// head's weight gradient (a launch of its own takes 4.6 us whatever it does).
+__global__ __launch_bounds__(256) void image_wgrad_final_kernel(ImageGradArgs a, int col_blocks, int main_blocks, int sum_blocks, int label_blocks) {
   const int b = (int)blockIdx.x;
   const int P = a.P, Cs = a.Cs;
   if (b < main_blocks) {
@@ -668,6 +669,19 @@ __global__ __launch_bounds__(256) void image_wgrad_final_kernel(ImageGradArgs a,
       if (threadIdx.x == 0) a.image_bias[(long long)l * a.pstride + c] = sh[0];
       __syncthreads();
     }
+    return;
+  }
+  if (b >= main_blocks + sum_blocks + label_blocks) {
+    const HeadSplits& h = a.head;
+    const long long idx = (long long)(b - main_blocks - sum_blocks - label_blocks) * 256 + threadIdx.x;
+    if (idx >= (long long)a.L * (h.K + 1)) return;
+    const int l = (int)(idx / (h.K + 1)), k = (int)(idx - (long long)l * (h.K + 1));      // (index K: the bias term)
+    if (a.tpre[l] == a.tpre[l + 1]) return;              // no samples
+    float s = 0.f;
+#pragma unroll 8
+    for (int sp = 0; sp < h.rsplit; ++sp) s += h.part[((long long)sp * a.L + l) * (h.K + 4) + k];     // loads in flight together, sum in order
+    if (k < h.K) h.dw[(long long)l * a.pstride + k] = s;
+    else h.db[(long long)l * a.pstride] = s;
     return;
   }
   const int e = (b - main_blocks - sum_blocks) * 256 + (int)threadIdx.x;      // (label, tap, cs), one model
@@ -753,9 +767,9 @@ void launch_image_wgrad_final(const ImageGradArgs& a, hipStream_t st) {
     return launch_fail("image-side weight gradient: null operand, or gradients that are not 16-byte aligned");
   const int cols = 16 * a.P * a.Cs / 64;
   const long long main_blocks = (long long)a.L * cols, sum_blocks = a.image_bias ? a.L : 0, label_blocks = ((long long)a.labels * 16 * a.Cs + 255) / 256;
-  if (main_blocks + sum_blocks + label_blocks >= (1LL << 31)) return launch_fail("image-side weight gradient: more blocks than a launch can have");
-  hipLaunchKernelGGL(image_wgrad_final_kernel, dim3((unsigned)(main_blocks + sum_blocks + label_blocks)), dim3(256), 0, st, a, cols, (int)main_blocks,
-                     (int)sum_blocks);
+  const long long head_blocks = a.head.part ? ((long long)a.L * (a.head.K + 1) + 255) / 256 : 0, blocks = main_blocks + sum_blocks + label_blocks + head_blocks;
+  if (blocks >= (1LL << 31)) return launch_fail("image-side weight gradient: more blocks than a launch can have");
+  hipLaunchKernelGGL(image_wgrad_final_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a, cols, (int)main_blocks, (int)sum_blocks, (int)label_blocks);
 }
 
 template <typename T> void launch_pack_image_w(const ImagePackArgs& a, hipStream_t st) {

@@ -145,7 +145,14 @@ struct ImageWgradArgs {
   int L, CB, Hs, Cs, seg_first, nseg, seg_samples, tile_samples;
 };
 template <typename T> void launch_image_wgrad(const ImageWgradArgs& a, int ub_tiles, hipStream_t st);
+// The row splits of the linear head's weight gradient (HeadArgs, rsplit > 1), which another kernel of D's backward pass adds up along the way
+struct HeadSplits {
+  const float* part;        // NULL: none
+  float *dw, *db;
+  int K, rsplit;
+};
 struct ImageGradArgs {      // the tiles' sums into the gradient blocks
+  HeadSplits head;          // (same pstride)
   const float* part;
   const float* pixel_sums;
   const int* tpre;
@@ -202,11 +209,12 @@ struct HeadArgs {
   Cost cost;
   float scale;
   // weight gradient: rsplit > 1 shares every model's rows among rsplit blocks per K chunk; their partial sums go to
-  // part[rsplit][L][K + 4] (the bias term at index K) and are added in order by a second kernel
+  // part[rsplit][L][K + 4] (the bias term at index K) and are added in order later (HeadSplits)
   float* part;
   int rsplit;
 };
-template <typename T> void launch_head_fwd(const HeadArgs& a, hipStream_t st);
+// BatchNorm and activation of the last feature map (as launch_bn_apply), the logits and the cost's derivatives by them
+template <typename T> void launch_bn_apply_head(const NormArgs& a, const HeadArgs& h, hipStream_t st);
 // the costs and the data gradient; weights: the weight gradient too
 template <typename T> void launch_head_bwd(const HeadArgs& a, bool weights, hipStream_t st);
 

@@ -316,6 +316,10 @@ template <int N> __device__ inline void load_params(const float* p, float (&v)[N
     v[k] = t.x; v[k + 1] = t.y; v[k + 2] = t.z; v[k + 3] = t.w;
   }
 }
+__device__ inline void store_cached(float* p, const float (&v)[4]) { store4(p, v); }        // (through the caches, for a tensor that is read next)
+__device__ inline void store_cached(bf16_t* p, const float (&v)[8]) {
+  *reinterpret_cast<uint4*>(p) = make_uint4(pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3]), pack2_bf16(v[4], v[5]), pack2_bf16(v[6], v[7]));
+}
 __device__ inline void storev(float* p, const float (&v)[4]) { store4(p, v); }
 __device__ inline void storev(bf16_t* p, const float (&v)[8]) {
   uint4 t;
@@ -467,10 +471,10 @@ static unsigned apply_split(const NormArgs& a, int epv) {
 // Row by row a thread had one or two loads on their way.  A hundred 32x32 pairs in bf16, GB/s: forward 5507 -> 5783, backward 5669 -> 5987; eight 64x64
 // pairs 4702 -> 4820, 5021 -> 5120.  (Four rows: the backward pass with an activation in front, PRE, gets slower, 5033 -> 4776 with the whole of the
 // tables' networks, so two there.)
-template <int U, typename P, typename R>
+template <int U, int NT = 256, typename P, typename R>
 __device__ __forceinline__ void walk_rows(int rps, int cg, P&& params, R&& rows) {
-  const int step = 256 * gridDim.z, total = rps * cg;
-  int t = blockIdx.z * 256 + threadIdx.x;
+  const int step = NT * gridDim.z, total = rps * cg;
+  int t = blockIdx.z * NT + threadIdx.x;
   if (t >= total) return;
   if (step % cg == 0) {
     const int dr = step / cg, g = t % cg;
@@ -784,40 +788,73 @@ __device__ inline float sigmoid_f(float u) {
 // scale*mean softplus(-s_fake') on segment seg_first.
 __device__ inline float head_sign(const HeadArgs& a, int seg) { return a.cost == COST_D && seg == 1 ? 1.f : -1.f; }
 
-// one wave per row: logit = <feat[row], w[model]> + b[model], and the cost's derivative by it
-template <typename T>
-__global__ __launch_bounds__(256) void head_fwd_kernel(HeadArgs a) {
-  const int lane = threadIdx.x & 63;
-  const long long wrow = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (wrow >= (long long)a.n * a.nseg) return;
-  const int sidx = (int)(wrow / a.n), j = (int)(wrow - (long long)sidx * a.n);
+// BatchNorm and activation of D's last feature map, its linear head and the cost's derivative: a block per (sample, segment) normalises as
+// bn_apply_kernel does and multiplies what it stores with the head's weights.  The head read the stored tensor once more and was a launch of its own:
+// a hundred 32x32 pairs, bf16, both segments 71 + 49 -> 101 us, one 38 + 27 -> 55; ten 28x28 pairs, fp32, 25 + 16 -> 28 and 14 + 11 -> 17; one 4.2 + 6.0 ->
+// 6.4.  The head's weight gradient reads the tensor next, which past the caches takes it longer (ten pairs, bf16, 26 us for 17).
+// A sample of few values (a 2 x 2 map of the tables' networks) is one wave's.
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void bn_apply_head_kernel(NormArgs a, HeadArgs h) {
+  constexpr int EPV = Vec16<T>::N;
+  __shared__ float red[NT / 64];
+  const int j = blockIdx.x, seg = a.seg_first + (int)blockIdx.y;
   if (j >= a.offs[a.L]) return;
   const int l = a.sample_model[j];
-  const long long r = (long long)(a.seg_first + sidx) * a.seg_samples + j;
-  const T* f = static_cast<const T*>(a.feat) + r * a.K;
-  const float* w = a.w + (long long)l * a.pstride;
-  float acc = 0.f;
-#pragma unroll 8
-  for (int k = lane * 4; k < a.K; k += 256) {     // (eight steps' loads in flight, added in order)
-    float v[4];
-    load4(f + k, v);
-    const float4 ww = *reinterpret_cast<const float4*>(w + k);
-    acc += v[0] * ww.x + v[1] * ww.y + v[2] * ww.z + v[3] * ww.w;
-  }
+  const long long row = (long long)seg * a.seg_samples + j;
+  const T* x = static_cast<const T*>(a.x) + row * h.K;
+  T* y = static_cast<T*>(a.y) + row * h.K;
+  const float* w = h.w + (long long)l * h.pstride;
+  const long long so = (long long)(seg * a.L + l) * a.C;
+  float sc[EPV], mu[EPV], be[EPV], acc = 0.f;
+  walk_rows<4, NT>(a.rps, a.C / EPV, [&](int g) __attribute__((always_inline)) {
+    float rs[EPV];
+    load_params(a.gamma + (long long)l * a.pstride + g * EPV, sc);
+    load_params(a.rstd + so + g * EPV, rs);
+    load_params(a.mean + so + g * EPV, mu);
+    load_params(a.beta + (long long)l * a.pstride + g * EPV, be);
+#pragma unroll
+    for (int k = 0; k < EPV; ++k) sc[k] *= rs[k];
+  }, [&](auto count, int r, int dr, int g) __attribute__((always_inline)) {
+    constexpr int U = decltype(count)::value;
+    float v[U][EPV], ww[U][EPV];
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      loadv(x + (long long)(r + i * dr) * a.C + g * EPV, v[i]);
+      load_params(w + (long long)(r + i * dr) * a.C + g * EPV, ww[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+#pragma unroll
+      for (int k = 0; k < EPV; ++k) {
+        const float u = (v[i][k] - mu[k]) * sc[k] + be[k];
+        v[i][k] = u > 0.f ? u : u * a.slope;
+        acc += to_float(from_float<T>(v[i][k])) * ww[i][k];
+      }
+      store_cached(y + (long long)(r + i * dr) * a.C + g * EPV, v[i]);
+    }
+  });
   acc = wave_sum(acc);
-  if (lane == 0) {
-    const float logit = acc + a.b[(long long)l * a.pstride], sign = head_sign(a, a.seg_first + sidx);
-    a.logits[r] = logit;
-    a.dlogits[r] = a.scale * sign * sigmoid_f(sign * logit) * (1.f / (float)(a.offs[l + 1] - a.offs[l]));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float sum = red[0];
+#pragma unroll
+    for (int i = 1; i < NT / 64; ++i) sum += red[i];
+    const float logit = sum + h.b[(long long)l * h.pstride], sign = head_sign(h, seg);
+    h.logits[row] = logit;
+    h.dlogits[row] = h.scale * sign * sigmoid_f(sign * logit) * (1.f / (float)(a.offs[l + 1] - a.offs[l]));
   }
 }
-template <typename T> void launch_head_fwd(const HeadArgs& a, hipStream_t st) {
-  const long long rows = (long long)a.n * a.nseg;
-  if (rows == 0) return;
-  hipLaunchKernelGGL((head_fwd_kernel<T>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, a);
+template <typename T> void launch_bn_apply_head(const NormArgs& a, const HeadArgs& h, hipStream_t st) {
+  if (a.n == 0 || a.nseg == 0) return;
+  if (h.K != a.rps * a.C || h.seg_first != a.seg_first || h.nseg != a.nseg || h.seg_samples != a.seg_samples)
+    return launch_fail("linear head: its rows are not the normalised tensor's samples");
+  const dim3 grid((unsigned)a.n, (unsigned)a.nseg);
+  if (h.K / Vec16<T>::N <= 128) hipLaunchKernelGGL((bn_apply_head_kernel<T, 64>), grid, dim3(64), 0, st, a, h);
+  else hipLaunchKernelGGL((bn_apply_head_kernel<T, 256>), grid, dim3(256), 0, st, a, h);
 }
-template void launch_head_fwd<float>(const HeadArgs&, hipStream_t);
-template void launch_head_fwd<bf16_t>(const HeadArgs&, hipStream_t);
+template void launch_bn_apply_head<float>(const NormArgs&, const HeadArgs&, hipStream_t);
+template void launch_bn_apply_head<bf16_t>(const NormArgs&, const HeadArgs&, hipStream_t);
 
 // One block per model: its cost, and the step count of the update that follows.
 __device__ inline void head_loss(const HeadArgs& a, int l) {
@@ -920,18 +957,6 @@ __global__ __launch_bounds__(256) void head_bwd_kernel(HeadArgs a, int w_blocks,
     head_data<T>(a, (int)sidx, (q - sidx * data_blocks) * 256u + threadIdx.x);
   }
 }
-// the row splits' partial sums, added in order (index K: the bias term)
-__global__ void head_bwd_w_final_kernel(HeadArgs a) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (long long)a.L * (a.K + 1)) return;
-  const int l = (int)(idx / (a.K + 1)), k = (int)(idx - (long long)l * (a.K + 1));
-  if (a.offs[l + 1] == a.offs[l]) return;
-  float s = 0.f;
-#pragma unroll 8
-  for (int sp = 0; sp < a.rsplit; ++sp) s += a.part[((long long)sp * a.L + l) * (a.K + 4) + k];     // loads in flight together, sum in order
-  if (k < a.K) a.dw[(long long)l * a.pstride + k] = s;
-  else a.db[(long long)l * a.pstride] = s;
-}
 template <typename T> void launch_head_bwd(const HeadArgs& a, bool weights, hipStream_t st) {
   if (a.nseg == 0 || a.L == 0) return;
   const long long tot = (long long)a.n * (a.K / 8), data_blocks = (tot + 255) / 256;
@@ -941,10 +966,6 @@ template <typename T> void launch_head_bwd(const HeadArgs& a, bool weights, hipS
   const long long w_blocks = weights ? (long long)((a.K + 1023) / 1024) * a.L * rsplit : 0, blocks = w_blocks + a.L + data_blocks * a.nseg;
   if (blocks >= (1LL << 31)) return launch_fail("linear head: more blocks than a launch can have");
   hipLaunchKernelGGL((head_bwd_kernel<T>), dim3((unsigned)blocks), dim3(256), 0, st, a, (int)w_blocks, (unsigned)data_blocks);
-  if (weights && rsplit > 1) {
-    const long long fin = (long long)a.L * (a.K + 1);
-    hipLaunchKernelGGL(head_bwd_w_final_kernel, dim3((unsigned)((fin + 255) / 256)), dim3(256), 0, st, a);
-  }
 }
 template void launch_head_bwd<float>(const HeadArgs&, bool, hipStream_t);
 template void launch_head_bwd<bf16_t>(const HeadArgs&, bool, hipStream_t);
