@@ -237,8 +237,13 @@ void order_after(gan_ctx* c, hipStream_t later, hipStream_t earlier) {
   hipStreamWaitEvent(later, e, 0);
 }
 
-template <typename T> void adam_region_call(gan_ctx* c, const AdamArgs& a, int region, hipStream_t st);
+template <typename T> void adam_region_call(gan_ctx* c, const AdamArgs& a, int region, hipStream_t st, const AdamSplits& sp = {});
 template <typename T> void pack_image_call(gan_ctx* c, const Net& net);
+// a region whose update a backward pass leaves to the last launch of the update, with the row splits of its gradient
+struct AdamTail {
+  int region = -1;
+  AdamSplits splits;
+};
 
 double valid_tap_fraction(int Hs) {   // k4 s2 p1: per axis 2 of the 4*Hs (row, tap) pairs fall outside
   const double f = (4.0 * Hs - 2.0) / (4.0 * Hs);
@@ -677,10 +682,12 @@ int wgrad_ksplit(const gan_ctx* c, int Cb, int Cs, int ntaps, int Hs, int nseg) 
 }
 
 // ksplit == 0: split as wgrad_ksplit says, through c->wg_part, and leave the sum in dW; ksplit >= 1: the caller's
-// own split (partials left at dW + split * L * stride).
+// own split (partials left at dW + split * L * stride).  leave (ksplit == 0): what the update of these weights, which has to come before the
+// next of these calls, adds up itself.
 template <typename T>
 void wgrad_call(gan_ctx* c, const char* name, const void* Big, const void* Small, float* dW, long long stride, int Cb, int Cs,
-                int Hs, int ntaps, int nseg, int n, double flops_alg = -1.0, int ksplit = 0, hipStream_t st = nullptr) {
+                int Hs, int ntaps, int nseg, int n, double flops_alg = -1.0, int ksplit = 0, hipStream_t st = nullptr,
+                AdamSplits* leave = nullptr) {
   if (!st) st = c->st;
   WgradArgs a = {};
   a.Big = Big; a.Small = Small; a.dW = dW; a.offs = c->rb.offs; a.order = c->rb.order; a.dw_stride = stride;
@@ -705,7 +712,8 @@ void wgrad_call(gan_ctx* c, const char* name, const void* Big, const void* Small
     Scope s(c, wgrad_variant_name((int)sizeof(T), a), flops_alg >= 0 ? flops_alg : 2.0 * rows * Cb * Cs * ntaps * frac, bytes, detail, st);
     launch_wgrad<T>(a, st);
   }
-  if (auto_split > 1) launch_sum_splits(c->wg_part, dW, stride, layer, c->L, auto_split, st);
+  if (leave) *leave = {c->wg_part, auto_split};
+  else if (auto_split > 1) launch_sum_splits(c->wg_part, dW, stride, layer, c->L, auto_split, st);
 }
 
 template <typename T>
@@ -787,7 +795,7 @@ void pack_image_call(gan_ctx* c, const Net& net) {
   const bool first = &net == &c->D;                 // (G's last layer: as its gradients read it)
   const ConvLayer& cl = first ? net.conv.front() : net.conv.back();
   ImagePackArgs a = {};
-  a.w = net.theta + cl.w; a.bias = first ? net.theta + cl.bias : nullptr; a.packed = first ? c->wpD : c->wpG; a.add = first ? c->addD : nullptr;
+  a.w = net.theta + cl.w; a.packed = first ? c->wpD : c->wpG; a.add = first && cl.CBT > cl.Cb ? c->addD : nullptr;
   a.pstride = net.P; a.L = c->L; a.CB = cl.Cb; a.CBT = cl.CBT; a.Cs = cl.Cs; a.P = image_values(cl.Cb); a.tables = c->labels > 0 ? c->labels : c->L;
   Scope s(c, "pack_w", 0, (double)c->L * cl.Cs * 16 * (4.0 * cl.CBT + a.P * sizeof(T)));
   launch_pack_image_w<T>(a, c->st);
@@ -797,7 +805,8 @@ void pack_image_call(gan_ctx* c, const Net& net) {
 template <typename T>
 void image_conv_call(gan_ctx* c, const ConvLayer& cl, const void* img, const float* real, void* out, bool grad, int seg_first, int nseg, int n) {
   ImageConvArgs a = {};
-  a.img = img; a.real = real; a.perm = c->rb.perm; a.w = grad ? c->wpG : c->wpD; a.add = grad ? nullptr : c->addD;
+  a.img = img; a.real = real; a.perm = c->rb.perm; a.w = grad ? c->wpG : c->wpD; a.add = grad || cl.CBT == cl.Cb ? nullptr : c->addD;
+  a.bias = grad ? nullptr : c->D.theta + cl.bias; a.bias_stride = c->D.P;
   a.sample_slot = !grad && c->labels > 0 ? c->rb.sample_slot : nullptr;
   a.out = out; a.offs = c->rb.offs; a.sample_model = c->rb.sample_model;
   a.L = c->L; a.n = n; a.CB = cl.Cb; a.Hs = cl.Hs; a.Cs = cl.Cs; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n;
@@ -911,7 +920,7 @@ void d_forward(gan_ctx* c, int n, Cost cost, bool update_running, const float* r
 // every part of it; the update of a convolution's weights is enqueued beside the chain as soon as its gradient is complete and its
 // data gradient has read the old ones.
 template <typename T>
-void d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_image, const float* real = nullptr, const AdamArgs* adam = nullptr) {
+void d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_image, const float* real = nullptr, const AdamArgs* adam = nullptr, AdamTail* tail = nullptr) {
   Net& D = c->D;
   const int seg_first = segments_of(cost).first, nseg = segments_of(cost).count;
   hipStream_t side = side_stream(c);
@@ -922,6 +931,7 @@ void d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_image, c
     launch_head_bwd<T>(head_args(c, n, cost), param_grads, c->st);
   }
   int pending = -1;                // region of D's planned update whose turn comes next
+  AdamSplits splits;               // and the row splits of its gradient
   for (int j = nl - 1; j >= 1; --j) {
     const ConvLayer& cl = D.conv[j];
     // in place: the pre-normalisation tensor is not needed again in this step, its gradient takes its place
@@ -933,8 +943,8 @@ void d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_image, c
       // Beside the chain, in this order: the update of the layer above (its data gradient, which read the old weights,
       // is done; being bandwidth-bound it pairs with the data-gradient GEMM below), then this layer's weight gradient.
       order_after(c, side, c->st);
-      if (adam && pending >= 0) adam_region_call<T>(c, *adam, pending, side);
-      wgrad_call<T>(c, "gemm_wgrad", c->dact[j - 1], dx, D.g + cl.w, D.P, cl.Cb, cl.Cs, cl.Hs, 16, nseg, n, -1.0, 0, side);
+      if (adam && pending >= 0) adam_region_call<T>(c, *adam, pending, side, splits);
+      wgrad_call<T>(c, "gemm_wgrad", c->dact[j - 1], dx, D.g + cl.w, D.P, cl.Cb, cl.Cs, cl.Hs, 16, nseg, n, -1.0, 0, side, adam ? &splits : nullptr);
       pending = j - 1;
     }
     // data gradient; for the first conv's output the LeakyReLU derivative is applied in the epilogue
@@ -942,8 +952,12 @@ void d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_image, c
                  j == 1 ? c->dact[0] : nullptr, cl.Cs, cl.Cb, cl.Hs, cl.Hs, seg_first, nseg, n);
   }
   if (param_grads && adam && pending >= 0) {
-    order_after(c, side, c->st);
-    adam_region_call<T>(c, *adam, pending, side);
+    if (side == c->st && adam_region_joins_rest(*adam, pending)) {
+      *tail = {pending, splits};
+    } else {
+      order_after(c, side, c->st);
+      adam_region_call<T>(c, *adam, pending, side, splits);
+    }
   }
   const ConvLayer& c1 = D.conv[0];
   if (param_grads) image_wgrad_call<T>(c, D, c1, c->xd, real, c->bufA, seg_first, nseg, n);
@@ -953,7 +967,7 @@ void d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_image, c
 
 // Backward through G from dimg (fake segment) = d cost / d (pre-tanh output).
 template <typename T>
-void g_backward(gan_ctx* c, int n, const AdamArgs* adam = nullptr) {
+void g_backward(gan_ctx* c, int n, const AdamArgs* adam = nullptr, AdamTail* tail = nullptr) {
   Net& G = c->G;
   hipStream_t side = side_stream(c);
   const int nl = (int)G.conv.size();
@@ -962,6 +976,7 @@ void g_backward(gan_ctx* c, int n, const AdamArgs* adam = nullptr) {
   image_wgrad_call<T>(c, G, last, dlast, nullptr, c->gact[nl - 1], 0, 1, n);
   image_conv_call<T>(c, last, dlast, nullptr, c->bufA, true, 0, 1, n);
   int pending = -1;
+  AdamSplits splits;
   for (int i = nl - 2; i >= 0; --i) {
     const ConvLayer& cl = G.conv[i];
     void* dx = c->gpre[i + 1];     // in place, as in D
@@ -969,8 +984,8 @@ void g_backward(gan_ctx* c, int n, const AdamArgs* adam = nullptr) {
                                    c->g_rstd[i + 1], c->g_sums[i + 1], 0, 1, n, 0.f),
                    c->gpre[i + 1], c->bufA, dx, true);
     order_after(c, side, c->st);
-    if (adam && pending >= 0) adam_region_call<T>(c, *adam, pending, side);      // as in D
-    wgrad_call<T>(c, "gemm_wgrad", dx, c->gact[i], G.g + cl.w, G.P, cl.Cb, cl.Cs, cl.Hs, 16, 1, n, -1.0, 0, side);
+    if (adam && pending >= 0) adam_region_call<T>(c, *adam, pending, side, splits);      // as in D
+    wgrad_call<T>(c, "gemm_wgrad", dx, c->gact[i], G.g + cl.w, G.P, cl.Cb, cl.Cs, cl.Hs, 16, 1, n, -1.0, 0, side, adam ? &splits : nullptr);
     pending = i;
     conv_call<T>(c, "gemm_down", MODE_DOWN, EPI_NONE, dx, layer_weights(c, G, cl, false), c->bufA, nullptr, cl.Cb, cl.Cs,
                  2 * cl.Hs, cl.Hs, 0, 1, n);
@@ -980,7 +995,10 @@ void g_backward(gan_ctx* c, int n, const AdamArgs* adam = nullptr) {
                  c->gpre[0], c->bufA, c->gpre[0], true);
   // (row-split partial sums share one scratch area with the weight gradients above: same stream)
   order_after(c, side, c->st);
-  if (adam && pending >= 0) adam_region_call<T>(c, *adam, pending, side);
+  if (adam && pending >= 0) {
+    if (side == c->st && adam_region_joins_rest(*adam, pending) && (splits.n < 2 || wgrad_ksplit(c, G.J, G.Kp, 1, 1, 1) == 1)) *tail = {pending, splits};
+    else adam_region_call<T>(c, *adam, pending, side, splits);
+  }
   wgrad_call<T>(c, "gemm_wgrad_dense", c->gpre[0], c->zin, G.g + G.fc_w, G.P, G.J, G.Kp, 1, 1, 1, n, -1.0, 0, side);
   order_after(c, c->st, side);
 }
@@ -1214,24 +1232,26 @@ AdamArgs adam_args(gan_ctx* c, Net& net) {
 // one; fp32: both as three planes, or with few rows a model the transposed one alone)
 inline double adam_bytes_per_element(const gan_ctx* c) { return 28.0 + (c->bf16 ? 2.0 : 0.0); }
 template <typename T>
-void adam_region_call(gan_ctx* c, const AdamArgs& a, int region, hipStream_t st) {
+void adam_region_call(gan_ctx* c, const AdamArgs& a, int region, hipStream_t st, const AdamSplits& sp) {
   double elems = 0;
   for (int r = 0; r < a.nregions; ++r)
     if (region < 0 || r == region) elems += 16.0 * a.reg_cb[r] * a.reg_cs[r];
   Scope s(c, "adam", 0, (double)c->L * elems * (adam_bytes_per_element(c) + (c->bf16 ? 2.0 : c->presplit ? 12.0 : 4.0)), nullptr, st);
-  launch_adam_region<T>(a, region, st);
+  launch_adam_region<T>(a, region, sp, st);
 }
-// what is left of a planned update once the regions are done (or enqueued beside): the gaps, and the packed weights of
-// the image-side layer, rebuilt from the new master weights
+// what is left of a planned update once the regions are done (or enqueued beside): the gaps, the operand of the image-side layer, and
+// the region that a backward pass has left (AdamTail)
 template <typename T>
-void adam_rest_call(gan_ctx* c, Net& net, const AdamArgs& a) {
-  {
-    double elems = 0;
-    for (int r = 0; r < a.ngaps; ++r) elems += (double)(a.gap_hi[r] - a.gap_lo[r]);
-    Scope s(c, "adam", 0, (double)c->L * elems * adam_bytes_per_element(c));
-    launch_adam_gaps(a, c->st);
-  }
-  pack_image_call<T>(c, net);
+void adam_rest_call(gan_ctx* c, Net& net, const AdamArgs& a, const AdamTail& tail = {}) {
+  double elems = tail.region >= 0 ? 16.0 * a.reg_cb[tail.region] * a.reg_cs[tail.region] : 0;
+  for (int r = 0; r < a.ngaps; ++r) elems += (double)(a.gap_hi[r] - a.gap_lo[r]);
+  const bool first = &net == &c->D;
+  const ConvLayer& cl = first ? net.conv.front() : net.conv.back();
+  AdamImage im;
+  im.w = cl.w; im.packed = first ? c->wpD : c->wpG; im.add = first && cl.CBT > cl.Cb ? c->addD : nullptr;
+  im.CB = cl.Cb; im.CBT = cl.CBT; im.Cs = cl.Cs; im.P = image_values(cl.Cb); im.tables = c->labels > 0 ? c->labels : c->L;
+  Scope s(c, "adam", 0, (double)c->L * elems * adam_bytes_per_element(c));
+  launch_adam_rest<T>(a, im, tail.region, tail.splits, c->st);
 }
 // the whole update on the caller's stream
 template <typename T>
@@ -1271,16 +1291,18 @@ void train_step(gan_ctx* c, const int32_t* label_ids, const float* noise, const 
   c->order_next = 0;
   {
     const AdamArgs aD = adam_args<T>(c, c->D);
-    d_backward<T>(c, n, COST_D, true, false, real, &aD); // Eq. 3; weight gradients and the convolutions' updates beside the chain
-    adam_rest_call<T>(c, c->D, aD);
+    AdamTail tail;
+    d_backward<T>(c, n, COST_D, true, false, real, &aD, &tail); // Eq. 3; weight gradients and the convolutions' updates beside the chain
+    adam_rest_call<T>(c, c->D, aD, tail);
     order_after(c, c->st, side_stream(c));
   }
   d_forward<T>(c, n, COST_G, true);                // updated D on the same fake batch
   d_backward<T>(c, n, COST_G, false, true);        // Eq. 4 (negated: minimised); only data gradients: theta_D is not G's to move
   {
     const AdamArgs aG = adam_args<T>(c, c->G);
-    g_backward<T>(c, n, &aG);
-    adam_rest_call<T>(c, c->G, aG);
+    AdamTail tail;
+    g_backward<T>(c, n, &aG, &tail);
+    adam_rest_call<T>(c, c->G, aG, tail);
     order_after(c, c->st, side_stream(c));
   }
 }

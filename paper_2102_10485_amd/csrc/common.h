@@ -133,6 +133,15 @@ __device__ inline int pos_class(int y, int x, int Hs) {
 
 // Whether the tap k (one axis) of the pixels of class cls along it (0 first, 1 inner, 2 last) lies inside the map.
 __device__ inline bool tap_inside(int cls, int k) { return !((cls == 0 && k == 0) || (cls == 2 && k == 3)); }
+// what the sixteen taps of a constant map add up to at a class of positions, as the storage type holds it
+template <typename T>
+__device__ inline float label_class_sum(const float (&v)[16], int cls) {
+  float s = 0.f;
+#pragma unroll
+  for (int tap = 0; tap < 16; ++tap)
+    if (tap_inside(cls / 3, tap >> 2) && tap_inside(cls % 3, tap & 3)) s += v[tap];
+  return to_float(from_float<T>(s));
+}
 
 template <typename T> void launch_conv(int mode, int epi, const ConvArgs& a, hipStream_t st);
 template <typename T> void launch_wgrad(const WgradArgs& a, hipStream_t st);

@@ -196,11 +196,16 @@ __global__ __launch_bounds__(256) void image_conv_kernel(ImageConvArgs a, Units 
   }
   float* const add = reinterpret_cast<float*>(lds + PL * plane);
   unsigned char* const patch = lds + PL * plane + 9 * CS * 4 + wave * (32 * OUT_ROW);
-  if (a.add) {
-    const float* src = a.add + (long long)(a.sample_slot ? a.sample_slot[j] : l) * 9 * CS;
-    for (int i = tid; i < 9 * CS / 4; i += 256) reinterpret_cast<float4*>(add)[i] = reinterpret_cast<const float4*>(src)[i];
-  } else {
-    for (int i = tid; i < 9 * CS / 4; i += 256) reinterpret_cast<float4*>(add)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  {
+    const float4* src = a.add ? reinterpret_cast<const float4*>(a.add + (long long)(a.sample_slot ? a.sample_slot[j] : l) * 9 * CS) : nullptr;
+    const float4* bias = a.bias ? reinterpret_cast<const float4*>(a.bias + l * a.bias_stride) : nullptr;
+    const auto in_t = [](float x) { return to_float(from_float<T>(x)); };
+    for (int i = tid; i < 9 * CS / 4; i += 256) {
+      float4 t = src ? src[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+      const float4 q = bias ? bias[i % (CS / 4)] : make_float4(0.f, 0.f, 0.f, 0.f);
+      t.x += in_t(q.x); t.y += in_t(q.y); t.z += in_t(q.z); t.w += in_t(q.w);
+      reinterpret_cast<float4*>(add)[i] = t;
+    }
   }
   image.put(lds, plane, u, tid, 256, nullptr);
   __syncthreads();
@@ -709,15 +714,10 @@ __global__ __launch_bounds__(256) void pack_image_w_kernel(ImagePackArgs a, int 
   if (idx >= a.tables * 9 * Cs) return;
   const int cs = idx % Cs, cls = idx / Cs % 9, t = idx / (9 * Cs), l = a.L == 1 ? 0 : t;
   const float* w = a.w + (long long)l * a.pstride;
-  float v[16], s = 0.f;                                // (all loads first: the kernel is bound by their latency)
-  if (a.CBT > a.CB) {
+  float v[16];                                         // (all loads first: the kernel is bound by their latency)
 #pragma unroll
-    for (int tap = 0; tap < 16; ++tap) v[tap] = w[((long long)tap * a.CBT + a.CB + t) * Cs + cs];
-#pragma unroll
-    for (int tap = 0; tap < 16; ++tap)
-      if (tap_inside(cls / 3, tap >> 2) && tap_inside(cls % 3, tap & 3)) s += v[tap];
-  }
-  a.add[idx] = to_float(from_float<T>(s)) + (a.bias ? to_float(from_float<T>(a.bias[(long long)l * a.pstride + cs])) : 0.f);
+  for (int tap = 0; tap < 16; ++tap) v[tap] = w[((long long)tap * a.CBT + a.CB + t) * Cs + cs];
+  a.add[idx] = label_class_sum<T>(v, cls);
 }
 
 // f(channels of the image, feature channels) as types

@@ -123,6 +123,8 @@ struct ImageConvArgs {
   const int* perm;
   const void* w;            // [L][Cs][16 P], launch_pack_image_w
   const float* add;         // [tables][9][Cs]: added to the outputs by position class, or NULL
+  const float* bias;        // [Cs] of model 0, bias_stride between models, or NULL
+  long long bias_stride;
   const int* sample_slot;   // the table of a sample, or NULL: its model's
   void* out;                // [rows][Cs], rows indexed by absolute sample
   const int* offs;
@@ -168,9 +170,8 @@ struct ImageGradArgs {      // the tiles' sums into the gradient blocks
 void launch_image_wgrad_final(const ImageGradArgs& a, hipStream_t st);
 struct ImagePackArgs {
   const float* w;           // model 0 master weights [16][CBT][Cs]; pstride between models
-  const float* bias;        // [Cs], or NULL
   void* packed;             // [L][Cs][16 P] storage type
-  float* add;               // [tables][9][Cs], or NULL
+  float* add;               // [tables][9][Cs] (label maps), or NULL
   long long pstride;
   int L, CB, CBT, Cs, P, tables;
 };
@@ -220,7 +221,8 @@ template <typename T> void launch_head_bwd(const HeadArgs& a, bool weights, hipS
 
 constexpr int ADAM_MAX_REGIONS = 8;
 struct AdamArgs {
-  float* theta; float* m; float* v; const float* g;
+  float* theta; float* m; float* v;
+  float* g;                 // read; written where the update adds up row splits
   void* shadow;             // storage-type copy of theta (NULL when the storage type is fp32)
   void* shadow_t;           // storage-type copy with every region below transposed: [tap][cs][cb]
   // fp32 storage, in place of the two copies: the regions, from element reg_part of a plane on, as three bf16 planes, as they are and
@@ -250,8 +252,21 @@ struct AdamArgs {
 // T: storage type of the shadows.  launch_adam does the whole update; the parts below do it piecewise (plan first).
 template <typename T> void launch_adam(AdamArgs a, hipStream_t st);
 bool adam_plan(AdamArgs& a);
-void launch_adam_gaps(const AdamArgs& a, hipStream_t st);
-template <typename T> void launch_adam_region(AdamArgs a, int region, hipStream_t st);
+// The gradient of one region as the row splits of its product, [n][L][16][Cb][Cs], which the update adds up into g on the way (n < 2: g holds it).
+struct AdamSplits {
+  const float* part = nullptr;
+  int n = 0;
+};
+template <typename T> void launch_adam_region(AdamArgs a, int region, const AdamSplits& sp, hipStream_t st);
+// The image-side layer among the gaps, whose operand (ImagePackArgs) is written along with its weights.
+struct AdamImage {
+  long long w = 0;          // its weights [16][CBT][Cs] in a model's block
+  void* packed = nullptr;   // NULL: no such layer
+  float* add = nullptr;     // [tables][9][Cs], or NULL
+  int CB = 0, CBT = 0, Cs = 0, P = 0, tables = 0;
+};
+bool adam_region_joins_rest(const AdamArgs& a, int region);      // few enough tiles for the launch below
+template <typename T> void launch_adam_rest(AdamArgs a, const AdamImage& im, int region, const AdamSplits& sp, hipStream_t st);
 template <typename T> void launch_cast_shadow(const float* theta, T* shadow, long long total, hipStream_t st);
 // dst[tap][cs][cb] <- src[tap][cb][cs] for every model (src: T or float master)
 template <typename T, typename S>

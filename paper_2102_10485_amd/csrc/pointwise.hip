@@ -985,32 +985,39 @@ __device__ inline void st_stream(float* p, const float4& v) {
   f4 t; t.x = v.x; t.y = v.y; t.z = v.z; t.w = v.w;
   __builtin_nontemporal_store(t, reinterpret_cast<f4*>(p));
 }
+__device__ inline float adam_update1(const AdamArgs& a, float bc1, float bc2, float g, float th, float& m, float& v) {
+  m = a.beta1 * m + (1.f - a.beta1) * g;
+  v = a.beta2 * v + (1.f - a.beta2) * g * g;
+  const float mh = m / bc1, vh = v / bc2;
+  return th - a.lr * mh / (sqrtf(vh) + a.eps);
+}
 __device__ inline void adam_update4(const AdamArgs& a, float bc1, float bc2, const float4& g, float4& th, float4& m, float4& v,
                                     float (&tt)[4]) {
-  const float gg[4] = {g.x, g.y, g.z, g.w};
-  float mm[4] = {m.x, m.y, m.z, m.w}, vv[4] = {v.x, v.y, v.z, v.w};
-  tt[0] = th.x; tt[1] = th.y; tt[2] = th.z; tt[3] = th.w;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    mm[e] = a.beta1 * mm[e] + (1.f - a.beta1) * gg[e];
-    vv[e] = a.beta2 * vv[e] + (1.f - a.beta2) * gg[e] * gg[e];
-    const float mh = mm[e] / bc1, vh = vv[e] / bc2;
-    tt[e] -= a.lr * mh / (sqrtf(vh) + a.eps);
-  }
+  tt[0] = adam_update1(a, bc1, bc2, g.x, th.x, m.x, v.x);
+  tt[1] = adam_update1(a, bc1, bc2, g.y, th.y, m.y, v.y);
+  tt[2] = adam_update1(a, bc1, bc2, g.z, th.z, m.z, v.z);
+  tt[3] = adam_update1(a, bc1, bc2, g.w, th.w, m.w, v.w);
   th = make_float4(tt[0], tt[1], tt[2], tt[3]);
-  m = make_float4(mm[0], mm[1], mm[2], mm[3]);
-  v = make_float4(vv[0], vv[1], vv[2], vv[3]);
 }
 
-// the ranges between the tiled regions
-__global__ __launch_bounds__(256) void adam_kernel(AdamArgs a) {
-  const int l = blockIdx.y;
+// The ranges between the tiled regions: block `block` of model l's.
+template <typename T>
+__device__ inline void adam_gap(const AdamArgs& a, const AdamImage& im, int l, int block) {
   if (a.counts[l] == 0) return;
   int r = 0;
-  while (r + 1 < a.ngaps && (int)blockIdx.x >= a.gap_blk0[r + 1]) ++r;
-  const long long i = a.gap_lo[r] + ((long long)(blockIdx.x - a.gap_blk0[r]) * 256 + threadIdx.x) * 4;
+  while (r + 1 < a.ngaps && block >= a.gap_blk0[r + 1]) ++r;
+  const long long i = a.gap_lo[r] + ((long long)(block - a.gap_blk0[r]) * 256 + threadIdx.x) * 4;
   if (i >= a.gap_hi[r]) return;
-  const long long o = (long long)l * a.P + i;
+  const long long o = (long long)l * a.P + i, in_image = i - im.w;
+  const bool image = im.packed && in_image >= 0 && in_image < 16LL * im.CBT * im.Cs;
+  int tap = 0, ch = 0, cs = 0;
+  if (image) {
+    const int row = (int)in_image / im.Cs;
+    cs = (int)in_image - row * im.Cs;
+    tap = row / im.CBT;
+    ch = row - tap * im.CBT;
+    if (im.add && ch >= im.CB && (a.L == 1 || ch - im.CB == l)) return;       // adam_label_maps's
+  }
   const float4 g = ld_stream(a.g + o);
   float4 th = ld_stream(a.theta + o);
   float4 m = ld_stream(a.m + o);
@@ -1021,6 +1028,40 @@ __global__ __launch_bounds__(256) void adam_kernel(AdamArgs a) {
   st_stream(a.m + o, m);
   st_stream(a.v + o, v);
   if (a.shadow) store4(static_cast<bf16_t*>(a.shadow) + o, tt);
+  if (image && ch < im.CB) {
+    T* const d = static_cast<T*>(im.packed) + ((long long)l * im.Cs + cs) * 16 * im.P + tap * im.P + ch;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) d[(long long)e * 16 * im.P] = from_float<T>(tt[e]);
+  }
+}
+// The label map of one table at one feature channel: its sixteen taps, and what they add up to at the nine classes of positions.
+template <typename T>
+__device__ inline void adam_label_maps(const AdamArgs& a, const AdamImage& im, int idx) {
+  if (idx >= im.tables * im.Cs) return;
+  const int t = idx / im.Cs, cs = idx - t * im.Cs, l = a.L == 1 ? 0 : t;
+  if (a.counts[l] == 0) return;
+  const long long o = (long long)l * a.P + im.w + (long long)(im.CB + t) * im.Cs + cs, step = (long long)im.CBT * im.Cs;
+  const float bc1 = a.bc[2 * l], bc2 = a.bc[2 * l + 1];
+  float th[16];
+#pragma unroll
+  for (int k0 = 0; k0 < 16; k0 += 8) {                 // eight at a time: all sixteen in flight would take the registers of half the kernel's waves
+    float g[8], m[8], v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const long long i = o + (k0 + k) * step;
+      g[k] = a.g[i]; th[k0 + k] = a.theta[i]; m[k] = a.m[i]; v[k] = a.v[i];
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const long long i = o + (k0 + k) * step;
+      const float t = adam_update1(a, bc1, bc2, g[k], th[k0 + k], m[k], v[k]);
+      th[k0 + k] = t;
+      a.theta[i] = t; a.m[i] = m[k]; a.v[i] = v[k];
+      if (a.shadow) static_cast<bf16_t*>(a.shadow)[i] = from_float<bf16_t>(t);
+    }
+  }
+#pragma unroll
+  for (int cls = 0; cls < 9; ++cls) im.add[((long long)t * 9 + cls) * im.Cs + cs] = label_class_sum<T>(th, cls);
 }
 
 // Four (eight) weights as bf16 parts, the planes `plane` elements apart.
@@ -1082,88 +1123,137 @@ void launch_split_weights(const SplitArgs& a, hipStream_t st) {
 // The tables' discriminator, whose k3 filters of 16 and 32 channels are held as k4 ones of 64: nothing of the fourth taps and of the padded channels
 // is read or written (a hundred pairs 136 -> 83 us a launch, and the four launches that cleared their gradients, 37 us, are gone).  The
 // same for the padded columns of G's linear layer, 28 of every 128, is slower than updating them: 566 -> 633 us for the holes in the lines.
-template <typename T>
-__global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a) {
-  constexpr int TSTRIDE = 64 * (int)sizeof(T) + 16;            // bytes per transposed row (64 cb)
+//
+// SPLITS: the gradient comes as the row splits of its product (AdamSplits), which are added here, in order, on their way and left in a.g.  A launch
+// of its own read the splits, wrote the sum and had it read again: eight 64x64 pairs, 512 and 1024 tiles of 64 x 64, 23 + 31 -> 40 us and 18 + 29 -> 42;
+// one 32x32 pair, 128 and 512 tiles, 14 + 9 -> 18 and 18 + 16 -> 29; one 28x28 pair, 32 tiles in 32 splits, 5 + 9 -> 10.
+// ROWS: rows (cb) of a tile a block takes; with fewer than all 64 a launch of few tiles has four times the blocks.
+template <typename T, int ROWS, bool SPLITS>
+__device__ inline void adam_tile(const AdamArgs& a, const AdamSplits& sp, unsigned block) {
+  constexpr int TSTRIDE = ROWS * (int)sizeof(T) + 16;          // bytes per transposed row (ROWS cb)
+  constexpr int NI = ROWS / 16, SUB = 64 / ROWS;
   __shared__ __attribute__((aligned(16))) unsigned char tile[64 * TSTRIDE];
-  // a block takes the (tile, model) pairs blockIdx.x, blockIdx.x + gridDim.x, ... of this launch (the launcher's
-  // grid covers them all)
-  const long long items = (long long)a.tile_count * a.L;
-  for (long long item = blockIdx.x; item < items; item += gridDim.x) {
-    const int l = (int)(item / a.tile_count);
-    if (a.counts[l] == 0) continue;
-    const int bx = (int)(item - (long long)l * a.tile_count) + a.tile_first;
-    int r = 0;
-    while (r + 1 < a.nregions && bx >= a.reg_tile0[r + 1]) ++r;
-    const int Cb = a.reg_cb[r], Cs = a.reg_cs[r];
-    const int tcs_n = Cs >> 6, tcb_n = Cb >> 6;
-    int q = bx - a.reg_tile0[r];
-    const int tcs = q % tcs_n; q /= tcs_n;
-    const int tcb = q % tcb_n;
-    const int tap = q / tcb_n;
-    if (a.k3 && ((tap >> 2) == 3 || (tap & 3) == 3)) continue;
-    const int cb_real = a.reg_cb_real[r] - tcb * 64, cs_real = a.reg_cs_real[r] - tcs * 64;      // inside the tile
-    const long long base = (long long)l * a.P + a.reg_w[r], part = 3 * (long long)l * a.plane + a.reg_part[r];
-    const float bc1 = a.bc[2 * l], bc2 = a.bc[2 * l + 1];
-    const int c4 = (threadIdx.x & 15) * 4, r0 = threadIdx.x >> 4;
-    const long long o0 = base + ((long long)tap * Cb + tcb * 64 + r0) * Cs + tcs * 64 + c4;
-    float4 gs[4], ths[4], ms[4], vs[4];      // all loads first: a launch of few tiles is one memory latency, not four
+  const int items = a.tile_count * SUB;                        // of a model
+  const int l = (int)(block / (unsigned)items), item = (int)(block - (unsigned)(l * items));
+  const bool moves = a.counts[l] != 0;
+  if (!moves && !SPLITS) return;
+  const int bx = item / SUB + a.tile_first, sub = (item % SUB) * ROWS;
+  int r = 0;
+  while (r + 1 < a.nregions && bx >= a.reg_tile0[r + 1]) ++r;
+  const int Cb = a.reg_cb[r], Cs = a.reg_cs[r];
+  const int tcs_n = Cs >> 6, tcb_n = Cb >> 6;
+  int q = bx - a.reg_tile0[r];
+  const int tcs = q % tcs_n; q /= tcs_n;
+  const int tcb = q % tcb_n;
+  const int tap = q / tcb_n;
+  if (a.k3 && ((tap >> 2) == 3 || (tap & 3) == 3)) return;
+  const int cb0 = tcb * 64 + sub, cb_real = a.reg_cb_real[r] - cb0, cs_real = a.reg_cs_real[r] - tcs * 64;      // inside the tile
+  const long long base = (long long)l * a.P + a.reg_w[r], part = 3 * (long long)l * a.plane + a.reg_part[r];
+  const float bc1 = a.bc[2 * l], bc2 = a.bc[2 * l + 1];
+  const int c4 = (threadIdx.x & 15) * 4, r0 = threadIdx.x >> 4;
+  const long long in0 = ((long long)tap * Cb + cb0 + r0) * Cs + tcs * 64 + c4, o0 = base + in0;
+  float4 gs[NI], ths[NI], ms[NI], vs[NI];      // all loads first: a launch of few tiles is one memory latency, not four
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const long long o = o0 + 16LL * i * Cs;
-      if (r0 + 16 * i >= cb_real || c4 >= cs_real) continue;
-      gs[i] = ld_stream(a.g + o);
-      ths[i] = ld_stream(a.theta + o);
-      ms[i] = ld_stream(a.m + o);
-      vs[i] = ld_stream(a.v + o);
-    }
+  for (int i = 0; i < NI; ++i) {
+    const long long o = o0 + 16LL * i * Cs;
+    if (r0 + 16 * i >= cb_real || c4 >= cs_real) continue;
+    if constexpr (!SPLITS) gs[i] = ld_stream(a.g + o);
+    ths[i] = ld_stream(a.theta + o);
+    ms[i] = ld_stream(a.m + o);
+    vs[i] = ld_stream(a.v + o);
+  }
+  if constexpr (SPLITS) {                                       // (no padding: the caller's regions are whole)
+    constexpr int DEEP = NI == 1 ? 16 : 4;                      // splits in flight
+    const long long layer = 16LL * Cb * Cs, step = (long long)a.L * layer;
+    const float* const p = sp.part + l * layer + in0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = r0 + 16 * i;                                // cb inside the tile
-      if (row >= cb_real || c4 >= cs_real) continue;
-      const long long o = o0 + 16LL * i * Cs;
-      float tt[4];
-      adam_update4(a, bc1, bc2, gs[i], ths[i], ms[i], vs[i], tt);
-      st_stream(a.theta + o, ths[i]);
-      st_stream(a.m + o, ms[i]);
-      st_stream(a.v + o, vs[i]);
-      if constexpr (sizeof(T) == 2) store4(static_cast<bf16_t*>(a.shadow) + o, tt);
-      else if (a.split_u) store_split4(a.split_u + part + (o - base), a.plane, tt);
+    for (int i = 0; i < NI; ++i) gs[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int k0 = 0; k0 < sp.n; k0 += DEEP) {
+      float4 t[DEEP][NI];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) *reinterpret_cast<T*>(tile + (c4 + e) * TSTRIDE + row * (int)sizeof(T)) = from_float<T>(tt[e]);
-    }
-    __syncthreads();
+      for (int k = 0; k < DEEP; ++k)
+        if (k0 + k < sp.n) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {                                 // eight values of a transposed row at a time
-      const int cid = threadIdx.x + 256 * i, cs = cid >> 3, ch = (cid & 7) * 8;
-      if (ch + 8 > cb_real || cs >= cs_real) {                    // padding, or the last real channels one by one
-        for (int k = 0; k < 8 && ch + k < cb_real && cs < cs_real; ++k) {
-          const T v = *reinterpret_cast<const T*>(tile + cs * TSTRIDE + (ch + k) * (int)sizeof(T));
-          const long long o = ((long long)tap * Cs + tcs * 64 + cs) * Cb + tcb * 64 + ch + k;
-          if constexpr (sizeof(T) == 2) static_cast<T*>(a.shadow_t)[base + o] = v;
-          else if (a.split_u) {
-            unsigned h, m, l_;
-            split_pair(v, 0.f, h, m, l_);
-            unsigned short* const d = a.split_d + part + o;
-            d[0] = (unsigned short)h; d[a.plane] = (unsigned short)m; d[2 * a.plane] = (unsigned short)l_;
-          } else static_cast<T*>(a.shadow_t)[(long long)l * a.plane + a.reg_part[r] + o] = v;
+          for (int i = 0; i < NI; ++i) t[k][i] = ld_stream(p + (k0 + k) * step + 16LL * i * Cs);
         }
-        continue;
-      }
-      const uint4* src = reinterpret_cast<const uint4*>(tile + cs * TSTRIDE + ch * (int)sizeof(T));
-      const long long o = ((long long)tap * Cs + tcs * 64 + cs) * Cb + tcb * 64 + ch;
-      if constexpr (sizeof(T) == 2) *reinterpret_cast<uint4*>(static_cast<T*>(a.shadow_t) + base + o) = src[0];
-      else if (a.split_u) store_split8(a.split_d + part + o, a.plane, src[0], src[1]);
-      else {
-        uint4* dst = reinterpret_cast<uint4*>(static_cast<T*>(a.shadow_t) + (long long)l * a.plane + a.reg_part[r] + o);
-        dst[0] = src[0];
-        dst[1] = src[1];
-      }
+#pragma unroll
+      for (int k = 0; k < DEEP; ++k)
+        if (k0 + k < sp.n) {
+#pragma unroll
+          for (int i = 0; i < NI; ++i) { gs[i].x += t[k][i].x; gs[i].y += t[k][i].y; gs[i].z += t[k][i].z; gs[i].w += t[k][i].w; }
+        }
     }
-    __syncthreads();                                              // the tile is rewritten by the next pair
+#pragma unroll
+    for (int i = 0; i < NI; ++i) st_stream(a.g + o0 + 16LL * i * Cs, gs[i]);
+    if (!moves) return;                                         // (the gradient of a model without samples is zero all the same)
+  }
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int row = r0 + 16 * i;                                // cb inside the tile
+    if (row >= cb_real || c4 >= cs_real) continue;
+    const long long o = o0 + 16LL * i * Cs;
+    float tt[4];
+    adam_update4(a, bc1, bc2, gs[i], ths[i], ms[i], vs[i], tt);
+    st_stream(a.theta + o, ths[i]);
+    st_stream(a.m + o, ms[i]);
+    st_stream(a.v + o, vs[i]);
+    if constexpr (sizeof(T) == 2) store4(static_cast<bf16_t*>(a.shadow) + o, tt);
+    else if (a.split_u) store_split4(a.split_u + part + (o - base), a.plane, tt);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) *reinterpret_cast<T*>(tile + (c4 + e) * TSTRIDE + row * (int)sizeof(T)) = from_float<T>(tt[e]);
+  }
+  __syncthreads();
+  for (int cid = threadIdx.x; cid < 8 * ROWS; cid += 256) {       // eight values of a transposed row at a time
+    const int cs = cid / (ROWS / 8), ch = cid % (ROWS / 8) * 8;
+    const long long o = ((long long)tap * Cs + tcs * 64 + cs) * Cb + cb0 + ch;
+    if (ch + 8 > cb_real || cs >= cs_real) {                    // padding, or the last real channels one by one
+      for (int k = 0; k < 8 && ch + k < cb_real && cs < cs_real; ++k) {
+        const T v = *reinterpret_cast<const T*>(tile + cs * TSTRIDE + (ch + k) * (int)sizeof(T));
+        if constexpr (sizeof(T) == 2) static_cast<T*>(a.shadow_t)[base + o + k] = v;
+        else if (a.split_u) {
+          unsigned h, m, l_;
+          split_pair(v, 0.f, h, m, l_);
+          unsigned short* const d = a.split_d + part + o + k;
+          d[0] = (unsigned short)h; d[a.plane] = (unsigned short)m; d[2 * a.plane] = (unsigned short)l_;
+        } else static_cast<T*>(a.shadow_t)[(long long)l * a.plane + a.reg_part[r] + o + k] = v;
+      }
+      continue;
+    }
+    const uint4* src = reinterpret_cast<const uint4*>(tile + cs * TSTRIDE + ch * (int)sizeof(T));
+    if constexpr (sizeof(T) == 2) *reinterpret_cast<uint4*>(static_cast<T*>(a.shadow_t) + base + o) = src[0];
+    else if (a.split_u) store_split8(a.split_d + part + o, a.plane, src[0], src[1]);
+    else {
+      uint4* dst = reinterpret_cast<uint4*>(static_cast<T*>(a.shadow_t) + (long long)l * a.plane + a.reg_part[r] + o);
+      dst[0] = src[0];
+      dst[1] = src[1];
+    }
   }
 }
 
+template <typename T, int ROWS, bool SPLITS>
+__global__ __launch_bounds__(256) void adam_tile_kernel(AdamArgs a, AdamSplits sp) { adam_tile<T, ROWS, SPLITS>(a, sp, blockIdx.x); }
+
+// What is left of an update, in one launch: the gaps, with the operand of the image-side layer written from the weights just computed, its label maps, and
+// (TILES) the last region in quarter tiles.  Three launches that waited for one another, the operand's reading the weights back: one 28x28 pair 10 + 4 + 3 -> 11 us
+// (D) and 10 + 7 + 3 -> 14 (G).  Of large blocks nothing changes (a hundred 32x32 pairs, G's gaps: 566 us, 5.3 TB/s).
+template <typename T, bool LABELS, bool TILES, bool SPLITS>
+__global__ __launch_bounds__(256) void adam_rest_kernel(AdamArgs a, AdamImage im, AdamSplits sp, unsigned tile_blocks, unsigned gap_blocks) {
+  unsigned b = blockIdx.x;
+  if constexpr (TILES) {
+    if (b < tile_blocks) return adam_tile<T, 16, SPLITS>(a, sp, b);
+    b -= tile_blocks;
+  }
+  if (b < gap_blocks) {
+    const unsigned per = (unsigned)a.gap_blk0[a.ngaps];
+    return adam_gap<T>(a, im, (int)(b / per), (int)(b % per));
+  }
+  if constexpr (LABELS) adam_label_maps<T>(a, im, (int)((b - gap_blocks) * 256 + threadIdx.x));
+}
+
+// Launches of at most this many 64 x 64 tiles take them in quarters: whole, they leave CUs without a block, or a second round nearly empty, and the update waits
+// for one block's chain of loads, divisions and stores.  Whole tiles and quarters, with splits: 32 tiles 18.3 and 9.9 us, 128 tiles 22.6 and 18.0, 320 18.4
+// and 16.3 (bf16), 22.2 and 19.7 to 23.2 (fp32), 512 28.1 and 29.5, 1024 41 and 41; without, 4096 91 and 90.
+constexpr long long ADAM_FEW_TILES = 512;
 // Fills the launch geometry: the tiled regions (sorted by offset: the caller's job) and the gaps between them, which
 // cover the rest of [0, P).  False (and a launch error) when the regions do not fit the kernels.
 bool adam_plan(AdamArgs& a) {
@@ -1196,29 +1286,67 @@ bool adam_plan(AdamArgs& a) {
   return true;
 }
 // The parts of one update of a planned AdamArgs, in any order after head_bwd_kernel, which advances the step counts and bias
-// corrections: the gaps; one tiled region (or all of them, region < 0).  Each element is updated by exactly one part.
-void launch_adam_gaps(const AdamArgs& a, hipStream_t st) {
-  if (a.ngaps > 0) hipLaunchKernelGGL(adam_kernel, dim3((unsigned)a.gap_blk0[a.ngaps], a.L), dim3(256), 0, st, a);
-}
-template <typename T>
-void launch_adam_region(AdamArgs a, int region, hipStream_t st) {
-  if (a.nregions == 0 || region >= a.nregions) return;
+// corrections: the rest (the gaps, if need be with a last region); one tiled region (or all of them, region < 0).  Each element is updated by
+// exactly one part.
+static bool set_region(AdamArgs& a, int region, const AdamSplits& sp) {
   const int first = region < 0 ? 0 : a.reg_tile0[region];
   const int last = region < 0 ? a.reg_tile0[a.nregions] : a.reg_tile0[region + 1];
   a.tile_first = first;
   a.tile_count = last - first;
-  const long long blocks = (long long)a.tile_count * a.L;
-  if (blocks > 0x7fffffffLL) return launch_fail("Adam: more than 2^31 weight tiles in one launch");
-  if (blocks > 0) hipLaunchKernelGGL((adam_tile_kernel<T>), dim3((unsigned)blocks), dim3(256), 0, st, a);
+  if ((long long)a.tile_count * a.L > 0x7fffffffLL) { launch_fail("Adam: more than 2^31 weight tiles in one launch"); return false; }
+  if (sp.n > 1 && (region < 0 || !sp.part || ((uintptr_t)sp.part & 15) != 0 || a.k3 || a.reg_cb_real[region] != a.reg_cb[region] || a.reg_cs_real[region] != a.reg_cs[region])) {
+    launch_fail("Adam: row splits are those of one region without padding");
+    return false;
+  }
+  return true;
 }
-template void launch_adam_region<float>(AdamArgs, int, hipStream_t);
-template void launch_adam_region<bf16_t>(AdamArgs, int, hipStream_t);
+bool adam_region_joins_rest(const AdamArgs& a, int region) {
+  return (long long)(a.reg_tile0[region + 1] - a.reg_tile0[region]) * a.L <= ADAM_FEW_TILES;
+}
+template <typename T>
+void launch_adam_rest(AdamArgs a, const AdamImage& im, int region, const AdamSplits& sp, hipStream_t st) {
+  const bool tiles = region >= 0 && region < a.nregions;
+  if (im.packed && (im.w % 4 != 0 || im.Cs % 4 != 0 || (im.add && (im.CBT <= im.CB || im.tables < 1)) || 16LL * im.CBT * im.Cs >= (1LL << 31)))
+    return launch_fail("Adam: image-side layer");
+  if (tiles && (!set_region(a, region, sp) || !adam_region_joins_rest(a, region))) return launch_fail("Adam: a region of too many tiles for the last launch");
+  const long long tile_blocks = tiles ? 4LL * a.tile_count * a.L : 0, gap_blocks = a.ngaps > 0 ? (long long)a.gap_blk0[a.ngaps] * a.L : 0;
+  const long long label_blocks = im.packed && im.add ? ((long long)im.tables * im.Cs + 255) / 256 : 0, blocks = tile_blocks + gap_blocks + label_blocks;
+  if (blocks > 0x7fffffffLL) return launch_fail("Adam: more blocks than a launch can have");
+  if (blocks == 0) return;
+  const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, a, im, sp, (unsigned)tile_blocks, (unsigned)gap_blocks); };
+  const auto with_labels = [&](auto labels) {
+    if (!tiles) go(adam_rest_kernel<T, labels.value, false, false>);
+    else if (sp.n > 1) go(adam_rest_kernel<T, labels.value, true, true>);
+    else go(adam_rest_kernel<T, labels.value, true, false>);
+  };
+  if (label_blocks > 0) with_labels(std::true_type{}); else with_labels(std::false_type{});
+}
+template void launch_adam_rest<float>(AdamArgs, const AdamImage&, int, const AdamSplits&, hipStream_t);
+template void launch_adam_rest<bf16_t>(AdamArgs, const AdamImage&, int, const AdamSplits&, hipStream_t);
+template <typename T>
+void launch_adam_region(AdamArgs a, int region, const AdamSplits& sp, hipStream_t st) {
+  if (a.nregions == 0 || region >= a.nregions) return;
+  if (!set_region(a, region, sp)) return;
+  const long long blocks = (long long)a.tile_count * a.L;
+  if (blocks == 0) return;
+  const bool quarters = blocks <= ADAM_FEW_TILES;
+  const dim3 grid((unsigned)(quarters ? 4 * blocks : blocks));
+  if (quarters) {
+    if (sp.n > 1) hipLaunchKernelGGL((adam_tile_kernel<T, 16, true>), grid, dim3(256), 0, st, a, sp);
+    else hipLaunchKernelGGL((adam_tile_kernel<T, 16, false>), grid, dim3(256), 0, st, a, sp);
+  } else {
+    if (sp.n > 1) hipLaunchKernelGGL((adam_tile_kernel<T, 64, true>), grid, dim3(256), 0, st, a, sp);
+    else hipLaunchKernelGGL((adam_tile_kernel<T, 64, false>), grid, dim3(256), 0, st, a, sp);
+  }
+}
+template void launch_adam_region<float>(AdamArgs, int, const AdamSplits&, hipStream_t);
+template void launch_adam_region<bf16_t>(AdamArgs, int, const AdamSplits&, hipStream_t);
 
 template <typename T>
 void launch_adam(AdamArgs a, hipStream_t st) {
   if (!adam_plan(a)) return;
-  launch_adam_gaps(a, st);
-  launch_adam_region<T>(a, -1, st);
+  launch_adam_rest<T>(a, AdamImage{}, -1, AdamSplits{}, st);
+  launch_adam_region<T>(a, -1, AdamSplits{}, st);
 }
 template void launch_adam<float>(AdamArgs, hipStream_t);
 template void launch_adam<bf16_t>(AdamArgs, hipStream_t);
