@@ -243,7 +243,9 @@ __global__ __launch_bounds__(256) void image_conv_kernel(ImageConvArgs a, Units 
         for (int b = 0; b < NB; ++b) mma_u4(acc[b], w[b][0][s], f);
       }
     } else {
-      floatx16 sum = {}, low = {};
+      floatx16 sum, low = {};                          // (what is added comes first: rounded with the products instead of once more behind them)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sum[e] = acc[0][e] * (1.f / SPLIT_UNSCALE);
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
         const u32x4 fh = pixels(s, 0), fm = pixels(s, 1), fl = pixels(s, 2);
@@ -258,7 +260,7 @@ __global__ __launch_bounds__(256) void image_conv_kernel(ImageConvArgs a, Units 
       for (int e = 0; e < 16; ++e) sum[e] = (sum[e] + low[e]) * SPLIT_UNSCALE;
       if (any_not_finite(sum)) {                       // what has no split: these 32 pixels again, value by value
         const T* w0 = static_cast<const T*>(a.w) + ((long long)l * CS + c0 + h * 8) * 16 * P;
-        sum = floatx16{};
+        sum = acc[0];
         for (int m = 0; m < 16 * P; ++m) {
           if (m % P >= CB) continue;
           const float v = patch_value<T, CB>(img, real, Hb, y, x, m);
@@ -267,7 +269,7 @@ __global__ __launch_bounds__(256) void image_conv_kernel(ImageConvArgs a, Units 
         }
       }
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[0][e] += sum[e];
+      for (int e = 0; e < 16; ++e) acc[0][e] = sum[e];
     }
     // into the patch: pixel r, channels 32 b + 16 g + 8 h .. + 7
 #pragma unroll
@@ -618,19 +620,19 @@ void wgrad_one(const ImageWgradArgs& a, int tiles, hipStream_t st) {
 }
 
 // The tiles' partial sums of every model, added in a fixed order, where the gradients belong.  A block takes 16 groups of four columns of one
-// model; lane group q adds the tiles q, q + 16, ... in turn, eight loads in flight, then the groups' sums are added in order.
+// model; lane group q adds the tiles q, q + 16, ... in turn, eight loads in flight, then the groups' sums are added in order, all in double (the loads are the time).
 // Blocks behind those: a model's pixel sums (the bias of G's last layer), the label maps' gradients from class sums, the row splits of the linear
 // head's weight gradient (a launch of its own takes 4.6 us whatever it does).
 __global__ __launch_bounds__(256) void image_wgrad_final_kernel(ImageGradArgs a, int col_blocks, int main_blocks, int sum_blocks, int label_blocks) {
   const int b = (int)blockIdx.x;
   const int P = a.P, Cs = a.Cs;
   if (b < main_blocks) {
-    __shared__ float4 red[16][16];
+    __shared__ double red[16][16][4];
     const int l = b / col_blocks, c = threadIdx.x & 15, q = threadIdx.x >> 4;
     const int t0 = a.tpre[l], t1 = a.tpre[l + 1], i = (b - l * col_blocks) * 16 + c;      // 16 P Cs / 4 is a multiple of 16
     const long long size4 = (long long)16 * P * Cs / 4;
     const float4* p = reinterpret_cast<const float4*>(a.part) + i;
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    double d[4] = {0., 0., 0., 0.};
     for (int k0 = t0 + q; k0 < t1; k0 += 8 * 16) {
       float4 t[8];
 #pragma unroll
@@ -638,16 +640,17 @@ __global__ __launch_bounds__(256) void image_wgrad_final_kernel(ImageGradArgs a,
         if (k0 + 16 * k < t1) t[k] = p[(long long)(k0 + 16 * k) * size4];
 #pragma unroll
       for (int k = 0; k < 8; ++k)
-        if (k0 + 16 * k < t1) { s.x += t[k].x; s.y += t[k].y; s.z += t[k].z; s.w += t[k].w; }
+        if (k0 + 16 * k < t1) { d[0] += t[k].x; d[1] += t[k].y; d[2] += t[k].z; d[3] += t[k].w; }
     }
-    red[q][c] = s;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[q][c][e] = d[e];
     __syncthreads();
     if (q > 0) return;
 #pragma unroll
-    for (int g = 1; g < 16; ++g) {
-      const float4 t = red[g][c];
-      s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
-    }
+    for (int g = 1; g < 16; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[e] += red[g][c][e];
+    const float4 s = make_float4((float)d[0], (float)d[1], (float)d[2], (float)d[3]);
     const int m = 4 * i / Cs, cs = 4 * i - m * Cs, tap = m / P, ch = m - tap * P;
     if (a.k3 && ((tap >> 2) == 3 || (tap & 3) == 3)) return;
     float* const dw = a.dw + (long long)l * a.pstride + ((long long)tap * a.CBT + ch) * Cs + cs;
@@ -659,11 +662,11 @@ __global__ __launch_bounds__(256) void image_wgrad_final_kernel(ImageGradArgs a,
     return;
   }
   if (b < main_blocks + sum_blocks) {
-    __shared__ float sh[256];
+    __shared__ double sh[256];
     const int l = b - main_blocks, t0 = a.tpre[l], t1 = a.tpre[l + 1];
     if (t0 == t1) return;
     for (int c = 0; c < a.CB; ++c) {
-      float s = 0.f;
+      double s = 0.;
       for (int t = t0 + (int)threadIdx.x; t < t1; t += 256) s += a.pixel_sums[t * 4 + c];
       sh[threadIdx.x] = s;
       __syncthreads();
@@ -671,7 +674,7 @@ __global__ __launch_bounds__(256) void image_wgrad_final_kernel(ImageGradArgs a,
         if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
         __syncthreads();
       }
-      if (threadIdx.x == 0) a.image_bias[(long long)l * a.pstride + c] = sh[0];
+      if (threadIdx.x == 0) a.image_bias[(long long)l * a.pstride + c] = (float)sh[0];
       __syncthreads();
     }
     return;
