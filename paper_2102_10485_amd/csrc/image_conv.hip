@@ -620,14 +620,14 @@ void wgrad_one(const ImageWgradArgs& a, int tiles, hipStream_t st) {
 }
 
 // The tiles' partial sums of every model, added in a fixed order, where the gradients belong.  A block takes 16 groups of four columns of one
-// model; lane group q adds the tiles q, q + 16, ... in turn, eight loads in flight, then the groups' sums are added in order, all in double (the loads are the time).
+// model; lane group q adds the tiles q, q + 16, ... in turn, eight loads in flight, then the groups' sums, rounded once, are added in order; both in double.
 // Blocks behind those: a model's pixel sums (the bias of G's last layer), the label maps' gradients from class sums, the row splits of the linear
 // head's weight gradient (a launch of its own takes 4.6 us whatever it does).
 __global__ __launch_bounds__(256) void image_wgrad_final_kernel(ImageGradArgs a, int col_blocks, int main_blocks, int sum_blocks, int label_blocks) {
   const int b = (int)blockIdx.x;
   const int P = a.P, Cs = a.Cs;
   if (b < main_blocks) {
-    __shared__ double red[16][16][4];
+    __shared__ float4 red[16][16];
     const int l = b / col_blocks, c = threadIdx.x & 15, q = threadIdx.x >> 4;
     const int t0 = a.tpre[l], t1 = a.tpre[l + 1], i = (b - l * col_blocks) * 16 + c;      // 16 P Cs / 4 is a multiple of 16
     const long long size4 = (long long)16 * P * Cs / 4;
@@ -642,14 +642,15 @@ __global__ __launch_bounds__(256) void image_wgrad_final_kernel(ImageGradArgs a,
       for (int k = 0; k < 8; ++k)
         if (k0 + 16 * k < t1) { d[0] += t[k].x; d[1] += t[k].y; d[2] += t[k].z; d[3] += t[k].w; }
     }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) red[q][c][e] = d[e];
+    red[q][c] = make_float4((float)d[0], (float)d[1], (float)d[2], (float)d[3]);
     __syncthreads();
     if (q > 0) return;
-#pragma unroll
-    for (int g = 1; g < 16; ++g)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) d[e] += red[g][c][e];
+    const int groups = min(16, t1 - t0);
+#pragma unroll 4
+    for (int g = 1; g < groups; ++g) {
+      const float4 t = red[g][c];
+      d[0] += t.x; d[1] += t.y; d[2] += t.z; d[3] += t.w;
+    }
     const float4 s = make_float4((float)d[0], (float)d[1], (float)d[2], (float)d[3]);
     const int m = 4 * i / Cs, cs = 4 * i - m * Cs, tap = m / P, ch = m - tap * P;
     if (a.k3 && ((tap >> 2) == 3 || (tap & 3) == 3)) return;
