@@ -21,17 +21,17 @@ PEAK = {"mfma_bf16": 2500.0, "mfma_fp32": 2500.0 / 6, "hbm": 8000.0}
 # the same counters read for the 1 GiB elementwise probe (fetch x 2.0, write x 1.0).  Valid only for the kernel sources they
 # were taken with: `sources` is the digest of csrc/ at that time, and the roofline reports null traffic when it differs.
 MEASURED_TRAFFIC = {
-    "sources": "d8bf973ac0f66674",
+    "sources": "9fce485a5b9f6fa6",
     "workload": "config 2 bf16",
     "fetch_scale": 2.000, "write_scale": 1.000,
     "kib_per_launch": {
-        "gemm_dense<64x64>": (103273, 121969),
-        "gemm_up<256x256>": (457694, 275201),
-        "gemm_up<256x128>": (159378, 435200),
-        "gemm_down<256x256>": (503275, 209600),
-        "wgrad<256x256>": (479946, 512070),
-        "gemm_up+actbwd<256x128>": (591646, 614400),
-        "wgrad<256x128>": (52088, 409989),
+        "gemm_dense<64x64>": (103273, 122664),
+        "gemm_up<256x256>": (457253, 275201),
+        "gemm_up<256x128>": (159455, 435200),
+        "gemm_down<256x256>": (502624, 209600),
+        "wgrad<256x256>": (472864, 512097),
+        "gemm_up+actbwd<256x128>": (595031, 614400),
+        "wgrad<256x128>": (52088, 410079),
     },
 }
 

@@ -7,8 +7,8 @@
 // pick the patches out of it.  Forward: a lane's eight values of K are neighbouring pixels of a tile row, 16 bytes.  Weight gradient: the
 // transposing LDS read takes an address of 8 bytes per lane, so that its rows are pixels and its columns the (tap, channel) of the patch.
 //
-// A one-hot label map is a constant plane.  Forward, it and the bias are a row per position class (3 x 3: which taps lie outside), added
-// behind the product.  Its gradient is that of the ones inside the image, and the bias's is the same at a tap that is never outside.
+// A one-hot label map is a constant plane.  Forward, it and the bias are a row per position class (3 x 3: which taps lie outside), from which
+// the accumulators start.  Its gradient is that of the ones inside the image, and the bias's is the same at a tap that is never outside.
 // One pair over many labels takes its label maps' gradients from class sums instead (launch_class_sums).
 //
 // fp32 storage: the tile, the weights and dy are split into three bf16 parts (split_mfma.h).
