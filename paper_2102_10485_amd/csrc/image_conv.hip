@@ -20,6 +20,7 @@
 // 28x28 pairs in fp32 93 -> 45, 31 -> 25, 69 -> 57, 62 -> 33.  Whole steps: +10 % (ten 28x28 pairs, bf16) to +2 % (twenty 32x32 pairs, fp32).
 #include <algorithm>
 
+#include "image_walk.h"
 #include "kernels.h"
 #include "lds_copy.h"
 #include "split_mfma.h"
@@ -28,25 +29,8 @@ namespace gan {
 
 namespace {
 
-constexpr int IMG_SIDE = 16;                 // outputs along x of a unit, at most
-constexpr int conv_side_y(int esize) { return esize == 4 ? 8 : 16; }      // along y: forward
-constexpr int WG_SIDE_Y = 8;                                              // and weight gradient, where one wave's registers hold the next unit's image
+constexpr int conv_side_y(int esize) { return esize == 4 ? 8 : 16; }      // outputs along y of a unit, forward (weight gradient: WG_SIDE_Y)
 constexpr int ZERO_ROWS = 4;                 // behind the weight gradient's tiles: what pixels outside the map read
-
-constexpr int img_values(int CB) { return CB == 1 ? 2 : (CB < 4 ? 4 : 8); }
-// Units of a map of side Hs: ph x pw outputs, their tile rows `pitch` bytes apart.  A pitch of 80 to 176 bytes modulo 256 keeps the rows that one
-// transposing read touches apart.
-struct Units { int pw, ph, nx, ny, pitch; };
-Units img_units(int Hs, int CB, int side_y) {
-  Units u;
-  u.nx = (Hs + IMG_SIDE - 1) / IMG_SIDE;
-  u.pw = (Hs + u.nx - 1) / u.nx;
-  u.ny = (Hs + side_y - 1) / side_y;
-  u.ph = (Hs + u.ny - 1) / u.ny;
-  u.pitch = ((2 * u.pw + 2) * 2 * img_values(CB) + 15) / 16 * 16;
-  while (u.pitch % 256 < 80 || u.pitch % 256 > 176) u.pitch += 16;
-  return u;
-}
 
 // one pixel of the tile: P values, fp32 in three planes `plane` bytes apart
 template <typename T, int CB>
@@ -321,8 +305,7 @@ void conv_one(const ImageConvArgs& a, hipStream_t st) {
 constexpr int wg_ring(int esize) { return esize == 4 ? 3 : 6; }      // K-steps of dy on their way, a wave (bf16: 1 KiB each, fp32: 2)
 constexpr int WG_THREADS = 320;
 
-// EVEN: units of sixteen columns that the map is a whole number of, so that a K-step is (part of) a row and the next one a fixed distance away;
-// every lane's addresses are then its own constants and wave-uniform offsets.
+// EVEN: even_units; every lane's addresses are then its own constants and wave-uniform offsets.
 template <typename T, int CB, int CS, bool EVEN>
 __global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? 4 : 3)) void image_wgrad_kernel(ImageWgradArgs a, Units u) {
   constexpr int P = img_values(CB), PB = 2 * P, NC = CS / 32, TURNS = 4 / NC, MF = P == 2 ? 1 : P / 2, PL = sizeof(T) == 4 ? 3 : 1;
@@ -334,32 +317,21 @@ __global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? 4 : 3))
   const int l = a.tmodel ? a.tmodel[tile] : 0;
   const int j0 = a.offs[l] + (tile - a.tpre[l]) * a.tile_samples, j1 = min(a.offs[l + 1], j0 + a.tile_samples);
   const int Hs = a.Hs, Hb = 2 * Hs, npix = Hb * Hb;
-  const int units = (j1 - j0) * u.nx * u.ny * a.nseg;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int trows = 2 * u.ph + 2, plane = (trows + ZERO_ROWS) * u.pitch, buf = PL * plane;
   unsigned char* const tiles = lds + 4 * RING_BYTES;                   // two
-  struct At { int seg, j, y0, x0; };
-  const auto next_unit = [&](At& t) __attribute__((always_inline)) {     // along x, along y, the next sample, the next segment
-    if ((t.x0 += u.pw) < Hs) return;
-    t.x0 = 0;
-    if ((t.y0 += u.ph) < Hs) return;
-    t.y0 = 0;
-    if (++t.j < j1) return;
-    t.j = j0;
-    ++t.seg;
-  };
-  const At first = {a.seg_first, j0, 0, 0};
+  const UnitAt first = {a.seg_first, j0, 0, 0};
   float own[CB];
 #pragma unroll
   for (int c = 0; c < CB; ++c) own[c] = 0.f;
   Stager<T, CB, (unit_pairs(WG_SIDE_Y) + 63) / 64> image;
-  At ahead = first;
+  UnitAt ahead = first;
   int place = a.real ? a.perm[j0] : 0;                                   // of the sample `ahead`, known a unit before it is needed
   const auto fetch = [&]() __attribute__((always_inline)) {
     const bool nchw = a.real && ahead.seg == 0;
     image.fetch(u, nchw ? nullptr : static_cast<const T*>(a.img) + ((long long)ahead.seg * a.seg_samples + ahead.j) * npix * CB,
                 nchw ? a.real + (long long)place * CB * npix : nullptr, Hb, ahead.y0, ahead.x0, lane, 64);
-    next_unit(ahead);
+    next_unit(ahead, u, Hs, j0, j1);
     if (a.real) place = a.perm[ahead.j];
   };
   const auto put = [&](int i) __attribute__((always_inline)) { image.put(tiles + (i & 1) * buf, plane, u, lane, 64, a.pixel_sums ? &own : nullptr); };
@@ -371,57 +343,18 @@ __global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? 4 : 3))
   }
 
   const int cb = wave % NC, turn = wave / NC % TURNS;
-  const int steps = ((u.ph * u.pw + 15) / 16 + TURNS - 1) / TURNS;     // K-steps of a unit, each of 16 pixels in row order, that this wave takes
   floatx16 acc[MF] = {}, low[PL == 3 ? MF : 1] = {};
   // ---- dy: lane -> pixel and 16 bytes of this wave's 32 channels, K-steps in the order of the units
   constexpr int LPP = PL == 1 ? 4 : 8, LOADS = PL == 1 ? 1 : 2;        // lanes a pixel, loads a K-step
-  const int dx16 = 16 * TURNS % u.pw, dy16 = 16 * TURNS / u.pw;
-  int at_unit = 0, at_step = 0, ly[LOADS], lx[LOADS];
-  At at = first;
-  const auto first_pixel = [&](int p, int& y, int& x) __attribute__((always_inline)) { y = p / u.pw; x = p - y * u.pw; };
-  int y_first[LOADS], x_first[LOADS];
+  int lane_pixel[LOADS];
 #pragma unroll
-  for (int i = 0; i < LOADS; ++i) {
-    first_pixel(16 * turn + lane / LPP + i * (64 / LPP), y_first[i], x_first[i]);
-    ly[i] = y_first[i]; lx[i] = x_first[i];
-  }
-  const T* dy_sample = static_cast<const T*>(a.dy) + ((long long)at.seg * a.seg_samples + at.j) * Hs * Hs * CS;
+  for (int i = 0; i < LOADS; ++i) lane_pixel[i] = lane / LPP + i * (64 / LPP);
+  GradWalk<LOADS, TURNS, EVEN> walk;
+  walk.start(u, Hs, first, j1, a.nseg, turn, lane_pixel, CS * (unsigned)sizeof(T), (unsigned)(cb * 32 + lane % LPP * (16 / (int)sizeof(T))) * (unsigned)sizeof(T), wave < 4);
+  const int units = walk.units, steps = walk.steps;                    // steps: K-steps of a unit, each of 16 pixels in row order, that this wave takes
+  const auto sample_grad = [&]() __attribute__((always_inline)) { return static_cast<const T*>(a.dy) + ((long long)walk.at.seg * a.seg_samples + walk.at.j) * Hs * Hs * CS; };
+  const T* dy_sample = sample_grad();
   const unsigned dy_bytes = (unsigned)(Hs * Hs * CS * (int)sizeof(T));
-  bool live = wave < 4;
-  const unsigned row_bytes = (unsigned)(Hs * CS * (int)sizeof(T));
-  const auto unit_off = [&](const At& t) __attribute__((always_inline)) { return (unsigned)t.y0 * row_bytes + (unsigned)(t.x0 * CS * (int)sizeof(T)); };
-  unsigned uoff = EVEN ? unit_off(at) : 0u;            // EVEN: of the K-step to load
-  unsigned lane_off[LOADS];
-#pragma unroll
-  for (int i = 0; i < LOADS; ++i)
-    lane_off[i] = (unsigned)turn * row_bytes + (unsigned)(((lane / LPP + i * (64 / LPP)) * CS + cb * 32 + lane % LPP * (16 / (int)sizeof(T))) * (int)sizeof(T));
-  const auto offset = [&](int i) __attribute__((always_inline)) {
-    if constexpr (EVEN) return lane_off[i];
-    const int y = at.y0 + ly[i], x = at.x0 + lx[i];
-    const bool ok = ly[i] < u.ph && y < Hs && x < Hs;
-    return ok ? (unsigned)(((y * Hs + x) * CS + cb * 32 + lane % LPP * (16 / (int)sizeof(T))) * (int)sizeof(T)) : NO_ROW;
-  };
-  const auto advance = [&]() __attribute__((always_inline)) {
-    if (++at_step < steps) {
-      if constexpr (EVEN) { uoff += TURNS * row_bytes; return; }
-#pragma unroll
-      for (int i = 0; i < LOADS; ++i) {
-        lx[i] += dx16; ly[i] += dy16;
-        if (lx[i] >= u.pw) { lx[i] -= u.pw; ++ly[i]; }
-      }
-      return;
-    }
-    at_step = 0;
-#pragma unroll
-    for (int i = 0; i < LOADS; ++i) { ly[i] = y_first[i]; lx[i] = x_first[i]; }
-    if (++at_unit < units) {
-      next_unit(at);
-      if constexpr (EVEN) uoff = unit_off(at);
-      dy_sample = static_cast<const T*>(a.dy) + ((long long)at.seg * a.seg_samples + at.j) * Hs * Hs * CS;
-    } else {
-      live = false;                                    // behind the last unit: an empty buffer, zeros
-    }
-  };
   // ---- operands: lane = 32 kgrp + 16 hb + s reads, for rows 8 kgrp + 4 half + s / 4 of a K-step (pixels), the 8 bytes s % 4 of the 16 columns hb
   const int s16 = lane & 15, hb = (lane >> 4) & 1, kgrp = lane >> 5, frow = 8 * kgrp + (s16 >> 2), sg = s16 & 3;
   // column group 4 hb + sg of fragment t: P = 4: tap (2 t + hb, sg); P = 2: taps (2 hb + sg / 2, 2 (sg % 2) ..); P = 8: half sg % 2 of tap (t, 2 hb + sg / 2)
@@ -429,22 +362,25 @@ __global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? 4 : 3))
   const int tstep = P == 4 ? 2 * u.pitch : u.pitch;
   int py_first[2], px_first[2], py[2], px[2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) first_pixel(16 * turn + frow + 4 * i, py_first[i], px_first[i]);
+  for (int i = 0; i < 2; ++i) {
+    const int p = 16 * turn + frow + 4 * i;
+    py_first[i] = p / u.pw; px_first[i] = p - py_first[i] * u.pw;
+  }
   unsigned char* const ring = lds + wave * RING_BYTES;
   const unsigned ring_lds = (unsigned)(uintptr_t)ring;
   const unsigned char* const bq = ring + frow * 64 + hb * 32 + sg * 8;
   u32x4 v[PL == 3 ? WG_RING : 1][2];
   const auto request = [&](auto slot) __attribute__((always_inline)) {
     if constexpr (PL == 1) {
-      load16_to_lds(make_rsrc(dy_sample, live ? dy_bytes : 0), offset(0), uoff, ring_lds + slot.value * 1024);
+      load16_to_lds(make_rsrc(dy_sample, walk.live ? dy_bytes : 0), walk.offset(0), walk.uniform, ring_lds + slot.value * 1024);
     } else {
-      const __amdgpu_buffer_rsrc_t rs = buffer_of(dy_sample, live ? dy_bytes : 0);
+      const __amdgpu_buffer_rsrc_t rs = buffer_of(dy_sample, walk.live ? dy_bytes : 0);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) v[slot.value][i] = __builtin_amdgcn_raw_buffer_load_b128(rs, offset(i), uoff, 0);
+      for (int i = 0; i < 2; ++i) v[slot.value][i] = __builtin_amdgcn_raw_buffer_load_b128(rs, walk.offset(i), walk.uniform, 0);
     }
-    advance();
+    if (walk.advance()) dy_sample = sample_grad();
   };
-  At cur = first;
+  UnitAt cur = first;
   const int even_first = 2 * turn * u.pitch;
   int even_row = even_first;                           // EVEN: tile row of the K-step to multiply, in bytes
   const auto multiply = [&](auto slot, const unsigned char* tb, bool there) __attribute__((always_inline)) {
@@ -474,7 +410,7 @@ __global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? 4 : 3))
     for (int i = 0; i < 2; ++i) {
       const bool ok = py[i] < u.ph && cur.y0 + py[i] < Hs && cur.x0 + px[i] < Hs;
       pa[i] = tb + (ok ? 2 * py[i] * u.pitch + 2 * px[i] * PB : trows * u.pitch) + goff;
-      px[i] += dx16; py[i] += dy16;
+      px[i] += walk.dx; py[i] += walk.dy;
       if (px[i] >= u.pw) { px[i] -= u.pw; ++py[i]; }
     }
 #pragma unroll
@@ -534,7 +470,7 @@ __global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? 4 : 3))
           __syncthreads();
           s = 0;
           ++i;
-          next_unit(cur);
+          next_unit(cur, u, Hs, j0, j1);
           even_row = even_first;
 #pragma unroll
           for (int q = 0; q < 2; ++q) { py[q] = py_first[q]; px[q] = px_first[q]; }
@@ -558,8 +494,8 @@ __global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? 4 : 3))
     if (bad) {                                         // what has no split: this wave's sums again with the fp32 MFMAs, from memory
 #pragma unroll
       for (int t = 0; t < MF; ++t) acc[t] = floatx16{};
-      At q = first;
-      for (int i = 0; i < units; ++i, next_unit(q)) {
+      UnitAt q = first;
+      for (int i = 0; i < units; ++i, next_unit(q, u, Hs, j0, j1)) {
         const bool nchw = a.real && q.seg == 0;
         const T* img = nchw ? nullptr : static_cast<const T*>(a.img) + ((long long)q.seg * a.seg_samples + q.j) * npix * CB;
         const float* real = nchw ? a.real + (long long)a.perm[q.j] * CB * npix : nullptr;
@@ -611,7 +547,7 @@ void wgrad_one(const ImageWgradArgs& a, int tiles, hipStream_t st) {
   const Units u = img_units(a.Hs, CB, WG_SIDE_Y);
   constexpr int PL = sizeof(T) == 4 ? 3 : 1, MF = img_values(CB) == 2 ? 1 : img_values(CB) / 2;
   const size_t lds = std::max<size_t>(4 * (PL == 1 ? wg_ring((int)sizeof(T)) * 1024 : 3 * 1024) + (size_t)2 * PL * (2 * u.ph + 2 + ZERO_ROWS) * u.pitch, CS == 64 ? 2 * MF * 16 * 64 * 4 : 0);
-  const bool even = u.pw == 16 && u.nx * u.pw == a.Hs && u.ny * u.ph == a.Hs && u.ph % (128 / CS) == 0;
+  const bool even = even_units(u, a.Hs, CS);
   const void* const kernel = even ? reinterpret_cast<const void*>(&image_wgrad_kernel<T, CB, CS, true>) : reinterpret_cast<const void*>(&image_wgrad_kernel<T, CB, CS, false>);
   if (lds > 48 * 1024)   // above the default dynamic limit: ask for it (idempotent, cheap)
     (void)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -3,6 +3,7 @@
 #pragma once
 
 #if defined(__HIPCC__)
+#include <hip/hip_runtime.h>
 #define GAN_DEVICE_INLINE __device__ __forceinline__
 #else
 #define GAN_DEVICE_INLINE inline
