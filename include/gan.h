@@ -273,6 +273,10 @@ gan_status gan_op_conv_up(gan_ctx* ctx, const void* small_in, const void* w_up, 
                           int32_t n_groups, int32_t n_samples, int32_t cb, int32_t cs, int32_t hs);
 gan_status gan_op_conv_wgrad(gan_ctx* ctx, const void* big, const void* small_in, float* dw, const int32_t* offs,
                              int32_t n_groups, int32_t n_samples, int32_t cb, int32_t cs, int32_t hs);
+/* The row splits of a weight gradient, DEVICE fp32 parts [splits][n_groups][4*4][cb][cs] (2 to 64 splits; cb and cs multiples of 64), added up as
+   the update of those weights does on its way: sum [n_groups][4*4][cb][cs], both 16-byte aligned.  Below 262144 values and from 16 splits on in four sums, split
+   k in sum k % 4, which are then added in order; otherwise one split after the other. */
+gan_status gan_op_split_sum(gan_ctx* ctx, const float* parts, float* sum, int32_t n_groups, int32_t splits, int32_t cb, int32_t cs);
 
 /* Single operations of the networks exactly as printed in Tables 1 and 2 (Section 4), synchronous like the ones above.
    (The training step for those networks is gan_train_step with family = GAN_FAMILY_PAPER.)

@@ -77,6 +77,7 @@ def load_library():
     L.gan_use_graphs.argtypes = [_VP, C.c_int32]
     L.gan_op_tile_rows.argtypes = [_VP, C.c_int32]
     L.gan_op_wgrad_parts.argtypes = [_VP, C.c_int32, C.c_int32]
+    L.gan_op_split_sum.argtypes = [_VP, _VP, _VP] + [C.c_int32] * 4
     L.gan_use_second_stream.argtypes = [_VP, C.c_int32]
     L.gan_graph_replays.argtypes = [_VP, C.POINTER(C.c_int64)]
     L.gan_profile_read.argtypes = [_VP, C.c_int32, C.POINTER(C.c_char_p), _I64P, C.POINTER(C.c_double),
@@ -300,6 +301,9 @@ class Gan:
 
     def op_conv_wgrad(self, big, small_in, dw, offs, n_groups, n_samples, cb, cs, hs):
         self._check(self.lib.gan_op_conv_wgrad(self.h, big, small_in, dw, offs, n_groups, n_samples, cb, cs, hs))
+
+    def op_split_sum(self, parts, out, n_groups, splits, cb, cs):
+        self._check(self.lib.gan_op_split_sum(self.h, parts, out, n_groups, splits, cb, cs))
 
     def op_dropout(self, x, offs, n_groups, n_samples, ch, h, w, p, seed, step, layer, pass_id):
         self._check(self.lib.gan_op_dropout(self.h, x, offs, n_groups, n_samples, ch, h, w, p, seed, step, layer, pass_id))

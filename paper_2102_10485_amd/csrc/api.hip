@@ -712,7 +712,7 @@ void wgrad_call(gan_ctx* c, const char* name, const void* Big, const void* Small
     Scope s(c, wgrad_variant_name((int)sizeof(T), a), flops_alg >= 0 ? flops_alg : 2.0 * rows * Cb * Cs * ntaps * frac, bytes, detail, st);
     launch_wgrad<T>(a, st);
   }
-  if (leave) *leave = {c->wg_part, auto_split};
+  if (leave) *leave = {c->wg_part, auto_split, split_chains(layer * c->L, auto_split)};
   else if (auto_split > 1) launch_sum_splits(c->wg_part, dW, stride, layer, c->L, auto_split, st);
 }
 
@@ -2064,6 +2064,40 @@ gan_status gan_op_conv_wgrad(gan_ctx* c, const void* big, const void* small_in, 
   a.split_stride = n_groups * a.dw_stride;
   if (c->bf16) launch_wgrad<bf16_t>(a, c->st); else launch_wgrad<float>(a, c->st);
   return finish_op(c);
+}
+
+gan_status gan_op_split_sum(gan_ctx* c, const float* parts, float* sum, int32_t n_groups, int32_t splits, int32_t cb, int32_t cs) {
+  if (!c || !parts || !sum || n_groups < 1 || splits < 2 || splits > WG_MAX_KSPLIT) return GAN_E_ARG;
+  if (cb < 64 || cs < 64 || cb % 64 || cs % 64) return fail(c, GAN_E_SHAPE, "channel counts must be multiples of 64");
+  (void)take_launch_error();
+  AdamArgs a = {};
+  const long long layer = 16LL * cb * cs, all = layer * n_groups;
+  // an update of zero weights with step counts and corrections of one: theta, m, v, the copies (bf16: two; fp32: one), counts, bc
+  float* scratch = nullptr;
+  const long long floats = 5 * all + 3LL * n_groups;
+  if (hipMalloc((void**)&scratch, (size_t)floats * 4) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(c, GAN_E_OOM, "update scratch alloc");
+  }
+  std::vector<float> ones((size_t)n_groups * 3, 1.f);
+  const int one = 1;
+  for (int l = 0; l < n_groups; ++l) memcpy(&ones[(size_t)l], &one, 4);
+  gan_status s = sync(c);
+  if (s == GAN_OK && (hipMemset(scratch, 0, (size_t)floats * 4) != hipSuccess ||
+                      hipMemcpy(scratch + 5 * all, ones.data(), ones.size() * 4, hipMemcpyHostToDevice) != hipSuccess)) s = fail(c, GAN_E_HIP, "copy failed");
+  if (s == GAN_OK) {
+    a.theta = scratch; a.m = scratch + all; a.v = scratch + 2 * all; a.g = sum; a.P = layer; a.plane = layer; a.L = n_groups;
+    if (c->bf16) a.shadow = scratch + 3 * all;
+    a.shadow_t = scratch + 4 * all;
+    a.counts = (const int*)(scratch + 5 * all); a.bc = scratch + 5 * all + n_groups;
+    a.lr = 0.f; a.beta1 = 0.5f; a.beta2 = 0.999f; a.eps = 1e-8f;
+    a.nregions = 1; a.reg_cb[0] = a.reg_cb_real[0] = cb; a.reg_cs[0] = a.reg_cs_real[0] = cs;
+    const AdamSplits sp = {parts, splits, split_chains(all, splits)};
+    if (adam_plan(a)) { if (c->bf16) launch_adam_region<bf16_t>(a, 0, sp, c->st); else launch_adam_region<float>(a, 0, sp, c->st); }
+    s = finish_op(c);
+  }
+  (void)hipFree(scratch);
+  return s;
 }
 
 gan_status gan_op_dropout(gan_ctx* c, void* x, const int32_t* offs, int32_t n_groups, int32_t n_samples, int32_t ch, int32_t h,

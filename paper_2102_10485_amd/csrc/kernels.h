@@ -252,10 +252,11 @@ struct AdamArgs {
 // T: storage type of the shadows.  launch_adam does the whole update; the parts below do it piecewise (plan first).
 template <typename T> void launch_adam(AdamArgs a, hipStream_t st);
 bool adam_plan(AdamArgs& a);
-// The gradient of one region as the row splits of its product, [n][L][16][Cb][Cs], which the update adds up into g on the way (n < 2: g holds it).
+// The gradient of one region as the row splits of its product, [n][L][16][Cb][Cs], which the update adds up into g on the way (n < 2: g holds it),
+// as launch_sum_splits does: chains is split_chains of them.
 struct AdamSplits {
   const float* part = nullptr;
-  int n = 0;
+  int n = 0, chains = 1;
 };
 template <typename T> void launch_adam_region(AdamArgs a, int region, const AdamSplits& sp, hipStream_t st);
 // The image-side layer among the gaps, whose operand (ImagePackArgs) is written along with its weights.
@@ -282,8 +283,11 @@ struct SplitArgs {
 };
 void launch_split_weights(const SplitArgs& a, hipStream_t st);
 
-// dW[l * dw_stride + i] = part[(0 * L + l) * size + i] + part[(1 * L + l) * size + i] + ... (nsplit terms, in this
-// order), i < size (a multiple of 4), l < L
+// How many sums the row splits of `elements` values (of all models) are added in: with four, split k goes to sum k % 4, in order, and the sums are
+// added in order.  Of many splits one sum's error is up to twice as large; many elements have few splits.
+inline int split_chains(long long elements, int nsplit) { return elements / 4 < 256 * 256 && nsplit >= 16 ? 4 : 1; }
+// dW[l * dw_stride + i] = part[(0 * L + l) * size + i] + part[(1 * L + l) * size + i] + ... (nsplit terms, in split_chains sums),
+// i < size (a multiple of 4), l < L
 void launch_sum_splits(const float* part, float* dW, long long dw_stride, long long size, int L, int nsplit, hipStream_t st);
 
 void launch_tile_prefix(const int* offs, int L, int rps, int tile_rows, int* tpre, hipStream_t st);

@@ -201,7 +201,7 @@ void launch_sum_splits(const float* part, float* dW, long long dw_stride, long l
   const long long tot = size / 4 * L;
   if (tot == 0) return;
   // (few elements: four threads each.  16 taps of 64 x 128 in 32 splits 8.0 -> 5.5 us)
-  if (tot < 256 * 256 && nsplit >= 16)
+  if (split_chains(size * L, nsplit) == 4)
     hipLaunchKernelGGL(sum_splits_kernel<4>, dim3((unsigned)((tot + 63) / 64)), dim3(256), 0, st, part, dW, dw_stride, size / 4, L, nsplit);
   else
     hipLaunchKernelGGL(sum_splits_kernel<1>, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, part, dW, dw_stride, size / 4, L, nsplit);
@@ -1124,10 +1124,11 @@ void launch_split_weights(const SplitArgs& a, hipStream_t st) {
 // is read or written (a hundred pairs 136 -> 83 us a launch, and the four launches that cleared their gradients, 37 us, are gone).  The
 // same for the padded columns of G's linear layer, 28 of every 128, is slower than updating them: 566 -> 633 us for the holes in the lines.
 //
-// SPLITS: the gradient comes as the row splits of its product (AdamSplits), which are added here, in order, on their way and left in a.g.  A launch
+// SPLITS: the gradient comes as the row splits of its product (AdamSplits), which are added here, in split_chains sums, on their way and left in a.g.  A launch
 // of its own read the splits, wrote the sum and had it read again: eight 64x64 pairs, 512 and 1024 tiles of 64 x 64, 23 + 31 -> 40 us and 18 + 29 -> 42;
 // one 32x32 pair, 128 and 512 tiles, 14 + 9 -> 18 and 18 + 16 -> 29; one 28x28 pair, 32 tiles in 32 splits, 5 + 9 -> 10.
 // ROWS: rows (cb) of a tile a block takes; with fewer than all 64 a launch of few tiles has four times the blocks.
+__device__ __forceinline__ void add4(float4& s, const float4& t) { s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w; }
 template <typename T, int ROWS, bool SPLITS>
 __device__ inline void adam_tile(const AdamArgs& a, const AdamSplits& sp, unsigned block) {
   constexpr int TSTRIDE = ROWS * (int)sizeof(T) + 16;          // bytes per transposed row (ROWS cb)
@@ -1163,7 +1164,9 @@ __device__ inline void adam_tile(const AdamArgs& a, const AdamSplits& sp, unsign
     vs[i] = ld_stream(a.v + o);
   }
   if constexpr (SPLITS) {                                       // (no padding: the caller's regions are whole)
-    constexpr int DEEP = NI == 1 ? 16 : 4;                      // splits in flight
+    constexpr int DEEP = NI == 1 ? 12 : 4;                      // splits in flight (sixteen and the four sums would cost the gaps' blocks a fifth of their waves)
+    float4 more[4] = {};                                        // (quarter tiles: the other three sums, where there are four)
+    const bool four = NI == 1 && sp.chains == 4;
     const long long layer = 16LL * Cb * Cs, step = (long long)a.L * layer;
     const float* const p = sp.part + l * layer + in0;
 #pragma unroll
@@ -1180,9 +1183,13 @@ __device__ inline void adam_tile(const AdamArgs& a, const AdamSplits& sp, unsign
       for (int k = 0; k < DEEP; ++k)
         if (k0 + k < sp.n) {
 #pragma unroll
-          for (int i = 0; i < NI; ++i) { gs[i].x += t[k][i].x; gs[i].y += t[k][i].y; gs[i].z += t[k][i].z; gs[i].w += t[k][i].w; }
+          for (int i = 0; i < NI; ++i)
+            if (four && k % 4 > 0) add4(more[k % 4 - 1], t[k][i]); else add4(gs[i], t[k][i]);
         }
     }
+    if (four)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) add4(gs[0], more[k]);
 #pragma unroll
     for (int i = 0; i < NI; ++i) st_stream(a.g + o0 + 16LL * i * Cs, gs[i]);
     if (!moves) return;                                         // (the gradient of a model without samples is zero all the same)
@@ -1298,6 +1305,7 @@ static bool set_region(AdamArgs& a, int region, const AdamSplits& sp) {
     launch_fail("Adam: row splits are those of one region without padding");
     return false;
   }
+  if (sp.chains != 1 && (long long)a.tile_count * a.L > ADAM_FEW_TILES) { launch_fail("Adam: whole tiles add their row splits in one sum"); return false; }
   return true;
 }
 bool adam_region_joins_rest(const AdamArgs& a, int region) {

@@ -21,6 +21,15 @@ CASES = [
 ]
 
 
+@pytest.fixture(scope="module")
+def ctxs():
+    st = U.torch_mod().cuda.current_stream().cuda_stream
+    c = {p: binding.Gan(binding.make_config(synth.SPECS["tiny3"], 3, 3, 48, p), st) for p in (binding.FP32, binding.BF16)}
+    yield c
+    for g in c.values():
+        g.close()
+
+
 @pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
 @pytest.mark.parametrize("channels,g_ch,d_ch,h0,models,labels,maps,n", CASES)
 def test_parts_of_the_update(prec, channels, g_ch, d_ch, h0, models, labels, maps, n):
@@ -60,3 +69,21 @@ def test_parts_of_the_update(prec, channels, g_ch, d_ch, h0, models, labels, map
                 again.set_params(which, l, want[0])
     for g in ctxs:
         g.close()
+
+
+def test_row_splits_are_added_in_the_stated_order(ctxs):
+    """Bit for bit the sums that launch_sum_splits leaves: few values in many splits go through four sums, whose error is half to two thirds of one's."""
+    torch = U.torch_mod()
+    for prec, L, splits, cb, cs in [(binding.FP32, 1, 64, 64, 128), (binding.BF16, 1, 33, 64, 64), (binding.FP32, 3, 16, 64, 64), (binding.BF16, 1, 15, 64, 128),
+                                    (binding.FP32, 1, 24, 128, 128), (binding.BF16, 1, 32, 128, 128), (binding.FP32, 10, 5, 256, 64)]:
+        parts = np.random.default_rng(splits).normal(size=(splits, L, 16, cb, cs)).astype(np.float32)
+        out = torch.full((L, 16, cb, cs), 7.0, device="cuda")
+        ctxs[prec].op_split_sum(U.dev(parts).data_ptr(), out.data_ptr(), L, splits, cb, cs)
+        chains = 4 if L * 4 * cb * cs < 65536 and splits >= 16 else 1
+        sums = [np.zeros(parts.shape[1:], np.float32) for _ in range(chains)]
+        for k in range(splits):
+            sums[k % chains] = sums[k % chains] + parts[k]
+        want = sums[0]
+        for s in sums[1:]:
+            want = want + s
+        assert np.array_equal(out.cpu().numpy(), want), (prec, L, splits, cb, cs)
