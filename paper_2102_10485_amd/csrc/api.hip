@@ -2066,6 +2066,86 @@ gan_status gan_op_conv_wgrad(gan_ctx* c, const void* big, const void* small_in, 
   return finish_op(c);
 }
 
+// What the two entries below share: the model of every sample, and what the launches need in device memory for as long as they run.
+struct ImageOp {
+  std::vector<int> offs;
+  std::vector<void*> held;
+  ~ImageOp() { for (void* p : held) (void)hipFree(p); }
+  void* hold(size_t bytes) {
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes < 16 ? 16 : bytes) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
+    held.push_back(p);
+    return p;
+  }
+  int* hold(const std::vector<int>& v) {
+    int* p = (int*)hold(v.size() * 4);
+    if (p && !v.empty() && hipMemcpy(p, v.data(), v.size() * 4, hipMemcpyHostToDevice) != hipSuccess) return nullptr;
+    return p;
+  }
+};
+static gan_status image_op_begin(gan_ctx* c, ImageOp& op, const void* img, const float* nchw, const int32_t* perm, const int32_t* offs, int32_t n_groups,
+                                 int32_t n_samples, int32_t cb, int32_t cs, int32_t hs, int32_t maps) {
+  if (!c || !offs || n_groups < 1 || n_samples < 1 || (nchw && !perm) || (!img && (!nchw || c->op_segments > 1))) return GAN_E_ARG;
+  if (cb < 1 || cb > 4 || (cs != 64 && cs != 128) || hs < 2 || (maps != 0 && maps != n_groups)) return fail(c, GAN_E_SHAPE, "image-side layers: 1 to 4 image channels, 64 or 128 feature channels");
+  (void)take_launch_error();
+  const gan_status s = sync(c);
+  if (s != GAN_OK) return s;
+  op.offs.resize(n_groups + 1);
+  if (hipMemcpy(op.offs.data(), offs, (size_t)(n_groups + 1) * 4, hipMemcpyDeviceToHost) != hipSuccess) return fail(c, GAN_E_HIP, "copy failed");
+  for (int l = 0; l < n_groups; ++l)
+    if (op.offs[l] < 0 || op.offs[l] > op.offs[l + 1]) return fail(c, GAN_E_ARG, "sample offsets must not decrease");
+  if (op.offs[n_groups] != n_samples) return fail(c, GAN_E_ARG, "n_samples must be offs[n_groups]");
+  return GAN_OK;
+}
+gan_status gan_op_image_conv(gan_ctx* c, const void* img, const float* nchw, const int32_t* perm, const float* w, const float* bias, void* small_out,
+                             const int32_t* offs, int32_t n_groups, int32_t n_samples, int32_t cb, int32_t cs, int32_t hs, int32_t maps) {
+  ImageOp op;
+  if (!w || !small_out) return GAN_E_ARG;
+  const gan_status s = image_op_begin(c, op, img, nchw, perm, offs, n_groups, n_samples, cb, cs, hs, maps);
+  if (s != GAN_OK) return s;
+  std::vector<int> model(n_samples);
+  for (int l = 0; l < n_groups; ++l) std::fill(model.begin() + op.offs[l], model.begin() + op.offs[l + 1], l);
+  ImagePackArgs p = {};
+  p.w = w; p.L = n_groups; p.CB = cb; p.CBT = cb + maps; p.Cs = cs; p.P = image_values(cb); p.pstride = 16LL * p.CBT * cs; p.tables = n_groups;
+  p.packed = op.hold((size_t)n_groups * 16 * p.P * cs * esize(c));
+  p.add = maps ? (float*)op.hold((size_t)n_groups * 9 * cs * 4) : nullptr;
+  ImageConvArgs a = {};
+  a.img = img ? img : nchw; a.real = nchw; a.perm = perm; a.w = p.packed; a.add = p.add; a.bias = bias; a.bias_stride = cs; a.out = small_out; a.offs = offs;
+  a.sample_model = op.hold(model);
+  if (!p.packed || (maps && !p.add) || !a.sample_model) return fail(c, GAN_E_OOM, "image-side operand alloc");
+  a.L = n_groups; a.n = n_samples; a.CB = cb; a.Hs = hs; a.Cs = cs; a.nseg = c->op_segments; a.seg_samples = n_samples; a.slope = 1.f;
+  if (c->bf16) { launch_pack_image_w<bf16_t>(p, c->st); launch_image_conv<bf16_t>(a, c->st); }
+  else { launch_pack_image_w<float>(p, c->st); launch_image_conv<float>(a, c->st); }
+  return finish_op(c);
+}
+gan_status gan_op_image_wgrad(gan_ctx* c, const void* img, const float* nchw, const int32_t* perm, const void* small_in, float* grad, const int32_t* offs,
+                              int32_t n_groups, int32_t n_samples, int32_t cb, int32_t cs, int32_t hs, int32_t maps, int32_t size_samples) {
+  ImageOp op;
+  if (!small_in || !grad || size_samples < n_samples) return GAN_E_ARG;
+  const gan_status s = image_op_begin(c, op, img, nchw, perm, offs, n_groups, n_samples, cb, cs, hs, maps);
+  if (s != GAN_OK) return s;
+  const int per = image_tile_samples((int)esize(c), size_samples), P = image_values(cb);
+  std::vector<int> tpre(1, 0), tmodel;
+  for (int l = 0; l < n_groups; ++l) {
+    tmodel.insert(tmodel.end(), (op.offs[l + 1] - op.offs[l] + per - 1) / per, l);
+    tpre.push_back((int)tmodel.size());
+  }
+  const int tiles = (int)tmodel.size();
+  ImageWgradArgs a = {};
+  a.img = img ? img : nchw; a.real = nchw; a.perm = perm; a.dy = small_in; a.offs = offs;
+  a.part = (float*)op.hold((size_t)tiles * 16 * P * cs * 4); a.pixel_sums = (float*)op.hold((size_t)tiles * 4 * 4);
+  a.tpre = op.hold(tpre); a.tmodel = op.hold(tmodel);
+  if (!a.part || !a.pixel_sums || !a.tpre || !a.tmodel) return fail(c, GAN_E_OOM, "image-side partial sums alloc");
+  a.L = n_groups; a.CB = cb; a.Hs = hs; a.Cs = cs; a.nseg = c->op_segments; a.seg_samples = n_samples; a.tile_samples = per;
+  ImageGradArgs g = {};
+  g.part = a.part; g.pixel_sums = a.pixel_sums; g.tpre = a.tpre; g.L = n_groups; g.CB = cb; g.CBT = cb + maps; g.Cs = cs; g.P = P; g.plane_labels = maps > 0;
+  const long long taps = 16LL * g.CBT * cs;
+  g.dw = grad; g.dbias = grad + taps; g.image_bias = grad + taps + cs; g.pstride = taps + cs + 4;
+  if (c->bf16) launch_image_wgrad<bf16_t>(a, tiles, c->st); else launch_image_wgrad<float>(a, tiles, c->st);
+  launch_image_wgrad_final(g, c->st);
+  return finish_op(c);
+}
+
 gan_status gan_op_split_sum(gan_ctx* c, const float* parts, float* sum, int32_t n_groups, int32_t splits, int32_t cb, int32_t cs) {
   if (!c || !parts || !sum || n_groups < 1 || splits < 2 || splits > WG_MAX_KSPLIT) return GAN_E_ARG;
   if (cb < 64 || cs < 64 || cb % 64 || cs % 64) return fail(c, GAN_E_SHAPE, "channel counts must be multiples of 64");
