@@ -304,10 +304,16 @@ void conv_one(const ImageConvArgs& a, hipStream_t st) {
 // ---------------------------------------------------------------------------------------------------------
 constexpr int wg_ring(int esize) { return esize == 4 ? 3 : 6; }      // K-steps of dy on their way, a wave (bf16: 1 KiB each, fp32: 2)
 constexpr int WG_THREADS = 320;
+// K-steps (16 pixels) whose products a wave's accumulators add up before they go to sums in memory.  An accumulator that takes a tile's pixels in one chain
+// rounds each against all in front of it, and the chains of large tiles were longer than the row splits in whose place the tiles came.  Error against 64-bit sums, one
+// chain -> these: twenty 32x32 pairs of 64 samples in fp32 2.2e-7 -> 1.5e-7, a hundred in bf16 4.2e-7 -> 2.9e-7 (the row splits: 0.9 of one chain's).  Both
+// weight gradients of a step 195 -> 205 and 350 -> 363 us; with fp32 chains of 15 1.0e-7 and 224 us, with a second set of registers for the sums 0.96e-7
+// and, of ten 28x28 pairs, 125 us for 78.
+constexpr int wg_chain(int esize) { return esize == 4 ? 48 : 162; }
 
-// EVEN: even_units; every lane's addresses are then its own constants and wave-uniform offsets.
+// EVEN: even_units; every lane's addresses are then its own constants and wave-uniform offsets.  (Registers: held to what the launches had without the sums in memory.)
 template <typename T, int CB, int CS, bool EVEN>
-__global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? 4 : 3)) void image_wgrad_kernel(ImageWgradArgs a, Units u) {
+__global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? (EVEN ? 5 : 4) : CB == 1 ? 4 : 3)) void image_wgrad_kernel(ImageWgradArgs a, Units u) {
   constexpr int P = img_values(CB), PB = 2 * P, NC = CS / 32, TURNS = 4 / NC, MF = P == 2 ? 1 : P / 2, PL = sizeof(T) == 4 ? 3 : 1;
   constexpr int WG_RING = wg_ring((int)sizeof(T));
   constexpr int RING_BYTES = PL == 1 ? WG_RING * 1024 : 3 * 1024;      // of a wave
@@ -447,6 +453,31 @@ __global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? 4 : 3))
       __builtin_amdgcn_wave_barrier();
     }
   };
+  // ---- what the accumulators have added up goes onto sums of the wave's own in memory and they start at zero again (more), or these are added to them.
+  // (its lines are those of the tile's partial sums, as the registers lie, and for the second turn others behind all of those)
+  int put_away = 0;                                    // K-steps whose sums lie there
+  const auto add_away = [&](auto more) __attribute__((always_inline)) {
+    // (addressed from their middle, which immediate offsets reach from; not through a buffer: a store of 16 bytes with a scalar offset is not kept apart from writes
+    // to its registers behind it, and lost some)
+    float4* const sums = reinterpret_cast<float4*>(a.part + (((long long)turn * gridDim.x + tile) * NC + cb) * (MF * 16 * 64)) + 256 + lane;
+    static_for<0, MF>([&](auto t) __attribute__((always_inline)) {
+      float4 q[4] = {};
+      if (put_away > 0)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) q[k] = sums[(4 * t.value + k - 4) * 64];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        q[k].x += acc[t.value][4 * k]; q[k].y += acc[t.value][4 * k + 1]; q[k].z += acc[t.value][4 * k + 2]; q[k].w += acc[t.value][4 * k + 3];
+        if constexpr (more.value) {
+          sums[(4 * t.value + k - 4) * 64] = q[k];
+        } else {
+          acc[t.value][4 * k] = q[k].x; acc[t.value][4 * k + 1] = q[k].y; acc[t.value][4 * k + 2] = q[k].z; acc[t.value][4 * k + 3] = q[k].w;
+        }
+      }
+      if constexpr (more.value) acc[t.value] = floatx16{};
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
   if (wave == 4) {
     put(0);
     if (units > 1) fetch();
@@ -463,7 +494,11 @@ __global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? 4 : 3))
 #pragma unroll
     for (int k = 0; k < 2; ++k) { py[k] = py_first[k]; px[k] = px_first[k]; }
     // (whole rounds of the ring, whose slots are registers or constant offsets: behind the last unit nothing is multiplied, for which the other tile may never have been written)
-    for (int g = 0; g < units * steps; g += WG_RING)
+    for (int g = 0; g < units * steps; g += WG_RING) {
+      if (g - put_away >= wg_chain((int)sizeof(T))) {
+        add_away(std::true_type{});
+        put_away = g;
+      }
       static_for<0, WG_RING>([&](auto k) __attribute__((always_inline)) {
         multiply(k, tiles + (i & 1) * buf, i < units);
         if (++s == steps && i < units) {
@@ -476,6 +511,8 @@ __global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? 4 : 3))
           for (int q = 0; q < 2; ++q) { py[q] = py_first[q]; px[q] = px_first[q]; }
         }
       });
+    }
+    if (put_away > 0) add_away(std::false_type{});
   }
   wait_vm<0>();
   __syncthreads();

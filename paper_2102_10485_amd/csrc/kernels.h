@@ -139,7 +139,7 @@ struct ImageWgradArgs {
   const float* real;
   const int* perm;
   const void* dy;           // [rows][Cs], rows indexed by absolute sample
-  float* part;              // [tiles][16 P][Cs], partial sums of every tile of tile_samples samples
+  float* part;              // [tiles][16 P][Cs], partial sums of every tile of tile_samples samples (Cs = 64: and as much again behind the launch's tiles, scratch)
   float* pixel_sums;        // [tiles][4]: the sums of the image's pixels, or NULL
   const int* offs;
   const int* tpre;          // the prefix array and models of the tiles (tmodel NULL: one model)

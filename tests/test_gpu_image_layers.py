@@ -151,6 +151,21 @@ def test_sums_of_whole_numbers(ctxs, prec, groups, size, segments, nchw, maps, h
     assert np.array_equal(got[3][some], want[3][some]), "pixel sums"
 
 
+@pytest.mark.parametrize("prec,chain", [(binding.FP32, 48), (binding.BF16, 162)])
+@pytest.mark.parametrize("hs,cs", [(16, 128), (18, 128), (16, 64)])
+def test_long_tiles_are_added_in_chains(ctxs, prec, chain, hs, cs):
+    """A tile of eighty samples, of two segments: a wave's accumulator takes at most `chain` sums of 16 pixels before they go to its partial sums.  Every addition rounds by
+    2^-24 of the running sum at most, which grows as the root of the terms: a chain of c leaves an error of 2^-24 sqrt(c / 2) of the result at most (root mean square over the
+    elements), of c sums of 16 pixels and of the partial sums behind them.  In one chain of more than a thousand the error is 1.5 (bf16) to 3 times this bound."""
+    bf = prec == binding.BF16
+    per = 80
+    n, hb = per, 128 // cs
+    x = layer(ctxs[prec], bf, [n], 3, cs, hs, 2, False, 0, np.random.default_rng([hs, cs]), False)
+    got, want = x.run(per * (700 if bf else 480))[1], x.reference()[1]
+    parts = -(-2 * n * -(-hs * hs // 16) // hb // chain) * hb
+    assert U.rel_l2(got, want) <= 2.0 ** -24 * np.sqrt((chain + parts) / 2)
+
+
 @pytest.mark.parametrize("hs", [4, 8, 16])
 @pytest.mark.parametrize("cs", [64, 128])
 @pytest.mark.parametrize("cb", [1, 3, 4])
