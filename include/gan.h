@@ -279,11 +279,11 @@ gan_status gan_op_conv_wgrad(gan_ctx* ctx, const void* big, const void* small_in
    maps: 0, or n_groups label maps (group g's is one, the others zero), which are input channels cb .. cb + maps - 1 of the weights.
      conv : small = down of the above, plus bias (DEVICE fp32 [n_groups][cs], or NULL); w: DEVICE fp32 [n_groups][4*4][cb + maps][cs], taken in the storage type
      wgrad: grad, DEVICE fp32 [n_groups][16*(cb + maps)*cs + cs + 4]: the weights' gradient, the bias's, and the sums of the image's channels, over
-            the segments.  Of the label maps, group g's own alone is written.  size_samples: the max_total_batch of the step whose sums these are. */
+            the segments.  Of the label maps, group g's own alone is written.  size_samples, size_models: the max_total_batch and n_models of the step whose sums these are. */
 gan_status gan_op_image_conv(gan_ctx* ctx, const void* img, const float* nchw, const int32_t* perm, const float* w, const float* bias, void* small_out,
                              const int32_t* offs, int32_t n_groups, int32_t n_samples, int32_t cb, int32_t cs, int32_t hs, int32_t maps);
 gan_status gan_op_image_wgrad(gan_ctx* ctx, const void* img, const float* nchw, const int32_t* perm, const void* small_in, float* grad,
-                              const int32_t* offs, int32_t n_groups, int32_t n_samples, int32_t cb, int32_t cs, int32_t hs, int32_t maps, int32_t size_samples);
+                              const int32_t* offs, int32_t n_groups, int32_t n_samples, int32_t cb, int32_t cs, int32_t hs, int32_t maps, int32_t size_samples, int32_t size_models);
 /* The row splits of a weight gradient, DEVICE fp32 parts [splits][n_groups][4*4][cb][cs] (2 to 64 splits; cb and cs multiples of 64), added up as
    the update of those weights does on its way: sum [n_groups][4*4][cb][cs], both 16-byte aligned.  Below 262144 values and from 16 splits on in four sums, split
    k in sum k % 4, which are then added in order; otherwise one split after the other. */

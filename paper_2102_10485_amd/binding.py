@@ -79,7 +79,7 @@ def load_library():
     L.gan_op_wgrad_parts.argtypes = [_VP, C.c_int32, C.c_int32]
     L.gan_op_split_sum.argtypes = [_VP, _VP, _VP] + [C.c_int32] * 4
     L.gan_op_image_conv.argtypes = [_VP] * 8 + [C.c_int32] * 6
-    L.gan_op_image_wgrad.argtypes = [_VP] * 7 + [C.c_int32] * 7
+    L.gan_op_image_wgrad.argtypes = [_VP] * 7 + [C.c_int32] * 8
     L.gan_use_second_stream.argtypes = [_VP, C.c_int32]
     L.gan_graph_replays.argtypes = [_VP, C.POINTER(C.c_int64)]
     L.gan_profile_read.argtypes = [_VP, C.c_int32, C.POINTER(C.c_char_p), _I64P, C.POINTER(C.c_double),
@@ -307,9 +307,9 @@ class Gan:
     def op_image_conv(self, img, nchw, perm, w, bias, small_out, offs, n_groups, n_samples, cb, cs, hs, maps=0):
         self._check(self.lib.gan_op_image_conv(self.h, img, nchw, perm, w, bias, small_out, offs, n_groups, n_samples, cb, cs, hs, maps))
 
-    def op_image_wgrad(self, img, nchw, perm, small_in, grad, offs, n_groups, n_samples, cb, cs, hs, maps=0, size_samples=None):
+    def op_image_wgrad(self, img, nchw, perm, small_in, grad, offs, n_groups, n_samples, cb, cs, hs, maps=0, size_samples=None, size_models=None):
         self._check(self.lib.gan_op_image_wgrad(self.h, img, nchw, perm, small_in, grad, offs, n_groups, n_samples, cb, cs, hs, maps,
-                                                n_samples if size_samples is None else size_samples))
+                                                n_samples if size_samples is None else size_samples, size_models or n_groups))
 
     def op_split_sum(self, parts, out, n_groups, splits, cb, cs):
         self._check(self.lib.gan_op_split_sum(self.h, parts, out, n_groups, splits, cb, cs))

@@ -90,7 +90,7 @@ struct gan_ctx {
   // image-side layers: packed weights (and what the label maps and the bias add, by position class), partial weight gradients
   void *wpD = nullptr, *wpG = nullptr;
   float *addD = nullptr, *img_part = nullptr, *img_sums = nullptr, *bias_partial = nullptr, *stat_partial = nullptr;
-  int img_tile = 1;                // samples of a tile of their weight gradients
+  ImageTiles img_tiles = {1, 1};   // of their weight gradients
   float* head_part = nullptr;      // row-split partial sums of the linear head's weight gradient (few models only)
   int head_rsplit = 1;
   float* wg_part = nullptr;        // row-split partial weight gradients (few models only)
@@ -164,24 +164,26 @@ bool dev_alloc(gan_ctx* c, void** p, size_t bytes) {
   return true;
 }
 
-int geom_id(gan_ctx* c, int rps, int tile_rows) {
+int find_geom(const gan_ctx* c, int rps, int tile_rows, int parts) {
   for (int i = 0; i < c->geoms.n; ++i)
-    if (c->geoms.rps[i] == rps && c->geoms.tile_rows[i] == tile_rows) return i;
+    if (c->geoms.rps[i] == rps && c->geoms.tile_rows[i] == tile_rows && c->geoms.parts[i] == parts) return i;
+  return -1;
+}
+int geom_id(gan_ctx* c, int rps, int tile_rows, int parts = 0) {
+  const int g = find_geom(c, rps, tile_rows, parts);
+  if (g >= 0) return g;
   if (c->geoms.n >= MAX_GEOMS) return -1;
   c->geoms.rps[c->geoms.n] = rps;
   c->geoms.tile_rows[c->geoms.n] = tile_rows;
+  c->geoms.parts[c->geoms.n] = parts;
   return c->geoms.n++;
 }
-const int* tmodel_of(gan_ctx* c, int rps, int tile_rows) {
-  if (c->L == 1) return nullptr;
-  for (int i = 0; i < c->geoms.n; ++i)
-    if (c->geoms.rps[i] == rps && c->geoms.tile_rows[i] == tile_rows) return c->rb.tmodel + (long long)i * c->rb.tmodel_stride;
-  return nullptr;
+const int* tmodel_of(gan_ctx* c, int rps, int tile_rows, int parts = 0) {
+  const int g = find_geom(c, rps, tile_rows, parts);
+  return c->L == 1 || g < 0 ? nullptr : c->rb.tmodel + (long long)g * c->rb.tmodel_stride;
 }
-const int* tpre_of(gan_ctx* c, int rps, int tile_rows) {
-  int g = -1;
-  for (int i = 0; i < c->geoms.n; ++i)
-    if (c->geoms.rps[i] == rps && c->geoms.tile_rows[i] == tile_rows) g = i;
+const int* tpre_of(gan_ctx* c, int rps, int tile_rows, int parts = 0) {
+  const int g = find_geom(c, rps, tile_rows, parts);
   if (g < 0) {   // every geometry a launch uses is registered at create; anything else would read an unbuilt prefix
     launch_fail("a launch asked for a tile geometry that was not registered when the context was created");
     return nullptr;   // the launchers refuse a null prefix array
@@ -821,12 +823,13 @@ void image_wgrad_call(gan_ctx* c, Net& net, const ConvLayer& cl, const void* img
   const bool first = &net == &c->D;
   ImageWgradArgs a = {};
   a.img = img; a.real = real; a.perm = c->rb.perm; a.dy = dy; a.part = c->img_part; a.pixel_sums = first ? nullptr : c->img_sums;
-  a.offs = c->rb.offs; a.tpre = tpre_of(c, 1, c->img_tile); a.tmodel = tmodel_of(c, 1, c->img_tile);
-  a.L = c->L; a.CB = cl.Cb; a.Hs = cl.Hs; a.Cs = cl.Cs; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n; a.tile_samples = c->img_tile;
+  a.tiles = c->img_tiles;
+  a.offs = c->rb.offs; a.tpre = tpre_of(c, 1, a.tiles.most, a.tiles.parts); a.tmodel = tmodel_of(c, 1, a.tiles.most, a.tiles.parts);
+  a.L = c->L; a.CB = cl.Cb; a.Hs = cl.Hs; a.Cs = cl.Cs; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n;
   const double rows = (double)n * nseg * cl.Hs * cl.Hs;
   {
     Scope s(c, "wgrad_image", img_flops(cl, n, nseg), sizeof(T) * rows * (4.0 * cl.Cb + cl.Cs));
-    launch_image_wgrad<T>(a, ub_tiles(c, n, 1, c->img_tile), c->st);
+    launch_image_wgrad<T>(a, (int)image_tile_bound(a.tiles, n, c->L), c->st);
   }
   if (first && c->labels > 0) {
     ClassSumArgs b;
@@ -1376,8 +1379,8 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
       reg_gemm(MODE_UP, cl.Cb, cl.Hs * cl.Hs, 1);                               // forward
       reg_gemm(MODE_DOWN, cl.Cs, cl.Hs * cl.Hs, 1);                             // data gradient
     }
-    c->img_tile = image_tile_samples((int)es, NB);
-    reg(1, c->img_tile);                                                        // the weight gradients of the image-side layers
+    c->img_tiles = image_tiles((int)es, NB, L);
+    if (geom_id(c, 1, c->img_tiles.most, c->img_tiles.parts) < 0) ok = false;   // the weight gradients of the image-side layers
     for (int nseg = 1; nseg <= 2; ++nseg) {                                     // D runs on one segment and on both
       for (size_t j = 1; j < c->D.conv.size(); ++j) {
         const ConvLayer& cl = c->D.conv[j];
@@ -1400,7 +1403,8 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
          dev_alloc(c, (void**)&r->sample_model, (size_t)NB * 4) && dev_alloc(c, (void**)&r->sample_slot, (size_t)NB * 4) &&
          dev_alloc(c, (void**)&r->tpre, (size_t)MAX_GEOMS * (L + 1) * 4) && dev_alloc(c, (void**)&r->order, (size_t)L * 4);
     int mx = 1;
-    for (int g = 0; g < c->geoms.n; ++g) mx = std::max(mx, ub_tiles(c, NB, c->geoms.rps[g], c->geoms.tile_rows[g]));
+    for (int g = 0; g < c->geoms.n; ++g)
+      mx = std::max(mx, c->geoms.parts[g] > 0 ? (int)image_tile_bound(c->img_tiles, NB, L) : ub_tiles(c, NB, c->geoms.rps[g], c->geoms.tile_rows[g]));
     r->tmodel_stride = mx;
     ok = ok && dev_alloc(c, (void**)&r->tmodel, (size_t)c->geoms.n * mx * 4);
   }
@@ -1483,7 +1487,7 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
       c->labels = cfg->cond_d;
       ok = ok && dev_alloc(c, (void**)&c->label_sums, (size_t)c->labels * 9 * c1.Cs * 4) && dev_alloc(c, (void**)&c->class_part, (size_t)2 * NB * 9 * c1.Cs * 4);
     }
-    const size_t d1 = (size_t)16 * image_values(c1.Cb) * c1.Cs, g1 = c->paper ? 0 : (size_t)16 * image_values(gl.Cb) * gl.Cs, part = 16 * image_values(c1.Cb) * 128, tiles = ub_tiles(c, NB, 1, c->img_tile);
+    const size_t d1 = (size_t)16 * image_values(c1.Cb) * c1.Cs, g1 = c->paper ? 0 : (size_t)16 * image_values(gl.Cb) * gl.Cs, part = 16 * image_values(c1.Cb) * 128, tiles = image_tile_bound(c->img_tiles, NB, L);
     ok = ok && dev_alloc(c, &c->wpD, (size_t)L * d1 * es) && dev_alloc(c, &c->wpG, (size_t)L * g1 * es) &&
          dev_alloc(c, (void**)&c->addD, (size_t)(c->labels > 0 ? c->labels : L) * 9 * c1.Cs * 4) &&
          dev_alloc(c, (void**)&c->img_part, tiles * part * 4) && dev_alloc(c, (void**)&c->img_sums, tiles * 4 * 4) &&
@@ -2119,15 +2123,18 @@ gan_status gan_op_image_conv(gan_ctx* c, const void* img, const float* nchw, con
   return finish_op(c);
 }
 gan_status gan_op_image_wgrad(gan_ctx* c, const void* img, const float* nchw, const int32_t* perm, const void* small_in, float* grad, const int32_t* offs,
-                              int32_t n_groups, int32_t n_samples, int32_t cb, int32_t cs, int32_t hs, int32_t maps, int32_t size_samples) {
+                              int32_t n_groups, int32_t n_samples, int32_t cb, int32_t cs, int32_t hs, int32_t maps, int32_t size_samples,
+                              int32_t size_models) {
   ImageOp op;
-  if (!small_in || !grad || size_samples < n_samples) return GAN_E_ARG;
+  if (!small_in || !grad || size_samples < n_samples || size_models < 1) return GAN_E_ARG;
   const gan_status s = image_op_begin(c, op, img, nchw, perm, offs, n_groups, n_samples, cb, cs, hs, maps);
   if (s != GAN_OK) return s;
-  const int per = image_tile_samples((int)esize(c), size_samples), P = image_values(cb);
+  const ImageTiles tiling = image_tiles((int)esize(c), size_samples, size_models);
+  const int P = image_values(cb);
   std::vector<int> tpre(1, 0), tmodel;
   for (int l = 0; l < n_groups; ++l) {
-    tmodel.insert(tmodel.end(), (op.offs[l + 1] - op.offs[l] + per - 1) / per, l);
+    const int own = op.offs[l + 1] - op.offs[l], per = image_tile(tiling, own);
+    tmodel.insert(tmodel.end(), (own + per - 1) / per, l);
     tpre.push_back((int)tmodel.size());
   }
   const int tiles = (int)tmodel.size();
@@ -2136,7 +2143,7 @@ gan_status gan_op_image_wgrad(gan_ctx* c, const void* img, const float* nchw, co
   a.part = (float*)op.hold((size_t)(128 / cs) * tiles * 16 * P * cs * 4); a.pixel_sums = (float*)op.hold((size_t)tiles * 4 * 4);
   a.tpre = op.hold(tpre); a.tmodel = op.hold(tmodel);
   if (!a.part || !a.pixel_sums || !a.tpre || !a.tmodel) return fail(c, GAN_E_OOM, "image-side partial sums alloc");
-  a.L = n_groups; a.CB = cb; a.Hs = hs; a.Cs = cs; a.nseg = c->op_segments; a.seg_samples = n_samples; a.tile_samples = per;
+  a.L = n_groups; a.CB = cb; a.Hs = hs; a.Cs = cs; a.nseg = c->op_segments; a.seg_samples = n_samples; a.tiles = tiling;
   ImageGradArgs g = {};
   g.part = a.part; g.pixel_sums = a.pixel_sums; g.tpre = a.tpre; g.L = n_groups; g.CB = cb; g.CBT = cb + maps; g.Cs = cs; g.P = P; g.plane_labels = maps > 0;
   const long long taps = 16LL * g.CBT * cs;

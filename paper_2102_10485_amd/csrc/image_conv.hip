@@ -321,7 +321,7 @@ __global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? (EVEN ?
   const int tile = blockIdx.x;
   if (tile >= a.tpre[a.L]) return;
   const int l = a.tmodel ? a.tmodel[tile] : 0;
-  const int j0 = a.offs[l] + (tile - a.tpre[l]) * a.tile_samples, j1 = min(a.offs[l + 1], j0 + a.tile_samples);
+  const int per_tile = image_tile(a.tiles, a.offs[l + 1] - a.offs[l]), j0 = a.offs[l] + (tile - a.tpre[l]) * per_tile, j1 = min(a.offs[l + 1], j0 + per_tile);
   const int Hs = a.Hs, Hb = 2 * Hs, npix = Hb * Hb;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int trows = 2 * u.ph + 2, plane = (trows + ZERO_ROWS) * u.pitch, buf = PL * plane;
@@ -714,8 +714,6 @@ template <typename F> bool with_channels(int CB, int Cs, F&& f) {
 }  // namespace
 
 int image_values(int CB) { return img_values(CB); }
-// Samples of a tile of the weight gradient: a round of blocks at the sizing batch, three a CU in bf16 and two in fp32.
-int image_tile_samples(int esize, int size_samples) { const int tiles = esize == 4 ? 480 : 700; return std::max(1, (size_samples + tiles - 1) / tiles); }
 
 template <typename T> void launch_image_conv(const ImageConvArgs& a, hipStream_t st) {
   if (a.n == 0 || a.nseg == 0) return;
@@ -730,7 +728,7 @@ template void launch_image_conv<bf16_t>(const ImageConvArgs&, hipStream_t);
 
 template <typename T> void launch_image_wgrad(const ImageWgradArgs& a, int ub_tiles, hipStream_t st) {
   if (ub_tiles == 0 || a.nseg == 0) return;
-  if (!a.img || !a.dy || !a.part || !a.offs || !a.tpre || (a.L > 1 && !a.tmodel) || (a.real && !a.perm) || a.tile_samples < 1 || a.Hs < 1)
+  if (!a.img || !a.dy || !a.part || !a.offs || !a.tpre || (a.L > 1 && !a.tmodel) || (a.real && !a.perm) || a.tiles.most < 1 || a.tiles.parts < 1 || a.Hs < 1)
     return launch_fail("image-side weight gradient: null operand");
   if ((long long)a.Hs * a.Hs * a.Cs * (long long)sizeof(T) >= (1LL << 31)) return launch_fail("image-side weight gradient: a sample of 2 GiB or larger");
   if (!with_channels(a.CB, a.Cs, [&](auto cb, auto cs) { wgrad_one<T, cb.value, cs.value>(a, ub_tiles, st); }))

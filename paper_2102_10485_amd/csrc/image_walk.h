@@ -28,6 +28,27 @@ inline Units img_units(int Hs, int CB, int side_y) {
 // a fixed distance apart.
 inline bool even_units(const Units& u, int Hs, int CS) { return u.pw == 16 && u.nx * u.pw == Hs && u.ny * u.ph == Hs && u.ph % (128 / CS) == 0; }
 
+// Samples of a tile of the weight gradient.  A model's tiles are `parts` of its own samples, of `most` samples at most: at the sizing batch a round of blocks over all
+// models (three a CU in bf16, two in fp32), and in calls of fewer samples as many blocks of shorter tiles.  What a model's tiles are follows from its own samples
+// and the configuration.  Steps of 64 samples of one pair sized for
+// 6400, with tiles of `most` (seven blocks) and with these, us: 28x28 in fp32 728 and 518, in bf16 448 and 369, 32x32 in bf16 1182 and 1093; of eight 64x64 pairs sized
+// for 1024 1564 and 1528; steps of the sizing batch as they were.
+struct ImageTiles { int most, parts; };
+inline ImageTiles image_tiles(int esize, long long size_samples, int L) {
+  const int tiles = esize == 4 ? 480 : 700;
+  const long long most = (size_samples + tiles - 1) / tiles, parts = tiles / L;
+  return ImageTiles{most < 1 ? 1 : (int)most, parts < 1 ? 1 : (int)parts};
+}
+GAN_HOST_DEVICE_INLINE int image_tile(const ImageTiles& t, int samples) {
+  const int per = (samples + t.parts - 1) / t.parts;
+  return per < 1 ? 1 : (per < t.most ? per : t.most);
+}
+// no more tiles than this of n samples, however they fall: a model has `parts`, or one more than whole ones of `most`
+inline long long image_tile_bound(const ImageTiles& t, long long n, int L) {
+  const long long b = (n < L ? n : L) * (long long)t.parts + n / t.most;
+  return b < n ? b : n;
+}
+
 struct UnitAt { int seg, j, y0, x0; };
 // along x, along y, the next sample, the next segment
 GAN_DEVICE_INLINE void next_unit(UnitAt& t, const Units& u, int Hs, int j0, int j1) {

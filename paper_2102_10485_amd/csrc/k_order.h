@@ -5,8 +5,10 @@
 #if defined(__HIPCC__)
 #include <hip/hip_runtime.h>
 #define GAN_DEVICE_INLINE __device__ __forceinline__
+#define GAN_HOST_DEVICE_INLINE __host__ __device__ __forceinline__
 #else
 #define GAN_DEVICE_INLINE inline
+#define GAN_HOST_DEVICE_INLINE inline
 #endif
 
 namespace gan {

@@ -3,17 +3,20 @@
 #pragma once
 
 #include "common.h"
+#include "image_walk.h"
 
 namespace gan {
 
 constexpr int ROUTE_WAVES = 16;     // runs of the flat batch, one wave each
 constexpr int MAX_GEOMS = 60;
 
-// One "geometry" = how rows of a layer split into tiles: rows per sample and rows per tile.
+// One "geometry" = how rows of a layer split into tiles: rows per sample and rows per tile; or, where parts is not 0 (one row a sample), the most of them a
+// tile, by ImageTiles.
 struct GeomTable {
   int n;
   int rps[MAX_GEOMS];
   int tile_rows[MAX_GEOMS];
+  int parts[MAX_GEOMS];
 };
 
 struct RouteBuffers {
@@ -133,18 +136,18 @@ struct ImageConvArgs {
   float slope;              // factor below zero
 };
 template <typename T> void launch_image_conv(const ImageConvArgs& a, hipStream_t st);
-int image_tile_samples(int esize, int size_samples);    // samples of a model that a tile of the weight gradient takes
 struct ImageWgradArgs {
   const void* img;
   const float* real;
   const int* perm;
   const void* dy;           // [rows][Cs], rows indexed by absolute sample
-  float* part;              // [tiles][16 P][Cs], partial sums of every tile of tile_samples samples (Cs = 64: and as much again behind the launch's tiles, scratch)
+  float* part;              // [tiles][16 P][Cs], partial sums of every tile (Cs = 64: and as much again behind the launch's tiles, scratch)
   float* pixel_sums;        // [tiles][4]: the sums of the image's pixels, or NULL
   const int* offs;
   const int* tpre;          // the prefix array and models of the tiles (tmodel NULL: one model)
   const int* tmodel;
-  int L, CB, Hs, Cs, seg_first, nseg, seg_samples, tile_samples;
+  int L, CB, Hs, Cs, seg_first, nseg, seg_samples;
+  ImageTiles tiles;
 };
 template <typename T> void launch_image_wgrad(const ImageWgradArgs& a, int ub_tiles, hipStream_t st);
 // The row splits of the linear head's weight gradient (HeadArgs, rsplit > 1), which another kernel of D's backward pass adds up along the way

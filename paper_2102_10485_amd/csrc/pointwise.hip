@@ -86,10 +86,17 @@ __global__ __launch_bounds__(ROUTE_THREADS) void route_kernel(const int* __restr
     const int rps = g < 0 ? 1 : geoms.rps[g], tr = g < 0 ? 1 : geoms.tile_rows[g];
     int* dst = g < 0 ? rb.offs : rb.tpre + (long long)g * (L + 1);
     const int sh = (tr & (tr - 1)) == 0 ? __ffs(tr) - 1 : -1;      // tile heights are powers of two
+    const int parts = g < 0 ? 0 : geoms.parts[g];
     int run = 0;
     for (int l0 = 0; l0 < L; l0 += 64) {
       const int c = l0 + lane < L ? cl[l0 + lane] * rps + tr - 1 : 0;
-      const int v = sh >= 0 ? c >> sh : c / tr;
+      int v;
+      if (parts > 0) {
+        const int own = l0 + lane < L ? cl[l0 + lane] : 0, per = image_tile(ImageTiles{tr, parts}, own);
+        v = (own + per - 1) / per;
+      } else {
+        v = sh >= 0 ? c >> sh : c / tr;
+      }
       int incl = v;
 #pragma unroll
       for (int d = 1; d < 64; d <<= 1) {

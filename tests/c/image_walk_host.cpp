@@ -30,3 +30,19 @@ extern "C" void image_walk(int esize, int CB, int Hs, int CS, int j0, int j1, in
   if (esize == 2) { if (CS == 64) GO(2, 64); else GO(2, 128); }
   else { if (CS == 64) GO(4, 64); else GO(4, 128); }
 }
+
+// tiles of the weight gradient: how many, of counts[0 .. L) samples, in a context sized for `size`; at[0], at[1]: the bound the host launches, the longest tile
+extern "C" int image_walk_tiles(int esize, int size, int L, const int* counts, int* at) {
+  const gan::ImageTiles t = gan::image_tiles(esize, size, L);
+  long long n = 0;
+  int tiles = 0;
+  at[1] = 0;
+  for (int l = 0; l < L; ++l) {
+    const int per = gan::image_tile(t, counts[l]);
+    tiles += (counts[l] + per - 1) / per;
+    if (counts[l] > 0 && per > at[1]) at[1] = per;
+    n += counts[l];
+  }
+  at[0] = (int)gan::image_tile_bound(t, n, L);
+  return tiles;
+}

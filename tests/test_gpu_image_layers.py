@@ -76,14 +76,14 @@ class Layer:
         self.g.op_wgrad_parts(self.S, 1)
         return self.d_img.data_ptr(), self.d_real.data_ptr() if self.nchw else None, self.d_perm.data_ptr()
 
-    def run(self, size_samples=None):
+    def run(self, size_samples=None, size_models=None):
         """forward [segments][n][cs][hs][hs]; gradients of weights [groups][cs][cb + maps][16], biases [groups][cs], pixel sums [groups][cb]"""
         try:
             src = self._parts()
             self.g.op_image_conv(*src, self.d_w.data_ptr(), self.d_bias.data_ptr(), self.out.data_ptr(), self.d_offs.data_ptr(), self.G, self.n, self.cb, self.cs,
                                  self.hs, self.maps)
             self.g.op_image_wgrad(*src, self.d_dy.data_ptr(), self.grad.data_ptr(), self.d_offs.data_ptr(), self.G, self.n, self.cb, self.cs, self.hs, self.maps,
-                                  size_samples)
+                                  size_samples, size_models)
         finally:
             self.g.op_wgrad_parts(1, 1)
         out = U.unpack(self.out, self.bf, (self.S, self.n, self.hs, self.hs, self.cs)).transpose(0, 1, 4, 2, 3)
@@ -123,7 +123,7 @@ def layer(g, bf, groups, cb, cs, hs, segments, nchw, maps, rng, whole):
 
 
 EXACT = [
-    # group sizes, sizing batch, segments, segment 0 from the caller's batch, label maps
+    # group sizes, sizing batch (of as many models that a model's samples are one tile if that may be so long), segments, segment 0 from the caller's batch, label maps
     ([3, 0, 2], 5, 2, True, True),         # a sample a tile
     ([5, 4], 2100, 2, True, False),        # tiles of three samples (bf16) and of five (fp32): full ones, ragged ones
     ([7], 4900, 1, False, False),          # one tile of all seven
@@ -142,7 +142,7 @@ def test_sums_of_whole_numbers(ctxs, prec, groups, size, segments, nchw, maps, h
     bf = prec == binding.BF16
     rng = np.random.default_rng([hs, cs, cb, size])
     x = layer(ctxs[prec], bf, groups, cb, cs, hs, segments, nchw, len(groups) if maps else 0, rng, True)
-    got, want = x.run(size), x.reference()
+    got, want = x.run(size, 700), x.reference()
     assert np.abs(want[0]).max() < 256 and max(np.abs(a).max() for a in want[1:]) < 2 ** 24
     assert np.array_equal(got[0], want[0]), "forward"
     assert np.array_equal(x.own_maps(got[1]), x.own_maps(want[1])), "weights' gradient"
@@ -161,7 +161,7 @@ def test_long_tiles_are_added_in_chains(ctxs, prec, chain, hs, cs):
     per = 80
     n, hb = per, 128 // cs
     x = layer(ctxs[prec], bf, [n], 3, cs, hs, 2, False, 0, np.random.default_rng([hs, cs]), False)
-    got, want = x.run(per * (700 if bf else 480))[1], x.reference()[1]
+    got, want = x.run(per * (700 if bf else 480), 700)[1], x.reference()[1]
     parts = -(-2 * n * -(-hs * hs // 16) // hb // chain) * hb
     assert U.rel_l2(got, want) <= 2.0 ** -24 * np.sqrt((chain + parts) / 2)
 

@@ -1,5 +1,5 @@
 """What the image-side weight gradient requests of the feature gradient (csrc/image_walk.h), on the host: every value of a tile's samples once, at
-its own address, and behind the last unit, where the buffer is empty, only offsets that cannot wrap its size round."""
+its own address, and behind the last unit, where the buffer is empty, only offsets that cannot wrap its size round.  And the tiles it takes them in."""
 import ctypes
 import os
 import subprocess
@@ -45,3 +45,36 @@ def test_requests(lib, esize, CS, side):
                 assert np.all(uni[:want] < per * 16) and byte.min(initial=0) >= 0 and byte.max(initial=0) + 16 <= per * 16
                 np.add.at(seen, (seg[:want][there], j[:want][there] - j0, byte // 16), 1)
     assert np.all(seen == 1)
+
+
+def tiles(lib, esize, size, counts):
+    at, c = (ctypes.c_int * 2)(), (ctypes.c_int * len(counts))(*[int(v) for v in counts])
+    return lib.image_walk_tiles(esize, size, len(counts), c, at), at[0], at[1]
+
+
+@pytest.mark.parametrize("esize", [2, 4])
+@pytest.mark.parametrize("L,size,n", [(1, 6400, 64), (1, 6400, 1), (10, 1280, 100), (100, 6400, 400), (100, 6400, 50), (8, 1024, 64), (20, 20000, 333)])
+def test_small_calls_of_large_contexts(lib, esize, L, size, n):
+    """A call of few samples has a block for nearly every sample, as long as that does not take more blocks than a full call: tiles as long as those of the
+    sizing batch were a chain of their ten or more samples in a few blocks."""
+    counts = np.full(L, n // L) + (np.arange(L) < n % L)
+    got, _, _ = tiles(lib, esize, size, counts)
+    assert got >= min(n, tiles(lib, esize, size, np.full(L, size // L))[0] // 2)
+
+
+@pytest.mark.parametrize("esize", [2, 4])
+@pytest.mark.parametrize("L", [1, 3, 10, 100, 479, 701, 2200])
+def test_bound_of_the_tiles(lib, esize, L):
+    """However the samples fall, no more tiles than the host launches blocks and holds partial sums for; none longer than at the sizing batch."""
+    rng = np.random.default_rng(L)
+    for _ in range(300):
+        size = int(np.exp(rng.uniform(0, np.log(30000)))) + 1
+        n = size if rng.random() < 0.3 else int(rng.integers(0, size + 1))
+        p = rng.dirichlet(np.full(L, np.exp(rng.uniform(-5, 4))))
+        counts = rng.multinomial(n, p / p.sum())
+        got, bound, longest = tiles(lib, esize, size, counts)
+        whole = tiles(lib, esize, size, [size] + [0] * (L - 1))[1]
+        assert got <= bound <= max(whole, n) and bound <= n and longest <= -(-size // (480 if esize == 4 else 700))
+    # evenly at the sizing batch: a round of blocks
+    if L <= 100:
+        assert tiles(lib, esize, 64 * L, np.full(L, 64))[0] <= (480 if esize == 4 else 700) + L
