@@ -1264,9 +1264,11 @@ __global__ __launch_bounds__(256) void adam_rest_kernel(AdamArgs a, AdamImage im
   if constexpr (LABELS) adam_label_maps<T>(a, im, (int)((b - gap_blocks) * 256 + threadIdx.x));
 }
 
-// Launches of at most this many 64 x 64 tiles take them in quarters: whole, they leave CUs without a block, or a second round nearly empty, and the update waits
+// Launches of fewer 64 x 64 tiles than this take them in quarters: whole, they leave CUs without a block, or a second round nearly empty, and the update waits
 // for one block's chain of loads, divisions and stores.  Whole tiles and quarters, with splits: 32 tiles 18.3 and 9.9 us, 128 tiles 22.6 and 18.0, 320 18.4
-// and 16.3 (bf16), 22.2 and 19.7 to 23.2 (fp32), 512 28.1 and 29.5, 1024 41 and 41; without, 4096 91 and 90.
+// and 16.3 (bf16), 22.2 and 19.7 to 23.2 (fp32), 512 28.1 and 29.5, 1024 41 and 41; without, 4096 91 and 90.  The launch of the gaps has quarters of as many all the
+// same, which cost less than a launch: all four of a 32x32 pair's update launches, with 512 tiles in each network, 87 us in fp32 and 78 in bf16; quarters in both
+// places 92 and 80, a launch more in place of the quarters 90 and 85.
 constexpr long long ADAM_FEW_TILES = 512;
 // Fills the launch geometry: the tiled regions (sorted by offset: the caller's job) and the gaps between them, which
 // cover the rest of [0, P).  False (and a launch error) when the regions do not fit the kernels.
@@ -1344,7 +1346,7 @@ void launch_adam_region(AdamArgs a, int region, const AdamSplits& sp, hipStream_
   if (!set_region(a, region, sp)) return;
   const long long blocks = (long long)a.tile_count * a.L;
   if (blocks == 0) return;
-  const bool quarters = blocks <= ADAM_FEW_TILES;
+  const bool quarters = blocks < ADAM_FEW_TILES;
   const dim3 grid((unsigned)(quarters ? 4 * blocks : blocks));
   if (quarters) {
     if (sp.n > 1) hipLaunchKernelGGL((adam_tile_kernel<T, 16, true>), grid, dim3(256), 0, st, a, sp);
