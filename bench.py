@@ -240,7 +240,7 @@ def mfma_summary(kern, peak):
 
 
 # the bandwidth-bound kernel families reported against the HBM peak (algorithmic bytes: every input read once, every
-# output written once, in the storage type; Adam: 28 B per parameter plus the storage-type copies)
+# output written once, in the storage type; Adam: 28 B per parameter plus the storage-type copies and the row splits of the gradients)
 ELEMENTWISE = ("adam", "bn_apply", "bn_bwd_reduce", "bn_bwd_apply", "bn_apply_head", "up_img", "head_bwd",
                "stage", "transpose_w")
 

@@ -1234,26 +1234,31 @@ AdamArgs adam_args(gan_ctx* c, Net& net) {
 // bytes one update moves per element: g, theta, m, v in; theta, m, v out; the storage-type copy (tiled regions: and the transposed
 // one; fp32: both as three planes, or with few rows a model the transposed one alone)
 inline double adam_bytes_per_element(const gan_ctx* c) { return 28.0 + (c->bf16 ? 2.0 : 0.0); }
+// ... of one region: what is moved of it, and, where the update adds up row splits, these and their sum in place of the gradient
+double adam_region_bytes(const gan_ctx* c, const AdamArgs& a, int region, const AdamSplits& sp) {
+  const double per = adam_bytes_per_element(c) + (c->bf16 ? 2.0 : c->presplit ? 12.0 : 4.0) + (sp.n > 1 ? 4.0 * sp.n : 0.0);
+  return (double)c->L * (a.k3 ? 9 : 16) * a.reg_cb_real[region] * a.reg_cs_real[region] * per;
+}
 template <typename T>
 void adam_region_call(gan_ctx* c, const AdamArgs& a, int region, hipStream_t st, const AdamSplits& sp) {
-  double elems = 0;
+  double bytes = 0;
   for (int r = 0; r < a.nregions; ++r)
-    if (region < 0 || r == region) elems += 16.0 * a.reg_cb[r] * a.reg_cs[r];
-  Scope s(c, "adam", 0, (double)c->L * elems * (adam_bytes_per_element(c) + (c->bf16 ? 2.0 : c->presplit ? 12.0 : 4.0)), nullptr, st);
+    if (region < 0 || r == region) bytes += adam_region_bytes(c, a, r, sp);
+  Scope s(c, "adam", 0, bytes, nullptr, st);
   launch_adam_region<T>(a, region, sp, st);
 }
 // what is left of a planned update once the regions are done (or enqueued beside): the gaps, the operand of the image-side layer, and
 // the region that a backward pass has left (AdamTail)
 template <typename T>
 void adam_rest_call(gan_ctx* c, Net& net, const AdamArgs& a, const AdamTail& tail = {}) {
-  double elems = tail.region >= 0 ? 16.0 * a.reg_cb[tail.region] * a.reg_cs[tail.region] : 0;
+  double elems = 0;
   for (int r = 0; r < a.ngaps; ++r) elems += (double)(a.gap_hi[r] - a.gap_lo[r]);
   const bool first = &net == &c->D;
   const ConvLayer& cl = first ? net.conv.front() : net.conv.back();
   AdamImage im;
   im.w = cl.w; im.packed = first ? c->wpD : c->wpG; im.add = first && cl.CBT > cl.Cb ? c->addD : nullptr;
   im.CB = cl.Cb; im.CBT = cl.CBT; im.Cs = cl.Cs; im.P = image_values(cl.Cb); im.tables = c->labels > 0 ? c->labels : c->L;
-  Scope s(c, "adam", 0, (double)c->L * elems * adam_bytes_per_element(c));
+  Scope s(c, "adam", 0, (double)c->L * elems * adam_bytes_per_element(c) + (tail.region >= 0 ? adam_region_bytes(c, a, tail.region, tail.splits) : 0));
   launch_adam_rest<T>(a, im, tail.region, tail.splits, c->st);
 }
 // the whole update on the caller's stream

@@ -139,3 +139,29 @@ def test_memory_of_parameters_in_fp32():
     linear = 16 * 512 * (64 + 1)
     want = 16 * (9 * w + linear) + 16 * w * (4 + 12) + 16 * 512 * 512 * 4
     assert 0.97 * want <= per <= 1.05 * want, (per, want)
+
+
+def _profiled(spec_name, models, labels, n, prec):
+    torch = U.torch_mod()
+    spec = synth.SPECS[spec_name]
+    g = binding.Gan(binding.make_config(spec, models, labels, n, prec), torch.cuda.current_stream().cuda_stream)
+    lab = torch.arange(n, dtype=torch.int32, device="cuda") % labels
+    z = torch.randn((n, spec["z_dim"]), device="cuda")
+    x = torch.randn((n, spec["img_c"], spec["img_hw"], spec["img_hw"]), device="cuda").tanh()
+    g.train_step(lab.data_ptr(), z.data_ptr(), x.data_ptr(), n)
+    g.profile_enable(True)
+    g.train_step(lab.data_ptr(), z.data_ptr(), x.data_ptr(), n)
+    prof = g.profile_read()
+    counts = [g.param_count(w) for w in (0, 1)]
+    g.close()
+    return spec, counts, prof
+
+
+def test_bytes_of_the_update():
+    """What the profile books for the update is what it moves: of the tables' discriminator no fourth taps and padded channels (a parameter is 28 bytes, its copies 2 each; the
+    rows of G's linear layer are padded from 100 to 128 columns), and of a pair whose weight gradients come in row splits these as well."""
+    spec, (g, d), prof = _profiled("paper32", 4, 4, 64, binding.BF16)
+    wide = 28 * spec["g_ch"][0] * spec["g_h0"] ** 2
+    assert 4 * 28 * (g + d) < prof["adam"]["bytes"] <= 1.02 * 4 * (32 * d + 30 * (g + wide))
+    _, (g, d), prof = _profiled("mnist", 1, 10, 64, binding.FP32)
+    assert prof["adam"]["bytes"] > 40 * (g + d)                   # (without the splits: 28 bytes, and 12 of copies at most)
