@@ -240,9 +240,10 @@ def mfma_summary(kern, peak):
 
 
 # the bandwidth-bound kernel families reported against the HBM peak (algorithmic bytes: every input read once, every
-# output written once, in the storage type; Adam: 28 B per parameter plus the storage-type copies and the row splits of the gradients)
+# output written once, in the storage type; Adam: 28 B per parameter plus the storage-type copies and the row splits of the gradients).  The image-side
+# layers are products, bound by the feature tensor that they write or read.
 ELEMENTWISE = ("adam", "bn_apply", "bn_bwd_reduce", "bn_bwd_apply", "bn_apply_head", "up_img", "head_bwd",
-               "stage", "transpose_w")
+               "image_conv", "image_conv_grad", "image_wgrad", "image_wgrad_sum", "stage", "transpose_w")
 
 
 def main():

@@ -814,7 +814,7 @@ void image_conv_call(gan_ctx* c, const ConvLayer& cl, const void* img, const flo
   a.L = c->L; a.n = n; a.CB = cl.Cb; a.Hs = cl.Hs; a.Cs = cl.Cs; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n;
   a.slope = grad ? 1.f : c->cfg.leaky_slope;
   const double rows = (double)n * nseg * cl.Hs * cl.Hs;
-  Scope s(c, grad ? "gemm_image_grad" : "gemm_image", img_flops(cl, n, nseg), sizeof(T) * rows * (4.0 * cl.Cb + cl.Cs));
+  Scope s(c, grad ? "image_conv_grad" : "image_conv", img_flops(cl, n, nseg), sizeof(T) * rows * (4.0 * cl.Cb + cl.Cs));
   launch_image_conv<T>(a, c->st);
 }
 // Its weight gradient, into the network's gradient block: the taps, the label maps and the bias of D's first layer, the taps and the bias of G's last.
@@ -828,7 +828,7 @@ void image_wgrad_call(gan_ctx* c, Net& net, const ConvLayer& cl, const void* img
   a.L = c->L; a.CB = cl.Cb; a.Hs = cl.Hs; a.Cs = cl.Cs; a.seg_first = seg_first; a.nseg = nseg; a.seg_samples = n;
   const double rows = (double)n * nseg * cl.Hs * cl.Hs;
   {
-    Scope s(c, "wgrad_image", img_flops(cl, n, nseg), sizeof(T) * rows * (4.0 * cl.Cb + cl.Cs));
+    Scope s(c, "image_wgrad", img_flops(cl, n, nseg), sizeof(T) * rows * (4.0 * cl.Cb + cl.Cs));
     launch_image_wgrad<T>(a, (int)image_tile_bound(a.tiles, n, c->L), c->st);
   }
   if (first && c->labels > 0) {
@@ -846,6 +846,10 @@ void image_wgrad_call(gan_ctx* c, Net& net, const ConvLayer& cl, const void* img
   if (first && c->head_rsplit > 1) g.head = {c->head_part, net.g + net.fc_w, net.g + net.fc_b, net.K, c->head_rsplit};
   g.labels = first ? c->labels : 0; g.label_sums = c->label_sums; g.plane_labels = first && cl.CBT > cl.Cb && c->labels == 0;
   g.pstride = net.P; g.L = c->L; g.CB = cl.Cb; g.CBT = cl.CBT; g.Cs = cl.Cs; g.P = image_values(cl.Cb);
+  // the tiles' sums (of as many tiles as evenly spread samples have), the gradients, the head's splits
+  const int own = (n + c->L - 1) / c->L, per = image_tile(a.tiles, own);
+  const double sums = (double)c->L * 16 * cl.Cs * ((own + per - 1) / per * g.P + cl.CBT), heads = g.head.part ? (double)c->L * (g.head.rsplit + 1) * g.head.K : 0;
+  Scope s(c, "image_wgrad_sum", 0, 4.0 * (sums + heads));
   launch_image_wgrad_final(g, c->st);
 }
 

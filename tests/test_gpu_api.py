@@ -165,3 +165,11 @@ def test_bytes_of_the_update():
     assert 4 * 28 * (g + d) < prof["adam"]["bytes"] <= 1.02 * 4 * (32 * d + 30 * (g + wide))
     _, (g, d), prof = _profiled("mnist", 1, 10, 64, binding.FP32)
     assert prof["adam"]["bytes"] > 40 * (g + d)                   # (without the splits: 28 bytes, and 12 of copies at most)
+
+
+def test_profile_rates_the_image_layers_against_memory():
+    """bench.py takes every family named gemm_.. or wgrad.. for a product bound by the matrix pipe; the image-side layers are bound by their feature tensors."""
+    _, _, prof = _profiled("tiny3", 3, 3, 48, binding.BF16)
+    assert {"image_conv", "image_conv_grad", "image_wgrad", "image_wgrad_sum"} <= set(prof)
+    import bench
+    assert not any(bench.is_mfma(k) for k in prof if "image" in k) and {k for k in prof if "image" in k} <= set(bench.ELEMENTWISE)
