@@ -159,7 +159,7 @@ def build_workload(args, config, torch, binding, synth, prec_name, single_pair=N
             n_labels = max(work.n_labels, 2)
             spec["cond_g"] = spec["cond_d"] = n_labels
             # one model owns the whole batch, and the library addresses one model's slice of any tensor with 32-bit
-            # byte offsets; the largest slice is the patch matrix of D's first layer, counted with a column per label and class
+            # byte offsets; gan_create counts D's first layer with 16 columns a channel and 9 a label, in lines of 64
             kc = -(-(16 * spec["img_c"] + 9 * n_labels + 1) // 64) * 64
             row_bytes = kc * (2 if prec_name == "bf16" else 4) * (spec["img_hw"] // 2) ** 2
             n = min(n, ((1 << 31) - 1) // row_bytes // 64 * 64)

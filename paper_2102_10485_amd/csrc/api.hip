@@ -623,10 +623,10 @@ Weights layer_weights(const gan_ctx* c, const Net& net, const ConvLayer& cl, boo
 }
 template <typename T>
 void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, const Weights& W, void* Out,
-               const void* Aux, int C, int N, int Hin, int Hr, int seg_first, int nseg, int n, int w_nstride = 0,
-               double flops_alg = -1.0, bool stats = false, const NormArgs* known = nullptr, const float* bias = nullptr) {
+               const void* Aux, int C, int N, int Hin, int Hr, int seg_first, int nseg, int n,
+               bool stats = false, const NormArgs* known = nullptr, const float* bias = nullptr) {
   ConvArgs a = {};
-  a.A = A; a.W = W.w; a.Out = Out; a.Aux = Aux; a.w_nstride = w_nstride ? w_nstride : N;
+  a.A = A; a.W = W.w; a.Out = Out; a.Aux = Aux; a.w_nstride = N;
   a.tile = layer_tile(c, mode, N, Hr * Hr, nseg);
   const int tr = conv_tile_rows((int)sizeof(T), a.tile);
   a.offs = c->rb.offs; a.tpre = tpre_of(c, Hr * Hr, tr); a.tmodel = tmodel_of(c, Hr * Hr, tr);
@@ -646,7 +646,7 @@ void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, c
   const int phases = mode == MODE_UP ? 4 : 1;
   const double rows = (double)n * nseg * Hr * Hr * phases;
   const double frac = mode == MODE_DENSE ? 1.0 : valid_tap_fraction(Hr);
-  const double flops = flops_alg >= 0 ? flops_alg : 2.0 * rows * N * C * ntaps * frac;
+  const double flops = 2.0 * rows * N * C * ntaps * frac;
   const double in_elems = mode == MODE_DENSE ? rows * C : (double)n * nseg * Hin * Hin * C;
   const double bytes = sizeof(T) * (in_elems + rows * N + (double)c->L * (mode == MODE_DENSE ? 1 : 16) * C * N);
   char detail[64];
@@ -660,7 +660,9 @@ void conv_call(gan_ctx* c, const char* name, int mode, int epi, const void* A, c
 // are shared by this many blocks per tile, whose partial results are added in a fixed order.  The number with the
 // smallest estimated time: the products at the rate a full chip reaches, stretched by what the last round of blocks
 // leaves idle, plus writing and adding the partial results.  A function of the configuration only -- the number of
-// models, the sizing batch and the layer's shape -- never of a call's batch.
+// models, the sizing batch and the layer's shape -- never of a call's batch.  Partial results are charged with their writing, their reading and a launch that
+// writes the sum.  That launch is left to the linear layers and the tables' networks; where the update adds them up on its way (wgrad_call, leave) a split
+// costs that much less than it is charged with, which no number of splits has been measured again for.
 int wgrad_ksplit(const gan_ctx* c, int Cb, int Cs, int ntaps, int Hs, int nseg) {
   const double blocks = (double)c->L * wgrad_tiles_per_model((int)esize(c), ntaps, Cb, Cs);
   const double rows = (double)c->NB * nseg * Hs * Hs, out = (double)c->L * ntaps * Cb * Cs * 4;
@@ -683,25 +685,19 @@ int wgrad_ksplit(const gan_ctx* c, int Cb, int Cs, int ntaps, int Hs, int nseg) 
   return best;
 }
 
-// ksplit == 0: split as wgrad_ksplit says, through c->wg_part, and leave the sum in dW; ksplit >= 1: the caller's
-// own split (partials left at dW + split * L * stride).  leave (ksplit == 0): what the update of these weights, which has to come before the
-// next of these calls, adds up itself.
+// A weight gradient into dW, its rows split as wgrad_ksplit says, through c->wg_part.  leave: the splits, which the update of these weights, which has to
+// come before the next of these calls, adds up itself.
 template <typename T>
-void wgrad_call(gan_ctx* c, const char* name, const void* Big, const void* Small, float* dW, long long stride, int Cb, int Cs,
-                int Hs, int ntaps, int nseg, int n, double flops_alg = -1.0, int ksplit = 0, hipStream_t st = nullptr,
-                AdamSplits* leave = nullptr) {
+void wgrad_call(gan_ctx* c, const void* Big, const void* Small, float* dW, long long stride, int Cb, int Cs, int Hs, int ntaps, int nseg, int n,
+                hipStream_t st = nullptr, AdamSplits* leave = nullptr) {
   if (!st) st = c->st;
   WgradArgs a = {};
   a.Big = Big; a.Small = Small; a.dW = dW; a.offs = c->rb.offs; a.order = c->rb.order; a.dw_stride = stride;
-  a.L = c->L; a.nseg = nseg; a.seg_samples = n; a.Cb = Cb; a.Cs = Cs; a.Hs = Hs; a.ntaps = ntaps; a.ksplit = ksplit;
-  a.split_stride = (long long)c->L * stride;
+  a.L = c->L; a.nseg = nseg; a.seg_samples = n; a.Cb = Cb; a.Cs = Cs; a.Hs = Hs; a.ntaps = ntaps;
   const long long layer = (long long)ntaps * Cb * Cs;
-  const int auto_split = ksplit == 0 ? wgrad_ksplit(c, Cb, Cs, ntaps, Hs, nseg) : 0;
-  if (ksplit == 0) {
-    a.ksplit = auto_split;
-    if (auto_split > 1) {
-      a.dW = c->wg_part; a.dw_stride = layer; a.split_stride = (long long)c->L * layer;
-    }
+  const int ksplit = a.ksplit = wgrad_ksplit(c, Cb, Cs, ntaps, Hs, nseg);
+  if (ksplit > 1) {
+    a.dW = c->wg_part; a.dw_stride = layer; a.split_stride = (long long)c->L * layer;
   }
   const double rows = (double)n * nseg * Hs * Hs;
   const double frac = ntaps == 1 ? 1.0 : valid_tap_fraction(Hs);
@@ -709,13 +705,12 @@ void wgrad_call(gan_ctx* c, const char* name, const void* Big, const void* Small
   const double bytes = sizeof(T) * (big_elems + rows * Cs) + 4.0 * c->L * ntaps * Cb * Cs;
   char detail[64];
   snprintf(detail, sizeof(detail), "[Cb%d Cs%d H%d seg%d]", Cb, Cs, Hs, nseg);
-  (void)name;
   {
-    Scope s(c, wgrad_variant_name((int)sizeof(T), a), flops_alg >= 0 ? flops_alg : 2.0 * rows * Cb * Cs * ntaps * frac, bytes, detail, st);
+    Scope s(c, wgrad_variant_name((int)sizeof(T), a), 2.0 * rows * Cb * Cs * ntaps * frac, bytes, detail, st);
     launch_wgrad<T>(a, st);
   }
-  if (leave) *leave = {c->wg_part, auto_split, split_chains(layer * c->L, auto_split)};
-  else if (auto_split > 1) launch_sum_splits(c->wg_part, dW, stride, layer, c->L, auto_split, st);
+  if (leave) *leave = {c->wg_part, ksplit, split_chains(layer * c->L, ksplit)};
+  else if (ksplit > 1) launch_sum_splits(c->wg_part, dW, stride, layer, c->L, ksplit, st);
 }
 
 template <typename T>
@@ -885,7 +880,7 @@ void g_forward(gan_ctx* c, int n, bool use_running, bool update_running, float* 
   const NormArgs a0 = norm_args<T>(c, G, G.C0, G.h0 * G.h0, G.fc_gamma, G.fc_beta, G.fc_rs, c->g_mean[0], c->g_var[0], c->g_rstd[0],
                                    c->g_sums[0], 0, 1, n, relu);
   conv_call<T>(c, "gemm_dense", MODE_DENSE, use_running ? EPI_BN : EPI_NONE, c->zin, Weights{(const T*)G.shadow_u + G.fc_w, G.P},
-               use_running ? c->gact[0] : c->gpre[0], nullptr, G.Kp, G.J, 1, 1, 0, 1, n, 0, -1.0, !use_running, &a0);
+               use_running ? c->gact[0] : c->gpre[0], nullptr, G.Kp, G.J, 1, 1, 0, 1, n, !use_running, &a0);
   if (!use_running) bn_forward<T>(c, a0, c->gpre[0], c->gact[0], update_running, MODE_DENSE, 1, G.h0 * G.h0);
   const int nl = (int)G.conv.size();
   for (int i = 0; i + 1 < nl; ++i) {
@@ -893,7 +888,7 @@ void g_forward(gan_ctx* c, int n, bool use_running, bool update_running, float* 
     const NormArgs a = norm_args<T>(c, G, cl.Cb, 4 * cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->g_mean[i + 1], c->g_var[i + 1],
                                     c->g_rstd[i + 1], c->g_sums[i + 1], 0, 1, n, relu);
     conv_call<T>(c, "gemm_up", MODE_UP, use_running ? EPI_BN : EPI_NONE, c->gact[i], layer_weights(c, G, cl, true),
-                 use_running ? c->gact[i + 1] : c->gpre[i + 1], nullptr, cl.Cs, cl.Cb, cl.Hs, cl.Hs, 0, 1, n, 0, -1.0, !use_running, &a);
+                 use_running ? c->gact[i + 1] : c->gpre[i + 1], nullptr, cl.Cs, cl.Cb, cl.Hs, cl.Hs, 0, 1, n, !use_running, &a);
     if (!use_running) bn_forward<T>(c, a, c->gpre[i + 1], c->gact[i + 1], update_running, MODE_UP, cl.Hs * cl.Hs);
   }
   // last transposed conv (+bias, tanh) straight into the fake half of D's image buffer
@@ -914,7 +909,7 @@ void d_forward(gan_ctx* c, int n, Cost cost, bool update_running, const float* r
   for (int j = 1; j < nl; ++j) {
     const ConvLayer& cl = D.conv[j];
     conv_call<T>(c, "gemm_down", MODE_DOWN, EPI_NONE, c->dact[j - 1], layer_weights(c, D, cl, false), c->dpre[j], nullptr, cl.Cb,
-                 cl.Cs, 2 * cl.Hs, cl.Hs, seg_first, nseg, n, 0, -1.0, true);
+                 cl.Cs, 2 * cl.Hs, cl.Hs, seg_first, nseg, n, true);
     bn_forward<T>(c, norm_args<T>(c, D, cl.Cs, cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->d_mean[j], c->d_var[j], c->d_rstd[j],
                                   c->d_sums[j], seg_first, nseg, n, slope),
                   c->dpre[j], c->dact[j], update_running, MODE_DOWN, cl.Hs * cl.Hs, 1, j == nl - 1 ? &head : nullptr);
@@ -951,7 +946,7 @@ void d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_image, c
       // is done; being bandwidth-bound it pairs with the data-gradient GEMM below), then this layer's weight gradient.
       order_after(c, side, c->st);
       if (adam && pending >= 0) adam_region_call<T>(c, *adam, pending, side, splits);
-      wgrad_call<T>(c, "gemm_wgrad", c->dact[j - 1], dx, D.g + cl.w, D.P, cl.Cb, cl.Cs, cl.Hs, 16, nseg, n, -1.0, 0, side, adam ? &splits : nullptr);
+      wgrad_call<T>(c, c->dact[j - 1], dx, D.g + cl.w, D.P, cl.Cb, cl.Cs, cl.Hs, 16, nseg, n, side, adam ? &splits : nullptr);
       pending = j - 1;
     }
     // data gradient; for the first conv's output the LeakyReLU derivative is applied in the epilogue
@@ -992,7 +987,7 @@ void g_backward(gan_ctx* c, int n, const AdamArgs* adam = nullptr, AdamTail* tai
                    c->gpre[i + 1], c->bufA, dx, true);
     order_after(c, side, c->st);
     if (adam && pending >= 0) adam_region_call<T>(c, *adam, pending, side, splits);      // as in D
-    wgrad_call<T>(c, "gemm_wgrad", dx, c->gact[i], G.g + cl.w, G.P, cl.Cb, cl.Cs, cl.Hs, 16, 1, n, -1.0, 0, side, adam ? &splits : nullptr);
+    wgrad_call<T>(c, dx, c->gact[i], G.g + cl.w, G.P, cl.Cb, cl.Cs, cl.Hs, 16, 1, n, side, adam ? &splits : nullptr);
     pending = i;
     conv_call<T>(c, "gemm_down", MODE_DOWN, EPI_NONE, dx, layer_weights(c, G, cl, false), c->bufA, nullptr, cl.Cb, cl.Cs,
                  2 * cl.Hs, cl.Hs, 0, 1, n);
@@ -1006,7 +1001,7 @@ void g_backward(gan_ctx* c, int n, const AdamArgs* adam = nullptr, AdamTail* tai
     if (side == c->st && adam_region_joins_rest(*adam, pending) && (splits.n < 2 || wgrad_ksplit(c, G.J, G.Kp, 1, 1, 1) == 1)) *tail = {pending, splits};
     else adam_region_call<T>(c, *adam, pending, side, splits);
   }
-  wgrad_call<T>(c, "gemm_wgrad_dense", c->gpre[0], c->zin, G.g + G.fc_w, G.P, G.J, G.Kp, 1, 1, 1, n, -1.0, 0, side);
+  wgrad_call<T>(c, c->gpre[0], c->zin, G.g + G.fc_w, G.P, G.J, G.Kp, 1, 1, 1, n, side);
   order_after(c, c->st, side);
 }
 
@@ -1057,7 +1052,7 @@ void paper_g_forward(gan_ctx* c, int n, bool use_running, bool update_running, f
                              c->g_sums[0], 0, 1, n, 1.f);
   a0.eps = f.bn_eps_first;
   conv_call<T>(c, "gemm_dense", MODE_DENSE, use_running ? EPI_BN : EPI_BIAS_ACT, c->zin, Weights{(const T*)G.shadow_u + G.fc_w, G.P},
-               use_running ? c->gact[0] : c->gpre[0], nullptr, G.Kp, G.J, 1, 1, 0, 1, n, 0, -1.0, false, &a0, G.theta + G.fc_bias);   // + bias, ReLU
+               use_running ? c->gact[0] : c->gpre[0], nullptr, G.Kp, G.J, 1, 1, 0, 1, n, false, &a0, G.theta + G.fc_bias);   // + bias, ReLU
   if (!use_running) bn_forward_direct<T>(c, a0, a0.C, c->gpre[0], c->gact[0], f.bn_eps_first, update_running);
   const int nl = (int)G.conv.size();
   for (int i = 0; i + 1 < nl; ++i) {                   // Upsample x2 + Conv k3 as a k4 s2 p1 transposed convolution
@@ -1065,7 +1060,7 @@ void paper_g_forward(gan_ctx* c, int n, bool use_running, bool update_running, f
     const NormArgs a = norm_args<T>(c, G, cl.Cb, 4 * cl.Hs * cl.Hs, cl.gamma, cl.beta, cl.rs, c->g_mean[i + 1], c->g_var[i + 1],
                                     c->g_rstd[i + 1], c->g_sums[i + 1], 0, 1, n, f.leaky_slope);
     conv_call<T>(c, "gemm_up", MODE_UP, use_running ? EPI_BN : EPI_NONE, c->gact[i], layer_weights(c, G, cl, true),
-                 use_running ? c->gact[i + 1] : c->gpre[i + 1], nullptr, cl.Cs, cl.Cb, cl.Hs, cl.Hs, 0, 1, n, 0, -1.0, !use_running, &a);
+                 use_running ? c->gact[i + 1] : c->gpre[i + 1], nullptr, cl.Cs, cl.Cb, cl.Hs, cl.Hs, 0, 1, n, !use_running, &a);
     // (the last block's BatchNorm and activation are part of the kernels that read its output)
     if (!use_running) bn_forward<T>(c, a, c->gpre[i + 1], i + 2 < nl ? c->gact[i + 1] : nullptr, update_running, MODE_UP, cl.Hs * cl.Hs);
   }
@@ -1131,7 +1126,7 @@ void paper_d_backward(gan_ctx* c, int n, Cost cost, bool param_grads, bool to_im
     if (param_grads) {
       const PointArgs a = point_args(c, c->bufB, cl.cs_real, cl.Cs, cl.Hs * cl.Hs, seg_first, nseg, n);
       launch_col_sum<T>(a, D.g + cl.bias, D.P, c->st);
-      wgrad_call<T>(c, "gemm_wgrad", c->dact[j - 1], c->bufB, D.g + cl.w, D.P, cl.Cb, cl.Cs, cl.Hs, 16, nseg, n);
+      wgrad_call<T>(c, c->dact[j - 1], c->bufB, D.g + cl.w, D.P, cl.Cb, cl.Cs, cl.Hs, 16, nseg, n);
     }
     const int first = f.dropout_p > 0.f ? EPI_DROP_BWD : EPI_ACT_BWD;         // the first block's LeakyReLU and dropout
     conv_call<T>(c, "gemm_up", MODE_UP, j == 1 ? first : EPI_NONE, c->bufB, layer_weights(c, D, cl, true), c->bufA,
@@ -1186,7 +1181,7 @@ void paper_g_backward(gan_ctx* c, int n) {
                                c->g_rstd[i + 1], c->g_sums[i + 1], 0, 1, n, f.leaky_slope);
     if (i < nl - 2) bn_backward<T>(c, na, c->gpre[i + 1], c->bufA, c->bufB, true);
     const long long per = (long long)16 * cl.Cb * cl.Cs;
-    wgrad_call<T>(c, "gemm_wgrad", c->bufB, c->gact[i], c->dw4, per, cl.Cb, cl.Cs, cl.Hs, 16, 1, n);
+    wgrad_call<T>(c, c->bufB, c->gact[i], c->dw4, per, cl.Cb, cl.Cs, cl.Hs, 16, 1, n);
     launch_dw4_to_dw3(c->dw4, G.g + cl.w, c->L, cl.Cb, cl.Cs, c->st, per, G.P);
     conv_call<T>(c, "gemm_down", MODE_DOWN, EPI_NONE, c->bufB, layer_weights(c, G, cl, false), c->bufA, nullptr, cl.Cb, cl.Cs,
                  2 * cl.Hs, cl.Hs, 0, 1, n);
@@ -1198,7 +1193,7 @@ void paper_g_backward(gan_ctx* c, int n) {
   bn_backward<T>(c, na, c->gpre[0], c->bufA, c->bufB, true);
   const PointArgs a = point_args(c, c->bufB, G.J, G.J, 1, 0, 1, n);
   launch_col_sum<T>(a, G.g + G.fc_bias, G.P, c->st);
-  wgrad_call<T>(c, "gemm_wgrad_dense", c->bufB, c->zin, G.g + G.fc_w, G.P, G.J, G.Kp, 1, 1, 1, n);
+  wgrad_call<T>(c, c->bufB, c->zin, G.g + G.fc_w, G.P, G.J, G.Kp, 1, 1, 1, n);
 }
 
 template <typename T>
@@ -1529,9 +1524,9 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
     if (c->head_rsplit > 1) ok = ok && dev_alloc(c, (void**)&c->head_part, (size_t)c->head_rsplit * L * (c->D.K + 4) * 4);
   }
   {
-    // the GEMM loaders address one segment of any activation tensor with 32-bit byte offsets.  The image-side layers count with 16 columns an
-    // image channel and 9 a label of one pair, in lines of 64: which batches a configuration takes follows from its shapes alone, not from
-    // the way those layers are computed.
+    // the GEMM loaders address one segment of any activation tensor with 32-bit byte offsets.  Beside those, a bound that no tensor asks for: the image-side
+    // layers count with 16 columns an image channel and 9 a label of one pair, in lines of 64, as when they were patch matrices.  A configuration
+    // takes the batches that it took then.
     const ConvLayer& c1 = c->D.conv[0];
     const ConvLayer& gl = c->G.conv.back();
     const long long lim = 1LL << 31, slots = cfg->cond_d > 0 && L == 1 ? cfg->cond_d : 1;

@@ -1766,7 +1766,7 @@ static void launch_wgrad_one(WgradArgs a, hipStream_t st) {
 
 // Which tile a layer's weight gradient uses, as f(tile, name)
 template <typename T, typename F>
-static void with_wgrad_tile(int ntaps, int Cb, int Cs, F&& f) {
+static void with_wgrad_tile(int Cs, F&& f) {
   if constexpr (sizeof(T) == 4) {
     if (Cs <= 64) f(TileWgF32N(), "wgrad<128x64>"); else f(TileWgF32(), "wgrad<128x128>");
   } else {
@@ -1781,18 +1781,18 @@ void launch_wgrad(const WgradArgs& a, hipStream_t st) {
   if (!a.Big || !a.Small || !a.dW || !a.offs || a.Cb % 8 || a.Cs % 8 || (a.ntaps != 1 && a.ntaps != 16) || a.ksplit < 1 ||
       (a.ksplit > 1 && a.split_stride <= 0))
     return launch_fail("weight gradient: null operand, channel counts that are not multiples of 8, or a bad row split");
-  with_wgrad_tile<T>(a.ntaps, a.Cb, a.Cs, [&](auto tile, const char*) { launch_wgrad_one<T, decltype(tile)>(a, st); });
+  with_wgrad_tile<T>(a.Cs, [&](auto tile, const char*) { launch_wgrad_one<T, decltype(tile)>(a, st); });
 }
 int wgrad_tiles_per_model(int esize, int ntaps, int Cb, int Cs) {
   int tiles = 0;
   const auto count = [&](auto tile, const char*) { tiles = (ntaps * Cb + tile.BM - 1) / tile.BM * ((Cs + tile.BN - 1) / tile.BN); };
-  if (esize == 4) with_wgrad_tile<float>(ntaps, Cb, Cs, count); else with_wgrad_tile<bf16_t>(ntaps, Cb, Cs, count);
+  if (esize == 4) with_wgrad_tile<float>(Cs, count); else with_wgrad_tile<bf16_t>(Cs, count);
   return tiles;
 }
 const char* wgrad_variant_name(int esize, const WgradArgs& a) {
   const char* name = "";
   const auto take = [&](auto, const char* n) { name = n; };
-  if (esize == 4) with_wgrad_tile<float>(a.ntaps, a.Cb, a.Cs, take); else with_wgrad_tile<bf16_t>(a.ntaps, a.Cb, a.Cs, take);
+  if (esize == 4) with_wgrad_tile<float>(a.Cs, take); else with_wgrad_tile<bf16_t>(a.Cs, take);
   return name;
 }
 template void launch_wgrad<float>(const WgradArgs&, hipStream_t);
