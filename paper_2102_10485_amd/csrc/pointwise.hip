@@ -1223,13 +1223,14 @@ __device__ inline void adam_tile(const AdamArgs& a, const AdamSplits& sp, unsign
     if (ch + 8 > cb_real || cs >= cs_real) {                    // padding, or the last real channels one by one
       for (int k = 0; k < 8 && ch + k < cb_real && cs < cs_real; ++k) {
         const T v = *reinterpret_cast<const T*>(tile + cs * TSTRIDE + (ch + k) * (int)sizeof(T));
-        if constexpr (sizeof(T) == 2) static_cast<T*>(a.shadow_t)[base + o + k] = v;
-        else if (a.split_u) {
+        if constexpr (sizeof(T) == 2) {
+          static_cast<T*>(a.shadow_t)[base + o + k] = v;
+        } else {                                                // (fp32 weights with padding are held split: adam_plan)
           unsigned h, m, l_;
           split_pair(v, 0.f, h, m, l_);
           unsigned short* const d = a.split_d + part + o + k;
           d[0] = (unsigned short)h; d[a.plane] = (unsigned short)m; d[2 * a.plane] = (unsigned short)l_;
-        } else static_cast<T*>(a.shadow_t)[(long long)l * a.plane + a.reg_part[r] + o + k] = v;
+        }
       }
       continue;
     }
@@ -1293,6 +1294,10 @@ bool adam_plan(AdamArgs& a) {
     if (r < a.nregions) {
       if (a.reg_cb[r] % 64 || a.reg_cs[r] % 64 || a.reg_cb_real[r] > a.reg_cb[r] || a.reg_cs_real[r] > a.reg_cs[r] || (a.split_u ? !a.split_d : !a.shadow_t) || a.plane % 8) {
         launch_fail("Adam: tiled regions need channel counts that are multiples of 64");
+        return false;
+      }
+      if (!a.shadow && !a.split_u && (a.reg_cb_real[r] < a.reg_cb[r] || a.reg_cs_real[r] < a.reg_cs[r])) {
+        launch_fail("Adam: padded fp32 weights without split copies");
         return false;
       }
       a.reg_tile0[r + 1] = a.reg_tile0[r] + 16 * (a.reg_cb[r] / 64) * (a.reg_cs[r] / 64);

@@ -188,6 +188,43 @@ def test_paper_channels_that_do_not_divide_the_threads(prec, monkeypatch):
     p.close()
 
 
+ODD = dict(family="paper", cond_g=0, cond_d=0, z_dim=16, img_c=3, img_hw=16, g_h0=4, g_ch=[64, 64, 64], d_ch=[18, 21, 70])
+
+
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+def test_channels_that_end_inside_a_group(prec, monkeypatch):
+    """18, 21 and 70 channels: the last real channels of D's filters end inside the update's groups of four and of eight, whose transposed copies it writes one by one.
+    Against the oracle (the cost of G's step and its gradients read the copies that D's update has written)."""
+    monkeypatch.setitem(synth.SPECS, "paper_odd", ODD)
+    p = PaperPair("paper_odd", 2, 24, prec)
+    for s, n in enumerate([19, 24]):
+        p.step(*batch(p.spec, np.arange(n) % 2, 640 + s))
+        p.compare("step %d" % s)
+    p.close()
+
+
+@pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
+def test_copies_of_channels_that_end_inside_a_group(prec):
+    """The same networks: three steps on the copies that the update leaves, and three with every copy made anew from the parameters in between, are equal bit for bit."""
+    torch = U.torch_mod()
+    st = torch.cuda.current_stream().cuda_stream
+    plain, again = (binding.Gan(binding.make_config(ODD, 2, 2, 24, prec, seed=4), st) for _ in range(2))
+    for s in range(3):
+        lab, z, x = batch(ODD, np.arange(24) % 2, 650 + s)
+        d = [torch.from_numpy(a).cuda() for a in (lab, z, x)]
+        for g in (plain, again):
+            g.train_step(*(t.data_ptr() for t in d), 24)
+        torch.cuda.synchronize()
+        for l in range(2):
+            for w in (0, 1):
+                for a, b in zip((plain.get_params(w, l), *plain.get_opt_state(w, l)[:2], plain.get_grads(w, l)),
+                                (again.get_params(w, l), *again.get_opt_state(w, l)[:2], again.get_grads(w, l))):
+                    assert np.array_equal(a, b), (s, w, l)
+                again.set_params(w, l, again.get_params(w, l))
+    plain.close()
+    again.close()
+
+
 @pytest.mark.parametrize("prec", [binding.FP32, binding.BF16])
 def test_zero_activations_behind_dropout(prec):
     """The backward pass reads the dropout mask off the stored activations, where a kept zero is not a dropped one: channels of
