@@ -1491,10 +1491,11 @@ gan_status gan_create(const gan_config* cfg, void* hip_stream, gan_ctx** out) {
       c->labels = cfg->cond_d;
       ok = ok && dev_alloc(c, (void**)&c->label_sums, (size_t)c->labels * 9 * c1.Cs * 4) && dev_alloc(c, (void**)&c->class_part, (size_t)2 * NB * 9 * c1.Cs * 4);
     }
-    const size_t d1 = (size_t)16 * image_values(c1.Cb) * c1.Cs, g1 = c->paper ? 0 : (size_t)16 * image_values(gl.Cb) * gl.Cs, part = 16 * image_values(c1.Cb) * 128, tiles = image_tile_bound(c->img_tiles, NB, L);
+    const size_t d1 = (size_t)16 * image_values(c1.Cb) * c1.Cs, g1 = c->paper ? 0 : (size_t)16 * image_values(gl.Cb) * gl.Cs, tiles = image_tile_bound(c->img_tiles, NB, L),
+                 part = std::max(image_part_floats((int)es, c1.Cb, c1.Hs, c1.Cs, 2, c->img_tiles, tiles), c->paper ? 0 : image_part_floats((int)es, gl.Cb, gl.Hs, gl.Cs, 1, c->img_tiles, tiles));
     ok = ok && dev_alloc(c, &c->wpD, (size_t)L * d1 * es) && dev_alloc(c, &c->wpG, (size_t)L * g1 * es) &&
          dev_alloc(c, (void**)&c->addD, (size_t)(c->labels > 0 ? c->labels : L) * 9 * c1.Cs * 4) &&
-         dev_alloc(c, (void**)&c->img_part, tiles * part * 4) && dev_alloc(c, (void**)&c->img_sums, tiles * 4 * 4) &&
+         dev_alloc(c, (void**)&c->img_part, part * 4) && dev_alloc(c, (void**)&c->img_sums, tiles * 4 * 4) &&
          dev_alloc(c, (void**)&c->bias_partial, c->paper ? (size_t)L * img_bias_chunks(L) * 4 * 4 : 0);
   }
   {
@@ -2144,7 +2145,7 @@ gan_status gan_op_image_wgrad(gan_ctx* c, const void* img, const float* nchw, co
   const int tiles = (int)tmodel.size();
   ImageWgradArgs a = {};
   a.img = img ? img : nchw; a.real = nchw; a.perm = perm; a.dy = small_in; a.offs = offs;
-  a.part = (float*)op.hold((size_t)(128 / cs) * tiles * 16 * P * cs * 4); a.pixel_sums = (float*)op.hold((size_t)tiles * 4 * 4);
+  a.part = (float*)op.hold((size_t)image_part_floats((int)esize(c), cb, hs, cs, c->op_segments, tiling, tiles) * 4); a.pixel_sums = (float*)op.hold((size_t)tiles * 4 * 4);
   a.tpre = op.hold(tpre); a.tmodel = op.hold(tmodel);
   if (!a.part || !a.pixel_sums || !a.tpre || !a.tmodel) return fail(c, GAN_E_OOM, "image-side partial sums alloc");
   a.L = n_groups; a.CB = cb; a.Hs = hs; a.Cs = cs; a.nseg = c->op_segments; a.seg_samples = n_samples; a.tiles = tiling;

@@ -714,6 +714,13 @@ template <typename F> bool with_channels(int CB, int Cs, F&& f) {
 }  // namespace
 
 int image_values(int CB) { return img_values(CB); }
+long long image_part_floats(int esize, int CB, int Hs, int Cs, int nseg, const ImageTiles& t, long long tiles) {
+  const Units u = img_units(Hs, CB, WG_SIDE_Y);
+  const int turns = 128 / Cs;
+  // (two waves that share 32 channels: the second one's chains go to lines of their own, where a tile has more than one)
+  const bool chains = (long long)t.most * nseg * u.nx * u.ny * (((u.ph * u.pw + 15) / 16 + turns - 1) / turns) > wg_chain(esize);
+  return tiles * 16 * img_values(CB) * Cs * (chains ? turns : 1);
+}
 
 template <typename T> void launch_image_conv(const ImageConvArgs& a, hipStream_t st) {
   if (a.n == 0 || a.nseg == 0) return;

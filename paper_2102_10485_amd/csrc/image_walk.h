@@ -40,8 +40,9 @@ inline ImageTiles image_tiles(int esize, long long size_samples, int L) {
   return ImageTiles{most < 1 ? 1 : (int)most, parts < 1 ? 1 : (int)parts};
 }
 GAN_HOST_DEVICE_INLINE int image_tile(const ImageTiles& t, int samples) {
+  if (samples <= t.parts) return 1;           // (small calls wait for no division)
   const int per = (samples + t.parts - 1) / t.parts;
-  return per < 1 ? 1 : (per < t.most ? per : t.most);
+  return per < t.most ? per : t.most;
 }
 // no more tiles than this of n samples, however they fall: a model has `parts`, or one more than whole ones of `most`
 inline long long image_tile_bound(const ImageTiles& t, long long n, int L) {

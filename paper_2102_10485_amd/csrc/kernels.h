@@ -141,7 +141,7 @@ struct ImageWgradArgs {
   const float* real;
   const int* perm;
   const void* dy;           // [rows][Cs], rows indexed by absolute sample
-  float* part;              // [tiles][16 P][Cs], partial sums of every tile (Cs = 64: and as much again behind the launch's tiles, scratch)
+  float* part;              // [tiles][16 P][Cs], partial sums of every tile, and scratch behind the launch's tiles: image_part_floats
   float* pixel_sums;        // [tiles][4]: the sums of the image's pixels, or NULL
   const int* offs;
   const int* tpre;          // the prefix array and models of the tiles (tmodel NULL: one model)
@@ -149,6 +149,8 @@ struct ImageWgradArgs {
   int L, CB, Hs, Cs, seg_first, nseg, seg_samples;
   ImageTiles tiles;
 };
+// floats of `part` for up to `tiles` tiles of up to nseg segments
+long long image_part_floats(int esize, int CB, int Hs, int Cs, int nseg, const ImageTiles& t, long long tiles);
 template <typename T> void launch_image_wgrad(const ImageWgradArgs& a, int ub_tiles, hipStream_t st);
 // The row splits of the linear head's weight gradient (HeadArgs, rsplit > 1), which another kernel of D's backward pass adds up along the way
 struct HeadSplits {

@@ -93,7 +93,8 @@ __global__ __launch_bounds__(ROUTE_THREADS) void route_kernel(const int* __restr
       int v;
       if (parts > 0) {
         const int own = l0 + lane < L ? cl[l0 + lane] : 0, per = image_tile(ImageTiles{tr, parts}, own);
-        v = (own + per - 1) / per;
+        v = own;
+        if (per > 1) v = (own + per - 1) / per;
       } else {
         v = sh >= 0 ? c >> sh : c / tr;
       }
