@@ -15,9 +15,9 @@
 //
 // What it replaced: patch matrices in memory, written by one kernel and read as the operand of a row-by-row GEMM and weight gradient.  us, before
 // -> now.  A hundred 32x32 pairs of 64 samples, 128 channels, bf16: both segments 388 -> 217 (now 4.4 TB/s of the 0.96 GB that have to move; 179
-// without the image's loads, 107 without the stores), one 129 -> 112, their weight gradients 320 -> 259 and 243 -> 113, which now includes the bias;
-// eight 64x64 pairs, 64 channels, 191 -> 88, 51 -> 40, 112 -> 80, 122 -> 48; twenty 32x32 pairs in fp32 184 -> 108, 68 -> 55, 144 -> 127, 105 -> 73; ten
-// 28x28 pairs in fp32 93 -> 45, 31 -> 25, 69 -> 57, 62 -> 33.  Whole steps: +10 % (ten 28x28 pairs, bf16) to +2 % (twenty 32x32 pairs, fp32).
+// without the image's loads, 107 without the stores), one 129 -> 112, their weight gradients 320 -> 258 and 243 -> 106, which now includes the bias;
+// eight 64x64 pairs, 64 channels, 191 -> 88, 51 -> 40, 112 -> 79, 122 -> 44; twenty 32x32 pairs in fp32 184 -> 108, 68 -> 55, 144 -> 133, 105 -> 74; ten
+// 28x28 pairs in fp32 93 -> 45, 31 -> 25, 69 -> 51, 62 -> 29.  Whole steps: +10 % (ten 28x28 pairs, bf16) to +2 % (twenty 32x32 pairs, fp32).
 #include <algorithm>
 
 #include "image_walk.h"
