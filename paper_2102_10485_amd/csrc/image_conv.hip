@@ -97,7 +97,8 @@ struct Stager {
       return __uint_as_float(nchw ? v[K][C][P] : v[K][e / 2][e % 2]);
     }
   }
-  __device__ __forceinline__ void put(unsigned char* tile, int plane, const Units& u, int tid, int nt, float (*own)[CB]) const {
+  __device__ __forceinline__ void put(unsigned char* tile, int plane, const Units& u, int tid, int nt, double (*own)[CB]) const {
+    float sum[CB] = {};                                        // of the unit
     constexpr int PB = 2 * img_values(CB);
     pairs(u, tid, nt, [&](auto k, int ty, int pr, bool there) __attribute__((always_inline)) {
       unsigned char* const at = tile + ty * u.pitch + (2 * pr + 1) * PB;
@@ -111,9 +112,10 @@ struct Stager {
       if (there && pr < u.pw) put_pixel<T, CB>(at + PB, plane, b, inside);
       if (own) {
         const bool mine = there && ty > 0 && ty <= 2 * u.ph && pr >= 0 && pr < u.pw;
-        static_for<0, CB>([&](auto c) __attribute__((always_inline)) { (*own)[c.value] += mine ? a[c.value] + b[c.value] : 0.f; });
+        static_for<0, CB>([&](auto c) __attribute__((always_inline)) { sum[c.value] += mine ? a[c.value] + b[c.value] : 0.f; });
       }
     });
+    if (own) static_for<0, CB>([&](auto c) __attribute__((always_inline)) { (*own)[c.value] += (double)sum[c.value]; });
   }
 };
 // pairs of the largest unit
@@ -328,9 +330,7 @@ __global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? (EVEN ?
   const int trows = 2 * u.ph + 2, plane = (trows + ZERO_ROWS) * u.pitch, buf = PL * plane;
   unsigned char* const tiles = lds + 4 * RING_BYTES;                   // two
   const UnitAt first = {a.seg_first, j0, 0, 0};
-  float own[CB];
-#pragma unroll
-  for (int c = 0; c < CB; ++c) own[c] = 0.f;
+  double own[CB] = {};                                                   // (in fp32 a tile's pixels are chains of hundreds)
   Stager<T, CB, (unit_pairs(WG_SIDE_Y) + 63) / 64> image;
   UnitAt ahead = first;
   int place = a.real ? a.perm[j0] : 0;                                   // of the sample `ahead`, known a unit before it is needed
@@ -573,10 +573,10 @@ __global__ __launch_bounds__(WG_THREADS, (CB == 4 ? 1 : sizeof(T) == 2 ? (EVEN ?
   if (wave == 4 && a.pixel_sums) {
 #pragma unroll
     for (int c = 0; c < CB; ++c) {
-      float s = own[c];
+      double s = own[c];
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-      if (lane == 0) a.pixel_sums[tile * 4 + c] = s;
+      if (lane == 0) a.pixel_sums[tile * 4 + c] = (float)s;
     }
   }
 }

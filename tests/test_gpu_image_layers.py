@@ -107,7 +107,7 @@ class Layer:
             out[:, a:b] = (p @ w.T + self.bias[l]).reshape(self.S, b - a, hs, hs, self.cs).transpose(0, 1, 4, 2, 3)
             d = self.dy[:, a:b].transpose(0, 1, 3, 4, 2).reshape(-1, self.cs).astype(np.float64)
             dw[l] = (d.T @ p).reshape(self.cs, self.cb + self.maps, 16)
-            db[l], px[l] = d.sum(0), self.images[:, a:b].sum(axis=(0, 1, 3, 4))
+            db[l], px[l] = d.sum(0), self.images[:, a:b].sum(axis=(0, 1, 3, 4), dtype=np.float64)
         return out, dw, db, px
 
     def own_maps(self, dw):
@@ -161,9 +161,12 @@ def test_long_tiles_are_added_in_chains(ctxs, prec, chain, hs, cs):
     per = 80
     n, hb = per, 128 // cs
     x = layer(ctxs[prec], bf, [n], 3, cs, hs, 2, False, 0, np.random.default_rng([hs, cs]), False)
-    got, want = x.run(per * (700 if bf else 480), 700)[1], x.reference()[1]
+    (_, got, _, px), (_, want, _, px_want) = x.run(per * (700 if bf else 480), 700), x.reference()
     parts = -(-2 * n * -(-hs * hs // 16) // hb // chain) * hb
     assert U.rel_l2(got, want) <= 2.0 ** -24 * np.sqrt((chain + parts) / 2)
+    # The sums of a channel's N pixels of variance 1: a lane adds twelve pixels of a unit at most in fp32 (an addition to k of them errs by 2^-24 sqrt(k / 3), root mean
+    # square: twelve by 2^-24 sqrt(24), N of them by 2^-24 sqrt(2 N)), the units in double, and the result is rounded twice (2^-24 sqrt(N / 3) each).  Four times that.
+    assert np.max(np.abs(px - px_want)) <= 4 * 2.0 ** -24 * np.sqrt((2 + 2 / 3) * x.images[:, :, 0].size)
 
 
 @pytest.mark.parametrize("hs", [4, 8, 16])
