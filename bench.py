@@ -21,20 +21,20 @@ PEAK = {"mfma_bf16": 2500.0, "mfma_fp32": 2500.0 / 6, "hbm": 8000.0}
 # the same counters read for the 1 GiB elementwise probe (fetch x 2.0, write x 1.0).  Valid only for the kernel sources they
 # were taken with: `sources` is the digest of csrc/ at that time, and the roofline reports null traffic when it differs.
 MEASURED_TRAFFIC = {
-    "sources": "c788d9c29b443571",
+    "sources": "c217f3f3ce028bfb",
     "workload": "config 2 bf16",
     "fetch_scale": 2.000, "write_scale": 1.000,
     "kib_per_launch": {
-        "gemm_dense<64x64>": (103273, 123112),
-        "gemm_up<256x256>": (457586, 275230),
-        "gemm_up<256x128>": (159233, 435200),
-        "gemm_down<256x256>": (502456, 209601),
-        "wgrad<256x256>": (476039, 512079),
-        "gemm_up+actbwd<256x128>": (596350, 614400),
-        "wgrad<256x128>": (52088, 410010),
-        "up_img": (242957, 46823),
-        "image_conv": (42924, 546133),
-        "image_wgrad": (352386, 35511),
+        "gemm_dense<64x64>": (103273, 122668),
+        "gemm_up<256x256>": (459860, 275201),
+        "gemm_up<256x128>": (159193, 435200),
+        "gemm_down<256x256>": (503846, 209600),
+        "wgrad<256x256>": (478691, 512079),
+        "gemm_up+actbwd<256x128>": (596221, 614400),
+        "wgrad<256x128>": (52088, 409978),
+        "up_img": (242794, 46832),
+        "image_conv": (42919, 546133),
+        "image_wgrad": (352371, 35511),
     },
 }
 
